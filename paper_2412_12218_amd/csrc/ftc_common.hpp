@@ -115,6 +115,13 @@ int32_t launch_permute_graph(const ftc_csr &g, const int *perm, const int *inv, 
                              int *flag, void *ws, hipStream_t s);
 int32_t launch_permute_rows(int n, const void *X, int ldx, int dt, int D, const int *map, void *out, int ldo,
                             hipStream_t s);
+// reorder_rows.hip: rows sorted one by one, for graphs of at most ROW_SORT_NODES nodes (a row above 8192 entries takes a
+// pass of LDS counters per 32 768 nodes, 128 of them here); larger graphs sort all entries by column and row instead
+constexpr int ROW_SORT_NODES = 1 << 22;
+size_t row_sort_ws(int n, int nnz);
+int32_t launch_relabel_rows(const ftc_csr &g, const int *perm, const int *inv, const int *rp, int *col_idx_out, int *flag,
+                            void *ws, hipStream_t s);
+int32_t launch_label_rounds(const ftc_csr &g, int iters, int *labels, void *ws, hipStream_t s);
 size_t build_windows_ws(int n, int nnz, int blk_h, int blk_w);
 int32_t launch_build_windows(const ftc_csr &g, ftc_windows &w, void *ws, size_t ws_bytes, const ftc_side_streams *side,
                              hipStream_t s);

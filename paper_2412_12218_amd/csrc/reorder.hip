@@ -294,8 +294,9 @@ size_t reorder_ws(int n, int nnz)
 {
     const int64_t m = n > nnz ? n : nnz;
     const size_t order = 4 * align_up(static_cast<size_t>(m) * sizeof(uint32_t), 256) + radix_ws(m) + scan_ws(static_cast<int64_t>(n) + 1);
-    const size_t lpa = label_propagation_ws(n, nnz);
-    return order > lpa ? order : lpa;
+    const size_t lpa = label_propagation_ws(n, nnz), rows = row_sort_ws(n, nnz);
+    const size_t most = order > lpa ? order : lpa;
+    return most > rows ? most : rows;
 }
 
 int32_t launch_degree_order(const ftc_csr &g, int mode, int *perm, int *inv, void *ws, hipStream_t s)
@@ -346,7 +347,7 @@ int32_t launch_order_by_key(int n, const int *keys_in, int *perm, int *inv, int 
 }
 
 // ---- label propagation ---------------------------------------------------------------------------
-// Every round: pairs (label of the entry's column, row) sorted by label and then, stably, by row put
+// Graphs of at most ROW_SORT_NODES nodes are handled row by row (reorder_rows.hip).  Above, every round: pairs (label of the entry's column, row) sorted by label and then, stably, by row put
 // equal labels of a row side by side; a run of equal (row, label) is one candidate, its length the
 // number of votes.  The candidate with the most votes and, among those, the smallest label wins:
 // the maximum of (votes << 32 | ~label), taken with a 64-bit atomic maximum per row (the maximum
@@ -445,6 +446,7 @@ int32_t launch_label_propagation(const ftc_csr &g, int iters, int *labels, void 
 {
     const int n = g.n, nnz = g.nnz;
     if (n == 0) return FTC_OK;
+    if (nnz > 0 && iters > 0 && n <= ROW_SORT_NODES) return launch_label_rounds(g, iters, labels, ws, s);
     hipLaunchKernelGGL(iota_kernel, dim3((n + 255) / 256), dim3(256), 0, s, n, labels);
     if (nnz == 0 || iters <= 0) return launch_status("label propagation");
     const int64_t m = n > nnz ? n : nnz;
@@ -487,6 +489,8 @@ int32_t launch_label_propagation(const ftc_csr &g, int iters, int *labels, void 
 }
 
 // ---- relabelled graph ----------------------------------------------------------------------------
+// Graphs of at most ROW_SORT_NODES nodes: the rows are sorted one by one (reorder_rows.hip); above, all entries by column and
+// row with the radix sort (relabel_kernel and below).
 // A (perm, inv) pair that is not a permutation and its inverse sets *flag and loses the entries of
 // the rows concerned; no index is followed before it is checked.
 __global__ __launch_bounds__(256) void permuted_degrees_kernel(int n, const int *__restrict__ row_ptr,
@@ -558,6 +562,8 @@ int32_t launch_permute_graph(const ftc_csr &g, const int *perm, const int *inv, 
     int32_t st = exclusive_scan(deg, n, row_ptr_out, true, ws_scan, s);
     if (st != FTC_OK) return st;
     if (nnz == 0) return FTC_OK;
+    // up to ROW_SORT_NODES nodes the rows are sorted one by one (the staged degrees are used up: the whole workspace is free)
+    if (n <= ROW_SORT_NODES) return launch_relabel_rows(g, perm, inv, row_ptr_out, col_idx_out, flag, ws, s);
     hipLaunchKernelGGL(fill_u32_kernel, dim3(ceil_div(nnz, 256)), dim3(256), 0, s, k0, v0, static_cast<int64_t>(nnz));
     hipLaunchKernelGGL(relabel_kernel, dim3(ceil_div(nnz, 256)), dim3(256), 0, s, n, nnz, g.row_ptr, g.col_idx, inv, perm,
                        row_ptr_out, k0, v0, flag);

@@ -1,0 +1,641 @@
+// Row-wise kernels of the reordering step for graphs of at most ROW_SORT_NODES nodes: the relabelled graph and a
+// round of label propagation both look every entry's column up in an array of n ints and need the results of ONE
+// row in ascending order -- the new columns to write them out, the labels to find the longest run of equal ones.
+// Rows are independent, so nothing is sorted across rows: a row is sorted where it fits,
+//   at most 32 / 64 entries     half a wave / a wave, one entry per lane (bitonic, data-parallel-primitive moves),
+//   at most 256 / 1024          a wave, 4 / 16 entries per lane,
+//   at most 8192                a workgroup of 1024 threads, in LDS,
+//   longer                      a bitmap of the columns in LDS (relabelling; duplicates: counters, see below) or
+//                               counters in LDS per 32 768 labels (label propagation).
+// What bounds them: the look-up.  Every entry is one 4-byte gather from an array that about fills an L2 (4 MB at
+// a million nodes); the streams around it (column ids in, columns out) are read and written once, non-temporal.
+// On the block model with a million nodes and 32 M entries a round of label propagation takes 0.28 ms and the
+// relabelled graph 0.35 ms (R-MAT, 2^20 nodes: 0.52); sorting all entries by label and row with the global radix sort took
+// 4.0 and 4.1 ms.
+// Larger graphs keep the radix sort: the counters of the long rows cost one pass over the row per 32 768 nodes.
+#include "ftc_common.hpp"
+
+namespace ftc {
+
+constexpr int RS_ROWS = 32;         // consecutive rows per wave of the short-row part
+constexpr int RS_SHORT = 64;        // longest row handled there; the queues hold the rows above
+constexpr int RS_MID = 256, RS_LONG = 1024, RS_LDS = 8192;  // longest row of queues 0, 1, 2; queue 3 has the rest
+constexpr int RS_RANGE = 32768;     // counters per pass over a long row
+constexpr int RS_BITS_LOG2 = 20;    // columns per bitmap pass over a long row (32 768 words)
+constexpr int RS_NONE = 0x7fffffff; // sorts behind every column and label
+
+// lengths of the rows: len[r] = rp[r + 1] - rp[r]; counts[q] rows of class q in rows[q]
+struct RowQueues {
+    int *counts;
+    int *rows[4];
+    int *dup_rows;               // relabelling: long rows with duplicate columns, counts[4] of them
+    unsigned long long *best;    // label propagation: winner of every row of queue 3
+};
+
+__global__ __launch_bounds__(1024) void row_classes_kernel(int n, const int *__restrict__ rp, RowQueues q)
+{
+    constexpr int PER = 4;
+    __shared__ int cnt_s[4], base_s[4];
+    if (threadIdx.x < 4) cnt_s[threadIdx.x] = 0;
+    __syncthreads();
+    int cls[PER], pos[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int64_t r = (static_cast<int64_t>(blockIdx.x) * PER + k) * 1024 + threadIdx.x;
+        const int len = r < n ? rp[r + 1] - rp[r] : 0;
+        cls[k] = len <= RS_SHORT ? -1 : len <= RS_MID ? 0 : len <= RS_LONG ? 1 : len <= RS_LDS ? 2 : 3;
+        pos[k] = cls[k] >= 0 ? atomicAdd(&cnt_s[cls[k]], 1) : 0;
+    }
+    __syncthreads();
+    if (threadIdx.x < 4 && cnt_s[threadIdx.x] > 0) base_s[threadIdx.x] = atomicAdd(&q.counts[threadIdx.x], cnt_s[threadIdx.x]);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < PER; ++k)
+        if (cls[k] >= 0)
+            q.rows[cls[k]][base_s[cls[k]] + pos[k]] = static_cast<int>((static_cast<int64_t>(blockIdx.x) * PER + k) * 1024 + threadIdx.x);
+}
+
+// ---- the two uses -----------------------------------------------------------------------------------
+// Row r of the result: entries [start, start + len) of col_idx; value(c) is what column c becomes.
+struct Relabel {
+    static constexpr bool VOTES = false;
+    int n;
+    const int *row_ptr, *col_idx, *perm, *map, *rp;  // map: inv; rp: row starts of the relabelled graph
+    int *out, *flag;
+    __device__ __forceinline__ void row(int r, int &start, int &len) const
+    {
+        len = rp[r + 1] - rp[r];
+        start = len > 0 ? row_ptr[perm[r]] : 0;  // a row that has entries has passed the check of perm[r]
+    }
+    __device__ __forceinline__ int value(int c) const
+    {
+        const bool in = c >= 0 && c < n;
+        const int v = in ? map[c] : -1;
+        if (v >= 0 && v < n) return v;
+        atomicOr(flag, 1);
+        return 0;
+    }
+};
+struct Votes {
+    static constexpr bool VOTES = true;
+    int n;
+    const int *col_idx, *map, *rp;  // map: labels of the round before
+    int *out;                       // labels of this round
+    __device__ __forceinline__ void row(int r, int &start, int &len) const
+    {
+        start = rp[r];
+        len = rp[r + 1] - start;
+    }
+    __device__ __forceinline__ int value(int c) const { return (c >= 0 && c < n) ? map[c] : 0; }  // out of range: a vote for label 0
+};
+
+// ---- sorting in registers ------------------------------------------------------------------------------
+// value of lane (lane ^ S)
+template <int S>
+__device__ __forceinline__ int lane_xor(int v)
+{
+    if constexpr (S == 1) return __builtin_amdgcn_update_dpp(0, v, 0xb1, 0xf, 0xf, true);         // quad_perm [1,0,3,2]
+    else if constexpr (S == 2) return __builtin_amdgcn_update_dpp(0, v, 0x4e, 0xf, 0xf, true);    // quad_perm [2,3,0,1]
+    else if constexpr (S == 4) {
+        const int m = __builtin_amdgcn_update_dpp(0, v, 0x141, 0xf, 0xf, true);                   // row_half_mirror: ^ 7
+        return __builtin_amdgcn_update_dpp(0, m, 0x1b, 0xf, 0xf, true);                           // quad_perm [3,2,1,0]: ^ 3
+    } else if constexpr (S == 8) return __builtin_amdgcn_update_dpp(0, v, 0x128, 0xf, 0xf, true); // row_ror:8
+    else return __shfl_xor(v, S, 64);
+}
+
+template <int STRIDE, int SIZE, int K, int W>
+__device__ __forceinline__ void bitonic_stage(int (&v)[K], int li)
+{
+    if constexpr (STRIDE >= 64) {  // the partner sits in the same lane
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            constexpr int KS = STRIDE / 64;
+            if ((k & KS) == 0) {
+                const bool up = ((k * 64) & SIZE) == 0;
+                const int a = v[k], b = v[k | KS];
+                v[k] = up ? min(a, b) : max(a, b);
+                v[k | KS] = up ? max(a, b) : min(a, b);
+            }
+        }
+    } else {
+        const bool lower = (li & STRIDE) == 0;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int o = lane_xor<STRIDE>(v[k]);
+            const bool up = SIZE >= K * W || ((k * 64 + li) & SIZE) == 0;
+            v[k] = (up == lower) ? min(v[k], o) : max(v[k], o);
+        }
+    }
+    if constexpr (STRIDE > 1) bitonic_stage<STRIDE / 2, SIZE, K, W>(v, li);
+}
+
+// Element i of the row sits in register i / 64, lane i % 64 (W = 64), or in lane i of the half wave (W = 32, K = 1).
+template <int SIZE, int K, int W>
+__device__ __forceinline__ void bitonic_sort(int (&v)[K], int li)
+{
+    if constexpr (SIZE > 2) bitonic_sort<SIZE / 2, K, W>(v, li);
+    bitonic_stage<SIZE / 2, SIZE, K, W>(v, li);
+}
+
+template <int W>
+__device__ __forceinline__ int group_max(int v)
+{
+    v = max(v, lane_xor<1>(v)); v = max(v, lane_xor<2>(v)); v = max(v, lane_xor<4>(v)); v = max(v, lane_xor<8>(v));
+    v = max(v, lane_xor<16>(v));
+    if constexpr (W == 64) v = max(v, lane_xor<32>(v));
+    return v;
+}
+template <int W>
+__device__ __forceinline__ int group_min(int v)
+{
+    v = min(v, lane_xor<1>(v)); v = min(v, lane_xor<2>(v)); v = min(v, lane_xor<4>(v)); v = min(v, lane_xor<8>(v));
+    v = min(v, lane_xor<16>(v));
+    if constexpr (W == 64) v = min(v, lane_xor<32>(v));
+    return v;
+}
+
+// The value of the longest run of equal values among the first `len` sorted ones, the smallest on a tie.
+template <int K, int W>
+__device__ __forceinline__ int longest_run(const int (&v)[K], int len, int lane)
+{
+    const int li = lane & (W - 1);
+    int best = 0, best_v = RS_NONE;
+    int next = len;  // where the first run after register k begins
+#pragma unroll
+    for (int k = K - 1; k >= 0; --k) {
+        int prev = __shfl_up(v[k], 1, 64);
+        if constexpr (K > 1) {
+            if (k > 0) {
+                const int last = __builtin_amdgcn_readlane(v[k > 0 ? k - 1 : 0], 63);
+                if (lane == 0) prev = last;
+            }
+        }
+        const int i = k * 64 + li;
+        const bool start = i < len && (i == 0 || prev != v[k]);
+        unsigned long long m = __builtin_amdgcn_ballot_w64(start);
+        if constexpr (W == 32) m = lane < 32 ? m & 0xffffffffull : m >> 32;
+        const unsigned long long above = li < 63 ? m & (~0ull << (li + 1)) : 0ull;
+        const int end = above ? k * 64 + __ffsll(static_cast<long long>(above)) - 1 : next;
+        if (start && end - i >= best) { best = end - i; best_v = v[k]; }  // registers descend: >= keeps the smaller value
+        if (m) next = k * 64 + __ffsll(static_cast<long long>(m)) - 1;
+    }
+    const int most = group_max<W>(best);
+    return group_min<W>(best == most ? best_v : RS_NONE);
+}
+
+// Sorted values of row r leave: all of them, or the winner's label.
+template <class Use, int K, int W>
+__device__ __forceinline__ void row_done(const Use &u, int r, int dst, int len, const int (&v)[K], int lane)
+{
+    const int li = lane & (W - 1);
+    if constexpr (Use::VOTES) {
+        const int w = longest_run<K, W>(v, len, lane);
+        if (li == 0 && len > 0) u.out[r] = w;
+    } else {
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            if (k * 64 + li < len) __builtin_nontemporal_store(v[k], u.out + dst + k * 64 + li);
+    }
+}
+
+// one row of a queue by one wave, K entries per lane
+template <class Use, int K>
+__device__ __forceinline__ void queued_row(const Use &u, int r, int lane)
+{
+    int start, len;
+    u.row(r, start, len);
+    int v[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = k * 64 + lane < len ? __builtin_nontemporal_load(u.col_idx + start + k * 64 + lane) : -1;
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = k * 64 + lane < len ? u.value(v[k]) : RS_NONE;
+    bitonic_sort<64 * K, K, 64>(v, lane);
+    row_done<Use, K, 64>(u, r, u.rp[r], len, v, lane);
+}
+
+// Workgroups below `queue_blocks` take the rows of 65 to 1024 entries from the queues, one wave a row; the
+// others take RS_ROWS consecutive rows per wave and sort the short ones among them: two rows of at most 32
+// entries side by side in the halves of the wave, four such pairs in flight, then the rows of 33 to 64.
+template <class Use>
+__global__ __launch_bounds__(256) void row_sort_kernel(Use u, RowQueues q, int queue_blocks)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (static_cast<int>(blockIdx.x) < queue_blocks) {
+        const int first = blockIdx.x * 4 + wave, step = queue_blocks * 4;
+        const int n1 = q.counts[1], n0 = q.counts[0];
+        if constexpr (Use::VOTES) {  // the rows above RS_LDS collect their winner in q.best (row_sort_big_kernel)
+            const int n3 = q.counts[3];
+            for (int i = blockIdx.x * 256 + threadIdx.x; i < n3; i += queue_blocks * 256) q.best[i] = 0ull;
+        }
+        for (int i = first; i < n1; i += step) queued_row<Use, RS_LONG / 64>(u, q.rows[1][i], lane);
+        for (int i = first; i < n0; i += step) queued_row<Use, RS_MID / 64>(u, q.rows[0][i], lane);
+        return;
+    }
+    const int64_t r0 = (static_cast<int64_t>(blockIdx.x - queue_blocks) * 4 + wave) * RS_ROWS;
+    if (r0 >= u.n) return;
+    int start_l = 0, len_l = 0, dst_l = 0;
+    const int r_l = static_cast<int>(r0) + lane;
+    if (lane < RS_ROWS && r_l < u.n) {
+        u.row(r_l, start_l, len_l);
+        dst_l = u.rp[r_l];
+        if constexpr (Use::VOTES) {
+            if (len_l == 0) u.out[r_l] = u.map[r_l];  // a row without entries keeps its label
+        }
+    }
+    const int half = lane >> 5, li = lane & 31;
+    constexpr int PAIRS = 4;
+    for (int p0 = 0; p0 < RS_ROWS / 2; p0 += PAIRS) {
+        int v[PAIRS], len[PAIRS], c[PAIRS];
+#pragma unroll
+        for (int p = 0; p < PAIRS; ++p) {
+            const int t = (p0 + p) * 2 + half;
+            const int st = __shfl(start_l, t, 64);
+            const int ln = __shfl(len_l, t, 64);
+            len[p] = ln <= 32 ? ln : 0;
+            c[p] = li < len[p] ? __builtin_nontemporal_load(u.col_idx + st + li) : -1;
+        }
+#pragma unroll
+        for (int p = 0; p < PAIRS; ++p) v[p] = li < len[p] ? u.value(c[p]) : RS_NONE;
+#pragma unroll
+        for (int p = 0; p < PAIRS; ++p) {
+            const int t = (p0 + p) * 2 + half;
+            int x[1] = {v[p]};
+            bitonic_sort<32, 1, 32>(x, li);
+            row_done<Use, 1, 32>(u, static_cast<int>(r0) + t, __shfl(dst_l, t, 64), len[p], x, lane);
+        }
+    }
+    unsigned long long rest = __builtin_amdgcn_ballot_w64(len_l > 32 && len_l <= RS_SHORT);
+    while (rest) {  // two rows in flight
+        const int t0 = __ffsll(static_cast<long long>(rest)) - 1;
+        rest &= rest - 1;
+        const int t1 = rest ? __ffsll(static_cast<long long>(rest)) - 1 : -1;
+        if (rest) rest &= rest - 1;
+        const int st0 = __builtin_amdgcn_readlane(start_l, t0), ln0 = __builtin_amdgcn_readlane(len_l, t0);
+        const int st1 = t1 >= 0 ? __builtin_amdgcn_readlane(start_l, t1) : 0, ln1 = t1 >= 0 ? __builtin_amdgcn_readlane(len_l, t1) : 0;
+        const int c0 = lane < ln0 ? __builtin_nontemporal_load(u.col_idx + st0 + lane) : -1;
+        const int c1 = lane < ln1 ? __builtin_nontemporal_load(u.col_idx + st1 + lane) : -1;
+        int x0[1] = {lane < ln0 ? u.value(c0) : RS_NONE};
+        int x1[1] = {lane < ln1 ? u.value(c1) : RS_NONE};
+        bitonic_sort<64, 1, 64>(x0, lane);
+        row_done<Use, 1, 64>(u, static_cast<int>(r0) + t0, __builtin_amdgcn_readlane(dst_l, t0), ln0, x0, lane);
+        if (t1 >= 0) {
+            bitonic_sort<64, 1, 64>(x1, lane);
+            row_done<Use, 1, 64>(u, static_cast<int>(r0) + t1, __builtin_amdgcn_readlane(dst_l, t1), ln1, x1, lane);
+        }
+    }
+}
+
+// ---- rows above 1024 entries: a workgroup of 1024 threads ------------------------------------------------
+constexpr int RS_NT = 1024;
+
+// exclusive sum over the workgroup; every thread gets its prefix, *total the sum
+__device__ __forceinline__ int group_exclusive_scan(int v, int *total, int *tmp)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int incl = wave_inclusive_scan(v);
+    __syncthreads();  // tmp of a previous call is consumed
+    if (lane == 63) tmp[wave] = incl;
+    __syncthreads();
+    int before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < RS_NT / 64; ++w) {
+        before += w < wave ? tmp[w] : 0;
+        all += tmp[w];
+    }
+    *total = all;
+    return before + incl - v;
+}
+
+// largest value over the workgroup, valid in thread 0
+__device__ __forceinline__ unsigned long long group_max_u64(unsigned long long v, unsigned long long *tmp)
+{
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) {
+        const unsigned long long o = __shfl_xor(v, m, 64);
+        v = o > v ? o : v;
+    }
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) tmp[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        for (int w = 1; w < RS_NT / 64; ++w) v = tmp[w] > v ? tmp[w] : v;
+    return v;
+}
+
+// votes and label as one number whose maximum is the winner: most votes, then the smallest label
+__device__ __forceinline__ unsigned long long ballot_of(int votes, int label)
+{
+    return (static_cast<unsigned long long>(static_cast<uint32_t>(votes)) << 32) | (0xffffffffu - static_cast<uint32_t>(label));
+}
+
+// 1025 .. 1024 K entries by 16 waves, K per lane (element i of the padded row in wave i / (64 K), register i / 64 % K, lane
+// i % 64).  Every wave sorts its share in registers, then the shares are merged: only the steps whose partner sits in
+// another wave go through LDS (ten of them, in two buffers taken in turn, one barrier each), the rest stays in registers.
+// A share that has to descend is sorted as its complement.  (All steps in LDS, 66 to 91
+// barriers a row: the kernel takes 0.60 ms on the R-MAT graph, this way 0.26.)
+template <class Use, int K>
+__device__ __forceinline__ void group_row(const Use &u, int r, int start, int len, int *s, unsigned long long *tmp)
+{
+    constexpr int SHARE = 64 * K, ALL = RS_NT * K;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, base = wave * SHARE;
+    int v[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int i = base + k * 64 + lane;
+        v[k] = i < len ? __builtin_nontemporal_load(u.col_idx + start + i) : -1;
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = base + k * 64 + lane < len ? u.value(v[k]) : RS_NONE;
+    const int flip0 = (base & SHARE) ? -1 : 0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] ^= flip0;
+    bitonic_sort<SHARE, K, 64>(v, lane);
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] ^= flip0;
+    __syncthreads();  // the row before is done with s
+    int *buf = s;
+    for (int size = 2 * SHARE; size <= ALL; size *= 2) {  // uniform
+        const bool up = (base & size) == 0;
+        for (int stride = size / 2; stride >= SHARE; stride /= 2) {
+#pragma unroll
+            for (int k = 0; k < K; ++k) buf[base + k * 64 + lane] = v[k];
+            __syncthreads();
+            const bool low = ((base & stride) == 0) == up;
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const int o = buf[(base ^ stride) + k * 64 + lane];
+                v[k] = low ? min(v[k], o) : max(v[k], o);
+            }
+            buf = buf == s ? s + ALL : s;  // the next step writes where nobody reads any more
+        }
+        const int flip = up ? 0 : -1;
+#pragma unroll
+        for (int k = 0; k < K; ++k) v[k] ^= flip;
+        bitonic_stage<SHARE / 2, SHARE, K, 64>(v, lane);
+#pragma unroll
+        for (int k = 0; k < K; ++k) v[k] ^= flip;
+    }
+    if constexpr (Use::VOTES) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) buf[base + k * 64 + lane] = v[k];
+        __syncthreads();
+        unsigned long long best = 0ull;
+        for (int i = threadIdx.x; i < len; i += RS_NT) {
+            const int x = buf[i];
+            if (i > 0 && buf[i - 1] == x) continue;
+            int lo = i + 1, hi = len;  // first element of the next run
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (buf[mid] == x) lo = mid + 1; else hi = mid;
+            }
+            const unsigned long long cand = ballot_of(lo - i, x);
+            best = cand > best ? cand : best;
+        }
+        best = group_max_u64(best, tmp);
+        if (threadIdx.x == 0) u.out[r] = static_cast<int>(0xffffffffu - static_cast<uint32_t>(best & 0xffffffffull));
+    } else {
+        const int dst = u.rp[r];
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            if (base + k * 64 + lane < len) __builtin_nontemporal_store(v[k], u.out + dst + base + k * 64 + lane);
+    }
+}
+
+template <class Use>
+__device__ __forceinline__ void lds_row(const Use &u, int r, int *s, unsigned long long *tmp)
+{
+    int start, len;
+    u.row(r, start, len);  // uniform
+    if (len <= 2 * RS_NT) group_row<Use, 2>(u, r, start, len, s, tmp);
+    else if (len <= 4 * RS_NT) group_row<Use, 4>(u, r, start, len, s, tmp);
+    else group_row<Use, 8>(u, r, start, len, s, tmp);
+}
+
+__device__ __forceinline__ int pad_word(int i) { return i + (i >> 5); }  // a thread's 32 consecutive words on all banks
+
+// more than RS_LDS entries, relabelling: the columns as bits, read back in ascending order.  false (uniform): a column
+// occurs twice.
+__device__ __forceinline__ bool bitmap_row(const Relabel &u, int r, uint32_t *bits, int *tmp, int *dup)
+{
+    int start, len;
+    u.row(r, start, len);
+    int dst = u.rp[r];
+    for (int base = 0; base < u.n; base += 1 << RS_BITS_LOG2) {
+        const int span = min(u.n - base, 1 << RS_BITS_LOG2);
+        __syncthreads();
+        for (int i = threadIdx.x; i < pad_word(1 << (RS_BITS_LOG2 - 5)); i += RS_NT) bits[i] = 0u;
+        if (threadIdx.x == 0) *dup = 0;
+        __syncthreads();
+        bool twice = false;
+        for (int i = threadIdx.x; i < len; i += RS_NT) {
+            const int c = u.value(u.col_idx[start + i]) - base;
+            if (c >= 0 && c < span) {
+                const uint32_t m = 1u << (c & 31);
+                twice = twice || (atomicOr(&bits[pad_word(c >> 5)], m) & m) != 0u;
+            }
+        }
+        if (twice) *dup = 1;
+        __syncthreads();
+        if (*dup) return false;
+        int mine = 0;
+        const int w0 = threadIdx.x * 32;
+        for (int w = 0; w < 32; ++w) mine += __popc(bits[pad_word(w0 + w)]);
+        int total;
+        int pos = dst + group_exclusive_scan(mine, &total, tmp);
+        if (mine > 0)
+            for (int w = 0; w < 32; ++w) {
+                uint32_t b = bits[pad_word(w0 + w)];
+                while (b) {
+                    u.out[pos++] = base + (w0 + w) * 32 + __ffs(static_cast<int>(b)) - 1;
+                    b &= b - 1;
+                }
+            }
+        dst += total;
+    }
+    return true;
+}
+
+// counters of the values [base, base + RS_RANGE) of a row; returns the thread's number of smaller values
+template <class Use>
+__device__ __forceinline__ int count_range(const Use &u, int start, int len, int base, int *cnt)
+{
+    __syncthreads();
+    for (int i = threadIdx.x; i < pad_word(RS_RANGE); i += RS_NT) cnt[i] = 0;
+    __syncthreads();
+    int less = 0;
+    for (int i = threadIdx.x; i < len; i += RS_NT) {
+        const int c = u.value(u.col_idx[start + i]) - base;
+        if (c < 0) ++less;
+        else if (c < RS_RANGE) atomicAdd(&cnt[pad_word(c)], 1);
+    }
+    __syncthreads();
+    return less;
+}
+
+template <class Use>
+__global__ __launch_bounds__(RS_NT) void row_sort_big_kernel(Use u, RowQueues q)
+{
+    __shared__ int s[RS_RANGE + RS_RANGE / 32];
+    __shared__ unsigned long long tmp64[RS_NT / 64];
+    __shared__ int tmp[RS_NT / 64];
+    __shared__ int dup;
+    const int n3 = q.counts[3], n2 = q.counts[2];
+    if constexpr (Use::VOTES) {
+        const int ranges = (u.n + RS_RANGE - 1) / RS_RANGE;
+        const int64_t tasks = static_cast<int64_t>(n3) * ranges;
+        for (int64_t t = blockIdx.x; t < tasks; t += gridDim.x) {  // uniform
+            const int h = static_cast<int>(t / ranges), base = static_cast<int>(t % ranges) * RS_RANGE;
+            int start, len;
+            u.row(q.rows[3][h], start, len);
+            count_range(u, start, len, base, s);
+            unsigned long long best = 0ull;
+            for (int i = threadIdx.x; i < RS_RANGE; i += RS_NT) {
+                const int votes = s[pad_word(i)];
+                const unsigned long long cand = votes > 0 ? ballot_of(votes, base + i) : 0ull;
+                best = cand > best ? cand : best;
+            }
+            best = group_max_u64(best, tmp64);
+            if (threadIdx.x == 0 && best != 0ull) atomicMax(&q.best[h], best);
+        }
+    } else {
+        for (int h = blockIdx.x; h < n3; h += gridDim.x) {
+            const int r = q.rows[3][h];
+            if (!bitmap_row(u, r, reinterpret_cast<uint32_t *>(s), tmp, &dup) && threadIdx.x == 0)
+                q.dup_rows[atomicAdd(&q.counts[4], 1)] = r;
+        }
+    }
+    for (int i = blockIdx.x; i < n2; i += gridDim.x) lds_row(u, q.rows[2][i], s, tmp64);
+}
+
+// long rows in which a column occurs more than once: counters instead of bits, one workgroup per row and range
+__global__ __launch_bounds__(RS_NT) void row_sort_dup_kernel(Relabel u, RowQueues q)
+{
+    __shared__ int s[RS_RANGE + RS_RANGE / 32];
+    __shared__ int tmp[RS_NT / 64];
+    const int ranges = (u.n + RS_RANGE - 1) / RS_RANGE;
+    const int64_t tasks = static_cast<int64_t>(q.counts[4]) * ranges;
+    for (int64_t t = blockIdx.x; t < tasks; t += gridDim.x) {  // uniform
+        const int r = q.dup_rows[t / ranges], base = static_cast<int>(t % ranges) * RS_RANGE;
+        int start, len;
+        u.row(r, start, len);
+        const int less = count_range(u, start, len, base, s);
+        int before;
+        group_exclusive_scan(less, &before, tmp);
+        int mine = 0;
+        const int i0 = threadIdx.x * 32;
+        for (int i = 0; i < 32; ++i) mine += s[pad_word(i0 + i)];
+        int total;
+        int pos = u.rp[r] + before + group_exclusive_scan(mine, &total, tmp);
+        if (mine > 0)
+            for (int i = 0; i < 32; ++i)
+                for (int k = s[pad_word(i0 + i)]; k > 0; --k) u.out[pos++] = base + i0 + i;
+    }
+}
+
+__global__ __launch_bounds__(256) void take_winners_kernel(RowQueues q, int *__restrict__ out)
+{
+    const int n3 = q.counts[3];
+    for (int h = blockIdx.x * 256 + threadIdx.x; h < n3; h += gridDim.x * 256)
+        out[q.rows[3][h]] = static_cast<int>(0xffffffffu - static_cast<uint32_t>(q.best[h] & 0xffffffffull));
+}
+
+// ---- launchers --------------------------------------------------------------------------------------------
+// Queue capacities for nnz entries, in rows.
+static int64_t queue_cap(int nnz, int longer_than) { return nnz / (longer_than + 1) + 1; }
+
+size_t row_sort_ws(int n, int nnz)
+{
+    auto ints = [](int64_t k) { return align_up(static_cast<size_t>(k) * sizeof(int), 256); };
+    return 256 + ints(queue_cap(nnz, RS_SHORT)) + ints(queue_cap(nnz, RS_MID)) + ints(queue_cap(nnz, RS_LONG)) +
+           2 * ints(queue_cap(nnz, RS_LDS)) + align_up(static_cast<size_t>(queue_cap(nnz, RS_LDS)) * 8, 256) + ints(n);
+}
+
+static RowQueues carve(int nnz, void *ws, int **labels)
+{
+    char *p = static_cast<char *>(ws);
+    auto ints = [&](int64_t k) {
+        int *a = reinterpret_cast<int *>(p);
+        p += align_up(static_cast<size_t>(k) * sizeof(int), 256);
+        return a;
+    };
+    RowQueues q;
+    q.counts = ints(64);
+    q.rows[0] = ints(queue_cap(nnz, RS_SHORT));
+    q.rows[1] = ints(queue_cap(nnz, RS_MID));
+    q.rows[2] = ints(queue_cap(nnz, RS_LONG));
+    q.rows[3] = ints(queue_cap(nnz, RS_LDS));
+    q.dup_rows = ints(queue_cap(nnz, RS_LDS));
+    q.best = reinterpret_cast<unsigned long long *>(p);
+    p += align_up(static_cast<size_t>(queue_cap(nnz, RS_LDS)) * 8, 256);
+    *labels = reinterpret_cast<int *>(p);
+    return q;
+}
+
+// clears the queue counters; labels: every node starts with its own id (NULL: none)
+__global__ __launch_bounds__(256) void row_sort_begin_kernel(int n, int *__restrict__ counts, int *__restrict__ labels)
+{
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < 64) counts[i] = 0;
+    if (labels && i < n) labels[i] = i;
+}
+
+struct RowSortGrid {
+    int queue_blocks, blocks, big_blocks;
+};
+
+static RowSortGrid row_sort_grid(int n, int nnz)
+{
+    RowSortGrid g;
+    const int64_t queued = queue_cap(nnz, RS_SHORT);
+    g.queue_blocks = static_cast<int>((queued + 3) / 4 < 1024 ? (queued + 3) / 4 : 1024);
+    g.blocks = g.queue_blocks + static_cast<int>((static_cast<int64_t>(n) + 4 * RS_ROWS - 1) / (4 * RS_ROWS));
+    const int64_t big = queue_cap(nnz, RS_LONG);
+    g.big_blocks = static_cast<int>(big < 256 ? big : 256);
+    return g;
+}
+
+static void classify_rows(int n, const int *rp, const RowQueues &q, int *labels, hipStream_t s)
+{
+    hipLaunchKernelGGL(row_sort_begin_kernel, dim3(labels ? (n + 255) / 256 : 1), dim3(256), 0, s, n, q.counts, labels);
+    hipLaunchKernelGGL(row_classes_kernel, dim3((n + 4095) / 4096), dim3(1024), 0, s, n, rp, q);
+}
+
+// rp: row starts of the relabelled graph, complete before this on the stream; ws: row_sort_ws(n, nnz) bytes
+int32_t launch_relabel_rows(const ftc_csr &g, const int *perm, const int *inv, const int *rp, int *col_idx_out, int *flag,
+                            void *ws, hipStream_t s)
+{
+    int *unused;
+    const RowQueues q = carve(g.nnz, ws, &unused);
+    const RowSortGrid grid = row_sort_grid(g.n, g.nnz);
+    const Relabel u{g.n, g.row_ptr, g.col_idx, perm, inv, rp, col_idx_out, flag};
+    classify_rows(g.n, rp, q, nullptr, s);
+    if (g.nnz > RS_LONG) hipLaunchKernelGGL(row_sort_big_kernel<Relabel>, dim3(grid.big_blocks), dim3(RS_NT), 0, s, u, q);
+    hipLaunchKernelGGL(row_sort_kernel<Relabel>, dim3(grid.blocks), dim3(256), 0, s, u, q, grid.queue_blocks);
+    if (g.nnz > RS_LDS) hipLaunchKernelGGL(row_sort_dup_kernel, dim3(grid.big_blocks), dim3(RS_NT), 0, s, u, q);
+    return launch_status("relabel rows");
+}
+
+// `labels` holds the labels after the last round; ws: row_sort_ws(n, nnz) bytes
+int32_t launch_label_rounds(const ftc_csr &g, int iters, int *labels, void *ws, hipStream_t s)
+{
+    int *other;
+    const RowQueues q = carve(g.nnz, ws, &other);
+    const RowSortGrid grid = row_sort_grid(g.n, g.nnz);
+    // the rounds alternate between the two arrays and end in `labels`
+    int *from = iters % 2 == 0 ? labels : other, *to = iters % 2 == 0 ? other : labels;
+    classify_rows(g.n, g.row_ptr, q, from, s);
+    for (int it = 0; it < iters; ++it) {
+        const Votes u{g.n, g.col_idx, from, g.row_ptr, to};
+        hipLaunchKernelGGL(row_sort_kernel<Votes>, dim3(grid.blocks), dim3(256), 0, s, u, q, grid.queue_blocks);
+        if (g.nnz > RS_LONG) hipLaunchKernelGGL(row_sort_big_kernel<Votes>, dim3(grid.big_blocks), dim3(RS_NT), 0, s, u, q);
+        if (g.nnz > RS_LDS)
+            hipLaunchKernelGGL(take_winners_kernel, dim3(static_cast<unsigned>((queue_cap(g.nnz, RS_LDS) + 255) / 256)),
+                               dim3(256), 0, s, q, to);
+        int *t = from;
+        from = to;
+        to = t;
+    }
+    return launch_status("label propagation");
+}
+
+}  // namespace ftc

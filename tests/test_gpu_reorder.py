@@ -273,3 +273,59 @@ def test_order_by_key_random_keys_and_negative_flag():
     keys[5] = -3
     _, _, flag = B.ftc_order_by_key(torch.from_numpy(keys).cuda())
     assert int(flag.item()) == 1
+
+
+# ------------------------------------------------------------------ row-wise sorting: edges of the row classes
+ROW_EDGES = [0, 1, 2, 31, 32, 33, 63, 64, 65, 255, 256, 257, 1023, 1024, 1025, 2048, 2049, 8191, 8192, 8193, 40_000]
+
+
+def edge_rows_graph(n, distinct, seed):
+    """Rows of every length at which the row-wise kernels change, in random places; columns unsorted, with or
+    without duplicates inside a row."""
+    rng = np.random.default_rng(seed)
+    deg = np.zeros(n, dtype=np.int64)
+    at = rng.choice(n, size=3 * len(ROW_EDGES), replace=False)
+    deg[at] = np.tile(ROW_EDGES, 3)
+    deg[rng.choice(n, size=min(n, 3000), replace=False)] += rng.integers(0, 5, size=min(n, 3000))
+    row_ptr = np.zeros(n + 1, dtype=np.int32)
+    row_ptr[1:] = np.cumsum(deg)
+    cols = []
+    for i in np.nonzero(deg)[0]:
+        cols.append(rng.choice(n, size=deg[i], replace=False) if distinct else rng.integers(0, max(1, n // 4), size=deg[i]))
+    return synth.Graph(n, row_ptr, np.concatenate(cols).astype(np.int32), "edges")
+
+
+def voted(rows, cand, n, keep):
+    """Most frequent candidate per row, the smallest on a tie; rows without entries keep theirs."""
+    key, votes = np.unique(rows * n + cand, return_counts=True)
+    order = np.lexsort((-(key % n), votes, key // n))       # per row ascending: the last one wins
+    r = (key // n)[order]
+    last = np.r_[r[1:] != r[:-1], True]
+    out = keep.copy()
+    out[r[last]] = (key % n)[order][last]
+    return out
+
+
+@pytest.mark.parametrize("n", [65_537, (1 << 20) + 77, 1 << 22, (1 << 22) + 1])
+@pytest.mark.parametrize("distinct", [True, False])
+def test_row_lengths_at_the_edges_of_the_row_classes(n, distinct):
+    """The last size is the first that sorts all entries at once instead of row by row."""
+    g = edge_rows_graph(n, distinct, seed=n + distinct)
+    say(f"row classes n={n} nnz={g.nnz} distinct={distinct}")
+    rows = np.repeat(np.arange(n, dtype=np.int64), np.diff(g.row_ptr))
+    col = g.col_idx.astype(np.int64)
+    perm = np.random.default_rng(3).permutation(n)
+    inv = np.empty(n, dtype=np.int64)
+    inv[perm] = np.arange(n)
+    dg = dev_graph(g)
+    i32 = lambda a: torch.from_numpy(a.astype(np.int32)).cuda()
+    pg, flag = B.ftc_permute_graph(dg, i32(perm), i32(inv))
+    key = np.sort(inv[rows] * n + inv[col])
+    assert int(flag.item()) == 0
+    assert np.array_equal(pg.row_ptr.cpu().numpy(), np.r_[0, np.cumsum(np.diff(g.row_ptr)[perm])])
+    assert np.array_equal(pg.col_idx.cpu().numpy(), key % n)
+    label = np.arange(n, dtype=np.int64)
+    for rounds in (1, 2):
+        label = voted(rows, label[col], n, label)
+        got = B.ftc_label_propagation(dg, rounds).cpu().numpy()
+        assert np.array_equal(got, label), f"{rounds} rounds"
