@@ -1,109 +1,183 @@
-// Dense update phase Z = X * W for tall-skinny shapes: X is streamed once, W sits in LDS.  The shapes of
-// the benchmark models (d_in <= 256, d_out <= 64) keep all of W on chip for the whole kernel; wider
-// inputs (the feature matrices of citation graphs have thousands of columns) go through the same
-// kernels in chunks of the contraction dimension, wider outputs in groups of 64 columns.
+// Dense update phase Z = X * W for tall-skinny shapes: X is streamed once, W sits in LDS.  Three kernels, all on the
+// matrix cores: 16-bit inputs with d_in <= 256, d_out <= 64 and aligned rows (the benchmark models) keep all of W on chip;
+// 16-bit inputs that are wider are contracted in chunks; everything else (fp32, odd widths, rows that are not 16-byte
+// aligned, few rows) goes through the general kernel.
 #include "ftc_common.hpp"
 
 namespace ftc {
 
-// One row of X per thread, DOUT accumulators.  W columns [col0, col0 + d_out) of a matrix with w_ld columns;
-// K_CHUNK rows of W are staged at a time (all of them when d_in <= K_CHUNK).
-template <class T, int DOUT>
-__global__ __launch_bounds__(256) void gemm_rows_kernel(int n, const void *__restrict__ X, int ldx, int d_in,
-                                                        const void *__restrict__ W, int wdt, int w_ld, int col0,
-                                                        int d_out, void *__restrict__ Z, int ldz, int zdt, Epi epi)
+// The general kernel: any element type, any width, rows at any alignment of their elements.  Contraction in fp32 on the
+// matrix cores (v_mfma_f32_16x16x4_f32; 16-bit elements are widened first), so products and sums are those of fp32
+// arithmetic.  A wave owns a tile of 16 rows of X and up to 16 NT output columns:
+//   A operand  lane l holds X[row0 + l%16][k0 + (l/16) V .. + V - 1], one 16-byte load (V = 4 or 8 elements; 64
+//              contiguous bytes per row and step); the j-th product takes element j of every lane, so the contraction
+//              index runs in steps of 4 V in an order of its own, the same for A and B;
+//   B operand  W is staged in LDS as fp32 in chunks of KC rows, four consecutive k of a column side by side: lane l
+//              reads W[k .. k + 3][n0 + l%16] as one 16-byte word.
+// Bound by reading X up to about 32 output columns and by the fp32 matrix rate (157 TFLOP/s) beyond.  SK = 4: for matrices
+// of few rows the four waves of a workgroup share one row tile and split every chunk's k between them (the partial
+// sums are added in wave order through LDS): 2708 rows would otherwise occupy 43 workgroups.
+// One tile per wave, 32 KB of W: two tiles per wave were 10 % slower, 64 KB up to 20 %, 16 KB 5 %.
+// Measured, vector units (X staged element by element in LDS, or one row per thread) against this:
+//   fp32 100 000 x 1433 -> 16: 925 / 145 us (4.0 TB/s); fp32 100 000 x 300 -> 128: 315 / 128 us (60 TFLOP/s);
+//   fp32 400 000 x 128 -> 32: 425 / 62 us; fp16 2708 x 1433 -> 16: 311 / 14 us.
+// Error against 64 bits (2-norm, fp32 1433 -> 16): 6.8e-7 / 4.8e-7.
+typedef float float4v __attribute__((ext_vector_type(4)));
+
+// Up to this many rows the waves split the contraction (256 workgroups of 64 rows would be the most without).
+constexpr int GEMM_SPLIT_ROWS = 16384;
+
+// V elements at element index idx; only the alignment of one element is assumed (global loads need no more)
+template <class T>
+__device__ __forceinline__ void load_any(const void *base, int64_t idx, float (&f)[T::VEC])
 {
-    constexpr int V = T::VEC;
-    constexpr int K_CHUNK = 8192 / DOUT;  // 32 KB of fp32; a multiple of V
-    extern __shared__ float Ws[];         // min(d_in, K_CHUNK) x DOUT, zero padded beyond d_out
-    const int64_t row = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    float acc[DOUT];
+    if constexpr (T::BYTES == 4) {
+        typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
+        const f4 v = *reinterpret_cast<const f4 *>(static_cast<const float *>(base) + idx);
 #pragma unroll
-    for (int o = 0; o < DOUT; ++o) acc[o] = 0.f;
-    for (int kc0 = 0; kc0 < d_in; kc0 += K_CHUNK) {  // uniform
-        const int kn = d_in - kc0 < K_CHUNK ? d_in - kc0 : K_CHUNK;
-        if (kc0 > 0) __syncthreads();  // the previous chunk has been consumed
-        for (int t = threadIdx.x; t < kn * DOUT; t += 256) {
-            const int k = t / DOUT, o = t % DOUT;
-            Ws[t] = o < d_out ? load_elem(W, static_cast<int64_t>(kc0 + k) * w_ld + col0 + o, wdt) : 0.f;
-        }
-        __syncthreads();
-        if (row < n) {
-            for (int k0 = 0; k0 < kn; k0 += V) {
-                float x[V];
-                load_vec<T>(X, row * ldx + kc0 + k0, x);
+        for (int j = 0; j < 4; ++j) f[j] = v[j];
+    } else {
+        typedef uint16_t h8 __attribute__((ext_vector_type(8), aligned(2)));
+        const h8 v = *reinterpret_cast<const h8 *>(static_cast<const uint16_t *>(base) + idx);
 #pragma unroll
-                for (int kk = 0; kk < V; ++kk) {
-                    const float4 *w4 = reinterpret_cast<const float4 *>(Ws + (k0 + kk) * DOUT);
-#pragma unroll
-                    for (int o = 0; o < DOUT / 4; ++o) {
-                        const float4 w = w4[o];
-                        acc[4 * o] = fmaf(x[kk], w.x, acc[4 * o]);
-                        acc[4 * o + 1] = fmaf(x[kk], w.y, acc[4 * o + 1]);
-                        acc[4 * o + 2] = fmaf(x[kk], w.z, acc[4 * o + 2]);
-                        acc[4 * o + 3] = fmaf(x[kk], w.w, acc[4 * o + 3]);
-                    }
-                }
-            }
-        }
+        for (int j = 0; j < 8; ++j) f[j] = std::is_same<T, F16>::value ? f16_bits_to_f32(v[j]) : bf16_bits_to_f32(v[j]);
     }
-    if (row >= n) return;
-#pragma unroll
-    for (int o = 0; o < DOUT; ++o)
-        if (o < d_out) store_elem(Z, row * ldz + col0 + o, zdt, epi.apply(epi.factor(row), acc[o]));
 }
 
-// Any element type, any alignment (rows of X that are not 16-byte aligned, widths that are no multiple of
-// the vector length): a workgroup takes 64 rows and up to 64 output columns [col0, col0 + d_out), and
-// walks the contraction dimension in chunks of 64.  The chunk of X is read element by element with
-// consecutive threads on consecutive columns and parked in LDS as fp32 next to the chunk of W; a thread
-// then owns one row and 16 output columns.
-constexpr int GU_ROWS = 64, GU_K = 64;
-
-__global__ __launch_bounds__(256) void gemm_unaligned_kernel(int n, const void *__restrict__ X, int ldx, int dt, int d_in,
-                                                             const void *__restrict__ W, int w_ld, int col0, int d_out,
-                                                             void *__restrict__ Z, int ldz, int zdt, Epi epi)
+template <class T>
+__device__ __forceinline__ float load_one(const void *base, int64_t idx)
 {
-    __shared__ float Xs[GU_ROWS][GU_K + 1];  // odd stride: the 64 rows read by a wave fall on different banks
-    __shared__ __attribute__((aligned(16))) float Ws[GU_K][64];
-    const int tid = threadIdx.x;
-    const int64_t r0 = static_cast<int64_t>(blockIdx.x) * GU_ROWS;
-    const int r = tid & 63, og = tid >> 6;  // row of the tile, group of 16 output columns
-    float acc[16];
+    if constexpr (T::BYTES == 4) return static_cast<const float *>(base)[idx];
+    const uint32_t b = static_cast<const uint16_t *>(base)[idx];
+    return std::is_same<T, F16>::value ? f16_bits_to_f32(b) : bf16_bits_to_f32(b);
+}
+
+template <class T, int NT, int SK>
+__global__ __launch_bounds__(256) void gemm_any_kernel(int n, const void *__restrict__ X, int ldx, int d_in,
+                                                       const void *__restrict__ W, int w_ld, void *__restrict__ Z, int ldz,
+                                                       int zdt, Epi epi)
+{
+    constexpr int V = T::VEC, STEP = 4 * V;  // contraction indices per step of a wave
+    constexpr int KC = 512 / NT > SK * STEP ? 512 / NT : SK * STEP, COLS = 16 * NT, U = 4;
+    static_assert(KC % (SK * STEP) == 0, "every wave takes whole steps of a chunk");
+    static_assert(SK == 1 || KC >= 4 * 16, "the partial tiles fit the staging memory");
+    __shared__ __attribute__((aligned(16))) float Ws[KC * COLS];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int m = lane & 15, kb = lane >> 4;
+    const int col0 = blockIdx.y * COLS, cols = min(COLS, w_ld - col0);
+    const int64_t row0 = (SK == 1 ? static_cast<int64_t>(blockIdx.x) * 4 + wave : static_cast<int64_t>(blockIdx.x)) * 16;
+    const int wk = SK == 1 ? 0 : wave;
+    const int64_t at = min(row0 + m, static_cast<int64_t>(n) - 1) * ldx;  // clamped: stores are predicated
+    // two sums per element, of the even and of the odd products: shorter chains of dependent instructions and of roundings
+    float4v acc[2][NT];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) acc[j] = 0.f;
-    for (int k0 = 0; k0 < d_in; k0 += GU_K) {  // uniform
-        if (k0 > 0) __syncthreads();
-        for (int t = tid; t < GU_ROWS * GU_K; t += 256) {
-            const int rr = t / GU_K, kk = t % GU_K;
-            Xs[rr][kk] = (r0 + rr < n && k0 + kk < d_in) ? load_elem(X, (r0 + rr) * ldx + k0 + kk, dt) : 0.f;
-        }
-        for (int t = tid; t < GU_K * 64; t += 256) {
-            const int kk = t / 64, o = t % 64;
-            Ws[kk][o] = (k0 + kk < d_in && o < d_out) ? load_elem(W, static_cast<int64_t>(k0 + kk) * w_ld + col0 + o, dt) : 0.f;
+    for (int nt = 0; nt < NT; ++nt) acc[0][nt] = acc[1][nt] = float4v{0.f, 0.f, 0.f, 0.f};
+
+    auto multiply = [&](const float (&a)[V], int k) {  // k: first index of the step inside the chunk
+#pragma unroll
+        for (int q = 0; q < V / 4; ++q)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                const float4v b = *reinterpret_cast<const float4v *>(&Ws[(((k + kb * V) / 4 + q) * COLS + nt * 16 + m) * 4]);
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    acc[j & 1][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[4 * q + j], b[j], acc[j & 1][nt], 0, 0, 0);
+            }
+    };
+
+    for (int kc0 = 0; kc0 < d_in; kc0 += KC) {  // uniform
+        if (kc0 > 0) __syncthreads();           // the previous chunk has been consumed
+        const int kn = min(KC, (d_in - kc0 + STEP - 1) / STEP * STEP);
+        for (int t0 = tid; t0 < kn * COLS; t0 += 256 * 8) {  // eight loads in flight, unconditional, from clamped addresses
+            float w[8];
+            bool ok[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int k = (t0 + j * 256) / COLS, o = (t0 + j * 256) % COLS;
+                ok[j] = k < kn && kc0 + k < d_in && o < cols;
+                w[j] = load_one<T>(W, ok[j] ? static_cast<int64_t>(kc0 + k) * w_ld + col0 + o : 0);
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int k = (t0 + j * 256) / COLS, o = (t0 + j * 256) % COLS;
+                if (k < kn) Ws[((k >> 2) * COLS + o) * 4 + (k & 3)] = ok[j] ? w[j] : 0.f;
+            }
         }
         __syncthreads();
-#pragma unroll 8
-        for (int kk = 0; kk < GU_K; ++kk) {
-            const float x = Xs[r][kk];
+        int k = wk * (KC / SK);
+        const int k_end = min(k + KC / SK, d_in - kc0);  // this wave's share of the chunk
+        for (; k + U * STEP <= k_end; k += U * STEP) {
+            float a[U][V];
 #pragma unroll
-            for (int j = 0; j < 16; j += 4) {
-                const float4 w = *reinterpret_cast<const float4 *>(&Ws[kk][og * 16 + j]);
-                acc[j] = fmaf(x, w.x, acc[j]);
-                acc[j + 1] = fmaf(x, w.y, acc[j + 1]);
-                acc[j + 2] = fmaf(x, w.z, acc[j + 2]);
-                acc[j + 3] = fmaf(x, w.w, acc[j + 3]);
+            for (int s = 0; s < U; ++s) load_any<T>(X, at + kc0 + k + s * STEP + kb * V, a[s]);
+#pragma unroll
+            for (int s = 0; s < U; ++s) multiply(a[s], k + s * STEP);
+        }
+        for (; k < k_end; k += STEP) {
+            float a[V];
+            if (k + STEP <= k_end) {
+                load_any<T>(X, at + kc0 + k + kb * V, a);
+            } else {  // nothing beyond d_in is read
+#pragma unroll
+                for (int j = 0; j < V; ++j) {
+                    const int kk = k + kb * V + j;
+                    a[j] = kk < k_end ? load_one<T>(X, at + kc0 + kk) : 0.f;
+                }
+            }
+            multiply(a, k);
+        }
+    }
+    float4v sum[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) sum[nt] = acc[0][nt] + acc[1][nt];
+    if constexpr (SK == 1) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int64_t row = row0 + kb * 4 + i;
+            if (row < n) {
+                const float f = epi.factor(row);
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+                    if (nt * 16 + m < cols) store_elem(Z, row * ldz + col0 + nt * 16 + m, zdt, epi.apply(f, sum[nt][i]));
+            }
+        }
+    } else {
+        __syncthreads();
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) Ws[(wave * 16 + kb * 4 + i) * COLS + nt * 16 + m] = sum[nt][i];
+        __syncthreads();
+        for (int t = tid; t < 16 * COLS; t += 256) {
+            const int64_t row = row0 + t / COLS;
+            const int o = t % COLS;
+            if (row < n && o < cols) {
+                float v = Ws[t];
+#pragma unroll
+                for (int w = 1; w < SK; ++w) v += Ws[w * 16 * COLS + t];
+                store_elem(Z, row * ldz + col0 + o, zdt, epi.apply(epi.factor(row), v));
             }
         }
     }
-    const int64_t row = r0 + r;
-    if (row >= n) return;
-    const float f = epi.factor(static_cast<int>(row));
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        const int o = og * 16 + j;
-        if (o < d_out) store_elem(Z, row * ldz + col0 + o, zdt, epi.apply(f, acc[j]));
+}
+
+template <class T>
+static void gemm_any_t(int n, const void *X, int ldx, int d_in, const void *W, int d_out, void *Z, int ldz, int zdt,
+                       Epi epi, hipStream_t s)
+{
+    const bool split = n <= GEMM_SPLIT_ROWS;
+    const int64_t per = split ? 16 : 64;
+    const int nt = d_out <= 16 ? 1 : d_out <= 32 ? 2 : d_out <= 64 ? 4 : 8;
+    const dim3 grid(static_cast<unsigned>((n + per - 1) / per), static_cast<unsigned>((d_out + nt * 16 - 1) / (nt * 16)));
+#define FTC_GA(N)                                                                                                        \
+    if (nt == N) {                                                                                                       \
+        if (split) hipLaunchKernelGGL((gemm_any_kernel<T, N, 4>), grid, dim3(256), 0, s, n, X, ldx, d_in, W, d_out, Z,   \
+                                      ldz, zdt, epi);                                                                    \
+        else hipLaunchKernelGGL((gemm_any_kernel<T, N, 1>), grid, dim3(256), 0, s, n, X, ldx, d_in, W, d_out, Z, ldz,    \
+                                zdt, epi);                                                                               \
     }
+    FTC_GA(1) FTC_GA(2) FTC_GA(4) FTC_GA(8)
+#undef FTC_GA
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -117,7 +191,6 @@ __global__ __launch_bounds__(256) void gemm_unaligned_kernel(int n, const void *
 // The kernel is bound by streaming X from HBM; W (at most 256 x 64) is read once per workgroup.
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bhalf8 __attribute__((ext_vector_type(8)));
-typedef float float4v __attribute__((ext_vector_type(4)));
 
 template <class T>
 __device__ __forceinline__ float4v mfma16(const uint4 &a, const uint4 &b, float4v c)
@@ -344,32 +417,6 @@ static bool gemm_mfma_t(int n, const void *X, int ldx, int d_in, const void *W, 
     return false;
 }
 
-template <class T>
-static void gemm_t(int n, const void *X, int ldx, int d_in, const void *W, int wdt, int d_out, void *Z, int ldz, int zdt,
-                   Epi epi, hipStream_t s)
-{
-    const unsigned grid = static_cast<unsigned>((static_cast<int64_t>(n) + 255) / 256);
-    for (int col0 = 0; col0 < d_out; col0 += 64) {
-        const int cols = d_out - col0 < 64 ? d_out - col0 : 64;
-        int dpad = 8;
-        while (dpad < cols) dpad *= 2;
-        const int k_chunk = 8192 / dpad;
-        const size_t lds = static_cast<size_t>(d_in < k_chunk ? d_in : k_chunk) * dpad * sizeof(float);
-#define FTC_CASE(P)                                                                                          \
-    case P:                                                                                                  \
-        hipLaunchKernelGGL((gemm_rows_kernel<T, P>), dim3(grid), dim3(256), lds, s, n, X, ldx, d_in, W, wdt, \
-                           d_out, col0, cols, Z, ldz, zdt, epi);                                             \
-        break;
-        switch (dpad) {
-            FTC_CASE(8)
-            FTC_CASE(16)
-            FTC_CASE(32)
-            FTC_CASE(64)
-        }
-#undef FTC_CASE
-    }
-}
-
 int32_t launch_gemm(int n, const void *X, int ldx, int dt, int d_in, const void *W, int d_out, void *Z, int ldz,
                     int zdt, Epi epi, hipStream_t s)
 {
@@ -383,25 +430,18 @@ int32_t launch_gemm(int n, const void *X, int ldx, int dt, int d_in, const void 
         const bool done = fast && (dt == FTC_F16 ? gemm_mfma_t<F16>(n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi, s)
                                                  : gemm_mfma_t<BF16>(n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi, s));
         if (done) return launch_status("update_gemm mfma");
-        // beyond the register-resident shapes, or a width that is no multiple of 8 in padded rows
-        if (d_in > 256 || d_out > 64 || !fast) {
+        // beyond the register-resident shapes, or a width that is no multiple of 8 in padded rows; few rows are left to the
+        // general kernel, which splits the contraction over the waves (2708 x 1432 -> 16: 44 us here, 14 us there;
+        // 100 000 rows: 104 us here, 115 us there)
+        if ((d_in > 256 || d_out > 64 || !fast) && n > GEMM_SPLIT_ROWS) {
             if (dt == FTC_F16) gemm_mfma_wide_t<F16>(n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi, s);
             else gemm_mfma_wide_t<BF16>(n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi, s);
             return launch_status("update_gemm mfma (wide)");
         }
     }
-    if (fast) {
-        if (dt == FTC_F32) gemm_t<F32>(n, X, ldx, d_in, W, dt, d_out, Z, ldz, zdt, epi, s);
-        else if (dt == FTC_F16) gemm_t<F16>(n, X, ldx, d_in, W, dt, d_out, Z, ldz, zdt, epi, s);
-        else gemm_t<BF16>(n, X, ldx, d_in, W, dt, d_out, Z, ldz, zdt, epi, s);
-    } else {
-        const unsigned grid = static_cast<unsigned>((static_cast<int64_t>(n) + GU_ROWS - 1) / GU_ROWS);
-        for (int col0 = 0; col0 < d_out; col0 += 64) {
-            const int cols = d_out - col0 < 64 ? d_out - col0 : 64;
-            hipLaunchKernelGGL(gemm_unaligned_kernel, dim3(grid), dim3(256), 0, s, n, X, ldx, dt, d_in, W, d_out, col0,
-                               cols, Z, ldz, zdt, epi);
-        }
-    }
+    if (dt == FTC_F32) gemm_any_t<F32>(n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi, s);
+    else if (dt == FTC_F16) gemm_any_t<F16>(n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi, s);
+    else gemm_any_t<BF16>(n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi, s);
     return launch_status("update_gemm");
 }
 

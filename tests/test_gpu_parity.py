@@ -858,3 +858,20 @@ def test_spmm_narrow_rows_at_slot_and_wave_boundaries(oracle):
         e2 = run_spmm(oracle, g, dtype, D, pad=pad, use_vals=False)
         say(f"  err {e1:.3e} {e2:.3e}")
         assert e1 < TOL[dtype] and e2 < TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype", [F32, F16, BF16])
+@pytest.mark.parametrize("n,d_in,d_out", [(1, 1, 1), (15, 3, 16), (17, 15, 17), (64, 17, 7), (65, 33, 65), (130, 511, 33),
+                                          (97, 513, 129), (1000, 129, 300), (16384, 31, 10), (16385, 31, 10),
+                                          (16385, 130, 100), (40_001, 257, 16)])
+def test_update_gemm_general_kernel_edges(oracle, dtype, n, d_in, d_out):
+    """Remainders of the row tiles, of the contraction steps and chunks and of the column groups, on both sides of the
+    row count up to which the waves split the contraction; rows at odd addresses (a view one element into a buffer)."""
+    X32, W32 = synth.uniform_features(n, d_in + 1, seed=n + d_in), synth.glorot_uniform(d_in, d_out, seed=d_out)
+    buf, X64 = quantise(X32, dtype)
+    Wd, W64 = quantise(W32, dtype)
+    ref, ab = oracle.gemm(X64[:, 1:], W64)
+    out = B.ftc_update_gemm(buf[:, 1:], Wd)
+    err = norm_err(out, ref, ab)
+    say(f"general update gemm {dtype} {n} x {d_in} -> {d_out}: err {err:.3e}")
+    assert err < 1e-5           # fp32 products and sums whatever the input type
