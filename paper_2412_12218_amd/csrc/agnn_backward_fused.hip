@@ -95,15 +95,15 @@ __global__ __launch_bounds__(256) void agnn_row_stats_kernel(int n, const void *
     }
 }
 
-template <class T, int VEC, int LPR>
+template <class T, int VEC, int LPR, int R>
 __global__ __launch_bounds__(256) void agnn_backward_fused_kernel(
     int nnz, int n_ranges, const int *__restrict__ col_idx, const int *__restrict__ edge_to_row,
     const void *__restrict__ HD, int D, float beta, const float2 *__restrict__ stats, float *__restrict__ QA,
     float *__restrict__ carry, int *__restrict__ carry_tail_row, float *__restrict__ dbeta_part)
 {
     constexpr int NG = 64 / LPR;
-    constexpr int RUN = SEG_R / NG;
-    constexpr int RP = SEG_R + NG;
+    constexpr int RUN = R / NG;
+    constexpr int RP = R + NG;
     constexpr int DP = LPR * VEC;
     constexpr int DP2 = 2 * DP;  // q slots, then agg slots
     constexpr int IDX_WORDS = 4 * 2 * RP;
@@ -119,11 +119,11 @@ __global__ __launch_bounds__(256) void agnn_backward_fused_kernel(
 
     const int v = xcd_chunked_block(blockIdx.x, gridDim.x) * 4 + wave;
     const bool active = v < n_ranges;
-    const int base = active ? v * SEG_R : 0;
-    const int n_valid = active ? min(SEG_R, nnz - base) : 0;
+    const int base = active ? v * R : 0;
+    const int n_valid = active ? min(R, nnz - base) : 0;
     // (the rows could come from the row starts as in the forward kernels; measured 3 % slower here)
 #pragma unroll
-    for (int j = 0; j < SEG_R / 64; ++j) {
+    for (int j = 0; j < R / 64; ++j) {
         const int i = j * 64 + lane;
         if (i < n_valid) {
             const int p = i + i / RUN;
@@ -132,8 +132,8 @@ __global__ __launch_bounds__(256) void agnn_backward_fused_kernel(
         }
     }
     const int prev_row = (active && base > 0) ? edge_to_row[base - 1] : -1;
-    const int next_row = (active && n_valid == SEG_R && base + SEG_R < nnz) ? edge_to_row[base + SEG_R] : -1;
-    const int far_row = (active && static_cast<int64_t>(base) + 2 * SEG_R < nnz) ? edge_to_row[base + 2 * SEG_R] : -1;
+    const int next_row = (active && n_valid == R && base + R < nnz) ? edge_to_row[base + R] : -1;
+    const int far_row = (active && static_cast<int64_t>(base) + 2 * R < nnz) ? edge_to_row[base + 2 * R] : -1;
     __syncthreads();
 
     const int rs = g * RUN;
@@ -368,28 +368,33 @@ static size_t bw_dp2(int dtype, int D)
     return 2 * static_cast<size_t>(vec) * lpr;
 }
 
-// [QA: n x DP2 fp32 | HD: n x DP2 elements | stats: n float2 | carry | tail rows | dbeta shares], DP2 of the
-// widest element type
-size_t agnn_backward_fused_ws(int n, int nnz, int D)
+static size_t bw_ws(int n, int nnz, int r, size_t dp2)
 {
-    size_t dp2 = 0;
-    if (agnn_backward_fused_shape(FTC_F32, D)) dp2 = bw_dp2(FTC_F32, D);
-    if (agnn_backward_fused_shape(FTC_F16, D) && bw_dp2(FTC_F16, D) > dp2) dp2 = bw_dp2(FTC_F16, D);
-    if (dp2 == 0) return 0;
-    const size_t n_ranges = (static_cast<size_t>(nnz) + SEG_R - 1) / SEG_R;
+    const size_t n_ranges = static_cast<size_t>(seg_count(nnz, r));
     return 2 * align_up(static_cast<size_t>(n) * dp2 * sizeof(float), 256) + align_up(static_cast<size_t>(n) * sizeof(float2), 256) +
            align_up(n_ranges * 2 * dp2 * sizeof(float), 256) + align_up(n_ranges * 2 * sizeof(int), 256) +
            align_up(n_ranges * sizeof(float), 256);
 }
 
-template <class T>
+// [QA: n x DP2 fp32 | HD: n x DP2 elements | stats: n float2 | carry | tail rows | dbeta shares], DP2 of the
+// widest element type
+size_t agnn_backward_fused_ws(int n, int nnz, int D, bool least)
+{
+    size_t dp2 = 0;
+    if (agnn_backward_fused_shape(FTC_F32, D)) dp2 = bw_dp2(FTC_F32, D);
+    if (agnn_backward_fused_shape(FTC_F16, D) && bw_dp2(FTC_F16, D) > dp2) dp2 = bw_dp2(FTC_F16, D);
+    if (dp2 == 0) return 0;
+    return bw_ws(n, nnz, least ? SEG_R : seg_range(nnz, SEG_AGNN_BACKWARD), dp2);
+}
+
+template <class T, int R>
 static void launch_bw_t(int vec, int lpr, unsigned grid, hipStream_t s, int nnz, int n_ranges, const ftc_csr &g,
                         const int *e2r, const void *HD, int D, float beta, const float2 *stats, float *QA, float *carry,
                         int *tail_row, float *dbeta_part)
 {
     constexpr int VM = T::VEC;
 #define FTC_BW(V, L)                                                                                                \
-    hipLaunchKernelGGL((agnn_backward_fused_kernel<T, V, L>), dim3(grid), dim3(256), 0, s, nnz, n_ranges, g.col_idx, \
+    hipLaunchKernelGGL((agnn_backward_fused_kernel<T, V, L, R>), dim3(grid), dim3(256), 0, s, nnz, n_ranges, g.col_idx, \
                        e2r, HD, D, beta, stats, QA, carry, tail_row, dbeta_part)
     if (vec == VM) {
         if (lpr == 4) FTC_BW(VM, 4);
@@ -408,13 +413,14 @@ static void launch_bw_t(int vec, int lpr, unsigned grid, hipStream_t s, int nnz,
 // 16-byte aligned with the same leading dimension, workspace of agnn_backward_fused_ws() bytes.
 int32_t launch_agnn_backward_fused(const ftc_csr &g, const ftc_windows &w, const void *H, const void *dY, int ld, int dt,
                                    int D, float beta, const float *row_z, const void *Y, int ldy, int ydt, void *dH,
-                                   int lddh, int dh_dt, float *dbeta, void *ws, hipStream_t s)
+                                   int lddh, int dh_dt, float *dbeta, void *ws, size_t ws_bytes, hipStream_t s)
 {
     int vec = 0, lpr = 0;
     seg_shape(dt, D, &vec, &lpr);
     const int dp = vec * lpr, dp2 = 2 * dp;
     const int n = g.n;
-    const int n_ranges = ceil_div(g.nnz, SEG_R);
+    const int r = ws_bytes >= bw_ws(n, g.nnz, seg_range(g.nnz, SEG_AGNN_BACKWARD), dp2) ? seg_range(g.nnz, SEG_AGNN_BACKWARD) : SEG_R;
+    const int n_ranges = static_cast<int>(seg_count(g.nnz, r));
     char *p = static_cast<char *>(ws);
     float *QA = reinterpret_cast<float *>(p);
     p += align_up(static_cast<size_t>(n) * dp2 * sizeof(float), 256);
@@ -440,21 +446,25 @@ int32_t launch_agnn_backward_fused(const ftc_csr &g, const ftc_windows &w, const
                            row_z, stats, HD);
     if (n_ranges > 0) {
         const unsigned grid = static_cast<unsigned>((n_ranges + 3) / 4);
-        if (dt == FTC_F32)
-            launch_bw_t<F32>(vec, lpr, grid, s, g.nnz, n_ranges, g, w.edge_to_row, HD, D, beta, stats, QA, carry, tail_row,
-                             dbeta_part);
-        else if (dt == FTC_F16)
-            launch_bw_t<F16>(vec, lpr, grid, s, g.nnz, n_ranges, g, w.edge_to_row, HD, D, beta, stats, QA, carry, tail_row,
-                             dbeta_part);
-        else
-            launch_bw_t<BF16>(vec, lpr, grid, s, g.nnz, n_ranges, g, w.edge_to_row, HD, D, beta, stats, QA, carry, tail_row,
-                              dbeta_part);
+#define FTC_BWR(T)                                                                                                        \
+    do {                                                                                                                  \
+        if (r == SEG_R) launch_bw_t<T, SEG_R>(vec, lpr, grid, s, g.nnz, n_ranges, g, w.edge_to_row, HD, D, beta, stats,   \
+                                              QA, carry, tail_row, dbeta_part);                                           \
+        else if (r == 256) launch_bw_t<T, 256>(vec, lpr, grid, s, g.nnz, n_ranges, g, w.edge_to_row, HD, D, beta, stats,  \
+                                               QA, carry, tail_row, dbeta_part);                                          \
+        else launch_bw_t<T, 128>(vec, lpr, grid, s, g.nnz, n_ranges, g, w.edge_to_row, HD, D, beta, stats, QA, carry,      \
+                                tail_row, dbeta_part);                                                                    \
+    } while (0)
+        if (dt == FTC_F32) FTC_BWR(F32);
+        else if (dt == FTC_F16) FTC_BWR(F16);
+        else FTC_BWR(BF16);
+#undef FTC_BWR
         const int32_t st = launch_status("agnn_backward_fused");
         if (st != FTC_OK) return st;
     }
     // rows cut by wave boundaries and rows without entries: the SpMM fix-up on the 2 * DP wide rows
     int32_t st = launch_seg_fixup(n, n_ranges, g.row_ptr, carry, tail_row, dp2, dp2, QA, dp2, FTC_F32, Epi{0, nullptr},
-                                  nullptr, SEG_R, s, "agnn_backward_fused fixup");
+                                  nullptr, r, s, "agnn_backward_fused fixup");
     if (st != FTC_OK) return st;
     hipLaunchKernelGGL(dbeta_sum_kernel, dim3(1), dim3(1024), 0, s, n_ranges, dbeta_part, dbeta);
     st = launch_status("agnn_backward_fused dbeta");

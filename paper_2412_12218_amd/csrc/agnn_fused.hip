@@ -14,7 +14,7 @@
 // random 4-byte gather per edge.
 //
 // Work partition, run structure and the handling of rows cut by run / wave boundaries are
-// those of the edge-balanced SpMM (spmm_seg.hip): 512 edges per wave staged in LDS, groups of
+// those of the edge-balanced SpMM (spmm_seg.hip): 512 edges per wave (fewer on small graphs) staged in LDS, groups of
 // LPR lanes walk contiguous runs, complete rows are stored from registers, cut rows are summed
 // in edge order in LDS and through a carry buffer.  The partial of a cut row is the pair
 // (numerator vector, denominator); the division happens once all pieces are added.
@@ -22,23 +22,27 @@
 
 namespace ftc {
 
-constexpr int AG_R = SEG_R;  // edges per wave
 constexpr int AG_B = 4;    // edges per batch
 
 bool seg_shape(int dtype, int D, int *vec, int *lpr);
 
-size_t agnn_fused_ws(int nnz, int D)
+static size_t ag_carry_ws(int nnz, int r, int dp)
+{
+    const size_t n_ranges = static_cast<size_t>(seg_count(nnz, r));
+    return align_up(n_ranges * 2 * (dp + 4) * sizeof(float), 256) + align_up(n_ranges * 2 * sizeof(int), 256);
+}
+
+size_t agnn_fused_ws(int nnz, int D, bool least)
 {
     int vec, lpr, dp = 0;
     if (seg_shape(FTC_F32, D, &vec, &lpr)) dp = vec * lpr;
     if (seg_shape(FTC_F16, D, &vec, &lpr) && vec * lpr > dp) dp = vec * lpr;
     if (dp == 0 || nnz == 0) return 0;
-    const size_t n_ranges = (static_cast<size_t>(nnz) + AG_R - 1) / AG_R;
-    return align_up(n_ranges * 2 * (dp + 4) * sizeof(float), 256) + align_up(n_ranges * 2 * sizeof(int), 256);
+    return ag_carry_ws(nnz, least ? SEG_R : seg_range(nnz, SEG_AGNN), dp);
 }
 
 // KEEP: also write what the backward pass needs (row_z, out32); compiled out of the inference kernel.
-template <class T, int VEC, int LPR, bool KEEP>
+template <class T, int VEC, int LPR, bool KEEP, int AG_R>
 __global__ __launch_bounds__(256) void agnn_fused_kernel(int nnz, int n_ranges, const int *__restrict__ row_ptr,
                                                          const int *__restrict__ col_idx,
                                                          const int *__restrict__ edge_to_row,
@@ -286,7 +290,7 @@ __global__ __launch_bounds__(256) void agnn_fused_fixup_kernel(int n, int n_rang
                                                                const int *__restrict__ carry_tail_row, int DP,
                                                                int D, void *__restrict__ out, int ldo, int odt,
                                                                float *__restrict__ row_z, float *__restrict__ out32,
-                                                               int ld32)
+                                                               int ld32, int seg_r)
 {
     constexpr int R = 64 / G;  // ranges per wave
     const int DPZ = DP + 4;
@@ -326,7 +330,7 @@ __global__ __launch_bounds__(256) void agnn_fused_fixup_kernel(int n, int n_rang
         longs &= longs - 1;
         const int v = __shfl(v_mine, src, 64), r = __shfl(rec.x, src, 64);
         {
-            const int last = (row_ptr[r + 1] - 1) / AG_R;
+            const int last = (row_ptr[r + 1] - 1) / seg_r;
             // teams of `dl` lanes (one lane per feature) share the ranges of a long row round-robin,
             // four loads in flight each; team sums are added in team order (fixed by the shape)
             int dl = 1;
@@ -383,7 +387,7 @@ __global__ __launch_bounds__(256) void agnn_fused_fixup_kernel(int n, int n_rang
     }
 }
 
-template <class T>
+template <class T, int R>
 static void launch_agnn_t(int vec, int lpr, unsigned grid, hipStream_t s, int nnz, int n_ranges, const ftc_csr &g,
                           const int *e2r, const void *H, int ld, int D, float beta, void *out,
                           int ldo, int odt, float *carry, int *tail_row, float *row_z, float *out32, int ld32)
@@ -391,10 +395,10 @@ static void launch_agnn_t(int vec, int lpr, unsigned grid, hipStream_t s, int nn
     constexpr int VM = T::VEC;
 #define FTC_AG(V, L)                                                                                                  \
     if (row_z || out32)                                                                                               \
-        hipLaunchKernelGGL((agnn_fused_kernel<T, V, L, true>), dim3(grid), dim3(256), 0, s, nnz, n_ranges, g.row_ptr, \
+        hipLaunchKernelGGL((agnn_fused_kernel<T, V, L, true, R>), dim3(grid), dim3(256), 0, s, nnz, n_ranges, g.row_ptr, \
                            g.col_idx, e2r, H, ld, D, beta, out, ldo, odt, carry, tail_row, row_z, out32, ld32);       \
     else                                                                                                              \
-        hipLaunchKernelGGL((agnn_fused_kernel<T, V, L, false>), dim3(grid), dim3(256), 0, s, nnz, n_ranges,           \
+        hipLaunchKernelGGL((agnn_fused_kernel<T, V, L, false, R>), dim3(grid), dim3(256), 0, s, nnz, n_ranges,           \
                            g.row_ptr, g.col_idx, e2r, H, ld, D, beta, out, ldo, odt, carry, tail_row, row_z, out32, ld32)
     if (vec == VM) {
         if (lpr == 4) { FTC_AG(VM, 4); }
@@ -410,29 +414,34 @@ static void launch_agnn_t(int vec, int lpr, unsigned grid, hipStream_t s, int nn
 }
 
 // Caller has checked: window index present, seg_shape() accepts (dt, D), rows of H and out 16-byte
-// aligned, workspace of agnn_fused_ws() bytes.
+// aligned, workspace of agnn_fused_ws(.., least) bytes.
 int32_t launch_agnn_fused(const ftc_csr &g, const ftc_windows &w, const void *H, int ld, int dt, int D,
                           float beta, void *out, int ldo, int odt, float *row_z, float *out32, int ld32, void *ws,
-                          hipStream_t s)
+                          size_t ws_bytes, hipStream_t s)
 {
     int vec = 0, lpr = 0;
     seg_shape(dt, D, &vec, &lpr);
     const int dp = vec * lpr;
-    const int n_ranges = ceil_div(g.nnz, AG_R);
+    const int r = ws_bytes >= ag_carry_ws(g.nnz, seg_range(g.nnz, SEG_AGNN), dp) ? seg_range(g.nnz, SEG_AGNN) : SEG_R;
+    const int n_ranges = static_cast<int>(seg_count(g.nnz, r));
     float *carry = static_cast<float *>(ws);
     int *tail_row = reinterpret_cast<int *>(
         static_cast<char *>(ws) + align_up(static_cast<size_t>(n_ranges) * 2 * (dp + 4) * sizeof(float), 256));
     if (n_ranges > 0) {
         const unsigned grid = static_cast<unsigned>((n_ranges + 3) / 4);
-        if (dt == FTC_F32)
-            launch_agnn_t<F32>(vec, lpr, grid, s, g.nnz, n_ranges, g, w.edge_to_row, H, ld, D, beta, out, ldo,
-                               odt, carry, tail_row, row_z, out32, ld32);
-        else if (dt == FTC_F16)
-            launch_agnn_t<F16>(vec, lpr, grid, s, g.nnz, n_ranges, g, w.edge_to_row, H, ld, D, beta, out, ldo,
-                               odt, carry, tail_row, row_z, out32, ld32);
-        else
-            launch_agnn_t<BF16>(vec, lpr, grid, s, g.nnz, n_ranges, g, w.edge_to_row, H, ld, D, beta, out, ldo,
-                                odt, carry, tail_row, row_z, out32, ld32);
+#define FTC_AGR(T)                                                                                                       \
+    do {                                                                                                                 \
+        if (r == SEG_R) launch_agnn_t<T, SEG_R>(vec, lpr, grid, s, g.nnz, n_ranges, g, w.edge_to_row, H, ld, D, beta,    \
+                                                out, ldo, odt, carry, tail_row, row_z, out32, ld32);                     \
+        else if (r == 256) launch_agnn_t<T, 256>(vec, lpr, grid, s, g.nnz, n_ranges, g, w.edge_to_row, H, ld, D, beta,   \
+                                                 out, ldo, odt, carry, tail_row, row_z, out32, ld32);                    \
+        else launch_agnn_t<T, 128>(vec, lpr, grid, s, g.nnz, n_ranges, g, w.edge_to_row, H, ld, D, beta, out, ldo, odt,   \
+                                  carry, tail_row, row_z, out32, ld32);                                                  \
+    } while (0)
+        if (dt == FTC_F32) FTC_AGR(F32);
+        else if (dt == FTC_F16) FTC_AGR(F16);
+        else FTC_AGR(BF16);
+#undef FTC_AGR
         const int32_t st = launch_status("agnn_fused");
         if (st != FTC_OK) return st;
     }
@@ -446,7 +455,7 @@ int32_t launch_agnn_fused(const ftc_csr &g, const ftc_windows &w, const void *H,
 #define FTC_FX(G)                                                                                                    \
     case G:                                                                                                          \
         hipLaunchKernelGGL(agnn_fused_fixup_kernel<G>, dim3(grid2), dim3(256), 0, s, g.n, n_ranges, g.row_ptr, carry, \
-                           tail_row, dp, D, out, ldo, odt, row_z, out32, ld32);                                      \
+                           tail_row, dp, D, out, ldo, odt, row_z, out32, ld32, r);                                   \
         break;
     switch (grp) {
         FTC_FX(1) FTC_FX(2) FTC_FX(4) FTC_FX(8) FTC_FX(16) FTC_FX(32) FTC_FX(64)

@@ -155,10 +155,14 @@ int32_t ftc_gcn_norm(const ftc_csr *g, const ftc_windows *w, float *vals, float 
     return launch_gcn_norm(*g, w, vals, dinv, static_cast<hipStream_t>(stream));
 }
 
+// What a call needs at least (`least`), or with room for the shorter ranges of small graphs and for odd widths: that is
+// what the *_workspace_bytes queries return; a call that gets less than that but at least the former runs with long ranges.
+static size_t spmm_ws(int32_t n, int32_t nnz, int32_t D, bool least) { return spmm_seg_ws(nnz, D, least) + flag_bytes(n); }
+
 size_t ftc_spmm_workspace_bytes(int32_t n, int32_t nnz, int32_t D)
 {
     if (n < 0 || nnz < 0 || D < 1) return 0;
-    return spmm_seg_ws(nnz, D) + flag_bytes(n);
+    return spmm_ws(n, nnz, D, false);
 }
 
 int32_t ftc_spmm(const ftc_csr *g, const ftc_windows *w, const float *vals, const void *X, int32_t ldx,
@@ -186,26 +190,36 @@ int32_t ftc_spmm(const ftc_csr *g, const ftc_windows *w, const float *vals, cons
                     "features with D a multiple of 8 (<= 256) and 16-byte aligned rows");
     // a graph without entries only has its output rows cleared, whatever the path
     const bool can_seg = seg_ok && g->nnz > 0, can_mfma = mfma_ok && g->nnz > 0;
+    hipStream_t hs = static_cast<hipStream_t>(stream);
     if (can_seg) {
-        const size_t need = ftc_spmm_workspace_bytes(g->n, g->nnz, D);
+        const size_t need = spmm_ws(g->n, g->nnz, D, true);
         if (!ws || ws_bytes < need)
             return fail(FTC_EWORKSPACE, "ftc_spmm: workspace of %zu bytes needed, %zu given", need,
                         ws ? ws_bytes : static_cast<size_t>(0));
         if (reinterpret_cast<uintptr_t>(ws) % 256 != 0)
             return fail(FTC_EALIGN, "ftc_spmm: workspace must be 256-byte aligned");
-        hipStream_t hs = static_cast<hipStream_t>(stream);
         uint8_t *flags = nullptr;
+        const size_t fb = flag_bytes(g->n);  // the flags take the end of the workspace, the carried pieces the rest
         const float reuse = path == FTC_PATH_MFMA ? 0.f : spmm_mfma_reuse(D);
         if (can_mfma && path != FTC_PATH_VALU && reuse >= 0.f) {
-            flags = reinterpret_cast<uint8_t *>(static_cast<char *>(ws) + spmm_seg_ws(g->nnz, D));
+            flags = reinterpret_cast<uint8_t *>(static_cast<char *>(ws) + (ws_bytes - fb) / 256 * 256);
             FTC_TRY(launch_classify(*g, *w, reuse, MFMA_MAX_WINDOW_EDGES, flags, hs));
         }
-        FTC_TRY(launch_spmm_seg(*g, *w, vals, X, ldx, x_dtype, D, out, ldo, out_dtype, epi, ws, flags, hs));
+        FTC_TRY(launch_spmm_seg(*g, *w, vals, X, ldx, x_dtype, D, out, ldo, out_dtype, epi, ws, (ws_bytes - fb) / 256 * 256,
+                                flags, hs));
         if (flags) return launch_spmm_mfma(*g, *w, vals, X, ldx, x_dtype, D, out, ldo, out_dtype, epi, flags, hs);
         return FTC_OK;
     }
-    return launch_spmm_rows(*g, vals, X, ldx, x_dtype, D, out, ldo, out_dtype, epi,
-                            static_cast<hipStream_t>(stream));
+    // Widths that are no multiple of a lane's piece, or rows that are not 16-byte aligned (7 classes, say): the edge-balanced
+    // kernels again, at element alignment, wherever the workspace holds their carried pieces.  The row-wise kernels below
+    // give a row to a thread per column, one after the other over its entries (fp32, 10 columns, power-law graph with
+    // 100 000 nodes: 305 us against 36).
+    if (w && g->nnz > 0 && ws && reinterpret_cast<uintptr_t>(ws) % 256 == 0 && ws_bytes >= spmm_ws(g->n, g->nnz, D, false)) {
+        const bool x16 = aligned16(X) && (static_cast<int64_t>(ldx) * elem_size(x_dtype)) % 16 == 0;
+        if ((x16 && spmm_lane_shape(x_dtype, D, ldx)) || spmm_ragged_ok(x_dtype, D))
+            return launch_spmm_seg(*g, *w, vals, X, ldx, x_dtype, D, out, ldo, out_dtype, epi, ws, ws_bytes, nullptr, hs);
+    }
+    return launch_spmm_rows(*g, vals, X, ldx, x_dtype, D, out, ldo, out_dtype, epi, hs);
 }
 
 // ftc_spmm for callers that can neither allocate nor hand over a workspace: the scratch memory of the
@@ -250,7 +264,7 @@ int32_t ftc_spmm_noalloc(const ftc_csr *g, const ftc_windows *w, const float *va
 {
     FTC_TRY(check_csr(g, "ftc_spmm_noalloc"));
     if (D < 1) return fail(FTC_EINVAL, "ftc_spmm_noalloc: need D >= 1");
-    const size_t need = ftc_spmm_workspace_bytes(g->n, g->nnz, D);
+    const size_t need = spmm_ws(g->n, g->nnz, D, true);
     if (need > NOALLOC_SCRATCH_BYTES)
         return fail(FTC_EWORKSPACE,
                     "ftc_spmm_noalloc: this graph and width need %zu bytes of scratch memory, the built-in buffer holds "
@@ -384,13 +398,18 @@ int32_t ftc_update_gemm(int32_t n, const void *X, int32_t ldx, int32_t dtype, in
 static int z_dtype_for(int dtype) { return dtype == FTC_F16 ? FTC_F16 : FTC_F32; }
 static int z_ld(int d_out, int zdt) { return zdt == FTC_F32 ? (d_out + 3) / 4 * 4 : (d_out + 7) / 8 * 8; }
 
-size_t ftc_gcn_layer_workspace_bytes(int32_t n, int32_t nnz, int32_t d_in, int32_t d_out)
+static size_t gcn_layer_ws(int32_t n, int32_t nnz, int32_t d_out, bool least)
 {
-    (void)d_in;
     if (n < 0 || nnz < 0 || d_out < 1) return 0;
     // sized for the fp32 intermediate, which covers the fp16 one
     const int ldz = z_ld(d_out, FTC_F32);
-    return align_up(static_cast<size_t>(n) * ldz * sizeof(float), 256) + ftc_spmm_workspace_bytes(n, nnz, d_out);
+    return align_up(static_cast<size_t>(n) * ldz * sizeof(float), 256) + spmm_ws(n, nnz, d_out, least);
+}
+
+size_t ftc_gcn_layer_workspace_bytes(int32_t n, int32_t nnz, int32_t d_in, int32_t d_out)
+{
+    (void)d_in;
+    return gcn_layer_ws(n, nnz, d_out, false);
 }
 
 int32_t ftc_gcn_layer(const ftc_csr *g, const ftc_windows *w, const float *vals, const float *dinv,
@@ -400,7 +419,7 @@ int32_t ftc_gcn_layer(const ftc_csr *g, const ftc_windows *w, const float *vals,
 {
     FTC_TRY(check_csr(g, "ftc_gcn_layer"));
     if (g->n == 0) return FTC_OK;
-    const size_t need = ftc_gcn_layer_workspace_bytes(g->n, g->nnz, d_in, d_out);
+    const size_t need = gcn_layer_ws(g->n, g->nnz, d_out, true);
     if (!ws || ws_bytes < need)
         return fail(FTC_EWORKSPACE, "ftc_gcn_layer: workspace of %zu bytes needed", need);
     if (reinterpret_cast<uintptr_t>(ws) % 256 != 0)
@@ -417,19 +436,21 @@ int32_t ftc_gcn_layer(const ftc_csr *g, const ftc_windows *w, const float *vals,
                     static_cast<char *>(ws) + zbytes, ws_bytes - zbytes, stream);
 }
 
-static size_t agnn_unfused_bytes(int32_t n, int32_t nnz, int32_t D)
+static size_t agnn_unfused_bytes(int32_t n, int32_t nnz, int32_t D, bool least)
 {
     return align_up(static_cast<size_t>(nnz) * sizeof(float), 256) +
            align_up(ftc_sddmm_workspace_bytes(n, nnz, D), 256) +
-           align_up(ftc_edge_softmax_workspace_bytes(n, nnz), 256) + ftc_spmm_workspace_bytes(n, nnz, D);
+           align_up(ftc_edge_softmax_workspace_bytes(n, nnz), 256) + spmm_ws(n, nnz, D, least);
 }
 
-size_t ftc_agnn_layer_workspace_bytes(int32_t n, int32_t nnz, int32_t D)
+static size_t agnn_layer_ws(int32_t n, int32_t nnz, int32_t D, bool least)
 {
     if (n < 0 || nnz < 0 || D < 1) return 0;
-    const size_t a = agnn_unfused_bytes(n, nnz, D), b = agnn_fused_ws(nnz, D);
+    const size_t a = agnn_unfused_bytes(n, nnz, D, least), b = agnn_fused_ws(nnz, D, least);
     return a > b ? a : b;
 }
+
+size_t ftc_agnn_layer_workspace_bytes(int32_t n, int32_t nnz, int32_t D) { return agnn_layer_ws(n, nnz, D, false); }
 
 int32_t ftc_agnn_layer(const ftc_csr *g, const ftc_windows *w, const void *H, int32_t ld, int32_t dtype,
                        int32_t D, float beta, void *out, int32_t ldo, int32_t out_dtype, float *edge_p, float *row_z,
@@ -441,7 +462,7 @@ int32_t ftc_agnn_layer(const ftc_csr *g, const ftc_windows *w, const void *H, in
     FTC_TRY(check_dense(out, ldo, out_dtype, D, "ftc_agnn_layer", "out"));
     if (out == H) return fail(FTC_EINVAL, "ftc_agnn_layer: out aliases H");
     if (w) FTC_TRY(check_windows(g, w, "ftc_agnn_layer", true));
-    const size_t need = ftc_agnn_layer_workspace_bytes(g->n, g->nnz, D);
+    const size_t need = agnn_layer_ws(g->n, g->nnz, D, true);
     if (!ws || ws_bytes < need)
         return fail(FTC_EWORKSPACE, "ftc_agnn_layer: workspace of %zu bytes needed", need);
     if (reinterpret_cast<uintptr_t>(ws) % 256 != 0)
@@ -466,7 +487,7 @@ int32_t ftc_agnn_layer(const ftc_csr *g, const ftc_windows *w, const void *H, in
     if (!edge_p && w && beta_ok && (g->nnz > 0 || keep) && path != FTC_PATH_MFMA && rows16 &&
         seg_shape(dtype, D, &vec, &lpr))
         return launch_agnn_fused(*g, *w, H, ld, dtype, D, beta, out, ldo, out_dtype, row_z, out_f32, ld_f32, p,
-                                 static_cast<hipStream_t>(stream));
+                                 ws_bytes, static_cast<hipStream_t>(stream));
     if (keep)
         return fail(FTC_EUNSUPPORTED,
                     "ftc_agnn_layer: |beta| < 43 is needed, and row_z and out_f32 come from the single-pass route only (window index, no edge_p, not "
@@ -586,12 +607,17 @@ int32_t ftc_update_gemm_backward(int32_t n, const void *X, int32_t ldx, int32_t 
     return FTC_OK;
 }
 
-size_t ftc_gcn_layer_backward_workspace_bytes(int32_t n, int32_t nnz, int32_t d_in, int32_t d_out)
+static size_t gcn_backward_ws(int32_t n, int32_t nnz, int32_t d_in, int32_t d_out, bool least)
 {
     if (n < 0 || nnz < 0 || d_in < 1 || d_out < 1) return 0;
     const size_t mat = align_up(static_cast<size_t>(n) * pad4(d_out) * sizeof(float), 256);
-    return 2 * mat + align_up(ftc_spmm_workspace_bytes(n, nnz, d_out), 256) + weight_grad_ws(n, d_in, d_out) +
+    return 2 * mat + align_up(spmm_ws(n, nnz, d_out, least), 256) + weight_grad_ws(n, d_in, d_out) +
            input_grad_ws(d_in, d_out);
+}
+
+size_t ftc_gcn_layer_backward_workspace_bytes(int32_t n, int32_t nnz, int32_t d_in, int32_t d_out)
+{
+    return gcn_backward_ws(n, nnz, d_in, d_out, false);
 }
 
 int32_t ftc_gcn_layer_backward(const ftc_csr *gT, const ftc_windows *wT, const float *valsT, const float *dinv,
@@ -607,7 +633,7 @@ int32_t ftc_gcn_layer_backward(const ftc_csr *gT, const ftc_windows *wT, const f
     if (dX) FTC_TRY(check_dense(dX, lddx, FTC_F32, d_in, "ftc_gcn_layer_backward", "dX"));
     if (!W || !dW) return fail(FTC_EINVAL, "ftc_gcn_layer_backward: W or dW is NULL");
     if (weight_grad_group(d_in, d_out) == 0) return fail(FTC_EUNSUPPORTED, "ftc_gcn_layer_backward: need d_out <= 504");
-    const size_t need = ftc_gcn_layer_backward_workspace_bytes(gT->n, gT->nnz, d_in, d_out);
+    const size_t need = gcn_backward_ws(gT->n, gT->nnz, d_in, d_out, true);
     if (!ws || ws_bytes < need)
         return fail(FTC_EWORKSPACE, "ftc_gcn_layer_backward: workspace of %zu bytes needed", need);
     if (reinterpret_cast<uintptr_t>(ws) % 256 != 0)
@@ -619,7 +645,8 @@ int32_t ftc_gcn_layer_backward(const ftc_csr *gT, const ftc_windows *wT, const f
     float *dP = reinterpret_cast<float *>(p);
     float *dZ = reinterpret_cast<float *>(p + mat);
     void *ws_spmm = p + 2 * mat;
-    const size_t spmm_bytes = align_up(ftc_spmm_workspace_bytes(n, gT->nnz, d_out), 256);
+    const bool least = ws_bytes < gcn_backward_ws(n, gT->nnz, d_in, d_out, false);
+    const size_t spmm_bytes = align_up(spmm_ws(n, gT->nnz, d_out, least), 256);
     void *ws_wg = p + 2 * mat + spmm_bytes;
     // dP = dY where the output was positive, rows scaled by dinv in the factored form
     FTC_TRY(launch_mask_scale(n, d_out, dY, lddy, Y, ldy, y_dtype, dinv, dP, ldp, hs));
@@ -633,15 +660,17 @@ int32_t ftc_gcn_layer_backward(const ftc_csr *gT, const ftc_windows *wT, const f
     return FTC_OK;
 }
 
-size_t ftc_agnn_layer_backward_workspace_bytes(int32_t n, int32_t nnz, int32_t D)
+static size_t agnn_backward_ws(int32_t n, int32_t nnz, int32_t D, bool least)
 {
     if (n < 0 || nnz < 0 || D < 1) return 0;
     const size_t edge = align_up(static_cast<size_t>(nnz) * sizeof(float), 256);
     return 3 * edge + align_up(static_cast<size_t>(n) * sizeof(float), 256) +
            2 * align_up(static_cast<size_t>(n) * pad4(D) * sizeof(float), 256) +
-           align_up(ftc_sddmm_workspace_bytes(n, nnz, D), 256) + align_up(ftc_spmm_workspace_bytes(n, nnz, D), 256) +
+           align_up(ftc_sddmm_workspace_bytes(n, nnz, D), 256) + align_up(spmm_ws(n, nnz, D, least), 256) +
            align_up(softmax_seg_ws(n, nnz), 256) + edge_dot_ws();
 }
+
+size_t ftc_agnn_layer_backward_workspace_bytes(int32_t n, int32_t nnz, int32_t D) { return agnn_backward_ws(n, nnz, D, false); }
 
 int32_t ftc_agnn_layer_backward(const ftc_csr *g, const ftc_windows *w, const int32_t *T, const void *H, int32_t ld,
                                 int32_t dtype, int32_t D, float beta, const float *p, const void *dY, int32_t lddy,
@@ -657,7 +686,7 @@ int32_t ftc_agnn_layer_backward(const ftc_csr *g, const ftc_windows *w, const in
     if (g->nnz > 0 && (!T || !p)) return fail(FTC_EINVAL, "ftc_agnn_layer_backward: T or p is NULL");
     if (dH == H || dH == dY) return fail(FTC_EINVAL, "ftc_agnn_layer_backward: dH aliases an input");
     if (ld != lddy) return fail(FTC_EINVAL, "ftc_agnn_layer_backward: H and dY need the same leading dimension");
-    const size_t need = ftc_agnn_layer_backward_workspace_bytes(g->n, g->nnz, D);
+    const size_t need = agnn_backward_ws(g->n, g->nnz, D, true);
     if (!ws || ws_bytes < need)
         return fail(FTC_EWORKSPACE, "ftc_agnn_layer_backward: workspace of %zu bytes needed", need);
     if (reinterpret_cast<uintptr_t>(ws) % 256 != 0)
@@ -673,7 +702,7 @@ int32_t ftc_agnn_layer_backward(const ftc_csr *g, const ftc_windows *w, const in
     float *q = reinterpret_cast<float *>(q8); q8 += align_up(static_cast<size_t>(n) * ldq * sizeof(float), 256);
     float *agg = reinterpret_cast<float *>(q8); q8 += align_up(static_cast<size_t>(n) * ldq * sizeof(float), 256);
     void *ws_sd = q8; const size_t sd = align_up(ftc_sddmm_workspace_bytes(n, nnz, D), 256); q8 += sd;
-    void *ws_sp = q8; const size_t sp = align_up(ftc_spmm_workspace_bytes(n, nnz, D), 256); q8 += sp;
+    void *ws_sp = q8; const size_t sp = align_up(spmm_ws(n, nnz, D, ws_bytes < agnn_backward_ws(n, nnz, D, false)), 256); q8 += sp;
     void *ws_sm = q8; const size_t sm = align_up(softmax_seg_ws(n, nnz), 256); q8 += sm;
     void *ws_dot = q8;
     FTC_TRY(launch_row_rnorm(n, H, ld, dtype, D, rinv, hs));
@@ -696,7 +725,7 @@ int32_t ftc_agnn_layer_backward(const ftc_csr *g, const ftc_windows *w, const in
 size_t ftc_agnn_layer_backward_fused_workspace_bytes(int32_t n, int32_t nnz, int32_t D)
 {
     if (n < 0 || nnz < 0 || D < 1) return 0;
-    return agnn_backward_fused_ws(n, nnz, D);
+    return agnn_backward_fused_ws(n, nnz, D, false);
 }
 
 int32_t ftc_agnn_layer_backward_fused(const ftc_csr *g, const ftc_windows *w, const void *H, int32_t ld, int32_t dtype,
@@ -723,13 +752,13 @@ int32_t ftc_agnn_layer_backward_fused(const ftc_csr *g, const ftc_windows *w, co
         return fail(FTC_EUNSUPPORTED,
                     "ftc_agnn_layer_backward_fused: needs |beta| < 43, 16-byte aligned rows and a width the "
                     "edge-balanced kernels cover with 2 * D <= 256 padded slots; use ftc_agnn_layer_backward");
-    const size_t need = agnn_backward_fused_ws(g->n, g->nnz, D);
+    const size_t need = agnn_backward_fused_ws(g->n, g->nnz, D, true);
     if (!ws || ws_bytes < need)
         return fail(FTC_EWORKSPACE, "ftc_agnn_layer_backward_fused: workspace of %zu bytes needed", need);
     if (reinterpret_cast<uintptr_t>(ws) % 256 != 0)
         return fail(FTC_EALIGN, "ftc_agnn_layer_backward_fused: workspace must be 256-byte aligned");
     FTC_TRY(launch_agnn_backward_fused(*g, *w, H, dY, ld, dtype, D, beta, row_z, Y, ldy, y_dtype, dH, lddh, dh_dtype,
-                                       dbeta, ws, static_cast<hipStream_t>(stream)));
+                                       dbeta, ws, ws_bytes, static_cast<hipStream_t>(stream)));
     if (pattern_flag)  // not a symmetric pattern: NaN instead of a gradient of nothing
         return launch_poison_if_flag(pattern_flag, g->n, D, dH, lddh, dh_dtype, dbeta, static_cast<hipStream_t>(stream));
     return FTC_OK;

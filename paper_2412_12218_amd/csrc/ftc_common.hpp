@@ -10,7 +10,9 @@
 namespace ftc {
 
 constexpr int WAVE = 64;
-constexpr int SEG_R = 512;  // edges per wave of the edge-balanced kernels (SpMM, fused AGNN forward / backward)
+// Edges per wave of the edge-balanced kernels (SpMM, fused AGNN forward / backward): SEG_R on graphs that fill the chip with
+// such ranges, fewer on smaller ones (seg_range()).
+constexpr int SEG_R = 512;
 
 // ---- host side -------------------------------------------------------------------------------
 void set_error(const char *fmt, ...);
@@ -23,6 +25,21 @@ inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 
 
 // ceil(a / b) for non-negative a up to INT32_MAX (the sum a + b - 1 would not fit)
 inline int ceil_div(int a, int b) { return static_cast<int>((static_cast<int64_t>(a) + b - 1) / b); }
+
+// Edges per wave for a graph of nnz entries.  A wave's groups of lanes walk their runs one batch of four gathers after the
+// other, so a range of R edges is a chain of R / 64 (rows of four lanes) to R / 8 batches, and with too few ranges the
+// chip waits for it; with many ranges what counts is the work per cut row, which long ranges have less of.  The two lines
+// are where the measured times cross (us at R = 512 / 256 / 128, fp16, 32 columns):
+//   entries               9 thousand       0.6 M            1.5 M            3.8 M            8 M
+//   SpMM                  29 / 20 / 16     33 / 24 / 21     41 / 33 / 38     76 / 68 / 71     100 / 98 / 119
+//   AGNN layer            30 / 20 / 16     33 / 26 / 24     41 / 41 / 45     70 / 70 / 85     102 / 114 / 150
+//   its backward pass     41 / 32 / 29     58 / 47 / 49     73 / 77 / 80     138 / 141 / 160  208 / 217 / 256
+struct SegLines {
+    int below_128, below_256;  // entry counts up to which ranges of 128, of 256 edges are taken
+};
+constexpr SegLines SEG_SPMM = {1 << 20, 1 << 23}, SEG_AGNN = {1 << 20, 1 << 21}, SEG_AGNN_BACKWARD = {1 << 19, 1 << 20};
+inline int seg_range(int nnz, const SegLines &l) { return nnz < l.below_128 ? 128 : nnz < l.below_256 ? 256 : SEG_R; }
+inline int64_t seg_count(int nnz, int r) { return (static_cast<int64_t>(nnz) + r - 1) / r; }
 
 // Epilogue of the kernels that produce dense rows: out = act(scale[row] * value), scale optional.
 struct Epi {
@@ -53,26 +70,30 @@ int32_t launch_gemm(int n, const void *X, int ldx, int dt, int d_in, const void 
 int32_t launch_gcn_norm(const ftc_csr &g, const ftc_windows *w, float *vals, float *dinv, hipStream_t s);
 int32_t launch_validate(const ftc_csr &g, int32_t *flag, hipStream_t s);
 bool seg_shape(int dtype, int D, int *vec, int *lpr);
-size_t spmm_seg_ws(int nnz, int D);
+// Workspaces of the edge-balanced kernels: `least` is what they need with ranges of SEG_R edges (of 1024 or 512 in the kernel
+// for narrow rows), otherwise room for the shorter ranges of small graphs; a launcher takes the shorter ranges when
+// the `ws_bytes` it is given hold them.
+bool spmm_ragged_ok(int dtype, int D);
+size_t spmm_seg_ws(int nnz, int D, bool least);
 bool spmm_lane_shape(int xdt, int D, int ldx);
-size_t spmm_lane_ws(int nnz);
+size_t spmm_lane_ws(int nnz, bool least);
 int32_t launch_spmm_lane(const ftc_csr &g, const ftc_windows &w, const float *vals, const void *X, int ldx, int xdt,
-                         int D, void *out, int ldo, int odt, Epi epi, void *ws, hipStream_t s);
+                         int D, void *out, int ldo, int odt, Epi epi, void *ws, size_t ws_bytes, hipStream_t s);
 int32_t launch_spmm_seg(const ftc_csr &g, const ftc_windows &w, const float *vals, const void *X, int ldx,
-                        int xdt, int D, void *out, int ldo, int odt, Epi epi, void *ws, const uint8_t *dense,
-                        hipStream_t s);
+                        int xdt, int D, void *out, int ldo, int odt, Epi epi, void *ws, size_t ws_bytes,
+                        const uint8_t *dense, hipStream_t s);
 int32_t launch_sddmm_edges(const ftc_csr &g, const ftc_windows &w, const void *X, const void *Y, int ld, int dt,
                            int D, const float *rs, const float *cs, float alpha, float *out, const uint8_t *dense,
                            bool cosine, hipStream_t s);
-size_t agnn_fused_ws(int nnz, int D);
+size_t agnn_fused_ws(int nnz, int D, bool least);
 int32_t launch_agnn_fused(const ftc_csr &g, const ftc_windows &w, const void *H, int ld, int dt, int D,
                           float beta, void *out, int ldo, int odt, float *row_z, float *out32, int ld32, void *ws,
-                          hipStream_t s);
+                          size_t ws_bytes, hipStream_t s);
 bool agnn_backward_fused_shape(int dtype, int D);
-size_t agnn_backward_fused_ws(int n, int nnz, int D);
+size_t agnn_backward_fused_ws(int n, int nnz, int D, bool least);
 int32_t launch_agnn_backward_fused(const ftc_csr &g, const ftc_windows &w, const void *H, const void *dY, int ld, int dt,
                                    int D, float beta, const float *row_z, const void *Y, int ldy, int ydt, void *dH,
-                                   int lddh, int dh_dt, float *dbeta, void *ws, hipStream_t s);
+                                   int lddh, int dh_dt, float *dbeta, void *ws, size_t ws_bytes, hipStream_t s);
 bool mfma_shape_ok(int dtype, int D);
 int32_t launch_classify(const ftc_csr &g, const ftc_windows &w, float reuse, int max_edges, uint8_t *flags,
                         hipStream_t s);
@@ -323,6 +344,40 @@ __device__ __forceinline__ void store_vec(void *base, int64_t idx, int dtype, co
             if constexpr (NV == 8) *reinterpret_cast<uint4 *>(q) = make_uint4(w[0], w[1], w[2], w[3]);
             else if constexpr (NV == 4) *reinterpret_cast<uint2 *>(q) = make_uint2(w[0], w[1]);
             else *reinterpret_cast<uint32_t *>(q) = w[0];
+        }
+    }
+}
+
+// Loads and stores of a 16-byte piece that is only aligned to its elements (a global access needs no more).
+template <class T>
+__device__ __forceinline__ void load_raw_any(const void *base, int64_t idx, RawVec<T, T::VEC> &r)
+{
+    if constexpr (T::BYTES == 4) {
+        typedef uint32_t u4 __attribute__((ext_vector_type(4), aligned(4)));
+        const u4 v = *reinterpret_cast<const u4 *>(static_cast<const float *>(base) + idx);
+        r.w[0] = v.x; r.w[1] = v.y; r.w[2] = v.z; r.w[3] = v.w;
+    } else {
+        typedef uint32_t u4 __attribute__((ext_vector_type(4), aligned(2)));
+        const u4 v = *reinterpret_cast<const u4 *>(static_cast<const uint16_t *>(base) + idx);
+        r.w[0] = v.x; r.w[1] = v.y; r.w[2] = v.z; r.w[3] = v.w;
+    }
+}
+template <int NV>  // 4 or 8 consecutive floats in the run-time output dtype
+__device__ __forceinline__ void store_vec_any(void *base, int64_t idx, int dtype, const float (&f)[NV])
+{
+    if (dtype == FTC_F32) {
+        typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
+#pragma unroll
+        for (int k = 0; k < NV / 4; ++k)
+            *reinterpret_cast<f4 *>(static_cast<float *>(base) + idx + 4 * k) = f4{f[4 * k], f[4 * k + 1], f[4 * k + 2], f[4 * k + 3]};
+    } else {
+        typedef uint16_t h4 __attribute__((ext_vector_type(4), aligned(2)));
+#pragma unroll
+        for (int k = 0; k < NV / 4; ++k) {
+            h4 v;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] = static_cast<uint16_t>(dtype == FTC_F16 ? f32_to_f16_bits(f[4 * k + j]) : f32_to_bf16_bits(f[4 * k + j]));
+            *reinterpret_cast<h4 *>(static_cast<uint16_t *>(base) + idx + 4 * k) = v;
         }
     }
 }

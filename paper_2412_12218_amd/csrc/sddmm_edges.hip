@@ -2,7 +2,7 @@
 //
 // The output has one value per stored entry (`EdgeValList`), so equal numbers of EDGES per wave
 // balance the work however skewed the rows are; edge_to_row of the window index gives each
-// edge its row.  A wave stages the (column, row) pairs of SEG_R consecutive edges in LDS, groups
+// edge its row.  A wave stages the (column, row) pairs of SD_R consecutive edges in LDS, groups
 // of LPR lanes walk contiguous runs of them, SD_B edges at a time: SD_B independent gathers of
 // Y rows in flight per lane, the X row is re-read only when the row changes.  Dot products are
 // reduced inside the group with DPP lane shuffles, parked in LDS, and written back scaled
@@ -11,7 +11,9 @@
 
 namespace ftc {
 
-constexpr int SD_R = 512;  // edges per wave
+// Edges per wave.  Nothing is carried from range to range here, so short ranges cost little: 128 against 512 edges take 12 / 18
+// us at 9 thousand entries, 18 / 27 at 1.5 M, 127 / 139 at 16 M and 266 / 277 at 32 M (R-MAT, fp16, 32 columns).
+constexpr int SD_R = 128;
 constexpr int SD_B = 4;    // edges per batch
 
 bool seg_shape(int dtype, int D, int *vec, int *lpr);  // spmm_seg.hip: same lane layout

@@ -3,7 +3,7 @@
 //
 // The edge-balanced kernel of spmm_seg.hip puts four lanes on a row; with rows this narrow a lane
 // then loads 4 or 8 bytes per edge and the per-edge bookkeeping outweighs the arithmetic.  Here a
-// SLOT of LPE lanes owns SL_L consecutive edges, and each of its lanes loads one 16-byte piece of
+// SLOT of LPE lanes owns 16 (small graphs: 4) consecutive edges, and each of its lanes loads one 16-byte piece of
 // every row (LPE = 1: rows of 16 bytes; LPE = 2: rows of 32 bytes, the two halves in neighbouring
 // lanes, so that a load instruction touches one contiguous segment per edge -- two loads per lane
 // for the two halves were measured slower than the four-lane layout, 0.35 against 0.30 ms on the
@@ -19,9 +19,10 @@
 
 namespace ftc {
 
-constexpr int SL_L = 16;         // consecutive edges per lane
-constexpr int SL_R = 64 * SL_L;  // edges per wave
-constexpr int SL_B = 8;          // gathers issued together
+// Consecutive edges per lane: 16, or 4 on graphs whose ranges of 1024 / 512 edges would leave the chip idle.  fp16, 8 columns,
+// us with 16 / 4: 20 / 13 at 9 thousand entries, 20 / 14 at 0.6 M, 23 / 20 at 1.5 M, 35 / 37 at 3.8 M.
+constexpr int SL_LONG = 16, SL_SHORT = 4;
+static int lane_edges(int nnz) { return nnz >= (1 << 21) ? SL_LONG : SL_SHORT; }
 
 template <int CTRL, int ROW_MASK>
 __device__ __forceinline__ int sl_dpp(int v)
@@ -80,7 +81,7 @@ __device__ __forceinline__ void wave_segmented_sum_slots(float (&x)[N], int head
 // LPE: lanes per edge (1: rows of one 16-byte piece; 2: rows of two pieces, neighbouring lanes load the two
 // halves of a row, so a load instruction still touches one contiguous 32-byte segment per edge).
 // VALS = false: all edge values are one.
-template <class T, int LPE, bool VALS>
+template <class T, int LPE, bool VALS, int SL_L>
 __global__ __launch_bounds__(256) void spmm_lane_kernel(int nnz, int n_ranges, const int *__restrict__ row_ptr,
                                                         const int *__restrict__ col_idx,
                                                         const int *__restrict__ edge_to_row,
@@ -91,7 +92,8 @@ __global__ __launch_bounds__(256) void spmm_lane_kernel(int nnz, int n_ranges, c
 {
     constexpr int V = T::VEC, DP = V, NV = 1;  // a lane holds one 16-byte piece of its rows
     constexpr int DPT = V * LPE;               // padded row width (carry rows)
-    constexpr int RANGE = SL_R / LPE;          // edges per wave
+    constexpr int RANGE = 64 * SL_L / LPE;     // edges per wave
+    constexpr int SL_B = SL_L < 8 ? SL_L : 8;  // gathers issued together
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int slot = lane / LPE, piece = lane % LPE;
     const int v = xcd_chunked_block(blockIdx.x, gridDim.x) * 4 + wave;
@@ -260,20 +262,25 @@ bool spmm_lane_shape(int xdt, int D, int ldx)
     return D >= 1 && lpe <= 2 && ldx >= lpe * per;
 }
 
-size_t spmm_lane_ws(int nnz)
+static size_t lane_carry_ws(int nnz, int range, int dp)
 {
-    if (nnz == 0) return 0;
-    const size_t n_ranges = (static_cast<size_t>(nnz) + SL_R / 2 - 1) / (SL_R / 2);  // the shorter ranges of LPE = 2
-    return align_up(n_ranges * 2 * 16 * sizeof(float), 256) + align_up(n_ranges * 2 * sizeof(int), 256);
+    const size_t n_ranges = static_cast<size_t>(seg_count(nnz, range));
+    return align_up(n_ranges * 2 * dp * sizeof(float), 256) + align_up(n_ranges * 2 * sizeof(int), 256);
 }
 
-template <class T>
+size_t spmm_lane_ws(int nnz, bool least)
+{
+    if (nnz == 0) return 0;
+    return lane_carry_ws(nnz, 64 * (least ? SL_LONG : lane_edges(nnz)) / 2, 16);  // the shorter ranges of LPE = 2
+}
+
+template <class T, int L>
 static void launch_lane_t(int lpe, unsigned grid, hipStream_t s, int nnz, int n_ranges, const ftc_csr &g, const int *e2r,
                           const float *vals, const void *X, int ldx, int D, void *out, int ldo, int odt, Epi epi,
                           float *carry, int *tail_row, int idx_vec, int out_vec)
 {
 #define FTC_LANE(LPE, VALS)                                                                                         \
-    hipLaunchKernelGGL((spmm_lane_kernel<T, LPE, VALS>), dim3(grid), dim3(256), 0, s, nnz, n_ranges, g.row_ptr, g.col_idx, e2r, \
+    hipLaunchKernelGGL((spmm_lane_kernel<T, LPE, VALS, L>), dim3(grid), dim3(256), 0, s, nnz, n_ranges, g.row_ptr, g.col_idx, e2r, \
                        vals, X, ldx, D, out, ldo, odt, epi, carry, tail_row, idx_vec, out_vec)
     if (lpe == 1) {
         if (vals) FTC_LANE(1, true);
@@ -286,12 +293,15 @@ static void launch_lane_t(int lpe, unsigned grid, hipStream_t s, int nnz, int n_
 }
 
 // Caller has checked: window index present, spmm_lane_shape(), rows of X 16-byte aligned, workspace
-// of spmm_lane_ws() bytes.
+// of spmm_lane_ws(.., least) bytes.
 int32_t launch_spmm_lane(const ftc_csr &g, const ftc_windows &w, const float *vals, const void *X, int ldx, int xdt,
-                         int D, void *out, int ldo, int odt, Epi epi, void *ws, hipStream_t s)
+                         int D, void *out, int ldo, int odt, Epi epi, void *ws, size_t ws_bytes, hipStream_t s)
 {
     const int per = xdt == FTC_F32 ? 4 : 8;
-    const int lpe = (D + per - 1) / per, dp = per * lpe, range = SL_R / lpe;
+    const int lpe = (D + per - 1) / per, dp = per * lpe;
+    const int short_range = 64 * lane_edges(g.nnz) / lpe;
+    const int range = ws_bytes >= lane_carry_ws(g.nnz, short_range, dp) ? short_range : 64 * SL_LONG / lpe;
+    const bool full = range == 64 * SL_LONG / lpe;
     const int n_ranges = ceil_div(g.nnz, range);
     float *carry = static_cast<float *>(ws);
     int *tail_row = reinterpret_cast<int *>(static_cast<char *>(ws) +
@@ -301,14 +311,26 @@ int32_t launch_spmm_lane(const ftc_csr &g, const ftc_windows &w, const float *va
     if (n_ranges > 0) {
         const unsigned grid = static_cast<unsigned>((n_ranges + 3) / 4);
         if (xdt == FTC_F32)
-            launch_lane_t<F32>(lpe, grid, s, g.nnz, n_ranges, g, w.edge_to_row, vals, X, ldx, D, out, ldo, odt, epi, carry,
+            {
+                if (full) launch_lane_t<F32, SL_LONG>(lpe, grid, s, g.nnz, n_ranges, g, w.edge_to_row, vals, X, ldx, D, out, ldo, odt, epi, carry,
                                tail_row, idx_vec, out_vec);
+                else launch_lane_t<F32, SL_SHORT>(lpe, grid, s, g.nnz, n_ranges, g, w.edge_to_row, vals, X, ldx, D, out, ldo, odt, epi, carry,
+                               tail_row, idx_vec, out_vec);
+            }
         else if (xdt == FTC_F16)
-            launch_lane_t<F16>(lpe, grid, s, g.nnz, n_ranges, g, w.edge_to_row, vals, X, ldx, D, out, ldo, odt, epi, carry,
+            {
+                if (full) launch_lane_t<F16, SL_LONG>(lpe, grid, s, g.nnz, n_ranges, g, w.edge_to_row, vals, X, ldx, D, out, ldo, odt, epi, carry,
                                tail_row, idx_vec, out_vec);
+                else launch_lane_t<F16, SL_SHORT>(lpe, grid, s, g.nnz, n_ranges, g, w.edge_to_row, vals, X, ldx, D, out, ldo, odt, epi, carry,
+                               tail_row, idx_vec, out_vec);
+            }
         else
-            launch_lane_t<BF16>(lpe, grid, s, g.nnz, n_ranges, g, w.edge_to_row, vals, X, ldx, D, out, ldo, odt, epi, carry,
+            {
+                if (full) launch_lane_t<BF16, SL_LONG>(lpe, grid, s, g.nnz, n_ranges, g, w.edge_to_row, vals, X, ldx, D, out, ldo, odt, epi, carry,
                                 tail_row, idx_vec, out_vec);
+                else launch_lane_t<BF16, SL_SHORT>(lpe, grid, s, g.nnz, n_ranges, g, w.edge_to_row, vals, X, ldx, D, out, ldo, odt, epi, carry,
+                                tail_row, idx_vec, out_vec);
+            }
         const int32_t st = launch_status("spmm_lane");
         if (st != FTC_OK) return st;
     }

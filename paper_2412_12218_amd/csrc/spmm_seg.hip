@@ -5,8 +5,8 @@
 // EDGES instead.  The window index supplies what makes that possible without searching:
 // edge_to_row (`edgeToRow`) tells every edge its output row.
 //
-//   - A wave owns SEG_R consecutive edges.  Their (column, value, row) triples are loaded once,
-//     coalesced, into LDS.
+//   - A wave owns R consecutive edges (512; 256 or 128 on small graphs, seg_range()).  Their (column, value, row)
+//     triples are loaded once, coalesced, into LDS.
 //   - The wave is cut into groups of LPR lanes; a group walks a contiguous run of the wave's
 //     edges, SEG_B at a time (SEG_B independent 16-byte gathers of X rows in flight per lane),
 //     and accumulates in registers while the row stays the same.
@@ -45,21 +45,62 @@ bool seg_shape(int dtype, int D, int *vec, int *lpr)
     return false;
 }
 
-size_t spmm_seg_ws(int nnz, int D)
+// The same for any width and any alignment: 16-byte pieces at element alignment; where the width is no multiple of a
+// piece the last lane's piece is moved back to end with the row (it then shares columns with its neighbour, both hold
+// the same sums).  Rows of at least one piece.
+static bool seg_shape_ragged(int dtype, int D, int *vec, int *lpr)
+{
+    const int v = dtype == FTC_F32 ? 4 : 8;
+    const int l = pow2_ceil((D + v - 1) / v);
+    if (D < v || l > 32) return false;
+    *vec = v;
+    *lpr = l < 4 ? 4 : l;
+    return true;
+}
+
+bool spmm_ragged_ok(int dtype, int D)
+{
+    int vec, lpr;
+    return seg_shape_ragged(dtype, D, &vec, &lpr);
+}
+
+static size_t seg_carry_ws(int nnz, int r, int dp)
+{
+    const size_t n_ranges = static_cast<size_t>(seg_count(nnz, r));
+    return align_up(n_ranges * 2 * dp * sizeof(float), 256) + align_up(n_ranges * 2 * sizeof(int), 256);
+}
+
+// Edges per wave for rows of dp slots: as seg_range() says, as long as the carried pieces stay below 32 MiB (they then fit
+// the built-in buffer of ftc_spmm_noalloc too, whose results are those of ftc_spmm bit for bit).
+static int spmm_range(int nnz, int dp)
+{
+    int r = seg_range(nnz, SEG_SPMM);
+    while (r < SEG_R && seg_carry_ws(nnz, r, dp) > (static_cast<size_t>(32) << 20)) r *= 2;
+    return r;
+}
+
+size_t spmm_seg_ws(int nnz, int D, bool least)
 {
     int vec, lpr, dp = 0;
-    if (seg_shape(FTC_F32, D, &vec, &lpr)) dp = vec * lpr;
-    if (seg_shape(FTC_F16, D, &vec, &lpr) && vec * lpr > dp) dp = vec * lpr;
-    if (dp == 0 || nnz == 0) return 0;
-    const size_t n_ranges = (static_cast<size_t>(nnz) + SEG_R - 1) / SEG_R;
-    const size_t seg = align_up(n_ranges * 2 * dp * sizeof(float), 256) + align_up(n_ranges * 2 * sizeof(int), 256);
-    const size_t lane = D <= 16 ? spmm_lane_ws(nnz) : 0;  // narrow rows may take the lane-per-edge kernel
+    if (nnz == 0) return 0;
+    size_t seg = 0;
+    for (const int dt : {FTC_F32, FTC_F16}) {
+        int w = 0;
+        if (seg_shape(dt, D, &vec, &lpr)) w = vec * lpr;
+        if (!least && seg_shape_ragged(dt, D, &vec, &lpr) && vec * lpr > w) w = vec * lpr;
+        if (w == 0) continue;
+        const size_t need = seg_carry_ws(nnz, least ? SEG_R : spmm_range(nnz, w), w);
+        seg = need > seg ? need : seg;
+        dp = w > dp ? w : dp;
+    }
+    if (dp == 0 && (least || D > 16)) return 0;
+    const size_t lane = D <= 16 ? spmm_lane_ws(nnz, least) : 0;  // narrow rows may take the lane-per-edge kernel
     return seg > lane ? seg : lane;
 }
 
 // VALS = false: all edge values are one (vals == NULL): nothing is staged or multiplied for them, which
-// also cuts the LDS footprint by a third (more workgroups per CU).
-template <class T, int VEC, int LPR, bool VALS>
+// also cuts the LDS footprint by a third (more workgroups per CU).  RAGGED: any width from one piece on, any alignment.
+template <class T, int VEC, int LPR, bool VALS, int R, bool RAGGED>
 __global__ __launch_bounds__(256) void spmm_seg_kernel(int nnz, int n_ranges, const int *__restrict__ row_ptr,
                                                        const int *__restrict__ col_idx,
                                                        const int *__restrict__ edge_to_row,
@@ -70,8 +111,8 @@ __global__ __launch_bounds__(256) void spmm_seg_kernel(int nnz, int n_ranges, co
                                                        const uint8_t *__restrict__ dense)
 {
     constexpr int NG = 64 / LPR;      // groups per wave
-    constexpr int RUN = SEG_R / NG;   // edges per group
-    constexpr int RP = SEG_R + NG;    // one pad word per run keeps the groups on different LDS banks
+    constexpr int RUN = R / NG;       // edges per group
+    constexpr int RP = R + NG;        // one pad word per run keeps the groups on different LDS banks
     constexpr int DP = LPR * VEC;     // padded feature width
     static_assert(RUN % SEG_B == 0, "runs are whole batches");
     constexpr int IDX_WORDS = 4 * (VALS ? 3 : 2) * RP;
@@ -87,12 +128,12 @@ __global__ __launch_bounds__(256) void spmm_seg_kernel(int nnz, int n_ranges, co
 
     const int v = xcd_chunked_block(blockIdx.x, gridDim.x) * 4 + wave;
     const bool active = v < n_ranges;
-    const int base = active ? v * SEG_R : 0;
-    const int n_valid = active ? min(SEG_R, nnz - base) : 0;
-    int rows[SEG_R / 64];
-    const bool from_starts = n_valid == SEG_R && rows_from_starts<SEG_R>(row_ptr, edge_to_row, base, lane, rows);
+    const int base = active ? v * R : 0;
+    const int n_valid = active ? min(R, nnz - base) : 0;
+    int rows[R / 64];
+    const bool from_starts = n_valid == R && rows_from_starts<R>(row_ptr, edge_to_row, base, lane, rows);
 #pragma unroll
-    for (int j = 0; j < SEG_R / 64; ++j) {
+    for (int j = 0; j < R / 64; ++j) {
         const int i = j * 64 + lane;
         if (i < n_valid) {
             const int p = i + i / RUN;
@@ -104,15 +145,16 @@ __global__ __launch_bounds__(256) void spmm_seg_kernel(int nnz, int n_ranges, co
         }
     }
     const int prev_row = (active && base > 0) ? edge_to_row[base - 1] : -1;
-    const int next_row = (active && n_valid == SEG_R && base + SEG_R < nnz) ? edge_to_row[base + SEG_R] : -1;
+    const int next_row = (active && n_valid == R && base + R < nnz) ? edge_to_row[base + R] : -1;
     // row of the first edge after the NEXT range: tells whether a row left open here ends there
-    const int far_row = (active && static_cast<int64_t>(base) + 2 * SEG_R < nnz) ? edge_to_row[base + 2 * SEG_R] : -1;
+    const int far_row = (active && static_cast<int64_t>(base) + 2 * R < nnz) ? edge_to_row[base + 2 * R] : -1;
     __syncthreads();
 
     const int rs = g * RUN;
     const int re = min(rs + RUN, n_valid);
     const bool has = rs < n_valid;
     const bool live = sub * VEC < D;
+    const int col0 = RAGGED ? min(sub * VEC, D - VEC) : sub * VEC;  // first column of this lane's piece
     float acc[VEC], hacc[VEC];
 #pragma unroll
     for (int j = 0; j < VEC; ++j) { acc[j] = 0.f; hacc[j] = 0.f; }
@@ -125,7 +167,8 @@ __global__ __launch_bounds__(256) void spmm_seg_kernel(int nnz, int n_ranges, co
             const float f = epi.factor(row);
 #pragma unroll
             for (int j = 0; j < VEC; ++j) o[j] = epi.apply(f, acc[j]);
-            store_vec_nt<VEC>(out, static_cast<int64_t>(row) * ldo + sub * VEC, odt, o);
+            if constexpr (RAGGED) store_vec_any<VEC>(out, static_cast<int64_t>(row) * ldo + col0, odt, o);
+            else store_vec_nt<VEC>(out, static_cast<int64_t>(row) * ldo + col0, odt, o);
         }
     };
 
@@ -148,8 +191,12 @@ __global__ __launch_bounds__(256) void spmm_seg_kernel(int nnz, int n_ranges, co
             }
 #pragma unroll
             for (int k = 0; k < SEG_B; ++k) {
-                if (r[k] >= 0 && c[k] >= 0 && live) load_raw<T, VEC>(X, static_cast<int64_t>(c[k]) * ldx + sub * VEC, x[k]);
-                else zero_raw(x[k]);
+                if (r[k] >= 0 && c[k] >= 0 && live) {
+                    if constexpr (RAGGED) load_raw_any<T>(X, static_cast<int64_t>(c[k]) * ldx + col0, x[k]);
+                    else load_raw<T, VEC>(X, static_cast<int64_t>(c[k]) * ldx + col0, x[k]);
+                } else {
+                    zero_raw(x[k]);
+                }
             }
 #pragma unroll
             for (int k = 0; k < SEG_B; ++k) {
@@ -192,13 +239,13 @@ __global__ __launch_bounds__(256) void spmm_seg_kernel(int nnz, int n_ranges, co
     __syncthreads();  // every wave is done with the staged indices: the LDS is reused for partials
 
     float *part = reinterpret_cast<float *>(smem) + wave * 2 * NG * DP;
-    if (have_head) {
+    if (have_head && (!RAGGED || live)) {
 #pragma unroll
-        for (int j = 0; j < VEC; ++j) part[(2 * g) * DP + sub * VEC + j] = hacc[j];
+        for (int j = 0; j < VEC; ++j) part[(2 * g) * DP + col0 + j] = hacc[j];
     }
-    if (have_tail) {
+    if (have_tail && (!RAGGED || live)) {
 #pragma unroll
-        for (int j = 0; j < VEC; ++j) part[(2 * g + 1) * DP + sub * VEC + j] = acc[j];
+        for (int j = 0; j < VEC; ++j) part[(2 * g + 1) * DP + col0 + j] = acc[j];
     }
     if (sub == 0) {
         s_meta[wave][0][g] = have_head ? head_row : -1;
@@ -351,67 +398,83 @@ int32_t launch_seg_fixup(int n, int n_ranges, const int *row_ptr, const float *c
     return launch_status(what);
 }
 
-template <class T>
-static void launch_seg_t(int vec, int lpr, unsigned grid, hipStream_t s, int nnz, int n_ranges,
-                         const ftc_csr &g, const int *e2r, const float *vals, const void *X, int ldx, int D,
-                         void *out, int ldo, int odt, Epi epi, float *carry, int *tail_row, const uint8_t *dense)
+template <class T, int R>
+static void launch_seg_t(int vec, int lpr, bool ragged, hipStream_t s, int n_ranges, const ftc_csr &g, const int *e2r,
+                         const float *vals, const void *X, int ldx, int D, void *out, int ldo, int odt, Epi epi,
+                         float *carry, int *tail_row, const uint8_t *dense)
 {
     constexpr int VM = T::VEC;
-#define FTC_SEG(V, L)                                                                                       \
-    do {                                                                                                    \
-        if (vals)                                                                                           \
-            hipLaunchKernelGGL((spmm_seg_kernel<T, V, L, true>), dim3(grid), dim3(256), 0, s, nnz, n_ranges, \
-                               g.row_ptr, g.col_idx, e2r, vals, X, ldx, D, out, ldo, odt, epi, carry,        \
-                               tail_row, dense);                                                            \
-        else                                                                                                \
-            hipLaunchKernelGGL((spmm_seg_kernel<T, V, L, false>), dim3(grid), dim3(256), 0, s, nnz,         \
-                               n_ranges, g.row_ptr, g.col_idx, e2r, vals, X, ldx, D, out, ldo, odt, epi,    \
-                               carry, tail_row, dense);                                                     \
+    const dim3 grid(static_cast<unsigned>((n_ranges + 3) / 4));
+#define FTC_SEG1(V, L, W, RG)                                                                                          \
+    hipLaunchKernelGGL((spmm_seg_kernel<T, V, L, W, R, RG>), grid, dim3(256), 0, s, g.nnz, n_ranges, g.row_ptr,        \
+                       g.col_idx, e2r, vals, X, ldx, D, out, ldo, odt, epi, carry, tail_row, dense)
+#define FTC_SEG(V, L, RG)                      \
+    do {                                       \
+        if (vals) FTC_SEG1(V, L, true, RG);    \
+        else FTC_SEG1(V, L, false, RG);        \
     } while (0)
-    if (vec == VM) {
-        if (lpr == 4) FTC_SEG(VM, 4);
-        else if (lpr == 8) FTC_SEG(VM, 8);
-        else if (lpr == 16) FTC_SEG(VM, 16);
-        else FTC_SEG(VM, 32);
+    if (ragged) {
+        if (lpr == 4) FTC_SEG(VM, 4, true);
+        else if (lpr == 8) FTC_SEG(VM, 8, true);
+        else if (lpr == 16) FTC_SEG(VM, 16, true);
+        else FTC_SEG(VM, 32, true);
+    } else if (vec == VM) {
+        if (lpr == 4) FTC_SEG(VM, 4, false);
+        else if (lpr == 8) FTC_SEG(VM, 8, false);
+        else if (lpr == 16) FTC_SEG(VM, 16, false);
+        else FTC_SEG(VM, 32, false);
     } else if (vec == VM / 2) {
-        FTC_SEG(VM / 2, 4);
+        FTC_SEG(VM / 2, 4, false);
     } else {
-        FTC_SEG(VM / 4, 4);
+        FTC_SEG(VM / 4, 4, false);
     }
 #undef FTC_SEG
+#undef FTC_SEG1
 }
 
-// Caller has checked: window index present, seg_shape() accepts (xdt, D), X and out rows 16-byte
-// aligned, workspace of spmm_seg_ws() bytes.
-int32_t launch_spmm_seg(const ftc_csr &g, const ftc_windows &w, const float *vals, const void *X, int ldx,
-                        int xdt, int D, void *out, int ldo, int odt, Epi epi, void *ws, const uint8_t *dense,
-                        hipStream_t s)
+template <class T>
+static void launch_seg_r(int r, int vec, int lpr, bool ragged, hipStream_t s, int n_ranges, const ftc_csr &g,
+                         const int *e2r, const float *vals, const void *X, int ldx, int D, void *out, int ldo, int odt,
+                         Epi epi, float *carry, int *tail_row, const uint8_t *dense)
 {
+    if (r == SEG_R) launch_seg_t<T, SEG_R>(vec, lpr, ragged, s, n_ranges, g, e2r, vals, X, ldx, D, out, ldo, odt, epi, carry, tail_row, dense);
+    else if (r == 256) launch_seg_t<T, 256>(vec, lpr, ragged, s, n_ranges, g, e2r, vals, X, ldx, D, out, ldo, odt, epi, carry, tail_row, dense);
+    else launch_seg_t<T, 128>(vec, lpr, ragged, s, n_ranges, g, e2r, vals, X, ldx, D, out, ldo, odt, epi, carry, tail_row, dense);
+}
+
+// Caller has checked: window index present, seg_shape() or spmm_ragged_ok() accepts (xdt, D) or the kernel for narrow rows
+// does (spmm_lane_shape, rows of X 16-byte aligned), workspace of spmm_seg_ws(.., least) bytes, of spmm_seg_ws(.., false)
+// unless seg_shape() accepts and the rows of X and out are 16-byte aligned.
+int32_t launch_spmm_seg(const ftc_csr &g, const ftc_windows &w, const float *vals, const void *X, int ldx,
+                        int xdt, int D, void *out, int ldo, int odt, Epi epi, void *ws, size_t ws_bytes,
+                        const uint8_t *dense, hipStream_t s)
+{
+    const bool x16 = aligned16(X) && (static_cast<int64_t>(ldx) * elem_size(xdt)) % 16 == 0;
+    const bool o16 = aligned16(out) && (static_cast<int64_t>(ldo) * elem_size(odt)) % 16 == 0;
     // rows of at most 32 bytes: one or two lanes per run of edges instead of four lanes per row
-    if (!dense && spmm_lane_shape(xdt, D, ldx))
-        return launch_spmm_lane(g, w, vals, X, ldx, xdt, D, out, ldo, odt, epi, ws, s);
+    if (!dense && x16 && spmm_lane_shape(xdt, D, ldx))
+        return launch_spmm_lane(g, w, vals, X, ldx, xdt, D, out, ldo, odt, epi, ws, ws_bytes, s);
     int vec = 0, lpr = 0;
-    seg_shape(xdt, D, &vec, &lpr);
+    const bool ragged = !(x16 && o16 && seg_shape(xdt, D, &vec, &lpr));
+    if (ragged) seg_shape_ragged(xdt, D, &vec, &lpr);
     const int dp = vec * lpr;
-    const int n_ranges = ceil_div(g.nnz, SEG_R);
+    const int short_r = spmm_range(g.nnz, dp);
+    const int r = ws_bytes >= seg_carry_ws(g.nnz, short_r, dp) ? short_r : SEG_R;
+    const int n_ranges = static_cast<int>(seg_count(g.nnz, r));
     float *carry = static_cast<float *>(ws);
     int *tail_row = reinterpret_cast<int *>(static_cast<char *>(ws) +
                                             align_up(static_cast<size_t>(n_ranges) * 2 * dp * sizeof(float), 256));
     if (n_ranges > 0) {
-        const unsigned grid = static_cast<unsigned>((n_ranges + 3) / 4);
         if (xdt == FTC_F32)
-            launch_seg_t<F32>(vec, lpr, grid, s, g.nnz, n_ranges, g, w.edge_to_row, vals, X, ldx, D, out, ldo,
-                              odt, epi, carry, tail_row, dense);
+            launch_seg_r<F32>(r, vec, lpr, ragged, s, n_ranges, g, w.edge_to_row, vals, X, ldx, D, out, ldo, odt, epi, carry, tail_row, dense);
         else if (xdt == FTC_F16)
-            launch_seg_t<F16>(vec, lpr, grid, s, g.nnz, n_ranges, g, w.edge_to_row, vals, X, ldx, D, out, ldo,
-                              odt, epi, carry, tail_row, dense);
+            launch_seg_r<F16>(r, vec, lpr, ragged, s, n_ranges, g, w.edge_to_row, vals, X, ldx, D, out, ldo, odt, epi, carry, tail_row, dense);
         else
-            launch_seg_t<BF16>(vec, lpr, grid, s, g.nnz, n_ranges, g, w.edge_to_row, vals, X, ldx, D, out, ldo,
-                               odt, epi, carry, tail_row, dense);
+            launch_seg_r<BF16>(r, vec, lpr, ragged, s, n_ranges, g, w.edge_to_row, vals, X, ldx, D, out, ldo, odt, epi, carry, tail_row, dense);
         const int32_t st = launch_status("spmm_seg");
         if (st != FTC_OK) return st;
     }
-    return launch_seg_fixup(g.n, n_ranges, g.row_ptr, carry, tail_row, dp, D, out, ldo, odt, epi, dense, SEG_R, s,
+    return launch_seg_fixup(g.n, n_ranges, g.row_ptr, carry, tail_row, dp, D, out, ldo, odt, epi, dense, r, s,
                             "spmm_seg fixup");
 }
 

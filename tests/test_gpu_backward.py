@@ -689,3 +689,20 @@ def test_agnn_backward_random_shapes(case):
         eh2, eb2 = term_err(dH2, dH_ref, tH), abs(float(dbeta2.item()) - dbeta_ref) / tb
         say(f"  single-pass route: dH err {eh2:.3e} dbeta err {eb2:.3e}")
         assert eh2 < 1e-5 and eb2 < 1e-5
+
+
+@pytest.mark.parametrize("n,deg", [(2000, 8), (40_000, 16), (56_000, 16)])
+def test_single_pass_backward_short_ranges(n, deg):
+    """0.02, 0.6 and 0.85 M entries: the edges per wave of the sweep change between them."""
+    g = synth.chung_lu(n, 2.1, deg, seed=n)
+    dg = dev_graph(g)
+    win = B.ftc_build_windows(dg)
+    say(f"backward short ranges n={n} nnz={g.nnz}")
+    Hd, H64 = quantise(synth.normal_features(n, 32, seed=1), F16)
+    dYd, dY64 = quantise(synth.normal_features(n, 32, seed=2), F16)
+    row_z = torch.empty(n, dtype=F32, device="cuda")
+    Y = B.ftc_agnn_layer(dg, win, Hd, beta=1.5, row_z=row_z)
+    dH, db = B.ftc_agnn_layer_backward_fused(dg, win, Hd, row_z, Y, dYd, beta=1.5)
+    ref, db_ref = OB.agnn_layer_backward(g.row_ptr, g.col_idx, H64, 1.5, dY64)
+    tH, tb = OB.agnn_layer_backward_terms(g.row_ptr, g.col_idx, H64, 1.5, dY64)
+    assert term_err(dH, ref, tH) < 1e-5 and abs(float(db.item()) - db_ref) / tb < 1e-5

@@ -875,3 +875,63 @@ def test_update_gemm_general_kernel_edges(oracle, dtype, n, d_in, d_out):
     err = norm_err(out, ref, ab)
     say(f"general update gemm {dtype} {n} x {d_in} -> {d_out}: err {err:.3e}")
     assert err < 1e-5           # fp32 products and sums whatever the input type
+
+
+# ------------------------------------------------------------------ widths and alignments of the edge-balanced SpMM
+@pytest.mark.parametrize("name", ["hub", "cfg2s"])
+@pytest.mark.parametrize("dtype", [F32, F16, BF16])
+@pytest.mark.parametrize("D", [3, 4, 5, 7, 9, 10, 13, 17, 22, 47, 65, 127, 128, 131, 255, 257])
+def test_spmm_any_width_and_alignment(oracle, graphs, name, dtype, D):
+    """Widths that are no multiple of a lane's piece, rows of X and of the output at element alignment, a view one
+    element into a wider buffer, a 16-bit output; with and without edge values, on hub rows, empty rows and
+    duplicates.  The last widths are beyond what one wave holds and take the row-wise kernels."""
+    g = graphs[name]
+    if name == "cfg2s" and D not in (7, 10, 47):
+        return
+    say(f"spmm any width {name} {dtype} D={D}")
+    dg = dev_graph(g)
+    win = B.ftc_build_windows(dg)
+    buf, X64 = quantise(synth.uniform_features(g.n, D + 3, seed=D), dtype)
+    vals = np.random.default_rng(2).uniform(-1, 1, size=g.nnz).astype(np.float32)
+    vd = torch.from_numpy(vals).cuda()
+    for lo in (0, 1):
+        Xd, x64 = buf[:, lo:lo + D], X64[:, lo:lo + D]
+        ref, ab = oracle.spmm(g.row_ptr, g.col_idx, vals.astype(np.float64), x64)
+        out = B.ftc_spmm(dg, win, vd, Xd.contiguous())
+        assert norm_err(out, ref, ab) < 1e-5
+        wide = torch.full((g.n, D + 2), 7.0, dtype=F32, device="cuda")
+        B.ftc_spmm(dg, win, vd, Xd, out=wide[:, 1:D + 1])
+        assert norm_err(wide[:, 1:D + 1], ref, ab) < 1e-5
+        assert torch.all(wide[:, 0] == 7) and torch.all(wide[:, D + 1] == 7)      # nothing beside the rows is written
+    ref, ab = oracle.spmm(g.row_ptr, g.col_idx, np.ones(g.nnz), X64[:, :D])
+    half = B.ftc_spmm(dg, win, None, buf[:, :D], out_dtype=F16, relu=True)
+    assert norm_err(half, np.maximum(ref, 0), ab, F16) < 1e-5
+    few = B._workspace(1, "cuda")                                                 # too small: the row-wise kernels
+    if B.lib().ftc_spmm_workspace_bytes(g.n, g.nnz, D) > few.numel() and D % 2 == 1:
+        assert norm_err(B.ftc_spmm(dg, win, None, buf[:, :D], ws=few), ref, ab) < 1e-5
+
+
+@pytest.mark.parametrize("n,deg", [(700, 8), (45_000, 16), (90_000, 16), (200_000, 20)])
+def test_short_ranges_on_small_graphs(oracle, n, deg):
+    """0.006, 0.6, 1.3 and 3.7 M entries: the edges per wave change between them; and the long ranges, which a
+    workspace of their size still gets."""
+    g = synth.chung_lu(n, 2.1, deg, seed=n)
+    dg = dev_graph(g)
+    win = B.ftc_build_windows(dg)
+    say(f"short ranges n={n} nnz={g.nnz}")
+    vals = np.random.default_rng(2).uniform(-1, 1, size=g.nnz).astype(np.float32)
+    vd, v64 = torch.from_numpy(vals).cuda(), vals.astype(np.float64)
+    for dtype, D in ((F16, 8), (F16, 16), (F16, 32), (F32, 10), (F32, 128)):
+        Xd, X64 = quantise(synth.uniform_features(n, D, seed=D), dtype)
+        ref, ab = oracle.spmm(g.row_ptr, g.col_idx, v64, X64)
+        assert norm_err(B.ftc_spmm(dg, win, vd, Xd), ref, ab) < 1e-5
+        if D != 10:                                  # ranges of 512 edges: their carried rows, and a byte per window
+            least = (g.nnz // 512 + 1) * (2 * 4 * max(D, 32) + 8) + 1024 + n // 16
+            assert norm_err(B.ftc_spmm(dg, win, vd, Xd, ws=B._workspace(least, "cuda")), ref, ab) < 1e-5
+    Hd, H64 = quantise(synth.normal_features(n, 32, seed=5), F16)
+    ref, ab, p = oracle.agnn_layer(g.row_ptr, g.col_idx, H64, 1.5)
+    assert norm_err(B.ftc_agnn_layer(dg, win, Hd, beta=1.5), ref, ab) < 1e-5
+    c = B.ftc_sddmm(dg, win, Hd, Hd, cosine=True)
+    h = H64 / np.maximum(np.linalg.norm(H64, axis=1, keepdims=True), 1e-12)
+    rows = np.repeat(np.arange(n), np.diff(g.row_ptr))
+    assert np.max(np.abs(c.cpu().double().numpy() - np.einsum("ij,ij->i", h[rows], h[g.col_idx]))) < 1e-5
