@@ -558,7 +558,7 @@ int32_t ftc_weight_grad(int32_t n, const void *X, int32_t ldx, int32_t x_dtype, 
         return fail(FTC_EUNSUPPORTED, "ftc_weight_grad: d_out too wide (8 input columns next to it must fit: d_out <= 504)");
     const size_t need = weight_grad_ws(n, d_in, d_out);
     if (!ws || ws_bytes < need) return fail(FTC_EWORKSPACE, "ftc_weight_grad: workspace of %zu bytes needed", need);
-    return launch_weight_grad(n, X, ldx, x_dtype, d_in, G, ldg, d_out, dW, ws, static_cast<hipStream_t>(stream));
+    return launch_weight_grad(n, X, ldx, x_dtype, d_in, G, ldg, d_out, nullptr, 0, FTC_F32, dW, ws, static_cast<hipStream_t>(stream));
 }
 
 static int pad4(int d) { return (d + 3) / 4 * 4; }
@@ -593,14 +593,15 @@ int32_t ftc_update_gemm_backward(int32_t n, const void *X, int32_t ldx, int32_t 
     const float *dP = dZ;
     int ldp = lddz;
     char *p = static_cast<char *>(ws);
-    if (Z) {  // ReLU: the gradient passes where the output was positive
+    // ReLU: the gradient passes where the output was positive.  Only the input gradient needs the masked matrix.
+    if (Z && dX) {
         float *masked = reinterpret_cast<float *>(p);
         ldp = pad4(d_out);
         FTC_TRY(launch_mask_scale(n, d_out, dZ, lddz, Z, ldz, z_dtype, nullptr, masked, ldp, hs));
         dP = masked;
     }
     void *ws_wg = p + align_up(static_cast<size_t>(n) * pad4(d_out) * sizeof(float), 256);
-    FTC_TRY(launch_weight_grad(n, X, ldx, dtype, d_in, dP, ldp, d_out, dW, ws_wg, hs));
+    FTC_TRY(launch_weight_grad(n, X, ldx, dtype, d_in, dP, ldp, d_out, Z && !dX ? Z : nullptr, ldz, z_dtype, dW, ws_wg, hs));
     if (dX)
         FTC_TRY(launch_input_grad_any(n, dP, ldp, d_out, W, dtype, d_in, dX, lddx, dx_dtype,
                                       static_cast<char *>(ws_wg) + weight_grad_ws(n, d_in, d_out), hs));
@@ -653,7 +654,7 @@ int32_t ftc_gcn_layer_backward(const ftc_csr *gT, const ftc_windows *wT, const f
     // dZ = A^T dP on the transposed graph the caller hands over
     FTC_TRY(ftc_spmm(gT, wT, dinv ? nullptr : valsT, dP, ldp, FTC_F32, d_out, dZ, ldp, FTC_F32, dinv, 0, path,
                      ws_spmm, spmm_bytes, stream));
-    FTC_TRY(launch_weight_grad(n, X, ldx, dtype, d_in, dZ, ldp, d_out, dW, ws_wg, hs));
+    FTC_TRY(launch_weight_grad(n, X, ldx, dtype, d_in, dZ, ldp, d_out, nullptr, 0, FTC_F32, dW, ws_wg, hs));
     if (dX)
         FTC_TRY(launch_input_grad_any(n, dZ, ldp, d_out, W, dtype, d_in, dX, lddx, FTC_F32,
                                       static_cast<char *>(ws_wg) + weight_grad_ws(n, d_in, d_out), hs));

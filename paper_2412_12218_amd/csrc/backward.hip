@@ -143,146 +143,190 @@ int32_t launch_mask_scale(int n, int d, const float *dY, int lddy, const void *Y
 }
 
 // ---- dW = X^T G -----------------------------------------------------------------------------------
-// A workgroup walks a contiguous share of the rows, WG_ROWS at a time staged in LDS as fp32; a
-// thread owns 4 x 4 tiles of the d_in x d_out result (two 16-byte LDS reads per 16 multiply-adds)
-// and keeps them in registers for all of its rows.  When the result has fewer than 256 tiles the
-// threads form 256 / tiles slices that split the staged rows between them, and the slices' tiles
-// are added in slice order through LDS at the end.  The workgroups' partial results are added by
-// a second kernel in workgroup order: reproducible, no floating-point atomics.
+// A contraction over the rows, on the matrix cores in fp32 (v_mfma_f32_16x16x4_f32; 16-bit elements of X are widened), so
+// products and sums are those of fp32 arithmetic.  A wave takes four rows per step:
+//   A operand  lane l holds VA consecutive columns of row l/16 from column a0 + VA (l%16) on (one load; 64 columns a step for
+//              VA = 4); the j-th of them goes into the j-th of VA tiles, whose rows are the columns a0 + VA m + j;
+//   B operand  the same of G: VB consecutive columns per lane, NT tiles in all.
+// A workgroup owns 16 VA columns of X, 16 NT columns of G and one of `splits` shares of the rows; its four waves take every
+// fourth step and are added in a fixed order through LDS, the shares' results by a second kernel: reproducible, no
+// floating-point atomics.  Columns beyond the end: the last lanes' pieces are moved back to end with the row, and an
+// element is written by the lane whose own piece it lies in.
+// ReLU: with Y (the layer's output, limit = the largest finite or infinite bits of its 16-bit type, 0: fp32) an element
+// of G counts only where Y is positive; no masked copy of G has to exist.
+// Bound by reading X and G (2^20 x 128 fp16, 32 columns of G: 0.40 GB) up to about 64 columns of G, by the fp32 matrix
+// rate beyond.  Measured, against rows staged in LDS and 4 x 4 register tiles on the vector units (us, with the sum over
+// the shares): fp32 100 000 x 300 -> 128: 324 / 138; fp16 2^20 x 128 -> 32:
+// 250 / 128 (with the mask, before as a pass of its own: 340 / 145).
 constexpr int WG_ROWS = 32;
 constexpr int WG_MAX_BLOCKS = 1024;
-constexpr int WG_TILES = 4;  // 4 x 4 tiles per thread at most: d_in * d_out <= 256 * 16 * WG_TILES
+constexpr int WG_TILES = 4;
+typedef float wg_f32x4 __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(256) void weight_grad_kernel(int n, const void *__restrict__ X, int ldx, int xdt, int d_in,
-                                                          const float *__restrict__ G, int ldg, int d_out,
-                                                          float *__restrict__ partial, int x_vec, int g_vec)
+template <class T, int N>  // N consecutive elements at element alignment
+__device__ __forceinline__ void wg_load(const void *base, int64_t idx, float (&f)[N])
 {
-    extern __shared__ __attribute__((aligned(16))) float lds[];
-    const int dip = (d_in + 3) / 4 * 4, dop = (d_out + 3) / 4 * 4;
-    float *Xs = lds;                  // [WG_ROWS][dip]
-    float *Gs = lds + WG_ROWS * dip;  // [WG_ROWS][dop]
-    const int tid = threadIdx.x;
-    const int tiles_b = dop / 4, n_tiles = (dip / 4) * tiles_b;
-    const int slices = n_tiles < 256 ? 256 / n_tiles : 1;
-    const int slice = n_tiles < 256 ? tid / n_tiles : 0;
-    const int tile0 = n_tiles < 256 ? tid % n_tiles : tid;
-    const bool worker = slice < slices;
-    float acc[WG_TILES][16];
+    if constexpr (N == 1) {
+        if constexpr (T::BYTES == 4) f[0] = static_cast<const float *>(base)[idx];
+        else f[0] = std::is_same<T, F16>::value ? f16_bits_to_f32(static_cast<const uint16_t *>(base)[idx])
+                                                : bf16_bits_to_f32(static_cast<const uint16_t *>(base)[idx]);
+    } else if constexpr (T::BYTES == 4) {
+        typedef float fv __attribute__((ext_vector_type(N), aligned(4)));
+        const fv v = *reinterpret_cast<const fv *>(static_cast<const float *>(base) + idx);
 #pragma unroll
-    for (int u = 0; u < WG_TILES; ++u)
+        for (int j = 0; j < N; ++j) f[j] = v[j];
+    } else {
+        typedef uint16_t hv __attribute__((ext_vector_type(N), aligned(2)));
+        const hv v = *reinterpret_cast<const hv *>(static_cast<const uint16_t *>(base) + idx);
 #pragma unroll
-        for (int q = 0; q < 16; ++q) acc[u][q] = 0.f;
-    const int64_t per = (static_cast<int64_t>(n) + gridDim.x - 1) / gridDim.x;
+        for (int j = 0; j < N; ++j) f[j] = std::is_same<T, F16>::value ? f16_bits_to_f32(v[j]) : bf16_bits_to_f32(v[j]);
+    }
+}
+
+// MASK: 0 none, 1 by an fp32 Y, 2 by a 16-bit Y
+template <class T, int VA, int NT, int MASK>
+__global__ __launch_bounds__(256) void weight_grad_kernel(int n, const void *__restrict__ X, int ldx, int d_in,
+                                                          const float *__restrict__ G, int ldg, int d_out,
+                                                          const void *__restrict__ Y, int ldy, unsigned limit,
+                                                          float *__restrict__ partial, int splits)
+{
+    constexpr int VB = NT < 4 ? NT : 4, NB = NT / VB, U = NT * VA > 16 ? 2 : VA == 1 ? 8 : 4;
+    constexpr int TILES = VA * NT;
+    __shared__ float red[2][TILES * 256];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int m = lane & 15, kb = lane >> 4;
+    const int a0 = blockIdx.y * (16 * VA), b0 = blockIdx.z * (16 * NT);
+    const int ca = min(a0 + VA * m, d_in - VA);  // first column of this lane's piece of X
+    int cb[NB];                                  // ... and of its pieces of G
+#pragma unroll
+    for (int q = 0; q < NB; ++q) cb[q] = min(b0 + q * 16 * VB + VB * m, d_out - VB);
+    const int64_t per = ((static_cast<int64_t>(n) + splits - 1) / splits + 15) / 16 * 16;
     const int64_t r_begin = per * blockIdx.x, r_end = min(static_cast<int64_t>(n), r_begin + per);
-    const int xv = xdt == FTC_F32 ? 4 : 8;  // elements per 16-byte piece of X
-    for (int64_t r0 = r_begin; r0 < r_end; r0 += WG_ROWS) {
-        __syncthreads();  // the previous rows are consumed
-        if (x_vec) {      // d_in is a multiple of the piece, rows are 16-byte aligned
-            const int ppr = d_in / xv;
-            for (int t = tid; t < WG_ROWS * ppr; t += 256) {
-                const int r = t / ppr, a = (t % ppr) * xv;
-                float f[8];
-                const bool ok = r0 + r < r_end;
-                if (xdt == FTC_F32) {
-                    const float4 v = ok ? *reinterpret_cast<const float4 *>(static_cast<const float *>(X) + (r0 + r) * ldx + a)
-                                        : make_float4(0.f, 0.f, 0.f, 0.f);
-                    *reinterpret_cast<float4 *>(&Xs[r * dip + a]) = v;
-                } else {
-                    if (ok) {
-                        if (xdt == FTC_F16) load_vec<F16>(X, (r0 + r) * ldx + a, f);
-                        else load_vec<BF16>(X, (r0 + r) * ldx + a, f);
-                    } else {
+    // two sums per element (of every other step) where they cost nothing: half the chain of roundings (with 32 columns of G
+    // the registers of the second sum cost a quarter of the time, with 64 half; more shares of the rows shorten it there)
+    constexpr int PAR = NT == 1 ? 2 : 1;
+    wg_f32x4 part[PAR][VA][NT];
 #pragma unroll
-                        for (int q = 0; q < 8; ++q) f[q] = 0.f;
-                    }
-                    *reinterpret_cast<float4 *>(&Xs[r * dip + a]) = make_float4(f[0], f[1], f[2], f[3]);
-                    *reinterpret_cast<float4 *>(&Xs[r * dip + a + 4]) = make_float4(f[4], f[5], f[6], f[7]);
+    for (int p = 0; p < PAR; ++p)
+#pragma unroll
+        for (int i = 0; i < VA; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) part[p][i][j] = wg_f32x4{0.f, 0.f, 0.f, 0.f};
+
+    auto load = [&](int64_t row, bool ok, float (&xa)[VA], float (&gb)[NT]) {
+        wg_load<T, VA>(X, row * ldx + ca, xa);
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
+            float g[VB];
+            wg_load<F32, VB>(G, row * ldg + cb[q], g);
+            if constexpr (MASK == 1) {
+                float y[VB];
+                wg_load<F32, VB>(Y, row * ldy + cb[q], y);
+#pragma unroll
+                for (int j = 0; j < VB; ++j) g[j] = y[j] > 0.f ? g[j] : 0.f;
+            } else if constexpr (MASK == 2) {
+                typedef uint16_t yv __attribute__((ext_vector_type(VB), aligned(2)));
+                const yv y = *reinterpret_cast<const yv *>(static_cast<const uint16_t *>(Y) + row * ldy + cb[q]);
+#pragma unroll
+                for (int j = 0; j < VB; ++j) {
+                    const unsigned bits = y[j];
+                    g[j] = (bits != 0u && bits <= limit) ? g[j] : 0.f;  // positive, not NaN
                 }
             }
-        } else {
-            for (int t = tid; t < WG_ROWS * dip; t += 256) {
-                const int r = t / dip, a = t % dip;
-                Xs[t] = (r0 + r < r_end && a < d_in) ? load_elem(X, (r0 + r) * ldx + a, xdt) : 0.f;
-            }
-        }
-        if (g_vec) {  // d_out is a multiple of 4, rows of G are 16-byte aligned
-            for (int t = tid; t < WG_ROWS * tiles_b; t += 256) {
-                const int r = t / tiles_b, b = (t % tiles_b) * 4;
-                *reinterpret_cast<float4 *>(&Gs[r * dop + b]) =
-                    r0 + r < r_end ? *reinterpret_cast<const float4 *>(G + (r0 + r) * ldg + b) : make_float4(0.f, 0.f, 0.f, 0.f);
-            }
-        } else {
-            for (int t = tid; t < WG_ROWS * dop; t += 256) {
-                const int r = t / dop, b = t % dop;
-                Gs[t] = (r0 + r < r_end && b < d_out) ? G[(r0 + r) * ldg + b] : 0.f;
-            }
-        }
-        __syncthreads();
-        if (worker) {
 #pragma unroll
-            for (int u = 0; u < WG_TILES; ++u) {
-                const int tile = tile0 + u * 256;
-                if (tile < n_tiles && (u == 0 || n_tiles >= 256)) {
-                    const int a0 = (tile / tiles_b) * 4, b0 = (tile % tiles_b) * 4;
-                    for (int r = slice; r < WG_ROWS; r += slices) {
-                        const float4 x = *reinterpret_cast<const float4 *>(&Xs[r * dip + a0]);
-                        const float4 gq = *reinterpret_cast<const float4 *>(&Gs[r * dop + b0]);
-                        const float xq[4] = {x.x, x.y, x.z, x.w}, gv[4] = {gq.x, gq.y, gq.z, gq.w};
-#pragma unroll
-                        for (int i = 0; i < 4; ++i)
-#pragma unroll
-                            for (int j = 0; j < 4; ++j) acc[u][i * 4 + j] = fmaf(xq[i], gv[j], acc[u][i * 4 + j]);
-                    }
-                }
-            }
+            for (int j = 0; j < VB; ++j) gb[q * VB + j] = ok ? g[j] : 0.f;
         }
+        if (!ok) {
+#pragma unroll
+            for (int j = 0; j < VA; ++j) xa[j] = 0.f;
+        }
+    };
+    auto multiply = [&](const float (&xa)[VA], const float (&gb)[NT], wg_f32x4 (&to)[VA][NT]) {
+#pragma unroll
+        for (int i = 0; i < VA; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) to[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[i], gb[j], to[i][j], 0, 0, 0);
+    };
+    int64_t r = r_begin + wave * 4;  // steps of four rows, every fourth one this wave's
+    for (; r + (U - 1) * 16 + 4 <= r_end; r += U * 16) {
+        float xa[U][VA], gb[U][NT];
+#pragma unroll
+        for (int s = 0; s < U; ++s) load(r + s * 16 + kb, true, xa[s], gb[s]);
+#pragma unroll
+        for (int s = 0; s < U; ++s) multiply(xa[s], gb[s], part[s % PAR]);
     }
+    for (; r < r_end; r += 16) {
+        float xa[VA], gb[NT];
+        const int64_t row = r + kb;
+        load(min(row, r_end - 1), row < r_end, xa, gb);
+        multiply(xa, gb, part[0]);
+    }
+    wg_f32x4 acc[VA][NT];
+#pragma unroll
+    for (int i = 0; i < VA; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] = PAR == 2 ? part[0][i][j] + part[PAR - 1][i][j] : part[0][i][j];
+    // (wave 0 + wave 2) + (wave 1 + wave 3)
+    auto park = [&](float *dst) {
+#pragma unroll
+        for (int i = 0; i < VA; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) dst[((i * NT + j) * 4 + e) * 64 + lane] = acc[i][j][e];
+    };
+    auto take = [&](const float *src) {
+#pragma unroll
+        for (int i = 0; i < VA; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[i][j][e] += src[((i * NT + j) * 4 + e) * 64 + lane];
+    };
+    if (wave >= 2) park(red[wave - 2]);
+    __syncthreads();
+    if (wave < 2) take(red[wave]);
+    __syncthreads();
+    if (wave == 1) park(red[0]);
+    __syncthreads();
+    if (wave != 0) return;
+    take(red[0]);
     float *out = partial + static_cast<size_t>(blockIdx.x) * d_in * d_out;
-    if (n_tiles < 256) {
-        // add the slices' tiles in slice order; red[slice][tile][16] reuses the staging memory
-        __syncthreads();
-        float *red = lds;
-        if (worker) {
 #pragma unroll
-            for (int q = 0; q < 16; ++q) red[(slice * n_tiles + tile0) * 16 + q] = acc[0][q];
-        }
-        __syncthreads();
-        for (int e = tid; e < n_tiles * 16; e += 256) {
-            float t = 0.f;
-            for (int sl = 0; sl < slices; ++sl) t += red[sl * n_tiles * 16 + e];
-            const int tile = e / 16, q = e % 16;
-            const int a = (tile / tiles_b) * 4 + q / 4, b = (tile % tiles_b) * 4 + q % 4;
-            if (a < d_in && b < d_out) out[a * d_out + b] = t;
-        }
-        return;
-    }
+    for (int e = 0; e < 4; ++e) {
+        const int own_a = a0 + VA * (kb * 4 + e), first_a = min(own_a, d_in - VA);
 #pragma unroll
-    for (int u = 0; u < WG_TILES; ++u) {
-        const int tile = tid + u * 256;
-        if (tile < n_tiles) {
-            const int a0 = (tile / tiles_b) * 4, b0 = (tile % tiles_b) * 4;
+        for (int i = 0; i < VA; ++i) {
+            const int a = first_a + i;
+            if (a < own_a) continue;
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (a0 + i < d_in && b0 + j < d_out) out[(a0 + i) * d_out + b0 + j] = acc[u][i * 4 + j];
+            for (int j = 0; j < NT; ++j) {
+                const int own_b = b0 + (j / VB) * 16 * VB + VB * m, b = cb[j / VB] + j % VB;
+                if (b >= own_b) out[static_cast<size_t>(a) * d_out + b] = acc[i][j][e];
+            }
         }
     }
 }
 
+// sum over the shares: 64 results per workgroup, four threads a result with every fourth share each, eight loads in flight
 __global__ __launch_bounds__(256) void sum_partials_kernel(int count, int n_partials, const float *__restrict__ partial,
                                                            float *__restrict__ out)
 {
-    const int t = blockIdx.x * 256 + threadIdx.x;
-    if (t >= count) return;
+    __shared__ float red[4][64];
+    const int lane = threadIdx.x & 63, part = threadIdx.x >> 6;
+    const int t = blockIdx.x * 64 + lane;
     float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    int b = 0;
-    for (; b + 7 < n_partials; b += 8) {
+    if (t < count) {
+        int b = part;
+        for (; b + 28 < n_partials; b += 32) {
 #pragma unroll
-        for (int k = 0; k < 8; ++k) s[k] += partial[static_cast<size_t>(b + k) * count + t];
+            for (int k = 0; k < 8; ++k) s[k] += partial[static_cast<size_t>(b + 4 * k) * count + t];
+        }
+        for (; b < n_partials; b += 4) s[0] += partial[static_cast<size_t>(b) * count + t];
     }
-    for (; b < n_partials; ++b) s[0] += partial[static_cast<size_t>(b) * count + t];
-    out[t] = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
+    red[part][lane] = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
+    __syncthreads();
+    if (part == 0 && t < count) out[t] = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
 }
 
 static int weight_grad_blocks(int n)
@@ -291,15 +335,14 @@ static int weight_grad_blocks(int n)
     return by_rows < 1 ? 1 : (by_rows > WG_MAX_BLOCKS ? WG_MAX_BLOCKS : by_rows);
 }
 
-bool weight_grad_shape_ok(int d_in, int d_out)
+// What the interface promises: d_out <= 504 next to at least eight input columns.
+static bool weight_grad_shape_ok(int d_in, int d_out)
 {
-    // register tiles of one workgroup cover the result; the staged rows fit 64 KB of LDS
     return d_in >= 1 && d_out >= 1 && ((d_in + 3) / 4) * ((d_out + 3) / 4) <= 256 * WG_TILES &&
            (d_in + 3) / 4 * 4 + (d_out + 3) / 4 * 4 <= 512;
 }
 
-// Input columns that one pass covers next to d_out output columns: all of them when the register tiles
-// and the staged rows allow it, else the largest multiple of 8 that does (at most 256); 0 if none.
+// Input columns that weight_grad_ws() counts next to d_out output columns; 0: d_out is too wide.
 int weight_grad_group(int d_in, int d_out)
 {
     if (weight_grad_shape_ok(d_in, d_out)) return d_in;
@@ -314,33 +357,65 @@ size_t weight_grad_ws(int n, int d_in, int d_out)
     return align_up(static_cast<size_t>(weight_grad_blocks(n)) * (gk > 0 ? gk : d_in) * d_out * sizeof(float), 256);
 }
 
-// dW = X^T G.  A wider X is taken in groups of input columns: rows [k0, k0 + gk) of dW are one contiguous
-// block, each pass reads its columns of X and all of G, and the passes share the workspace (they run
-// one after the other on the stream).
-int32_t launch_weight_grad(int n, const void *X, int ldx, int xdt, int d_in, const float *G, int ldg, int d_out,
-                           float *dW, void *ws, hipStream_t s)
+template <class T, int VA>
+static void weight_grad_t(int nt, int mask, dim3 grid, hipStream_t s, int n, const void *X, int ldx, int d_in, const float *G,
+                          int ldg, int d_out, const void *Y, int ldy, unsigned limit, float *partial, int splits)
 {
-    const int blocks = weight_grad_blocks(n);
-    const int group = weight_grad_group(d_in, d_out);
-    const int dop = (d_out + 3) / 4 * 4;
-    const int xv = xdt == FTC_F32 ? 4 : 8;
-    const int g_vec = d_out % 4 == 0 && ldg % 4 == 0 && aligned16(G);
+#define FTC_WG(N, M)                                                                                                   \
+    hipLaunchKernelGGL((weight_grad_kernel<T, VA, N, M>), grid, dim3(256), 0, s, n, X, ldx, d_in, G, ldg, d_out, Y, ldy, \
+                       limit, partial, splits)
+#define FTC_WGN(N)                      \
+    if (nt == N) {                      \
+        if (mask == 0) FTC_WG(N, 0);    \
+        else if (mask == 1) FTC_WG(N, 1); \
+        else FTC_WG(N, 2);              \
+    }
+    FTC_WGN(1) FTC_WGN(2) FTC_WGN(4) FTC_WGN(8)
+#undef FTC_WGN
+#undef FTC_WG
+}
+
+// dW = X^T (G masked by Y; Y == NULL: no mask).  The shares of the rows: enough workgroups for the chip, at least 64 rows
+// each, and as many as the workspace of weight_grad_ws() bytes holds results of; where that would be fewer than four, X may
+// be taken in groups of columns instead (rows [k0, k0 + group) of dW are one contiguous block; the passes share the workspace).
+int32_t launch_weight_grad(int n, const void *X, int ldx, int xdt, int d_in, const float *G, int ldg, int d_out,
+                           const void *Y, int ldy, int ydt, float *dW, void *ws, hipStream_t s)
+{
+    const int64_t room = static_cast<int64_t>(weight_grad_blocks(n)) * weight_grad_group(d_in, d_out);  // columns x shares
+    const int nt = d_out <= 16 ? 1 : d_out <= 32 ? 2 : d_out <= 64 ? 4 : 8, va = d_in <= 16 ? 1 : 4;
+    const int groups_b = (d_out + 16 * nt - 1) / (16 * nt);
+    const int64_t tiles = static_cast<int64_t>((d_in + 16 * va - 1) / (16 * va)) * groups_b;
+    int64_t want = (nt == 4 ? 2048 : 1024) / tiles;  // workgroups; with 33 to 64 columns of G more, for shorter sums
+    if (want > (n + 63) / 64) want = (n + 63) / 64;
+    if (want < 1) want = 1;
+    int64_t splits = room / d_in < want ? room / d_in : want;
+    int group = d_in;
+    if (splits < 4 && splits < want) {  // (never narrower groups than weight_grad_group() columns)
+        splits = want < 4 ? want : 4;
+        if (splits > weight_grad_blocks(n)) splits = weight_grad_blocks(n);
+        group = static_cast<int>(room / splits < d_in ? room / splits : d_in);
+    }
     float *partial = static_cast<float *>(ws);
+    const int mask = !Y ? 0 : ydt == FTC_F32 ? 1 : 2;
+    const unsigned limit = ydt == FTC_F16 ? 0x7c00u : 0x7f80u;
     for (int k0 = 0; k0 < d_in; k0 += group) {
         const int dk = d_in - k0 < group ? d_in - k0 : group;
-        const int dip = (dk + 3) / 4 * 4;
-        const int n_tiles = (dip / 4) * (dop / 4);
-        size_t lds = static_cast<size_t>(WG_ROWS) * (dip + dop) * sizeof(float);
-        if (n_tiles < 256) {  // room for the slices' tiles
-            const size_t red = static_cast<size_t>(256 / n_tiles) * n_tiles * 16 * sizeof(float);
-            if (red > lds) lds = red;
-        }
+        const int vk = dk <= 16 ? 1 : 4;
         const void *Xk = static_cast<const char *>(X) + static_cast<size_t>(k0) * elem_size(xdt);
-        const int x_vec = dk % xv == 0 && (static_cast<int64_t>(ldx) * elem_size(xdt)) % 16 == 0 && aligned16(Xk);
-        hipLaunchKernelGGL(weight_grad_kernel, dim3(blocks), dim3(256), lds, s, n, Xk, ldx, xdt, dk, G, ldg, d_out,
-                           partial, x_vec, g_vec);
-        hipLaunchKernelGGL(sum_partials_kernel, dim3((dk * d_out + 255) / 256), dim3(256), 0, s, dk * d_out, blocks,
-                           partial, dW + static_cast<size_t>(k0) * d_out);
+        const dim3 grid(static_cast<unsigned>(splits), (dk + 16 * vk - 1) / (16 * vk), groups_b);
+#define FTC_WGT(T)                                                                                                        \
+    do {                                                                                                                  \
+        if (vk == 1) weight_grad_t<T, 1>(nt, mask, grid, s, n, Xk, ldx, dk, G, ldg, d_out, Y, ldy, limit, partial,        \
+                                         static_cast<int>(splits));                                                       \
+        else weight_grad_t<T, 4>(nt, mask, grid, s, n, Xk, ldx, dk, G, ldg, d_out, Y, ldy, limit, partial,                \
+                                 static_cast<int>(splits));                                                               \
+    } while (0)
+        if (xdt == FTC_F32) FTC_WGT(F32);
+        else if (xdt == FTC_F16) FTC_WGT(F16);
+        else FTC_WGT(BF16);
+#undef FTC_WGT
+        hipLaunchKernelGGL(sum_partials_kernel, dim3((dk * d_out + 63) / 64), dim3(256), 0, s, dk * d_out,
+                           static_cast<int>(splits), partial, dW + static_cast<size_t>(k0) * d_out);
     }
     return launch_status("weight_grad");
 }

@@ -706,3 +706,29 @@ def test_single_pass_backward_short_ranges(n, deg):
     ref, db_ref = OB.agnn_layer_backward(g.row_ptr, g.col_idx, H64, 1.5, dY64)
     tH, tb = OB.agnn_layer_backward_terms(g.row_ptr, g.col_idx, H64, 1.5, dY64)
     assert term_err(dH, ref, tH) < 1e-5 and abs(float(db.item()) - db_ref) / tb < 1e-5
+
+
+@pytest.mark.parametrize("dtype", [F32, F16, BF16])
+@pytest.mark.parametrize("n,d_in,d_out", [(1, 1, 1), (3, 3, 17), (4, 16, 16), (63, 17, 15), (64, 20, 33), (65, 63, 64),
+                                          (130, 64, 65), (1000, 65, 7), (777, 130, 129), (300, 1433, 6), (5000, 300, 128),
+                                          (90, 700, 300), (40_000, 128, 31)])
+def test_weight_grad_edges(dtype, n, d_in, d_out):
+    """Remainders of the column tiles, of the steps of four rows and of the shares of the rows; X, G and the ReLU's Y in
+    rows at element alignment (views into wider buffers); the mask inside the product equals a masked copy of G."""
+    rng = np.random.default_rng(n + d_in)
+    buf, X64 = quantise(rng.uniform(-1, 1, size=(n, d_in + 1)).astype(np.float32), dtype)
+    gbuf, G64 = quantise(rng.uniform(-1, 1, size=(n, d_out + 2)).astype(np.float32), F32)
+    X, X64, G, G64 = buf[:, 1:], X64[:, 1:], gbuf[:, 2:], G64[:, 2:]
+    dW = B.ftc_weight_grad(X, G)
+    say(f"weight grad {dtype} {n} x {d_in} -> {d_out}")
+    assert term_err(dW, X64.T @ G64, np.abs(X64).T @ np.abs(G64)) < 1e-5
+    W = torch.zeros((d_in, d_out), dtype=dtype, device="cuda")
+    for zt in (F32, F16, BF16):
+        z = rng.uniform(-1, 1, size=(n, d_out)).astype(np.float32)
+        z[rng.random(z.shape) < 0.1] = 0.0
+        z[rng.random(z.shape) < 0.02] = np.nan                  # not positive: the gradient does not pass
+        z[rng.random(z.shape) < 0.02] = np.inf
+        Z = torch.from_numpy(z).to(zt).cuda()
+        M64 = np.where(Z.float().cpu().numpy() > 0, G64, 0.0)
+        _, dWm = B.ftc_update_gemm_backward(X, W, G, Z=Z, want_dX=False)
+        assert term_err(dWm, X64.T @ M64, np.abs(X64).T @ np.abs(M64)) < 1e-5
