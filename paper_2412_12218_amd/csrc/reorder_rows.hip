@@ -198,6 +198,13 @@ __device__ __forceinline__ void row_done(const Use &u, int r, int dst, int len, 
     }
 }
 
+// A label that more than half of a row's entries hold wins without any sorting; two of the entries are tried.  Labels settle
+// after a few rounds and most rows pass then.  Returns the winner, or -1 where neither is one.
+__device__ __forceinline__ int majority_of(unsigned long long eq0, unsigned long long eq1, int c0, int c1, int len)
+{
+    return 2 * __popcll(eq0) > len ? c0 : 2 * __popcll(eq1) > len ? c1 : -1;
+}
+
 // one row of a queue by one wave, K entries per lane
 template <class Use, int K>
 __device__ __forceinline__ void queued_row(const Use &u, int r, int lane)
@@ -211,6 +218,24 @@ __device__ __forceinline__ void queued_row(const Use &u, int r, int lane)
     for (int k = 0; k < K; ++k) v[k] = k * 64 + lane < len ? u.value(v[k]) : RS_NONE;
     bitonic_sort<64 * K, K, 64>(v, lane);
     row_done<Use, K, 64>(u, r, u.rp[r], len, v, lane);
+}
+
+// one row of 33 to 64 entries by one wave
+template <class Use>
+__device__ __forceinline__ void wave_row(const Use &u, int r, int dst, int len, int (&x)[1], int lane)
+{
+    if constexpr (Use::VOTES) {
+        const int c0 = __builtin_amdgcn_readlane(x[0], 0), c1 = __builtin_amdgcn_readlane(x[0], 7);
+        const unsigned long long e0 = __builtin_amdgcn_ballot_w64(lane < len && x[0] == c0);
+        const unsigned long long e1 = __builtin_amdgcn_ballot_w64(lane < len && x[0] == c1);
+        const int w = majority_of(e0, e1, c0, c1, len);
+        if (w >= 0) {  // uniform
+            if (lane == 0) u.out[r] = w;
+            return;
+        }
+    }
+    bitonic_sort<64, 1, 64>(x, lane);
+    row_done<Use, 1, 64>(u, r, dst, len, x, lane);
 }
 
 // Workgroups below `queue_blocks` take the rows of 65 to 1024 entries from the queues, one wave a row; the
@@ -259,6 +284,20 @@ __global__ __launch_bounds__(256) void row_sort_kernel(Use u, RowQueues q, int q
 #pragma unroll
         for (int p = 0; p < PAIRS; ++p) {
             const int t = (p0 + p) * 2 + half;
+            if constexpr (Use::VOTES) {
+                const int la = __builtin_amdgcn_readlane(len[p], 0), lb = __builtin_amdgcn_readlane(len[p], 32);
+                const int a0 = __builtin_amdgcn_readlane(v[p], 0), a1 = __builtin_amdgcn_readlane(v[p], 7);
+                const int b0 = __builtin_amdgcn_readlane(v[p], 32), b1 = __builtin_amdgcn_readlane(v[p], 39);
+                const bool in = li < len[p];
+                const unsigned long long e0 = __builtin_amdgcn_ballot_w64(in && v[p] == (half ? b0 : a0));
+                const unsigned long long e1 = __builtin_amdgcn_ballot_w64(in && v[p] == (half ? b1 : a1));
+                const int wa = majority_of(e0 & 0xffffffffull, e1 & 0xffffffffull, a0, a1, la);
+                const int wb = majority_of(e0 >> 32, e1 >> 32, b0, b1, lb);
+                if ((la == 0 || wa >= 0) && (lb == 0 || wb >= 0)) {  // uniform
+                    if (li == 0 && len[p] > 0) u.out[static_cast<int>(r0) + t] = half ? wb : wa;
+                    continue;
+                }
+            }
             int x[1] = {v[p]};
             bitonic_sort<32, 1, 32>(x, li);
             row_done<Use, 1, 32>(u, static_cast<int>(r0) + t, __shfl(dst_l, t, 64), len[p], x, lane);
@@ -276,12 +315,8 @@ __global__ __launch_bounds__(256) void row_sort_kernel(Use u, RowQueues q, int q
         const int c1 = lane < ln1 ? __builtin_nontemporal_load(u.col_idx + st1 + lane) : -1;
         int x0[1] = {lane < ln0 ? u.value(c0) : RS_NONE};
         int x1[1] = {lane < ln1 ? u.value(c1) : RS_NONE};
-        bitonic_sort<64, 1, 64>(x0, lane);
-        row_done<Use, 1, 64>(u, static_cast<int>(r0) + t0, __builtin_amdgcn_readlane(dst_l, t0), ln0, x0, lane);
-        if (t1 >= 0) {
-            bitonic_sort<64, 1, 64>(x1, lane);
-            row_done<Use, 1, 64>(u, static_cast<int>(r0) + t1, __builtin_amdgcn_readlane(dst_l, t1), ln1, x1, lane);
-        }
+        wave_row(u, static_cast<int>(r0) + t0, __builtin_amdgcn_readlane(dst_l, t0), ln0, x0, lane);
+        if (t1 >= 0) wave_row(u, static_cast<int>(r0) + t1, __builtin_amdgcn_readlane(dst_l, t1), ln1, x1, lane);
     }
 }
 
