@@ -122,7 +122,9 @@ int32_t ftc_build_windows(const ftc_csr *g, ftc_windows *out, void *ws, size_t w
  * forks into the side streams through `fork` after the classification and waits for `join[i]` of
  * each before the final scan, so for the caller everything still happens in stream order and nothing
  * waits on the host.  The handles are used only during the call; two calls that overlap in time need
- * two sets.  side == NULL is ftc_build_windows.
+ * two sets.  side == NULL is ftc_build_windows.  Small graphs (up to 2^18 nodes, depending on the
+ * density) are transformed by one kernel after the other on `stream`, which is faster there; the side
+ * streams are then left alone.
  */
 typedef struct {
     void *stream[3]; /* hipStream_t */

@@ -2,7 +2,8 @@
 //
 // Every row window is independent (the paper parallelises the same step over CPU threads).  How
 // a window is condensed depends on its edge count, because power-law graphs have windows of a
-// few edges next to windows of 10^5:
+// few edges next to windows of 10^5 (on graphs of at most FLAT_NODES nodes one kernel with a bitmap of all columns takes
+// windows of every size, see there):
 //   1. up to WAVE_CAP edges: one wave sorts the column ids in registers with a bitonic network
 //      (lane shuffles, no barriers), de-duplicates with a flag scan and finds every edge's rank by
 //      binary search in the unique list parked in LDS;
@@ -1435,6 +1436,285 @@ __global__ __launch_bounds__(256) void win_pack_kernel(int n_windows, const int 
         if (src[j] >= 0) __builtin_nontemporal_store(val[j], win_cols + o_first + j * 64 + lane);
 }
 
+// ---- graphs of at most FLAT_NODES nodes: one kernel for the windows of every size ------------------------------
+// A bitmap of all n columns fits into a fraction of a CU's LDS, so a window needs neither a size class nor a coarse
+// level: 256 threads set a bit per edge, scan the popcounts of the 16-byte pieces (PPT consecutive pieces per thread, their
+// order inside the thread's share turned so that 16 threads touch all banks; pads would cost a workgroup per CU), and
+// every edge's rank is its piece's prefix plus the bits below its own.  Windows above `limit` edges are queued in parts for win_flat_big_kernel: every part builds the
+// window's bitmap and ranks and writes its own edges.
+// Bound by latency: a workgroup is a chain of row start, column ids, three passes over LDS; the LDS of the bitmap (8, 16 or
+// 32 KB) says how many of them hide each other.  Measured against the size classes with their queues (us, whole build):
+//   2708 nodes, 13 thousand entries: 30 / 13 (93 / 13 with side streams); R-MAT, 65 536 nodes, 2.0 M: 119 / 56;
+//   power law, 100 000 nodes, 1.5 M: 60 / 32; power law, 200 000 nodes, 3.8 M: 84 / 64.
+constexpr int FLAT_NODES = 1 << 18;
+constexpr int FLAT_ALL_EDGES = 32768;  // graphs of at most this many entries queue nothing: the kernel walks any window itself
+
+// parts of a window above MID_CAP edges: at most cnt / (MID_CAP + 1), what the queue has room for
+__device__ __forceinline__ int flat_parts(int cnt) { return max(1, min(cnt / 8192, 64)); }
+
+// the piece of column col and what is set in it below the column
+__device__ __forceinline__ int bits_below(const uint4 &v, int col)
+{
+    const int j = (col >> 5) & 3;
+    const uint32_t word = j == 0 ? v.x : j == 1 ? v.y : j == 2 ? v.z : v.w;
+    int r = __popc(word & ((1u << (col & 31)) - 1u));
+    r += j > 0 ? __popc(v.x) : 0;
+    r += j > 1 ? __popc(v.y) : 0;
+    r += j > 2 ? __popc(v.z) : 0;
+    return r;
+}
+
+template <int WORDS>
+__global__ __launch_bounds__(256) void win_flat_kernel(int n, const int *__restrict__ row_ptr, const int *__restrict__ col_idx,
+                                                       int blk_h, int *__restrict__ edge_to_row,
+                                                       int *__restrict__ edge_to_col, int *__restrict__ uniq_count,
+                                                       int *__restrict__ tmp_cols, int limit, int4 *__restrict__ list_direct,
+                                                       int *__restrict__ counters)
+{
+    constexpr int PIECES = WORDS / 4, PPT = PIECES / 256, EPT = MID_CAP / 256;
+    static_assert(PPT >= 1, "a thread owns at least one piece");
+    __shared__ uint4 bits[PIECES];
+    __shared__ uint16_t pre[PIECES];  // unique columns before each piece (at most FLAT_ALL_EDGES in all)
+    __shared__ int rp[65];
+    __shared__ int wtot[4];
+    constexpr int TURN = PPT == 8 ? 1 : PPT == 4 ? 2 : 3;  // log2(threads whose shares cover the 64 banks once)
+    auto place = [](int piece) { return (piece & ~(PPT - 1)) | ((piece ^ (piece / PPT >> TURN)) & (PPT - 1)); };
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int w = blockIdx.x, r0 = w * blk_h, rows = min(n, r0 + blk_h) - r0;
+    const int e0 = row_ptr[r0], cnt = row_ptr[r0 + rows] - e0;  // uniform
+    if (cnt > limit) {
+        if (tid == 0) {
+            const int parts = flat_parts(cnt), at = atomicAdd(&counters[C_DIRECT], parts);
+            for (int p = 0; p < parts; ++p) list_direct[at + p] = make_int4(w, e0, cnt, p | (parts << 8));
+        }
+        return;
+    }
+    int c[EPT];
+#pragma unroll
+    for (int k = 0; k < EPT; ++k) {
+        c[k] = -1;
+        if (k * 256 < cnt) c[k] = k * 256 + tid < cnt ? col_idx[e0 + k * 256 + tid] : -1;
+    }
+#pragma unroll
+    for (int q = 0; q < PPT; ++q) bits[q * 256 + tid] = make_uint4(0u, 0u, 0u, 0u);
+    if (tid <= rows) rp[tid] = row_ptr[r0 + tid];
+    __syncthreads();
+    uint32_t *words = reinterpret_cast<uint32_t *>(bits);
+    auto set = [&](int col) {
+        uint32_t *p = &words[place(col >> 7) * 4 + ((col >> 5) & 3)];
+        atomicOr(p, 1u << (col & 31));
+    };
+#pragma unroll
+    for (int k = 0; k < EPT; ++k)
+        if (c[k] >= 0) set(c[k]);
+    for (int i = MID_CAP + tid; i < cnt; i += 256) set(col_idx[e0 + i]);
+    __syncthreads();
+    int before[PPT], mine = 0;
+#pragma unroll
+    for (int q = 0; q < PPT; ++q) {
+        const uint4 v = bits[place(tid * PPT + q)];
+        before[q] = mine;
+        mine += __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
+    }
+    const int incl = wave_inclusive_scan(mine);
+    if (lane == 63) wtot[wave] = incl;
+    __syncthreads();
+    int off = incl - mine, total = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        off += k < wave ? wtot[k] : 0;
+        total += wtot[k];
+    }
+#pragma unroll
+    for (int q = 0; q < PPT; ++q) pre[tid * PPT + q] = static_cast<uint16_t>(off + before[q]);
+    __syncthreads();
+    auto rank = [&](int col, int i) {
+        const int r = pre[col >> 7] + bits_below(bits[place(col >> 7)], col);
+        __builtin_nontemporal_store(r, edge_to_col + e0 + i);
+        tmp_cols[e0 + r] = col;  // edges with the same column store the same value
+    };
+#pragma unroll
+    for (int k = 0; k < EPT; ++k)
+        if (c[k] >= 0) rank(c[k], k * 256 + tid);
+    for (int i = MID_CAP + tid; i < cnt; i += 256) rank(col_idx[e0 + i], i);
+    for (int r = wave; r < rows; r += 4)
+        for (int e = rp[r] + lane; e < rp[r + 1]; e += 64) __builtin_nontemporal_store(r0 + r, edge_to_row + e);
+    if (tid == 0) uniq_count[w] = total;
+}
+
+// The queued windows, a part at a time.
+template <int WORDS>
+__global__ __launch_bounds__(WORDS / 4 < 1024 ? WORDS / 4 : 1024) void win_flat_big_kernel(
+    int n, const int *__restrict__ row_ptr, const int *__restrict__ col_idx, int blk_h, int *__restrict__ edge_to_row,
+    int *__restrict__ edge_to_col, int *__restrict__ uniq_count, int *__restrict__ tmp_cols, const int4 *__restrict__ list,
+    const int *__restrict__ count)
+{
+    constexpr int PIECES = WORDS / 4, NT = PIECES < 1024 ? PIECES : 1024, PPT = PIECES / NT, EB = 8;
+    __shared__ uint4 bits[PIECES];
+    __shared__ int pre[PIECES];
+    __shared__ int rp[65];
+    __shared__ int wtot[NT / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    uint32_t *words = reinterpret_cast<uint32_t *>(bits);
+    const int n_items = *count;
+    for (int item = blockIdx.x; item < n_items; item += gridDim.x) {  // uniform
+        const int4 ent = list[item];
+        const int w = ent.x, e0 = ent.y, cnt = ent.z, part = ent.w & 255, parts = ent.w >> 8;
+        const int per = ((cnt + parts - 1) / parts + NT - 1) / NT * NT;
+        const int i_lo = min(cnt, part * per), i_hi = min(cnt, i_lo + per);
+        const int r0 = w * blk_h, rows = min(n, r0 + blk_h) - r0;
+        __syncthreads();  // the previous part is done with the bitmap
+#pragma unroll
+        for (int q = 0; q < PPT; ++q) bits[q * NT + tid] = make_uint4(0u, 0u, 0u, 0u);
+        if (tid <= rows) rp[tid] = row_ptr[r0 + tid];
+        __syncthreads();
+        // EB loads in flight, unconditional, from an index clamped into the window
+        auto for_edges = [&](int lo, int hi, auto f) {
+            for (int ib = lo + tid; ib < hi; ib += NT * EB) {
+                int c[EB];
+#pragma unroll
+                for (int j = 0; j < EB; ++j) c[j] = col_idx[e0 + min(ib + j * NT, cnt - 1)];
+#pragma unroll
+                for (int j = 0; j < EB; ++j)
+                    if (ib + j * NT < hi) f(c[j], ib + j * NT);
+            }
+        };
+        for_edges(0, cnt, [&](int col, int) {
+            // the popular columns of a large window are hit thousands of times and atomics on one address serialise
+            uint32_t *p = &words[col >> 5];
+            const uint32_t m = 1u << (col & 31);
+            if ((__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) & m) == 0u) atomicOr(p, m);
+        });
+        __syncthreads();
+        int before[PPT], mine = 0;
+#pragma unroll
+        for (int q = 0; q < PPT; ++q) {
+            const uint4 v = bits[tid * PPT + q];
+            before[q] = mine;
+            mine += __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
+        }
+        const int incl = wave_inclusive_scan(mine);
+        if (lane == 63) wtot[wave] = incl;
+        __syncthreads();
+        int off = incl - mine, total = 0;
+#pragma unroll
+        for (int k = 0; k < NT / 64; ++k) {
+            off += k < wave ? wtot[k] : 0;
+            total += wtot[k];
+        }
+#pragma unroll
+        for (int q = 0; q < PPT; ++q) pre[tid * PPT + q] = off + before[q];
+        __syncthreads();
+        for_edges(i_lo, i_hi, [&](int col, int i) {
+            const int r = pre[col >> 7] + bits_below(bits[col >> 7], col);
+            __builtin_nontemporal_store(r, edge_to_col + e0 + i);
+            tmp_cols[e0 + r] = col;  // the same whichever edge, of whichever part, writes it
+        });
+        for (int r = wave; r < rows; r += NT / 64) {
+            const int b = min(rp[r + 1], e0 + i_hi);
+            for (int e = max(rp[r], e0 + i_lo) + lane; e < b; e += 64) __builtin_nontemporal_store(r0 + r, edge_to_row + e);
+        }
+        if (tid == 0 && part == 0) uniq_count[w] = total;
+    }
+}
+
+// Prefix of the unique counts, window arrays and packed lists in one kernel, for at most FINISH_WINDOWS windows: every
+// workgroup adds up the counts before its FINISH_PER windows itself (at most 16 loads per thread).
+constexpr int FINISH_WINDOWS = 4096, FINISH_PER = 2;
+
+__global__ __launch_bounds__(256) void win_finish_kernel(int n, int n_windows, int blk_h, int blk_w, const int *__restrict__ row_ptr,
+                                                         const int *__restrict__ uniq_count, const int *__restrict__ tmp_cols,
+                                                         int *__restrict__ win_col_ptr, int *__restrict__ block_partition,
+                                                         int64_t *__restrict__ summary, int *__restrict__ win_cols)
+{
+    __shared__ int su[4];
+    __shared__ long long sb[4];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int shift = (blk_w & (blk_w - 1)) == 0 ? __ffs(blk_w) - 1 : -1;
+    const int w0 = blockIdx.x * FINISH_PER, here = min(FINISH_PER, n_windows - w0);
+    const bool last = blockIdx.x == gridDim.x - 1;
+    int a = 0;
+    long long b = 0;
+    const int upto = last ? n_windows : w0;
+    for (int i = tid; i < upto; i += 256) {
+        const int u = uniq_count[i];
+        a += i < w0 ? u : 0;
+        if (last) b += tiles_of(u, blk_w, shift);
+    }
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) {
+        a += __shfl_xor(a, m, 64);
+        b += __shfl_xor(b, m, 64);
+    }
+    if (lane == 0) { su[tid >> 6] = a; sb[tid >> 6] = b; }
+    __syncthreads();
+    int pos = su[0] + su[1] + su[2] + su[3];
+    for (int k = 0; k < here; ++k) {  // uniform
+        const int w = w0 + k, u = uniq_count[w], first = row_ptr[w * blk_h];
+        if (tid == 0) {
+            win_col_ptr[w] = pos;
+            block_partition[w] = tiles_of(u, blk_w, shift);
+        }
+        for (int i = tid; i < u; i += 256 * 8) {  // eight loads in flight, from indexes clamped into the list
+            int v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = tmp_cols[first + min(i + j * 256, u - 1)];
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (i + j * 256 < u) __builtin_nontemporal_store(v[j], win_cols + pos + i + j * 256);
+        }
+        pos += u;
+    }
+    if (last && tid == 0) {
+        win_col_ptr[n_windows] = pos;
+        summary[0] = pos;
+        summary[1] = sb[0] + sb[1] + sb[2] + sb[3];
+    }
+}
+
+// Words of the bitmap of the flat kernel, 0: the size classes take the graph.  Clearing and scanning the bitmap is a fixed
+// cost per window, so windows have to hold enough edges: at 200 000 nodes the lines cross between 143 edges a window on
+// average (55 us here, 50 there) and 269 (62, 85); with the smaller bitmaps the flat kernel was ahead at every
+// density that was measured (80 edges a window: 100 000 nodes 31 / 38 us, 60 000 nodes 21 / 31 us).
+static int flat_words(int n, int nnz, int n_windows)
+{
+    if (n > FLAT_NODES || nnz == 0) return 0;
+    const int words = n <= (1 << 16) ? 2048 : n <= (1 << 17) ? 4096 : 8192;
+    return n_windows <= FINISH_WINDOWS || nnz / n_windows >= (words == 8192 ? 192 : words / 64) ? words : 0;
+}
+
+// Everything after the windows are condensed: prefix of the unique counts, window arrays, packed lists.
+static int32_t finish_windows(const ftc_csr &g, ftc_windows &w, const WinWorkspace &k, hipStream_t s)
+{
+    int32_t st;
+    if (w.n_windows <= FINISH_WINDOWS && g.nnz > 0) {
+        hipLaunchKernelGGL(win_finish_kernel, dim3(ceil_div(w.n_windows, FINISH_PER)), dim3(256), 0, s, g.n, w.n_windows,
+                           w.blk_h, w.blk_w, g.row_ptr, k.uniq_count, k.tmp_cols, w.win_col_ptr, w.block_partition,
+                           w.summary, w.win_cols);
+        return launch_status("build_windows finish");
+    }
+    const int chunks = ceil_div(w.n_windows, SCAN_CHUNK);
+    if (chunks > 1 && chunks <= SCAN_CHUNKS_MAX && g.nnz > 0) {
+        hipLaunchKernelGGL(win_chunk_sums_kernel, dim3(chunks), dim3(256), 0, s, w.n_windows, w.blk_w, k.uniq_count,
+                           k.chunk_uniq, k.chunk_blocks);
+        hipLaunchKernelGGL(win_chunk_scan_kernel, dim3(chunks), dim3(256), 0, s, w.n_windows, w.blk_w, k.uniq_count,
+                           k.chunk_uniq, k.chunk_blocks, w.win_col_ptr, w.block_partition, w.summary, k.pack_win);
+        st = launch_status("build_windows scan (chunks)");
+        if (st != FTC_OK) return st;
+    } else {
+        hipLaunchKernelGGL(win_scan_kernel, dim3(1), dim3(1024), 0, s, w.n_windows, w.blk_w, k.uniq_count,
+                           w.win_col_ptr, w.block_partition, w.summary);
+        st = launch_status("build_windows scan");
+        if (st != FTC_OK) return st;
+        if (g.nnz == 0) return FTC_OK;
+        hipLaunchKernelGGL(win_pack_plan_kernel, dim3((w.n_windows + 255) / 256), dim3(256), 0, s, w.n_windows, w.win_col_ptr,
+                           k.pack_win);
+    }
+    hipLaunchKernelGGL(win_pack_kernel, dim3(ceil_div(g.nnz, 4 * PACK_PER_WAVE)), dim3(256), 0, s,
+                       w.n_windows, g.row_ptr, w.blk_h, w.win_col_ptr, k.pack_win, k.tmp_cols, w.win_cols);
+    return launch_status("build_windows pack");
+}
+
 // The classes of windows are condensed by different kernels, none of which depends on another and each of
 // which fills only part of the GPU.  With three side streams and four events from the caller they run side
 // by side after the classification: the caller's stream forks into the side streams with an event and
@@ -1449,6 +1729,7 @@ int32_t launch_build_windows(const ftc_csr &g, ftc_windows &w, void *ws, size_t 
                            w.block_partition, w.summary);
         return launch_status("build_windows scan");
     }
+    const int flat = flat_words(g.n, g.nnz, w.n_windows);
     const int hub_thr = hub_threshold(g.n, g.nnz);
     const bool direct = (static_cast<int64_t>(g.n) + (1 << WB_RANGE_LOG2) - 1) >> WB_RANGE_LOG2 <= DIRECT_MAX_RANGES;
     const bool queued = g.nnz > WAVE_CAP;  // otherwise no window can be queued
@@ -1461,6 +1742,27 @@ int32_t launch_build_windows(const ftc_csr &g, ftc_windows &w, void *ws, size_t 
         n_cu < 1) {
         (void)hipGetLastError();
         n_cu = 256;
+    }
+    if (flat) {
+        const int limit = g.nnz > FLAT_ALL_EDGES ? MID_CAP : FLAT_ALL_EDGES;
+        if (g.nnz > limit) hipLaunchKernelGGL(win_clear_kernel, dim3(1), dim3(64), 0, s, k.counters);
+        const int big = k.cap_direct < 2 * n_cu ? k.cap_direct : 2 * n_cu;
+#define FTC_FLAT(W)                                                                                                    \
+    do {                                                                                                               \
+        hipLaunchKernelGGL(win_flat_kernel<W>, dim3(w.n_windows), dim3(256), 0, s, g.n, g.row_ptr, g.col_idx, w.blk_h, \
+                           w.edge_to_row, w.edge_to_col, k.uniq_count, k.tmp_cols, limit, k.list_direct, k.counters);  \
+        if (g.nnz > limit)                                                                                             \
+            hipLaunchKernelGGL(win_flat_big_kernel<W>, dim3(big), dim3(W / 4 < 1024 ? W / 4 : 1024), 0, s, g.n,        \
+                               g.row_ptr, g.col_idx, w.blk_h, w.edge_to_row, w.edge_to_col, k.uniq_count, k.tmp_cols,  \
+                               k.list_direct, k.counters + C_DIRECT);                                                  \
+    } while (0)
+        if (flat == 2048) FTC_FLAT(2048);
+        else if (flat == 4096) FTC_FLAT(4096);
+        else FTC_FLAT(8192);
+#undef FTC_FLAT
+        st = launch_status("build_windows flat");
+        if (st != FTC_OK) return st;
+        return finish_windows(g, w, k, s);
     }
     if (queued) {
         hipLaunchKernelGGL(win_clear_kernel, dim3(1), dim3(64), 0, s, k.counters);
@@ -1572,26 +1874,7 @@ int32_t launch_build_windows(const ftc_csr &g, ftc_windows &w, void *ws, size_t 
         }
     }
     if (st != FTC_OK) return st;
-    const int chunks = ceil_div(w.n_windows, SCAN_CHUNK);
-    if (chunks > 1 && chunks <= SCAN_CHUNKS_MAX && g.nnz > 0) {
-        hipLaunchKernelGGL(win_chunk_sums_kernel, dim3(chunks), dim3(256), 0, s, w.n_windows, w.blk_w, k.uniq_count,
-                           k.chunk_uniq, k.chunk_blocks);
-        hipLaunchKernelGGL(win_chunk_scan_kernel, dim3(chunks), dim3(256), 0, s, w.n_windows, w.blk_w, k.uniq_count,
-                           k.chunk_uniq, k.chunk_blocks, w.win_col_ptr, w.block_partition, w.summary, k.pack_win);
-        st = launch_status("build_windows scan (chunks)");
-        if (st != FTC_OK) return st;
-    } else {
-        hipLaunchKernelGGL(win_scan_kernel, dim3(1), dim3(1024), 0, s, w.n_windows, w.blk_w, k.uniq_count,
-                           w.win_col_ptr, w.block_partition, w.summary);
-        st = launch_status("build_windows scan");
-        if (st != FTC_OK) return st;
-        if (g.nnz == 0) return FTC_OK;
-        hipLaunchKernelGGL(win_pack_plan_kernel, dim3((w.n_windows + 255) / 256), dim3(256), 0, s, w.n_windows, w.win_col_ptr,
-                           k.pack_win);
-    }
-    hipLaunchKernelGGL(win_pack_kernel, dim3(ceil_div(g.nnz, 4 * PACK_PER_WAVE)), dim3(256), 0, s,
-                       w.n_windows, g.row_ptr, w.blk_h, w.win_col_ptr, k.pack_win, k.tmp_cols, w.win_cols);
-    return launch_status("build_windows pack");
+    return finish_windows(g, w, k, s);
 }
 
 }  // namespace ftc

@@ -935,3 +935,40 @@ def test_short_ranges_on_small_graphs(oracle, n, deg):
     h = H64 / np.maximum(np.linalg.norm(H64, axis=1, keepdims=True), 1e-12)
     rows = np.repeat(np.arange(n), np.diff(g.row_ptr))
     assert np.max(np.abs(c.cpu().double().numpy() - np.einsum("ij,ij->i", h[rows], h[g.col_idx]))) < 1e-5
+
+
+# ------------------------------------------------------------------ window build: one bitmap of all columns, or size classes
+@pytest.mark.parametrize("n,blk_h", [(65_536, 16), (65_537, 16), (131_072, 16), (131_073, 16), (262_144, 16), (262_145, 16),
+                                     (40_000, 1), (30_000, 64), (150_000, 5)])
+def test_window_sizes_on_both_sides_of_the_bitmap_rule(oracle, n, blk_h):
+    """Windows of every size at which the build changes its kernel, with duplicate columns, first and last column
+    included, on graphs at the edges of the bitmap sizes; with and without side streams."""
+    rng = np.random.default_rng(n + blk_h)
+    n_win = (n + blk_h - 1) // blk_h
+    sizes = [0, 1, 63, 64, 65, 255, 256, 257, 1024, 1025, 2048, 2049, 4095, 4096, 4097, 8191, 8192, 8193, 16_384, 16_385,
+             33_000, 70_000]
+    per_row = np.full(n, 12, dtype=np.int64)
+    for i, w in enumerate(rng.choice(n_win, size=len(sizes), replace=False)):
+        r0, r1 = w * blk_h, min(n, (w + 1) * blk_h)
+        cuts = np.sort(rng.integers(0, sizes[i] + 1, size=r1 - r0 - 1))
+        per_row[r0:r1] = np.diff(np.r_[0, cuts, sizes[i]])
+    row_ptr = np.zeros(n + 1, dtype=np.int32)
+    row_ptr[1:] = np.cumsum(per_row)
+    col = rng.integers(0, n, size=int(row_ptr[-1])).astype(np.int32)
+    col[rng.integers(0, col.size, size=2000)] = 0
+    col[rng.integers(0, col.size, size=2000)] = n - 1
+    g = synth.Graph(n, row_ptr, col, "sizes")
+    say(f"window sizes n={n} blk_h={blk_h} nnz={g.nnz}")
+    ref = oracle.build_windows(g.row_ptr, g.col_idx, blk_h, 8)
+    dg = dev_graph(g)
+    check_windows(B.ftc_build_windows(dg, blk_h=blk_h), ref)
+    check_windows(B.ftc_build_windows_concurrent(dg, B.SideStreams(), blk_h=blk_h), ref)
+
+
+def test_one_window_holds_a_small_graph_whole(oracle):
+    """All 30 000 entries in the first window, the others empty: nothing is queued at this size."""
+    n = 5000
+    row_ptr = np.full(n + 1, 30_000, dtype=np.int32)
+    row_ptr[:17] = np.linspace(0, 30_000, 17).astype(np.int32)
+    g = synth.Graph(n, row_ptr, np.random.default_rng(1).integers(0, n, size=30_000).astype(np.int32), "one window")
+    check_windows(B.ftc_build_windows(dev_graph(g)), oracle.build_windows(g.row_ptr, g.col_idx))
