@@ -213,9 +213,23 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(int n, const uint16_t *_
 {
     constexpr int KP = KS * 32 + 8;  // padded k extent of a W^T row (keeps 16-byte alignment, spreads banks)
     __shared__ __attribute__((aligned(16))) uint16_t Wt[NT * 16 * KP];
-    for (int t = threadIdx.x; t < NT * 16 * KS * 32; t += 256) {
-        const int nn = t / (KS * 32), k = t % (KS * 32);
-        Wt[nn * KP + k] = (nn < d_out && k < d_in) ? W[static_cast<size_t>(k) * d_out + nn] : uint16_t(0);
+    // W is read along its rows (consecutive threads, consecutive columns), all of a thread's loads issued together from clamped
+    // addresses: one after the other they cost every workgroup 6 us before its first row (100 000 x 128 -> 32: 16.1 us
+    // against 10.6; 2^20 x 128 -> 32: 89 against 78)
+    constexpr int PER = NT * 16 * KS * 32 / 256, BATCH = PER <= 16 ? PER : PER % 16 == 0 ? 16 : 8;
+    static_assert(PER % BATCH == 0, "whole batches");
+    for (int t0 = threadIdx.x; t0 < NT * 16 * KS * 32; t0 += 256 * BATCH) {
+        uint16_t wv[BATCH];
+#pragma unroll
+        for (int j = 0; j < BATCH; ++j) {
+            const int k = (t0 + j * 256) / (NT * 16), nn = (t0 + j * 256) % (NT * 16);
+            wv[j] = W[(nn < d_out && k < d_in) ? static_cast<size_t>(k) * d_out + nn : 0];
+        }
+#pragma unroll
+        for (int j = 0; j < BATCH; ++j) {
+            const int k = (t0 + j * 256) / (NT * 16), nn = (t0 + j * 256) % (NT * 16);
+            Wt[nn * KP + k] = (nn < d_out && k < d_in) ? wv[j] : uint16_t(0);
+        }
     }
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -332,10 +346,18 @@ __global__ __launch_bounds__(256) void gemm_mfma_wide_kernel(int n, const uint16
         for (int kc0 = 0; kc0 < d_in; kc0 += WIDE_KC) {
             __syncthreads();  // the previous chunk (or batch) has been consumed
             const int nn_n = nt_n * 16;  // only the column tiles that are used
-            for (int t = threadIdx.x; t < nn_n * WIDE_KC; t += 256) {
-                const int k = t / nn_n, nn = t % nn_n;  // consecutive threads read consecutive columns of W
-                Wt[nn * KP + k] = (nn < d_out && kc0 + k < d_in) ? W[static_cast<size_t>(kc0 + k) * w_ld + col0 + nn]
-                                                                 : uint16_t(0);
+            for (int t0 = threadIdx.x; t0 < nn_n * WIDE_KC; t0 += 256 * 16) {  // (nn_n * WIDE_KC is a multiple of 256 * 16)
+                uint16_t wv[16];  // (100 000 x 1432 -> 16: 106 us with a load at a time, 93 like this)
+#pragma unroll
+                for (int j = 0; j < 16; ++j) {
+                    const int t = t0 + j * 256, k = t / nn_n, nn = t % nn_n;  // consecutive threads read consecutive columns of W
+                    wv[j] = W[(nn < d_out && kc0 + k < d_in) ? static_cast<size_t>(kc0 + k) * w_ld + col0 + nn : 0];
+                }
+#pragma unroll
+                for (int j = 0; j < 16; ++j) {
+                    const int t = t0 + j * 256, k = t / nn_n, nn = t % nn_n;
+                    Wt[nn * KP + k] = (nn < d_out && kc0 + k < d_in) ? wv[j] : uint16_t(0);
+                }
             }
             __syncthreads();
 #pragma unroll
@@ -432,7 +454,7 @@ int32_t launch_gemm(int n, const void *X, int ldx, int dt, int d_in, const void 
         if (done) return launch_status("update_gemm mfma");
         // beyond the register-resident shapes, or a width that is no multiple of 8 in padded rows; few rows are left to the
         // general kernel, which splits the contraction over the waves (2708 x 1432 -> 16: 44 us here, 14 us there;
-        // 100 000 rows: 104 us here, 115 us there)
+        // 100 000 rows: 93 us here, 115 us there)
         if ((d_in > 256 || d_out > 64 || !fast) && n > GEMM_SPLIT_ROWS) {
             if (dt == FTC_F16) gemm_mfma_wide_t<F16>(n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi, s);
             else gemm_mfma_wide_t<BF16>(n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi, s);
