@@ -243,8 +243,8 @@ int32_t ftc_gcn_layer(const ftc_csr *g, const ftc_windows *w, const float *vals,
 /*
  * AGNN propagation layer forward: s_ij = beta * cos(h_i, h_j) on the stored entries,
  * P = edge softmax of s, out = P * H (H not normalised).  edge_p, when not NULL,
- * receives P (nnz floats).  Without edge_p (and with a window index) scores, softmax and
- * aggregation run fused in one pass over the edges; the softmax is then shifted by |beta|,
+ * receives P (nnz floats).  With a window index scores, softmax and aggregation run fused in one
+ * pass over the edges (P follows from the pass's weights); the softmax is then shifted by |beta|,
  * an upper bound of every score, instead of by the row maximum (same result); for |beta| >= 43 the
  * unfused chain with the row-wise softmax is used.
  * row_z, when not NULL, receives the softmax denominators of that pass,

@@ -13,6 +13,11 @@
 // (a second DPP reduction in the lane group), so the pass needs no array of inverse norms and no
 // random 4-byte gather per edge.
 //
+// When the caller wants the probabilities the pass also writes the weight of every entry, parked in LDS over the column
+// ids that have been used, and a second kernel divides by the rows' sums: one gather of H per entry instead of the two of
+// scores, softmax and aggregation one after the other (fp16, 32 columns, power law, 200 000 nodes, 3.8 M entries: 127 us
+// against 89).
+//
 // Work partition, run structure and the handling of rows cut by run / wave boundaries are
 // those of the edge-balanced SpMM (spmm_seg.hip): 512 edges per wave (fewer on small graphs) staged in LDS, groups of
 // LPR lanes walk contiguous runs, complete rows are stored from registers, cut rows are summed
@@ -41,8 +46,9 @@ size_t agnn_fused_ws(int nnz, int D, bool least)
     return ag_carry_ws(nnz, least ? SEG_R : seg_range(nnz, SEG_AGNN), dp);
 }
 
-// KEEP: also write what the backward pass needs (row_z, out32); compiled out of the inference kernel.
-template <class T, int VEC, int LPR, bool KEEP, int AG_R>
+// MODE 0: inference.  1: also write what the backward pass needs (row_z, out32).  2: also write the weight w_ij of every entry
+// (edge_w) and row_z; agnn_edge_p_kernel turns the weights into probabilities once every row's sum is known.
+template <class T, int VEC, int LPR, int MODE, int AG_R>
 __global__ __launch_bounds__(256) void agnn_fused_kernel(int nnz, int n_ranges, const int *__restrict__ row_ptr,
                                                          const int *__restrict__ col_idx,
                                                          const int *__restrict__ edge_to_row,
@@ -50,8 +56,9 @@ __global__ __launch_bounds__(256) void agnn_fused_kernel(int nnz, int n_ranges, 
                                                          void *__restrict__ out, int ldo, int odt,
                                                          float *__restrict__ carry, int *__restrict__ carry_tail_row,
                                                          float *__restrict__ row_z, float *__restrict__ out32,
-                                                         int ld32)
+                                                         int ld32, float *__restrict__ edge_w)
 {
+    constexpr bool KEEP = MODE != 0;
     constexpr int NG = 64 / LPR;
     constexpr int RUN = AG_R / NG;
     constexpr int RP = AG_R + NG;
@@ -103,23 +110,43 @@ __global__ __launch_bounds__(256) void agnn_fused_kernel(int nnz, int n_ranges, 
     const bool has = rs < n_valid;
     const bool live = sub * VEC < D;
     const float absb = fabsf(beta);
+    const float beta2 = beta * 1.44269504f;  // log2(e) = 1.44269502162933 (its nearest fp32) + 1.92596299e-8
+    const float beta2_rest = fmaf(beta, 1.92596299e-8f, fmaf(beta, 1.44269504f, -beta2));
     float acc[VEC], hacc[VEC];
 #pragma unroll
     for (int j = 0; j < VEC; ++j) { acc[j] = 0.f; hacc[j] = 0.f; }
     RawVec<T, VEC> xi;  // slice of H[i,:] of the current row, as loaded
     zero_raw(xi);
     float z = 0.f, hz = 0.f, ri = 0.f;
+    // MODE 2 sums every other entry apart and joins the halves in the quotient (its two fma round about as often as one sum):
+    // that is what makes the output as exact as the three kernels', whose weights were divided by z before they were summed.
+    constexpr int ODD = MODE == 2 ? VEC : 1;
+    float odd[ODD], odd_z = 0.f;
+#pragma unroll
+    for (int j = 0; j < ODD; ++j) odd[j] = 0.f;
+    auto join_odd = [&]() {  // for a piece of a row
+        if constexpr (MODE == 2) {
+#pragma unroll
+            for (int j = 0; j < VEC; ++j) acc[j] += odd[j];
+            z += odd_z;
+        }
+    };
     bool have_head = false, head_closed = false, have_tail = false;
     int head_row = -1, cur = -1;
     bool first = true;
     const int left_row = !has ? -2 : (rs == 0 ? prev_row : s_row[rs - 1 + g - 1]);
 
     auto direct_store = [&](int row) {
+        if constexpr (MODE == 2) z += odd_z;
         if (live) {
             const float inv = __builtin_amdgcn_rcpf(z);  // v_rcp_f32: one ulp, one instruction
+            const float rest = fmaf(-z, inv, 1.f) * inv;  // what the reciprocal is short of
             float o[VEC];
 #pragma unroll
-            for (int j = 0; j < VEC; ++j) o[j] = acc[j] * inv;
+            for (int j = 0; j < VEC; ++j) {
+                if constexpr (MODE == 2) o[j] = fmaf(acc[j], inv, fmaf(odd[j], inv, (acc[j] + odd[j]) * rest));
+                else o[j] = acc[j] * inv;
+            }
             store_vec_nt<VEC>(out, static_cast<int64_t>(row) * ldo + sub * VEC, odt, o);
             if constexpr (KEEP)
                 if (out32) store_vec<VEC>(out32, static_cast<int64_t>(row) * ld32 + sub * VEC, FTC_F32, o);  // unrounded copy
@@ -161,6 +188,7 @@ __global__ __launch_bounds__(256) void agnn_fused_kernel(int nnz, int n_ranges, 
             if (need[k]) {  // a new row starts: close the segment of the previous one
                 if (cur >= 0) {
                     if (first && left_row == cur) {
+                        join_odd();
 #pragma unroll
                         for (int j = 0; j < VEC; ++j) hacc[j] = acc[j];
                         hz = z;
@@ -174,6 +202,11 @@ __global__ __launch_bounds__(256) void agnn_fused_kernel(int nnz, int n_ranges, 
 #pragma unroll
                 for (int j = 0; j < VEC; ++j) acc[j] = 0.f;
                 z = 0.f;
+                if constexpr (MODE == 2) {
+#pragma unroll
+                    for (int j = 0; j < VEC; ++j) odd[j] = 0.f;
+                    odd_z = 0.f;
+                }
                 xi = xs[k];
                 const float q = group_sum_dpp<LPR>(dot_raw<T, VEC>(xi, xi, 0.f));  // the group's lanes branch together
                 ri = __frsqrt_rn(fmaxf(q, 1e-24f));  // = 1 / max(||h_i||, 1e-12)
@@ -182,12 +215,28 @@ __global__ __launch_bounds__(256) void agnn_fused_kernel(int nnz, int n_ranges, 
             const float qj = group_sum_dpp<LPR>(dot_raw<T, VEC>(y[k], y[k], 0.f));
             if (r[k] >= 0) {
                 const float rj = __frsqrt_rn(fmaxf(qj, 1e-24f));
-                const float wgt = __expf(beta * ri * rj * d - absb);
+                float wgt;
+                if constexpr (MODE == 2) {  // in powers of two: the large part of the exponent is rounded once instead of twice
+                    const float cosine = ri * rj * d;
+                    wgt = __builtin_amdgcn_exp2f(fmaf(beta2_rest, cosine, fmaf(beta2, cosine, -fabsf(beta2))));
+                } else {
+                    wgt = __expf(beta * ri * rj * d - absb);
+                }
                 float yf[VEC];
                 unpack<T, VEC>(y[k], yf);
 #pragma unroll
-                for (int j = 0; j < VEC; ++j) acc[j] = fmaf(wgt, yf[j], acc[j]);
-                z += wgt;
+                for (int j = 0; j < VEC; ++j) {
+                    if constexpr (MODE == 2) {
+                        float &a = (k & 1) ? odd[j] : acc[j];
+                        a = fmaf(wgt, yf[j], a);
+                    } else {
+                        acc[j] = fmaf(wgt, yf[j], acc[j]);
+                    }
+                }
+                if (MODE == 2 && (k & 1)) odd_z += wgt;
+                else z += wgt;
+                if constexpr (MODE == 2)
+                    if (sub == 0) s_col[b + k + g] = __float_as_int(wgt);  // the entry's column has been used
             }
         }
     }
@@ -197,6 +246,7 @@ __global__ __launch_bounds__(256) void agnn_fused_kernel(int nnz, int n_ranges, 
         else right_row = next_row;
         const bool right_open = right_row == cur;
         if (first && left_row == cur) {
+            join_odd();
 #pragma unroll
             for (int j = 0; j < VEC; ++j) hacc[j] = acc[j];
             hz = z;
@@ -204,10 +254,19 @@ __global__ __launch_bounds__(256) void agnn_fused_kernel(int nnz, int n_ranges, 
         } else if (!right_open) {
             direct_store(cur);
         } else {
+            join_odd();
             have_tail = true;
         }
     }
     __syncthreads();  // staged indices are dead: the LDS is reused for partials
+    if constexpr (MODE == 2) {
+#pragma unroll
+        for (int j = 0; j < AG_R / 64; ++j) {
+            const int i = j * 64 + lane;
+            if (i < n_valid) edge_w[base + i] = __int_as_float(s_col[i + i / RUN]);
+        }
+        __syncthreads();
+    }
 
     float *part = reinterpret_cast<float *>(smem) + wave * 2 * NG * DPZ;
     if (have_head) {
@@ -387,19 +446,40 @@ __global__ __launch_bounds__(256) void agnn_fused_fixup_kernel(int n, int n_rang
     }
 }
 
+// p[e] = w[e] / z[row of e], in place, four entries per thread and 64 apart in the wave
+__global__ __launch_bounds__(256) void agnn_edge_p_kernel(int nnz, const int *__restrict__ edge_to_row,
+                                                          const float *__restrict__ row_z, float *__restrict__ edge_w)
+{
+    const int64_t e0 = static_cast<int64_t>(blockIdx.x) * 1024 + (threadIdx.x >> 6) * 256 + (threadIdx.x & 63);
+    float a[4], z[4];
+    int r[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int64_t e = min(e0 + 64 * k, static_cast<int64_t>(nnz) - 1);
+        r[k] = __builtin_nontemporal_load(edge_to_row + e);
+        a[k] = edge_w[e];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) z[k] = row_z[r[k]];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if (e0 + 64 * k < nnz) __builtin_nontemporal_store(a[k] / z[k], edge_w + e0 + 64 * k);
+}
+
 template <class T, int R>
 static void launch_agnn_t(int vec, int lpr, unsigned grid, hipStream_t s, int nnz, int n_ranges, const ftc_csr &g,
                           const int *e2r, const void *H, int ld, int D, float beta, void *out,
-                          int ldo, int odt, float *carry, int *tail_row, float *row_z, float *out32, int ld32)
+                          int ldo, int odt, float *carry, int *tail_row, float *row_z, float *out32, int ld32,
+                          float *edge_w)
 {
     constexpr int VM = T::VEC;
-#define FTC_AG(V, L)                                                                                                  \
-    if (row_z || out32)                                                                                               \
-        hipLaunchKernelGGL((agnn_fused_kernel<T, V, L, true, R>), dim3(grid), dim3(256), 0, s, nnz, n_ranges, g.row_ptr, \
-                           g.col_idx, e2r, H, ld, D, beta, out, ldo, odt, carry, tail_row, row_z, out32, ld32);       \
-    else                                                                                                              \
-        hipLaunchKernelGGL((agnn_fused_kernel<T, V, L, false, R>), dim3(grid), dim3(256), 0, s, nnz, n_ranges,           \
-                           g.row_ptr, g.col_idx, e2r, H, ld, D, beta, out, ldo, odt, carry, tail_row, row_z, out32, ld32)
+#define FTC_AG1(V, L, M)                                                                                              \
+    hipLaunchKernelGGL((agnn_fused_kernel<T, V, L, M, R>), dim3(grid), dim3(256), 0, s, nnz, n_ranges, g.row_ptr,     \
+                       g.col_idx, e2r, H, ld, D, beta, out, ldo, odt, carry, tail_row, row_z, out32, ld32, edge_w)
+#define FTC_AG(V, L)                         \
+    if (edge_w) FTC_AG1(V, L, 2);            \
+    else if (row_z || out32) FTC_AG1(V, L, 1); \
+    else FTC_AG1(V, L, 0)
     if (vec == VM) {
         if (lpr == 4) { FTC_AG(VM, 4); }
         else if (lpr == 8) { FTC_AG(VM, 8); }
@@ -411,12 +491,13 @@ static void launch_agnn_t(int vec, int lpr, unsigned grid, hipStream_t s, int nn
         FTC_AG(VM / 4, 4);
     }
 #undef FTC_AG
+#undef FTC_AG1
 }
 
 // Caller has checked: window index present, seg_shape() accepts (dt, D), rows of H and out 16-byte
 // aligned, workspace of agnn_fused_ws(.., least) bytes.
 int32_t launch_agnn_fused(const ftc_csr &g, const ftc_windows &w, const void *H, int ld, int dt, int D,
-                          float beta, void *out, int ldo, int odt, float *row_z, float *out32, int ld32, void *ws,
+                          float beta, void *out, int ldo, int odt, float *row_z, float *out32, int ld32, float *edge_w, void *ws,
                           size_t ws_bytes, hipStream_t s)
 {
     int vec = 0, lpr = 0;
@@ -432,11 +513,11 @@ int32_t launch_agnn_fused(const ftc_csr &g, const ftc_windows &w, const void *H,
 #define FTC_AGR(T)                                                                                                       \
     do {                                                                                                                 \
         if (r == SEG_R) launch_agnn_t<T, SEG_R>(vec, lpr, grid, s, g.nnz, n_ranges, g, w.edge_to_row, H, ld, D, beta,    \
-                                                out, ldo, odt, carry, tail_row, row_z, out32, ld32);                     \
+                                                out, ldo, odt, carry, tail_row, row_z, out32, ld32, edge_w);             \
         else if (r == 256) launch_agnn_t<T, 256>(vec, lpr, grid, s, g.nnz, n_ranges, g, w.edge_to_row, H, ld, D, beta,   \
-                                                 out, ldo, odt, carry, tail_row, row_z, out32, ld32);                    \
+                                                 out, ldo, odt, carry, tail_row, row_z, out32, ld32, edge_w);            \
         else launch_agnn_t<T, 128>(vec, lpr, grid, s, g.nnz, n_ranges, g, w.edge_to_row, H, ld, D, beta, out, ldo, odt,   \
-                                  carry, tail_row, row_z, out32, ld32);                                                  \
+                                  carry, tail_row, row_z, out32, ld32, edge_w);                                          \
     } while (0)
         if (dt == FTC_F32) FTC_AGR(F32);
         else if (dt == FTC_F16) FTC_AGR(F16);
@@ -461,6 +542,9 @@ int32_t launch_agnn_fused(const ftc_csr &g, const ftc_windows &w, const void *H,
         FTC_FX(1) FTC_FX(2) FTC_FX(4) FTC_FX(8) FTC_FX(16) FTC_FX(32) FTC_FX(64)
     }
 #undef FTC_FX
+    if (edge_w && g.nnz > 0)
+        hipLaunchKernelGGL(agnn_edge_p_kernel, dim3(ceil_div(g.nnz, 1024)), dim3(256), 0, s, g.nnz, w.edge_to_row, row_z,
+                           edge_w);
     return launch_status("agnn_fused fixup");
 }
 

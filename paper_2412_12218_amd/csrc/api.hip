@@ -446,7 +446,9 @@ static size_t agnn_unfused_bytes(int32_t n, int32_t nnz, int32_t D, bool least)
 static size_t agnn_layer_ws(int32_t n, int32_t nnz, int32_t D, bool least)
 {
     if (n < 0 || nnz < 0 || D < 1) return 0;
-    const size_t a = agnn_unfused_bytes(n, nnz, D, least), b = agnn_fused_ws(nnz, D, least);
+    // the single pass, and the rows' sums when the probabilities are asked for
+    const size_t a = agnn_unfused_bytes(n, nnz, D, least);
+    const size_t b = agnn_fused_ws(nnz, D, least) + (least ? 0 : align_up(static_cast<size_t>(n) * sizeof(float), 256));
     return a > b ? a : b;
 }
 
@@ -469,7 +471,7 @@ int32_t ftc_agnn_layer(const ftc_csr *g, const ftc_windows *w, const void *H, in
         return fail(FTC_EALIGN, "ftc_agnn_layer: workspace must be 256-byte aligned");
     char *p = static_cast<char *>(ws);
 
-    // One pass over the edges when the probabilities are not asked for and the vector path applies.
+    // One pass over the edges when the vector path applies.
     int vec, lpr;
     const bool rows16 = aligned16(H) && aligned16(out) && (static_cast<int64_t>(ld) * elem_size(dtype)) % 16 == 0 &&
                         (static_cast<int64_t>(ldo) * elem_size(out_dtype)) % 16 == 0;
@@ -486,8 +488,17 @@ int32_t ftc_agnn_layer(const ftc_csr *g, const ftc_windows *w, const void *H, in
     const bool beta_ok = fabsf(beta) < AGNN_FUSED_MAX_BETA;
     if (!edge_p && w && beta_ok && (g->nnz > 0 || keep) && path != FTC_PATH_MFMA && rows16 &&
         seg_shape(dtype, D, &vec, &lpr))
-        return launch_agnn_fused(*g, *w, H, ld, dtype, D, beta, out, ldo, out_dtype, row_z, out_f32, ld_f32, p,
+        return launch_agnn_fused(*g, *w, H, ld, dtype, D, beta, out, ldo, out_dtype, row_z, out_f32, ld_f32, nullptr, p,
                                  ws_bytes, static_cast<hipStream_t>(stream));
+    // The probabilities come from the same pass; the rows' sums take the end of the workspace.  (A workspace without room for
+    // them gets the three kernels below.)
+    const size_t z_bytes = align_up(static_cast<size_t>(g->n) * sizeof(float), 256);
+    if (edge_p && !keep && w && beta_ok && g->nnz > 0 && path != FTC_PATH_MFMA && rows16 && seg_shape(dtype, D, &vec, &lpr) &&
+        ws_bytes >= agnn_fused_ws(g->nnz, D, true) + z_bytes) {
+        const size_t at = (ws_bytes - z_bytes) / 256 * 256;
+        return launch_agnn_fused(*g, *w, H, ld, dtype, D, beta, out, ldo, out_dtype, reinterpret_cast<float *>(p + at), nullptr, 0,
+                                 edge_p, p, at, static_cast<hipStream_t>(stream));
+    }
     if (keep)
         return fail(FTC_EUNSUPPORTED,
                     "ftc_agnn_layer: |beta| < 43 is needed, and row_z and out_f32 come from the single-pass route only (window index, no edge_p, not "

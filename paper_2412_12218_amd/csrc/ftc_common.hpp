@@ -87,8 +87,8 @@ int32_t launch_sddmm_edges(const ftc_csr &g, const ftc_windows &w, const void *X
                            bool cosine, hipStream_t s);
 size_t agnn_fused_ws(int nnz, int D, bool least);
 int32_t launch_agnn_fused(const ftc_csr &g, const ftc_windows &w, const void *H, int ld, int dt, int D,
-                          float beta, void *out, int ldo, int odt, float *row_z, float *out32, int ld32, void *ws,
-                          size_t ws_bytes, hipStream_t s);
+                          float beta, void *out, int ldo, int odt, float *row_z, float *out32, int ld32, float *edge_w,
+                          void *ws, size_t ws_bytes, hipStream_t s);
 bool agnn_backward_fused_shape(int dtype, int D);
 size_t agnn_backward_fused_ws(int n, int nnz, int D, bool least);
 int32_t launch_agnn_backward_fused(const ftc_csr &g, const ftc_windows &w, const void *H, const void *dY, int ld, int dt,

@@ -972,3 +972,28 @@ def test_one_window_holds_a_small_graph_whole(oracle):
     row_ptr[:17] = np.linspace(0, 30_000, 17).astype(np.int32)
     g = synth.Graph(n, row_ptr, np.random.default_rng(1).integers(0, n, size=30_000).astype(np.int32), "one window")
     check_windows(B.ftc_build_windows(dev_graph(g)), oracle.build_windows(g.row_ptr, g.col_idx))
+
+
+@pytest.mark.parametrize("dtype,D", [(F16, 32), (BF16, 64), (F32, 8), (F32, 128), (F16, 24)])
+@pytest.mark.parametrize("name", ["hub", "cfg2s", "cfg3"])
+def test_attention_weights_of_the_single_pass(oracle, graphs, name, dtype, D):
+    """P and the aggregated rows from one pass (hub rows, empty rows, duplicates; ranges of 128 to 512 entries), and from the
+    three kernels, which a workspace without room for the rows' sums still gets."""
+    g = synth.config_graph(3) if name == "cfg3" else graphs[name]
+    if name == "cfg3" and D != 32:
+        return
+    dg = dev_graph(g)
+    win = B.ftc_build_windows(dg)
+    Hd, H64 = quantise(synth.normal_features(g.n, D, seed=D), dtype)
+    for beta in (1.0, -2.5, 12.0):
+        ref, ab, p_ref = oracle.agnn_layer(g.row_ptr, g.col_idx, H64, beta)
+        for least in (False, True):
+            p = torch.full((g.nnz,), -1.0, dtype=F32, device="cuda")
+            ws = None
+            if least:                               # scores (4 bytes), softmax and SpMM workspaces of ranges of 512 entries
+                ws = B._workspace(B.lib().ftc_sddmm_workspace_bytes(g.n, g.nnz, D) + 4 * g.nnz + 2048 + g.n // 16 +
+                                  B.lib().ftc_edge_softmax_workspace_bytes(g.n, g.nnz) +
+                                  (g.nnz // 512 + 1) * (8 * (max(D, 32) + 4) + 8), "cuda")
+            out = B.ftc_agnn_layer(dg, win, Hd, beta=beta, edge_p=p, ws=ws)
+            say(f"attention {name} {dtype} D={D} beta={beta} least={least}: p {rel_err(p, p_ref):.2e} out {norm_err(out, ref, ab):.2e}")
+            assert rel_err(p, p_ref) < P_TOL and norm_err(out, ref, ab) < 1e-5
