@@ -27,14 +27,13 @@
 // win_cols.  The kernels of the size classes are independent: with side streams from the caller they
 // run side by side.
 #include "ftc_common.hpp"
-
+#include "window_queue.hpp"
 
 namespace ftc {
 
 constexpr int WAVE_CAP = 256;       // edges per window sorted by a single wave in registers
 constexpr int B1_CAP = 1024;        // edges per window of the three size classes of the wave-level bitmap kernel
 constexpr int B2_CAP = 2048;
-constexpr int MID_CAP = 4096;
 constexpr int B4_CAP = 16384;       // ... and of the same kernel with sixteen waves per window
 constexpr int DIRECT_MAX_RANGES = 4; // graphs of up to this many 2^20-column ranges: every window above MID_CAP edges takes
                                      // the direct-bitmap kernel (a workgroup per window, one bit per column of a range)
@@ -43,20 +42,6 @@ constexpr int HUB_SLOTS_MAX = 1024; // hub windows handled at once (one thread e
 constexpr int HUB_CHUNK = 4096;     // edges per work item of the edge-parallel hub kernels
 constexpr int HUB_GROUP = 8;        // bitmap words per stored prefix (one 32-byte load)
 constexpr int HUB_GRID = 2048;      // workgroups of the edge-parallel hub kernels (grid-stride over chunks)
-
-// Parts a window of `cnt` edges is queued in for the direct kernel: every part builds the window's whole bitmap
-// and ranks DIRECT_PART_EDGES of its edges or fewer, so that the few windows of 10^5 edges of a power-law graph do not
-// keep one workgroup busy long after every other one has finished (one workgroup took 0.31 ms for the R-MAT
-// benchmark graph's largest window, 256 000 edges; building the bitmap is the cheaper half of the work, 0.18 ns per
-// edge against 0.40 ns for ranking and writing).  cnt / DIRECT_PART_EDGES + 1 <= cnt / (MID_CAP + 1) above
-// DIRECT_SPLIT_MIN: the queue's capacity of nnz / (MID_CAP + 1) + 1 entries holds.
-constexpr int DIRECT_SPLIT_MIN = 32768, DIRECT_PART_EDGES = 16384, DIRECT_PARTS_MAX = 16;
-__host__ __device__ inline int direct_parts(int cnt)
-{
-    if (cnt <= DIRECT_SPLIT_MIN) return 1;
-    const int p = (cnt + DIRECT_PART_EDGES - 1) / DIRECT_PART_EDGES;
-    return p < DIRECT_PARTS_MAX ? p : DIRECT_PARTS_MAX;
-}
 
 enum { C_B1 = 0, C_B2 = 1, C_B3 = 2, C_B4 = 3, C_LARGE = 4, C_HUB = 5, C_DIRECT = 6, C_CHUNKS = 7, C_LARGE_NEXT = 8,
        C_DIRECT_NEXT = 9, C_WORDS = 16 };
@@ -115,10 +100,7 @@ static WinWorkspace carve(void *ws, int n, int nnz, int n_windows)
     };
     const int lower[4] = {WAVE_CAP, B1_CAP, B2_CAP, MID_CAP};
     for (int i = 0; i < 4; ++i) w.cap_b[i] = nnz / (lower[i] + 1) + 1 < n_windows ? nnz / (lower[i] + 1) + 1 : n_windows;
-    {
-        const int64_t by_parts = static_cast<int64_t>(n_windows) * DIRECT_PARTS_MAX;
-        w.cap_direct = nnz / (MID_CAP + 1) + 1 < by_parts ? nnz / (MID_CAP + 1) + 1 : static_cast<int>(by_parts);
-    }
+    w.cap_direct = direct_capacity(nnz, n_windows);
     w.cap_large = nnz / (B4_CAP + 1) + 1 < n_windows ? nnz / (B4_CAP + 1) + 1 : n_windows;
     w.slots = hub_slots(n, nnz);
     w.wps = hub_words_per_slot(n);
@@ -1449,9 +1431,6 @@ __global__ __launch_bounds__(256) void win_pack_kernel(int n_windows, const int 
 constexpr int FLAT_NODES = 1 << 18;
 constexpr int FLAT_ALL_EDGES = 32768;  // graphs of at most this many entries queue nothing: the kernel walks any window itself
 
-// parts of a window above MID_CAP edges: at most cnt / (MID_CAP + 1), what the queue has room for
-__device__ __forceinline__ int flat_parts(int cnt) { return max(1, min(cnt / 8192, 64)); }
-
 // the piece of column col and what is set in it below the column
 __device__ __forceinline__ int bits_below(const uint4 &v, int col)
 {
@@ -1484,7 +1463,7 @@ __global__ __launch_bounds__(256) void win_flat_kernel(int n, const int *__restr
     const int e0 = row_ptr[r0], cnt = row_ptr[r0 + rows] - e0;  // uniform
     if (cnt > limit) {
         if (tid == 0) {
-            const int parts = flat_parts(cnt), at = atomicAdd(&counters[C_DIRECT], parts);
+            const int parts = direct_parts(cnt), at = atomicAdd(&counters[C_DIRECT], parts);
             for (int p = 0; p < parts; ++p) list_direct[at + p] = make_int4(w, e0, cnt, p | (parts << 8));
         }
         return;

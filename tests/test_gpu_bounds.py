@@ -5,7 +5,7 @@ import pytest
 import torch
 
 import synth
-from parity import dev_graph
+from parity import check_windows, dev_graph
 from paper_2412_12218_amd import binding as B
 
 pytestmark = pytest.mark.gpu
@@ -74,6 +74,24 @@ def test_build_windows_stays_in_bounds(gi):
     assert torch.all(wc.buf[:GUARD] == -77) and torch.all(wc.buf[-GUARD:] == -77)
     assert torch.all(wc.view[uniq:] == -77) and not torch.any(wc.view[:uniq] == -77)
     assert torch.all(ws.buf[:GUARD] == 0) and torch.all(ws.buf[-GUARD:] == 0)
+
+
+@pytest.mark.parametrize("n,blk_h,per_row", [(16, 16, 37_500), (1, 1, 700_000), (2200, 64, 2200), (1500, 16, 9000)])
+def test_build_windows_of_dense_graphs_stays_in_bounds(oracle, n, blk_h, per_row):
+    """Windows of 139 000 edges and more (one window, whole rows of a complete graph, repeated columns): each is queued in
+    as many parts as one window may be, and the queue is as full as it gets."""
+    rng = np.random.default_rng(n)
+    row_ptr = (np.arange(n + 1, dtype=np.int64) * per_row).astype(np.int32)
+    col = np.tile(np.arange(n, dtype=np.int32), n) if per_row == n else rng.integers(0, n, size=n * per_row).astype(np.int32)
+    g = synth.Graph(n, row_ptr, col, "dense")
+    print(f"dense windows n={n} blk_h={blk_h} nnz={g.nnz}", flush=True)
+    dg = dev_graph(g)
+    nbytes = B.lib().ftc_build_windows_workspace_bytes(g.n, g.nnz, blk_h, 8)
+    ws = guarded_ws(nbytes)
+    w = B.ftc_build_windows(dg, blk_h=blk_h, ws=ws.view)
+    torch.cuda.synchronize()
+    ws_intact(ws)
+    check_windows(w, oracle.build_windows(g.row_ptr, g.col_idx, blk_h, 8))
 
 
 @pytest.mark.parametrize("gi", [0, 1])
