@@ -1521,19 +1521,22 @@ __global__ __launch_bounds__(256) void win_flat_kernel(int n, const int *__restr
     if (tid == 0) uniq_count[w] = total;
 }
 
-// The queued windows, a part at a time.
+// The queued windows, a part at a time, 1024 threads each whatever the size of the bitmap: with a thread per piece (512 for
+// graphs of up to 65 536 nodes) a CU held half as many waves (us): 20 000 nodes with 2000 entries a row 283 / 227, with 9000
+// 1680 / 1520; one window of 9.6 M entries 2511 / 1584.
 template <int WORDS>
-__global__ __launch_bounds__(WORDS / 4 < 1024 ? WORDS / 4 : 1024) void win_flat_big_kernel(
+__global__ __launch_bounds__(1024) void win_flat_big_kernel(
     int n, const int *__restrict__ row_ptr, const int *__restrict__ col_idx, int blk_h, int *__restrict__ edge_to_row,
     int *__restrict__ edge_to_col, int *__restrict__ uniq_count, int *__restrict__ tmp_cols, const int4 *__restrict__ list,
     const int *__restrict__ count)
 {
-    constexpr int PIECES = WORDS / 4, NT = PIECES < 1024 ? PIECES : 1024, PPT = PIECES / NT, EB = 8;
+    constexpr int PIECES = WORDS / 4, NT = 1024, PPT = PIECES < NT ? 1 : PIECES / NT, EB = 8;
     __shared__ uint4 bits[PIECES];
     __shared__ int pre[PIECES];
     __shared__ int rp[65];
     __shared__ int wtot[NT / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const bool owner = tid < PIECES;  // of a share of the bitmap
     uint32_t *words = reinterpret_cast<uint32_t *>(bits);
     const int n_items = *count;
     for (int item = blockIdx.x; item < n_items; item += gridDim.x) {  // uniform
@@ -1543,8 +1546,10 @@ __global__ __launch_bounds__(WORDS / 4 < 1024 ? WORDS / 4 : 1024) void win_flat_
         const int i_lo = min(cnt, part * per), i_hi = min(cnt, i_lo + per);
         const int r0 = w * blk_h, rows = min(n, r0 + blk_h) - r0;
         __syncthreads();  // the previous part is done with the bitmap
+        if (owner) {
 #pragma unroll
-        for (int q = 0; q < PPT; ++q) bits[q * NT + tid] = make_uint4(0u, 0u, 0u, 0u);
+            for (int q = 0; q < PPT; ++q) bits[q * NT + tid] = make_uint4(0u, 0u, 0u, 0u);
+        }
         if (tid <= rows) rp[tid] = row_ptr[r0 + tid];
         __syncthreads();
         // EB loads in flight, unconditional, from an index clamped into the window
@@ -1568,7 +1573,7 @@ __global__ __launch_bounds__(WORDS / 4 < 1024 ? WORDS / 4 : 1024) void win_flat_
         int before[PPT], mine = 0;
 #pragma unroll
         for (int q = 0; q < PPT; ++q) {
-            const uint4 v = bits[tid * PPT + q];
+            const uint4 v = owner ? bits[tid * PPT + q] : make_uint4(0u, 0u, 0u, 0u);
             before[q] = mine;
             mine += __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
         }
@@ -1581,8 +1586,10 @@ __global__ __launch_bounds__(WORDS / 4 < 1024 ? WORDS / 4 : 1024) void win_flat_
             off += k < wave ? wtot[k] : 0;
             total += wtot[k];
         }
+        if (owner) {
 #pragma unroll
-        for (int q = 0; q < PPT; ++q) pre[tid * PPT + q] = off + before[q];
+            for (int q = 0; q < PPT; ++q) pre[tid * PPT + q] = off + before[q];
+        }
         __syncthreads();
         for_edges(i_lo, i_hi, [&](int col, int i) {
             const int r = pre[col >> 7] + bits_below(bits[col >> 7], col);
@@ -1598,7 +1605,9 @@ __global__ __launch_bounds__(WORDS / 4 < 1024 ? WORDS / 4 : 1024) void win_flat_
 }
 
 // Prefix of the unique counts, window arrays and packed lists in one kernel, for at most FINISH_WINDOWS windows: every
-// workgroup adds up the counts before its FINISH_PER windows itself (at most 16 loads per thread).
+// workgroup adds up the counts before its FINISH_PER windows itself (at most 16 loads per thread).  Only after the flat
+// kernel: with the long lists of the dense graphs that the size classes take it is the slower way (65 536 nodes with 2000
+// entries a row: whole build 946 us, 860 with the scan and the pack kernel).
 constexpr int FINISH_WINDOWS = 4096, FINISH_PER = 2;
 
 __global__ __launch_bounds__(256) void win_finish_kernel(int n, int n_windows, int blk_h, int blk_w, const int *__restrict__ row_ptr,
@@ -1655,23 +1664,26 @@ __global__ __launch_bounds__(256) void win_finish_kernel(int n, int n_windows, i
 // cost per window, so windows have to hold enough edges: at 200 000 nodes the lines cross between 143 edges a window on
 // average (55 us here, 50 there) and 269 (62, 85); with the smaller bitmaps the flat kernel was ahead at every
 // density that was measured (80 edges a window: 100 000 nodes 31 / 38 us, 60 000 nodes 21 / 31 us).
+// Where most windows are above MID_CAP edges the first kernel only queues them, one workgroup and one atomic on the same
+// counter each, which the size classes do 1024 windows at a time (us here / there, equal rows): 100 000 nodes with 250
+// entries a row 154 / 184, with 270 269 / 248, with 512 399 / 376; 200 000 nodes with 250 359 / 350, with 270 531 / 481;
+// 262 144 nodes with 200 375 / 386, with 250 488 / 454.  Up to FINISH_WINDOWS windows the one kernel that finishes them makes
+// up for it, with more than 2048 of them as long as they are not larger still (65 536 nodes with 270 entries a row 162 / 175,
+// with 512 244 / 247, with 1000 471 / 429; 40 000 with 1000 269 / 270, with 2000 533 / 509; 20 000 with 512 78 / 97, with 2000
+// 227 / 232, with 9000 1520 / 1853).
 static int flat_words(int n, int nnz, int n_windows)
 {
     if (n > FLAT_NODES || nnz == 0) return 0;
     const int words = n <= (1 << 16) ? 2048 : n <= (1 << 17) ? 4096 : 8192;
-    return n_windows <= FINISH_WINDOWS || nnz / n_windows >= (words == 8192 ? 192 : words / 64) ? words : 0;
+    const int mean = nnz / n_windows;  // edges a window
+    if (n_windows <= FINISH_WINDOWS) return n_windows <= 2048 || mean < 3 * MID_CAP ? words : 0;
+    return mean >= (words == 8192 ? 192 : words / 64) && mean < (words == 8192 ? 3584 : MID_CAP) ? words : 0;
 }
 
 // Everything after the windows are condensed: prefix of the unique counts, window arrays, packed lists.
 static int32_t finish_windows(const ftc_csr &g, ftc_windows &w, const WinWorkspace &k, hipStream_t s)
 {
     int32_t st;
-    if (w.n_windows <= FINISH_WINDOWS && g.nnz > 0) {
-        hipLaunchKernelGGL(win_finish_kernel, dim3(ceil_div(w.n_windows, FINISH_PER)), dim3(256), 0, s, g.n, w.n_windows,
-                           w.blk_h, w.blk_w, g.row_ptr, k.uniq_count, k.tmp_cols, w.win_col_ptr, w.block_partition,
-                           w.summary, w.win_cols);
-        return launch_status("build_windows finish");
-    }
     const int chunks = ceil_div(w.n_windows, SCAN_CHUNK);
     if (chunks > 1 && chunks <= SCAN_CHUNKS_MAX && g.nnz > 0) {
         hipLaunchKernelGGL(win_chunk_sums_kernel, dim3(chunks), dim3(256), 0, s, w.n_windows, w.blk_w, k.uniq_count,
@@ -1731,9 +1743,9 @@ int32_t launch_build_windows(const ftc_csr &g, ftc_windows &w, void *ws, size_t 
         hipLaunchKernelGGL(win_flat_kernel<W>, dim3(w.n_windows), dim3(256), 0, s, g.n, g.row_ptr, g.col_idx, w.blk_h, \
                            w.edge_to_row, w.edge_to_col, k.uniq_count, k.tmp_cols, limit, k.list_direct, k.counters);  \
         if (g.nnz > limit)                                                                                             \
-            hipLaunchKernelGGL(win_flat_big_kernel<W>, dim3(big), dim3(W / 4 < 1024 ? W / 4 : 1024), 0, s, g.n,        \
-                               g.row_ptr, g.col_idx, w.blk_h, w.edge_to_row, w.edge_to_col, k.uniq_count, k.tmp_cols,  \
-                               k.list_direct, k.counters + C_DIRECT);                                                  \
+            hipLaunchKernelGGL(win_flat_big_kernel<W>, dim3(big), dim3(1024), 0, s, g.n, g.row_ptr, g.col_idx, w.blk_h, \
+                               w.edge_to_row, w.edge_to_col, k.uniq_count, k.tmp_cols, k.list_direct,                  \
+                               k.counters + C_DIRECT);                                                                 \
     } while (0)
         if (flat == 2048) FTC_FLAT(2048);
         else if (flat == 4096) FTC_FLAT(4096);
@@ -1741,7 +1753,11 @@ int32_t launch_build_windows(const ftc_csr &g, ftc_windows &w, void *ws, size_t 
 #undef FTC_FLAT
         st = launch_status("build_windows flat");
         if (st != FTC_OK) return st;
-        return finish_windows(g, w, k, s);
+        if (w.n_windows > FINISH_WINDOWS) return finish_windows(g, w, k, s);
+        hipLaunchKernelGGL(win_finish_kernel, dim3(ceil_div(w.n_windows, FINISH_PER)), dim3(256), 0, s, g.n, w.n_windows,
+                           w.blk_h, w.blk_w, g.row_ptr, k.uniq_count, k.tmp_cols, w.win_col_ptr, w.block_partition,
+                           w.summary, w.win_cols);
+        return launch_status("build_windows finish");
     }
     if (queued) {
         hipLaunchKernelGGL(win_clear_kernel, dim3(1), dim3(64), 0, s, k.counters);

@@ -965,6 +965,20 @@ def test_window_sizes_on_both_sides_of_the_bitmap_rule(oracle, n, blk_h):
     check_windows(B.ftc_build_windows_concurrent(dg, B.SideStreams(), blk_h=blk_h), ref)
 
 
+@pytest.mark.parametrize("n,blk_h,per_row", [(2049, 1, 12_288), (2048, 1, 12_288), (65_552, 16, 257), (65_552, 16, 250)])
+def test_windows_all_above_the_queue_line(oracle, n, blk_h, per_row):
+    """Dense graphs, on both sides of the lines from which the size classes take them instead of the one bitmap: more than
+    2048 windows of 12 288 edges, more than 4096 windows of 4096 edges."""
+    rng = np.random.default_rng(n + per_row)
+    row_ptr = (np.arange(n + 1, dtype=np.int64) * per_row).astype(np.int32)
+    g = synth.Graph(n, row_ptr, rng.integers(0, n, size=n * per_row).astype(np.int32), "dense")
+    say(f"dense windows n={n} blk_h={blk_h} nnz={g.nnz}")
+    ref = oracle.build_windows(g.row_ptr, g.col_idx, blk_h, 8)
+    dg = dev_graph(g)
+    check_windows(B.ftc_build_windows(dg, blk_h=blk_h), ref)
+    check_windows(B.ftc_build_windows_concurrent(dg, B.SideStreams(), blk_h=blk_h), ref)
+
+
 def test_one_window_holds_a_small_graph_whole(oracle):
     """All 30 000 entries in the first window, the others empty: nothing is queued at this size."""
     n = 5000
