@@ -377,8 +377,17 @@ __global__ __launch_bounds__(256) void agnn_fused_fixup_kernel(int n, int n_rang
         if (ok && r >= 0 && rec.y && sub * 4 < D) {
             const float o[4] = {(h4.x + t4.x) / spec_z, (h4.y + t4.y) / spec_z, (h4.z + t4.z) / spec_z,
                                 (h4.w + t4.w) / spec_z};
-            store_vec<4>(out, static_cast<int64_t>(r) * ldo + sub * 4, odt, o);
-            if (out32) store_vec<4>(out32, static_cast<int64_t>(r) * ld32 + sub * 4, FTC_F32, o);
+            if (sub * 4 + 4 <= D) {
+                store_vec<4>(out, static_cast<int64_t>(r) * ldo + sub * 4, odt, o);
+                if (out32) store_vec<4>(out32, static_cast<int64_t>(r) * ld32 + sub * 4, FTC_F32, o);
+            } else {  // widths of 3 and 6: the row's last piece is a short one
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (sub * 4 + i < D) {
+                        store_elem(out, static_cast<int64_t>(r) * ldo + sub * 4 + i, odt, o[i]);
+                        if (out32) out32[static_cast<int64_t>(r) * ld32 + sub * 4 + i] = o[i];
+                    }
+            }
         }
         if (ok && r >= 0 && rec.y && row_z && sub == 0) row_z[r] = spec_z;
     }

@@ -155,6 +155,29 @@ def test_layers_stay_in_bounds(dtype, D):
     r.check()
 
 
+@pytest.mark.parametrize("dtype,D,out_dtype", [(F32, 3, F32), (F32, 6, F32), (F16, 6, F32), (F16, 6, F16), (BF16, 12, BF16)])
+def test_agnn_layer_leaves_the_padding_columns_alone(dtype, D, out_dtype):
+    """Widths whose last piece is shorter than the four columns a lane finishes a cut row with, in padded rows: by the
+    single pass with and without the probabilities, and with the unrounded copy."""
+    g = graphs()[0]
+    dg = dev_graph(g)
+    win = B.ftc_build_windows(dg)
+    ld = (D + 7) // 8 * 8
+    H = torch.randn((g.n, ld), device="cuda").to(dtype)[:, :D]
+    for p in (None, Guarded((g.nnz,), F32)):
+        out = Guarded((g.n, D), out_dtype, pad=ld - D)
+        B.ftc_agnn_layer(dg, win, H, beta=1.0, out=out.view, edge_p=None if p is None else p.view)
+        torch.cuda.synchronize()
+        out.check()
+        if p is not None:
+            p.check()
+    out, out32, z = Guarded((g.n, D), out_dtype, pad=ld - D), Guarded((g.n, D), F32, pad=ld - D), Guarded((g.n,), F32)
+    B.ftc_agnn_layer(dg, win, H, beta=1.0, out=out.view, row_z=z.view, out_f32=out32.view)
+    torch.cuda.synchronize()
+    for t in (out, out32, z):
+        t.check()
+
+
 def symmetric_graph():
     """The hub graph of graphs(), symmetrised (ascending, duplicate-free rows) for the backward pass."""
     import scipy.sparse as sp
