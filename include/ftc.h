@@ -245,8 +245,9 @@ int32_t ftc_gcn_layer(const ftc_csr *g, const ftc_windows *w, const float *vals,
  * P = edge softmax of s, out = P * H (H not normalised).  edge_p, when not NULL,
  * receives P (nnz floats).  With a window index scores, softmax and aggregation run fused in one
  * pass over the edges (P follows from the pass's weights); the softmax is then shifted by |beta|,
- * an upper bound of every score, instead of by the row maximum (same result); for |beta| >= 43 the
- * unfused chain with the row-wise softmax is used.
+ * an upper bound of every score, instead of by the row maximum.  Above |beta| = 16 when edge_p is
+ * given, and from 43 on without it, the unfused chain with the row-wise softmax is used (the
+ * weights of a row whose neighbours all point away are exp(-2 |beta|)).
  * row_z, when not NULL, receives the softmax denominators of that pass,
  * z_i = sum over row i of exp(beta * cos - |beta|) (n floats, 0 for a row without entries): what
  * ftc_agnn_layer_backward_fused needs instead of P.  out_f32, when not NULL, receives the result

@@ -87,6 +87,12 @@ static float sddmm_mfma_reuse(int D) { return D >= 256 ? 2.6f : -1.f; }
 static constexpr int MFMA_MAX_WINDOW_EDGES = 4096;
 // |beta| up to which the single-pass AGNN kernels (forward and backward) are used
 static constexpr float AGNN_FUSED_MAX_BETA = 43.f;
+// |beta| up to which the single pass also gives the probabilities; above, the three kernels, whose weights are relative to
+// the row's maximum.  A row whose neighbours all point away has weights of exp(-2 |beta|) here, and the products with H
+// must not become subnormal before they are divided by the row's sum: exp(-32) h is a normal number for |h| above 1e-24,
+// which is 1e-12 of the smallest norm that is not clamped.  Error of the single pass against the three kernels in such rows:
+// at 42 5e-5 / 1e-6 with features of 1e-3 and 6e-3 / 1e-6 with 1e-5, at 36 1e-2 / 1e-6 with 3e-11, at 16 7e-7 / 6e-7 with any.
+static constexpr float AGNN_EDGE_P_MAX_BETA = 16.f;
 
 static size_t flag_bytes(int32_t n) { return align_up(static_cast<size_t>((n + 15) / 16), 256); }
 
@@ -490,11 +496,10 @@ int32_t ftc_agnn_layer(const ftc_csr *g, const ftc_windows *w, const void *H, in
         seg_shape(dtype, D, &vec, &lpr))
         return launch_agnn_fused(*g, *w, H, ld, dtype, D, beta, out, ldo, out_dtype, row_z, out_f32, ld_f32, nullptr, p,
                                  ws_bytes, static_cast<hipStream_t>(stream));
-    // The probabilities come from the same pass; the rows' sums take the end of the workspace.  (A workspace without room for
-    // them gets the three kernels below.)
+    // The probabilities come from the same pass; the rows' sums take the end of the workspace.
     const size_t z_bytes = align_up(static_cast<size_t>(g->n) * sizeof(float), 256);
-    if (edge_p && !keep && w && beta_ok && g->nnz > 0 && path != FTC_PATH_MFMA && rows16 && seg_shape(dtype, D, &vec, &lpr) &&
-        ws_bytes >= agnn_fused_ws(g->nnz, D, true) + z_bytes) {
+    if (edge_p && !keep && w && fabsf(beta) <= AGNN_EDGE_P_MAX_BETA && g->nnz > 0 && path != FTC_PATH_MFMA && rows16 &&
+        seg_shape(dtype, D, &vec, &lpr) && ws_bytes >= agnn_fused_ws(g->nnz, D, true) + z_bytes) {
         const size_t at = (ws_bytes - z_bytes) / 256 * 256;
         return launch_agnn_fused(*g, *w, H, ld, dtype, D, beta, out, ldo, out_dtype, reinterpret_cast<float *>(p + at), nullptr, 0,
                                  edge_p, p, at, static_cast<hipStream_t>(stream));

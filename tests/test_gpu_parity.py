@@ -752,6 +752,31 @@ def test_agnn_layer_fused_large_beta_and_fp16_out(oracle, graphs):
         assert err < 2e-3
 
 
+@pytest.mark.parametrize("scale", [1e-3, 1e-5, 3e-11])
+def test_attention_of_rows_that_point_away_from_all_their_neighbours(oracle, scale):
+    """Two halves of opposite direction, every entry from one to the other: all scores are -beta, and weights relative to |beta|
+    instead of the row's maximum would be exp(-2 |beta|).  Small features next to that may not lose more than the
+    accumulation does (fp32, 1e-5), on both sides of every line in beta at which the layer changes its kernels.
+    The probabilities' relative error is the absolute error of the differences of scores, beta times that of two cosines: eight
+    roundings each (four products a lane, three steps of the lanes' sum, the norms under a root), 16 * 2^-24 * beta."""
+    rng = np.random.default_rng(2)
+    n, D, deg = 600, 32, 9
+    other = (np.arange(n)[:, None] < n // 2) * (n // 2)
+    cols = np.sort(other + rng.integers(0, n // 2, size=(n, deg)), axis=1)
+    g = synth.Graph(n, (np.arange(n + 1) * deg).astype(np.int32), cols.reshape(-1).astype(np.int32), "halves")
+    v = rng.standard_normal(D)
+    H = np.where(np.arange(n)[:, None] < n // 2, 1.0, -1.0) * v * rng.uniform(0.5, 2.0, size=(n, 1)) * scale
+    Hd, H64 = quantise(H.astype(np.float32), F32)
+    dg = dev_graph(g)
+    win = B.ftc_build_windows(dg)
+    for beta in (15.9, 16.0, 16.1, 36.0, 42.0, 42.9, 43.0):
+        ref, ab, p_ref = oracle.agnn_layer(g.row_ptr, g.col_idx, H64, beta)
+        p = torch.full((g.nnz,), -1.0, dtype=F32, device="cuda")
+        out = B.ftc_agnn_layer(dg, win, Hd, beta=beta, edge_p=p)
+        say(f"opposite halves, features {scale}, beta {beta}: out {norm_err(out, ref, ab):.2e} p {rel_err(p, p_ref):.2e}")
+        assert norm_err(out, ref, ab) < 1e-5 and rel_err(p, p_ref) < max(P_TOL, 16 * 2.0 ** -24 * beta)
+
+
 # ------------------------------------------------------------------ the step as a HIP graph
 def test_hot_path_step_replayed_as_a_graph_matches_eager_runs():
     """Capture the whole step (window build with its side streams, both models) once, replay it several
