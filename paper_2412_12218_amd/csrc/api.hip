@@ -496,10 +496,12 @@ int32_t ftc_agnn_layer(const ftc_csr *g, const ftc_windows *w, const void *H, in
         seg_shape(dtype, D, &vec, &lpr))
         return launch_agnn_fused(*g, *w, H, ld, dtype, D, beta, out, ldo, out_dtype, row_z, out_f32, ld_f32, nullptr, p,
                                  ws_bytes, static_cast<hipStream_t>(stream));
-    // The probabilities come from the same pass; the rows' sums take the end of the workspace.
+    // The probabilities come from the same pass; the rows' sums take the end of the workspace.  (The size that was checked
+    // above is at least that of the three kernels, which counts the scores and two arrays of n floats: the carried pieces of
+    // ranges of SEG_R entries and the sums fit into that.)
     const size_t z_bytes = align_up(static_cast<size_t>(g->n) * sizeof(float), 256);
     if (edge_p && !keep && w && fabsf(beta) <= AGNN_EDGE_P_MAX_BETA && g->nnz > 0 && path != FTC_PATH_MFMA && rows16 &&
-        seg_shape(dtype, D, &vec, &lpr) && ws_bytes >= agnn_fused_ws(g->nnz, D, true) + z_bytes) {
+        seg_shape(dtype, D, &vec, &lpr)) {
         const size_t at = (ws_bytes - z_bytes) / 256 * 256;
         return launch_agnn_fused(*g, *w, H, ld, dtype, D, beta, out, ldo, out_dtype, reinterpret_cast<float *>(p + at), nullptr, 0,
                                  edge_p, p, at, static_cast<hipStream_t>(stream));

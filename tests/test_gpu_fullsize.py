@@ -70,11 +70,15 @@ def test_cfg3_agnn_layer_full(oracle, threads):
     out = B.ftc_agnn_layer(dg, win, Hd, beta=1.0)
     err = norm_err(out, ref, ab)
     p = torch.empty(g.nnz, dtype=F32, device="cuda")
-    out_u = B.ftc_agnn_layer(dg, win, Hd, beta=1.0, edge_p=p)
-    err_u = norm_err(out_u, ref, ab)
-    perr = float(np.max(np.abs(p.cpu().double().numpy() - pref) / pref))
-    say(f"  fused err {err:.3e}, unfused err {err_u:.3e}, p err {perr:.3e}")
-    assert err < 2e-3 and err_u < 2e-3 and perr < 2e-3
+    out_p = B.ftc_agnn_layer(dg, win, Hd, beta=1.0, edge_p=p)
+    p_chain = B.ftc_edge_softmax(dg, win, B.ftc_sddmm(dg, win, Hd, Hd, alpha=1.0, cosine=True))
+    out_chain = B.ftc_spmm(dg, win, p_chain, Hd)
+    say(f"  single pass err {err:.3e}")
+    assert err < 2e-3
+    for what, o, q in (("with probabilities", out_p, p), ("chain", out_chain, p_chain)):
+        e, perr = norm_err(o, ref, ab), float(np.max(np.abs(q.cpu().double().numpy() - pref) / pref))
+        say(f"  {what} err {e:.3e}, p err {perr:.3e}")
+        assert e < 2e-3 and perr < 2e-3
 
 
 def test_cfg4_spmm_sddmm_full(oracle, threads):

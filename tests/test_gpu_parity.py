@@ -690,13 +690,19 @@ def test_update_gemm_row_scale(oracle, dtype, d_in, d_out):
     assert norm_err(Z, ref, ab) < TOL[dtype]
 
 
+def attention_chain(dg, win, Hd, beta, path=B.FTC_PATH_AUTO):
+    """The layer as its three steps, one call each: cosine scores, edge softmax, aggregation."""
+    p = B.ftc_edge_softmax(dg, win, B.ftc_sddmm(dg, win, Hd, Hd, alpha=beta, cosine=True, path=path))
+    return B.ftc_spmm(dg, win, p, Hd, path=path), p
+
+
 @pytest.mark.parametrize("name,dtype,D", [("cfg1", F32, 16), ("cfg3s", F16, 32), ("cfg5s", F16, 32),
                                           ("cfg4s", BF16, 64), ("hub", F16, 8), ("hub", F16, 128),
                                           ("mixed", BF16, 16), ("cfg5s", F32, 32), ("hub", F16, 24)])
 @pytest.mark.parametrize("beta", [1.0, 2.5, -3.0])
 def test_agnn_layer(oracle, graphs, name, dtype, D, beta):
-    """Both routes of the layer: the unfused chain (taken when the probabilities are requested) and
-    the single-pass fused kernel, each against the oracle."""
+    """Every route of the layer against the oracle: the single pass with and without the probabilities, the chain of scores,
+    softmax and aggregation, and the row kernels."""
     g = graphs[name]
     say(f"agnn_layer {name} {dtype} D={D} beta={beta}")
     Hd, H64 = quantise(synth.normal_features(g.n, D, seed=11), dtype)
@@ -705,11 +711,12 @@ def test_agnn_layer(oracle, graphs, name, dtype, D, beta):
     win = B.ftc_build_windows(dg)
     p = torch.empty(g.nnz, dtype=F32, device="cuda")
     out = B.ftc_agnn_layer(dg, win, Hd, beta=beta, edge_p=p)
-    err = norm_err(out, ref, ab)
-    perr = rel_err(p, pref)
-    say(f"  unfused err {err:.3e} p err {perr:.3e}")
-    assert err < TOL[dtype]
-    assert perr < P_TOL
+    out_c, p_c = attention_chain(dg, win, Hd, beta)
+    for what, o, q in (("with probabilities", out, p), ("chain", out_c, p_c)):
+        err, perr = norm_err(o, ref, ab), rel_err(q, pref)
+        say(f"  {what} err {err:.3e} p err {perr:.3e}")
+        assert err < TOL[dtype]
+        assert perr < P_TOL
     out2 = B.ftc_agnn_layer(dg, win, Hd, beta=beta)      # fused: no P output
     err2 = norm_err(out2, ref, ab)
     say(f"  fused err {err2:.3e}")
@@ -1016,15 +1023,15 @@ def test_one_window_holds_a_small_graph_whole(oracle):
 @pytest.mark.parametrize("dtype,D", [(F16, 32), (BF16, 64), (F32, 8), (F32, 128), (F16, 24)])
 @pytest.mark.parametrize("name", ["hub", "cfg2s", "cfg3"])
 def test_attention_weights_of_the_single_pass(oracle, graphs, name, dtype, D):
-    """P and the aggregated rows from one pass (hub rows, empty rows, duplicates; ranges of 128 to 512 entries), and from the
-    three kernels, which a workspace without room for the rows' sums still gets."""
+    """P and the aggregated rows from one pass (hub rows, empty rows, duplicates; ranges of 128 to 512 entries, and of 512 in a
+    workspace that holds no shorter ones), and from the three kernels that give them above |beta| = 16."""
     g = synth.config_graph(3) if name == "cfg3" else graphs[name]
     if name == "cfg3" and D != 32:
         return
     dg = dev_graph(g)
     win = B.ftc_build_windows(dg)
     Hd, H64 = quantise(synth.normal_features(g.n, D, seed=D), dtype)
-    for beta in (1.0, -2.5, 12.0):
+    for beta in (1.0, -2.5, 12.0, 16.5):
         ref, ab, p_ref = oracle.agnn_layer(g.row_ptr, g.col_idx, H64, beta)
         for least in (False, True):
             p = torch.full((g.nnz,), -1.0, dtype=F32, device="cuda")
@@ -1036,3 +1043,6 @@ def test_attention_weights_of_the_single_pass(oracle, graphs, name, dtype, D):
             out = B.ftc_agnn_layer(dg, win, Hd, beta=beta, edge_p=p, ws=ws)
             say(f"attention {name} {dtype} D={D} beta={beta} least={least}: p {rel_err(p, p_ref):.2e} out {norm_err(out, ref, ab):.2e}")
             assert rel_err(p, p_ref) < P_TOL and norm_err(out, ref, ab) < 1e-5
+            if beta > 16:  # the same kernels, called one by one
+                chain, p_chain = attention_chain(dg, win, Hd, beta)
+                assert torch.equal(p, p_chain) and (least or torch.equal(out, chain))
