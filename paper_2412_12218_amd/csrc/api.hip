@@ -94,7 +94,6 @@ static constexpr float AGNN_FUSED_MAX_BETA = 43.f;
 // at 42 5e-5 / 1e-6 with features of 1e-3 and 6e-3 / 1e-6 with 1e-5, at 36 1e-2 / 1e-6 with 3e-11, at 16 7e-7 / 6e-7 with any.
 static constexpr float AGNN_EDGE_P_MAX_BETA = 16.f;
 
-static size_t flag_bytes(int32_t n) { return align_up(static_cast<size_t>((n + 15) / 16), 256); }
 
 #define FTC_TRY(expr)                   \
     do {                                \
@@ -163,7 +162,7 @@ int32_t ftc_gcn_norm(const ftc_csr *g, const ftc_windows *w, float *vals, float 
 
 // What a call needs at least (`least`), or with room for the shorter ranges of small graphs and for odd widths: that is
 // what the *_workspace_bytes queries return; a call that gets less than that but at least the former runs with long ranges.
-static size_t spmm_ws(int32_t n, int32_t nnz, int32_t D, bool least) { return spmm_seg_ws(nnz, D, least) + flag_bytes(n); }
+static size_t spmm_ws(int32_t n, int32_t nnz, int32_t D, bool least) { return spmm_seg_ws(n, nnz, D, least) + flag_bytes(n); }
 
 size_t ftc_spmm_workspace_bytes(int32_t n, int32_t nnz, int32_t D)
 {
@@ -220,9 +219,10 @@ int32_t ftc_spmm(const ftc_csr *g, const ftc_windows *w, const float *vals, cons
     // kernels again, at element alignment, wherever the workspace holds their carried pieces.  The row-wise kernels below
     // give a row to a thread per column, one after the other over its entries (fp32, 10 columns, power-law graph with
     // 100 000 nodes: 305 us against 36).
-    if (w && g->nnz > 0 && ws && reinterpret_cast<uintptr_t>(ws) % 256 == 0 && ws_bytes >= spmm_ws(g->n, g->nnz, D, false)) {
+    if (w && g->nnz > 0 && ws && reinterpret_cast<uintptr_t>(ws) % 256 == 0) {
         const bool x16 = aligned16(X) && (static_cast<int64_t>(ldx) * elem_size(x_dtype)) % 16 == 0;
-        if ((x16 && spmm_lane_shape(x_dtype, D, ldx)) || spmm_ragged_ok(x_dtype, D))
+        const size_t any = spmm_any_width_ws(x_dtype, D, g->n, g->nnz, x16 && spmm_lane_shape(x_dtype, D, ldx));
+        if (any > 0 && ws_bytes >= any)
             return launch_spmm_seg(*g, *w, vals, X, ldx, x_dtype, D, out, ldo, out_dtype, epi, ws, ws_bytes, nullptr, hs);
     }
     return launch_spmm_rows(*g, vals, X, ldx, x_dtype, D, out, ldo, out_dtype, epi, hs);
@@ -234,7 +234,6 @@ int32_t ftc_spmm(const ftc_csr *g, const ftc_windows *w, const float *vals, cons
 // device address is asked for once per device and kept.
 }  // extern "C"
 namespace {
-constexpr size_t NOALLOC_SCRATCH_BYTES = static_cast<size_t>(FTC_NOALLOC_SCRATCH_MIB) << 20;
 static __device__ __align__(256) unsigned char scratch[NOALLOC_SCRATCH_BYTES];
 constexpr int NOALLOC_MAX_DEVICES = 64;
 void *g_scratch_ptr[NOALLOC_MAX_DEVICES];  // device address of `scratch` on every device that has asked
@@ -270,7 +269,7 @@ int32_t ftc_spmm_noalloc(const ftc_csr *g, const ftc_windows *w, const float *va
 {
     FTC_TRY(check_csr(g, "ftc_spmm_noalloc"));
     if (D < 1) return fail(FTC_EINVAL, "ftc_spmm_noalloc: need D >= 1");
-    const size_t need = spmm_ws(g->n, g->nnz, D, true);
+    const size_t need = ftc_spmm_workspace_bytes(g->n, g->nnz, D);
     if (need > NOALLOC_SCRATCH_BYTES)
         return fail(FTC_EWORKSPACE,
                     "ftc_spmm_noalloc: this graph and width need %zu bytes of scratch memory, the built-in buffer holds "

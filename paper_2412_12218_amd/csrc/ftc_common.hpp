@@ -23,6 +23,13 @@ inline int elem_size(int dtype) { return dtype == FTC_F32 ? 4 : 2; }
 inline bool valid_dtype(int d) { return d == FTC_F32 || d == FTC_F16 || d == FTC_BF16; }
 inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
+// one flag per window, for the dispatch of windows to the matrix cores
+inline size_t flag_bytes(int32_t n) { return align_up(static_cast<size_t>((static_cast<int64_t>(n) + 15) / 16), 256); }
+
+// Scratch memory of ftc_spmm_noalloc.  Its results are those of ftc_spmm, so whatever ftc_spmm chooses by the size of
+// its scratch memory (kernel, length of the ranges) is chosen such that it fits into this.
+constexpr size_t NOALLOC_SCRATCH_BYTES = static_cast<size_t>(FTC_NOALLOC_SCRATCH_MIB) << 20;
+
 // ceil(a / b) for non-negative a up to INT32_MAX (the sum a + b - 1 would not fit)
 inline int ceil_div(int a, int b) { return static_cast<int>((static_cast<int64_t>(a) + b - 1) / b); }
 
@@ -73,8 +80,8 @@ bool seg_shape(int dtype, int D, int *vec, int *lpr);
 // Workspaces of the edge-balanced kernels: `least` is what they need with ranges of SEG_R edges (of 1024 or 512 in the kernel
 // for narrow rows), otherwise room for the shorter ranges of small graphs; a launcher takes the shorter ranges when
 // the `ws_bytes` it is given hold them.
-bool spmm_ragged_ok(int dtype, int D);
-size_t spmm_seg_ws(int nnz, int D, bool least);
+size_t spmm_any_width_ws(int dtype, int D, int n, int nnz, bool lane);
+size_t spmm_seg_ws(int n, int nnz, int D, bool least);
 bool spmm_lane_shape(int xdt, int D, int ldx);
 size_t spmm_lane_ws(int nnz, bool least);
 int32_t launch_spmm_lane(const ftc_csr &g, const ftc_windows &w, const float *vals, const void *X, int ldx, int xdt,

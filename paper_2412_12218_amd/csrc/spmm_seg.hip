@@ -58,44 +58,56 @@ static bool seg_shape_ragged(int dtype, int D, int *vec, int *lpr)
     return true;
 }
 
-bool spmm_ragged_ok(int dtype, int D)
-{
-    int vec, lpr;
-    return seg_shape_ragged(dtype, D, &vec, &lpr);
-}
-
 static size_t seg_carry_ws(int nnz, int r, int dp)
 {
     const size_t n_ranges = static_cast<size_t>(seg_count(nnz, r));
     return align_up(n_ranges * 2 * dp * sizeof(float), 256) + align_up(n_ranges * 2 * sizeof(int), 256);
 }
 
-// Edges per wave for rows of dp slots: as seg_range() says, as long as the carried pieces stay below 32 MiB (they then fit
-// the built-in buffer of ftc_spmm_noalloc too, whose results are those of ftc_spmm bit for bit).
-static int spmm_range(int nnz, int dp)
+// Edges per wave for rows of dp slots: as seg_range() says, as long as the carried pieces stay below 32 MiB and, with the
+// flags of the windows, fit the built-in buffer of ftc_spmm_noalloc.
+static int spmm_range(int n, int nnz, int dp)
 {
     int r = seg_range(nnz, SEG_SPMM);
-    while (r < SEG_R && seg_carry_ws(nnz, r, dp) > (static_cast<size_t>(32) << 20)) r *= 2;
+    while (r < SEG_R && (seg_carry_ws(nnz, r, dp) > (static_cast<size_t>(32) << 20) ||
+                         seg_carry_ws(nnz, r, dp) + flag_bytes(n) > NOALLOC_SCRATCH_BYTES))
+        r *= 2;
     return r;
 }
 
-size_t spmm_seg_ws(int nnz, int D, bool least)
+// Scratch memory of the kernel that takes widths or alignments seg_shape() does not (lane: the kernel for narrow rows), 0 where
+// none does: where it would not fit the built-in buffer of ftc_spmm_noalloc (47 columns, 67 M entries; a wider X more) both
+// calls stay with the row-wise kernel.
+size_t spmm_any_width_ws(int dtype, int D, int n, int nnz, bool lane)
 {
-    int vec, lpr, dp = 0;
+    int vec, lpr;
+    size_t need = 0;
+    if (lane) need = spmm_lane_ws(nnz, false);
+    else if (seg_shape_ragged(dtype, D, &vec, &lpr)) need = seg_carry_ws(nnz, spmm_range(n, nnz, vec * lpr), vec * lpr);
+    return need + flag_bytes(n) <= NOALLOC_SCRATCH_BYTES ? need : 0;
+}
+
+size_t spmm_seg_ws(int n, int nnz, int D, bool least)
+{
     if (nnz == 0) return 0;
-    size_t seg = 0;
+    size_t need = 0;
+    int vec, lpr;
+    bool any = false;
     for (const int dt : {FTC_F32, FTC_F16}) {
-        int w = 0;
-        if (seg_shape(dt, D, &vec, &lpr)) w = vec * lpr;
-        if (!least && seg_shape_ragged(dt, D, &vec, &lpr) && vec * lpr > w) w = vec * lpr;
-        if (w == 0) continue;
-        const size_t need = seg_carry_ws(nnz, least ? SEG_R : spmm_range(nnz, w), w);
-        seg = need > seg ? need : seg;
-        dp = w > dp ? w : dp;
+        size_t k = 0;
+        if (seg_shape(dt, D, &vec, &lpr)) {
+            any = true;
+            k = seg_carry_ws(nnz, least ? SEG_R : spmm_range(n, nnz, vec * lpr), vec * lpr);
+        }
+        need = k > need ? k : need;
+        k = least ? 0 : spmm_any_width_ws(dt, D, n, nnz, false);
+        need = k > need ? k : need;
     }
-    if (dp == 0 && (least || D > 16)) return 0;
-    const size_t lane = D <= 16 ? spmm_lane_ws(nnz, least) : 0;  // narrow rows may take the lane-per-edge kernel
-    return seg > lane ? seg : lane;
+    if (D <= 16) {  // narrow rows may take the lane-per-edge kernel
+        const size_t lane = any ? spmm_lane_ws(nnz, least) : least ? 0 : spmm_any_width_ws(FTC_F32, D, n, nnz, true);
+        need = lane > need ? lane : need;
+    }
+    return need;
 }
 
 // VALS = false: all edge values are one (vals == NULL): nothing is staged or multiplied for them, which
@@ -442,9 +454,8 @@ static void launch_seg_r(int r, int vec, int lpr, bool ragged, hipStream_t s, in
     else launch_seg_t<T, 128>(vec, lpr, ragged, s, n_ranges, g, e2r, vals, X, ldx, D, out, ldo, odt, epi, carry, tail_row, dense);
 }
 
-// Caller has checked: window index present, seg_shape() or spmm_ragged_ok() accepts (xdt, D) or the kernel for narrow rows
-// does (spmm_lane_shape, rows of X 16-byte aligned), workspace of spmm_seg_ws(.., least) bytes, of spmm_seg_ws(.., false)
-// unless seg_shape() accepts and the rows of X and out are 16-byte aligned.
+// Caller has checked: window index present; seg_shape() accepts (xdt, D), rows of X and out 16-byte aligned and a workspace of
+// spmm_seg_ws(.., least) bytes, or a workspace of spmm_any_width_ws() > 0 bytes.
 int32_t launch_spmm_seg(const ftc_csr &g, const ftc_windows &w, const float *vals, const void *X, int ldx,
                         int xdt, int D, void *out, int ldo, int odt, Epi epi, void *ws, size_t ws_bytes,
                         const uint8_t *dense, hipStream_t s)
@@ -458,7 +469,7 @@ int32_t launch_spmm_seg(const ftc_csr &g, const ftc_windows &w, const float *val
     const bool ragged = !(x16 && o16 && seg_shape(xdt, D, &vec, &lpr));
     if (ragged) seg_shape_ragged(xdt, D, &vec, &lpr);
     const int dp = vec * lpr;
-    const int short_r = spmm_range(g.nnz, dp);
+    const int short_r = spmm_range(g.n, g.nnz, dp);
     const int r = ws_bytes >= seg_carry_ws(g.nnz, short_r, dp) ? short_r : SEG_R;
     const int n_ranges = static_cast<int>(seg_count(g.nnz, r));
     float *carry = static_cast<float *>(ws);

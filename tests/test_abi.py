@@ -191,3 +191,19 @@ def test_header_is_plain_c(tmp_path):
                    '    return (int)sizeof(ftc_plan) > 0 && FTC_NOALLOC_SCRATCH_MIB > 0 ? 0 : 1; }\n')
     subprocess.run(["gcc", "-std=c99", "-Wall", "-Wextra", "-pedantic", "-Werror", "-fsyntax-only",
                     "-I", os.path.join(ROOT, "include"), str(src)], check=True)
+
+
+def test_scratch_of_odd_widths_fits_the_built_in_buffer():
+    """Widths that only the any-width kernels take: ftc_spmm asks for no more scratch memory than ftc_spmm_noalloc has, so the
+    two choose the same kernel however many entries there are; a width the aligned kernels take may ask for more."""
+    L = B.lib()
+    room = 64 << 20
+    for D in (1, 2, 5, 7, 9, 10, 13, 17, 22, 47, 50, 65, 100 + 1, 127, 131, 250, 255, 257, 1433):
+        for n in (1000, 1 << 20, 60_000_000):
+            for nnz in (1, 1000, (1 << 20) - 1, 1 << 20, (1 << 23) - 1, 1 << 23, 17_000_000, 70_000_000, 2 ** 31 - 1):
+                assert 0 < L.ftc_spmm_workspace_bytes(n, nnz, D) <= room, (n, nnz, D)
+    up = lambda b: (b + 255) // 256 * 256
+    for D in (8, 32, 64, 128, 256):
+        ranges = 200_000_000 // 512
+        assert L.ftc_spmm_workspace_bytes(1 << 20, 200_000_000, D) >= up(ranges * 8 * D) + up(ranges * 8) + (1 << 20) // 16
+    assert L.ftc_spmm_workspace_bytes(1 << 20, 200_000_000, 64) > room

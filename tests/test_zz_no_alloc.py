@@ -46,6 +46,41 @@ def test_two_calls_in_a_row_the_second_smaller(oracle):
     one_call(oracle, synth.config_graph(4, 0.02), torch.bfloat16, 64, True, 5)
 
 
+@pytest.mark.parametrize("dtype,D,ldx", [(torch.float16, 7, 8), (torch.float16, 7, 7), (torch.float32, 10, 12), (torch.float32, 10, 10),
+                                         (torch.bfloat16, 47, 47), (torch.float16, 131, 136), (torch.float32, 64, 65)])
+def test_odd_widths_and_unaligned_rows(oracle, dtype, D, ldx):
+    """The any-width kernels, in the built-in buffer and in a workspace: the same bits."""
+    for g in (synth.config_graph(5, 1 / 32), synth.config_graph(1)):
+        rng = np.random.default_rng(D)
+        X32 = rng.uniform(-1, 1, size=(g.n, D)).astype(np.float32)
+        Xq, X64 = quantise(X32, dtype)
+        Xd = torch.zeros((g.n, ldx), dtype=dtype, device="cuda")[:, :D]
+        Xd.copy_(Xq)
+        dg = dev_graph(g)
+        win = B.ftc_build_windows(dg)
+        want = B.ftc_spmm(dg, win, None, Xd)
+        got = torch.full((g.n, D), float("nan"), dtype=torch.float32, device="cuda")
+        B.ftc_spmm_noalloc(dg, win, None, Xd, got)
+        assert torch.equal(got, want)
+        assert norm_err(got, *oracle.spmm(g.row_ptr, g.col_idx, None, X64)) < TOL[dtype]
+
+
+def test_odd_width_whose_pieces_do_not_fit_the_buffer():
+    """47 columns and 72 M entries: the carried pieces of the any-width kernel would be larger than the built-in buffer, so
+    both calls take the row-wise kernel and agree bit for bit."""
+    n, per_row, D = 200_000, 360, 47
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    row_ptr = (torch.arange(n + 1, device="cuda") * per_row).to(torch.int32)
+    dg = B.Graph(row_ptr, torch.randint(n, (n * per_row,), generator=gen, device="cuda", dtype=torch.int32))
+    win = B.ftc_build_windows(dg)
+    X = torch.rand((n, D), generator=gen, device="cuda").to(torch.bfloat16)
+    want = B.ftc_spmm(dg, win, None, X)
+    got = torch.full((n, D), float("nan"), dtype=torch.float32, device="cuda")
+    B.ftc_spmm_noalloc(dg, win, None, X, got)
+    assert torch.equal(got, want)
+
+
 def test_sizes_beyond_the_buffer_are_refused():
     L = B.lib()
     I = C.c_int32
