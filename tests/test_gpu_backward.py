@@ -732,3 +732,29 @@ def test_weight_grad_edges(dtype, n, d_in, d_out):
         M64 = np.where(Z.float().cpu().numpy() > 0, G64, 0.0)
         _, dWm = B.ftc_update_gemm_backward(X, W, G, Z=Z, want_dX=False)
         assert term_err(dWm, X64.T @ M64, np.abs(X64).T @ np.abs(M64)) < 1e-5
+
+
+@pytest.mark.parametrize("n,d_in,d_out,dtype", [(200_000, 1433, 256, F16), (100_000, 1024, 504, BF16), (300_000, 700, 100, F32)])
+def test_weight_grad_of_wide_products_over_many_rows(n, d_in, d_out, dtype):
+    """The chains of additions are bounded however wide the product: a wave adds a quarter of a share of at most
+    384 + n / 384 rows.  Roundings of a chain of L normal terms add up to about 0.3 * 2^-24 * sqrt(L) of its sum (2-norm), and
+    twice that is allowed; without the bound the shares of these products have 4000 to 12 500 rows.  Against 64 bits in torch
+    (the oracle's loops would take minutes); where an input is infinite the sums are infinite, not NaN."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n)
+    X = torch.randn((n, d_in), generator=gen, device="cuda").to(dtype)
+    G = torch.randn((n, d_out), generator=gen, device="cuda")
+    say(f"weight grad {dtype} {n} x {d_in} -> {d_out}")
+    dW = B.ftc_weight_grad(X, G)
+    ref = torch.zeros((d_in, d_out), dtype=torch.float64, device="cuda")
+    for i in range(0, n, 50_000):
+        ref += X[i:i + 50_000].double().t().contiguous() @ G[i:i + 50_000].double()
+    err = float((dW - ref).norm() / ref.norm())
+    bar = 2 * 0.3 * 2.0 ** -24 * ((384 + n / 384) / 4) ** 0.5
+    say(f"  error {err:.2e}, allowed {bar:.2e}")
+    assert err < bar
+    X[:, 1:] = 0.0
+    X[:, 0] = 1.0
+    G[n // 3, 0] = float("inf")
+    dW = B.ftc_weight_grad(X, G)
+    assert torch.isposinf(dW[0, 0]) and torch.isfinite(dW[0, 1:]).all()
