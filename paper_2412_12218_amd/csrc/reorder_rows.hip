@@ -6,13 +6,17 @@
 //   at most 256 / 1024          a wave, 4 / 16 entries per lane,
 //   at most 8192                a workgroup of 1024 threads, in LDS,
 //   longer                      a bitmap of the columns in LDS (relabelling; duplicates: counters, see below) or
-//                               counters in LDS per 32 768 labels (label propagation).
+//                               counters in LDS per 32 768 labels (label propagation); with more than 2^19 nodes those of
+//                               at most 32 768 entries are sorted in LDS instead of counted (many_ranges()).
 // What bounds them: the look-up.  Every entry is one 4-byte gather from an array that about fills an L2 (4 MB at
 // a million nodes); the streams around it (column ids in, columns out) are read and written once, non-temporal.
 // On the block model with a million nodes and 32 M entries a round of label propagation takes 0.28 ms and the
 // relabelled graph 0.35 ms (R-MAT, 2^20 nodes: 0.52); sorting all entries by label and row with the global radix sort took
 // 4.0 and 4.1 ms.
-// Larger graphs keep the radix sort: the counters of the long rows cost one pass over the row per 32 768 nodes.
+// Larger graphs keep the radix sort: the counters of the long rows cost one pass over the row per 32 768 nodes.  Up to
+// ROW_SORT_NODES the rows are ahead on every graph that was measured but for one kind: the relabelled graph where nearly all
+// entries are in rows of more than 32 768 entries with repeated columns (2^22 nodes, 65 M entries, 95 % of them in rows of
+// 60 000: 18 against 9 ms; half of them: 9.7 against 9.4; label propagation on the first: 16 ms a round on either).
 #include "ftc_common.hpp"
 
 namespace ftc {
@@ -20,7 +24,9 @@ namespace ftc {
 constexpr int RS_ROWS = 32;         // consecutive rows per wave of the short-row part
 constexpr int RS_SHORT = 64;        // longest row handled there; the queues hold the rows above
 constexpr int RS_MID = 256, RS_LONG = 1024, RS_LDS = 8192;  // longest row of queues 0, 1, 2; queue 3 has the rest
+constexpr int RS_LDS_MOST = 32768;  // longest row of queue 2 in label propagation on many nodes (many_ranges())
 constexpr int RS_RANGE = 32768;     // counters per pass over a long row
+constexpr int RS_WORDS = RS_RANGE + RS_RANGE / 32;  // LDS words of the workgroups that take long rows
 constexpr int RS_BITS_LOG2 = 20;    // columns per bitmap pass over a long row (32 768 words)
 constexpr int RS_NONE = 0x7fffffff; // sorts behind every column and label
 
@@ -30,9 +36,23 @@ struct RowQueues {
     int *rows[4];
     int *dup_rows;               // relabelling: long rows with duplicate columns, counts[4] of them
     unsigned long long *best;    // label propagation: winner of every row of queue 3
+    int *values;                 // what the columns of the counted rows become, at the place of the entry; NULL: not kept
 };
 
-__global__ __launch_bounds__(1024) void row_classes_kernel(int n, const int *__restrict__ rp, RowQueues q)
+// Passes over a row longer than queue 2's: counters for RS_RANGE of the n values each.
+__host__ __device__ inline int value_ranges(int n) { return (n + RS_RANGE - 1) / RS_RANGE; }
+
+// From this many passes on rows of up to 32 768 entries are sorted instead of counted (an entry costs about 25 ps sorted, 6 a
+// pass counted, but one row of 30 000 entries alone keeps a workgroup for 60 us), and the look-ups of the counted rows are made
+// once and kept.  Ten rounds of label propagation, ms, counted with a look-up in every pass / sorted or looked up once / radix
+// sort of all entries ("share": of the 64 M entries, with 2^18 nodes 16 M, that are in rows of 8200 or of 60 000 entries):
+//   2^18 nodes, 8 passes     0.1 of 8200 2.0 / 1.6 / 18, of 60 000 1.8 / 2.0 / 19; R-MAT, degree 64 2.9 / 3.5 / 16
+//   2^19 nodes, 16 passes    R-MAT, degree 16 1.7 / 2.3 / 8.7; degree 64 6.1 / 5.6 / 31
+//   2^20 nodes, 32 passes    0.95 of 8200 124 / 17 / 106, of 60 000 87 / 43 / 106; R-MAT, degree 8 2.2 / 2.6 / 10, 32 9.0 / 6.4 / 32
+//   2^22 nodes, 128 passes   0.5 of 8200 273 / 15 / 102, of 60 000 190 / 78 / 105; R-MAT, degree 16 33 / 16 / 67
+__host__ __device__ inline bool many_ranges(int n) { return value_ranges(n) > 16; }
+
+__global__ __launch_bounds__(1024) void row_classes_kernel(int n, const int *__restrict__ rp, int in_lds, RowQueues q)
 {
     constexpr int PER = 4;
     __shared__ int cnt_s[4], base_s[4];
@@ -43,7 +63,7 @@ __global__ __launch_bounds__(1024) void row_classes_kernel(int n, const int *__r
     for (int k = 0; k < PER; ++k) {
         const int64_t r = (static_cast<int64_t>(blockIdx.x) * PER + k) * 1024 + threadIdx.x;
         const int len = r < n ? rp[r + 1] - rp[r] : 0;
-        cls[k] = len <= RS_SHORT ? -1 : len <= RS_MID ? 0 : len <= RS_LONG ? 1 : len <= RS_LDS ? 2 : 3;
+        cls[k] = len <= RS_SHORT ? -1 : len <= RS_MID ? 0 : len <= RS_LONG ? 1 : len <= in_lds ? 2 : 3;
         pos[k] = cls[k] >= 0 ? atomicAdd(&cnt_s[cls[k]], 1) : 0;
     }
     __syncthreads();
@@ -365,7 +385,8 @@ __device__ __forceinline__ unsigned long long ballot_of(int votes, int label)
 
 // 1025 .. 1024 K entries by 16 waves, K per lane (element i of the padded row in wave i / (64 K), register i / 64 % K, lane
 // i % 64).  Every wave sorts its share in registers, then the shares are merged: only the steps whose partner sits in
-// another wave go through LDS (ten of them, in two buffers taken in turn, one barrier each), the rest stays in registers.
+// another wave go through LDS (ten of them, in two buffers taken in turn with one barrier each, or for K = 32 in one buffer with
+// two), the rest stays in registers.
 // A share that has to descend is sorted as its complement.  (All steps in LDS, 66 to 91
 // barriers a row: the kernel takes 0.60 ms on the R-MAT graph, this way 0.26.)
 template <class Use, int K>
@@ -401,7 +422,8 @@ __device__ __forceinline__ void group_row(const Use &u, int r, int start, int le
                 const int o = buf[(base ^ stride) + k * 64 + lane];
                 v[k] = low ? min(v[k], o) : max(v[k], o);
             }
-            buf = buf == s ? s + ALL : s;  // the next step writes where nobody reads any more
+            if constexpr (2 * ALL <= RS_WORDS) buf = buf == s ? s + ALL : s;  // the next step writes where nobody reads any more
+            else __syncthreads();
         }
         const int flip = up ? 0 : -1;
 #pragma unroll
@@ -443,7 +465,9 @@ __device__ __forceinline__ void lds_row(const Use &u, int r, int *s, unsigned lo
     u.row(r, start, len);  // uniform
     if (len <= 2 * RS_NT) group_row<Use, 2>(u, r, start, len, s, tmp);
     else if (len <= 4 * RS_NT) group_row<Use, 4>(u, r, start, len, s, tmp);
-    else group_row<Use, 8>(u, r, start, len, s, tmp);
+    else if (len <= 8 * RS_NT) group_row<Use, 8>(u, r, start, len, s, tmp);
+    else if (len <= 16 * RS_NT) group_row<Use, 16>(u, r, start, len, s, tmp);
+    else group_row<Use, 32>(u, r, start, len, s, tmp);
 }
 
 __device__ __forceinline__ int pad_word(int i) { return i + (i >> 5); }  // a thread's 32 consecutive words on all banks
@@ -490,16 +514,17 @@ __device__ __forceinline__ bool bitmap_row(const Relabel &u, int r, uint32_t *bi
     return true;
 }
 
-// counters of the values [base, base + RS_RANGE) of a row; returns the thread's number of smaller values
+// counters of the values [base, base + RS_RANGE) of a row (values: looked up before, or NULL); returns the thread's number of
+// smaller values
 template <class Use>
-__device__ __forceinline__ int count_range(const Use &u, int start, int len, int base, int *cnt)
+__device__ __forceinline__ int count_range(const Use &u, const int *__restrict__ values, int start, int len, int base, int *cnt)
 {
     __syncthreads();
     for (int i = threadIdx.x; i < pad_word(RS_RANGE); i += RS_NT) cnt[i] = 0;
     __syncthreads();
     int less = 0;
     for (int i = threadIdx.x; i < len; i += RS_NT) {
-        const int c = u.value(u.col_idx[start + i]) - base;
+        const int c = (values ? values[start + i] : u.value(u.col_idx[start + i])) - base;
         if (c < 0) ++less;
         else if (c < RS_RANGE) atomicAdd(&cnt[pad_word(c)], 1);
     }
@@ -507,22 +532,45 @@ __device__ __forceinline__ int count_range(const Use &u, int start, int len, int
     return less;
 }
 
+// The look-ups of the rows that are counted, once instead of in every pass: one workgroup a row, eight in flight a thread.
+// *count rows in `rows`.
+template <class Use>
+__global__ __launch_bounds__(RS_NT) void long_row_values_kernel(Use u, const int *__restrict__ rows, const int *__restrict__ count,
+                                                                int *__restrict__ values)
+{
+    const int n_rows = *count;
+    for (int h = blockIdx.x; h < n_rows; h += gridDim.x) {
+        int start, len;
+        u.row(rows[h], start, len);
+        for (int i0 = threadIdx.x; i0 < len; i0 += RS_NT * 8) {
+            int c[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) c[k] = u.col_idx[start + min(i0 + k * RS_NT, len - 1)];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) c[k] = u.value(c[k]);
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (i0 + k * RS_NT < len) values[start + i0 + k * RS_NT] = c[k];
+        }
+    }
+}
+
 template <class Use>
 __global__ __launch_bounds__(RS_NT) void row_sort_big_kernel(Use u, RowQueues q)
 {
-    __shared__ int s[RS_RANGE + RS_RANGE / 32];
+    __shared__ int s[RS_WORDS];
     __shared__ unsigned long long tmp64[RS_NT / 64];
     __shared__ int tmp[RS_NT / 64];
     __shared__ int dup;
     const int n3 = q.counts[3], n2 = q.counts[2];
     if constexpr (Use::VOTES) {
-        const int ranges = (u.n + RS_RANGE - 1) / RS_RANGE;
+        const int ranges = value_ranges(u.n);
         const int64_t tasks = static_cast<int64_t>(n3) * ranges;
         for (int64_t t = blockIdx.x; t < tasks; t += gridDim.x) {  // uniform
             const int h = static_cast<int>(t / ranges), base = static_cast<int>(t % ranges) * RS_RANGE;
             int start, len;
             u.row(q.rows[3][h], start, len);
-            count_range(u, start, len, base, s);
+            count_range(u, q.values, start, len, base, s);
             unsigned long long best = 0ull;
             for (int i = threadIdx.x; i < RS_RANGE; i += RS_NT) {
                 const int votes = s[pad_word(i)];
@@ -535,8 +583,9 @@ __global__ __launch_bounds__(RS_NT) void row_sort_big_kernel(Use u, RowQueues q)
     } else {
         for (int h = blockIdx.x; h < n3; h += gridDim.x) {
             const int r = q.rows[3][h];
-            if (!bitmap_row(u, r, reinterpret_cast<uint32_t *>(s), tmp, &dup) && threadIdx.x == 0)
-                q.dup_rows[atomicAdd(&q.counts[4], 1)] = r;
+            if (bitmap_row(u, r, reinterpret_cast<uint32_t *>(s), tmp, &dup)) continue;  // uniform
+            if (many_ranges(u.n) && u.rp[r + 1] - u.rp[r] <= RS_LDS_MOST) lds_row(u, r, s, tmp64);
+            else if (threadIdx.x == 0) q.dup_rows[atomicAdd(&q.counts[4], 1)] = r;
         }
     }
     for (int i = blockIdx.x; i < n2; i += gridDim.x) lds_row(u, q.rows[2][i], s, tmp64);
@@ -545,15 +594,15 @@ __global__ __launch_bounds__(RS_NT) void row_sort_big_kernel(Use u, RowQueues q)
 // long rows in which a column occurs more than once: counters instead of bits, one workgroup per row and range
 __global__ __launch_bounds__(RS_NT) void row_sort_dup_kernel(Relabel u, RowQueues q)
 {
-    __shared__ int s[RS_RANGE + RS_RANGE / 32];
+    __shared__ int s[RS_WORDS];
     __shared__ int tmp[RS_NT / 64];
-    const int ranges = (u.n + RS_RANGE - 1) / RS_RANGE;
+    const int ranges = value_ranges(u.n);
     const int64_t tasks = static_cast<int64_t>(q.counts[4]) * ranges;
     for (int64_t t = blockIdx.x; t < tasks; t += gridDim.x) {  // uniform
         const int r = q.dup_rows[t / ranges], base = static_cast<int>(t % ranges) * RS_RANGE;
         int start, len;
         u.row(r, start, len);
-        const int less = count_range(u, start, len, base, s);
+        const int less = count_range(u, q.values, start, len, base, s);
         int before;
         group_exclusive_scan(less, &before, tmp);
         int mine = 0;
@@ -582,10 +631,11 @@ size_t row_sort_ws(int n, int nnz)
 {
     auto ints = [](int64_t k) { return align_up(static_cast<size_t>(k) * sizeof(int), 256); };
     return 256 + ints(queue_cap(nnz, RS_SHORT)) + ints(queue_cap(nnz, RS_MID)) + ints(queue_cap(nnz, RS_LONG)) +
-           2 * ints(queue_cap(nnz, RS_LDS)) + align_up(static_cast<size_t>(queue_cap(nnz, RS_LDS)) * 8, 256) + ints(n);
+           2 * ints(queue_cap(nnz, RS_LDS)) + align_up(static_cast<size_t>(queue_cap(nnz, RS_LDS)) * 8, 256) + ints(n) +
+           (nnz > RS_LDS_MOST && many_ranges(n) ? ints(nnz) : 0);
 }
 
-static RowQueues carve(int nnz, void *ws, int **labels)
+static RowQueues carve(int n, int nnz, void *ws, int **labels)
 {
     char *p = static_cast<char *>(ws);
     auto ints = [&](int64_t k) {
@@ -602,7 +652,8 @@ static RowQueues carve(int nnz, void *ws, int **labels)
     q.dup_rows = ints(queue_cap(nnz, RS_LDS));
     q.best = reinterpret_cast<unsigned long long *>(p);
     p += align_up(static_cast<size_t>(queue_cap(nnz, RS_LDS)) * 8, 256);
-    *labels = reinterpret_cast<int *>(p);
+    *labels = ints(n);
+    q.values = nnz > RS_LDS_MOST && many_ranges(n) ? ints(nnz) : nullptr;
     return q;
 }
 
@@ -629,10 +680,10 @@ static RowSortGrid row_sort_grid(int n, int nnz)
     return g;
 }
 
-static void classify_rows(int n, const int *rp, const RowQueues &q, int *labels, hipStream_t s)
+static void classify_rows(int n, const int *rp, int in_lds, const RowQueues &q, int *labels, hipStream_t s)
 {
     hipLaunchKernelGGL(row_sort_begin_kernel, dim3(labels ? (n + 255) / 256 : 1), dim3(256), 0, s, n, q.counts, labels);
-    hipLaunchKernelGGL(row_classes_kernel, dim3((n + 4095) / 4096), dim3(1024), 0, s, n, rp, q);
+    hipLaunchKernelGGL(row_classes_kernel, dim3((n + 4095) / 4096), dim3(1024), 0, s, n, rp, in_lds, q);
 }
 
 // rp: row starts of the relabelled graph, complete before this on the stream; ws: row_sort_ws(n, nnz) bytes
@@ -640,13 +691,18 @@ int32_t launch_relabel_rows(const ftc_csr &g, const int *perm, const int *inv, c
                             void *ws, hipStream_t s)
 {
     int *unused;
-    const RowQueues q = carve(g.nnz, ws, &unused);
+    const RowQueues q = carve(g.n, g.nnz, ws, &unused);
     const RowSortGrid grid = row_sort_grid(g.n, g.nnz);
     const Relabel u{g.n, g.row_ptr, g.col_idx, perm, inv, rp, col_idx_out, flag};
-    classify_rows(g.n, rp, q, nullptr, s);
+    classify_rows(g.n, rp, RS_LDS, q, nullptr, s);
     if (g.nnz > RS_LONG) hipLaunchKernelGGL(row_sort_big_kernel<Relabel>, dim3(grid.big_blocks), dim3(RS_NT), 0, s, u, q);
     hipLaunchKernelGGL(row_sort_kernel<Relabel>, dim3(grid.blocks), dim3(256), 0, s, u, q, grid.queue_blocks);
-    if (g.nnz > RS_LDS) hipLaunchKernelGGL(row_sort_dup_kernel, dim3(grid.big_blocks), dim3(RS_NT), 0, s, u, q);
+    if (g.nnz > RS_LDS) {
+        if (q.values)
+            hipLaunchKernelGGL(long_row_values_kernel<Relabel>, dim3(grid.big_blocks), dim3(RS_NT), 0, s, u, q.dup_rows,
+                               q.counts + 4, q.values);
+        hipLaunchKernelGGL(row_sort_dup_kernel, dim3(grid.big_blocks), dim3(RS_NT), 0, s, u, q);
+    }
     return launch_status("relabel rows");
 }
 
@@ -654,14 +710,17 @@ int32_t launch_relabel_rows(const ftc_csr &g, const int *perm, const int *inv, c
 int32_t launch_label_rounds(const ftc_csr &g, int iters, int *labels, void *ws, hipStream_t s)
 {
     int *other;
-    const RowQueues q = carve(g.nnz, ws, &other);
+    const RowQueues q = carve(g.n, g.nnz, ws, &other);
     const RowSortGrid grid = row_sort_grid(g.n, g.nnz);
     // the rounds alternate between the two arrays and end in `labels`
     int *from = iters % 2 == 0 ? labels : other, *to = iters % 2 == 0 ? other : labels;
-    classify_rows(g.n, g.row_ptr, q, from, s);
+    classify_rows(g.n, g.row_ptr, many_ranges(g.n) ? RS_LDS_MOST : RS_LDS, q, from, s);
     for (int it = 0; it < iters; ++it) {
         const Votes u{g.n, g.col_idx, from, g.row_ptr, to};
         hipLaunchKernelGGL(row_sort_kernel<Votes>, dim3(grid.blocks), dim3(256), 0, s, u, q, grid.queue_blocks);
+        if (q.values)
+            hipLaunchKernelGGL(long_row_values_kernel<Votes>, dim3(grid.big_blocks), dim3(RS_NT), 0, s, u, q.rows[3], q.counts + 3,
+                               q.values);
         if (g.nnz > RS_LONG) hipLaunchKernelGGL(row_sort_big_kernel<Votes>, dim3(grid.big_blocks), dim3(RS_NT), 0, s, u, q);
         if (g.nnz > RS_LDS)
             hipLaunchKernelGGL(take_winners_kernel, dim3(static_cast<unsigned>((queue_cap(g.nnz, RS_LDS) + 255) / 256)),

@@ -276,7 +276,8 @@ def test_order_by_key_random_keys_and_negative_flag():
 
 
 # ------------------------------------------------------------------ row-wise sorting: edges of the row classes
-ROW_EDGES = [0, 1, 2, 31, 32, 33, 63, 64, 65, 255, 256, 257, 1023, 1024, 1025, 2048, 2049, 8191, 8192, 8193, 40_000]
+ROW_EDGES = [0, 1, 2, 31, 32, 33, 63, 64, 65, 255, 256, 257, 1023, 1024, 1025, 2048, 2049, 4096, 4097, 8191, 8192, 8193,
+             16_384, 16_385, 32_768, 32_769, 40_000]
 
 
 def edge_rows_graph(n, distinct, seed):
@@ -306,10 +307,11 @@ def voted(rows, cand, n, keep):
     return out
 
 
-@pytest.mark.parametrize("n", [65_537, (1 << 20) + 77, 1 << 22, (1 << 22) + 1])
+@pytest.mark.parametrize("n", [65_537, 1 << 19, (1 << 19) + 1, (1 << 20) + 77, 1 << 22, (1 << 22) + 1])
 @pytest.mark.parametrize("distinct", [True, False])
 def test_row_lengths_at_the_edges_of_the_row_classes(n, distinct):
-    """The last size is the first that sorts all entries at once instead of row by row."""
+    """The last size is the first that sorts all entries at once instead of row by row; above 2^19 nodes longer rows are sorted
+    in LDS."""
     g = edge_rows_graph(n, distinct, seed=n + distinct)
     say(f"row classes n={n} nnz={g.nnz} distinct={distinct}")
     rows = np.repeat(np.arange(n, dtype=np.int64), np.diff(g.row_ptr))
