@@ -215,14 +215,16 @@ int32_t ftc_spmm(const ftc_csr *g, const ftc_windows *w, const float *vals, cons
         if (flags) return launch_spmm_mfma(*g, *w, vals, X, ldx, x_dtype, D, out, ldo, out_dtype, epi, flags, hs);
         return FTC_OK;
     }
-    // Widths that are no multiple of a lane's piece, or rows that are not 16-byte aligned (7 classes, say): the edge-balanced
-    // kernels again, at element alignment, wherever the workspace holds their carried pieces.  The row-wise kernels below
-    // give a row to a thread per column, one after the other over its entries (fp32, 10 columns, power-law graph with
-    // 100 000 nodes: 305 us against 36).
-    if (w && g->nnz > 0 && ws && reinterpret_cast<uintptr_t>(ws) % 256 == 0) {
+    // Widths that are no multiple of a lane's piece, or rows that are not 16-byte aligned (7 classes, say): on small graphs a
+    // kernel of its own that takes no scratch memory, else the edge-balanced kernels again, at element alignment, wherever the
+    // workspace holds their carried pieces.  The row-wise kernels below give a row to a thread per column, one after the
+    // other over its entries (fp32, 10 columns, power-law graph with 100 000 nodes: 305 us against 36).
+    if (w && g->nnz > 0) {
         const bool x16 = aligned16(X) && (static_cast<int64_t>(ldx) * elem_size(x_dtype)) % 16 == 0;
         const size_t any = spmm_any_width_ws(x_dtype, D, g->n, g->nnz, x16 && spmm_lane_shape(x_dtype, D, ldx));
-        if (any > 0 && ws_bytes >= any)
+        if (any > 0 && spmm_small_ok(D, g->nnz))
+            return launch_spmm_small(*g, vals, X, ldx, x_dtype, D, out, ldo, out_dtype, epi, hs);
+        if (any > 0 && ws && reinterpret_cast<uintptr_t>(ws) % 256 == 0 && ws_bytes >= any)
             return launch_spmm_seg(*g, *w, vals, X, ldx, x_dtype, D, out, ldo, out_dtype, epi, ws, ws_bytes, nullptr, hs);
     }
     return launch_spmm_rows(*g, vals, X, ldx, x_dtype, D, out, ldo, out_dtype, epi, hs);

@@ -65,6 +65,9 @@ struct Epi {
 // Entry points implemented in the individual .hip files (host launchers, no validation).
 int32_t launch_spmm_rows(const ftc_csr &g, const float *vals, const void *X, int ldx, int xdt, int D,
                          void *out, int ldo, int odt, Epi epi, hipStream_t s);
+bool spmm_small_ok(int D, int nnz);
+int32_t launch_spmm_small(const ftc_csr &g, const float *vals, const void *X, int ldx, int xdt, int D, void *out, int ldo,
+                          int odt, Epi epi, hipStream_t s);
 int32_t launch_sddmm_rows(const ftc_csr &g, const void *X, const void *Y, int ld, int dt, int D,
                           const float *rs, const float *cs, float alpha, float *out, hipStream_t s);
 int32_t launch_softmax(const ftc_csr &g, const float *in, float *out, hipStream_t s);

@@ -943,6 +943,41 @@ def test_spmm_any_width_and_alignment(oracle, graphs, name, dtype, D):
         assert norm_err(B.ftc_spmm(dg, win, None, buf[:, :D], ws=few), ref, ab) < 1e-5
 
 
+@pytest.mark.parametrize("dtype", [F32, F16, BF16])
+@pytest.mark.parametrize("D", [7, 10, 15, 16, 17, 22, 33, 64, 65, 127, 255, 256])
+def test_spmm_any_width_on_small_graphs(oracle, dtype, D):
+    """One kernel for graphs of few entries: rows of every length at which it changes from threads to a wave to the workgroup,
+    empty rows, duplicates; and graphs with as many entries as it takes, and one more."""
+    rng = np.random.default_rng(D)
+    slots = 64 // D
+    lens = [0, 1, 2, 31, 32, 33, 95, 96, 97, 96 * slots, 96 * slots + 1, 129, 1000, 1025, 5000]
+    n = 701
+    deg = rng.integers(0, 9, size=n)
+    deg[rng.choice(n, size=len(lens), replace=False)] = lens
+    line = (320 if D <= 16 else 80) << 10
+    for total in (None, line, line + 1):
+        d = deg.copy()
+        if total is not None:                                  # spread what is missing over all rows, one row takes the rest
+            d += (total - d.sum()) // n
+            d[5] += total - d.sum()
+        row_ptr = np.r_[0, np.cumsum(d)].astype(np.int32)
+        g = synth.Graph(n, row_ptr, rng.integers(0, n, size=row_ptr[-1]).astype(np.int32), "small")
+        buf, X64 = quantise(rng.uniform(-1, 1, size=(n, D + 1)).astype(np.float32), dtype)   # rows at element alignment
+        vals = rng.uniform(-1, 1, size=g.nnz).astype(np.float32)
+        scale = rng.uniform(0.5, 2.0, size=n).astype(np.float32)
+        dg = dev_graph(g)
+        win = B.ftc_build_windows(dg)
+        say(f"spmm small {dtype} D={D} nnz={g.nnz}")
+        for v, sc, relu in ((vals, scale, False), (None, None, True)):
+            ref, ab = oracle.spmm(g.row_ptr, g.col_idx, None if v is None else v.astype(np.float64), X64[:, 1:])
+            if sc is not None:
+                ref, ab = ref * sc[:, None], ab * sc[:, None]
+            out = torch.full((n, D + 3), float("nan"), dtype=F32, device="cuda")[:, :D]
+            B.ftc_spmm(dg, win, None if v is None else torch.from_numpy(v).cuda(), buf[:, 1:], out=out, relu=relu,
+                       out_scale=None if sc is None else torch.from_numpy(sc).cuda())
+            assert norm_err(out, np.maximum(ref, 0) if relu else ref, ab) < 1e-5
+
+
 @pytest.mark.parametrize("n,deg", [(700, 8), (45_000, 16), (90_000, 16), (200_000, 20)])
 def test_short_ranges_on_small_graphs(oracle, n, deg):
     """0.006, 0.6, 1.3 and 3.7 M entries: the edges per wave change between them; and the long ranges, which a
