@@ -156,7 +156,7 @@ int32_t launch_mask_scale(int n, int d, const float *dY, int lddy, const void *Y
 // of G counts only where Y is positive; no masked copy of G has to exist.
 // Bound by reading X and G (2^20 x 128 fp16, 32 columns of G: 0.40 GB) up to about 64 columns of G, by the fp32 matrix
 // rate beyond.  Measured, against rows staged in LDS and 4 x 4 register tiles on the vector units (us, with the sum over
-// the shares): fp32 100 000 x 300 -> 128: 324 / 138; fp16 2^20 x 128 -> 32:
+// the shares): fp32 100 000 x 300 -> 128: 324 / 126; fp16 2^20 x 128 -> 32:
 // 250 / 128 (with the mask, before as a pass of its own: 340 / 145).
 constexpr int WG_ROWS = 32;
 constexpr int WG_MAX_BLOCKS = 1024;
@@ -383,9 +383,36 @@ static void weight_grad_t(int nt, int mask, dim3 grid, hipStream_t s, int n, con
         else if (mask == 1) FTC_WG(N, 1); \
         else FTC_WG(N, 2);              \
     }
-    FTC_WGN(1) FTC_WGN(2) FTC_WGN(4) FTC_WGN(8)
+    FTC_WGN(1) FTC_WGN(2) FTC_WGN(4)
+    if constexpr (VA < 4) { FTC_WGN(8) }  // (never the tile of least cost with VA = 4)
 #undef FTC_WGN
 #undef FTC_WG
+}
+
+// Tile of the weight gradient: 16 va columns of X and 16 nt columns of G per workgroup.  Time goes with the padded area of
+// the result, and the more of it a workgroup holds the less often X and G are read; COST is the measured time per padded
+// element and row (10^-4 ps, 2^20 rows, median over 117 widths).  X of up to 16 columns: va = 1.  The vector units' 4 x 4 register
+// tiles / va = 4 with nt by the width of G alone / this (10^6 rows, us): fp16 65 x 136 536 / 1100 / 543, 17 x 136 286 / 511 / 186,
+// 128 x 136 804 / 1156 / 540; fp32 100 000 x 300 -> 128 328 / 140 / 126.  Results that pad by half and more stay behind those by up
+// to 1.3 (fp32 200 x 136 1108 / 2049 / 1456, 200 x 65 670 / 1099 / 877).
+struct WgTile { int va, nt; };
+static WgTile weight_grad_tile(int d_in, int d_out)
+{
+    constexpr int COST[3][4] = {{1440, 760, 505, 387}, {790, 430, 320, 300}, {450, 310, 298, 0}};  // [log2 va][log2 nt]
+    WgTile best = {1, 1};
+    int64_t least = INT64_MAX;
+    for (int i = d_in <= 16 ? 0 : 2; i >= (d_in <= 16 ? 0 : 1); --i)
+        for (int j = 3; j >= 0; --j) {
+            const int va = 1 << i, nt = 1 << j;
+            if (COST[i][j] == 0 || (nt > 1 && d_out <= 8 * nt)) continue;  // (a piece of G is no wider than G)
+            const int64_t area = static_cast<int64_t>((d_in + 16 * va - 1) / (16 * va) * (16 * va)) *
+                                 ((d_out + 16 * nt - 1) / (16 * nt) * (16 * nt));
+            if (area * COST[i][j] < least) {
+                least = area * COST[i][j];
+                best = {va, nt};
+            }
+        }
+    return best;
 }
 
 // dW = X^T (G masked by Y; Y == NULL: no mask).  The shares of the rows: enough workgroups for the chip, at least 64 rows
@@ -394,16 +421,17 @@ static void weight_grad_t(int nt, int mask, dim3 grid, hipStream_t s, int n, con
 // A wave adds up a quarter of a share's rows in one chain, so the shares are also bounded from above: with at most
 // 384 + n / 384 rows each the error stays below that of the kernel this one replaced (which had n / 1024 rows, but added
 // twice as many shares in a chain; normal inputs, 2-norm against 64 bits, former kernel / chip-filling shares / this):
-//   400 000 x 1433 -> 128 4.1e-7 / 8.6e-7 / 3.1e-7 (us 3970 / 2110 / 2640), 400 000 x 1433 -> 256 4.1e-7 / 1.2e-6 / 3.3e-7 (7430 /
-//   4330 / 4660), 2^20 x 1433 -> 128 6.1e-7 / 1.4e-6 / 4.9e-7 (8780 / 5710 / 6640), 2^20 x 1024 -> 504 6.1e-7 / 3.2e-6 / 5.0e-7
-//   (113 000 / 15 300 / 18 400), 20 000 x 1433 -> 64 2.3e-7 / 2.5e-7 / 1.9e-7 (598 / 69 / 94).
+//   400 000 x 1433 -> 128 4.1e-7 / 8.6e-7 / 3.1e-7 (us 3970 / 2110 / 2030), 400 000 x 1433 -> 256 4.1e-7 / 1.2e-6 / 3.3e-7 (7430 /
+//   4330 / 3760), 2^20 x 1433 -> 128 6.1e-7 / 1.4e-6 / 4.9e-7 (8780 / 5710 / 4890), 2^20 x 1024 -> 504 6.1e-7 / 3.2e-6 / 5.0e-7
+//   (113 000 / 15 300 / 14 100), 20 000 x 1433 -> 64 2.3e-7 / 2.5e-7 / 1.9e-7 (598 / 69 / 94).
 // Where the workspace does not hold so many results the rows are taken in rounds, each added to dW with the error of the
 // additions carried along.
 int32_t launch_weight_grad(int n, const void *X, int ldx, int xdt, int d_in, const float *G, int ldg, int d_out,
                            const void *Y, int ldy, int ydt, float *dW, void *ws, hipStream_t s)
 {
     const int64_t room = static_cast<int64_t>(weight_grad_blocks(n)) * weight_grad_group(d_in, d_out);  // columns x shares
-    const int nt = d_out <= 16 ? 1 : d_out <= 32 ? 2 : d_out <= 64 ? 4 : 8, va = d_in <= 16 ? 1 : 4;
+    const WgTile tile = weight_grad_tile(d_in, d_out);
+    const int nt = tile.nt, va = tile.va;
     const int groups_b = (d_out + 16 * nt - 1) / (16 * nt);
     const int64_t tiles = static_cast<int64_t>((d_in + 16 * va - 1) / (16 * va)) * groups_b;
     const int64_t least = n / (384 + n / 384);
@@ -429,7 +457,7 @@ int32_t launch_weight_grad(int n, const void *X, int ldx, int xdt, int d_in, con
     const unsigned limit = ydt == FTC_F16 ? 0x7c00u : 0x7f80u;
     for (int k0 = 0; k0 < d_in; k0 += group) {
         const int dk = d_in - k0 < group ? d_in - k0 : group;
-        const int vk = dk <= 16 ? 1 : 4;
+        const int vk = dk <= 16 ? 1 : va;
         const dim3 grid(static_cast<unsigned>(splits), (dk + 16 * vk - 1) / (16 * vk), groups_b);
         float *lost = rounds > 1 ? partial + static_cast<size_t>(splits) * dk * d_out : nullptr;
         int64_t r0 = 0;
@@ -442,6 +470,8 @@ int32_t launch_weight_grad(int n, const void *X, int ldx, int xdt, int d_in, con
     do {                                                                                                                  \
         if (vk == 1) weight_grad_t<T, 1>(nt, mask, grid, s, rows, Xr, ldx, dk, Gr, ldg, d_out, Yr, ldy, limit, partial,   \
                                          static_cast<int>(splits));                                                       \
+        else if (vk == 2) weight_grad_t<T, 2>(nt, mask, grid, s, rows, Xr, ldx, dk, Gr, ldg, d_out, Yr, ldy, limit,       \
+                                              partial, static_cast<int>(splits));                                         \
         else weight_grad_t<T, 4>(nt, mask, grid, s, rows, Xr, ldx, dk, Gr, ldg, d_out, Yr, ldy, limit, partial,           \
                                  static_cast<int>(splits));                                                               \
     } while (0)
