@@ -161,6 +161,47 @@ __global__ __launch_bounds__(256) void gemm_any_kernel(int n, const void *__rest
     }
 }
 
+// fp32 rows of few aligned columns into few: a thread per row, W in LDS.  Bound by reading X and writing Z; the general kernel
+// leaves most of its matrix products empty here and stages W anew every 64 rows (10^6 rows, us, there / here: 4 -> 1 41 / 4,
+// 4 -> 4 42 / 9, 16 -> 7 44 / 25, 20 -> 4 50 / 18, 32 -> 8 51 / 46).
+constexpr int GN_IN = 32;
+static bool narrow_shape(int d_in, int d_out) { return (d_in <= GN_IN && d_out <= 8) || (d_in <= 16 && d_out <= 12); }
+
+template <int GN_OUT>
+__global__ __launch_bounds__(256) void gemm_narrow_kernel(int n, const float *__restrict__ X, int ldx, int d_in,
+                                                          const float *__restrict__ W, int d_out, void *__restrict__ Z, int ldz,
+                                                          int zdt, Epi epi)
+{
+    __shared__ float Ws[GN_IN * GN_OUT];
+    for (int t = threadIdx.x; t < GN_IN * GN_OUT; t += 256) {
+        const int k = t / GN_OUT, o = t % GN_OUT;
+        Ws[t] = k < d_in && o < d_out ? W[k * d_out + o] : 0.f;
+    }
+    __syncthreads();
+    const int64_t row = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    if (row >= n) return;
+    float4 x[GN_IN / 4];
+#pragma unroll
+    for (int q = 0; q < GN_IN / 4; ++q)
+        x[q] = 4 * q < d_in ? *reinterpret_cast<const float4 *>(X + row * ldx + 4 * q) : make_float4(0.f, 0.f, 0.f, 0.f);
+    float acc[GN_OUT];
+#pragma unroll
+    for (int o = 0; o < GN_OUT; ++o) acc[o] = 0.f;
+#pragma unroll
+    for (int q = 0; q < GN_IN / 4; ++q) {
+        if (4 * q >= d_in) break;  // uniform
+        const float xk[4] = {x[q].x, x[q].y, x[q].z, x[q].w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int o = 0; o < GN_OUT; ++o) acc[o] = fmaf(xk[j], Ws[(4 * q + j) * GN_OUT + o], acc[o]);
+    }
+    const float f = epi.factor(row);
+#pragma unroll
+    for (int o = 0; o < GN_OUT; ++o)
+        if (o < d_out) store_elem(Z, row * ldz + o, zdt, epi.apply(f, acc[o]));
+}
+
 template <class T>
 static void gemm_any_t(int n, const void *X, int ldx, int d_in, const void *W, int d_out, void *Z, int ldz, int zdt,
                        Epi epi, hipStream_t s)
@@ -460,6 +501,13 @@ int32_t launch_gemm(int n, const void *X, int ldx, int dt, int d_in, const void 
             else gemm_mfma_wide_t<BF16>(n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi, s);
             return launch_status("update_gemm mfma (wide)");
         }
+    }
+    if (dt == FTC_F32 && fast && narrow_shape(d_in, d_out)) {
+        const dim3 grid(static_cast<unsigned>((static_cast<int64_t>(n) + 255) / 256));
+        const float *x = static_cast<const float *>(X), *w = static_cast<const float *>(W);
+        if (d_out <= 8) hipLaunchKernelGGL(gemm_narrow_kernel<8>, grid, dim3(256), 0, s, n, x, ldx, d_in, w, d_out, Z, ldz, zdt, epi);
+        else hipLaunchKernelGGL(gemm_narrow_kernel<12>, grid, dim3(256), 0, s, n, x, ldx, d_in, w, d_out, Z, ldz, zdt, epi);
+        return launch_status("update_gemm narrow");
     }
     if (dt == FTC_F32) gemm_any_t<F32>(n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi, s);
     else if (dt == FTC_F16) gemm_any_t<F16>(n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi, s);

@@ -910,6 +910,20 @@ def test_update_gemm_general_kernel_edges(oracle, dtype, n, d_in, d_out):
 
 
 # ------------------------------------------------------------------ widths and alignments of the edge-balanced SpMM
+@pytest.mark.parametrize("d_in,d_out", [(4, 1), (4, 12), (4, 13), (16, 8), (16, 12), (20, 8), (20, 9), (32, 1), (32, 8), (36, 8)])
+@pytest.mark.parametrize("n", [1, 255, 257, 5000])
+def test_update_gemm_of_few_aligned_columns(oracle, n, d_in, d_out):
+    """The widths of the row-per-thread kernel and the first beyond them, with a row scale and ReLU and a 16-bit result."""
+    Xd, X64 = quantise(synth.uniform_features(n, d_in, seed=n + d_in), F32)
+    Wd, W64 = quantise(synth.glorot_uniform(d_in, d_out, seed=d_out), F32)
+    ref, ab = oracle.gemm(X64, W64)
+    assert norm_err(B.ftc_update_gemm(Xd, Wd), ref, ab) < 1e-5
+    scale = np.random.default_rng(1).uniform(0.5, 2.0, size=n).astype(np.float32)
+    Z = torch.empty((n, d_out), dtype=F16, device="cuda")
+    B.ftc_update_gemm(Xd, Wd, out=Z, relu=True, row_scale=torch.from_numpy(scale).cuda())
+    assert norm_err(Z, np.maximum(ref * scale[:, None], 0), ab * scale[:, None], F16) < 1e-5
+
+
 @pytest.mark.parametrize("name", ["hub", "cfg2s"])
 @pytest.mark.parametrize("dtype", [F32, F16, BF16])
 @pytest.mark.parametrize("D", [3, 4, 5, 7, 9, 10, 13, 17, 22, 47, 65, 127, 128, 131, 255, 257])
