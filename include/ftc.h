@@ -22,8 +22,10 @@
  *    with ftc_validate_csr.
  *  - Dense matrices are row-major with a leading dimension in ELEMENTS.  The vector
  *    kernels need the base pointer 16-byte aligned and ld * sizeof(element) a multiple of
- *    16 with D a multiple of 8 (16-bit types) or 4 (fp32); other shapes take a slower
- *    generic kernel.  Outputs never alias inputs unless stated.
+ *    16 with D a multiple of 8 (16-bit types) or 4 (fp32).  Other shapes are taken too: by
+ *    kernels of the same kind at element alignment in ftc_spmm (with a window index), the
+ *    dense update and the weight gradient, by slower row-wise kernels elsewhere.  Outputs
+ *    never alias inputs unless stated.
  *  - n == 0 or nnz == 0 is legal.  A row without stored entries produces a zero output row
  *    (SpMM / layers) and no softmax output.
  */
@@ -290,10 +292,9 @@ int32_t ftc_edge_softmax_backward(const ftc_csr *g, const ftc_windows *w, const 
 
 /*
  * Weight gradient of the update phase: dW = X^T * G, X n x d_in (x_dtype), G n x d_out (fp32),
- * dW d_in x d_out row-major (fp32).  One pass covers ceil(d_in / 4) * ceil(d_out / 4) <= 1024 and
- * d_in + d_out <= 506; a wider X is taken in groups of up to 256 input columns (every pass reads G
- * again), d_out <= 504 (FTC_EUNSUPPORTED beyond).  Partial sums of row blocks are added in a fixed
- * order (reproducible).
+ * dW d_in x d_out row-major (fp32).  Any d_in, d_out <= 504 (FTC_EUNSUPPORTED beyond).  Partial sums
+ * of row blocks are added in a fixed order (reproducible); where the workspace holds few of them
+ * (wide products) the rows are taken in several rounds.
  */
 size_t ftc_weight_grad_workspace_bytes(int32_t n, int32_t d_in, int32_t d_out);
 int32_t ftc_weight_grad(int32_t n, const void *X, int32_t ldx, int32_t x_dtype, int32_t d_in,

@@ -158,9 +158,6 @@ int32_t launch_mask_scale(int n, int d, const float *dY, int lddy, const void *Y
 // rate beyond.  Measured, against rows staged in LDS and 4 x 4 register tiles on the vector units (us, with the sum over
 // the shares): fp32 100 000 x 300 -> 128: 324 / 126; fp16 2^20 x 128 -> 32:
 // 250 / 128 (with the mask, before as a pass of its own: 340 / 145).
-constexpr int WG_ROWS = 32;
-constexpr int WG_MAX_BLOCKS = 1024;
-constexpr int WG_TILES = 4;
 typedef float wg_f32x4 __attribute__((ext_vector_type(4)));
 
 template <class T, int N>  // N consecutive elements at element alignment
@@ -342,17 +339,19 @@ __global__ __launch_bounds__(256) void sum_partials_kernel(int count, int n_part
     }
 }
 
+// The workspace and the widest d_out are part of the interface (ftc_weight_grad_workspace_bytes, FTC_EUNSUPPORTED): room for
+// min(n / 128, 1024) partial results of weight_grad_group() columns of X, whatever the kernels make of it.
+constexpr int WG_MAX_BLOCKS = 1024, WG_MAX_PIECES = 1024, WG_MAX_COLUMNS = 512;
 static int weight_grad_blocks(int n)
 {
-    const int by_rows = (n + 4 * WG_ROWS - 1) / (4 * WG_ROWS);  // at least four row groups per workgroup
+    const int by_rows = (n + 127) / 128;
     return by_rows < 1 ? 1 : (by_rows > WG_MAX_BLOCKS ? WG_MAX_BLOCKS : by_rows);
 }
 
-// What the interface promises: d_out <= 504 next to at least eight input columns.
-static bool weight_grad_shape_ok(int d_in, int d_out)
+static bool weight_grad_shape_ok(int d_in, int d_out)  // at least eight columns of X fit next to up to 504 of G
 {
-    return d_in >= 1 && d_out >= 1 && ((d_in + 3) / 4) * ((d_out + 3) / 4) <= 256 * WG_TILES &&
-           (d_in + 3) / 4 * 4 + (d_out + 3) / 4 * 4 <= 512;
+    return d_in >= 1 && d_out >= 1 && ((d_in + 3) / 4) * ((d_out + 3) / 4) <= WG_MAX_PIECES &&
+           (d_in + 3) / 4 * 4 + (d_out + 3) / 4 * 4 <= WG_MAX_COLUMNS;
 }
 
 // Input columns that weight_grad_ws() counts next to d_out output columns; 0: d_out is too wide.

@@ -347,10 +347,10 @@ int32_t launch_order_by_key(int n, const int *keys_in, int *perm, int *inv, int 
 }
 
 // ---- label propagation ---------------------------------------------------------------------------
-// Graphs of at most ROW_SORT_NODES nodes are handled row by row (reorder_rows.hip).  Above, every round: pairs (label of the entry's column, row) sorted by label and then, stably, by row put
-// equal labels of a row side by side; a run of equal (row, label) is one candidate, its length the
-// number of votes.  The candidate with the most votes and, among those, the smallest label wins:
-// the maximum of (votes << 32 | ~label), taken with a 64-bit atomic maximum per row (the maximum
+// Graphs of at most ROW_SORT_NODES nodes are handled row by row (reorder_rows.hip).  Above, every round: pairs (label of the
+// entry's column, row) sorted by label and then, stably, by row put equal labels of a row side by side; a run of equal
+// (row, label) is one candidate, its length the number of votes.  The candidate with the most votes and, among those, the
+// smallest label wins: the maximum of (votes << 32 | ~label), taken with a 64-bit atomic maximum per row (the maximum
 // does not depend on the order of the updates, so the result is reproducible).
 __global__ __launch_bounds__(256) void entry_rows_kernel(int n, int nnz, const int *__restrict__ row_ptr,
                                                          uint32_t *__restrict__ rows)

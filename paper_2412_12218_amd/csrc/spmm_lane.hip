@@ -310,27 +310,17 @@ int32_t launch_spmm_lane(const ftc_csr &g, const ftc_windows &w, const float *va
     const int out_vec = D == dp && aligned16(out) && (static_cast<int64_t>(ldo) * elem_size(odt)) % 16 == 0;
     if (n_ranges > 0) {
         const unsigned grid = static_cast<unsigned>((n_ranges + 3) / 4);
-        if (xdt == FTC_F32)
-            {
-                if (full) launch_lane_t<F32, SL_LONG>(lpe, grid, s, g.nnz, n_ranges, g, w.edge_to_row, vals, X, ldx, D, out, ldo, odt, epi, carry,
-                               tail_row, idx_vec, out_vec);
-                else launch_lane_t<F32, SL_SHORT>(lpe, grid, s, g.nnz, n_ranges, g, w.edge_to_row, vals, X, ldx, D, out, ldo, odt, epi, carry,
-                               tail_row, idx_vec, out_vec);
-            }
-        else if (xdt == FTC_F16)
-            {
-                if (full) launch_lane_t<F16, SL_LONG>(lpe, grid, s, g.nnz, n_ranges, g, w.edge_to_row, vals, X, ldx, D, out, ldo, odt, epi, carry,
-                               tail_row, idx_vec, out_vec);
-                else launch_lane_t<F16, SL_SHORT>(lpe, grid, s, g.nnz, n_ranges, g, w.edge_to_row, vals, X, ldx, D, out, ldo, odt, epi, carry,
-                               tail_row, idx_vec, out_vec);
-            }
-        else
-            {
-                if (full) launch_lane_t<BF16, SL_LONG>(lpe, grid, s, g.nnz, n_ranges, g, w.edge_to_row, vals, X, ldx, D, out, ldo, odt, epi, carry,
-                                tail_row, idx_vec, out_vec);
-                else launch_lane_t<BF16, SL_SHORT>(lpe, grid, s, g.nnz, n_ranges, g, w.edge_to_row, vals, X, ldx, D, out, ldo, odt, epi, carry,
-                                tail_row, idx_vec, out_vec);
-            }
+#define FTC_LANES(T)                                                                                                      \
+    do {                                                                                                                  \
+        if (full) launch_lane_t<T, SL_LONG>(lpe, grid, s, g.nnz, n_ranges, g, w.edge_to_row, vals, X, ldx, D, out, ldo,   \
+                                            odt, epi, carry, tail_row, idx_vec, out_vec);                                 \
+        else launch_lane_t<T, SL_SHORT>(lpe, grid, s, g.nnz, n_ranges, g, w.edge_to_row, vals, X, ldx, D, out, ldo, odt,   \
+                                        epi, carry, tail_row, idx_vec, out_vec);                                          \
+    } while (0)
+        if (xdt == FTC_F32) FTC_LANES(F32);
+        else if (xdt == FTC_F16) FTC_LANES(F16);
+        else FTC_LANES(BF16);
+#undef FTC_LANES
         const int32_t st = launch_status("spmm_lane");
         if (st != FTC_OK) return st;
     }
