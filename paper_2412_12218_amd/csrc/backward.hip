@@ -180,12 +180,12 @@ __device__ __forceinline__ void wg_load(const void *base, int64_t idx, float (&f
     }
 }
 
-// MASK: 0 none, 1 by an fp32 Y, 2 by a 16-bit Y
+// MASK: 0 none, 1 by an fp32 Y, 2 by a 16-bit Y.  ldp: columns of a whole result, of which these d_out are some
 template <class T, int VA, int NT, int MASK>
 __global__ __launch_bounds__(256) void weight_grad_kernel(int n, const void *__restrict__ X, int ldx, int d_in,
                                                           const float *__restrict__ G, int ldg, int d_out,
                                                           const void *__restrict__ Y, int ldy, unsigned limit,
-                                                          float *__restrict__ partial, int splits)
+                                                          float *__restrict__ partial, int ldp, int splits)
 {
     constexpr int VB = NT < 4 ? NT : 4, NB = NT / VB, U = NT * VA > 16 ? 2 : VA == 1 ? 8 : 4;
     constexpr int TILES = VA * NT;
@@ -288,7 +288,7 @@ __global__ __launch_bounds__(256) void weight_grad_kernel(int n, const void *__r
     __syncthreads();
     if (wave != 0) return;
     take(red[0]);
-    float *out = partial + static_cast<size_t>(blockIdx.x) * d_in * d_out;
+    float *out = partial + static_cast<size_t>(blockIdx.x) * d_in * ldp;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const int own_a = a0 + VA * (kb * 4 + e), first_a = min(own_a, d_in - VA);
@@ -299,7 +299,7 @@ __global__ __launch_bounds__(256) void weight_grad_kernel(int n, const void *__r
 #pragma unroll
             for (int j = 0; j < NT; ++j) {
                 const int own_b = b0 + (j / VB) * 16 * VB + VB * m, b = cb[j / VB] + j % VB;
-                if (b >= own_b) out[static_cast<size_t>(a) * d_out + b] = acc[i][j][e];
+                if (b >= own_b) out[static_cast<size_t>(a) * ldp + b] = acc[i][j][e];
             }
         }
     }
@@ -371,11 +371,11 @@ size_t weight_grad_ws(int n, int d_in, int d_out)
 
 template <class T, int VA>
 static void weight_grad_t(int nt, int mask, dim3 grid, hipStream_t s, int n, const void *X, int ldx, int d_in, const float *G,
-                          int ldg, int d_out, const void *Y, int ldy, unsigned limit, float *partial, int splits)
+                          int ldg, int d_out, const void *Y, int ldy, unsigned limit, float *partial, int ldp, int splits)
 {
 #define FTC_WG(N, M)                                                                                                   \
     hipLaunchKernelGGL((weight_grad_kernel<T, VA, N, M>), grid, dim3(256), 0, s, n, X, ldx, d_in, G, ldg, d_out, Y, ldy, \
-                       limit, partial, splits)
+                       limit, partial, ldp, splits)
 #define FTC_WGN(N)                      \
     if (nt == N) {                      \
         if (mask == 0) FTC_WG(N, 0);    \
@@ -392,26 +392,39 @@ static void weight_grad_t(int nt, int mask, dim3 grid, hipStream_t s, int n, con
 // the result, and the more of it a workgroup holds the less often X and G are read; COST is the measured time per padded
 // element and row (10^-4 ps, 2^20 rows, median over 117 widths).  X of up to 16 columns: va = 1.  The vector units' 4 x 4 register
 // tiles / va = 4 with nt by the width of G alone / this (10^6 rows, us): fp16 65 x 136 536 / 1100 / 543, 17 x 136 286 / 511 / 186,
-// 128 x 136 804 / 1156 / 540; fp32 100 000 x 300 -> 128 328 / 140 / 126.  Results that pad by half and more stay behind those by up
-// to 1.3 (fp32 200 x 136 1108 / 2049 / 1456, 200 x 65 670 / 1099 / 877).
-struct WgTile { int va, nt; };
-static WgTile weight_grad_tile(int d_in, int d_out)
+// 128 x 136 804 / 1156 / 540; fp32 100 000 x 300 -> 128 328 / 140 / 126.  At 10^6 rows a few results that pad by half stay
+// behind the register tiles: fp32 100 x 136 585 / - / 759, 200 x 72 631 / - / 826, 200 x 65 670 / 1099 / 877.
+struct WgTile { int va, nt; int64_t cost; };
+static int64_t weight_grad_cost(int i, int j, int d_in, int d_out)
 {
     constexpr int COST[3][4] = {{1440, 760, 505, 387}, {790, 430, 320, 300}, {450, 310, 298, 0}};  // [log2 va][log2 nt]
-    WgTile best = {1, 1};
-    int64_t least = INT64_MAX;
+    const int a = 16 << i, b = 16 << j;
+    return static_cast<int64_t>((d_in + a - 1) / a * a) * ((d_out + b - 1) / b * b) * COST[i][j];
+}
+static WgTile weight_grad_tile(int d_in, int d_out)
+{
+    WgTile best = {1, 1, INT64_MAX};
     for (int i = d_in <= 16 ? 0 : 2; i >= (d_in <= 16 ? 0 : 1); --i)
         for (int j = 3; j >= 0; --j) {
-            const int va = 1 << i, nt = 1 << j;
-            if (COST[i][j] == 0 || (nt > 1 && d_out <= 8 * nt)) continue;  // (a piece of G is no wider than G)
-            const int64_t area = static_cast<int64_t>((d_in + 16 * va - 1) / (16 * va) * (16 * va)) *
-                                 ((d_out + 16 * nt - 1) / (16 * nt) * (16 * nt));
-            if (area * COST[i][j] < least) {
-                least = area * COST[i][j];
-                best = {va, nt};
-            }
+            if ((i == 2 && j == 3) || (j > 0 && d_out <= 8 << j)) continue;  // (a piece of G is no wider than G)
+            const int64_t cost = weight_grad_cost(i, j, d_in, d_out);
+            if (cost < best.cost) best = {1 << i, 1 << j, cost};
         }
     return best;
+}
+
+// Columns of G that come first: all of them, or whole tiles of 128 where up to eight more are cheaper on a narrow tile in a
+// launch of their own.  X is read once more for those, so the line lies where the table says a sixth of the time and 20 us
+// less, next to more than 64 columns of X in fp32 (24 such products of 200 000 to 10^6 rows: 0.82 of the time on average, at
+// most 1.03; fp32 10^6 x 200 -> 136 1433 / 1192 us, 200 000 x 200 -> 129 327 / 199).  With a tenth instead of a sixth 100 -> 129 and
+// 65 -> 264 lose 10 to 17 % at 500 000 rows; 16-bit X, where the first launch is bound by its reads sooner, up to 16 %.
+static int weight_grad_first_columns(int n, int xdt, int d_in, int d_out)
+{
+    const int first = d_out / 128 * 128, rest = d_out - first;
+    if (xdt != FTC_F32 || first == 0 || rest == 0 || rest > 8 || d_in <= 64) return d_out;
+    const int64_t whole = weight_grad_tile(d_in, d_out).cost;  // 10^-4 ps a row
+    const int64_t saved = whole - weight_grad_tile(d_in, first).cost - weight_grad_tile(d_in, rest).cost;
+    return saved * 6 >= whole && saved >= 200000000000 / (n < 1 ? 1 : n) ? first : d_out;
 }
 
 // dW = X^T (G masked by Y; Y == NULL: no mask).  The shares of the rows: enough workgroups for the chip, at least 64 rows
@@ -429,12 +442,17 @@ int32_t launch_weight_grad(int n, const void *X, int ldx, int xdt, int d_in, con
                            const void *Y, int ldy, int ydt, float *dW, void *ws, hipStream_t s)
 {
     const int64_t room = static_cast<int64_t>(weight_grad_blocks(n)) * weight_grad_group(d_in, d_out);  // columns x shares
-    const WgTile tile = weight_grad_tile(d_in, d_out);
-    const int nt = tile.nt, va = tile.va;
-    const int groups_b = (d_out + 16 * nt - 1) / (16 * nt);
-    const int64_t tiles = static_cast<int64_t>((d_in + 16 * va - 1) / (16 * va)) * groups_b;
+    const int first = weight_grad_first_columns(n, xdt, d_in, d_out);
     const int64_t least = n / (384 + n / 384);
-    int64_t want = (nt == 4 ? 2048 : 1024) / tiles;  // workgroups; with 33 to 64 columns of G more, for shorter sums
+    int64_t want = 0;
+    for (int b = 0; b < d_out; b = b == 0 ? first : d_out) {
+        const int db = b == 0 ? first : d_out - first;
+        const WgTile tile = weight_grad_tile(d_in, db);
+        const int64_t tiles = static_cast<int64_t>((d_in + 16 * tile.va - 1) / (16 * tile.va)) *
+                              ((db + 16 * tile.nt - 1) / (16 * tile.nt));
+        const int64_t fill = (tile.nt == 4 ? 2048 : 1024) / tiles;  // with 33 to 64 columns of G more, for shorter sums
+        if (fill > want) want = fill;
+    }
     if (want < least) want = least;
     if (want > (n + 63) / 64) want = (n + 63) / 64;
     if (want < 1) want = 1;
@@ -456,28 +474,32 @@ int32_t launch_weight_grad(int n, const void *X, int ldx, int xdt, int d_in, con
     const unsigned limit = ydt == FTC_F16 ? 0x7c00u : 0x7f80u;
     for (int k0 = 0; k0 < d_in; k0 += group) {
         const int dk = d_in - k0 < group ? d_in - k0 : group;
-        const int vk = dk <= 16 ? 1 : va;
-        const dim3 grid(static_cast<unsigned>(splits), (dk + 16 * vk - 1) / (16 * vk), groups_b);
         float *lost = rounds > 1 ? partial + static_cast<size_t>(splits) * dk * d_out : nullptr;
         int64_t r0 = 0;
         do {  // once with n == 0: dW is cleared
             const int rows = static_cast<int>(n - r0 < per_round ? n - r0 : per_round);
             const void *Xr = static_cast<const char *>(X) + (r0 * ldx + k0) * elem_size(xdt);
-            const float *Gr = G + r0 * ldg;
-            const void *Yr = Y ? static_cast<const char *>(Y) + r0 * ldy * elem_size(ydt) : nullptr;
+            for (int b = 0; b < d_out; b = b == 0 ? first : d_out) {
+                const int db = b == 0 ? first : d_out - first;
+                const WgTile tile = weight_grad_tile(d_in, db);
+                const int nt = tile.nt, va = dk <= 16 ? 1 : tile.va;
+                const dim3 grid(static_cast<unsigned>(splits), (dk + 16 * va - 1) / (16 * va), (db + 16 * nt - 1) / (16 * nt));
+                const float *Gr = G + r0 * ldg + b;
+                const void *Yr = Y ? static_cast<const char *>(Y) + (r0 * ldy + b) * elem_size(ydt) : nullptr;
 #define FTC_WGT(T)                                                                                                        \
     do {                                                                                                                  \
-        if (vk == 1) weight_grad_t<T, 1>(nt, mask, grid, s, rows, Xr, ldx, dk, Gr, ldg, d_out, Yr, ldy, limit, partial,   \
-                                         static_cast<int>(splits));                                                       \
-        else if (vk == 2) weight_grad_t<T, 2>(nt, mask, grid, s, rows, Xr, ldx, dk, Gr, ldg, d_out, Yr, ldy, limit,       \
-                                              partial, static_cast<int>(splits));                                         \
-        else weight_grad_t<T, 4>(nt, mask, grid, s, rows, Xr, ldx, dk, Gr, ldg, d_out, Yr, ldy, limit, partial,           \
+        if (va == 1) weight_grad_t<T, 1>(nt, mask, grid, s, rows, Xr, ldx, dk, Gr, ldg, db, Yr, ldy, limit, partial + b,  \
+                                         d_out, static_cast<int>(splits));                                                \
+        else if (va == 2) weight_grad_t<T, 2>(nt, mask, grid, s, rows, Xr, ldx, dk, Gr, ldg, db, Yr, ldy, limit,          \
+                                              partial + b, d_out, static_cast<int>(splits));                              \
+        else weight_grad_t<T, 4>(nt, mask, grid, s, rows, Xr, ldx, dk, Gr, ldg, db, Yr, ldy, limit, partial + b, d_out,   \
                                  static_cast<int>(splits));                                                               \
     } while (0)
-            if (xdt == FTC_F32) FTC_WGT(F32);
-            else if (xdt == FTC_F16) FTC_WGT(F16);
-            else FTC_WGT(BF16);
+                if (xdt == FTC_F32) FTC_WGT(F32);
+                else if (xdt == FTC_F16) FTC_WGT(F16);
+                else FTC_WGT(BF16);
 #undef FTC_WGT
+            }
             hipLaunchKernelGGL(sum_partials_kernel, dim3((dk * d_out + 63) / 64), dim3(256), 0, s, dk * d_out,
                                static_cast<int>(splits), partial, dW + static_cast<size_t>(k0) * d_out, lost, r0 == 0);
             r0 += per_round;

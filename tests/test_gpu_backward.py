@@ -734,6 +734,26 @@ def test_weight_grad_edges(dtype, n, d_in, d_out):
         assert term_err(dWm, X64.T @ M64, np.abs(X64).T @ np.abs(M64)) < 1e-5
 
 
+@pytest.mark.parametrize("n,d_in,d_out", [(100_000, 200, 136), (200_001, 65, 129), (150_007, 257, 257)])
+def test_weight_grad_with_a_few_columns_beyond_the_tiles_of_128(n, d_in, d_out):
+    """fp32 products whose last columns of G (8 and 1 beyond 128, 1 beyond 256) take a launch of their own: both write their part
+    of every share's result; rows at element alignment, with and without the mask.  Against 64 bits in torch."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n)
+    X = torch.randn((n, d_in + 1), generator=gen, device="cuda")[:, 1:]
+    G = torch.randn((n, d_out + 2), generator=gen, device="cuda")[:, 2:]
+    say(f"weight grad fp32 {n} x {d_in} -> {d_out}")
+    X64, G64 = X.double().cpu(), G.double().cpu()
+    terms = (X64.abs().T @ G64.abs()).numpy()
+    assert term_err(B.ftc_weight_grad(X, G), (X64.T @ G64).numpy(), terms) < 1e-5
+    W = torch.zeros((d_in, d_out), device="cuda")
+    for zt in (F32, F16):
+        Z = torch.randn((n, d_out), generator=gen, device="cuda").to(zt)
+        M64 = torch.where(Z.cpu() > 0, G64, 0.0)
+        _, dW = B.ftc_update_gemm_backward(X, W, G, Z=Z, want_dX=False)
+        assert term_err(dW, (X64.T @ M64).numpy(), terms) < 1e-5
+
+
 @pytest.mark.parametrize("n,d_in,d_out,dtype", [(200_000, 1433, 256, F16), (100_000, 1024, 504, BF16), (300_000, 700, 100, F32)])
 def test_weight_grad_of_wide_products_over_many_rows(n, d_in, d_out, dtype):
     """The chains of additions are bounded however wide the product: a wave adds a quarter of a share of at most
