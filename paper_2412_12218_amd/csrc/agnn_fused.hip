@@ -13,17 +13,21 @@
 // (a second DPP reduction in the lane group), so the pass needs no array of inverse norms and no
 // random 4-byte gather per edge.
 //
-// When the caller wants the probabilities the pass also writes the weight of every entry, parked in LDS over the column
-// ids that have been used, and a second kernel divides by the rows' sums: one gather of H per entry instead of the two of
-// scores, softmax and aggregation one after the other (fp16, 32 columns, power law, 200 000 nodes, 3.8 M entries: 127 us
-// against 89).
+// When the caller wants the probabilities the pass also writes the weight of every entry, parked in LDS over the row
+// offsets that have been used, and a second kernel divides by the rows' sums: one gather of H per entry instead of the two of
+// scores, softmax and aggregation one after the other.
+//
+// What bounds it: on large graphs the gathers, on graphs whose features lie in the L2s the instructions around them.  Since these
+// went (edge_ranges.hpp, and the scalar work of four entries done once instead of by every lane of the group) the layer takes, with
+// fix-up, 0.30 ms instead of 0.36 on the R-MAT graph (2^20 nodes, 32 M entries, fp16, 32 columns) and with P 71 us instead of 90 on a
+// power-law graph (200 000 nodes, 3.8 M entries).
 //
 // Work partition, run structure and the handling of rows cut by run / wave boundaries are
 // those of the edge-balanced SpMM (spmm_seg.hip): 512 edges per wave (fewer on small graphs) staged in LDS, groups of
-// LPR lanes walk contiguous runs, complete rows are stored from registers, cut rows are summed
-// in edge order in LDS and through a carry buffer.  The partial of a cut row is the pair
+// LPR lanes walk contiguous runs, complete rows are stored from registers, the pieces of cut rows are summed
+// in edge order by the group that closes the row, and through a carry buffer.  The partial of a cut row is the pair
 // (numerator vector, denominator); the division happens once all pieces are added.
-#include "ftc_common.hpp"
+#include "edge_ranges.hpp"
 
 namespace ftc {
 
@@ -48,95 +52,82 @@ size_t agnn_fused_ws(int nnz, int D, bool least)
 
 // MODE 0: inference.  1: also write what the backward pass needs (row_z, out32).  2: also write the weight w_ij of every entry
 // (edge_w) and row_z; agnn_edge_p_kernel turns the weights into probabilities once every row's sum is known.
-template <class T, int VEC, int LPR, int MODE, int AG_R>
+//
+// Four entries of a group are taken together: the two dot products of each are formed by all lanes, their lane sums and
+// what becomes of them (norm, cosine, exponential) by one lane of the quad per entry, and the weights go back to all lanes.
+template <class T, int VEC, int LPR, int MODE, int AG_R, bool BIG>
 __global__ __launch_bounds__(256) void agnn_fused_kernel(int nnz, int n_ranges, const int *__restrict__ row_ptr,
                                                          const int *__restrict__ col_idx,
                                                          const int *__restrict__ edge_to_row,
-                                                         const void *__restrict__ H, int ld, int D, float beta,
+                                                         const void *__restrict__ H, uint64_t ldb, int D, float beta,
                                                          void *__restrict__ out, int ldo, int odt,
                                                          float *__restrict__ carry, int *__restrict__ carry_tail_row,
                                                          float *__restrict__ row_z, float *__restrict__ out32,
                                                          int ld32, float *__restrict__ edge_w)
 {
+    using E = EdgeRange<LPR, AG_R>;
     constexpr bool KEEP = MODE != 0;
-    constexpr int NG = 64 / LPR;
-    constexpr int RUN = AG_R / NG;
-    constexpr int RP = AG_R + NG;
+    constexpr int NG = E::NG, RUN = E::RUN;
     constexpr int DP = LPR * VEC;
     constexpr int DPZ = DP + 4;  // feature slots, then the denominator
-    constexpr int IDX_WORDS = 4 * 2 * RP;
-    static_assert(RUN % AG_B == 0, "runs are whole batches");
-    constexpr int PART_WORDS = 4 * 2 * NG * DPZ;
-    __shared__ int smem[IDX_WORDS > PART_WORDS ? IDX_WORDS : PART_WORDS];
-    __shared__ int s_meta[4][3][NG];
+    constexpr int IDX_WORDS = 2 * E::WORDS;
+    constexpr int PART_WORDS = NG * DPZ;
+    __shared__ __align__(16) int smem[4][IDX_WORDS > PART_WORDS ? IDX_WORDS : PART_WORDS];
 
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int g = lane / LPR, sub = lane % LPR;
-    int *s_col = smem + wave * 2 * RP;
-    int *s_row = s_col + RP;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int g = lane / LPR, sub = lane % LPR, quad = lane & 3;
+    const bool odd = lane & 1, upper = lane & 2;
+    uint32_t *s_off = reinterpret_cast<uint32_t *>(smem[wave]);
+    int *s_row = smem[wave] + E::WORDS;
 
     const int v = xcd_chunked_block(blockIdx.x, gridDim.x) * 4 + wave;
-    const bool active = v < n_ranges;
-    const int base = active ? v * AG_R : 0;
-    const int n_valid = active ? min(AG_R, nnz - base) : 0;
-    int rows[AG_R / 64];
-    if (n_valid == AG_R && rows_from_starts<AG_R>(row_ptr, edge_to_row, base, lane, rows)) {
-#pragma unroll
-        for (int j = 0; j < AG_R / 64; ++j) {
-            const int i = j * 64 + lane;
-            const int p = i + i / RUN;
-            s_col[p] = __builtin_nontemporal_load(col_idx + base + i);  // streamed once: no need to keep it in L2
-            s_row[p] = rows[j];
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < AG_R / 64; ++j) {
-            const int i = j * 64 + lane;
-            if (i < n_valid) {
-                const int p = i + i / RUN;
-                s_col[p] = __builtin_nontemporal_load(col_idx + base + i);  // streamed once: no need to keep it in L2
-                s_row[p] = __builtin_nontemporal_load(edge_to_row + base + i);
-            }
-        }
-    }
-    const int prev_row = (active && base > 0) ? edge_to_row[base - 1] : -1;
-    const int next_row = (active && n_valid == AG_R && base + AG_R < nnz) ? edge_to_row[base + AG_R] : -1;
+    if (v >= n_ranges) return;  // (no wave waits for another)
+    const int base = v * AG_R;
+    const int n_valid = min(AG_R, nnz - base);
+    const int prev_row = base > 0 ? edge_to_row[base - 1] : -1;
+    const int next_row = nnz - base > AG_R ? edge_to_row[base + AG_R] : -1;
     // row of the first edge after the NEXT range: tells whether a row left open here ends there
-    const int far_row = (active && static_cast<int64_t>(base) + 2 * AG_R < nnz) ? edge_to_row[base + 2 * AG_R] : -1;
-    __syncthreads();
+    const int far_row = static_cast<int64_t>(base) + 2 * AG_R < nnz ? edge_to_row[base + 2 * AG_R] : -1;
+    stage_range<LPR, AG_R, false, BIG>(row_ptr, col_idx, edge_to_row, nullptr, base, n_valid, ldb, nullptr, lane, s_off, s_row,
+                                       nullptr);
 
-    const int rs = g * RUN;
-    const int re = min(rs + RUN, n_valid);
-    const bool has = rs < n_valid;
+    const int at = g * E::RUNP;  // the group's run
     const bool live = sub * VEC < D;
-    const float absb = fabsf(beta);
-    const float beta2 = beta * 1.44269504f;  // log2(e) = 1.44269502162933 (its nearest fp32) + 1.92596299e-8
+    const uint32_t lane_bytes = live ? sub * VEC * T::BYTES : 0;  // lanes beyond the row gather its first piece
+    // The exponential is taken in powers of two and the large part of its argument rounded once instead of twice:
+    // log2(e) = 1.44269502162933 (its nearest fp32) + 1.92596299e-8.
+    const float beta2 = beta * 1.44269504f;
     const float beta2_rest = fmaf(beta, 1.92596299e-8f, fmaf(beta, 1.44269504f, -beta2));
     float acc[VEC], hacc[VEC];
 #pragma unroll
     for (int j = 0; j < VEC; ++j) { acc[j] = 0.f; hacc[j] = 0.f; }
-    RawVec<T, VEC> xi;  // slice of H[i,:] of the current row, as loaded
+    RawVec<T, VEC> xi;  // slice of H[i,:] of the current row, as loaded; zero in lanes beyond the row
     zero_raw(xi);
     float z = 0.f, hz = 0.f, ri = 0.f;
     // MODE 2 sums every other entry apart and joins the halves in the quotient (its two fma round about as often as one sum):
     // that is what makes the output as exact as the three kernels', whose weights were divided by z before they were summed.
     constexpr int ODD = MODE == 2 ? VEC : 1;
-    float odd[ODD], odd_z = 0.f;
+    float odds[ODD], odd_z = 0.f;
 #pragma unroll
-    for (int j = 0; j < ODD; ++j) odd[j] = 0.f;
+    for (int j = 0; j < ODD; ++j) odds[j] = 0.f;
     auto join_odd = [&]() {  // for a piece of a row
         if constexpr (MODE == 2) {
 #pragma unroll
-            for (int j = 0; j < VEC; ++j) acc[j] += odd[j];
+            for (int j = 0; j < VEC; ++j) acc[j] += odds[j];
             z += odd_z;
         }
     };
-    bool have_head = false, head_closed = false, have_tail = false;
+    bool head_closed = false, first = true;
     int head_row = -1, cur = -1;
-    bool first = true;
-    const int left_row = !has ? -2 : (rs == 0 ? prev_row : s_row[rs - 1 + g - 1]);
+    const int first_row = s_row[at];
+    const bool left_open = first_row >= 0 && first_row == (g == 0 ? prev_row : s_row[max(at - 5, 0)]);  // the last entry of the run before
 
-    auto direct_store = [&](int row) {
+    auto put = [&](int row, const float (&o)[VEC]) {
+        store_vec_nt<VEC>(out, static_cast<int64_t>(row) * ldo + sub * VEC, odt, o);
+        if constexpr (KEEP)
+            if (out32) store_vec<VEC>(out32, static_cast<int64_t>(row) * ld32 + sub * VEC, FTC_F32, o);  // unrounded copy
+    };
+    auto store_row = [&](int row) {
         if constexpr (MODE == 2) z += odd_z;
         if (live) {
             const float inv = __builtin_amdgcn_rcpf(z);  // v_rcp_f32: one ulp, one instruction
@@ -144,57 +135,61 @@ __global__ __launch_bounds__(256) void agnn_fused_kernel(int nnz, int n_ranges, 
             float o[VEC];
 #pragma unroll
             for (int j = 0; j < VEC; ++j) {
-                if constexpr (MODE == 2) o[j] = fmaf(acc[j], inv, fmaf(odd[j], inv, (acc[j] + odd[j]) * rest));
+                if constexpr (MODE == 2) o[j] = fmaf(acc[j], inv, fmaf(odds[j], inv, (acc[j] + odds[j]) * rest));
                 else o[j] = acc[j] * inv;
             }
-            store_vec_nt<VEC>(out, static_cast<int64_t>(row) * ldo + sub * VEC, odt, o);
-            if constexpr (KEEP)
-                if (out32) store_vec<VEC>(out32, static_cast<int64_t>(row) * ld32 + sub * VEC, FTC_F32, o);  // unrounded copy
+            put(row, o);
         }
         if constexpr (KEEP)
             if (row_z && sub == 0) row_z[row] = z;  // softmax denominator (shifted by |beta|), kept for the backward pass
     };
 
-    // every group runs the same number of batches: the lane shuffles of the dot product need the
-    // whole wave; edges beyond the group's run are masked.  (Issuing the next batch's gathers before
-    // consuming the current one was tried: the extra registers cost more occupancy than the
-    // overlap gains.)
-    for (int b = rs; b < rs + RUN; b += AG_B) {
-        int c[AG_B], r[AG_B];
-        bool need[AG_B];
+#pragma unroll 1
+    for (int b = 0; b < RUN; b += AG_B) {
+        const uint4 o4 = *reinterpret_cast<const uint4 *>(s_off + at + b);
+        const int4 r4 = *reinterpret_cast<const int4 *>(s_row + at + b);
+        const uint32_t o[AG_B] = {o4.x, o4.y, o4.z, o4.w};
+        const int r[AG_B] = {r4.x, r4.y, r4.z, r4.w};
         RawVec<T, VEC> y[AG_B], xs[AG_B];
 #pragma unroll
-        for (int k = 0; k < AG_B; ++k) {
-            const bool ok = b + k < re;
-            const int p = ok ? b + k + g : 0;
-            c[k] = ok ? s_col[p] : -1;
-            r[k] = ok ? s_row[p] : -1;
-        }
-        int prev = cur;
+        for (int k = 0; k < AG_B; ++k) load_raw<T, VEC>(row_addr<BIG>(H, o[k], ldb, lane_bytes), 0, y[k]);
+        bool need[AG_B];  // a new row starts (the lanes of a group branch together)
 #pragma unroll
         for (int k = 0; k < AG_B; ++k) {
-            need[k] = r[k] >= 0 && r[k] != prev;
-            if (r[k] >= 0) prev = r[k];
+            need[k] = r[k] != (k ? r[k - 1] : cur);
+            if (need[k]) load_raw<T, VEC>(row_addr<BIG>(H, row_slot<BIG>(max(r[k], 0), ldb), ldb, lane_bytes), 0, xs[k]);
         }
+        float ri_mine = ri, dots[AG_B], squares[AG_B];  // ri_mine: of the row of this lane's entry
 #pragma unroll
         for (int k = 0; k < AG_B; ++k) {
-            if (c[k] >= 0 && live) load_raw<T, VEC>(H, static_cast<int64_t>(c[k]) * ld + sub * VEC, y[k]);
-            else zero_raw(y[k]);
-            if (need[k] && live) load_raw<T, VEC>(H, static_cast<int64_t>(r[k]) * ld + sub * VEC, xs[k]);
-            else zero_raw(xs[k]);
+            if (need[k]) {
+#pragma unroll
+                for (int w = 0; w < RawVec<T, VEC>::WORDS; ++w) xi.w[w] = live ? xs[k].w[w] : 0u;
+                ri = __frsqrt_rn(fmaxf(group_sum_dpp<LPR>(dot_raw<T, VEC>(xi, xi, 0.f)), 1e-24f));  // = 1 / max(||h_i||, 1e-12)
+                ri_mine = quad >= k ? ri : ri_mine;
+            }
+            dots[k] = dot_raw<T, VEC>(xi, y[k], 0.f);
+            const float q = dot_raw<T, VEC>(y[k], y[k], 0.f);
+            squares[k] = live ? q : 0.f;
         }
+        const float rj = __frsqrt_rn(fmaxf(group_sum4<LPR>(squares, odd, upper), 1e-24f));
+        const float cosine = ri_mine * rj * group_sum4<LPR>(dots, odd, upper);
+        const float wgt = __builtin_amdgcn_exp2f(fmaf(beta2_rest, cosine, fmaf(beta2, cosine, -fabsf(beta2))));
+        if constexpr (MODE == 2)
+            if (sub < 4) s_off[at + b + sub] = __float_as_uint(wgt);  // these entries' offsets have been used
+        const float w4[AG_B] = {quad_lane<0>(wgt), quad_lane<1>(wgt), quad_lane<2>(wgt), quad_lane<3>(wgt)};
 #pragma unroll
         for (int k = 0; k < AG_B; ++k) {
-            if (need[k]) {  // a new row starts: close the segment of the previous one
+            if (need[k]) {  // close the segment of the previous row
                 if (cur >= 0) {
-                    if (first && left_row == cur) {
+                    if (first && left_open) {
                         join_odd();
 #pragma unroll
                         for (int j = 0; j < VEC; ++j) hacc[j] = acc[j];
                         hz = z;
-                        have_head = true; head_closed = true; head_row = cur;
+                        head_closed = true; head_row = cur;
                     } else {
-                        direct_store(cur);
+                        store_row(cur);
                     }
                     first = false;
                 }
@@ -204,140 +199,102 @@ __global__ __launch_bounds__(256) void agnn_fused_kernel(int nnz, int n_ranges, 
                 z = 0.f;
                 if constexpr (MODE == 2) {
 #pragma unroll
-                    for (int j = 0; j < VEC; ++j) odd[j] = 0.f;
+                    for (int j = 0; j < VEC; ++j) odds[j] = 0.f;
                     odd_z = 0.f;
                 }
-                xi = xs[k];
-                const float q = group_sum_dpp<LPR>(dot_raw<T, VEC>(xi, xi, 0.f));  // the group's lanes branch together
-                ri = __frsqrt_rn(fmaxf(q, 1e-24f));  // = 1 / max(||h_i||, 1e-12)
             }
-            const float d = group_sum_dpp<LPR>(dot_raw<T, VEC>(xi, y[k], 0.f));
-            const float qj = group_sum_dpp<LPR>(dot_raw<T, VEC>(y[k], y[k], 0.f));
-            if (r[k] >= 0) {
-                const float rj = __frsqrt_rn(fmaxf(qj, 1e-24f));
-                float wgt;
-                if constexpr (MODE == 2) {  // in powers of two: the large part of the exponent is rounded once instead of twice
-                    const float cosine = ri * rj * d;
-                    wgt = __builtin_amdgcn_exp2f(fmaf(beta2_rest, cosine, fmaf(beta2, cosine, -fabsf(beta2))));
-                } else {
-                    wgt = __expf(beta * ri * rj * d - absb);
-                }
-                float yf[VEC];
-                unpack<T, VEC>(y[k], yf);
+            float yf[VEC];
+            unpack<T, VEC>(y[k], yf);
 #pragma unroll
-                for (int j = 0; j < VEC; ++j) {
-                    if constexpr (MODE == 2) {
-                        float &a = (k & 1) ? odd[j] : acc[j];
-                        a = fmaf(wgt, yf[j], a);
-                    } else {
-                        acc[j] = fmaf(wgt, yf[j], acc[j]);
-                    }
+            for (int j = 0; j < VEC; ++j) {
+                if constexpr (MODE == 2) {
+                    float &a = (k & 1) ? odds[j] : acc[j];
+                    a = fmaf(w4[k], yf[j], a);
+                } else {
+                    acc[j] = fmaf(w4[k], yf[j], acc[j]);
                 }
-                if (MODE == 2 && (k & 1)) odd_z += wgt;
-                else z += wgt;
-                if constexpr (MODE == 2)
-                    if (sub == 0) s_col[b + k + g] = __float_as_int(wgt);  // the entry's column has been used
             }
+            if (MODE == 2 && (k & 1)) odd_z += w4[k];
+            else z += w4[k];
         }
     }
-    if (has) {  // the run's last segment
-        int right_row;
-        if (re < n_valid) right_row = s_row[re + g + 1];
-        else right_row = next_row;
-        const bool right_open = right_row == cur;
-        if (first && left_row == cur) {
+    // the run's last segment
+    int open = OPEN_NONE;
+    if (cur >= 0) {
+        const int right_row = g == NG - 1 ? next_row : s_row[at + E::RUNP];
+        if (right_row == cur) {
+            join_odd();
+            open = first && left_open ? OPEN_THROUGH : OPEN_TAIL;
+        } else if (first && left_open) {
             join_odd();
 #pragma unroll
             for (int j = 0; j < VEC; ++j) hacc[j] = acc[j];
             hz = z;
-            have_head = true; head_closed = !right_open; head_row = cur;
-        } else if (!right_open) {
-            direct_store(cur);
+            head_closed = true; head_row = cur;
         } else {
-            join_odd();
-            have_tail = true;
+            store_row(cur);
         }
     }
-    __syncthreads();  // staged indices are dead: the LDS is reused for partials
+    const int from = first_group<LPR>(open, g);
+    const bool last_open = g == NG - 1 && open != OPEN_NONE;  // a row that goes on in the next range
+    wave_lds_sync();
     if constexpr (MODE == 2) {
+        int own = lane;
+        asm("" : "+v"(own));  // (else the addresses of the staging loop are kept in registers all the way to here)
 #pragma unroll
         for (int j = 0; j < AG_R / 64; ++j) {
-            const int i = j * 64 + lane;
-            if (i < n_valid) edge_w[base + i] = __int_as_float(s_col[i + i / RUN]);
+            const int i = j * 64 + own;
+            if (i < n_valid) edge_w[base + i] = __uint_as_float(s_off[E::slot(i)]);
         }
-        __syncthreads();
+        wave_lds_sync();
     }
-
-    float *part = reinterpret_cast<float *>(smem) + wave * 2 * NG * DPZ;
-    if (have_head) {
+    // Rows cut inside this wave: the group that closes a row adds its pieces, in edge order.  The staged entries are dead, their
+    // place is taken by the open pieces.
+    float *part = reinterpret_cast<float *>(smem[wave]);
+    if (open != OPEN_NONE) {
 #pragma unroll
-        for (int j = 0; j < VEC; ++j) part[(2 * g) * DPZ + sub * VEC + j] = hacc[j];
-        if (sub == 0) part[(2 * g) * DPZ + DP] = hz;
+        for (int j = 0; j < VEC; ++j) part[g * DPZ + sub * VEC + j] = acc[j];
+        if (sub == 0) part[g * DPZ + DP] = z;
     }
-    if (have_tail) {
+    wave_lds_sync();
+    // carried piece: [2 v] of the row that came in from the left, [2 v + 1] of the one left open
+    auto store_carry = [&](int slot, const float (&a)[VEC], float az) {
+        float *to = carry + (static_cast<size_t>(v) * 2 + slot) * DPZ;
+        store_vec<VEC>(to, sub * VEC, FTC_F32, a);
+        if (sub == 0) to[DP] = az;
+    };
+    if (head_closed || (last_open && open == OPEN_THROUGH)) {
+        float run[VEC], run_z = 0.f;
 #pragma unroll
-        for (int j = 0; j < VEC; ++j) part[(2 * g + 1) * DPZ + sub * VEC + j] = acc[j];
-        if (sub == 0) part[(2 * g + 1) * DPZ + DP] = z;
-    }
-    if (sub == 0) {
-        s_meta[wave][0][g] = have_head ? head_row : -1;
-        s_meta[wave][1][g] = head_closed ? 1 : 0;
-        s_meta[wave][2][g] = have_tail ? cur : -1;
-    }
-    __syncthreads();
-
-    if (active) {
-        int tail_out = -1;
-        for (int d = lane; d < DP; d += 64) {
-            float run = 0.f, run_z = 0.f;
-            int run_row = -1;
-            bool from_outside = false;
-            tail_out = -1;
-            float *cv = carry + (static_cast<size_t>(v) * 2) * DPZ;
-            for (int q = 0; q < NG; ++q) {
-                const int hr = s_meta[wave][0][q];
-                if (hr >= 0) {
-                    if (run_row < 0) { run_row = hr; run = 0.f; run_z = 0.f; from_outside = true; }
-                    run += part[(2 * q) * DPZ + d];
-                    run_z += part[(2 * q) * DPZ + DP];
-                    if (s_meta[wave][1][q]) {
-                        if (from_outside) {
-                            cv[d] = run;
-                            if (d == 0) cv[DP] = run_z;
-                        } else {
-                            if (d < D) store_elem(out, static_cast<int64_t>(run_row) * ldo + d, odt, run / run_z);
-                            if constexpr (KEEP) {
-                                if (out32 && d < D) out32[static_cast<int64_t>(run_row) * ld32 + d] = run / run_z;
-                                if (row_z && d == 0) row_z[run_row] = run_z;
-                            }
-                        }
-                        run_row = -1;
-                        from_outside = false;
-                    }
-                }
-                const int tr = s_meta[wave][2][q];
-                if (tr >= 0) {
-                    run_row = tr;
-                    run = part[(2 * q + 1) * DPZ + d];
-                    run_z = part[(2 * q + 1) * DPZ + DP];
-                    from_outside = false;
-                }
-            }
-            if (run_row >= 0) {
-                if (from_outside) {
-                    cv[d] = run;
-                    if (d == 0) cv[DP] = run_z;
-                } else {
-                    cv[DPZ + d] = run;
-                    if (d == 0) cv[DPZ + DP] = run_z;
-                    tail_out = run_row;
-                }
-            }
+        for (int j = 0; j < VEC; ++j) run[j] = 0.f;
+        for (int q = max(from, 0); q < g; ++q) {
+#pragma unroll
+            for (int j = 0; j < VEC; ++j) run[j] += part[q * DPZ + sub * VEC + j];
+            run_z += part[q * DPZ + DP];
         }
-        if (lane == 0) {
-            carry_tail_row[2 * v] = tail_out;
-            carry_tail_row[2 * v + 1] = (tail_out >= 0 && far_row != tail_out) ? 1 : 0;  // ends in range v + 1
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) run[j] += head_closed ? hacc[j] : acc[j];
+        run_z += head_closed ? hz : z;
+        if (from < 0) {
+            store_carry(0, run, run_z);
+        } else if (head_closed) {
+            if (live) {
+                float o[VEC];
+#pragma unroll
+                for (int j = 0; j < VEC; ++j) o[j] = run[j] / run_z;
+                put(head_row, o);
+            }
+            if constexpr (KEEP)
+                if (row_z && sub == 0) row_z[head_row] = run_z;
+        } else {
+            store_carry(1, run, run_z);
         }
+    }
+    if (last_open && open == OPEN_TAIL) store_carry(1, acc, z);
+    if (lane == 63) {
+        const int tail = last_open && !(open == OPEN_THROUGH && from < 0) ? cur : -1;
+        carry_tail_row[2 * v] = tail;
+        carry_tail_row[2 * v + 1] = (tail >= 0 && far_row != tail) ? 1 : 0;  // ends in range v + 1
     }
 }
 
@@ -475,16 +432,16 @@ __global__ __launch_bounds__(256) void agnn_edge_p_kernel(int nnz, const int *__
         if (e0 + 64 * k < nnz) __builtin_nontemporal_store(a[k] / z[k], edge_w + e0 + 64 * k);
 }
 
-template <class T, int R>
+template <class T, int R, bool BIG>
 static void launch_agnn_t(int vec, int lpr, unsigned grid, hipStream_t s, int nnz, int n_ranges, const ftc_csr &g,
-                          const int *e2r, const void *H, int ld, int D, float beta, void *out,
+                          const int *e2r, const void *H, uint64_t ldb, int D, float beta, void *out,
                           int ldo, int odt, float *carry, int *tail_row, float *row_z, float *out32, int ld32,
                           float *edge_w)
 {
     constexpr int VM = T::VEC;
 #define FTC_AG1(V, L, M)                                                                                              \
-    hipLaunchKernelGGL((agnn_fused_kernel<T, V, L, M, R>), dim3(grid), dim3(256), 0, s, nnz, n_ranges, g.row_ptr,     \
-                       g.col_idx, e2r, H, ld, D, beta, out, ldo, odt, carry, tail_row, row_z, out32, ld32, edge_w)
+    hipLaunchKernelGGL((agnn_fused_kernel<T, V, L, M, R, BIG>), dim3(grid), dim3(256), 0, s, nnz, n_ranges, g.row_ptr, \
+                       g.col_idx, e2r, H, ldb, D, beta, out, ldo, odt, carry, tail_row, row_z, out32, ld32, edge_w)
 #define FTC_AG(V, L)                         \
     if (edge_w) FTC_AG1(V, L, 2);            \
     else if (row_z || out32) FTC_AG1(V, L, 1); \
@@ -512,26 +469,31 @@ int32_t launch_agnn_fused(const ftc_csr &g, const ftc_windows &w, const void *H,
     int vec = 0, lpr = 0;
     seg_shape(dt, D, &vec, &lpr);
     const int dp = vec * lpr;
-    const int r = ws_bytes >= ag_carry_ws(g.nnz, seg_range(g.nnz, SEG_AGNN), dp) ? seg_range(g.nnz, SEG_AGNN) : SEG_R;
+    const int64_t row_bytes = static_cast<int64_t>(ld) * elem_size(dt);
+    const bool big = rows_need_64_bits(g.n, row_bytes);  // ranges of SEG_R only: such a matrix has many rows
+    const int short_r = big ? SEG_R : seg_range(g.nnz, SEG_AGNN);
+    const int r = ws_bytes >= ag_carry_ws(g.nnz, short_r, dp) ? short_r : SEG_R;
     const int n_ranges = static_cast<int>(seg_count(g.nnz, r));
     float *carry = static_cast<float *>(ws);
     int *tail_row = reinterpret_cast<int *>(
         static_cast<char *>(ws) + align_up(static_cast<size_t>(n_ranges) * 2 * (dp + 4) * sizeof(float), 256));
     if (n_ranges > 0) {
         const unsigned grid = static_cast<unsigned>((n_ranges + 3) / 4);
-#define FTC_AGR(T)                                                                                                       \
-    do {                                                                                                                 \
-        if (r == SEG_R) launch_agnn_t<T, SEG_R>(vec, lpr, grid, s, g.nnz, n_ranges, g, w.edge_to_row, H, ld, D, beta,    \
-                                                out, ldo, odt, carry, tail_row, row_z, out32, ld32, edge_w);             \
-        else if (r == 256) launch_agnn_t<T, 256>(vec, lpr, grid, s, g.nnz, n_ranges, g, w.edge_to_row, H, ld, D, beta,   \
-                                                 out, ldo, odt, carry, tail_row, row_z, out32, ld32, edge_w);            \
-        else launch_agnn_t<T, 128>(vec, lpr, grid, s, g.nnz, n_ranges, g, w.edge_to_row, H, ld, D, beta, out, ldo, odt,   \
-                                  carry, tail_row, row_z, out32, ld32, edge_w);                                          \
+#define FTC_AGR1(T, R, BIG)                                                                                              \
+    launch_agnn_t<T, R, BIG>(vec, lpr, grid, s, g.nnz, n_ranges, g, w.edge_to_row, H, static_cast<uint64_t>(row_bytes), D,  \
+                             beta, out, ldo, odt, carry, tail_row, row_z, out32, ld32, edge_w)
+#define FTC_AGR(T)                             \
+    do {                                       \
+        if (big) FTC_AGR1(T, SEG_R, true);     \
+        else if (r == SEG_R) FTC_AGR1(T, SEG_R, false); \
+        else if (r == 256) FTC_AGR1(T, 256, false);     \
+        else FTC_AGR1(T, 128, false);          \
     } while (0)
         if (dt == FTC_F32) FTC_AGR(F32);
         else if (dt == FTC_F16) FTC_AGR(F16);
         else FTC_AGR(BF16);
 #undef FTC_AGR
+#undef FTC_AGR1
         const int32_t st = launch_status("agnn_fused");
         if (st != FTC_OK) return st;
     }

@@ -36,15 +36,15 @@ inline int ceil_div(int a, int b) { return static_cast<int>((static_cast<int64_t
 // Edges per wave for a graph of nnz entries.  A wave's groups of lanes walk their runs one batch of four gathers after the
 // other, so a range of R edges is a chain of R / 64 (rows of four lanes) to R / 8 batches, and with too few ranges the
 // chip waits for it; with many ranges what counts is the work per cut row, which long ranges have less of.  The two lines
-// are where the measured times cross (us at R = 512 / 256 / 128, fp16, 32 columns):
-//   entries               9 thousand       0.6 M            1.5 M            3.8 M            8 M
-//   SpMM                  29 / 20 / 16     33 / 24 / 21     41 / 33 / 38     76 / 68 / 71     100 / 98 / 119
-//   AGNN layer            30 / 20 / 16     33 / 26 / 24     41 / 41 / 45     70 / 70 / 85     102 / 114 / 150
+// are where the measured times cross (us at R = 512 / 256 / 128, fp16, 32 columns, power law):
+//   entries               9 thousand       0.6 M            1.5 M            3.8 M            8 M               16 M
+//   SpMM                  17 / 11 / 11     18 / 15 / 14     25 / 23 / 26     52 / 50 / 51     106 / 106 / 108   201 / 201 / 206
+//   AGNN layer with P     23 / 16 / 15     28 / 24 / 24     38 / 39 / 42     72 / 72 / 83     136 / 135 / 150   253 / 248 / 265
 //   its backward pass     41 / 32 / 29     58 / 47 / 49     73 / 77 / 80     138 / 141 / 160  208 / 217 / 256
 struct SegLines {
     int below_128, below_256;  // entry counts up to which ranges of 128, of 256 edges are taken
 };
-constexpr SegLines SEG_SPMM = {1 << 20, 1 << 23}, SEG_AGNN = {1 << 20, 1 << 21}, SEG_AGNN_BACKWARD = {1 << 19, 1 << 20};
+constexpr SegLines SEG_SPMM = {1 << 20, 1 << 23}, SEG_AGNN = {1 << 20, 1 << 24}, SEG_AGNN_BACKWARD = {1 << 19, 1 << 20};
 inline int seg_range(int nnz, const SegLines &l) { return nnz < l.below_128 ? 128 : nnz < l.below_256 ? 256 : SEG_R; }
 inline int64_t seg_count(int nnz, int r) { return (static_cast<int64_t>(nnz) + r - 1) / r; }
 
@@ -322,6 +322,19 @@ __device__ __forceinline__ void load_n(const void *base, int64_t idx, float (&f)
     unpack<T, NV>(r, f);
 }
 
+// NV floats (2, 4 or 8) as packed fp16 or bf16: the run-time type is looked at once, not per element.
+template <int NV>
+__device__ __forceinline__ void pack_16bit(int dtype, const float (&f)[NV], uint32_t (&w)[NV / 2])
+{
+    if (dtype == FTC_F16) {
+#pragma unroll
+        for (int k = 0; k < NV / 2; ++k) w[k] = f32_to_f16_bits(f[2 * k]) | (f32_to_f16_bits(f[2 * k + 1]) << 16);
+    } else {
+#pragma unroll
+        for (int k = 0; k < NV / 2; ++k) w[k] = f32_to_bf16_bits(f[2 * k]) | (f32_to_bf16_bits(f[2 * k + 1]) << 16);
+    }
+}
+
 // Store NV consecutive floats (NV = 1, 2, 4 or 8) at element index idx (multiple of NV; rows are
 // 16-byte aligned by the caller's checks) in the run-time output dtype.
 template <int NV>
@@ -344,12 +357,7 @@ __device__ __forceinline__ void store_vec(void *base, int64_t idx, int dtype, co
             *q = static_cast<uint16_t>(dtype == FTC_F16 ? f32_to_f16_bits(f[0]) : f32_to_bf16_bits(f[0]));
         } else {
             uint32_t w[NV / 2];
-#pragma unroll
-            for (int k = 0; k < NV / 2; ++k) {
-                const uint32_t lo = dtype == FTC_F16 ? f32_to_f16_bits(f[2 * k]) : f32_to_bf16_bits(f[2 * k]);
-                const uint32_t hi = dtype == FTC_F16 ? f32_to_f16_bits(f[2 * k + 1]) : f32_to_bf16_bits(f[2 * k + 1]);
-                w[k] = lo | (hi << 16);
-            }
+            pack_16bit<NV>(dtype, f, w);
             if constexpr (NV == 8) *reinterpret_cast<uint4 *>(q) = make_uint4(w[0], w[1], w[2], w[3]);
             else if constexpr (NV == 4) *reinterpret_cast<uint2 *>(q) = make_uint2(w[0], w[1]);
             else *reinterpret_cast<uint32_t *>(q) = w[0];
@@ -415,12 +423,7 @@ __device__ __forceinline__ void store_vec_nt(void *base, int64_t idx, int dtype,
         uint16_t *q = static_cast<uint16_t *>(base) + idx;
         if constexpr (NV == 8 || NV == 4) {
             uint32_t w[NV / 2];
-#pragma unroll
-            for (int k = 0; k < NV / 2; ++k) {
-                const uint32_t lo = dtype == FTC_F16 ? f32_to_f16_bits(f[2 * k]) : f32_to_bf16_bits(f[2 * k]);
-                const uint32_t hi = dtype == FTC_F16 ? f32_to_f16_bits(f[2 * k + 1]) : f32_to_bf16_bits(f[2 * k + 1]);
-                w[k] = lo | (hi << 16);
-            }
+            pack_16bit<NV>(dtype, f, w);
             if constexpr (NV == 8) {
                 ftc_u32x4 v = {w[0], w[1], w[2], w[3]};
                 __builtin_nontemporal_store(v, reinterpret_cast<ftc_u32x4 *>(q));

@@ -11,11 +11,16 @@
 //     edges, SEG_B at a time (SEG_B independent 16-byte gathers of X rows in flight per lane),
 //     and accumulates in registers while the row stays the same.
 //   - A row that lies completely inside one run is stored straight from registers.  A row cut by
-//     a run boundary leaves a partial sum: the pieces inside one wave are added in LDS in edge
-//     order; the pieces that cross a wave boundary go to a small carry buffer and are added, again
+//     a run boundary leaves partial sums: those inside one wave are added in edge order by the group that
+//     closes the row (all groups at once; one lane per feature walking over the groups took as long as two batches of
+//     gathers on short ranges); the pieces that cross a wave boundary go to a small carry buffer and are added, again
 //     in edge order, by a second tiny kernel.  No floating-point atomics: results are
 //     reproducible bit for bit.
-#include "ftc_common.hpp"
+//
+// What bounds it: gathers that miss L2 on large graphs (block model, 10^6 nodes, bf16, 64 columns: 0.67 ms, a kernel that only
+// gathers these rows 0.58), else the instructions around the gather (edge_ranges.hpp) and, on small graphs, the chain
+// index, gather, sum of a wave (GCN layer with 100 000 nodes, fp16 128 -> 32: 44 -> 33 us with the update before it).
+#include "edge_ranges.hpp"
 
 namespace ftc {
 
@@ -111,199 +116,167 @@ size_t spmm_seg_ws(int n, int nnz, int D, bool least)
 }
 
 // VALS = false: all edge values are one (vals == NULL): nothing is staged or multiplied for them, which
-// also cuts the LDS footprint by a third (more workgroups per CU).  RAGGED: any width from one piece on, any alignment.
-template <class T, int VEC, int LPR, bool VALS, int R, bool RAGGED>
+// also cuts the LDS footprint (more workgroups per CU).  RAGGED: any width from one piece on, any alignment.
+template <class T, int VEC, int LPR, bool VALS, int R, bool RAGGED, bool BIG>
 __global__ __launch_bounds__(256) void spmm_seg_kernel(int nnz, int n_ranges, const int *__restrict__ row_ptr,
                                                        const int *__restrict__ col_idx,
                                                        const int *__restrict__ edge_to_row,
                                                        const float *__restrict__ vals,
-                                                       const void *__restrict__ X, int ldx, int D,
+                                                       const void *__restrict__ X, uint64_t ldb, int D,
                                                        void *__restrict__ out, int ldo, int odt, Epi epi,
                                                        float *__restrict__ carry, int *__restrict__ carry_tail_row,
                                                        const uint8_t *__restrict__ dense)
 {
-    constexpr int NG = 64 / LPR;      // groups per wave
-    constexpr int RUN = R / NG;       // edges per group
-    constexpr int RP = R + NG;        // one pad word per run keeps the groups on different LDS banks
+    using E = EdgeRange<LPR, R>;
+    constexpr int NG = E::NG, RUN = E::RUN;
     constexpr int DP = LPR * VEC;     // padded feature width
-    static_assert(RUN % SEG_B == 0, "runs are whole batches");
-    constexpr int IDX_WORDS = 4 * (VALS ? 3 : 2) * RP;
-    constexpr int PART_WORDS = 4 * 2 * NG * DP;
-    __shared__ int smem[IDX_WORDS > PART_WORDS ? IDX_WORDS : PART_WORDS];
-    __shared__ int s_meta[4][3][NG];
+    constexpr int IDX_WORDS = (VALS ? 3 : 2) * E::WORDS;
+    constexpr int PART_WORDS = NG * DP;
+    __shared__ __align__(16) int smem[4][IDX_WORDS > PART_WORDS ? IDX_WORDS : PART_WORDS];
 
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int g = lane / LPR, sub = lane % LPR;
-    int *s_col = smem + wave * (VALS ? 3 : 2) * RP;
-    int *s_row = s_col + RP;
-    float *s_val = reinterpret_cast<float *>(s_row + RP);  // only with VALS
+    uint32_t *s_off = reinterpret_cast<uint32_t *>(smem[wave]);
+    int *s_row = smem[wave] + E::WORDS;
+    float *s_val = reinterpret_cast<float *>(smem[wave] + 2 * E::WORDS);  // only with VALS
 
     const int v = xcd_chunked_block(blockIdx.x, gridDim.x) * 4 + wave;
-    const bool active = v < n_ranges;
-    const int base = active ? v * R : 0;
-    const int n_valid = active ? min(R, nnz - base) : 0;
-    int rows[R / 64];
-    const bool from_starts = n_valid == R && rows_from_starts<R>(row_ptr, edge_to_row, base, lane, rows);
-#pragma unroll
-    for (int j = 0; j < R / 64; ++j) {
-        const int i = j * 64 + lane;
-        if (i < n_valid) {
-            const int p = i + i / RUN;
-            const int er = from_starts ? rows[j] : edge_to_row[base + i];
-            // edges of windows that go to the matrix cores are skipped here (column -1)
-            s_col[p] = (dense && dense[er >> 4]) ? -1 : __builtin_nontemporal_load(col_idx + base + i);  // streamed once
-            s_row[p] = er;
-            if constexpr (VALS) s_val[p] = __builtin_nontemporal_load(vals + base + i);
-        }
-    }
-    const int prev_row = (active && base > 0) ? edge_to_row[base - 1] : -1;
-    const int next_row = (active && n_valid == R && base + R < nnz) ? edge_to_row[base + R] : -1;
+    if (v >= n_ranges) return;  // (no wave waits for another)
+    const int base = v * R;
+    const int n_valid = min(R, nnz - base);
+    const int prev_row = base > 0 ? edge_to_row[base - 1] : -1;
+    const int next_row = nnz - base > R ? edge_to_row[base + R] : -1;
     // row of the first edge after the NEXT range: tells whether a row left open here ends there
-    const int far_row = (active && static_cast<int64_t>(base) + 2 * R < nnz) ? edge_to_row[base + 2 * R] : -1;
-    __syncthreads();
+    const int far_row = static_cast<int64_t>(base) + 2 * R < nnz ? edge_to_row[base + 2 * R] : -1;
+    stage_range<LPR, R, VALS, BIG>(row_ptr, col_idx, edge_to_row, vals, base, n_valid, ldb, dense, lane, s_off, s_row, s_val);
 
-    const int rs = g * RUN;
-    const int re = min(rs + RUN, n_valid);
-    const bool has = rs < n_valid;
+    const int at = g * E::RUNP;  // the group's run
     const bool live = sub * VEC < D;
-    const int col0 = RAGGED ? min(sub * VEC, D - VEC) : sub * VEC;  // first column of this lane's piece
+    // first column of this lane's piece; lanes beyond the row gather its first piece and store nothing
+    const int col0 = RAGGED ? min(sub * VEC, D - VEC) : live ? sub * VEC : 0;
+    const uint32_t lane_bytes = static_cast<uint32_t>(col0) * T::BYTES;
     float acc[VEC], hacc[VEC];
 #pragma unroll
     for (int j = 0; j < VEC; ++j) { acc[j] = 0.f; hacc[j] = 0.f; }
-    bool have_head = false, head_closed = false, have_tail = false;
-    int head_row = -1, cur = -1;
+    bool head_closed = false;
+    int head_row = -1;
+    // an fp16 element is widened by the multiply-add that also takes the value, so without values a one that the compiler
+    // does not know takes their place (one instruction per element instead of two)
+    float one = 1.f;
+    if constexpr (!VALS && std::is_same<T, F16>::value) asm("" : "+v"(one));
 
-    auto direct_store = [&](int row) {
+    auto store_row = [&](int row, float f, const float (&a)[VEC]) {
         if (live && !(dense && dense[row >> 4])) {
             float o[VEC];
-            const float f = epi.factor(row);
 #pragma unroll
-            for (int j = 0; j < VEC; ++j) o[j] = epi.apply(f, acc[j]);
+            for (int j = 0; j < VEC; ++j) o[j] = epi.apply(f, a[j]);
             if constexpr (RAGGED) store_vec_any<VEC>(out, static_cast<int64_t>(row) * ldo + col0, odt, o);
             else store_vec_nt<VEC>(out, static_cast<int64_t>(row) * ldo + col0, odt, o);
         }
     };
 
-    if (has) {
-        cur = s_row[rs + g];
-        const int left_row = rs == 0 ? prev_row : s_row[rs - 1 + g - 1];
-        const bool left_open = left_row == cur;
-        bool first = true;
-        for (int b = rs; b < re; b += SEG_B) {
-            int c[SEG_B], r[SEG_B];
-            float a[SEG_B];
-            RawVec<T, VEC> x[SEG_B];
+    int cur = s_row[at];
+    const bool left_open = cur >= 0 && cur == (g == 0 ? prev_row : s_row[max(at - 5, 0)]);  // the last entry of the run before
+    bool first = true;
+    float factor = epi.factor(max(cur, 0));  // loaded where the row begins: where it ends nothing has to be waited for
+#pragma unroll 1
+    for (int b = 0; b < RUN; b += SEG_B) {
+        const uint4 o4 = *reinterpret_cast<const uint4 *>(s_off + at + b);
+        const int4 r4 = *reinterpret_cast<const int4 *>(s_row + at + b);
+        const uint32_t o[SEG_B] = {o4.x, o4.y, o4.z, o4.w};
+        const int r[SEG_B] = {r4.x, r4.y, r4.z, r4.w};
+        float a[SEG_B];
+        if constexpr (VALS) {
+            const float4 a4 = *reinterpret_cast<const float4 *>(s_val + at + b);
+            a[0] = a4.x; a[1] = a4.y; a[2] = a4.z; a[3] = a4.w;
+        } else {
 #pragma unroll
-            for (int k = 0; k < SEG_B; ++k) {
-                const bool ok = b + k < re;
-                const int p = (ok ? b + k : rs) + g;
-                c[k] = s_col[p];
-                r[k] = ok ? s_row[p] : -1;
-                a[k] = VALS ? s_val[p] : 1.f;
-            }
-#pragma unroll
-            for (int k = 0; k < SEG_B; ++k) {
-                if (r[k] >= 0 && c[k] >= 0 && live) {
-                    if constexpr (RAGGED) load_raw_any<T>(X, static_cast<int64_t>(c[k]) * ldx + col0, x[k]);
-                    else load_raw<T, VEC>(X, static_cast<int64_t>(c[k]) * ldx + col0, x[k]);
-                } else {
-                    zero_raw(x[k]);
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < SEG_B; ++k) {
-                if (r[k] >= 0) {
-                    if (r[k] != cur) {  // the segment of row `cur` ends here
-                        if (first && left_open) {
-#pragma unroll
-                            for (int j = 0; j < VEC; ++j) hacc[j] = acc[j];
-                            have_head = true; head_closed = true; head_row = cur;
-                        } else {
-                            direct_store(cur);
-                        }
-                        first = false;
-                        cur = r[k];
-#pragma unroll
-                        for (int j = 0; j < VEC; ++j) acc[j] = 0.f;
-                    }
-                    float xf[VEC];
-                    unpack<T, VEC>(x[k], xf);
-#pragma unroll
-                    for (int j = 0; j < VEC; ++j) acc[j] = VALS ? fmaf(a[k], xf[j], acc[j]) : acc[j] + xf[j];
-                }
-            }
+            for (int k = 0; k < SEG_B; ++k) a[k] = one;
         }
-        // the run's last segment
-        int right_row;
-        if (re < n_valid) right_row = s_row[re + g + 1];
-        else right_row = next_row;  // -1 when the edge list ends here
-        const bool right_open = right_row == cur;
-        if (first && left_open) {
+        RawVec<T, VEC> x[SEG_B];
+#pragma unroll
+        for (int k = 0; k < SEG_B; ++k) {
+            const char *p = row_addr<BIG>(X, o[k], ldb, lane_bytes);
+            if constexpr (RAGGED) load_raw_any<T>(p, 0, x[k]);
+            else load_raw<T, VEC>(p, 0, x[k]);
+        }
+#pragma unroll
+        for (int k = 0; k < SEG_B; ++k) {
+            if (r[k] != cur) {  // the segment of row `cur` ends here
+                if (cur >= 0) {
+                    if (first && left_open) {
+#pragma unroll
+                        for (int j = 0; j < VEC; ++j) hacc[j] = acc[j];
+                        head_closed = true; head_row = cur;
+                    } else {
+                        store_row(cur, factor, acc);
+                    }
+                }
+                first = false;
+                cur = r[k];
+                factor = epi.factor(max(cur, 0));
+#pragma unroll
+                for (int j = 0; j < VEC; ++j) acc[j] = 0.f;
+            }
+            float xf[VEC];
+            unpack<T, VEC>(x[k], xf);
+#pragma unroll
+            for (int j = 0; j < VEC; ++j)
+                acc[j] = VALS || std::is_same<T, F16>::value ? fmaf(a[k], xf[j], acc[j]) : acc[j] + xf[j];
+        }
+    }
+    // the run's last segment
+    int open = OPEN_NONE;
+    if (cur >= 0) {
+        const int right_row = g == NG - 1 ? next_row : s_row[at + E::RUNP];
+        if (right_row == cur) {
+            open = first && left_open ? OPEN_THROUGH : OPEN_TAIL;
+        } else if (first && left_open) {
 #pragma unroll
             for (int j = 0; j < VEC; ++j) hacc[j] = acc[j];
-            have_head = true; head_closed = !right_open; head_row = cur;
-        } else if (!right_open) {
-            direct_store(cur);
+            head_closed = true; head_row = cur;
         } else {
-            have_tail = true;
+            store_row(cur, factor, acc);
         }
     }
-    __syncthreads();  // every wave is done with the staged indices: the LDS is reused for partials
-
-    float *part = reinterpret_cast<float *>(smem) + wave * 2 * NG * DP;
-    if (have_head && (!RAGGED || live)) {
+    // Rows cut inside this wave: the group that closes a row adds its pieces, in edge order.
+    const int from = first_group<LPR>(open, g);
+    const bool last_open = g == NG - 1 && open != OPEN_NONE;  // a row that goes on in the next range
+    wave_lds_sync();  // the staged entries are dead: their place is taken by the open pieces
+    float *part = reinterpret_cast<float *>(smem[wave]);
+    if (open != OPEN_NONE && live) {
 #pragma unroll
-        for (int j = 0; j < VEC; ++j) part[(2 * g) * DP + col0 + j] = hacc[j];
+        for (int j = 0; j < VEC; ++j) part[g * DP + col0 + j] = acc[j];
     }
-    if (have_tail && (!RAGGED || live)) {
+    wave_lds_sync();
+    // carried piece: [2 v] of the row that came in from the left, [2 v + 1] of the one left open
+    auto store_carry = [&](int slot, const float (&a)[VEC]) {
+        const int64_t to = (static_cast<int64_t>(v) * 2 + slot) * DP + col0;
+        if constexpr (RAGGED) {
+            if (live) store_vec_any<VEC>(carry, to, FTC_F32, a);
+        } else {
+            if (live) store_vec<VEC>(carry, to, FTC_F32, a);
+        }
+    };
+    if (head_closed || (last_open && open == OPEN_THROUGH)) {
+        float run[VEC];
 #pragma unroll
-        for (int j = 0; j < VEC; ++j) part[(2 * g + 1) * DP + col0 + j] = acc[j];
-    }
-    if (sub == 0) {
-        s_meta[wave][0][g] = have_head ? head_row : -1;
-        s_meta[wave][1][g] = head_closed ? 1 : 0;
-        s_meta[wave][2][g] = have_tail ? cur : -1;
-    }
-    __syncthreads();
-
-    // Add the pieces of rows cut inside this wave, in edge order; one lane per feature.
-    if (active) {
-        int tail_out = -1;
-        for (int d = lane; d < DP; d += 64) {
-            float run = 0.f;
-            int run_row = -1;
-            bool from_outside = false;
-            tail_out = -1;
-            for (int q = 0; q < NG; ++q) {
-                const int hr = s_meta[wave][0][q];
-                if (hr >= 0) {
-                    if (run_row < 0) { run_row = hr; run = 0.f; from_outside = true; }
-                    run += part[(2 * q) * DP + d];
-                    if (s_meta[wave][1][q]) {
-                        if (from_outside) carry[(static_cast<size_t>(v) * 2) * DP + d] = run;
-                        else if (d < D && !(dense && dense[run_row >> 4]))
-                            store_elem(out, static_cast<int64_t>(run_row) * ldo + d, odt,
-                                       epi.apply(epi.factor(run_row), run));
-                        run_row = -1;
-                        from_outside = false;
-                    }
-                }
-                const int tr = s_meta[wave][2][q];
-                if (tr >= 0) { run_row = tr; run = part[(2 * q + 1) * DP + d]; from_outside = false; }
-            }
-            if (run_row >= 0) {
-                if (from_outside) {
-                    carry[(static_cast<size_t>(v) * 2) * DP + d] = run;  // the row covers the whole wave
-                } else {
-                    carry[(static_cast<size_t>(v) * 2 + 1) * DP + d] = run;
-                    tail_out = run_row;
-                }
-            }
+        for (int j = 0; j < VEC; ++j) run[j] = 0.f;
+        for (int q = max(from, 0); q < g; ++q) {
+#pragma unroll
+            for (int j = 0; j < VEC; ++j) run[j] += part[q * DP + col0 + j];
         }
-        if (lane == 0) {
-            carry_tail_row[2 * v] = tail_out;
-            carry_tail_row[2 * v + 1] = (tail_out >= 0 && far_row != tail_out) ? 1 : 0;  // ends in range v + 1
-        }
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) run[j] += head_closed ? hacc[j] : acc[j];
+        if (from < 0) store_carry(0, run);
+        else if (head_closed) store_row(head_row, epi.factor(head_row), run);
+        else store_carry(1, run);
+    }
+    if (last_open && open == OPEN_TAIL) store_carry(1, acc);
+    if (lane == 63) {
+        const int tail = last_open && !(open == OPEN_THROUGH && from < 0) ? cur : -1;
+        carry_tail_row[2 * v] = tail;
+        carry_tail_row[2 * v + 1] = (tail >= 0 && far_row != tail) ? 1 : 0;  // ends in range v + 1
     }
 }
 
@@ -410,16 +383,16 @@ int32_t launch_seg_fixup(int n, int n_ranges, const int *row_ptr, const float *c
     return launch_status(what);
 }
 
-template <class T, int R>
+template <class T, int R, bool BIG>
 static void launch_seg_t(int vec, int lpr, bool ragged, hipStream_t s, int n_ranges, const ftc_csr &g, const int *e2r,
-                         const float *vals, const void *X, int ldx, int D, void *out, int ldo, int odt, Epi epi,
+                         const float *vals, const void *X, uint64_t ldb, int D, void *out, int ldo, int odt, Epi epi,
                          float *carry, int *tail_row, const uint8_t *dense)
 {
     constexpr int VM = T::VEC;
     const dim3 grid(static_cast<unsigned>((n_ranges + 3) / 4));
 #define FTC_SEG1(V, L, W, RG)                                                                                          \
-    hipLaunchKernelGGL((spmm_seg_kernel<T, V, L, W, R, RG>), grid, dim3(256), 0, s, g.nnz, n_ranges, g.row_ptr,        \
-                       g.col_idx, e2r, vals, X, ldx, D, out, ldo, odt, epi, carry, tail_row, dense)
+    hipLaunchKernelGGL((spmm_seg_kernel<T, V, L, W, R, RG, BIG>), grid, dim3(256), 0, s, g.nnz, n_ranges, g.row_ptr,   \
+                       g.col_idx, e2r, vals, X, ldb, D, out, ldo, odt, epi, carry, tail_row, dense)
 #define FTC_SEG(V, L, RG)                      \
     do {                                       \
         if (vals) FTC_SEG1(V, L, true, RG);    \
@@ -445,13 +418,17 @@ static void launch_seg_t(int vec, int lpr, bool ragged, hipStream_t s, int n_ran
 }
 
 template <class T>
-static void launch_seg_r(int r, int vec, int lpr, bool ragged, hipStream_t s, int n_ranges, const ftc_csr &g,
-                         const int *e2r, const float *vals, const void *X, int ldx, int D, void *out, int ldo, int odt,
+static void launch_seg_r(int r, bool big, int vec, int lpr, bool ragged, hipStream_t s, int n_ranges, const ftc_csr &g,
+                         const int *e2r, const float *vals, const void *X, uint64_t ldb, int D, void *out, int ldo, int odt,
                          Epi epi, float *carry, int *tail_row, const uint8_t *dense)
 {
-    if (r == SEG_R) launch_seg_t<T, SEG_R>(vec, lpr, ragged, s, n_ranges, g, e2r, vals, X, ldx, D, out, ldo, odt, epi, carry, tail_row, dense);
-    else if (r == 256) launch_seg_t<T, 256>(vec, lpr, ragged, s, n_ranges, g, e2r, vals, X, ldx, D, out, ldo, odt, epi, carry, tail_row, dense);
-    else launch_seg_t<T, 128>(vec, lpr, ragged, s, n_ranges, g, e2r, vals, X, ldx, D, out, ldo, odt, epi, carry, tail_row, dense);
+#define FTC_SEGR(R, BIG) \
+    launch_seg_t<T, R, BIG>(vec, lpr, ragged, s, n_ranges, g, e2r, vals, X, ldb, D, out, ldo, odt, epi, carry, tail_row, dense)
+    if (big) FTC_SEGR(SEG_R, true);
+    else if (r == SEG_R) FTC_SEGR(SEG_R, false);
+    else if (r == 256) FTC_SEGR(256, false);
+    else FTC_SEGR(128, false);
+#undef FTC_SEGR
 }
 
 // Caller has checked: window index present; seg_shape() accepts (xdt, D), rows of X and out 16-byte aligned and a workspace of
@@ -469,7 +446,9 @@ int32_t launch_spmm_seg(const ftc_csr &g, const ftc_windows &w, const float *val
     const bool ragged = !(x16 && o16 && seg_shape(xdt, D, &vec, &lpr));
     if (ragged) seg_shape_ragged(xdt, D, &vec, &lpr);
     const int dp = vec * lpr;
-    const int short_r = spmm_range(g.n, g.nnz, dp);
+    const int64_t row_bytes = static_cast<int64_t>(ldx) * elem_size(xdt);
+    const bool big = rows_need_64_bits(g.n, row_bytes);  // ranges of SEG_R only: such a matrix has many rows
+    const int short_r = big ? SEG_R : spmm_range(g.n, g.nnz, dp);
     const int r = ws_bytes >= seg_carry_ws(g.nnz, short_r, dp) ? short_r : SEG_R;
     const int n_ranges = static_cast<int>(seg_count(g.nnz, r));
     float *carry = static_cast<float *>(ws);
@@ -477,11 +456,11 @@ int32_t launch_spmm_seg(const ftc_csr &g, const ftc_windows &w, const float *val
                                             align_up(static_cast<size_t>(n_ranges) * 2 * dp * sizeof(float), 256));
     if (n_ranges > 0) {
         if (xdt == FTC_F32)
-            launch_seg_r<F32>(r, vec, lpr, ragged, s, n_ranges, g, w.edge_to_row, vals, X, ldx, D, out, ldo, odt, epi, carry, tail_row, dense);
+            launch_seg_r<F32>(r, big, vec, lpr, ragged, s, n_ranges, g, w.edge_to_row, vals, X, static_cast<uint64_t>(row_bytes), D, out, ldo, odt, epi, carry, tail_row, dense);
         else if (xdt == FTC_F16)
-            launch_seg_r<F16>(r, vec, lpr, ragged, s, n_ranges, g, w.edge_to_row, vals, X, ldx, D, out, ldo, odt, epi, carry, tail_row, dense);
+            launch_seg_r<F16>(r, big, vec, lpr, ragged, s, n_ranges, g, w.edge_to_row, vals, X, static_cast<uint64_t>(row_bytes), D, out, ldo, odt, epi, carry, tail_row, dense);
         else
-            launch_seg_r<BF16>(r, vec, lpr, ragged, s, n_ranges, g, w.edge_to_row, vals, X, ldx, D, out, ldo, odt, epi, carry, tail_row, dense);
+            launch_seg_r<BF16>(r, big, vec, lpr, ragged, s, n_ranges, g, w.edge_to_row, vals, X, static_cast<uint64_t>(row_bytes), D, out, ldo, odt, epi, carry, tail_row, dense);
         const int32_t st = launch_status("spmm_seg");
         if (st != FTC_OK) return st;
     }

@@ -1,0 +1,120 @@
+"""The edge-balanced kernels where a range of entries can go wrong: rows that end at, before and behind the ends of runs and
+ranges, rows without entries among them, more rows than a range has marks for, a last range of one entry, long and short ranges,
+lanes beyond the row, and feature matrices of more than 4 GiB.  Compared with plain fp64 torch, element by element,
+relative to the sum of the absolute terms; 1e-5, the bar of fp32 sums, also for 16-bit inputs (they are taken as they are)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2412_12218_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+F32, F16, BF16 = torch.float32, torch.float16, torch.bfloat16
+
+
+def row_lengths(which):
+    if which == "edges":  # around the lengths of runs (8 to 128) and ranges (128, 512)
+        return [0, 0, 1, 7, 8, 9, 0, 31, 32, 33, 1, 127, 128, 129, 0, 0, 3, 511, 512, 513, 1, 1, 255, 256, 257, 64, 0, 1025, 2, 1, 5000, 6]
+    if which == "ones":  # more row starts than half a range
+        return [1] * 700 + [0] * 50 + [1, 2] * 300 + [1]
+    if which == "aligned":  # every row ends with a range
+        return [128] * 8 + [512] * 4 + [64, 64] * 4
+    return [3000] + [0] * 600 + [1] * 3  # one row over many ranges, then a gap of rows without entries
+
+
+def graph(lengths, seed=0):
+    rng = np.random.default_rng(seed)
+    n = len(lengths)
+    ptr = np.zeros(n + 1, dtype=np.int32)
+    ptr[1:] = np.cumsum(lengths)
+    return B.Graph.from_numpy(ptr, rng.integers(0, n, size=int(ptr[-1])).astype(np.int32))
+
+
+def rows_of(g):
+    rp = g.row_ptr.long()
+    return torch.repeat_interleave(torch.arange(g.n, device="cuda"), rp[1:] - rp[:-1])
+
+
+def close(got, ref, terms, tol=1e-5):
+    err = (got.double() - ref).abs() / terms.clamp(min=1e-300)
+    assert torch.all(got[terms == 0] == 0)
+    assert float(torch.where(terms > 0, err, torch.zeros_like(err)).max()) <= tol
+
+
+def check_spmm(g, win, vals, X, out):
+    rows, cols = rows_of(g), g.col_idx.long()
+    t = X.double()[cols] * (1.0 if vals is None else vals.double()[:, None])
+    ref = torch.zeros(out.shape, dtype=torch.float64, device="cuda")
+    close(out, ref.clone().index_add_(0, rows, t), ref.clone().index_add_(0, rows, t.abs()))
+
+
+def attention(g, X, beta):
+    rows, cols = rows_of(g), g.col_idx.long()
+    H = X.double()
+    Hn = H / H.norm(dim=1).clamp(min=1e-12)[:, None]
+    w = torch.exp(beta * (Hn[rows] * Hn[cols]).sum(1) - abs(beta))
+    z = torch.zeros(g.n, dtype=torch.float64, device="cuda").index_add_(0, rows, w)
+    p = w / z[rows]
+    t = H[cols] * p[:, None]
+    ref = torch.zeros(X.shape, dtype=torch.float64, device="cuda")
+    return p, z, ref.clone().index_add_(0, rows, t), ref.clone().index_add_(0, rows, t.abs())
+
+
+def smallest_workspace(call, nbytes):
+    """The smallest workspace (a multiple of 256 bytes) that a call accepts: with it the kernels use their longest ranges."""
+    lo, hi = 0, nbytes // 256 + 1
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        try:
+            call(torch.empty(mid * 256, dtype=torch.uint8, device="cuda"))
+            hi = mid
+        except B.FtcError:
+            lo = mid
+    return torch.full((hi * 256,), 0xff, dtype=torch.uint8, device="cuda")
+
+
+SHAPES = [(F16, 32), (F16, 64), (BF16, 128), (F16, 40), (BF16, 24), (F32, 128), (F32, 32), (F32, 12), (F16, 16), (F16, 8), (F16, 256)]
+
+
+@pytest.mark.parametrize("which", ["edges", "ones", "aligned", "gap"])
+@pytest.mark.parametrize("dtype,D", SHAPES)
+def test_rows_at_the_ends_of_runs_and_ranges(which, dtype, D):
+    g = graph(row_lengths(which))
+    win = B.ftc_build_windows(g)
+    gen = torch.Generator(device="cuda").manual_seed(D)
+    X = torch.randn((g.n, D), generator=gen, device="cuda").to(dtype)
+    vals = torch.rand(g.nnz, generator=gen, device="cuda") + 0.5
+    L = B.lib()
+    long_ws = smallest_workspace(lambda ws: B.ftc_spmm(g, win, vals, X, ws=ws), L.ftc_spmm_workspace_bytes(g.n, g.nnz, D))
+    for ws in (None, long_ws):
+        for v in (vals, None):
+            check_spmm(g, win, v, X, B.ftc_spmm(g, win, v, X, ws=ws))
+    p, z, ref, terms = attention(g, X, 1.5)
+    nbytes = L.ftc_agnn_layer_workspace_bytes(g.n, g.nnz, D)
+    long_ws = smallest_workspace(lambda ws: B.ftc_agnn_layer(g, win, X, beta=1.5, ws=ws), nbytes)
+    for ws in (None, long_ws):
+        close(B.ftc_agnn_layer(g, win, X, beta=1.5, ws=ws), ref, terms)
+        row_z = torch.empty(g.n, device="cuda")
+        out32 = torch.empty((g.n, (D + 3) // 4 * 4), device="cuda")
+        close(B.ftc_agnn_layer(g, win, X, beta=1.5, row_z=row_z, out_f32=out32, ws=ws), ref, terms)
+        close(out32[:, :D], ref, terms)
+        close(row_z, z, z)
+        edge_p = torch.empty(g.nnz, device="cuda")
+        close(B.ftc_agnn_layer(g, win, X, beta=1.5, edge_p=edge_p, ws=ws), ref, terms)
+        close(edge_p, p, p)
+
+
+@pytest.mark.parametrize("dtype", [F16, F32])
+def test_feature_matrix_of_more_than_4_gib(dtype):
+    n, D, ld = 70_000, 32, 32_768 if dtype == F16 else 16_384  # 4.6 GB, most of it between the rows
+    rng = np.random.default_rng(1)
+    lengths = rng.integers(1, 8, size=n)
+    lengths[5] = 3000
+    g = graph(list(lengths))
+    win = B.ftc_build_windows(g)
+    X = torch.empty((n, ld), dtype=dtype, device="cuda")[:, :D]
+    X.copy_(torch.randn((n, D), device="cuda"))
+    vals = torch.rand(g.nnz, device="cuda") + 0.5
+    check_spmm(g, win, vals, X, B.ftc_spmm(g, win, vals, X))
+    _, _, ref, terms = attention(g, X, 1.5)
+    close(B.ftc_agnn_layer(g, win, X, beta=1.5), ref, terms)
