@@ -7,7 +7,7 @@
 // e = (i, j), c_T(e) = c_e and a_T(e) = a_e:
 //     dp_e = <dY_i, h_j>                 ds_e    = p_e (dp_e - t_i)
 //     p_T(e) = a_e / z_j                 ds_T(e) = p_T(e) (<h_i, dY_j> - t_j)
-//     dbeta = sum_e ds_e c_e
+//     dbeta = sum_e ds_e c_e = sum_e ds_e (c_e - 1/2)
 //     q_i   = beta sum_e (ds_e + ds_T(e)) hn_j        (gradient w.r.t. the normalised row hn_i)
 //     agg_i = sum_e p_T(e) dY_j                       (through the aggregated rows)
 //     dH_i  = agg_i + (q_i - hn_i <hn_i, q_i>) / |h_i|
@@ -19,16 +19,51 @@
 // line, so the two 64-byte rows an entry needs cost one line instead of two.
 //
 // Work partition, runs and the handling of rows cut by run / wave boundaries are those of the
-// edge-balanced SpMM (spmm_seg.hip): the pair (q_i, agg_i) is one output row of width 2 * DP, cut
-// rows go through the same carry buffer and are finished by the SpMM fix-up kernel; a row kernel
-// (backward.hip) then applies the derivative of the normalisation.
-#include "ftc_common.hpp"
+// edge-balanced SpMM (spmm_seg.hip); the partial of a cut row is the pair (q_i, agg_i), 2 * DP slots.  Whoever completes a row
+// -- the group that closes it, or the second kernel for rows cut by a range boundary -- applies the derivative of the
+// normalisation and writes dH_i: the pairs, 256 bytes a row at D = 32, do not travel through HBM (before: 268 MB written
+// and read again by a kernel of its own, next to one for the norms; R-MAT graph, 2^20 nodes, 32 M entries, fp16, D = 32).
+#include "edge_ranges.hpp"
 
 namespace ftc {
 
 constexpr int BW_B = 4;  // edges per batch
 
 bool seg_shape(int dtype, int D, int *vec, int *lpr);
+
+// Where dH goes.  `poison`, when not NULL and pointing at a non-zero value, turns every gradient into NaN (the pattern is not
+// symmetric).  vec: rows are 16-byte aligned.
+struct GradOut {
+    void *dH;
+    int ld, dt;
+    bool vec;
+    const int32_t *poison;
+    template <int NV>
+    __device__ __forceinline__ void store(int64_t row, int k, const float (&o)[NV]) const
+    {
+        if (vec) {
+            store_vec_nt<NV>(dH, row * ld + k, dt, o);
+        } else {
+#pragma unroll
+            for (int j = 0; j < NV; ++j) store_elem(dH, row * ld + k + j, dt, o[j]);
+        }
+    }
+};
+__device__ __forceinline__ bool poisoned(const int32_t *flag) { return flag && *flag != 0; }
+
+// 1 / max(|h|, 1e-12) from |h|^2: the hardware's reciprocal root and one Newton step
+__device__ __forceinline__ float inverse_norm(float hh)
+{
+    const float q = fmaxf(hh, 1e-24f);
+    const float r = __builtin_amdgcn_rsqf(q);
+    const float better = fmaf(0.5f * r, fmaf(-q * r, r, 1.f), r);
+    return q < 1e38f ? better : r;  // (an overflowed square keeps its 0)
+}
+
+// dH = agg + (q - hn <hn, q>) / |h| for one element; ri = 1 / |h|, t = <hn, q> / |h| (0 where the norm was clamped: the row is a
+// plain scaling there)
+__device__ __forceinline__ float through_norm(float agg, float q, float h, float ri, float t) { return fmaf(ri, fmaf(-h, t, q), agg); }
+__device__ __forceinline__ float projection(float hq, float ri) { return ri >= 0.999e12f ? 0.f : hq * ri * ri; }
 
 // stats[i] = (1 / z_i, <dY_i, Y_i>) and HD[i] = [h_i | dY_i] (element type of H, halves of DP
 // elements, zero padded).  Eight lanes per row, 16 bytes of H and dY per lane and step (the caller
@@ -95,262 +130,378 @@ __global__ __launch_bounds__(256) void agnn_row_stats_kernel(int n, const void *
     }
 }
 
-template <class T, int VEC, int LPR, int R>
-__global__ __launch_bounds__(256) void agnn_backward_fused_kernel(
-    int nnz, int n_ranges, const int *__restrict__ col_idx, const int *__restrict__ edge_to_row,
-    const void *__restrict__ HD, int D, float beta, const float2 *__restrict__ stats, float *__restrict__ QA,
+// Four entries of a group are taken together, as in the forward pass: four dot products per entry by all lanes, their
+// lane sums and the scalar work by one lane of the quad per entry (which also loads that entry's pair (1 / z_j, t_j)), the two
+// coefficients back to all lanes.  Three waves per SIMD: what four have room for spills inside the loop (R-MAT graph, 2^20 nodes,
+// 32 M entries, fp16, D = 32, forward and backward of four layers: 5.58 ms before, 5.06 with four waves, 4.87 with three).
+template <class T, int VEC, int LPR, int R, bool BIG>
+__global__ __launch_bounds__(256, 3) void agnn_backward_fused_kernel(
+    int nnz, int n_ranges, const int *__restrict__ row_ptr, const int *__restrict__ col_idx, const int *__restrict__ edge_to_row,
+    const void *__restrict__ HD, int D, float beta, const float2 *__restrict__ stats, GradOut grad,
     float *__restrict__ carry, int *__restrict__ carry_tail_row, float *__restrict__ dbeta_part)
 {
-    constexpr int NG = 64 / LPR;
-    constexpr int RUN = R / NG;
-    constexpr int RP = R + NG;
+    using E = EdgeRange<LPR, R>;
+    constexpr int NG = E::NG, RUN = E::RUN;
     constexpr int DP = LPR * VEC;
     constexpr int DP2 = 2 * DP;  // q slots, then agg slots
-    constexpr int IDX_WORDS = 4 * 2 * RP;
-    static_assert(RUN % BW_B == 0, "runs are whole batches");
-    constexpr int PART_WORDS = 4 * 2 * NG * DP2;
-    __shared__ int smem[IDX_WORDS > PART_WORDS ? IDX_WORDS : PART_WORDS];
-    __shared__ int s_meta[4][3][NG];
+    constexpr uint64_t ROW = DP2 * T::BYTES;  // bytes of a row of HD
+    constexpr int IDX_WORDS = 2 * E::WORDS;
+    constexpr int PART_WORDS = NG * DP2;
+    __shared__ __align__(16) int smem[4][(IDX_WORDS > PART_WORDS ? IDX_WORDS : PART_WORDS) + PART_WORDS];
 
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int g = lane / LPR, sub = lane % LPR;
-    int *s_col = smem + wave * 2 * RP;
-    int *s_row = s_col + RP;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int g = lane / LPR, sub = lane % LPR, quad = lane & 3;
+    const bool odd = lane & 1, upper = lane & 2;
+    uint32_t *s_off = reinterpret_cast<uint32_t *>(smem[wave]);
+    int *s_row = smem[wave] + E::WORDS;
+    // the sums of the row that a group closes first, if it came in from the left: parked here, they are needed at the end only
+    float *s_head = reinterpret_cast<float *>(smem[wave] + (IDX_WORDS > PART_WORDS ? IDX_WORDS : PART_WORDS)) + g * DP2 + sub * VEC;
 
     const int v = xcd_chunked_block(blockIdx.x, gridDim.x) * 4 + wave;
-    const bool active = v < n_ranges;
-    const int base = active ? v * R : 0;
-    const int n_valid = active ? min(R, nnz - base) : 0;
-    // (the rows could come from the row starts as in the forward kernels; measured 3 % slower here)
-#pragma unroll
-    for (int j = 0; j < R / 64; ++j) {
-        const int i = j * 64 + lane;
-        if (i < n_valid) {
-            const int p = i + i / RUN;
-            s_col[p] = __builtin_nontemporal_load(col_idx + base + i);  // streamed once: no need to keep them in L2
-            s_row[p] = __builtin_nontemporal_load(edge_to_row + base + i);
-        }
-    }
-    const int prev_row = (active && base > 0) ? edge_to_row[base - 1] : -1;
-    const int next_row = (active && n_valid == R && base + R < nnz) ? edge_to_row[base + R] : -1;
-    const int far_row = (active && static_cast<int64_t>(base) + 2 * R < nnz) ? edge_to_row[base + 2 * R] : -1;
-    __syncthreads();
+    if (v >= n_ranges) return;  // (no wave waits for another)
+    const int base = v * R;
+    const int n_valid = min(R, nnz - base);
+    const int prev_row = base > 0 ? edge_to_row[base - 1] : -1;
+    const int next_row = nnz - base > R ? edge_to_row[base + R] : -1;
+    const int far_row = static_cast<int64_t>(base) + 2 * R < nnz ? edge_to_row[base + 2 * R] : -1;
+    if (poisoned(grad.poison)) beta = __int_as_float(0x7fc00000);  // every weight is NaN then
+    stage_range<LPR, R, false, BIG>(row_ptr, col_idx, edge_to_row, nullptr, base, n_valid, ROW, nullptr, lane, s_off, s_row, nullptr);
 
-    const int rs = g * RUN;
-    const int re = min(rs + RUN, n_valid);
-    const bool has = rs < n_valid;
+    const int at = g * E::RUNP;  // the group's run
     const bool live = sub * VEC < D;
-    const float absb = fabsf(beta);
-    float acc[2 * VEC], hacc[2 * VEC];  // [0, VEC): q slice, [VEC, 2 VEC): agg slice
+    const uint32_t h_bytes = sub * VEC * T::BYTES, d_bytes = h_bytes + DP * T::BYTES;  // this lane's pieces of a row of HD
+    const float beta2 = beta * 1.44269504f;  // powers of two, as in the forward pass
+    const float beta2_rest = fmaf(beta, 1.92596299e-8f, fmaf(beta, 1.44269504f, -beta2));
+    float acc[2 * VEC];  // [0, VEC): q slice, [VEC, 2 VEC): agg slice
 #pragma unroll
-    for (int j = 0; j < 2 * VEC; ++j) { acc[j] = 0.f; hacc[j] = 0.f; }
-    RawVec<T, VEC> xi, dxi;  // slices of H[i,:] and dY[i,:] of the current row, as loaded
+    for (int j = 0; j < 2 * VEC; ++j) acc[j] = 0.f;
+    // slices of the current row: of H[i,:] and dY[i,:] (for the dot products, ahead of the sums by up to a batch) and of H[i,:]
+    // of the row whose sums are in acc
+    RawVec<T, VEC> xi, dxi, xc;
     zero_raw(xi);
     zero_raw(dxi);
-    float ri = 0.f, zi_inv = 0.f, ti = 0.f, dbeta_acc = 0.f;
-    bool have_head = false, head_closed = false, have_tail = false;
+    zero_raw(xc);
+    float ri = 0.f, dbeta_acc = 0.f;
+    float2 si = make_float2(0.f, 0.f);
+    bool head_closed = false, first = true;
     int head_row = -1, cur = -1;
-    bool first = true;
-    const int left_row = !has ? -2 : (rs == 0 ? prev_row : s_row[rs - 1 + g - 1]);
+    const int first_row = s_row[at];
+    const bool left_open = first_row >= 0 && first_row == (g == 0 ? prev_row : s_row[max(at - 5, 0)]);  // the last entry of the run before
 
-    auto direct_store = [&](int row) {
-        if (live) {
-            float q[VEC], a[VEC];
+    auto load_h = [&](int row, RawVec<T, VEC> &x) { load_raw<T, VEC>(row_addr<BIG>(HD, row_slot<BIG>(max(row, 0), ROW), ROW, h_bytes), 0, x); };
+    auto load_d = [&](int row, RawVec<T, VEC> &x) { load_raw<T, VEC>(row_addr<BIG>(HD, row_slot<BIG>(max(row, 0), ROW), ROW, d_bytes), 0, x); };
+    // the sums of a complete row become its gradient (all lanes of the group)
+    auto store_row = [&](int row, const RawVec<T, VEC> &x, const float (&a)[2 * VEC]) {
+        float h[VEC], hq = 0.f, o[VEC];
+        unpack<T, VEC>(x, h);
 #pragma unroll
-            for (int j = 0; j < VEC; ++j) { q[j] = acc[j]; a[j] = acc[VEC + j]; }
-            store_vec<VEC>(QA, static_cast<int64_t>(row) * DP2 + sub * VEC, FTC_F32, q);
-            store_vec<VEC>(QA, static_cast<int64_t>(row) * DP2 + DP + sub * VEC, FTC_F32, a);
-        }
+        for (int j = 0; j < VEC; ++j) hq = fmaf(h[j], a[j], hq);
+        const float r = inverse_norm(group_sum_dpp<LPR>(dot_raw<T, VEC>(x, x, 0.f)));
+        const float t = projection(group_sum_dpp<LPR>(hq), r);
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) o[j] = through_norm(a[VEC + j], a[j], h[j], r, t);
+        if (live) grad.store<VEC>(row, sub * VEC, o);
     };
 
-    // every group runs the same number of batches: the lane-group sums need the whole wave; edges
-    // beyond the group's run are masked
-    for (int b = rs; b < rs + RUN; b += BW_B) {
-        int c[BW_B], r[BW_B];
-        bool need[BW_B];
+#pragma unroll 1
+    for (int b = 0; b < RUN; b += BW_B) {
+        const uint4 o4 = *reinterpret_cast<const uint4 *>(s_off + at + b);
+        const int4 r4 = *reinterpret_cast<const int4 *>(s_row + at + b);
+        const uint32_t o[BW_B] = {o4.x, o4.y, o4.z, o4.w};
+        const int r[BW_B] = {r4.x, r4.y, r4.z, r4.w};
+        const uint32_t o_mine = s_off[at + b + quad];
+        const int r_mine = s_row[at + b + quad];
         RawVec<T, VEC> y[BW_B], dy[BW_B];
-        float2 st[BW_B];
 #pragma unroll
         for (int k = 0; k < BW_B; ++k) {
-            const bool ok = b + k < re;
-            const int p = ok ? b + k + g : 0;
-            c[k] = ok ? s_col[p] : -1;
-            r[k] = ok ? s_row[p] : -1;
+            load_raw<T, VEC>(row_addr<BIG>(HD, o[k], ROW, h_bytes), 0, y[k]);
+            load_raw<T, VEC>(row_addr<BIG>(HD, o[k], ROW, d_bytes), 0, dy[k]);
         }
-        int prev = cur;
+        const float2 sj = stats[BIG ? o_mine : o_mine / static_cast<uint32_t>(ROW)];
+        bool need[BW_B];  // a new row starts (the lanes of a group branch together)
+        int begins = -2;  // the first of them: its slices are loaded ahead
 #pragma unroll
-        for (int k = 0; k < BW_B; ++k) {
-            need[k] = r[k] >= 0 && r[k] != prev;
-            if (r[k] >= 0) prev = r[k];
+        for (int k = BW_B - 1; k >= 0; --k) {
+            need[k] = r[k] != (k ? r[k - 1] : cur);
+            begins = need[k] ? r[k] : begins;
         }
+        RawVec<T, VEC> xs, dxs;
+        float2 ss;
+        if (begins != -2) {
+            load_h(begins, xs);
+            load_d(begins, dxs);
+            ss = stats[max(begins, 0)];
+        }
+        float ri_mine = ri, hh[BW_B], squares[BW_B], dp[BW_B], dpt[BW_B];  // *_mine: of the row of this lane's entry
+        float2 si_mine = si;
 #pragma unroll
         for (int k = 0; k < BW_B; ++k) {
-            if (c[k] >= 0 && live) {
-                load_raw<T, VEC>(HD, static_cast<int64_t>(c[k]) * DP2 + sub * VEC, y[k]);
-                load_raw<T, VEC>(HD, static_cast<int64_t>(c[k]) * DP2 + DP + sub * VEC, dy[k]);
-            } else {
-                zero_raw(y[k]);
-                zero_raw(dy[k]);
+            if (need[k]) {
+                if (r[k] == begins) {
+                    xi = xs;
+                    dxi = dxs;
+                    si = ss;
+                } else {
+                    load_h(r[k], xi);
+                    load_d(r[k], dxi);
+                    si = stats[max(r[k], 0)];
+                }
+                ri = __frsqrt_rn(fmaxf(group_sum_dpp<LPR>(dot_raw<T, VEC>(xi, xi, 0.f)), 1e-24f));  // 1 / max(|h_i|, 1e-12)
+                ri_mine = quad >= k ? ri : ri_mine;
+                si_mine.x = quad >= k ? si.x : si_mine.x;
+                si_mine.y = quad >= k ? si.y : si_mine.y;
             }
-            st[k] = c[k] >= 0 ? stats[c[k]] : make_float2(0.f, 0.f);
+            hh[k] = dot_raw<T, VEC>(xi, y[k], 0.f);
+            squares[k] = dot_raw<T, VEC>(y[k], y[k], 0.f);
+            dp[k] = dot_raw<T, VEC>(dxi, y[k], 0.f);
+            dpt[k] = dot_raw<T, VEC>(xi, dy[k], 0.f);
         }
+        const float rj = __frsqrt_rn(fmaxf(group_sum4<LPR>(squares, odd, upper), 1e-24f));
+        const float cs = ri_mine * rj * group_sum4<LPR>(hh, odd, upper);
+        const float a = __builtin_amdgcn_exp2f(fmaf(beta2_rest, cs, fmaf(beta2, cs, -fabsf(beta2))));
+        const float ds = a * si_mine.x * (group_sum4<LPR>(dp, odd, upper) - si_mine.y);
+        const float pt = a * sj.x;
+        const float dst = pt * (group_sum4<LPR>(dpt, odd, upper) - sj.y);
+        const float coef = beta * (ds + dst) * rj;
+        // The ds of a row add up to zero, so a constant may be taken from its cosines: what z_i and t_i are off by then enters
+        // with their mean less 1/2 instead of their mean, which lies between 1/3 and 1 for the non-negative rows behind a ReLU.
+        if (r_mine >= 0 && sub < 4) dbeta_acc = fmaf(ds, cs - 0.5f, dbeta_acc);
+        const float c4[BW_B] = {quad_lane<0>(coef), quad_lane<1>(coef), quad_lane<2>(coef), quad_lane<3>(coef)};
+        const float p4[BW_B] = {quad_lane<0>(pt), quad_lane<1>(pt), quad_lane<2>(pt), quad_lane<3>(pt)};
 #pragma unroll
         for (int k = 0; k < BW_B; ++k) {
-            if (need[k]) {  // a new row starts (the lanes of a group branch together)
+            if (need[k]) {  // the previous row ends here
                 if (cur >= 0) {
-                    if (first && left_row == cur) {
+                    if (first && left_open) {
+                        head_closed = true; head_row = cur;
 #pragma unroll
-                        for (int j = 0; j < 2 * VEC; ++j) hacc[j] = acc[j];
-                        have_head = true; head_closed = true; head_row = cur;
+                        for (int j = 0; j < VEC; ++j) { s_head[j] = acc[j]; s_head[DP + j] = acc[VEC + j]; }
                     } else {
-                        direct_store(cur);
+                        store_row(cur, xc, acc);
                     }
                     first = false;
                 }
                 cur = r[k];
+                if (r[k] == begins) xc = xs;
+                else load_h(r[k], xc);
 #pragma unroll
                 for (int j = 0; j < 2 * VEC; ++j) acc[j] = 0.f;
-                if (live) {
-                    load_raw<T, VEC>(HD, static_cast<int64_t>(cur) * DP2 + sub * VEC, xi);
-                    load_raw<T, VEC>(HD, static_cast<int64_t>(cur) * DP2 + DP + sub * VEC, dxi);
-                } else {
-                    zero_raw(xi);
-                    zero_raw(dxi);
-                }
-                const float2 si = stats[cur];
-                zi_inv = si.x;
-                ti = si.y;
-                ri = __frsqrt_rn(fmaxf(group_sum_dpp<LPR>(dot_raw<T, VEC>(xi, xi, 0.f)), 1e-24f));  // 1 / max(|h_i|, 1e-12)
             }
-            const float d_hh = group_sum_dpp<LPR>(dot_raw<T, VEC>(xi, y[k], 0.f));
-            const float qj = group_sum_dpp<LPR>(dot_raw<T, VEC>(y[k], y[k], 0.f));
-            const float dp = group_sum_dpp<LPR>(dot_raw<T, VEC>(dxi, y[k], 0.f));
-            const float dpt = group_sum_dpp<LPR>(dot_raw<T, VEC>(xi, dy[k], 0.f));
-            if (r[k] >= 0) {
-                const float rj = __frsqrt_rn(fmaxf(qj, 1e-24f));
-                const float cs = ri * rj * d_hh;
-                const float a = __expf(beta * cs - absb);
-                const float ds = a * zi_inv * (dp - ti);
-                const float pt = a * st[k].x;
-                const float dst = pt * (dpt - st[k].y);
-                const float coef = beta * (ds + dst) * rj;
-                float yf[VEC], dyf[VEC];
-                unpack<T, VEC>(y[k], yf);
-                unpack<T, VEC>(dy[k], dyf);
+            float yf[VEC], dyf[VEC];
+            unpack<T, VEC>(y[k], yf);
+            unpack<T, VEC>(dy[k], dyf);
 #pragma unroll
-                for (int j = 0; j < VEC; ++j) {
-                    acc[j] = fmaf(coef, yf[j], acc[j]);
-                    acc[VEC + j] = fmaf(pt, dyf[j], acc[VEC + j]);
-                }
-                if (sub == 0) dbeta_acc = fmaf(ds, cs, dbeta_acc);
+            for (int j = 0; j < VEC; ++j) {
+                acc[j] = fmaf(c4[k], yf[j], acc[j]);
+                acc[VEC + j] = fmaf(p4[k], dyf[j], acc[VEC + j]);
             }
         }
     }
-    if (has) {  // the run's last segment
-        int right_row;
-        if (re < n_valid) right_row = s_row[re + g + 1];
-        else right_row = next_row;
-        const bool right_open = right_row == cur;
-        if (first && left_row == cur) {
+    // the run's last segment
+    int open = OPEN_NONE;
+    if (cur >= 0) {
+        const int right_row = g == NG - 1 ? next_row : s_row[at + E::RUNP];
+        if (right_row == cur) {
+            open = first && left_open ? OPEN_THROUGH : OPEN_TAIL;
+        } else if (first && left_open) {
+            head_closed = true; head_row = cur;
 #pragma unroll
-            for (int j = 0; j < 2 * VEC; ++j) hacc[j] = acc[j];
-            have_head = true; head_closed = !right_open; head_row = cur;
-        } else if (!right_open) {
-            direct_store(cur);
+            for (int j = 0; j < VEC; ++j) { s_head[j] = acc[j]; s_head[DP + j] = acc[VEC + j]; }
         } else {
-            have_tail = true;
+            store_row(cur, xc, acc);
         }
     }
     // the wave's share of dbeta: lanes in a fixed order
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) dbeta_acc += __shfl_xor(dbeta_acc, m, 64);
-    if (active && lane == 0) dbeta_part[v] = dbeta_acc;
-    __syncthreads();  // staged indices are dead: the LDS is reused for partials
-
-    float *part = reinterpret_cast<float *>(smem) + wave * 2 * NG * DP2;
-    if (have_head) {
+    if (lane == 0) dbeta_part[v] = dbeta_acc;
+    // Rows cut inside this wave: the group that closes a row adds its pieces, in edge order.
+    const int from = first_group<LPR>(open, g);
+    const bool last_open = g == NG - 1 && open != OPEN_NONE;  // a row that goes on in the next range
+    wave_lds_sync();  // the staged entries are dead: their place is taken by the open pieces
+    float *part = reinterpret_cast<float *>(smem[wave]) + sub * VEC;
+    if (open != OPEN_NONE) {
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) { part[g * DP2 + j] = acc[j]; part[g * DP2 + DP + j] = acc[VEC + j]; }
+    }
+    wave_lds_sync();
+    // carried piece: [2 v] of the row that came in from the left, [2 v + 1] of the one left open
+    auto store_carry = [&](int slot, const float (&x)[2 * VEC]) {
+        float q[VEC], ag[VEC];
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) { q[j] = x[j]; ag[j] = x[VEC + j]; }
+        const int64_t to = (static_cast<int64_t>(v) * 2 + slot) * DP2 + sub * VEC;
+        store_vec<VEC>(carry, to, FTC_F32, q);
+        store_vec<VEC>(carry, to + DP, FTC_F32, ag);
+    };
+    if (head_closed || (last_open && open == OPEN_THROUGH)) {
+        if (head_closed) load_h(head_row, xi);
+        float run[2 * VEC];
+#pragma unroll
+        for (int j = 0; j < 2 * VEC; ++j) run[j] = 0.f;
+        for (int q = max(from, 0); q < g; ++q) {
+#pragma unroll
+            for (int j = 0; j < VEC; ++j) { run[j] += part[q * DP2 + j]; run[VEC + j] += part[q * DP2 + DP + j]; }
+        }
 #pragma unroll
         for (int j = 0; j < VEC; ++j) {
-            part[(2 * g) * DP2 + sub * VEC + j] = hacc[j];
-            part[(2 * g) * DP2 + DP + sub * VEC + j] = hacc[VEC + j];
+            run[j] += head_closed ? s_head[j] : acc[j];
+            run[VEC + j] += head_closed ? s_head[DP + j] : acc[VEC + j];
         }
+        if (from < 0) store_carry(0, run);
+        else if (head_closed) store_row(head_row, xi, run);
+        else store_carry(1, run);
     }
-    if (have_tail) {
-#pragma unroll
-        for (int j = 0; j < VEC; ++j) {
-            part[(2 * g + 1) * DP2 + sub * VEC + j] = acc[j];
-            part[(2 * g + 1) * DP2 + DP + sub * VEC + j] = acc[VEC + j];
-        }
-    }
-    if (sub == 0) {
-        s_meta[wave][0][g] = have_head ? head_row : -1;
-        s_meta[wave][1][g] = head_closed ? 1 : 0;
-        s_meta[wave][2][g] = have_tail ? cur : -1;
-    }
-    __syncthreads();
-
-    // Add the pieces of rows cut inside this wave, in edge order; one lane per output slot.
-    if (active) {
-        int tail_out = -1;
-        for (int d = lane; d < DP2; d += 64) {
-            float run = 0.f;
-            int run_row = -1;
-            bool from_outside = false;
-            tail_out = -1;
-            for (int q = 0; q < NG; ++q) {
-                const int hr = s_meta[wave][0][q];
-                if (hr >= 0) {
-                    if (run_row < 0) { run_row = hr; run = 0.f; from_outside = true; }
-                    run += part[(2 * q) * DP2 + d];
-                    if (s_meta[wave][1][q]) {
-                        if (from_outside) carry[(static_cast<size_t>(v) * 2) * DP2 + d] = run;
-                        else QA[static_cast<int64_t>(run_row) * DP2 + d] = run;
-                        run_row = -1;
-                        from_outside = false;
-                    }
-                }
-                const int tr = s_meta[wave][2][q];
-                if (tr >= 0) { run_row = tr; run = part[(2 * q + 1) * DP2 + d]; from_outside = false; }
-            }
-            if (run_row >= 0) {
-                if (from_outside) {
-                    carry[(static_cast<size_t>(v) * 2) * DP2 + d] = run;  // the row covers the whole wave
-                } else {
-                    carry[(static_cast<size_t>(v) * 2 + 1) * DP2 + d] = run;
-                    tail_out = run_row;
-                }
-            }
-        }
-        if (lane == 0) {
-            carry_tail_row[2 * v] = tail_out;
-            carry_tail_row[2 * v + 1] = (tail_out >= 0 && far_row != tail_out) ? 1 : 0;  // ends in range v + 1
-        }
+    if (last_open && open == OPEN_TAIL) store_carry(1, acc);
+    if (lane == 63) {
+        const int tail = last_open && !(open == OPEN_THROUGH && from < 0) ? cur : -1;
+        carry_tail_row[2 * v] = tail;
+        carry_tail_row[2 * v + 1] = (tail >= 0 && far_row != tail) ? 1 : 0;  // ends in range v + 1
     }
 }
 
-// sum of the waves' shares in a fixed order: one workgroup of 1024 threads, four loads in flight each
-__global__ __launch_bounds__(1024) void dbeta_sum_kernel(int count, const float *__restrict__ partial, float *out)
+// Sum of the waves' shares in a fixed order by one workgroup of 256 threads.
+__device__ __forceinline__ void dbeta_sum(int count, const float *__restrict__ partial, bool poison, float *out)
 {
-    __shared__ float red[16];
-    float t0 = 0.f, t1 = 0.f, t2 = 0.f, t3 = 0.f;
+    __shared__ float red[4];
+    float t[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     int i = threadIdx.x;
-    for (; i + 3 * 1024 < count; i += 4 * 1024) {
-        t0 += partial[i];
-        t1 += partial[i + 1024];
-        t2 += partial[i + 2048];
-        t3 += partial[i + 3072];
-    }
-    for (; i < count; i += 1024) t0 += partial[i];
-    float t = (t0 + t1) + (t2 + t3);
+    for (; i + 7 * 256 < count; i += 8 * 256) {
 #pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) t += __shfl_xor(t, m, 64);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = t;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        float a = 0.f;
-        for (int w = 0; w < 16; ++w) a += red[w];
-        *out = a;
+        for (int k = 0; k < 8; ++k) t[k] += partial[i + k * 256];
     }
+    for (; i < count; i += 256) t[0] += partial[i];
+    float s = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) s += __shfl_xor(s, m, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) *out = poison ? __int_as_float(0x7fc00000) : (red[0] + red[1]) + (red[2] + red[3]);
+}
+
+// Second pass: rows cut by a range boundary, rows without entries (gradient 0) and, in the first workgroup, the sum of dbeta.  As
+// in the SpMM's second pass G lanes (four features of q and of agg each) finish a row, 64 / G rows per wave; the long rows of a
+// power-law graph, which span more than two ranges, are taken one at a time by the whole wave.
+template <class T, int G>
+__global__ __launch_bounds__(256) void agnn_backward_fixup_kernel(int n, int n_ranges, const int *__restrict__ row_ptr,
+                                                                  const float *__restrict__ carry,
+                                                                  const int *__restrict__ carry_tail_row, int D,
+                                                                  const void *__restrict__ HD, GradOut grad, int seg_r,
+                                                                  const float *__restrict__ dbeta_part, float *__restrict__ dbeta)
+{
+    constexpr int R = 64 / G, DP = 4 * G, DP2 = 2 * DP;
+    const bool poison = poisoned(grad.poison);
+    if (blockIdx.x == 0) {
+        dbeta_sum(n_ranges, dbeta_part, poison, dbeta);
+        return;
+    }
+    const int block = blockIdx.x - 1;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int sub = lane % G;
+    const int v_mine = (block * 4 + wave) * R + lane / G;
+    int2 rec = make_int2(-1, 0);
+    if (v_mine < n_ranges) rec = reinterpret_cast<const int2 *>(carry_tail_row)[v_mine];
+    {
+        // nearly every open row ends in the next range: its pieces are loaded together with the range's record
+        const bool ok = v_mine + 1 < n_ranges;
+        const float *head = carry + (ok ? static_cast<size_t>(v_mine) + 1 : 0) * 2 * DP2 + sub * 4;
+        const float *tail = carry + ((ok ? static_cast<size_t>(v_mine) : 0) * 2 + 1) * DP2 + sub * 4;
+        float4 hq = make_float4(0.f, 0.f, 0.f, 0.f), ha = hq, tq = hq, ta = hq;
+        if (ok) {
+            hq = *reinterpret_cast<const float4 *>(head);
+            ha = *reinterpret_cast<const float4 *>(head + DP);
+            tq = *reinterpret_cast<const float4 *>(tail);
+            ta = *reinterpret_cast<const float4 *>(tail + DP);
+        }
+        const bool mine = ok && rec.x >= 0 && rec.y;
+        RawVec<T, 4> x;
+        zero_raw(x);
+        if (mine) load_raw<T, 4>(HD, static_cast<int64_t>(rec.x) * DP2 + sub * 4, x);
+        float h[4];
+        unpack<T, 4>(x, h);
+        const float q[4] = {hq.x + tq.x, hq.y + tq.y, hq.z + tq.z, hq.w + tq.w};
+        const float ag[4] = {ha.x + ta.x, ha.y + ta.y, ha.z + ta.z, ha.w + ta.w};
+        float hh = dot_raw<T, 4>(x, x, 0.f), p = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) p = sub * 4 + i < D ? fmaf(h[i], q[i], p) : p;
+#pragma unroll
+        for (int m = G / 2; m >= 1; m >>= 1) { hh += __shfl_xor(hh, m, 64); p += __shfl_xor(p, m, 64); }
+        if (mine) {
+            const float ri = inverse_norm(hh), t = projection(p, ri);
+            float o[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o[i] = through_norm(ag[i], q[i], h[i], ri, t);
+            if (sub * 4 + 4 <= D) {
+                grad.store<4>(rec.x, sub * 4, o);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (sub * 4 + i < D) store_elem(grad.dH, static_cast<int64_t>(rec.x) * grad.ld + sub * 4 + i, grad.dt, o[i]);
+            }
+        }
+    }
+    // rows that go on beyond the next range
+    unsigned long long longs = __builtin_amdgcn_ballot_w64(rec.x >= 0 && !rec.y && sub == 0);
+    while (longs) {
+        const int src = __ffsll(static_cast<long long>(longs)) - 1;
+        longs &= longs - 1;
+        const int v = __shfl(v_mine, src, 64), r = __shfl(rec.x, src, 64);
+        const int last = (row_ptr[r + 1] - 1) / seg_r;  // range holding the row's final entry
+        // teams of DL lanes (one per slot) share the row's ranges round-robin, four loads in flight each; their sums are added in
+        // team order: fixed by the shape alone
+        constexpr int DL = DP2 < 64 ? DP2 : 64, PARTS = 64 / DL, STEPS = DP2 / DL;
+        const int part = lane / DL;
+        float sum[STEPS];
+#pragma unroll
+        for (int st = 0; st < STEPS; ++st) {
+            const int d = st * 64 + lane % DL;
+            const float *from = carry + d;
+            float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
+            int u = v + 1 + part;
+            for (; u + 3 * PARTS <= last; u += 4 * PARTS) {
+                const float a0 = from[(static_cast<size_t>(u) * 2) * DP2];
+                const float a1 = from[(static_cast<size_t>(u + PARTS) * 2) * DP2];
+                const float a2 = from[(static_cast<size_t>(u + 2 * PARTS) * 2) * DP2];
+                const float a3 = from[(static_cast<size_t>(u + 3 * PARTS) * 2) * DP2];
+                s0 += a0; s1 += a1; s2 += a2; s3 += a3;
+            }
+            for (; u <= last; u += PARTS) s0 += from[(static_cast<size_t>(u) * 2) * DP2];
+            float s = (s0 + s1) + (s2 + s3);
+            for (int off = 32; off >= DL; off >>= 1) s += __shfl_down(s, off, 64);
+            sum[st] = s + carry[(static_cast<size_t>(v) * 2 + 1) * DP2 + d];  // meant for the lanes below DL
+        }
+        // slots [0, DP): q, [DP, 2 DP): agg of the same features.  DP < 64: both in one step, DP lanes apart; else in two steps.
+        constexpr int FS = DP < 64 ? 1 : DP / 64;  // steps over the features
+        const bool feat = lane < (DP < 64 ? DP : 64);
+        float h[FS], hh = 0.f, p = 0.f;
+#pragma unroll
+        for (int st = 0; st < FS; ++st) {
+            const int d = st * 64 + lane;
+            h[st] = 0.f;
+            if (feat && d < D) {
+                RawVec<T, 2> x;  // (an element's pair: rows of HD are padded to whole pieces)
+                load_raw<T, 2>(HD, static_cast<int64_t>(r) * DP2 + (d & ~1), x);
+                float f[2];
+                unpack<T, 2>(x, f);
+                h[st] = f[d & 1];
+                hh = fmaf(h[st], h[st], hh);
+                p = fmaf(h[st], sum[st], p);
+            }
+        }
+#pragma unroll
+        for (int m = 32; m >= 1; m >>= 1) { hh += __shfl_xor(hh, m, 64); p += __shfl_xor(p, m, 64); }
+        const float ri = inverse_norm(hh), t = projection(p, ri);
+#pragma unroll
+        for (int st = 0; st < FS; ++st) {
+            const int d = st * 64 + lane;
+            const float ag = DP < 64 ? __shfl(sum[0], (lane + DP) & 63, 64) : sum[(st + FS) % STEPS];
+            if (feat && d < D)
+                store_elem(grad.dH, static_cast<int64_t>(r) * grad.ld + d, grad.dt, through_norm(ag, sum[st], h[st], ri, t));
+        }
+    }
+    const int64_t row = static_cast<int64_t>(block) * 256 + threadIdx.x;
+    if (row < n && row_ptr[row] == row_ptr[row + 1])
+        for (int d = 0; d < D; ++d) store_elem(grad.dH, row * grad.ld + d, grad.dt, poison ? __int_as_float(0x7fc00000) : 0.f);
 }
 
 // The fused pass covers the shapes of the edge-balanced kernels whose pair (q, agg) still fits the
@@ -371,13 +522,12 @@ static size_t bw_dp2(int dtype, int D)
 static size_t bw_ws(int n, int nnz, int r, size_t dp2)
 {
     const size_t n_ranges = static_cast<size_t>(seg_count(nnz, r));
-    return 2 * align_up(static_cast<size_t>(n) * dp2 * sizeof(float), 256) + align_up(static_cast<size_t>(n) * sizeof(float2), 256) +
+    return align_up(static_cast<size_t>(n) * dp2 * sizeof(float), 256) + align_up(static_cast<size_t>(n) * sizeof(float2), 256) +
            align_up(n_ranges * 2 * dp2 * sizeof(float), 256) + align_up(n_ranges * 2 * sizeof(int), 256) +
            align_up(n_ranges * sizeof(float), 256);
 }
 
-// [QA: n x DP2 fp32 | HD: n x DP2 elements | stats: n float2 | carry | tail rows | dbeta shares], DP2 of the
-// widest element type
+// [HD: n x DP2 elements | stats: n float2 | carry | tail rows | dbeta shares], DP2 of the widest element type
 size_t agnn_backward_fused_ws(int n, int nnz, int D, bool least)
 {
     size_t dp2 = 0;
@@ -387,15 +537,15 @@ size_t agnn_backward_fused_ws(int n, int nnz, int D, bool least)
     return bw_ws(n, nnz, least ? SEG_R : seg_range(nnz, SEG_AGNN_BACKWARD), dp2);
 }
 
-template <class T, int R>
+template <class T, int R, bool BIG>
 static void launch_bw_t(int vec, int lpr, unsigned grid, hipStream_t s, int nnz, int n_ranges, const ftc_csr &g,
-                        const int *e2r, const void *HD, int D, float beta, const float2 *stats, float *QA, float *carry,
+                        const int *e2r, const void *HD, int D, float beta, const float2 *stats, GradOut grad, float *carry,
                         int *tail_row, float *dbeta_part)
 {
     constexpr int VM = T::VEC;
 #define FTC_BW(V, L)                                                                                                \
-    hipLaunchKernelGGL((agnn_backward_fused_kernel<T, V, L, R>), dim3(grid), dim3(256), 0, s, nnz, n_ranges, g.col_idx, \
-                       e2r, HD, D, beta, stats, QA, carry, tail_row, dbeta_part)
+    hipLaunchKernelGGL((agnn_backward_fused_kernel<T, V, L, R, BIG>), dim3(grid), dim3(256), 0, s, nnz, n_ranges,   \
+                       g.row_ptr, g.col_idx, e2r, HD, D, beta, stats, grad, carry, tail_row, dbeta_part)
     if (vec == VM) {
         if (lpr == 4) FTC_BW(VM, 4);
         else if (lpr == 8) FTC_BW(VM, 8);
@@ -409,71 +559,74 @@ static void launch_bw_t(int vec, int lpr, unsigned grid, hipStream_t s, int nnz,
 #undef FTC_BW
 }
 
+template <class T>
+static int32_t launch_bw(int vec, int lpr, int r, hipStream_t s, const ftc_csr &g, const int *e2r, const void *H, const void *dY,
+                         int ld, int D, float beta, const float *row_z, const void *Y, int ldy, int ydt, GradOut grad, float *dbeta,
+                         void *HD, float2 *stats, float *carry, int *tail_row, float *dbeta_part)
+{
+    const int n = g.n, dp = vec * lpr, n_ranges = static_cast<int>(seg_count(g.nnz, r));
+    const unsigned grid_rows8 = static_cast<unsigned>((static_cast<int64_t>(n) * 8 + 255) / 256);
+    hipLaunchKernelGGL(agnn_row_stats_kernel<T>, dim3(grid_rows8), dim3(256), 0, s, n, H, dY, ld, Y, ldy, ydt, D, dp, row_z, stats,
+                       HD);
+    if (n_ranges > 0) {
+        const unsigned grid = static_cast<unsigned>((n_ranges + 3) / 4);
+#define FTC_BWR(R, BIG) \
+    launch_bw_t<T, R, BIG>(vec, lpr, grid, s, g.nnz, n_ranges, g, e2r, HD, D, beta, stats, grad, carry, tail_row, dbeta_part)
+        if (rows_need_64_bits(n, 2 * static_cast<int64_t>(dp) * T::BYTES)) FTC_BWR(SEG_R, true);
+        else if (r == SEG_R) FTC_BWR(SEG_R, false);
+        else if (r == 256) FTC_BWR(256, false);
+        else FTC_BWR(128, false);
+#undef FTC_BWR
+        const int32_t st = launch_status("agnn_backward_fused");
+        if (st != FTC_OK) return st;
+    }
+    const int lanes = dp / 4;  // of a cut row: four features each
+    const int64_t blocks_rows = (static_cast<int64_t>(n) + 255) / 256;
+    const int64_t blocks_ranges = ceil_div(n_ranges, 4 * (64 / lanes));
+    const unsigned grid2 = static_cast<unsigned>((blocks_rows > blocks_ranges ? blocks_rows : blocks_ranges) + 1);
+#define FTC_FX(G)                                                                                                          \
+    case G:                                                                                                                \
+        hipLaunchKernelGGL((agnn_backward_fixup_kernel<T, G>), dim3(grid2), dim3(256), 0, s, n, n_ranges, g.row_ptr, carry, \
+                           tail_row, D, HD, grad, r, dbeta_part, dbeta);                                                   \
+        break;
+    switch (lanes) {
+        FTC_FX(1) FTC_FX(2) FTC_FX(4) FTC_FX(8) FTC_FX(16) FTC_FX(32)
+    }
+#undef FTC_FX
+    return launch_status("agnn_backward_fused fixup");
+}
+
 // Caller has checked: window index present, agnn_backward_fused_shape(dt, D), rows of H and dY
-// 16-byte aligned with the same leading dimension, workspace of agnn_backward_fused_ws() bytes.
+// 16-byte aligned with the same leading dimension, workspace of agnn_backward_fused_ws() bytes.  pattern_flag: see GradOut.
 int32_t launch_agnn_backward_fused(const ftc_csr &g, const ftc_windows &w, const void *H, const void *dY, int ld, int dt,
                                    int D, float beta, const float *row_z, const void *Y, int ldy, int ydt, void *dH,
-                                   int lddh, int dh_dt, float *dbeta, void *ws, size_t ws_bytes, hipStream_t s)
+                                   int lddh, int dh_dt, float *dbeta, const int32_t *pattern_flag, void *ws, size_t ws_bytes,
+                                   hipStream_t s)
 {
     int vec = 0, lpr = 0;
     seg_shape(dt, D, &vec, &lpr);
-    const int dp = vec * lpr, dp2 = 2 * dp;
-    const int n = g.n;
-    const int r = ws_bytes >= bw_ws(n, g.nnz, seg_range(g.nnz, SEG_AGNN_BACKWARD), dp2) ? seg_range(g.nnz, SEG_AGNN_BACKWARD) : SEG_R;
-    const int n_ranges = static_cast<int>(seg_count(g.nnz, r));
+    const int dp2 = 2 * vec * lpr, n = g.n;
+    const bool big = rows_need_64_bits(n, static_cast<int64_t>(dp2) * elem_size(dt));  // ranges of SEG_R only
+    const int short_r = big ? SEG_R : seg_range(g.nnz, SEG_AGNN_BACKWARD);
+    const int r = ws_bytes >= bw_ws(n, g.nnz, short_r, dp2) ? short_r : SEG_R;
+    const size_t n_ranges = static_cast<size_t>(seg_count(g.nnz, r));
     char *p = static_cast<char *>(ws);
-    float *QA = reinterpret_cast<float *>(p);
-    p += align_up(static_cast<size_t>(n) * dp2 * sizeof(float), 256);
     void *HD = p;
     p += align_up(static_cast<size_t>(n) * dp2 * sizeof(float), 256);
     float2 *stats = reinterpret_cast<float2 *>(p);
     p += align_up(static_cast<size_t>(n) * sizeof(float2), 256);
     float *carry = reinterpret_cast<float *>(p);
-    p += align_up(static_cast<size_t>(n_ranges) * 2 * dp2 * sizeof(float), 256);
+    p += align_up(n_ranges * 2 * dp2 * sizeof(float), 256);
     int *tail_row = reinterpret_cast<int *>(p);
-    p += align_up(static_cast<size_t>(n_ranges) * 2 * sizeof(int), 256);
+    p += align_up(n_ranges * 2 * sizeof(int), 256);
     float *dbeta_part = reinterpret_cast<float *>(p);
-
-    const unsigned grid_rows8 = static_cast<unsigned>((static_cast<int64_t>(n) * 8 + 255) / 256);
-    if (dt == FTC_F32)
-        hipLaunchKernelGGL(agnn_row_stats_kernel<F32>, dim3(grid_rows8), dim3(256), 0, s, n, H, dY, ld, Y, ldy, ydt, D, dp,
-                           row_z, stats, HD);
-    else if (dt == FTC_F16)
-        hipLaunchKernelGGL(agnn_row_stats_kernel<F16>, dim3(grid_rows8), dim3(256), 0, s, n, H, dY, ld, Y, ldy, ydt, D, dp,
-                           row_z, stats, HD);
-    else
-        hipLaunchKernelGGL(agnn_row_stats_kernel<BF16>, dim3(grid_rows8), dim3(256), 0, s, n, H, dY, ld, Y, ldy, ydt, D, dp,
-                           row_z, stats, HD);
-    if (n_ranges > 0) {
-        const unsigned grid = static_cast<unsigned>((n_ranges + 3) / 4);
-#define FTC_BWR(T)                                                                                                        \
-    do {                                                                                                                  \
-        if (r == SEG_R) launch_bw_t<T, SEG_R>(vec, lpr, grid, s, g.nnz, n_ranges, g, w.edge_to_row, HD, D, beta, stats,   \
-                                              QA, carry, tail_row, dbeta_part);                                           \
-        else if (r == 256) launch_bw_t<T, 256>(vec, lpr, grid, s, g.nnz, n_ranges, g, w.edge_to_row, HD, D, beta, stats,  \
-                                               QA, carry, tail_row, dbeta_part);                                          \
-        else launch_bw_t<T, 128>(vec, lpr, grid, s, g.nnz, n_ranges, g, w.edge_to_row, HD, D, beta, stats, QA, carry,      \
-                                tail_row, dbeta_part);                                                                    \
-    } while (0)
-        if (dt == FTC_F32) FTC_BWR(F32);
-        else if (dt == FTC_F16) FTC_BWR(F16);
-        else FTC_BWR(BF16);
-#undef FTC_BWR
-        const int32_t st = launch_status("agnn_backward_fused");
-        if (st != FTC_OK) return st;
-    }
-    // rows cut by wave boundaries and rows without entries: the SpMM fix-up on the 2 * DP wide rows
-    int32_t st = launch_seg_fixup(n, n_ranges, g.row_ptr, carry, tail_row, dp2, dp2, QA, dp2, FTC_F32, Epi{0, nullptr},
-                                  nullptr, r, s, "agnn_backward_fused fixup");
-    if (st != FTC_OK) return st;
-    hipLaunchKernelGGL(dbeta_sum_kernel, dim3(1), dim3(1024), 0, s, n_ranges, dbeta_part, dbeta);
-    st = launch_status("agnn_backward_fused dbeta");
-    if (st != FTC_OK) return st;
-    // dH = agg + (q - hn <hn, q>) / |h|, rounded once to the requested type
-    float *rinv = reinterpret_cast<float *>(stats);  // the pairs are dead: their array takes the inverse norms
-    st = launch_row_rnorm(n, H, ld, dt, D, rinv, s);
-    if (st != FTC_OK) return st;
-    return launch_cos_backward_rows(n, H, ld, dt, D, rinv, QA, dp2, QA + dp, dp2, dH, lddh, dh_dt, s);
+    const GradOut grad{dH, lddh, dh_dt, aligned16(dH) && (static_cast<int64_t>(lddh) * elem_size(dh_dt)) % 16 == 0, pattern_flag};
+#define FTC_BWT(T) \
+    launch_bw<T>(vec, lpr, r, s, g, w.edge_to_row, H, dY, ld, D, beta, row_z, Y, ldy, ydt, grad, dbeta, HD, stats, carry, tail_row, dbeta_part)
+    if (dt == FTC_F32) return FTC_BWT(F32);
+    if (dt == FTC_F16) return FTC_BWT(F16);
+    return FTC_BWT(BF16);
+#undef FTC_BWT
 }
 
 }  // namespace ftc

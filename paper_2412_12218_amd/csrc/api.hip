@@ -777,11 +777,9 @@ int32_t ftc_agnn_layer_backward_fused(const ftc_csr *g, const ftc_windows *w, co
         return fail(FTC_EWORKSPACE, "ftc_agnn_layer_backward_fused: workspace of %zu bytes needed", need);
     if (reinterpret_cast<uintptr_t>(ws) % 256 != 0)
         return fail(FTC_EALIGN, "ftc_agnn_layer_backward_fused: workspace must be 256-byte aligned");
-    FTC_TRY(launch_agnn_backward_fused(*g, *w, H, dY, ld, dtype, D, beta, row_z, Y, ldy, y_dtype, dH, lddh, dh_dtype,
-                                       dbeta, ws, ws_bytes, static_cast<hipStream_t>(stream)));
-    if (pattern_flag)  // not a symmetric pattern: NaN instead of a gradient of nothing
-        return launch_poison_if_flag(pattern_flag, g->n, D, dH, lddh, dh_dtype, dbeta, static_cast<hipStream_t>(stream));
-    return FTC_OK;
+    // pattern_flag not zero, not a symmetric pattern: NaN instead of a gradient of nothing
+    return launch_agnn_backward_fused(*g, *w, H, dY, ld, dtype, D, beta, row_z, Y, ldy, y_dtype, dH, lddh, dh_dtype, dbeta,
+                                      pattern_flag, ws, ws_bytes, static_cast<hipStream_t>(stream));
 }
 
 // ---- locality reordering (preprocessing) ---------------------------------------------------------

@@ -40,7 +40,9 @@ inline int ceil_div(int a, int b) { return static_cast<int>((static_cast<int64_t
 //   entries               9 thousand       0.6 M            1.5 M            3.8 M            8 M               16 M
 //   SpMM                  17 / 11 / 11     18 / 15 / 14     25 / 23 / 26     52 / 50 / 51     106 / 106 / 108   201 / 201 / 206
 //   AGNN layer with P     23 / 16 / 15     28 / 24 / 24     38 / 39 / 42     72 / 72 / 83     136 / 135 / 150   253 / 248 / 265
-//   its backward pass     41 / 32 / 29     58 / 47 / 49     73 / 77 / 80     138 / 141 / 160  208 / 217 / 256
+// and of the AGNN model with four layers, forward and backward:
+//   entries               9 thousand       150 thousand     0.6 M            1.5 M            3.8 M            8 M
+//   R of the backward     217 / 178 / 177  237 / 196 / 181  323 / 281 / 284  440 / 451 / 457  786 / 796 / 857  1526 / 1547 / 1647
 struct SegLines {
     int below_128, below_256;  // entry counts up to which ranges of 128, of 256 edges are taken
 };
@@ -103,7 +105,8 @@ bool agnn_backward_fused_shape(int dtype, int D);
 size_t agnn_backward_fused_ws(int n, int nnz, int D, bool least);
 int32_t launch_agnn_backward_fused(const ftc_csr &g, const ftc_windows &w, const void *H, const void *dY, int ld, int dt,
                                    int D, float beta, const float *row_z, const void *Y, int ldy, int ydt, void *dH,
-                                   int lddh, int dh_dt, float *dbeta, void *ws, size_t ws_bytes, hipStream_t s);
+                                   int lddh, int dh_dt, float *dbeta, const int32_t *pattern_flag, void *ws, size_t ws_bytes,
+                                   hipStream_t s);
 bool mfma_shape_ok(int dtype, int D);
 int32_t launch_classify(const ftc_csr &g, const ftc_windows &w, float reuse, int max_edges, uint8_t *flags,
                         hipStream_t s);
@@ -113,7 +116,6 @@ int32_t launch_sddmm_mfma(const ftc_csr &g, const ftc_windows &w, const void *X,
 int32_t launch_spmm_mfma(const ftc_csr &g, const ftc_windows &w, const float *vals, const void *X, int ldx, int dt,
                          int D, void *out, int ldo, int odt, Epi epi, const uint8_t *flags, hipStream_t s);
 // backward.hip
-int32_t launch_poison_if_flag(const int32_t *flag, int n, int D, void *M, int ld, int dt, float *scalar, hipStream_t s);
 int32_t launch_transpose_index(const ftc_csr &g, const int *edge_to_row, int *T, int *flag, hipStream_t s);
 int32_t launch_softmax_backward(const ftc_csr &g, const float *p, const float *dp, float *ds, hipStream_t s);
 int32_t launch_softmax_backward_seg(const ftc_csr &g, const ftc_windows &w, const float *p, const float *dp, float *ds,

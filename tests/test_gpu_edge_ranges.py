@@ -118,3 +118,77 @@ def test_feature_matrix_of_more_than_4_gib(dtype):
     check_spmm(g, win, vals, X, B.ftc_spmm(g, win, vals, X))
     _, _, ref, terms = attention(g, X, 1.5)
     close(B.ftc_agnn_layer(g, win, X, beta=1.5), ref, terms)
+
+
+def symmetric_graph(n, rng):
+    """Rows of all kinds: two hubs, a ring, pairs far apart, every tenth node without entries."""
+    u = [np.arange(1, n), np.full(n // 2, 3), np.full(n - 5, n - 2), rng.integers(0, n, 3 * n)]
+    v = [np.arange(n - 1), np.arange(n // 2), np.arange(n - 5), rng.integers(0, n, 3 * n)]
+    u, v = np.concatenate(u), np.concatenate(v)
+    keep = (u % 10 != 7) & (v % 10 != 7)
+    u, v = u[keep], v[keep]
+    key = np.unique(np.concatenate([u * n + v, v * n + u]))
+    ptr = np.zeros(n + 1, dtype=np.int32)
+    ptr[1:] = np.cumsum(np.bincount(key // n, minlength=n))
+    return ptr, (key % n).astype(np.int32)
+
+
+def attention_gradients(g, X, beta, dY):
+    X = X.double().clone().requires_grad_()
+    b = torch.tensor(float(beta), dtype=torch.float64, device="cuda", requires_grad=True)
+    rows, cols = rows_of(g), g.col_idx.long()
+    Xn = X / X.norm(dim=1).clamp(min=1e-12)[:, None]
+    w = torch.exp(b * (Xn[rows] * Xn[cols]).sum(1))
+    z = torch.zeros(g.n, dtype=torch.float64, device="cuda").index_add(0, rows, w)
+    out = torch.zeros(X.shape, dtype=torch.float64, device="cuda").index_add(0, rows, X[cols] * (w / z[rows])[:, None])
+    out.backward(dY.double())
+    return X.grad, b.grad
+
+
+@pytest.mark.parametrize("dtype,D,pad", [(F16, 32, 0), (F16, 64, 0), (BF16, 40, 0), (F32, 32, 0), (F32, 128, 0), (F16, 16, 0), (F32, 12, 0),
+                                         (F16, 32, 3), (F32, 128, 1), (BF16, 128, 0)])
+def test_single_pass_backward_writes_complete_gradients(dtype, D, pad):
+    n = 2003
+    ptr, cols = symmetric_graph(n, np.random.default_rng(D))
+    g = B.Graph.from_numpy(ptr, cols)
+    win = B.ftc_build_windows(g)
+    gen = torch.Generator(device="cuda").manual_seed(D)
+    X = torch.randn((n, D), generator=gen, device="cuda").to(dtype)
+    dY = torch.randn((n, D), generator=gen, device="cuda").to(dtype)
+    X[11] *= 1e-4
+    z = torch.empty(n, device="cuda")
+    y32 = torch.empty((n, (D + 3) // 4 * 4), device="cuda")
+    B.ftc_agnn_layer(g, win, X, beta=1.5, row_z=z, out_f32=y32)
+    ref, dbeta = attention_gradients(g, X, 1.5, dY)
+    buf = torch.full((n, D + pad), 7.0, device="cuda")  # with padding: rows that are not 16-byte aligned
+    dH, db = B.ftc_agnn_layer_backward_fused(g, win, X, z, y32[:, :D], dY, beta=1.5, dH=buf[:, :D])
+    assert torch.all(buf[:, D:] == 7.0)
+    empty = g.row_ptr[1:] == g.row_ptr[:-1]
+    assert int(empty.sum()) > 100 and torch.all(dH[empty] == 0)
+    # fp32 sums: relative to the largest element of the row (at least 1, the size of dY)
+    scale = ref.abs().max(dim=1).values.clamp(min=1.0)
+    assert float(((dH.double() - ref).abs().max(dim=1).values / scale).max()) <= 1e-5
+    assert abs(float(db) - float(dbeta)) <= 1e-6 * g.nnz
+
+
+def test_single_pass_backward_of_more_than_4_gib():
+    """Copies of one graph side by side, 4.3 M nodes with rows of 1 KiB in the workspace: every copy has the gradients of the one."""
+    n, copies, D = 43_000, 100, 128
+    ptr, cols = symmetric_graph(n, np.random.default_rng(3))
+    nnz = int(ptr[-1])
+    small = B.Graph.from_numpy(ptr, cols)
+    k = torch.arange(copies, device="cuda", dtype=torch.int32)[:, None]
+    row_ptr = torch.cat([(small.row_ptr[None, :-1] + k * nnz).reshape(-1), torch.tensor([copies * nnz], dtype=torch.int32, device="cuda")])
+    big = B.Graph(row_ptr, (small.col_idx[None] + k * n).reshape(-1).contiguous())
+    gen = torch.Generator(device="cuda").manual_seed(0)
+    X, dY = (torch.randn((n, D), generator=gen, device="cuda") for _ in range(2))
+    results = []
+    for g, rep in ((small, 1), (big, copies)):
+        win = B.ftc_build_windows(g)
+        H, d = X.repeat(rep, 1), dY.repeat(rep, 1)
+        z = torch.empty(g.n, device="cuda")
+        Y = B.ftc_agnn_layer(g, win, H, beta=1.0, row_z=z)
+        results.append(B.ftc_agnn_layer_backward_fused(g, win, H, z, Y, d, beta=1.0))
+    (a, da), (b, db) = results
+    assert float((b.view(copies, n, D) - a).abs().max()) <= 1e-5 * float(a.abs().max())
+    assert abs(float(db) / copies - float(da)) <= 1e-6 * nnz
