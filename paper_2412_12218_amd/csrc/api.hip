@@ -203,6 +203,8 @@ int32_t ftc_spmm(const ftc_csr *g, const ftc_windows *w, const float *vals, cons
                         ws ? ws_bytes : static_cast<size_t>(0));
         if (reinterpret_cast<uintptr_t>(ws) % 256 != 0)
             return fail(FTC_EALIGN, "ftc_spmm: workspace must be 256-byte aligned");
+        if (path != FTC_PATH_MFMA && spmm_group_ok(g->n, static_cast<int64_t>(ldx) * elem_size(x_dtype), D * elem_size(x_dtype), g->nnz))
+            return launch_spmm_group(*g, vals, X, ldx, x_dtype, D, out, ldo, out_dtype, epi, hs);
         uint8_t *flags = nullptr;
         const size_t fb = flag_bytes(g->n);  // the flags take the end of the workspace, the carried pieces the rest
         const float reuse = path == FTC_PATH_MFMA ? 0.f : spmm_mfma_reuse(D);
@@ -494,15 +496,22 @@ int32_t ftc_agnn_layer(const ftc_csr *g, const ftc_windows *w, const void *H, in
     // normal fp32 number; beyond that the chain with the row-wise softmax takes over
     const bool beta_ok = fabsf(beta) < AGNN_FUSED_MAX_BETA;
     if (!edge_p && w && beta_ok && (g->nnz > 0 || keep) && path != FTC_PATH_MFMA && rows16 &&
-        seg_shape(dtype, D, &vec, &lpr))
+        seg_shape(dtype, D, &vec, &lpr)) {
+        if (agnn_group_ok(g->n, static_cast<int64_t>(ld) * elem_size(dtype), D * elem_size(dtype), g->nnz))
+            return launch_agnn_group(*g, H, ld, dtype, D, beta, out, ldo, out_dtype, row_z, out_f32, ld_f32, nullptr,
+                                     static_cast<hipStream_t>(stream));
         return launch_agnn_fused(*g, *w, H, ld, dtype, D, beta, out, ldo, out_dtype, row_z, out_f32, ld_f32, nullptr, p,
                                  ws_bytes, static_cast<hipStream_t>(stream));
+    }
     // The probabilities come from the same pass; the rows' sums take the end of the workspace.  (The size that was checked
     // above is at least that of the three kernels, which counts the scores and two arrays of n floats: the carried pieces of
     // ranges of SEG_R entries and the sums fit into that.)
     const size_t z_bytes = align_up(static_cast<size_t>(g->n) * sizeof(float), 256);
     if (edge_p && !keep && w && fabsf(beta) <= AGNN_EDGE_P_MAX_BETA && g->nnz > 0 && path != FTC_PATH_MFMA && rows16 &&
         seg_shape(dtype, D, &vec, &lpr)) {
+        if (agnn_group_ok(g->n, static_cast<int64_t>(ld) * elem_size(dtype), D * elem_size(dtype), g->nnz))
+            return launch_agnn_group(*g, H, ld, dtype, D, beta, out, ldo, out_dtype, nullptr, nullptr, 0, edge_p,
+                                     static_cast<hipStream_t>(stream));
         const size_t at = (ws_bytes - z_bytes) / 256 * 256;
         return launch_agnn_fused(*g, *w, H, ld, dtype, D, beta, out, ldo, out_dtype, reinterpret_cast<float *>(p + at), nullptr, 0,
                                  edge_p, p, at, static_cast<hipStream_t>(stream));

@@ -97,6 +97,13 @@ int32_t launch_spmm_seg(const ftc_csr &g, const ftc_windows &w, const float *val
 int32_t launch_sddmm_edges(const ftc_csr &g, const ftc_windows &w, const void *X, const void *Y, int ld, int dt,
                            int D, const float *rs, const float *cs, float alpha, float *out, const uint8_t *dense,
                            bool cosine, hipStream_t s);
+// small_graphs.hip: row_bytes between the rows of X or H, piece_bytes of one that are gathered
+bool spmm_group_ok(int n, int64_t row_bytes, int piece_bytes, int nnz);
+bool agnn_group_ok(int n, int64_t row_bytes, int piece_bytes, int nnz);
+int32_t launch_spmm_group(const ftc_csr &g, const float *vals, const void *X, int ldx, int xdt, int D, void *out, int ldo, int odt,
+                          Epi epi, hipStream_t s);
+int32_t launch_agnn_group(const ftc_csr &g, const void *H, int ld, int dt, int D, float beta, void *out, int ldo, int odt,
+                          float *row_z, float *out32, int ld32, float *edge_p, hipStream_t s);
 size_t agnn_fused_ws(int nnz, int D, bool least);
 int32_t launch_agnn_fused(const ftc_csr &g, const ftc_windows &w, const void *H, int ld, int dt, int D,
                           float beta, void *out, int ldo, int odt, float *row_z, float *out32, int ld32, float *edge_w,

@@ -76,10 +76,13 @@ def smallest_workspace(call, nbytes):
 SHAPES = [(F16, 32), (F16, 64), (BF16, 128), (F16, 40), (BF16, 24), (F32, 128), (F32, 32), (F32, 12), (F16, 16), (F16, 8), (F16, 256)]
 
 
-@pytest.mark.parametrize("which", ["edges", "ones", "aligned", "gap"])
+@pytest.mark.parametrize("which,times", [("edges", 1), ("ones", 1), ("aligned", 1), ("gap", 1), ("edges", 60), ("ones", 330), ("aligned", 150)])
 @pytest.mark.parametrize("dtype,D", SHAPES)
-def test_rows_at_the_ends_of_runs_and_ranges(which, dtype, D):
-    g = graph(row_lengths(which))
+def test_rows_at_the_ends_of_runs_and_ranges(which, times, dtype, D):
+    """Once: the kernels for small graphs, which have one launch and cut no rows; many times over, more than half a million entries:
+    the edge-balanced ones."""
+    g = graph(row_lengths(which) * times)
+    assert times == 1 or g.nnz > 512 << 10
     win = B.ftc_build_windows(g)
     gen = torch.Generator(device="cuda").manual_seed(D)
     X = torch.randn((g.n, D), generator=gen, device="cuda").to(dtype)
