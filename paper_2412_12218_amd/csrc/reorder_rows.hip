@@ -10,14 +10,16 @@
 //                               at most 32 768 entries are sorted in LDS instead of counted (many_ranges()).
 // What bounds them: the look-up.  Every entry is one 4-byte gather from an array that about fills an L2 (4 MB at
 // a million nodes); the streams around it (column ids in, columns out) are read and written once, non-temporal.
-// On the block model with a million nodes and 32 M entries a round of label propagation takes 0.28 ms and the
-// relabelled graph 0.35 ms (R-MAT, 2^20 nodes: 0.52); sorting all entries by label and row with the global radix sort took
-// 4.0 and 4.1 ms.
+// On the block model with a million nodes and 32 M entries a round of label propagation takes 0.21 ms and the
+// relabelled graph 0.33 ms (R-MAT, 2^20 nodes: 0.48); sorting all entries by label and row with the global radix sort took
+// 4.0 and 4.1 ms.  The sorting network is the other half: with min, max and a selection per stage, rows of 33 to 64 two at a time,
+// rows of any length below side by side in halves of the wave and each row's look-ups waiting for the one's before, a round took
+// 0.24 ms (500 000 nodes with nine entries each, the whole plan: 1.39 / 1.01 ms).
 // Larger graphs keep the radix sort: the counters of the long rows cost one pass over the row per 32 768 nodes.  Up to
 // ROW_SORT_NODES the rows are ahead on every graph that was measured but for one kind: the relabelled graph where nearly all
 // entries are in rows of more than 32 768 entries with repeated columns (2^22 nodes, 65 M entries, 95 % of them in rows of
 // 60 000: 18 against 9 ms; half of them: 9.7 against 9.4; label propagation on the first: 16 ms a round on either).
-#include "ftc_common.hpp"
+#include "edge_ranges.hpp"
 
 namespace ftc {
 
@@ -76,7 +78,10 @@ __global__ __launch_bounds__(1024) void row_classes_kernel(int n, const int *__r
 }
 
 // ---- the two uses -----------------------------------------------------------------------------------
-// Row r of the result: entries [start, start + len) of col_idx; value(c) is what column c becomes.
+// Row r of the result: entries [start, start + len) of col_idx; value(c) is what column c becomes: map[lookup_index(c)], checked by
+// settle().  Loads are unconditional and the checks made on what came back: a load inside a branch is waited for at the branch's
+// end, so that the look-ups of several rows would follow one another instead of being in flight together.
+__device__ __forceinline__ int lookup_index(int c, int n) { return static_cast<unsigned>(c) < static_cast<unsigned>(n) ? c : 0; }
 struct Relabel {
     static constexpr bool VOTES = false;
     int n;
@@ -87,14 +92,13 @@ struct Relabel {
         len = rp[r + 1] - rp[r];
         start = len > 0 ? row_ptr[perm[r]] : 0;  // a row that has entries has passed the check of perm[r]
     }
-    __device__ __forceinline__ int value(int c) const
+    __device__ __forceinline__ int settle(int c, int v, bool active) const
     {
-        const bool in = c >= 0 && c < n;
-        const int v = in ? map[c] : -1;
-        if (v >= 0 && v < n) return v;
+        if (!active || (c >= 0 && c < n && v >= 0 && v < n)) return v;
         atomicOr(flag, 1);
         return 0;
     }
+    __device__ __forceinline__ int value(int c) const { return settle(c, map[lookup_index(c, n)], true); }
 };
 struct Votes {
     static constexpr bool VOTES = true;
@@ -106,7 +110,8 @@ struct Votes {
         start = rp[r];
         len = rp[r + 1] - start;
     }
-    __device__ __forceinline__ int value(int c) const { return (c >= 0 && c < n) ? map[c] : 0; }  // out of range: a vote for label 0
+    __device__ __forceinline__ int settle(int c, int v, bool) const { return c >= 0 && c < n ? v : 0; }  // out of range: a vote for label 0
+    __device__ __forceinline__ int value(int c) const { return settle(c, map[lookup_index(c, n)], true); }
 };
 
 // ---- sorting in registers ------------------------------------------------------------------------------
@@ -120,11 +125,38 @@ __device__ __forceinline__ int lane_xor(int v)
         const int m = __builtin_amdgcn_update_dpp(0, v, 0x141, 0xf, 0xf, true);                   // row_half_mirror: ^ 7
         return __builtin_amdgcn_update_dpp(0, m, 0x1b, 0xf, 0xf, true);                           // quad_perm [3,2,1,0]: ^ 3
     } else if constexpr (S == 8) return __builtin_amdgcn_update_dpp(0, v, 0x128, 0xf, 0xf, true); // row_ror:8
-    else return __shfl_xor(v, S, 64);
+    else if constexpr (S == 16) {  // [0]: the even rows of 16 lanes twice, [1]: the odd ones
+        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        return threadIdx.x & 16 ? r[0] : r[1];
+    } else {
+        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);  // the halves of the wave
+        return threadIdx.x & 32 ? r[0] : r[1];
+    }
+}
+
+// The lanes that keep the smaller element in the stage (STRIDE, SIZE) of a sort of `all` elements, W lanes each, register 0.
+constexpr unsigned long long lanes_of_the_smaller(int stride, int size, int all, int W)
+{
+    unsigned long long m = 0ull;
+    for (int lane = 0; lane < 64; ++lane) {
+        const int li = lane % W;
+        const bool up = size >= all || (li & size) == 0;
+        if (up == ((li & stride) == 0)) m |= 1ull << lane;
+    }
+    return m;
+}
+// The smaller of a and b in the lanes of `smaller`, the larger in the others.  Two instructions (min, max and a selection
+// are three), and the mask stays in scalar registers: as a bound per stage in vector registers, which the compiler makes of it
+// by itself, the masks of all sorts cost half of the occupancy.
+__device__ __forceinline__ int pick(int a, int b, unsigned long long smaller)
+{
+    int r;
+    asm("v_cndmask_b32_e64 %0, %4, %5, %3\n\tv_med3_i32 %0, %1, %2, %0" : "=&v"(r) : "v"(a), "v"(b), "s"(smaller), "v"(INT32_MAX), "v"(INT32_MIN));
+    return r;
 }
 
 template <int STRIDE, int SIZE, int K, int W>
-__device__ __forceinline__ void bitonic_stage(int (&v)[K], int li)
+__device__ __forceinline__ void bitonic_stage(int (&v)[K])
 {
     if constexpr (STRIDE >= 64) {  // the partner sits in the same lane
 #pragma unroll
@@ -138,52 +170,50 @@ __device__ __forceinline__ void bitonic_stage(int (&v)[K], int li)
             }
         }
     } else {
-        const bool lower = (li & STRIDE) == 0;
+        constexpr unsigned long long smaller = lanes_of_the_smaller(STRIDE, SIZE, K * W, W);
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             const int o = lane_xor<STRIDE>(v[k]);
-            const bool up = SIZE >= K * W || ((k * 64 + li) & SIZE) == 0;
-            v[k] = (up == lower) ? min(v[k], o) : max(v[k], o);
+            const bool down = SIZE < K * W && ((k * 64) & SIZE) != 0;
+            v[k] = pick(v[k], o, down ? ~smaller : smaller);
         }
     }
-    if constexpr (STRIDE > 1) bitonic_stage<STRIDE / 2, SIZE, K, W>(v, li);
+    if constexpr (STRIDE > 1) bitonic_stage<STRIDE / 2, SIZE, K, W>(v);
 }
 
-// Element i of the row sits in register i / 64, lane i % 64 (W = 64), or in lane i of the half wave (W = 32, K = 1).
+// Element i of the row sits in register i / 64, lane i % 64 (W = 64), or in lane i of its W lanes (W = 16 or 32, K = 1).
 template <int SIZE, int K, int W>
-__device__ __forceinline__ void bitonic_sort(int (&v)[K], int li)
+__device__ __forceinline__ void bitonic_sort(int (&v)[K])
 {
-    if constexpr (SIZE > 2) bitonic_sort<SIZE / 2, K, W>(v, li);
-    bitonic_stage<SIZE / 2, SIZE, K, W>(v, li);
+    if constexpr (SIZE > 2) bitonic_sort<SIZE / 2, K, W>(v);
+    bitonic_stage<SIZE / 2, SIZE, K, W>(v);
 }
 
 template <int W>
-__device__ __forceinline__ int group_max(int v)
+__device__ __forceinline__ uint32_t group_max(uint32_t x)
 {
-    v = max(v, lane_xor<1>(v)); v = max(v, lane_xor<2>(v)); v = max(v, lane_xor<4>(v)); v = max(v, lane_xor<8>(v));
-    v = max(v, lane_xor<16>(v));
-    if constexpr (W == 64) v = max(v, lane_xor<32>(v));
-    return v;
-}
-template <int W>
-__device__ __forceinline__ int group_min(int v)
-{
-    v = min(v, lane_xor<1>(v)); v = min(v, lane_xor<2>(v)); v = min(v, lane_xor<4>(v)); v = min(v, lane_xor<8>(v));
-    v = min(v, lane_xor<16>(v));
-    if constexpr (W == 64) v = min(v, lane_xor<32>(v));
-    return v;
+    int v = static_cast<int>(x);
+    auto larger = [](int a, int b) { return static_cast<int>(max(static_cast<uint32_t>(a), static_cast<uint32_t>(b))); };
+    v = larger(v, lane_xor<1>(v)); v = larger(v, lane_xor<2>(v)); v = larger(v, lane_xor<4>(v)); v = larger(v, lane_xor<8>(v));
+    if constexpr (W >= 32) v = larger(v, lane_xor<16>(v));
+    if constexpr (W == 64) v = larger(v, lane_xor<32>(v));
+    return static_cast<uint32_t>(v);
 }
 
-// The value of the longest run of equal values among the first `len` sorted ones, the smallest on a tie.
+// The value of the longest run of equal values among the first `len` sorted ones, the smallest on a tie.  Values lie below
+// ROW_SORT_NODES and a row here has at most RS_LONG entries: length and value are one 32-bit word.
 template <int K, int W>
 __device__ __forceinline__ int longest_run(const int (&v)[K], int len, int lane)
 {
+    constexpr int VALUE_BITS = 22;
+    constexpr uint32_t VALUES = (1u << VALUE_BITS) - 1u;
+    static_assert(ROW_SORT_NODES <= 1 << VALUE_BITS && RS_LONG <= 1 << (32 - VALUE_BITS), "a run and its value fit into 32 bits");
     const int li = lane & (W - 1);
-    int best = 0, best_v = RS_NONE;
+    uint32_t best = 0u;
     int next = len;  // where the first run after register k begins
 #pragma unroll
     for (int k = K - 1; k >= 0; --k) {
-        int prev = __shfl_up(v[k], 1, 64);
+        int prev = __builtin_amdgcn_update_dpp(0, v[k], 0x138, 0xf, 0xf, false);  // wave_shr:1
         if constexpr (K > 1) {
             if (k > 0) {
                 const int last = __builtin_amdgcn_readlane(v[k > 0 ? k - 1 : 0], 63);
@@ -192,15 +222,22 @@ __device__ __forceinline__ int longest_run(const int (&v)[K], int len, int lane)
         }
         const int i = k * 64 + li;
         const bool start = i < len && (i == 0 || prev != v[k]);
-        unsigned long long m = __builtin_amdgcn_ballot_w64(start);
-        if constexpr (W == 32) m = lane < 32 ? m & 0xffffffffull : m >> 32;
-        const unsigned long long above = li < 63 ? m & (~0ull << (li + 1)) : 0ull;
-        const int end = above ? k * 64 + __ffsll(static_cast<long long>(above)) - 1 : next;
-        if (start && end - i >= best) { best = end - i; best_v = v[k]; }  // registers descend: >= keeps the smaller value
-        if (m) next = k * 64 + __ffsll(static_cast<long long>(m)) - 1;
+        const unsigned long long all = __builtin_amdgcn_ballot_w64(start);
+        int end;
+        if constexpr (W == 64) {
+            const unsigned long long above = li < 63 ? all & (~0ull << (li + 1)) : 0ull;
+            end = above ? k * 64 + __ffsll(static_cast<long long>(above)) - 1 : next;
+            if (all) next = k * 64 + __ffsll(static_cast<long long>(all)) - 1;
+        } else {
+            uint32_t m = lane < 32 ? static_cast<uint32_t>(all) : static_cast<uint32_t>(all >> 32);
+            if constexpr (W == 16) m = m >> (lane & 16) & 0xffffu;
+            const uint32_t above = m & (0xfffffffeu << li);
+            end = above ? __ffs(static_cast<int>(above)) - 1 : len;
+        }
+        const uint32_t score = static_cast<uint32_t>(end - i - 1) << VALUE_BITS | (VALUES - (static_cast<uint32_t>(v[k]) & VALUES));
+        best = start ? max(best, score) : best;
     }
-    const int most = group_max<W>(best);
-    return group_min<W>(best == most ? best_v : RS_NONE);
+    return static_cast<int>(VALUES - (group_max<W>(best) & VALUES));
 }
 
 // Sorted values of row r leave: all of them, or the winner's label.
@@ -218,51 +255,85 @@ __device__ __forceinline__ void row_done(const Use &u, int r, int dst, int len, 
     }
 }
 
-// A label that more than half of a row's entries hold wins without any sorting; two of the entries are tried.  Labels settle
-// after a few rounds and most rows pass then.  Returns the winner, or -1 where neither is one.
-__device__ __forceinline__ int majority_of(unsigned long long eq0, unsigned long long eq1, int c0, int c1, int len)
-{
-    return 2 * __popcll(eq0) > len ? c0 : 2 * __popcll(eq1) > len ? c1 : -1;
-}
-
 // one row of a queue by one wave, K entries per lane
 template <class Use, int K>
 __device__ __forceinline__ void queued_row(const Use &u, int r, int lane)
 {
     int start, len;
     u.row(r, start, len);
-    int v[K];
+    int c[K], v[K];
 #pragma unroll
-    for (int k = 0; k < K; ++k) v[k] = k * 64 + lane < len ? __builtin_nontemporal_load(u.col_idx + start + k * 64 + lane) : -1;
+    for (int k = 0; k < K; ++k) c[k] = __builtin_nontemporal_load(u.col_idx + start + min(k * 64 + lane, len - 1));  // (no queued row is empty)
 #pragma unroll
-    for (int k = 0; k < K; ++k) v[k] = k * 64 + lane < len ? u.value(v[k]) : RS_NONE;
-    bitonic_sort<64 * K, K, 64>(v, lane);
+    for (int k = 0; k < K; ++k) v[k] = u.map[lookup_index(c[k], u.n)];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const bool in = k * 64 + lane < len;
+        v[k] = u.settle(c[k], v[k], in);
+        if (!in) v[k] = RS_NONE;
+    }
+    bitonic_sort<64 * K, K, 64>(v);
     row_done<Use, K, 64>(u, r, u.rp[r], len, v, lane);
 }
 
-// one row of 33 to 64 entries by one wave
-template <class Use>
-__device__ __forceinline__ void wave_row(const Use &u, int r, int dst, int len, int (&x)[1], int lane)
+// The rows among the wave's RS_ROWS with more than `above` and at most W entries: 64 / W of them side by side in the wave, SETS such
+// sets in flight.  order: LDS of the wave.
+template <class Use, int W, int SETS>
+__device__ __forceinline__ void short_rows(const Use &u, int r0, int above, int start_l, int len_l, int dst_l, int lane, int *order)
 {
-    if constexpr (Use::VOTES) {
-        const int c0 = __builtin_amdgcn_readlane(x[0], 0), c1 = __builtin_amdgcn_readlane(x[0], 7);
-        const unsigned long long e0 = __builtin_amdgcn_ballot_w64(lane < len && x[0] == c0);
-        const unsigned long long e1 = __builtin_amdgcn_ballot_w64(lane < len && x[0] == c1);
-        const int w = majority_of(e0, e1, c0, c1, len);
-        if (w >= 0) {  // uniform
-            if (lane == 0) u.out[r] = w;
-            return;
+    constexpr int PER = 64 / W;
+    const int part = lane / W, li = lane % W;
+    const bool mine = len_l > above && len_l <= W;
+    const unsigned long long rows = __builtin_amdgcn_ballot_w64(mine);
+    const int count = __popcll(rows);
+    if (count == 0) return;  // uniform
+    wave_lds_sync();  // the order of the class before has been read
+    if (mine) order[__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(rows >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(rows), 0u))] = lane;
+    wave_lds_sync();
+    for (int s0 = 0; s0 < count; s0 += PER * SETS) {
+        int t[SETS], len[SETS], c[SETS], v[SETS];
+#pragma unroll
+        for (int p = 0; p < SETS; ++p) {
+            const int at = s0 + p * PER + part;
+            t[p] = order[min(at, count - 1)];
+            const int st = __shfl(start_l, t[p], 64), ln = __shfl(len_l, t[p], 64);
+            c[p] = __builtin_nontemporal_load(u.col_idx + st + min(li, ln - 1));
+            len[p] = at < count ? ln : 0;
+        }
+#pragma unroll
+        for (int p = 0; p < SETS; ++p) v[p] = u.map[lookup_index(c[p], u.n)];
+#pragma unroll
+        for (int p = 0; p < SETS; ++p) {
+            if (s0 + p * PER >= count) break;  // uniform
+            const bool in = li < len[p];
+            int x[1] = {u.settle(c[p], v[p], in)};
+            if (!in) x[0] = RS_NONE;
+            if constexpr (Use::VOTES && W > 16) {
+                // a label that more than half of a row's entries hold wins without any sorting; two of the entries are tried.
+                // Labels settle after a few rounds and most rows pass then
+                const int c0 = __shfl(x[0], lane & ~(W - 1), 64), c1 = __shfl(x[0], (lane & ~(W - 1)) + 7, 64);
+                unsigned long long e0 = __builtin_amdgcn_ballot_w64(in && x[0] == c0), e1 = __builtin_amdgcn_ballot_w64(in && x[0] == c1);
+                if constexpr (W == 32) {
+                    e0 = lane < 32 ? e0 & 0xffffffffull : e0 >> 32;
+                    e1 = lane < 32 ? e1 & 0xffffffffull : e1 >> 32;
+                }
+                const bool won0 = 2 * __popcll(e0) > len[p], won1 = 2 * __popcll(e1) > len[p];
+                if (__builtin_amdgcn_ballot_w64(len[p] > 0 && !won0 && !won1) == 0ull) {
+                    if (li == 0 && len[p] > 0) u.out[r0 + t[p]] = won0 ? c0 : c1;
+                    continue;
+                }
+            }
+            bitonic_sort<W, 1, W>(x);
+            row_done<Use, 1, W>(u, r0 + t[p], __shfl(dst_l, t[p], 64), len[p], x, lane);
         }
     }
-    bitonic_sort<64, 1, 64>(x, lane);
-    row_done<Use, 1, 64>(u, r, dst, len, x, lane);
 }
 
 // Workgroups below `queue_blocks` take the rows of 65 to 1024 entries from the queues, one wave a row; the
-// others take RS_ROWS consecutive rows per wave and sort the short ones among them: two rows of at most 32
-// entries side by side in the halves of the wave, four such pairs in flight, then the rows of 33 to 64.
+// others take RS_ROWS consecutive rows per wave and sort the short ones among them: rows of at most 16 entries four at
+// a time, of at most 32 two at a time, then those of 33 to 64; four sets in flight.
 template <class Use>
-__global__ __launch_bounds__(256) void row_sort_kernel(Use u, RowQueues q, int queue_blocks)
+__global__ __launch_bounds__(256, 6) void row_sort_kernel(Use u, RowQueues q, int queue_blocks)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (static_cast<int>(blockIdx.x) < queue_blocks) {
@@ -287,57 +358,10 @@ __global__ __launch_bounds__(256) void row_sort_kernel(Use u, RowQueues q, int q
             if (len_l == 0) u.out[r_l] = u.map[r_l];  // a row without entries keeps its label
         }
     }
-    const int half = lane >> 5, li = lane & 31;
-    constexpr int PAIRS = 4;
-    for (int p0 = 0; p0 < RS_ROWS / 2; p0 += PAIRS) {
-        int v[PAIRS], len[PAIRS], c[PAIRS];
-#pragma unroll
-        for (int p = 0; p < PAIRS; ++p) {
-            const int t = (p0 + p) * 2 + half;
-            const int st = __shfl(start_l, t, 64);
-            const int ln = __shfl(len_l, t, 64);
-            len[p] = ln <= 32 ? ln : 0;
-            c[p] = li < len[p] ? __builtin_nontemporal_load(u.col_idx + st + li) : -1;
-        }
-#pragma unroll
-        for (int p = 0; p < PAIRS; ++p) v[p] = li < len[p] ? u.value(c[p]) : RS_NONE;
-#pragma unroll
-        for (int p = 0; p < PAIRS; ++p) {
-            const int t = (p0 + p) * 2 + half;
-            if constexpr (Use::VOTES) {
-                const int la = __builtin_amdgcn_readlane(len[p], 0), lb = __builtin_amdgcn_readlane(len[p], 32);
-                const int a0 = __builtin_amdgcn_readlane(v[p], 0), a1 = __builtin_amdgcn_readlane(v[p], 7);
-                const int b0 = __builtin_amdgcn_readlane(v[p], 32), b1 = __builtin_amdgcn_readlane(v[p], 39);
-                const bool in = li < len[p];
-                const unsigned long long e0 = __builtin_amdgcn_ballot_w64(in && v[p] == (half ? b0 : a0));
-                const unsigned long long e1 = __builtin_amdgcn_ballot_w64(in && v[p] == (half ? b1 : a1));
-                const int wa = majority_of(e0 & 0xffffffffull, e1 & 0xffffffffull, a0, a1, la);
-                const int wb = majority_of(e0 >> 32, e1 >> 32, b0, b1, lb);
-                if ((la == 0 || wa >= 0) && (lb == 0 || wb >= 0)) {  // uniform
-                    if (li == 0 && len[p] > 0) u.out[static_cast<int>(r0) + t] = half ? wb : wa;
-                    continue;
-                }
-            }
-            int x[1] = {v[p]};
-            bitonic_sort<32, 1, 32>(x, li);
-            row_done<Use, 1, 32>(u, static_cast<int>(r0) + t, __shfl(dst_l, t, 64), len[p], x, lane);
-        }
-    }
-    unsigned long long rest = __builtin_amdgcn_ballot_w64(len_l > 32 && len_l <= RS_SHORT);
-    while (rest) {  // two rows in flight
-        const int t0 = __ffsll(static_cast<long long>(rest)) - 1;
-        rest &= rest - 1;
-        const int t1 = rest ? __ffsll(static_cast<long long>(rest)) - 1 : -1;
-        if (rest) rest &= rest - 1;
-        const int st0 = __builtin_amdgcn_readlane(start_l, t0), ln0 = __builtin_amdgcn_readlane(len_l, t0);
-        const int st1 = t1 >= 0 ? __builtin_amdgcn_readlane(start_l, t1) : 0, ln1 = t1 >= 0 ? __builtin_amdgcn_readlane(len_l, t1) : 0;
-        const int c0 = lane < ln0 ? __builtin_nontemporal_load(u.col_idx + st0 + lane) : -1;
-        const int c1 = lane < ln1 ? __builtin_nontemporal_load(u.col_idx + st1 + lane) : -1;
-        int x0[1] = {lane < ln0 ? u.value(c0) : RS_NONE};
-        int x1[1] = {lane < ln1 ? u.value(c1) : RS_NONE};
-        wave_row(u, static_cast<int>(r0) + t0, __builtin_amdgcn_readlane(dst_l, t0), ln0, x0, lane);
-        if (t1 >= 0) wave_row(u, static_cast<int>(r0) + t1, __builtin_amdgcn_readlane(dst_l, t1), ln1, x1, lane);
-    }
+    __shared__ int order[4][RS_ROWS];
+    short_rows<Use, 16, 4>(u, static_cast<int>(r0), 0, start_l, len_l, dst_l, lane, order[wave]);
+    short_rows<Use, 32, 4>(u, static_cast<int>(r0), 16, start_l, len_l, dst_l, lane, order[wave]);
+    short_rows<Use, 64, 4>(u, static_cast<int>(r0), 32, start_l, len_l, dst_l, lane, order[wave]);
 }
 
 // ---- rows above 1024 entries: a workgroup of 1024 threads ------------------------------------------------
@@ -405,7 +429,7 @@ __device__ __forceinline__ void group_row(const Use &u, int r, int start, int le
     const int flip0 = (base & SHARE) ? -1 : 0;
 #pragma unroll
     for (int k = 0; k < K; ++k) v[k] ^= flip0;
-    bitonic_sort<SHARE, K, 64>(v, lane);
+    bitonic_sort<SHARE, K, 64>(v);
 #pragma unroll
     for (int k = 0; k < K; ++k) v[k] ^= flip0;
     __syncthreads();  // the row before is done with s
@@ -428,7 +452,7 @@ __device__ __forceinline__ void group_row(const Use &u, int r, int start, int le
         const int flip = up ? 0 : -1;
 #pragma unroll
         for (int k = 0; k < K; ++k) v[k] ^= flip;
-        bitonic_stage<SHARE / 2, SHARE, K, 64>(v, lane);
+        bitonic_stage<SHARE / 2, SHARE, K, 64>(v);
 #pragma unroll
         for (int k = 0; k < K; ++k) v[k] ^= flip;
     }
