@@ -14,18 +14,23 @@ namespace ftc {
 //              index runs in steps of 4 V in an order of its own, the same for A and B;
 //   B operand  W is staged in LDS as fp32 in chunks of KC rows, four consecutive k of a column side by side: lane l
 //              reads W[k .. k + 3][n0 + l%16] as one 16-byte word.
-// Bound by reading X up to about 32 output columns and by the fp32 matrix rate (157 TFLOP/s) beyond.  SK = 4: for matrices
-// of few rows the four waves of a workgroup share one row tile and split every chunk's k between them (the partial
+// Bound by reading X up to about 32 output columns and by the fp32 matrix rate (157 TFLOP/s) beyond.  SK = 4 or 16: for matrices
+// of few rows the waves of a workgroup share one row tile and split every chunk's k between them (the partial
 // sums are added in wave order through LDS): 2708 rows would otherwise occupy 43 workgroups.
 // One tile per wave, 32 KB of W: two tiles per wave were 10 % slower, 64 KB up to 20 %, 16 KB 5 %.
 // Measured, vector units (X staged element by element in LDS, or one row per thread) against this:
-//   fp32 100 000 x 1433 -> 16: 925 / 145 us (4.0 TB/s); fp32 100 000 x 300 -> 128: 315 / 128 us (60 TFLOP/s);
-//   fp32 400 000 x 128 -> 32: 425 / 62 us; fp16 2708 x 1433 -> 16: 311 / 14 us.
+//   fp32 100 000 x 1433 -> 16: 925 / 145 us (4.0 TB/s); fp32 100 000 x 300 -> 128: 315 / 110 us (70 TFLOP/s);
+//   fp32 400 000 x 128 -> 32: 425 / 62 us; fp16 2708 x 1433 -> 16: 311 / 10 us.
 // Error against 64 bits (2-norm, fp32 1433 -> 16): 6.8e-7 / 4.8e-7.
 typedef float float4v __attribute__((ext_vector_type(4)));
 
 // Up to this many rows the waves split the contraction (256 workgroups of 64 rows would be the most without).
 constexpr int GEMM_SPLIT_ROWS = 16384;
+// Few rows and a long contraction are split over 16 waves instead of 4: a workgroup is a chain of chunks (stage W, wait, load X,
+// multiply), which a quarter of the chunks is a quarter of.  us, 4 / 16 waves: fp16 2708 x 1433 -> 16 14.2 / 9.8, -> 32 22.1 / 14.8, bf16
+// 2708 x 3703 -> 32 53 / 33, fp32 8000 x 1433 -> 64 52 / 45, 2708 x 500 -> 32 9.0 / 8.8; but 8000 x 300 -> 32 9.0 / 9.4, 16 000 x 1433 -> 32 46 / 55.
+// The chunk of 16 waves has to fit into LDS: up to 64 columns in fp32, 32 in 16 bits.
+constexpr int GEMM_SPLIT16_ROWS = 8192, GEMM_SPLIT16_IN = 512;
 
 // V elements at element index idx; only the alignment of one element is assumed (global loads need no more)
 template <class T>
@@ -53,14 +58,15 @@ __device__ __forceinline__ float load_one(const void *base, int64_t idx)
 }
 
 template <class T, int NT, int SK>
-__global__ __launch_bounds__(256) void gemm_any_kernel(int n, const void *__restrict__ X, int ldx, int d_in,
+__global__ __launch_bounds__(SK == 16 ? 1024 : 256) void gemm_any_kernel(int n, const void *__restrict__ X, int ldx, int d_in,
                                                        const void *__restrict__ W, int w_ld, void *__restrict__ Z, int ldz,
                                                        int zdt, Epi epi)
 {
     constexpr int V = T::VEC, STEP = 4 * V;  // contraction indices per step of a wave
     constexpr int KC = 512 / NT > SK * STEP ? 512 / NT : SK * STEP, COLS = 16 * NT, U = 4;
+    constexpr int TH = SK == 16 ? 1024 : 256;  // threads
     static_assert(KC % (SK * STEP) == 0, "every wave takes whole steps of a chunk");
-    static_assert(SK == 1 || KC >= 4 * 16, "the partial tiles fit the staging memory");
+    static_assert(SK == 1 || KC >= SK * 16, "the partial tiles fit the staging memory");
     __shared__ __attribute__((aligned(16))) float Ws[KC * COLS];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int m = lane & 15, kb = lane >> 4;
@@ -88,18 +94,18 @@ __global__ __launch_bounds__(256) void gemm_any_kernel(int n, const void *__rest
     for (int kc0 = 0; kc0 < d_in; kc0 += KC) {  // uniform
         if (kc0 > 0) __syncthreads();           // the previous chunk has been consumed
         const int kn = min(KC, (d_in - kc0 + STEP - 1) / STEP * STEP);
-        for (int t0 = tid; t0 < kn * COLS; t0 += 256 * 8) {  // eight loads in flight, unconditional, from clamped addresses
+        for (int t0 = tid; t0 < kn * COLS; t0 += TH * 8) {  // eight loads in flight, unconditional, from clamped addresses
             float w[8];
             bool ok[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                const int k = (t0 + j * 256) / COLS, o = (t0 + j * 256) % COLS;
+                const int k = (t0 + j * TH) / COLS, o = (t0 + j * TH) % COLS;
                 ok[j] = k < kn && kc0 + k < d_in && o < cols;
                 w[j] = load_one<T>(W, ok[j] ? static_cast<int64_t>(kc0 + k) * w_ld + col0 + o : 0);
             }
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                const int k = (t0 + j * 256) / COLS, o = (t0 + j * 256) % COLS;
+                const int k = (t0 + j * TH) / COLS, o = (t0 + j * TH) % COLS;
                 if (k < kn) Ws[((k >> 2) * COLS + o) * 4 + (k & 3)] = ok[j] ? w[j] : 0.f;
             }
         }
@@ -148,7 +154,7 @@ __global__ __launch_bounds__(256) void gemm_any_kernel(int n, const void *__rest
 #pragma unroll
             for (int i = 0; i < 4; ++i) Ws[(wave * 16 + kb * 4 + i) * COLS + nt * 16 + m] = sum[nt][i];
         __syncthreads();
-        for (int t = tid; t < 16 * COLS; t += 256) {
+        for (int t = tid; t < 16 * COLS; t += TH) {
             const int64_t row = row0 + t / COLS;
             const int o = t % COLS;
             if (row < n && o < cols) {
@@ -208,17 +214,25 @@ static void gemm_any_t(int n, const void *X, int ldx, int d_in, const void *W, i
 {
     const bool split = n <= GEMM_SPLIT_ROWS;
     const int64_t per = split ? 16 : 64;
-    const int nt = d_out <= 16 ? 1 : d_out <= 32 ? 2 : d_out <= 64 ? 4 : 8;
+    // 64 columns a workgroup at most: with 128 the accumulators leave half as many workgroups to the chip, the last ones alone
+    // (fp32 100 000 x 300 -> 128 118 / 110 us, 400 000 x 64 -> 128 147 / 119, 20 000 x 300 -> 100 39 / 30)
+    const int nt = d_out <= 16 ? 1 : d_out <= 32 ? 2 : d_out <= 64 || !split ? 4 : 8;
+    const bool split16 = n <= GEMM_SPLIT16_ROWS && d_in >= GEMM_SPLIT16_IN && nt <= (T::BYTES == 4 ? 4 : 2);
     const dim3 grid(static_cast<unsigned>((n + per - 1) / per), static_cast<unsigned>((d_out + nt * 16 - 1) / (nt * 16)));
-#define FTC_GA(N)                                                                                                        \
-    if (nt == N) {                                                                                                       \
-        if (split) hipLaunchKernelGGL((gemm_any_kernel<T, N, 4>), grid, dim3(256), 0, s, n, X, ldx, d_in, W, d_out, Z,   \
-                                      ldz, zdt, epi);                                                                    \
-        else hipLaunchKernelGGL((gemm_any_kernel<T, N, 1>), grid, dim3(256), 0, s, n, X, ldx, d_in, W, d_out, Z, ldz,    \
-                                zdt, epi);                                                                               \
+#define FTC_GA1(N, SK, TH)                                                                                                   \
+    hipLaunchKernelGGL((gemm_any_kernel<T, N, SK>), grid, dim3(TH), 0, s, n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi)
+#define FTC_GA(N)                                       \
+    if (nt == N) {                                      \
+        if constexpr (N <= (T::BYTES == 4 ? 4 : 2)) {   \
+            if (split16) FTC_GA1(N, 16, 1024);          \
+            else if (split) FTC_GA1(N, 4, 256);         \
+            else FTC_GA1(N, 1, 256);                    \
+        } else if (split) FTC_GA1(N, 4, 256);           \
+        else if constexpr (N <= 4) FTC_GA1(N, 1, 256);  \
     }
     FTC_GA(1) FTC_GA(2) FTC_GA(4) FTC_GA(8)
 #undef FTC_GA
+#undef FTC_GA1
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -494,7 +508,7 @@ int32_t launch_gemm(int n, const void *X, int ldx, int dt, int d_in, const void 
                                                  : gemm_mfma_t<BF16>(n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi, s));
         if (done) return launch_status("update_gemm mfma");
         // beyond the register-resident shapes, or a width that is no multiple of 8 in padded rows; few rows are left to the
-        // general kernel, which splits the contraction over the waves (2708 x 1432 -> 16: 44 us here, 14 us there;
+        // general kernel, which splits the contraction over the waves (2708 x 1432 -> 16: 44 us here, 10 us there;
         // 100 000 rows: 93 us here, 115 us there)
         if ((d_in > 256 || d_out > 64 || !fast) && n > GEMM_SPLIT_ROWS) {
             if (dt == FTC_F16) gemm_mfma_wide_t<F16>(n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi, s);
