@@ -447,26 +447,15 @@ __global__ __launch_bounds__(256) void agnn_backward_fixup_kernel(int n, int n_r
         longs &= longs - 1;
         const int v = __shfl(v_mine, src, 64), r = __shfl(rec.x, src, 64);
         const int last = (row_ptr[r + 1] - 1) / seg_r;  // range holding the row's final entry
-        // teams of DL lanes (one per slot) share the row's ranges round-robin, four loads in flight each; their sums are added in
-        // team order: fixed by the shape alone
+        // teams of DL lanes (one per slot) share the row's ranges round-robin; their sums are added in team order: fixed by the
+        // shape alone
         constexpr int DL = DP2 < 64 ? DP2 : 64, PARTS = 64 / DL, STEPS = DP2 / DL;
         const int part = lane / DL;
         float sum[STEPS];
 #pragma unroll
         for (int st = 0; st < STEPS; ++st) {
             const int d = st * 64 + lane % DL;
-            const float *from = carry + d;
-            float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-            int u = v + 1 + part;
-            for (; u + 3 * PARTS <= last; u += 4 * PARTS) {
-                const float a0 = from[(static_cast<size_t>(u) * 2) * DP2];
-                const float a1 = from[(static_cast<size_t>(u + PARTS) * 2) * DP2];
-                const float a2 = from[(static_cast<size_t>(u + 2 * PARTS) * 2) * DP2];
-                const float a3 = from[(static_cast<size_t>(u + 3 * PARTS) * 2) * DP2];
-                s0 += a0; s1 += a1; s2 += a2; s3 += a3;
-            }
-            for (; u <= last; u += PARTS) s0 += from[(static_cast<size_t>(u) * 2) * DP2];
-            float s = (s0 + s1) + (s2 + s3);
+            float s = sum_pieces(carry + d, 2 * static_cast<size_t>(DP2), v + 1 + part, last, PARTS);
             for (int off = 32; off >= DL; off >>= 1) s += __shfl_down(s, off, 64);
             sum[st] = s + carry[(static_cast<size_t>(v) * 2 + 1) * DP2 + d];  // meant for the lanes below DL
         }

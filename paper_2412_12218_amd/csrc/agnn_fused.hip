@@ -356,8 +356,8 @@ __global__ __launch_bounds__(256) void agnn_fused_fixup_kernel(int n, int n_rang
         const int v = __shfl(v_mine, src, 64), r = __shfl(rec.x, src, 64);
         {
             const int last = (row_ptr[r + 1] - 1) / seg_r;
-            // teams of `dl` lanes (one lane per feature) share the ranges of a long row round-robin,
-            // four loads in flight each; team sums are added in team order (fixed by the shape)
+            // teams of `dl` lanes (one lane per feature) share the ranges of a long row round-robin;
+            // team sums are added in team order (fixed by the shape)
             int dl = 1;
             while (dl < D && dl < 64) dl <<= 1;
             const int parts = 64 / dl;
@@ -365,16 +365,7 @@ __global__ __launch_bounds__(256) void agnn_fused_fixup_kernel(int n, int n_rang
             // denominator: every lane adds all pieces
             float zsum;
             {
-                float z0 = 0.f, z1 = 0.f, z2 = 0.f, z3 = 0.f;
-                int u = v + 1 + part;
-                for (; u + 3 * parts <= last; u += 4 * parts) {
-                    z0 += carry[(static_cast<size_t>(u) * 2) * DPZ + DP];
-                    z1 += carry[(static_cast<size_t>(u + parts) * 2) * DPZ + DP];
-                    z2 += carry[(static_cast<size_t>(u + 2 * parts) * 2) * DPZ + DP];
-                    z3 += carry[(static_cast<size_t>(u + 3 * parts) * 2) * DPZ + DP];
-                }
-                for (; u <= last; u += parts) z0 += carry[(static_cast<size_t>(u) * 2) * DPZ + DP];
-                zsum = (z0 + z1) + (z2 + z3);
+                zsum = sum_pieces(carry + DP, 2 * static_cast<size_t>(DPZ), v + 1 + part, last, parts);
                 for (int off = 32; off >= dl; off >>= 1) zsum += __shfl_down(zsum, off, 64);
                 zsum = __shfl(zsum, 0, 64) + carry[(static_cast<size_t>(v) * 2 + 1) * DPZ + DP];
                 if (row_z && lane == 0) row_z[r] = zsum;
@@ -383,17 +374,7 @@ __global__ __launch_bounds__(256) void agnn_fused_fixup_kernel(int n, int n_rang
                 const int d = d0 + lane % dl;
                 const bool dok = d < D;
                 const float *base = carry + (dok ? d : 0);
-                float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-                int u = v + 1 + part;
-                for (; u + 3 * parts <= last; u += 4 * parts) {
-                    const float a0 = base[(static_cast<size_t>(u) * 2) * DPZ];
-                    const float a1 = base[(static_cast<size_t>(u + parts) * 2) * DPZ];
-                    const float a2 = base[(static_cast<size_t>(u + 2 * parts) * 2) * DPZ];
-                    const float a3 = base[(static_cast<size_t>(u + 3 * parts) * 2) * DPZ];
-                    s0 += a0; s1 += a1; s2 += a2; s3 += a3;
-                }
-                for (; u <= last; u += parts) s0 += base[(static_cast<size_t>(u) * 2) * DPZ];
-                float sum = (s0 + s1) + (s2 + s3);
+                float sum = sum_pieces(base, 2 * static_cast<size_t>(DPZ), v + 1 + part, last, parts);
                 for (int off = 32; off >= dl; off >>= 1) sum += __shfl_down(sum, off, 64);
                 if (lane < dl && dok) {
                     sum += carry[(static_cast<size_t>(v) * 2 + 1) * DPZ + d];

@@ -329,7 +329,7 @@ __global__ __launch_bounds__(256) void spmm_seg_fixup_kernel(int n, int n_ranges
         const int last = (row_ptr[r + 1] - 1) / seg_r;  // wave range holding the row's final edge
         // A hub row can span hundreds of ranges.  The 64 lanes are split into `parts` teams of
         // `dl` lanes (one lane per feature); team p adds the head pieces of ranges v+1+p,
-        // v+1+p+parts, ... four at a time, then the teams' sums are added in team order.  The
+        // v+1+p+parts, ..., then the teams' sums are added in team order.  The
         // order is fixed by the shape alone, so the result is reproducible.
         int dl = 1;
         while (dl < D && dl < 64) dl <<= 1;
@@ -339,17 +339,7 @@ __global__ __launch_bounds__(256) void spmm_seg_fixup_kernel(int n, int n_ranges
             const int d = d0 + lane % dl;
             const bool dok = d < D;
             const float *base = carry + (dok ? d : 0);
-            float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-            int u = v + 1 + part;
-            for (; u + 3 * parts <= last; u += 4 * parts) {
-                const float a0 = base[(static_cast<size_t>(u) * 2) * DP];
-                const float a1 = base[(static_cast<size_t>(u + parts) * 2) * DP];
-                const float a2 = base[(static_cast<size_t>(u + 2 * parts) * 2) * DP];
-                const float a3 = base[(static_cast<size_t>(u + 3 * parts) * 2) * DP];
-                s0 += a0; s1 += a1; s2 += a2; s3 += a3;
-            }
-            for (; u <= last; u += parts) s0 += base[(static_cast<size_t>(u) * 2) * DP];
-            float sum = (s0 + s1) + (s2 + s3);
+            float sum = sum_pieces(base, 2 * static_cast<size_t>(DP), v + 1 + part, last, parts);
             for (int off = 32; off >= dl; off >>= 1) sum += __shfl_down(sum, off, 64);
             if (lane < dl && dok) {
                 sum += carry[(static_cast<size_t>(v) * 2 + 1) * DP + d];
