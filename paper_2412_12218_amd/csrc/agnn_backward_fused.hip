@@ -7,7 +7,7 @@
 // e = (i, j), c_T(e) = c_e and a_T(e) = a_e:
 //     dp_e = <dY_i, h_j>                 ds_e    = p_e (dp_e - t_i)
 //     p_T(e) = a_e / z_j                 ds_T(e) = p_T(e) (<h_i, dY_j> - t_j)
-//     dbeta = sum_e ds_e c_e = sum_e ds_e (c_e - 1/2)
+//     dbeta = sum_e ds_e c_e = sum_e ds_e (c_e - m_i)   for any m_i of the row, its ds add up to zero
 //     q_i   = beta sum_e (ds_e + ds_T(e)) hn_j        (gradient w.r.t. the normalised row hn_i)
 //     agg_i = sum_e p_T(e) dY_j                       (through the aggregated rows)
 //     dH_i  = agg_i + (q_i - hn_i <hn_i, q_i>) / |h_i|
@@ -47,6 +47,22 @@ struct GradOut {
 #pragma unroll
             for (int j = 0; j < NV; ++j) store_elem(dH, row * ld + k + j, dt, o[j]);
         }
+    }
+};
+
+// m_i of dbeta = sum ds_e (c_e - m_i): the nearer to the mean of the row's cosines, the less of what z_i and t_i are off by gets into dbeta
+// (t_i's error times mean c - m_i).  log(z_i / length) is beta mean c - |beta| to first order, whatever the signs and norms of the features.
+// slope = 1 / (beta log2(e)), shift = the sign of beta; where beta is too small for the quotient both are 0, and so is m_i.
+// Standard deviation of dbeta's error with m_i = 0, 1/2 and this, 2000 rows of 64 neighbours, D = 32, Y in fp16, beta = 1: signed
+// features 2.9e-4 / 3.3e-3 / 1.2e-4, behind a ReLU 7.0e-3 / 3.3e-3 / 1.7e-4; the sweep takes 1 % longer than with a constant.
+struct CosineMean {
+    float slope, shift;
+    explicit CosineMean(float beta)
+        : slope(fabsf(beta) < 1e-4f ? 0.f : 0.693147181f / beta), shift(fabsf(beta) < 1e-4f ? 0.f : beta < 0.f ? -1.f : 1.f) {}
+    __device__ __forceinline__ float operator()(float inv_z, int length) const
+    {
+        const float m = fmaf(-__builtin_amdgcn_logf(inv_z * static_cast<float>(length)), slope, shift);
+        return slope == 0.f ? 0.f : fminf(fmaxf(m, -1.f), 1.f);
     }
 };
 __device__ __forceinline__ bool poisoned(const int32_t *flag) { return flag && *flag != 0; }
@@ -137,8 +153,8 @@ __global__ __launch_bounds__(256) void agnn_row_stats_kernel(int n, const void *
 template <class T, int VEC, int LPR, int R, bool BIG>
 __global__ __launch_bounds__(256, 3) void agnn_backward_fused_kernel(
     int nnz, int n_ranges, const int *__restrict__ row_ptr, const int *__restrict__ col_idx, const int *__restrict__ edge_to_row,
-    const void *__restrict__ HD, int D, float beta, const float2 *__restrict__ stats, GradOut grad,
-    float *__restrict__ carry, int *__restrict__ carry_tail_row, float *__restrict__ dbeta_part)
+    const void *__restrict__ HD, int D, float beta, const float2 *__restrict__ stats, CosineMean row_mean,
+    GradOut grad, float *__restrict__ carry, int *__restrict__ carry_tail_row, float *__restrict__ dbeta_part)
 {
     using E = EdgeRange<LPR, R>;
     constexpr int NG = E::NG, RUN = E::RUN;
@@ -181,8 +197,9 @@ __global__ __launch_bounds__(256, 3) void agnn_backward_fused_kernel(
     zero_raw(xi);
     zero_raw(dxi);
     zero_raw(xc);
-    float ri = 0.f, dbeta_acc = 0.f;
-    float2 si = make_float2(0.f, 0.f);
+    // of the row of this lane's entry: 1 / |h_i|, the pair (1 / z_i, t_i), the mean of the cosines
+    float ri_mine = 0.f, mi_mine = 0.f, dbeta_acc = 0.f;
+    float2 si_mine = make_float2(0.f, 0.f);
     bool head_closed = false, first = true;
     int head_row = -1, cur = -1;
     const int first_row = s_row[at];
@@ -227,27 +244,38 @@ __global__ __launch_bounds__(256, 3) void agnn_backward_fused_kernel(
         }
         RawVec<T, VEC> xs, dxs;
         float2 ss;
+        int s0, s1;
         if (begins != -2) {
             load_h(begins, xs);
             load_d(begins, dxs);
             ss = stats[max(begins, 0)];
+            s0 = row_ptr[max(begins, 0)];
+            s1 = row_ptr[max(begins, 0) + 1];
         }
-        float ri_mine = ri, hh[BW_B], squares[BW_B], dp[BW_B], dpt[BW_B];  // *_mine: of the row of this lane's entry
-        float2 si_mine = si;
+        float hh[BW_B], squares[BW_B], dp[BW_B], dpt[BW_B];
+        ri_mine = quad_lane<3>(ri_mine);  // until a row begins: those of the batch's last entry before
+        mi_mine = quad_lane<3>(mi_mine);
+        si_mine = make_float2(quad_lane<3>(si_mine.x), quad_lane<3>(si_mine.y));
 #pragma unroll
         for (int k = 0; k < BW_B; ++k) {
             if (need[k]) {
+                float2 si;
+                int length;
                 if (r[k] == begins) {
                     xi = xs;
                     dxi = dxs;
                     si = ss;
+                    length = s1 - s0;
                 } else {
                     load_h(r[k], xi);
                     load_d(r[k], dxi);
                     si = stats[max(r[k], 0)];
+                    length = row_ptr[max(r[k], 0) + 1] - row_ptr[max(r[k], 0)];
                 }
-                ri = __frsqrt_rn(fmaxf(group_sum_dpp<LPR>(dot_raw<T, VEC>(xi, xi, 0.f)), 1e-24f));  // 1 / max(|h_i|, 1e-12)
+                const float ri = __frsqrt_rn(fmaxf(group_sum_dpp<LPR>(dot_raw<T, VEC>(xi, xi, 0.f)), 1e-24f));  // 1 / max(|h_i|, 1e-12)
+                const float mi = row_mean(si.x, length);
                 ri_mine = quad >= k ? ri : ri_mine;
+                mi_mine = quad >= k ? mi : mi_mine;
                 si_mine.x = quad >= k ? si.x : si_mine.x;
                 si_mine.y = quad >= k ? si.y : si_mine.y;
             }
@@ -263,9 +291,8 @@ __global__ __launch_bounds__(256, 3) void agnn_backward_fused_kernel(
         const float pt = a * sj.x;
         const float dst = pt * (group_sum4<LPR>(dpt, odd, upper) - sj.y);
         const float coef = beta * (ds + dst) * rj;
-        // The ds of a row add up to zero, so a constant may be taken from its cosines: what z_i and t_i are off by then enters
-        // with their mean less 1/2 instead of their mean, which lies between 1/3 and 1 for the non-negative rows behind a ReLU.
-        if (r_mine >= 0 && sub < 4) dbeta_acc = fmaf(ds, cs - 0.5f, dbeta_acc);
+        // What z_i and t_i are off by enters with what is left of the mean of the row's cosines, not with all of it
+        if (r_mine >= 0 && sub < 4) dbeta_acc = fmaf(ds, cs - mi_mine, dbeta_acc);
         const float c4[BW_B] = {quad_lane<0>(coef), quad_lane<1>(coef), quad_lane<2>(coef), quad_lane<3>(coef)};
         const float p4[BW_B] = {quad_lane<0>(pt), quad_lane<1>(pt), quad_lane<2>(pt), quad_lane<3>(pt)};
 #pragma unroll
@@ -534,7 +561,7 @@ static void launch_bw_t(int vec, int lpr, unsigned grid, hipStream_t s, int nnz,
     constexpr int VM = T::VEC;
 #define FTC_BW(V, L)                                                                                                \
     hipLaunchKernelGGL((agnn_backward_fused_kernel<T, V, L, R, BIG>), dim3(grid), dim3(256), 0, s, nnz, n_ranges,   \
-                       g.row_ptr, g.col_idx, e2r, HD, D, beta, stats, grad, carry, tail_row, dbeta_part)
+                       g.row_ptr, g.col_idx, e2r, HD, D, beta, stats, CosineMean(beta), grad, carry, tail_row, dbeta_part)
     if (vec == VM) {
         if (lpr == 4) FTC_BW(VM, 4);
         else if (lpr == 8) FTC_BW(VM, 8);

@@ -175,6 +175,45 @@ def test_single_pass_backward_writes_complete_gradients(dtype, D, pad):
     assert abs(float(db) - float(dbeta)) <= 1e-6 * g.nnz
 
 
+def ring(n, hops):
+    """Every node with its 2 * hops neighbours at the given distances: a symmetric pattern, ascending rows."""
+    rng = np.random.default_rng(hops)
+    d = rng.choice(np.arange(1, n // 2), size=hops, replace=False)
+    cols = np.sort((np.arange(n)[:, None] + np.concatenate([d, n - d])[None]) % n, axis=1)
+    return B.Graph.from_numpy((np.arange(n + 1) * 2 * hops).astype(np.int32), cols.reshape(-1).astype(np.int32))
+
+
+@pytest.mark.parametrize("features", ["signed", "behind a ReLU"])
+@pytest.mark.parametrize("beta", [1.0, -1.0, 3.0, 1e-6])
+@pytest.mark.parametrize("ydt", [F32, F16, BF16])
+@pytest.mark.parametrize("dtype,D,hops", [(F32, 32, 32), (F16, 32, 16), (F32, 128, 32)])
+def test_dbeta_is_as_exact_as_the_plain_sum(dtype, D, hops, ydt, beta, features):
+    """dbeta = sum of ds_e c_e.  What a rounded Y puts t_i = <dY_i, Y_i> off by, d_i, enters with what is left of the row's mean
+    cosine c_i: no more than four standard deviations of independent errors d_i c_i, the plain sum's, and the roundings of the
+    entries in fp32 (of about twenty operations each, 2^-24 every one, independent of one another)."""
+    n = 2003
+    g = ring(n, hops)
+    gen = torch.Generator(device="cuda").manual_seed(D + hops)
+    H = torch.randn((n, D), generator=gen, device="cuda")
+    H = (torch.relu(H) if features != "signed" else H).to(dtype)
+    dY = torch.randn((n, D), generator=gen, device="cuda").to(dtype)
+    rows, cols = rows_of(g), g.col_idx.long()
+    p, z, Y, _ = attention(g, H, beta)
+    Hn = H.double() / H.double().norm(dim=1, keepdim=True)
+    c = (Hn[rows] * Hn[cols]).sum(1)
+    t = (dY.double() * Y).sum(1)
+    ds = p * ((dY.double()[rows] * H.double()[cols]).sum(1) - t[rows])
+    Yq = Y.to(ydt)
+    off = (dY.double() * Yq.double()).sum(1) - t
+    mean = torch.zeros(n, dtype=torch.float64, device="cuda").index_add_(0, rows, p * c)
+    bar = 4 * float((off * mean).norm()) + 20 * 2.0 ** -24 * 4 * float((ds * c).norm())
+    win = B.ftc_build_windows(g)
+    _, db = B.ftc_agnn_layer_backward_fused(g, win, H, z.float(), Yq, dY, beta=beta)
+    err = abs(float(db) - float((ds * c).sum()))
+    print(f"dbeta {dtype} D={D} {2 * hops} neighbours Y {ydt} beta {beta} {features}: error {err:.2e}, bar {bar:.2e}", flush=True)
+    assert err <= bar
+
+
 def test_single_pass_backward_of_more_than_4_gib():
     """Copies of one graph side by side, 4.3 M nodes with rows of 1 KiB in the workspace: every copy has the gradients of the one."""
     n, copies, D = 43_000, 100, 128
