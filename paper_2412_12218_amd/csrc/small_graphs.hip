@@ -3,9 +3,9 @@
 // Bound by latency: launch, row start, column ids, gathered rows, store, each a dependent step of about a microsecond.  The
 // edge-balanced kernels take two launches (the second one for rows cut by a range boundary) and a chain of their own in each; here rows
 // are not cut.  A row belongs to 16 lanes (more where one row of the matrix takes more): S groups of LPR lanes take every S-th
-// entry, several gathers in flight, and their sums are added in the wave.  Rows of more than LONG entries are put aside and
-// summed by the whole workgroup, so that the hubs of a small power-law graph do not hold up the rest; a workgroup's rows lie gridDim.x apart
-// (the long rows of an R-MAT graph lie side by side).  No scratch memory, no float atomics: reproducible bit for bit.
+// entry, several gathers in flight, and their sums are added in the wave.  Rows of more than SHORT entries are put aside and
+// summed by the whole workgroup, so that the hubs of a small power-law graph do not hold up the rest; a workgroup's rows lie gridDim.x apart,
+// a prime number (the long rows of an R-MAT graph lie side by side).  No scratch memory, no float atomics: reproducible bit for bit.
 #include "edge_ranges.hpp"
 
 namespace ftc {
@@ -97,7 +97,8 @@ __device__ __forceinline__ void small_rows(int n, const int *__restrict__ row_pt
     }
 }
 
-// D <= LPR * VEC; rows of X are 16-byte aligned (or whole pieces of narrower lanes) and at least LPR * VEC elements long where D is no
+// blockIdx.y: the columns, LPR * VEC at a time, so that a long row is shared by as many workgroups as its width allows.
+// D <= gridDim.y * LPR * VEC; rows of X are 16-byte aligned (or whole pieces of narrower lanes) and at least LPR * VEC elements long where D is no
 // multiple of VEC.
 template <class T, int VEC, int LPR>
 __global__ __launch_bounds__(SG_NT) void spmm_group_kernel(int n, const int *__restrict__ row_ptr, const int *__restrict__ col_idx,
@@ -105,7 +106,7 @@ __global__ __launch_bounds__(SG_NT) void spmm_group_kernel(int n, const int *__r
                                                            uint32_t ldb, int D, void *__restrict__ out, int ldo, int odt, Epi epi,
                                                            bool out_vec)
 {
-    const int sub = threadIdx.x % LPR;
+    const int sub = blockIdx.y * LPR + threadIdx.x % LPR;  // the lane's piece of a row
     const bool live = sub * VEC < D;
     const int col0 = live ? sub * VEC : 0;  // lanes beyond the row gather its first piece and store nothing
     const uint32_t lane_bytes = static_cast<uint32_t>(col0) * T::BYTES;
@@ -231,29 +232,53 @@ __global__ __launch_bounds__(SG_NT) void agnn_group_kernel(int n, const int *__r
 
 bool seg_shape(int dtype, int D, int *vec, int *lpr);
 
-// Up to which graphs: where the edge-balanced kernels draw level on the graphs that suit them least and these most, R-MAT.  us, edge-balanced / here
-// (8 to 9 us are what a launch takes from Python):
-//   SpMM, entries         9 thousand   40 th., R-MAT   80 th., R-MAT   150 th., power law   300 th., R-MAT   600 th., power law / uniform
-//   fp16, 8 columns       12.0 / 9.1   12.3 / 9.2      13.9 / 9.1      12.2 / 9.1           15.4 / 11.2      13.4 / 11.7   12.1 / 9.3
-//   fp16, 32 columns      12.1 / 9.0   12.2 / 9.2      12.4 / 9.3      12.3 / 9.2           13.2 / 19.4      14.1 / 19.7   12.2 / 11.5
-//   bf16, 64 columns      12.2 / 9.1   13.5 / 10.2     13.4 / 13.6     12.3 / 11.9          15.1 / 25.1      16.8 / 25.9   15.6 / 17.8
-//   fp32, 128 columns     15.2 / 9.0   23.4 / 18.7     26.1 / 26.3     20.4 / 19.5          34.3 / 71.8      39.3 / 51.2   53.1 / 51.1
-//   AGNN layer with P, fp16, 32 columns: 9 thousand 15.3 / 9.7; 40 thousand, uniform 15.5 / 9.7, power law 15.5 / 10.9, R-MAT 16.4 / 14.3;
-//   fp32, 128 columns: 9 thousand 23.7 / 9.8.
+// Up to which graphs.  Two things speak for the edge-balanced kernels: many entries, and a long row, which is one workgroup's chain here
+// (of up to 1024 gathers at a time, about 90 GB/s).  The host knows no row length, but a row without repeated columns has at most n entries,
+// so the lines are drawn by nnz and by n.  us, edge-balanced kernels / here (6 us are what a call takes from Python):
+//   SpMM, entries         uniform, 2048 nodes  uniform, 8192 nodes  R-MAT, 8192 nodes  uniform, 16 384  star, 4000    star, 8000    star, 16 000
+//                         8 th.                33 th.               59 th.             66 th.           8 th.         16 th.        32 th.
+//   fp16, 8 columns       8.4 / 5.8            8.8 / 5.8            11.4 / 7.1         8.8 / 6.0        8.0 / 6.1     8.1 / 7.0     8.8 / 8.8
+//   fp16, 32 columns      11.7 / 5.8           12.0 / 5.8           14.4 / 9.3         12.1 / 8.7       9.6 / 7.9     10.5 / 11.2   11.5 / 12.7
+//   bf16, 64 columns      20.9 / 5.8           20.8 / 5.9           22.8 / 11.5        21.3 / 9.0       16.5 / 12.2   17.8 / 19.8   19.5 / 21.0
+//   fp32, 64 columns      19.1 / 5.9           19.7 / 5.9           21.5 / 11.3        20.1 / 7.0       16.5 / 10.4   18.0 / 16.7   20.1 / 29.5
+//   fp32, 128 columns     29.9 / 5.9           30.5 / 6.9           35.4 / 13.0        33.2 / 11.7      28.9 / 11.1   31.5 / 18.1   35.5 / 45.2
+//   AGNN layer with P     uniform, 2048        uniform, 4096        R-MAT, 2048        uniform, 10 000  star, 2000    star, 4000    star, 8000
+//                         8 th.                16 th.               14 th.             40 th.           4 th.         8 th.         16 th.
+//   fp16, 32 columns      15.4 / 6.0           15.3 / 6.2           17.2 / 10.7        15.8 / 7.8       13.7 / 10.9   14.7 / 14.2   16.1 / 21.1
+//   fp32, 128 columns     39.5 / 6.1           39.6 / 6.3           43.4 / 14.7                         42.0 / 31.1   44.3 / 56.5   48.2 / 141
+// At the lines what uniform graphs gain is about what a star, which is all one row, loses: without a line by n a star of 64 000 nodes took
+// 18 / 90 (fp16, 32 columns), and a million nodes with 40 000 entries 19 / 101 (fp16, 8 columns): 16 lanes a row, empty ones too.
 bool spmm_group_ok(int n, int64_t row_bytes, int piece_bytes, int nnz)
 {
     const int most = piece_bytes <= 16 ? 512 << 10 : piece_bytes <= 64 ? 160 << 10 : 80 << 10;
-    return nnz <= most && !rows_need_64_bits(n, row_bytes);
+    const int rows = piece_bytes <= 16 ? 32 << 10 : piece_bytes <= 128 ? 20 << 10 : 16 << 10;
+    return nnz <= most && n <= rows && !rows_need_64_bits(n, row_bytes);
 }
 bool agnn_group_ok(int n, int64_t row_bytes, int piece_bytes, int nnz)
 {
     const int most = piece_bytes <= 64 ? 48 << 10 : piece_bytes <= 128 ? 32 << 10 : 16 << 10;
-    return nnz <= most && !rows_need_64_bits(n, row_bytes);
+    const int rows = piece_bytes <= 64 ? 10 << 10 : piece_bytes <= 128 ? 8 << 10 : 4 << 10;
+    return nnz <= most && n <= rows && !rows_need_64_bits(n, row_bytes);
 }
 
-// an odd number of workgroups: the long rows of an R-MAT graph are those whose numbers have few one-bits, a power of two would hand
-// many of them to one workgroup
-static unsigned group_grid(int n, int lpr) { return static_cast<unsigned>(ceil_div(n, SG_NT / (lpr <= 16 ? 16 : lpr))) | 1u; }
+// Lanes of the SpMM per row and workgroup: 8, the other columns are other workgroups', and half of the row's above 8192 nodes, where a
+// row may be so long that the chip has to share it: us with whole rows / halves, fp16, 32 columns: uniform, 16 384 nodes 5.9 / 8.7, star, 16 000
+// nodes 17.9 / 12.7; bf16, 64 columns: 6.3 / 9.0, 34 / 21; pieces of 512 bytes whole / in pieces of 128: star, 8000 nodes 84 / 18, uniform, 8192 nodes 5.9 / 6.9.
+static int group_lanes(int n, int lpr) { return lpr > 8 ? 8 : n > 8 << 10 && lpr > 2 ? lpr / 2 : lpr; }
+
+// Workgroups: a prime number of them, so that rows any distance apart fall to different ones.  (The long rows of an R-MAT graph are those
+// whose numbers have few one-bits, those of a batch of like graphs lie a period apart.)
+static unsigned group_grid(int n, int lpr)
+{
+    unsigned p = static_cast<unsigned>(ceil_div(n, SG_NT / (lpr <= 16 ? 16 : lpr))) | 1u;
+    auto prime = [](unsigned x) {
+        for (unsigned d = 3; d * d <= x; d += 2)
+            if (x % d == 0) return false;
+        return true;
+    };
+    while (!prime(p)) p += 2;
+    return p;
+}
 
 int32_t launch_spmm_group(const ftc_csr &g, const float *vals, const void *X, int ldx, int xdt, int D, void *out, int ldo, int odt,
                           Epi epi, hipStream_t s)
@@ -261,9 +286,10 @@ int32_t launch_spmm_group(const ftc_csr &g, const float *vals, const void *X, in
     const int vm = xdt == FTC_F32 ? 4 : 8;
     int vec = vm, lpr = (D + vm - 1) / vm;  // one or two lanes: rows of at most 32 bytes, as in spmm_lane.hip
     if (!spmm_lane_shape(xdt, D, ldx)) seg_shape(xdt, D, &vec, &lpr);
+    lpr = group_lanes(g.n, lpr);
     const uint32_t ldb = static_cast<uint32_t>(ldx) * elem_size(xdt);
     const bool out_vec = D % vec == 0 && aligned16(out) && (static_cast<int64_t>(ldo) * elem_size(odt)) % 16 == 0;
-    const dim3 grid(group_grid(g.n, lpr));
+    const dim3 grid(group_grid(g.n, lpr), ceil_div(D, vec * lpr));
 #define FTC_SG(T, V, L)                                                                                                  \
     hipLaunchKernelGGL((spmm_group_kernel<T, V, L>), grid, dim3(SG_NT), 0, s, g.n, g.row_ptr, g.col_idx, vals, X, ldb, D, \
                        out, ldo, odt, epi, out_vec)
@@ -273,9 +299,7 @@ int32_t launch_spmm_group(const ftc_csr &g, const float *vals, const void *X, in
         if (lpr == 1) FTC_SG(T, VM, 1);                \
         else if (lpr == 2) FTC_SG(T, VM, 2);           \
         else if (lpr == 4) FTC_SG(T, VM, 4);           \
-        else if (lpr == 8) FTC_SG(T, VM, 8);           \
-        else if (lpr == 16) FTC_SG(T, VM, 16);         \
-        else FTC_SG(T, VM, 32);                        \
+        else FTC_SG(T, VM, 8);                         \
     } while (0)
     if (xdt == FTC_F32) FTC_SGT(F32);
     else if (xdt == FTC_F16) FTC_SGT(F16);
