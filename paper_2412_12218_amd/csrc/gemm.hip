@@ -215,8 +215,13 @@ static void gemm_any_t(int n, const void *X, int ldx, int d_in, const void *W, i
     const bool split = n <= GEMM_SPLIT_ROWS;
     const int64_t per = split ? 16 : 64;
     // 64 columns a workgroup at most: with 128 the accumulators leave half as many workgroups to the chip, the last ones alone
-    // (fp32 100 000 x 300 -> 128 118 / 110 us, 400 000 x 64 -> 128 147 / 119, 20 000 x 300 -> 100 39 / 30)
-    const int nt = d_out <= 16 ? 1 : d_out <= 32 ? 2 : d_out <= 64 || !split ? 4 : 8;
+    // (fp32 100 000 x 300 -> 128 119 / 111 us, 400 000 x 65 -> 128 159 / 141, -> 256 301 / 292; fp16 200 000 x 1433 -> 256 1925 / 1851), and 129 to 192
+    // would be padded (100 000 x 300 -> 160 199 / 155).  Each group reads X again: fp32 rows that the memory-side cache no longer holds by
+    // then, with the columns written in between, stay with 128 (400 000 x 300 -> 128 430 / 446, 800 000 x 65 -> 80 270 / 287, 100 000 x 1433 -> 512 1782 / 1873;
+    // the others of the sweep draw level at 290 to 310 MB), where these still are 3000 workgroups (1563: 100 000 x 1433 -> 128 526 / 511).
+    const bool reread = T::BYTES == 4 && (d_out + 63) / 64 % 2 == 0 && n * (4 * static_cast<int64_t>(d_in) + 256) > 300000000 &&
+                        (static_cast<int64_t>(n) + 63) / 64 * ((d_out + 127) / 128) >= 3000;
+    const int nt = d_out <= 16 ? 1 : d_out <= 32 ? 2 : d_out <= 64 || !(split || reread) ? 4 : 8;
     const bool split16 = n <= GEMM_SPLIT16_ROWS && d_in >= GEMM_SPLIT16_IN && nt <= (T::BYTES == 4 ? 4 : 2);
     const dim3 grid(static_cast<unsigned>((n + per - 1) / per), static_cast<unsigned>((d_out + nt * 16 - 1) / (nt * 16)));
 #define FTC_GA1(N, SK, TH)                                                                                                   \
@@ -228,7 +233,7 @@ static void gemm_any_t(int n, const void *X, int ldx, int d_in, const void *W, i
             else if (split) FTC_GA1(N, 4, 256);         \
             else FTC_GA1(N, 1, 256);                    \
         } else if (split) FTC_GA1(N, 4, 256);           \
-        else if constexpr (N <= 4) FTC_GA1(N, 1, 256);  \
+        else if constexpr (N <= 4 || T::BYTES == 4) FTC_GA1(N, 1, 256); \
     }
     FTC_GA(1) FTC_GA(2) FTC_GA(4) FTC_GA(8)
 #undef FTC_GA

@@ -23,3 +23,10 @@ def test_update_gemm_at_the_lines_of_its_split(dtype, n, d_in, d_out):
     s = scale.double()[:, None]
     assert float(((Z.double() - (ref * s).clamp(min=0)).abs() / (terms * s)).max()) <= 1e-5
     assert torch.all(out[:, d_out:] == 7.0)
+
+
+@pytest.mark.parametrize("n", [380_000, 401_003])
+@pytest.mark.parametrize("d_out", [65, 128, 130, 200])
+def test_update_gemm_of_rows_read_more_than_once(n, d_out):
+    """fp32, 130 columns: groups of 64 output columns below 300 MB, above it of 128 where these need no padding."""
+    test_update_gemm_at_the_lines_of_its_split(F32, n, 130, d_out)
