@@ -566,7 +566,7 @@ static void launch_bw_t(int vec, int lpr, unsigned grid, hipStream_t s, int nnz,
         if (lpr == 4) FTC_BW(VM, 4);
         else if (lpr == 8) FTC_BW(VM, 8);
         else if (lpr == 16) FTC_BW(VM, 16);
-        else FTC_BW(VM, 32);
+        else if constexpr (T::BYTES == 4) FTC_BW(VM, 32);  // (16-bit pairs of that width are beyond agnn_backward_fused_shape())
     } else if (vec == VM / 2) {
         FTC_BW(VM / 2, 4);
     } else {
