@@ -117,9 +117,15 @@ def _ptr(t):
     return t.data_ptr() if t is not None else None
 
 
+# not part of torch's public interface: without it the handle comes from a stream object
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
     """Handle of torch's current stream on the current device."""
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _dt(t):

@@ -115,3 +115,12 @@ def test_rows_without_entries_cost_little():
     a, b = time_of(many), time_of(few)
     print(f"2^20 nodes {a:.1f} us, 10 000 nodes {b:.1f} us", flush=True)
     assert a < 8 * b
+
+
+def test_calls_go_to_the_current_stream(monkeypatch):
+    side = torch.cuda.Stream()
+    for raw in (B._raw_stream, None):
+        monkeypatch.setattr(B, "_raw_stream", raw)
+        assert B._stream() == torch.cuda.current_stream().cuda_stream
+        with torch.cuda.stream(side):
+            assert B._stream() == side.cuda_stream != torch.cuda.default_stream().cuda_stream
