@@ -46,7 +46,11 @@ def graphs():
     row_ptr = np.zeros(n + 1, dtype=np.int32)
     row_ptr[1:] = np.cumsum([len(r) for r in rows])
     hub = synth.Graph(n, row_ptr, np.concatenate(rows).astype(np.int32))
-    return [hub, synth.config_graph(5, 1 / 64)]
+    return [hub, synth.config_graph(5, 1 / 64), synth.config_graph(5, 1 / 32)]
+
+
+# entries up to which the AGNN layer of rows of up to 64 bytes, and the SpMM of 16-byte rows, may take the kernels without cut rows
+SMALL_AGNN, SMALL_SPMM = 48 << 10, 512 << 10
 
 
 @pytest.mark.parametrize("gi", [0, 1])
@@ -94,7 +98,7 @@ def test_build_windows_of_dense_graphs_stays_in_bounds(oracle, n, blk_h, per_row
     check_windows(w, oracle.build_windows(g.row_ptr, g.col_idx, blk_h, 8))
 
 
-@pytest.mark.parametrize("gi", [0, 1])
+@pytest.mark.parametrize("gi", [0, 1, 2])
 @pytest.mark.parametrize("dtype,D,pad", [(F16, 32, 0), (F16, 32, 8), (BF16, 64, 0), (F32, 16, 4), (F16, 8, 8),
                                          (F16, 20, 3)])
 @pytest.mark.parametrize("path", [B.FTC_PATH_AUTO, B.FTC_PATH_MFMA])
@@ -102,6 +106,7 @@ def test_spmm_sddmm_softmax_stay_in_bounds(gi, dtype, D, pad, path):
     if path == B.FTC_PATH_MFMA and (dtype == F32 or D % 8 != 0 or (pad % 8) != 0):
         pytest.skip("matrix-core path needs 16-bit features with aligned rows")
     g = graphs()[gi]
+    assert (g.nnz > SMALL_SPMM) == (gi == 2)
     dg = dev_graph(g)
     win = B.ftc_build_windows(dg)
     X = torch.randn((g.n, D + pad), device="cuda").to(dtype)[:, :D]
@@ -123,9 +128,11 @@ def test_spmm_sddmm_softmax_stay_in_bounds(gi, dtype, D, pad, path):
     p.check()
 
 
+@pytest.mark.parametrize("gi", [0, 1])
 @pytest.mark.parametrize("dtype,D", [(F16, 32), (BF16, 64), (F32, 16), (F16, 8)])
-def test_layers_stay_in_bounds(dtype, D):
-    g = graphs()[0]
+def test_layers_stay_in_bounds(dtype, D, gi):
+    g = graphs()[gi]
+    assert (g.nnz > SMALL_AGNN) == (gi == 1)
     dg = dev_graph(g)
     win = B.ftc_build_windows(dg)
     H = torch.randn((g.n, D), device="cuda").to(dtype)
@@ -155,11 +162,13 @@ def test_layers_stay_in_bounds(dtype, D):
     r.check()
 
 
+@pytest.mark.parametrize("gi", [0, 1])
 @pytest.mark.parametrize("dtype,D,out_dtype", [(F32, 3, F32), (F32, 6, F32), (F16, 6, F32), (F16, 6, F16), (BF16, 12, BF16)])
-def test_agnn_layer_leaves_the_padding_columns_alone(dtype, D, out_dtype):
+def test_agnn_layer_leaves_the_padding_columns_alone(dtype, D, out_dtype, gi):
     """Widths whose last piece is shorter than the four columns a lane finishes a cut row with, in padded rows: by the
-    single pass with and without the probabilities, and with the unrounded copy."""
-    g = graphs()[0]
+    single pass with and without the probabilities, and with the unrounded copy; without cut rows and with them."""
+    g = graphs()[gi]
+    assert (g.nnz > SMALL_AGNN) == (gi == 1)
     dg = dev_graph(g)
     win = B.ftc_build_windows(dg)
     ld = (D + 7) // 8 * 8
@@ -178,10 +187,10 @@ def test_agnn_layer_leaves_the_padding_columns_alone(dtype, D, out_dtype):
         t.check()
 
 
-def symmetric_graph():
-    """The hub graph of graphs(), symmetrised (ascending, duplicate-free rows) for the backward pass."""
+def symmetric_graph(gi=0):
+    """A graph of graphs(), symmetrised (ascending, duplicate-free rows) for the backward pass."""
     import scipy.sparse as sp
-    g = graphs()[0]
+    g = graphs()[gi]
     rows = np.repeat(np.arange(g.n), np.diff(g.row_ptr))
     A = sp.csr_matrix((np.ones(g.nnz), (rows, g.col_idx)), shape=(g.n, g.n))
     A = (A + A.T).tocsr()
@@ -198,24 +207,27 @@ def ws_intact(ws):
     assert torch.all(ws.buf[:GUARD] == 0) and torch.all(ws.buf[-GUARD:] == 0), "workspace guard zone overwritten"
 
 
-@pytest.mark.parametrize("dtype,D", [(F16, 32), (BF16, 24), (F32, 16), (F16, 64)])
-def test_agnn_training_pair_stays_in_bounds(dtype, D):
+@pytest.mark.parametrize("gi", [0, 1])
+@pytest.mark.parametrize("dtype,D", [(F16, 32), (BF16, 24), (F32, 16), (F16, 64), (F32, 3), (F32, 6), (F16, 6)])
+def test_agnn_training_pair_stays_in_bounds(dtype, D, gi):
     """Single-pass forward with its two extra outputs, both backward routes, the transposed index and
-    the softmax backward: outputs and workspaces between guard zones."""
-    g = symmetric_graph()
+    the softmax backward: outputs and workspaces between guard zones; widths of 3 and 6 in padded rows."""
+    g = symmetric_graph(gi)
+    assert (g.nnz > SMALL_AGNN) == (gi == 1)
     dg = dev_graph(g)
     win = B.ftc_build_windows(dg)
     L = B.lib()
-    H = torch.randn((g.n, D), device="cuda").to(dtype)
-    dY = torch.randn((g.n, D), device="cuda").to(dtype)
-    out, z = Guarded((g.n, D), dtype), Guarded((g.n,), F32)
+    pad = (-D) % 8
+    H = torch.randn((g.n, D + pad), device="cuda").to(dtype)[:, :D]
+    dY = torch.randn((g.n, D + pad), device="cuda").to(dtype)[:, :D]
+    out, z = Guarded((g.n, D), dtype, pad=pad), Guarded((g.n,), F32)
     y32 = Guarded((g.n, D), F32, pad=(-D) % 4)
     ws = guarded_ws(L.ftc_agnn_layer_workspace_bytes(g.n, g.nnz, D))
     B.ftc_agnn_layer(dg, win, H, beta=1.0, out=out.view, row_z=z.view, out_f32=y32.full, ws=ws.view)
     torch.cuda.synchronize()
     out.check(); z.check(); ws_intact(ws)
     assert torch.all(y32.buf[:GUARD] == y32.sentinel) and torch.all(y32.buf[-GUARD:] == y32.sentinel)
-    dH, dbeta = Guarded((g.n, D), dtype), Guarded((1,), F32)
+    dH, dbeta = Guarded((g.n, D), dtype, pad=pad), Guarded((1,), F32)
     ws = guarded_ws(L.ftc_agnn_layer_backward_fused_workspace_bytes(g.n, g.nnz, D))
     B.ftc_agnn_layer_backward_fused(dg, win, H, z.view, y32.full[:, :D], dY, dH=dH.view, dbeta=dbeta.view, ws=ws.view)
     torch.cuda.synchronize()

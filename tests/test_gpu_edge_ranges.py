@@ -107,6 +107,30 @@ def test_rows_at_the_ends_of_runs_and_ranges(which, times, dtype, D):
         close(edge_p, p, p)
 
 
+@pytest.mark.parametrize("dtype,D", [(F16, 8), (BF16, 5), (F32, 3), (F16, 16), (BF16, 12), (F32, 8), (F32, 6)])
+@pytest.mark.parametrize("times", [60, 240])
+def test_output_scales_of_narrow_rows(dtype, D, times):
+    """Rows of at most 32 bytes: their scales are staged where a range of entries has at most 128 rows; more, up to 128 and one row in a
+    range, long rows over many; 4 and 16 entries a lane."""
+    g = graph(([1] * 700 + [5] * 300 + [8] * 128 + [1024, 3, 0, 0, 2000, 17] + [40] * 30 + [3000]) * times)
+    assert g.nnz > (512 << 10 if times == 60 else 2 << 20)
+    win = B.ftc_build_windows(g)
+    gen = torch.Generator(device="cuda").manual_seed(D)
+    ld = (D + 7) // 8 * 8
+    X = torch.randn((g.n, ld), generator=gen, device="cuda").to(dtype)[:, :D]
+    vals, scale = torch.rand(g.nnz, generator=gen, device="cuda") + 0.5, torch.rand(g.n, generator=gen, device="cuda") + 0.5
+    rows, cols, s = rows_of(g), g.col_idx.long(), scale.double()[:, None]
+    for v in (vals, None):
+        t = X.double()[cols] * (1.0 if v is None else v.double()[:, None])
+        zero = torch.zeros((g.n, D), dtype=torch.float64, device="cuda")
+        ref, terms = zero.clone().index_add_(0, rows, t) * s, zero.clone().index_add_(0, rows, t.abs()) * s
+        for relu in (False, True):
+            out = torch.full((g.n, ld), 7.0, device="cuda")
+            B.ftc_spmm(g, win, v, X, out=out[:, :D], out_scale=scale, relu=relu)
+            close(out[:, :D], torch.relu(ref) if relu else ref, terms)
+            assert torch.all(out[:, D:] == 7.0)
+
+
 @pytest.mark.parametrize("dtype,D", [(F16, 32), (F32, 32), (F16, 16), (F32, 4)])
 def test_feature_matrix_of_more_than_4_gib(dtype, D):
     n, ld = 70_000, 32_768 if dtype == F16 else 16_384  # 4.6 GB, most of it between the rows
@@ -149,20 +173,32 @@ def attention_gradients(g, X, beta, dY):
     return X.grad, b.grad
 
 
+def dbeta_bar(g, X, beta, dY):
+    """What the roundings of dbeta's terms ds_e c_e add up to: about twenty of 2^-24 in each, independent of one another; four standard
+    deviations."""
+    p, _, Y, _ = attention(g, X, beta)
+    rows, cols = rows_of(g), g.col_idx.long()
+    H, d = X.double(), dY.double()
+    Hn = H / H.norm(dim=1).clamp(min=1e-12)[:, None]
+    ds = p * ((d[rows] * H[cols]).sum(1) - (d * Y).sum(1)[rows])
+    return 4 * 20 * 2.0 ** -24 * float((ds * (Hn[rows] * Hn[cols]).sum(1)).norm())
+
+
 @pytest.mark.parametrize("dtype,D,pad", [(F16, 32, 0), (F16, 64, 0), (BF16, 40, 0), (F32, 32, 0), (F32, 128, 0), (F16, 16, 0), (F32, 12, 0),
-                                         (F16, 32, 3), (F32, 128, 1), (BF16, 128, 0)])
+                                         (F16, 32, 3), (F32, 128, 1), (BF16, 128, 0), (F32, 3, 5), (F32, 6, 2), (F16, 6, 2)])
 def test_single_pass_backward_writes_complete_gradients(dtype, D, pad):
     n = 2003
     ptr, cols = symmetric_graph(n, np.random.default_rng(D))
     g = B.Graph.from_numpy(ptr, cols)
     win = B.ftc_build_windows(g)
     gen = torch.Generator(device="cuda").manual_seed(D)
-    X = torch.randn((n, D), generator=gen, device="cuda").to(dtype)
-    dY = torch.randn((n, D), generator=gen, device="cuda").to(dtype)
+    ld = D if D >= 8 else 8  # 16-byte aligned rows
+    X = torch.randn((n, ld), generator=gen, device="cuda").to(dtype)[:, :D]
+    dY = torch.randn((n, ld), generator=gen, device="cuda").to(dtype)[:, :D]
     X[11] *= 1e-4
     z = torch.empty(n, device="cuda")
     y32 = torch.empty((n, (D + 3) // 4 * 4), device="cuda")
-    B.ftc_agnn_layer(g, win, X, beta=1.5, row_z=z, out_f32=y32)
+    B.ftc_agnn_layer(g, win, X, beta=1.5, out=torch.empty((n, ld), device="cuda")[:, :D], row_z=z, out_f32=y32)
     ref, dbeta = attention_gradients(g, X, 1.5, dY)
     buf = torch.full((n, D + pad), 7.0, device="cuda")  # with padding: rows that are not 16-byte aligned
     dH, db = B.ftc_agnn_layer_backward_fused(g, win, X, z, y32[:, :D], dY, beta=1.5, dH=buf[:, :D])
@@ -172,7 +208,9 @@ def test_single_pass_backward_writes_complete_gradients(dtype, D, pad):
     # fp32 sums: relative to the largest element of the row (at least 1, the size of dY)
     scale = ref.abs().max(dim=1).values.clamp(min=1.0)
     assert float(((dH.double() - ref).abs().max(dim=1).values / scale).max()) <= 1e-5
-    assert abs(float(db) - float(dbeta)) <= 1e-6 * g.nnz
+    bar = dbeta_bar(g, X, 1.5, dY)
+    print(f"dbeta {float(db):.6f}, error {abs(float(db) - float(dbeta)):.2e}, bar {bar:.2e}", flush=True)
+    assert abs(float(db) - float(dbeta)) <= bar
 
 
 def ring(n, hops):
@@ -234,4 +272,6 @@ def test_single_pass_backward_of_more_than_4_gib():
         results.append(B.ftc_agnn_layer_backward_fused(g, win, H, z, Y, d, beta=1.0))
     (a, da), (b, db) = results
     assert float((b.view(copies, n, D) - a).abs().max()) <= 1e-5 * float(a.abs().max())
-    assert abs(float(db) / copies - float(da)) <= 1e-6 * nnz
+    bar = dbeta_bar(small, X, 1.0, dY)
+    print(f"dbeta {float(da):.6f}, of a copy {float(db) / copies:.6f}, bar {bar:.2e}", flush=True)
+    assert abs(float(db) / copies - float(da)) <= 2 * bar

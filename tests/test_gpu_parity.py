@@ -872,15 +872,18 @@ def test_spmm_sddmm_agnn_random_shapes(oracle, case):
     assert serr < TOL[dtype]
 
 
-def test_spmm_narrow_rows_at_slot_and_wave_boundaries(oracle):
+@pytest.mark.parametrize("times", [1, 60, 240])
+def test_spmm_narrow_rows_at_slot_and_wave_boundaries(oracle, times):
     """Row lengths that end exactly on slot (16 edges) and wave (512 / 1024 edges) boundaries, a row
-    covering several whole waves, empty rows in between, and a total that is a multiple of 1024."""
+    covering several whole waves, empty rows in between, and a total that is a multiple of 1024.  Once: the kernel for small
+    graphs; 60 times: slots of 4 edges, 240 times: of 16."""
     deg = [16, 0, 16, 32, 0, 0, 1024, 1, 15, 512, 3000, 0, 48, 1024 - 16, 2048, 0, 7]
     deg.append((-sum(deg)) % 1024 + 1024)
+    deg *= times
     n = len(deg)
     row_ptr = np.zeros(n + 1, dtype=np.int32)
     row_ptr[1:] = np.cumsum(deg)
-    assert row_ptr[-1] % 1024 == 0
+    assert row_ptr[-1] % 1024 == 0 and (times == 1 or row_ptr[-1] > {60: 512 << 10, 240: 2 << 20}[times])
     rng = np.random.default_rng(5)
     g = synth.Graph(n, row_ptr, rng.integers(0, n, size=int(row_ptr[-1])).astype(np.int32), "boundaries")
     for dtype, D in ((F16, 8), (F16, 16), (F32, 4), (F32, 8), (BF16, 5)):
