@@ -19,7 +19,7 @@
 //
 // What bounds it: on large graphs the gathers, on graphs whose features lie in the L2s the instructions around them.  Since these
 // went (edge_ranges.hpp, and the scalar work of four entries done once instead of by every lane of the group) the layer takes, with
-// fix-up, 0.30 ms instead of 0.36 on the R-MAT graph (2^20 nodes, 32 M entries, fp16, 32 columns) and with P 71 us instead of 90 on a
+// fix-up, 0.33 ms instead of 0.37 on the R-MAT graph (2^20 nodes, 32 M entries, fp16, 32 columns) and with P 72 us instead of 90 on a
 // power-law graph (200 000 nodes, 3.8 M entries).
 //
 // Work partition, run structure and the handling of rows cut by run / wave boundaries are

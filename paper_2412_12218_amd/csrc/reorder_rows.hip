@@ -2,7 +2,7 @@
 // round of label propagation both look every entry's column up in an array of n ints and need the results of ONE
 // row in ascending order -- the new columns to write them out, the labels to find the longest run of equal ones.
 // Rows are independent, so nothing is sorted across rows: a row is sorted where it fits,
-//   at most 32 / 64 entries     half a wave / a wave, one entry per lane (bitonic, data-parallel-primitive moves),
+//   at most 16 / 32 / 64        a quarter, half or whole wave, one entry per lane (bitonic, data-parallel-primitive moves),
 //   at most 256 / 1024          a wave, 4 / 16 entries per lane,
 //   at most 8192                a workgroup of 1024 threads, in LDS,
 //   longer                      a bitmap of the columns in LDS (relabelling; duplicates: counters, see below) or
