@@ -248,17 +248,22 @@ bool seg_shape(int dtype, int D, int *vec, int *lpr);
 //   fp32, 128 columns     39.5 / 6.1           39.6 / 6.3           43.4 / 14.7                         42.0 / 31.1   44.3 / 56.5   48.2 / 141
 // At the lines what uniform graphs gain is about what a star, which is all one row, loses: without a line by n a star of 64 000 nodes took
 // 18 / 90 (fp16, 32 columns), and a million nodes with 40 000 entries 19 / 101 (fp16, 8 columns): 16 lanes a row, empty ones too.
+// Dense graphs leave their entries to few workgroups, of 32 rows each, so there is a line by the mean row as well.  Complete graphs of 50 / 120 / 200 / 280
+// nodes, edge-balanced kernels / here: fp16, 32 columns 8.1 / 5.5, 8.1 / 7.7, 10.3 / 12.0, 10.8 / 14.4; bf16, 64 columns 8.3 / 6.8, 8.7 / 10.9,
+// 9.9 / 19, 9.6 / 50; AGNN layer, bf16, 64 columns 9.3 / 9.8, 10.0 / 15.7; with P, fp32, 128 columns 18.5 / 13.9, 18.7 / 36.5.  Rows of 16 bytes have the
+// edge-balanced kernel for narrow rows against them: 400 nodes 16.2 / 10.4, 50 with 800 entries each (repeated columns) 14.9 / 10.0, 3000 each 8.3 / 42.
+static bool rows_fit(int n, int nnz, int most_rows, int mean) { return n <= most_rows && nnz <= static_cast<int64_t>(n) * mean; }
 bool spmm_group_ok(int n, int64_t row_bytes, int piece_bytes, int nnz)
 {
     const int most = piece_bytes <= 16 ? 512 << 10 : piece_bytes <= 64 ? 160 << 10 : 80 << 10;
     const int rows = piece_bytes <= 16 ? 32 << 10 : piece_bytes <= 128 ? 20 << 10 : 16 << 10;
-    return nnz <= most && n <= rows && !rows_need_64_bits(n, row_bytes);
+    return nnz <= most && rows_fit(n, nnz, rows, piece_bytes <= 16 ? 1024 : 96) && !rows_need_64_bits(n, row_bytes);
 }
 bool agnn_group_ok(int n, int64_t row_bytes, int piece_bytes, int nnz)
 {
     const int most = piece_bytes <= 64 ? 48 << 10 : piece_bytes <= 128 ? 32 << 10 : 16 << 10;
     const int rows = piece_bytes <= 64 ? 10 << 10 : piece_bytes <= 128 ? 8 << 10 : 4 << 10;
-    return nnz <= most && n <= rows && !rows_need_64_bits(n, row_bytes);
+    return nnz <= most && rows_fit(n, nnz, rows, 64) && !rows_need_64_bits(n, row_bytes);
 }
 
 // Lanes of the SpMM per row and workgroup: 8, the other columns are other workgroups', and half of the row's above 8192 nodes, where a

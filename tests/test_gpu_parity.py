@@ -875,8 +875,8 @@ def test_spmm_sddmm_agnn_random_shapes(oracle, case):
 @pytest.mark.parametrize("times", [1, 60, 240])
 def test_spmm_narrow_rows_at_slot_and_wave_boundaries(oracle, times):
     """Row lengths that end exactly on slot (16 edges) and wave (512 / 1024 edges) boundaries, a row
-    covering several whole waves, empty rows in between, and a total that is a multiple of 1024.  Once: the kernel for small
-    graphs; 60 times: slots of 4 edges, 240 times: of 16."""
+    covering several whole waves, empty rows in between, and a total that is a multiple of 1024.  Once: rows of
+    16 bytes by the kernel for small graphs; the others and 60 times: slots of 4 edges, 240 times: of 16."""
     deg = [16, 0, 16, 32, 0, 0, 1024, 1, 15, 512, 3000, 0, 48, 1024 - 16, 2048, 0, 7]
     deg.append((-sum(deg)) % 1024 + 1024)
     deg *= times

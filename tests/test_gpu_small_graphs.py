@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 import torch
 
-from test_gpu_edge_ranges import attention, close, graph, rows_of
+from test_gpu_edge_ranges import attention, check_spmm, close, graph, rows_of
 from paper_2412_12218_amd import binding as B
 
 pytestmark = pytest.mark.gpu
@@ -104,6 +104,33 @@ def test_a_row_with_most_entries_does_not_hold_up_the_rest(call, dtype, D, n):
     a, b = time_of(call(star, D, dtype)), time_of(call(ring, D, dtype))
     print(f"{call.__name__} {dtype} D={D} n={n}: star {a:.1f} us, ring {b:.1f} us", flush=True)
     assert a < 4 * b
+
+
+@pytest.mark.parametrize("call,dtype,D,n,each", [(spmm_call, BF16, 64, 280, 280), (spmm_call, F16, 32, 50, 3000), (spmm_call, F16, 8, 50, 3000),
+                                                 (agnn_call, F16, 32, 10, 4000)])
+def test_few_long_rows_are_not_left_to_few_workgroups(call, dtype, D, n, each):
+    """A dense graph (with repeated columns where a row is longer than n) against a ring with as many entries: less than three times its
+    time (measured: 0.8 to 1.1; with a workgroup for every 32 rows 5 to 8)."""
+    dense, ring = graph([each] * n), graph([2] * (n * each // 2))
+    a, b = time_of(call(dense, D, dtype)), time_of(call(ring, D, dtype))
+    print(f"{call.__name__} {dtype} D={D}: {n} rows of {each} {a:.1f} us, ring {b:.1f} us", flush=True)
+    assert a < 3 * b
+
+
+@pytest.mark.parametrize("D,each", [(8, 1024), (32, 96), (64, 64)])
+def test_layers_at_the_lines_of_the_mean_row(D, each):
+    """Rows of 16, 64 and 128 bytes on both sides of the longest mean row of the kernels for small graphs."""
+    for more in (0, 1):
+        n = 40
+        g = graph([each - 1] * (n // 2) + [each + 1] * (n // 2 - 1) + [each + 1 + more])
+        win = B.ftc_build_windows(g)
+        X = torch.randn((n, D), generator=torch.Generator(device="cuda").manual_seed(D), device="cuda").to(F16)
+        vals = torch.rand(g.nnz, device="cuda") + 0.5
+        check_spmm(g, win, vals, X, B.ftc_spmm(g, win, vals, X))
+        p, z, ref, terms = attention(g, X, 1.5)
+        edge_p = torch.empty(g.nnz, device="cuda")
+        close(B.ftc_agnn_layer(g, win, X, beta=1.5, edge_p=edge_p), ref, terms)
+        close(edge_p, p, p)
 
 
 def test_rows_without_entries_cost_little():
