@@ -149,9 +149,10 @@ __device__ __forceinline__ int first_group(int open, int g)
     return before ? (63 - __builtin_clzll(before)) / LPR : -1;
 }
 
-// Sum of one slot of the head pieces of ranges first, first + step, ... last, stride floats from range to range: the ranges of a long row,
+// Called by whole waves.  Sum of one slot of the head pieces of ranges first, first + step, ... last, stride floats from range to range: the ranges of a long row,
 // shared by teams of lanes.  Sixteen loads in flight (a hub of the R-MAT graph spans 126 ranges: one after the other, four at a time, they
-// were what the second pass waited for: fused AGNN layer 17.9 / 14.6 us), the remainder four at a time from clamped addresses; the order depends on the shape alone.
+// were what the second pass waited for: fused AGNN layer 17.9 / 14.6 us), the remainder four at a time from clamped addresses, or
+// one, which is all there is where a row has no more pieces than teams (four always: 8 fp16 columns, rows of 600 entries 18.6 / 19.8 us); the order depends on the shape alone.
 __device__ __forceinline__ float sum_pieces(const float *__restrict__ base, size_t stride, int first, int last, int step)
 {
     constexpr int U = 16;
@@ -164,13 +165,14 @@ __device__ __forceinline__ float sum_pieces(const float *__restrict__ base, size
 #pragma unroll
         for (int j = 0; j < U; ++j) s[j & 3] += a[j];
     }
-    for (; u <= last; u += 4 * step) {
+    for (; __builtin_amdgcn_ballot_w64(u + step <= last); u += 4 * step) {  // uniform: one wait for all teams
         float a[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) a[j] = base[static_cast<size_t>(min(u + j * step, last)) * stride];
 #pragma unroll
         for (int j = 0; j < 4; ++j) s[j] += u + j * step <= last ? a[j] : 0.f;
     }
+    if (u <= last) s[0] += base[static_cast<size_t>(u) * stride];
     return (s[0] + s[1]) + (s[2] + s[3]);
 }
 
