@@ -594,8 +594,7 @@ static int pad4(int d) { return (d + 3) / 4 * 4; }
 size_t ftc_update_gemm_backward_workspace_bytes(int32_t n, int32_t d_in, int32_t d_out)
 {
     if (n < 0 || d_in < 1 || d_out < 1) return 0;
-    return align_up(static_cast<size_t>(n) * pad4(d_out) * sizeof(float), 256) + weight_grad_ws(n, d_in, d_out) +
-           input_grad_ws(d_in, d_out);
+    return align_up(static_cast<size_t>(n) * pad4(d_out) * sizeof(float), 256) + weight_grad_ws(n, d_in, d_out);
 }
 
 int32_t ftc_update_gemm_backward(int32_t n, const void *X, int32_t ldx, int32_t dtype, int32_t d_in, const void *W,
@@ -631,8 +630,7 @@ int32_t ftc_update_gemm_backward(int32_t n, const void *X, int32_t ldx, int32_t 
     void *ws_wg = p + align_up(static_cast<size_t>(n) * pad4(d_out) * sizeof(float), 256);
     FTC_TRY(launch_weight_grad(n, X, ldx, dtype, d_in, dP, ldp, d_out, Z && !dX ? Z : nullptr, ldz, z_dtype, dW, ws_wg, hs));
     if (dX)
-        FTC_TRY(launch_input_grad_any(n, dP, ldp, d_out, W, dtype, d_in, dX, lddx, dx_dtype,
-                                      static_cast<char *>(ws_wg) + weight_grad_ws(n, d_in, d_out), hs));
+        FTC_TRY(launch_input_grad(n, dP, ldp, d_out, W, dtype, d_in, dX, lddx, dx_dtype, hs));
     return FTC_OK;
 }
 
@@ -640,8 +638,7 @@ static size_t gcn_backward_ws(int32_t n, int32_t nnz, int32_t d_in, int32_t d_ou
 {
     if (n < 0 || nnz < 0 || d_in < 1 || d_out < 1) return 0;
     const size_t mat = align_up(static_cast<size_t>(n) * pad4(d_out) * sizeof(float), 256);
-    return 2 * mat + align_up(spmm_ws(n, nnz, d_out, least), 256) + weight_grad_ws(n, d_in, d_out) +
-           input_grad_ws(d_in, d_out);
+    return 2 * mat + align_up(spmm_ws(n, nnz, d_out, least), 256) + weight_grad_ws(n, d_in, d_out);
 }
 
 size_t ftc_gcn_layer_backward_workspace_bytes(int32_t n, int32_t nnz, int32_t d_in, int32_t d_out)
@@ -684,8 +681,7 @@ int32_t ftc_gcn_layer_backward(const ftc_csr *gT, const ftc_windows *wT, const f
                      ws_spmm, spmm_bytes, stream));
     FTC_TRY(launch_weight_grad(n, X, ldx, dtype, d_in, dZ, ldp, d_out, nullptr, 0, FTC_F32, dW, ws_wg, hs));
     if (dX)
-        FTC_TRY(launch_input_grad_any(n, dZ, ldp, d_out, W, dtype, d_in, dX, lddx, FTC_F32,
-                                      static_cast<char *>(ws_wg) + weight_grad_ws(n, d_in, d_out), hs));
+        FTC_TRY(launch_input_grad(n, dZ, ldp, d_out, W, dtype, d_in, dX, lddx, FTC_F32, hs));
     return FTC_OK;
 }
 

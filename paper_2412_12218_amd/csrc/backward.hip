@@ -508,90 +508,6 @@ int32_t launch_weight_grad(int n, const void *X, int ldx, int xdt, int d_in, con
     return launch_status("weight_grad");
 }
 
-// ---- dX = G W^T -----------------------------------------------------------------------------------
-// A thread owns one input feature a and keeps row a of W in registers; the rows of G are staged in
-// LDS and read as broadcasts.
-constexpr int IG_ROWS = 64;
-
-template <int DOUT>  // d_out padded to a multiple of 4
-__global__ __launch_bounds__(256) void input_grad_kernel(int n, const float *__restrict__ G, int ldg, int d_out,
-                                                         const void *__restrict__ W, int wdt, int d_in,
-                                                         void *__restrict__ dX, int lddx, int dx_dt)
-{
-    __shared__ __attribute__((aligned(16))) float Gs[IG_ROWS * DOUT];
-    const int tid = threadIdx.x;
-    const int64_t r0 = static_cast<int64_t>(blockIdx.x) * IG_ROWS;
-    for (int t = tid; t < IG_ROWS * DOUT; t += 256) {
-        const int r = t / DOUT, b = t % DOUT;
-        Gs[t] = (r0 + r < n && b < d_out) ? G[(r0 + r) * ldg + b] : 0.f;
-    }
-    __syncthreads();
-    for (int a = tid; a < d_in; a += 256) {
-        float w[DOUT];
-#pragma unroll
-        for (int b = 0; b < DOUT; ++b) w[b] = b < d_out ? load_elem(W, static_cast<int64_t>(a) * d_out + b, wdt) : 0.f;
-        for (int r = 0; r < IG_ROWS && r0 + r < n; ++r) {
-            float acc = 0.f;
-#pragma unroll
-            for (int b = 0; b < DOUT; b += 4) {
-                const float4 z = *reinterpret_cast<const float4 *>(&Gs[r * DOUT + b]);
-                acc = fmaf(z.x, w[b], acc);
-                acc = fmaf(z.y, w[b + 1], acc);
-                acc = fmaf(z.z, w[b + 2], acc);
-                acc = fmaf(z.w, w[b + 3], acc);
-            }
-            store_elem(dX, (r0 + r) * lddx + a, dx_dt, acc);
-        }
-    }
-}
-
-int32_t launch_input_grad(int n, const float *G, int ldg, int d_out, const void *W, int wdt, int d_in, void *dX,
-                          int lddx, int dx_dt, hipStream_t s)
-{
-    if (n == 0) return FTC_OK;
-    const unsigned grid = static_cast<unsigned>((static_cast<int64_t>(n) + IG_ROWS - 1) / IG_ROWS);
-#define FTC_IG(P)                                                                                               \
-    hipLaunchKernelGGL(input_grad_kernel<P>, dim3(grid), dim3(256), 0, s, n, G, ldg, d_out, W, wdt, d_in, dX, lddx, \
-                       dx_dt)
-    if (d_out <= 8) FTC_IG(8);
-    else if (d_out <= 16) FTC_IG(16);
-    else if (d_out <= 32) FTC_IG(32);
-    else FTC_IG(64);
-#undef FTC_IG
-    return launch_status("input_grad");
-}
-
-// More than 64 output columns: dX = G W^T is the dense update of the fp32 matrix G with the weights W^T, so
-// W is transposed into the workspace as fp32 (d_out x d_in) and the forward kernels do the rest.
-__global__ __launch_bounds__(256) void transpose_weights_kernel(int d_in, int d_out, const void *__restrict__ W,
-                                                                int wdt, float *__restrict__ Wt)
-{
-    const int64_t t = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (t >= static_cast<int64_t>(d_in) * d_out) return;
-    const int b = static_cast<int>(t / d_in), a = static_cast<int>(t % d_in);  // consecutive threads write consecutive entries
-    Wt[t] = load_elem(W, static_cast<int64_t>(a) * d_out + b, wdt);
-}
-
-size_t input_grad_ws(int d_in, int d_out)
-{
-    return d_out > 64 ? align_up(static_cast<size_t>(d_in) * d_out * sizeof(float), 256) : 0;
-}
-
-// ws: input_grad_ws(d_in, d_out) bytes, used when d_out > 64
-int32_t launch_input_grad_any(int n, const float *G, int ldg, int d_out, const void *W, int wdt, int d_in, void *dX,
-                              int lddx, int dx_dt, void *ws, hipStream_t s)
-{
-    if (d_out <= 64) return launch_input_grad(n, G, ldg, d_out, W, wdt, d_in, dX, lddx, dx_dt, s);
-    if (n == 0) return FTC_OK;
-    float *Wt = static_cast<float *>(ws);
-    const int64_t total = static_cast<int64_t>(d_in) * d_out;
-    hipLaunchKernelGGL(transpose_weights_kernel, dim3(static_cast<unsigned>((total + 255) / 256)), dim3(256), 0, s, d_in,
-                       d_out, W, wdt, Wt);
-    const int32_t st = launch_status("input_grad transpose");
-    if (st != FTC_OK) return st;
-    return launch_gemm(n, G, ldg, FTC_F32, d_out, Wt, d_in, dX, lddx, dx_dt, Epi{0, nullptr}, s);
-}
-
 // ---- out[e] = alpha * (wa * a[e] + wb * a[T[e]]) * cs[col[e]] -------------------------------------
 __global__ __launch_bounds__(256) void edge_combine_kernel(int nnz, const float *__restrict__ a,
                                                            const int *__restrict__ T, float wa, float wb, float alpha,

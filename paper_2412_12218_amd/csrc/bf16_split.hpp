@@ -1,0 +1,62 @@
+// fp32 products on the bf16 matrix cores.  A float has 24 significant bits, a bf16 eight, so a = a1 + a2 + a3 with three
+// bf16 numbers, exactly: a1 = a rounded, a2 = (a - a1) rounded, a3 = the rest.  Of the nine products of two such sums the
+// three smallest (a2 b3, a3 b2, a3 b3: together below 2^-24 of a b, an fp32 rounding) are left out; the other six are exact in fp32
+// and take six instructions at sixteen times the rate of v_mfma_f32_16x16x4_f32.
+// Not so: infinities and NaN (inf - inf in the second piece), numbers that round to an infinite a1, and rests below the
+// smallest normal number.  All of these show in the last piece (NaN, or subnormal), so that is what is looked at, and the
+// step of the contraction they are in takes the fp32 instruction instead.
+#pragma once
+#include "ftc_common.hpp"
+
+namespace ftc {
+#if defined(__HIPCC__)
+
+typedef float split_f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 split_bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 split_bf16x8 __attribute__((ext_vector_type(8)));
+typedef float split_f32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ uint32_t bf16_pair(float x, float y)
+{
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((split_f32x2{x, y}), split_bf16x2));
+}
+
+// Pieces of eight numbers, packed in order; true: some of them can't be taken in pieces (this lane's).
+__device__ __forceinline__ bool split8(const float (&a)[8], uint4 (&p)[3])
+{
+    uint32_t w[3][4];
+    bool odd = false;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        float x = a[2 * j], y = a[2 * j + 1];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            w[q][j] = bf16_pair(x, y);
+            x -= __uint_as_float(w[q][j] << 16);
+            y -= __uint_as_float(w[q][j] & 0xffff0000u);
+        }
+        w[2][j] = bf16_pair(x, y);
+        constexpr int ODD = 0x3 | 0x204 | 0x90;  // NaN, infinite, subnormal
+        odd |= __builtin_amdgcn_classf(x, ODD) | __builtin_amdgcn_classf(y, ODD);
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) p[q] = make_uint4(w[q][0], w[q][1], w[q][2], w[q][3]);
+    return odd;
+}
+
+// lo, hi += the six products of a step of 32: the large one apart from the small ones, whose roundings then don't count
+__device__ __forceinline__ void mfma_split(const uint4 (&a)[3], const uint4 (&b)[3], split_f32x4 &hi, split_f32x4 &lo)
+{
+    auto go = [](const uint4 &x, const uint4 &y, split_f32x4 c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(split_bf16x8, x), __builtin_bit_cast(split_bf16x8, y), c, 0, 0, 0);
+    };
+    hi = go(a[0], b[0], hi);
+    lo = go(a[0], b[2], lo);
+    lo = go(a[2], b[0], lo);
+    lo = go(a[1], b[1], lo);
+    lo = go(a[0], b[1], lo);
+    lo = go(a[1], b[0], lo);
+}
+
+#endif  // __HIPCC__
+}  // namespace ftc

@@ -79,6 +79,12 @@ int32_t launch_softmax_seg(const ftc_csr &g, const ftc_windows &w, const float *
 int32_t launch_row_rnorm(int n, const void *H, int ld, int dt, int D, float *rinv, hipStream_t s);
 int32_t launch_gemm(int n, const void *X, int ldx, int dt, int d_in, const void *W, int d_out, void *Z,
                     int ldz, int zdt, Epi epi, hipStream_t s);
+// gemm_tile.hip
+bool gemm_tile_better(int n, int dt, int d_in, int d_out);
+int32_t launch_gemm_tile(int n, const void *X, int ldx, int dt, int d_in, const void *W, int d_out, void *Z, int ldz, int zdt, Epi epi,
+                         hipStream_t s);
+int32_t launch_input_grad(int n, const float *G, int ldg, int d_out, const void *W, int wdt, int d_in, void *dX, int lddx, int dx_dt,
+                          hipStream_t s);
 int32_t launch_gcn_norm(const ftc_csr &g, const ftc_windows *w, float *vals, float *dinv, hipStream_t s);
 int32_t launch_validate(const ftc_csr &g, int32_t *flag, hipStream_t s);
 bool seg_shape(int dtype, int D, int *vec, int *lpr);
@@ -130,14 +136,9 @@ int32_t launch_softmax_backward_seg(const ftc_csr &g, const ftc_windows &w, cons
 int32_t launch_mask_scale(int n, int d, const float *dY, int lddy, const void *Y, int ldy, int ydt,
                           const float *scale, float *out, int ldo, hipStream_t s);
 int weight_grad_group(int d_in, int d_out);
-size_t input_grad_ws(int d_in, int d_out);
-int32_t launch_input_grad_any(int n, const float *G, int ldg, int d_out, const void *W, int wdt, int d_in, void *dX,
-                              int lddx, int dx_dt, void *ws, hipStream_t s);
 size_t weight_grad_ws(int n, int d_in, int d_out);
 int32_t launch_weight_grad(int n, const void *X, int ldx, int xdt, int d_in, const float *G, int ldg, int d_out,
                            const void *Y, int ldy, int ydt, float *dW, void *ws, hipStream_t s);
-int32_t launch_input_grad(int n, const float *G, int ldg, int d_out, const void *W, int wdt, int d_in, void *dX,
-                          int lddx, int dx_dt, hipStream_t s);
 int32_t launch_edge_combine(int nnz, const float *a, const int *T, float wa, float wb, float alpha, const float *cs,
                             const int *col_idx, float *out, hipStream_t s);
 size_t edge_dot_ws();

@@ -1,34 +1,32 @@
 // Dense update phase Z = X * W for tall-skinny shapes: X is streamed once, W sits in LDS.  Three kernels, all on the
 // matrix cores: 16-bit inputs with d_in <= 256, d_out <= 64 and aligned rows (the benchmark models) keep all of W on chip;
-// 16-bit inputs that are wider are contracted in chunks; everything else (fp32, odd widths, rows that are not 16-byte
-// aligned, few rows) goes through the general kernel.
+// everything else (fp32, odd widths, rows that are not 16-byte aligned) goes through the kernels of gemm_tile.hip, and through
+// gemm_any_kernel where rows are few or, in fp32, columns.
 #include "ftc_common.hpp"
 
 namespace ftc {
 
-// The general kernel: any element type, any width, rows at any alignment of their elements.  Contraction in fp32 on the
-// matrix cores (v_mfma_f32_16x16x4_f32; 16-bit elements are widened first), so products and sums are those of fp32
-// arithmetic.  A wave owns a tile of 16 rows of X and up to 16 NT output columns:
+// The kernel for few rows (GEMM_SPLIT_ROWS), and in fp32 for few columns of any number of rows: any element type, any width, rows at
+// any alignment of their elements.  Contraction in fp32 on the matrix cores (v_mfma_f32_16x16x4_f32; 16-bit elements are widened
+// first), so products and sums are those of fp32 arithmetic.  A wave owns a tile of 16 rows of X and up to 16 NT output columns:
 //   A operand  lane l holds X[row0 + l%16][k0 + (l/16) V .. + V - 1], one 16-byte load (V = 4 or 8 elements; 64
 //              contiguous bytes per row and step); the j-th product takes element j of every lane, so the contraction
 //              index runs in steps of 4 V in an order of its own, the same for A and B;
 //   B operand  W is staged in LDS as fp32 in chunks of KC rows, four consecutive k of a column side by side: lane l
 //              reads W[k .. k + 3][n0 + l%16] as one 16-byte word.
-// Bound by reading X up to about 32 output columns and by the fp32 matrix rate (157 TFLOP/s) beyond.  SK = 4 or 16: for matrices
-// of few rows the waves of a workgroup share one row tile and split every chunk's k between them (the partial
-// sums are added in wave order through LDS): 2708 rows would otherwise occupy 43 workgroups.
+// Bound by the chain of chunks (few rows) or by reading X.  SK = 4 or 16: the waves of a workgroup share one row tile and split every
+// chunk's k between them (the partial sums are added in wave order through LDS): 2708 rows would otherwise occupy 43 workgroups.
 // One tile per wave, 32 KB of W: two tiles per wave were 10 % slower, 64 KB up to 20 %, 16 KB 5 %.
-// Measured, vector units (X staged element by element in LDS, or one row per thread) against this:
-//   fp32 100 000 x 1433 -> 16: 925 / 145 us (4.0 TB/s); fp32 100 000 x 300 -> 128: 315 / 110 us (70 TFLOP/s);
-//   fp32 400 000 x 128 -> 32: 425 / 62 us; fp16 2708 x 1433 -> 16: 311 / 10 us.
-// Error against 64 bits (2-norm, fp32 1433 -> 16): 6.8e-7 / 4.8e-7.
+// Measured, vector units (X staged element by element in LDS, or one row per thread) against this: fp32 65 000 x 65 -> 7 6.4 us here, 7.2 in
+// gemm_tile.hip; fp16 2708 x 1433 -> 16: 311 / 10 us, 20 in gemm_tile.hip.
 typedef float float4v __attribute__((ext_vector_type(4)));
 
 // Up to this many rows the waves split the contraction (256 workgroups of 64 rows would be the most without).
 constexpr int GEMM_SPLIT_ROWS = 16384;
 // Few rows and a long contraction are split over 16 waves instead of 4: a workgroup is a chain of chunks (stage W, wait, load X,
 // multiply), which a quarter of the chunks is a quarter of.  us, 4 / 16 waves: fp16 2708 x 1433 -> 16 14.2 / 9.8, -> 32 22.1 / 14.8, bf16
-// 2708 x 3703 -> 32 53 / 33, fp32 8000 x 1433 -> 64 52 / 45, 2708 x 500 -> 32 9.0 / 8.8; but 8000 x 300 -> 32 9.0 / 9.4, 16 000 x 1433 -> 32 46 / 55.
+// 2708 x 3703 -> 32 53 / 33, fp32 8000 x 1433 -> 64 52 / 45, 2708 x 500 -> 32 9.0 / 8.8; but 8000 x 300 -> 32 9.0 / 9.4, 16 000 x 1433 -> 32 46 / 55
+// (the 16-bit ones above 4096 rows: gemm_tile.hip).
 // The chunk of 16 waves has to fit into LDS: up to 64 columns in fp32, 32 in 16 bits.
 constexpr int GEMM_SPLIT16_ROWS = 8192, GEMM_SPLIT16_IN = 512;
 
@@ -214,28 +212,19 @@ static void gemm_any_t(int n, const void *X, int ldx, int d_in, const void *W, i
 {
     const bool split = n <= GEMM_SPLIT_ROWS;
     const int64_t per = split ? 16 : 64;
-    // 64 columns a workgroup at most: with 128 the accumulators leave half as many workgroups to the chip, the last ones alone
-    // (fp32 100 000 x 300 -> 128 119 / 111 us, 400 000 x 65 -> 128 159 / 141, -> 256 301 / 292; fp16 200 000 x 1433 -> 256 1925 / 1851), and 129 to 192
-    // would be padded (100 000 x 300 -> 160 199 / 155).  Each group reads X again: fp32 rows that the memory-side cache no longer holds by
-    // then, with the columns written in between, stay with 128 (400 000 x 300 -> 128 430 / 446, 800 000 x 65 -> 80 270 / 287, 100 000 x 1433 -> 512 1782 / 1873;
-    // the others of the sweep draw level at 290 to 310 MB), where these still are 3000 workgroups (1563: 100 000 x 1433 -> 128 526 / 511).
-    const bool reread = T::BYTES == 4 && (d_out + 63) / 64 % 2 == 0 && n * (4 * static_cast<int64_t>(d_in) + 256) > 300000000 &&
-                        (static_cast<int64_t>(n) + 63) / 64 * ((d_out + 127) / 128) >= 3000;
-    const int nt = d_out <= 16 ? 1 : d_out <= 32 ? 2 : d_out <= 64 || !(split || reread) ? 4 : 8;
+    const int nt = d_out <= 16 ? 1 : d_out <= 32 ? 2 : 4;  // (more than 64 columns: gemm_tile.hip)
     const bool split16 = n <= GEMM_SPLIT16_ROWS && d_in >= GEMM_SPLIT16_IN && nt <= (T::BYTES == 4 ? 4 : 2);
     const dim3 grid(static_cast<unsigned>((n + per - 1) / per), static_cast<unsigned>((d_out + nt * 16 - 1) / (nt * 16)));
 #define FTC_GA1(N, SK, TH)                                                                                                   \
     hipLaunchKernelGGL((gemm_any_kernel<T, N, SK>), grid, dim3(TH), 0, s, n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi)
 #define FTC_GA(N)                                       \
     if (nt == N) {                                      \
-        if constexpr (N <= (T::BYTES == 4 ? 4 : 2)) {   \
-            if (split16) FTC_GA1(N, 16, 1024);          \
-            else if (split) FTC_GA1(N, 4, 256);         \
-            else FTC_GA1(N, 1, 256);                    \
-        } else if (split) FTC_GA1(N, 4, 256);           \
-        else if constexpr (N <= 4 || T::BYTES == 4) FTC_GA1(N, 1, 256); \
+        if constexpr (N <= (T::BYTES == 4 ? 4 : 2))     \
+            if (split16) { FTC_GA1(N, 16, 1024); return; } \
+        if (split) FTC_GA1(N, 4, 256);                  \
+        else if constexpr (N == 1 && T::BYTES == 4) FTC_GA1(N, 1, 256); \
     }
-    FTC_GA(1) FTC_GA(2) FTC_GA(4) FTC_GA(8)
+    FTC_GA(1) FTC_GA(2) FTC_GA(4)
 #undef FTC_GA
 #undef FTC_GA1
 }
@@ -379,105 +368,6 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(int n, const uint16_t *_
     }
 }
 
-// The same contraction for any d_in (rows of X 16-byte aligned; the last piece of a width that is no
-// multiple of 8 is read element by element) and a group of up to 64 output columns [col0, col0 + d_out)
-// of a W with w_ld columns: W^T is staged in chunks of 256 rows of W, a workgroup keeps the
-// accumulators of 4 x RT tiles of 16 rows across the chunks, and B operands come from LDS.
-constexpr int WIDE_KC = 256;
-
-template <class T, int WIDE_RT>
-__global__ __launch_bounds__(256) void gemm_mfma_wide_kernel(int n, const uint16_t *__restrict__ X, int ldx, int d_in,
-                                                             const uint16_t *__restrict__ W, int w_ld, int col0,
-                                                             int d_out, void *__restrict__ Z, int ldz, int zdt,
-                                                             Epi epi, int n_batches)
-{
-    constexpr int NT = 4, KP = WIDE_KC + 8;
-    __shared__ __attribute__((aligned(16))) uint16_t Wt[NT * 16 * KP];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int m = lane & 15, kb = lane >> 4;
-    const int nt_n = (d_out + 15) / 16;
-    for (int batch = blockIdx.x; batch < n_batches; batch += gridDim.x) {  // uniform over the workgroup
-        const int tile0 = (batch * 4 + wave) * WIDE_RT;
-        float4v c[WIDE_RT][NT];
-#pragma unroll
-        for (int rt = 0; rt < WIDE_RT; ++rt)
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) c[rt][nt] = float4v{0.f, 0.f, 0.f, 0.f};
-        for (int kc0 = 0; kc0 < d_in; kc0 += WIDE_KC) {
-            __syncthreads();  // the previous chunk (or batch) has been consumed
-            const int nn_n = nt_n * 16;  // only the column tiles that are used
-            for (int t0 = threadIdx.x; t0 < nn_n * WIDE_KC; t0 += 256 * 16) {  // (nn_n * WIDE_KC is a multiple of 256 * 16)
-                uint16_t wv[16];  // (100 000 x 1432 -> 16: 106 us with a load at a time, 93 like this)
-#pragma unroll
-                for (int j = 0; j < 16; ++j) {
-                    const int t = t0 + j * 256, k = t / nn_n, nn = t % nn_n;  // consecutive threads read consecutive columns of W
-                    wv[j] = W[(nn < d_out && kc0 + k < d_in) ? static_cast<size_t>(kc0 + k) * w_ld + col0 + nn : 0];
-                }
-#pragma unroll
-                for (int j = 0; j < 16; ++j) {
-                    const int t = t0 + j * 256, k = t / nn_n, nn = t % nn_n;
-                    Wt[nn * KP + k] = (nn < d_out && kc0 + k < d_in) ? wv[j] : uint16_t(0);
-                }
-            }
-            __syncthreads();
-#pragma unroll
-            for (int ks = 0; ks < WIDE_KC / 32; ++ks) {
-                const int k = kc0 + ks * 32 + kb * 8;
-                uint4 a[WIDE_RT];
-#pragma unroll
-                for (int rt = 0; rt < WIDE_RT; ++rt) {
-                    const int64_t row = min(static_cast<int64_t>(tile0 + rt) * 16 + m, static_cast<int64_t>(n) - 1);
-                    if (k + 8 <= d_in) {
-                        a[rt] = *reinterpret_cast<const uint4 *>(X + row * ldx + k);
-                    } else {  // the last piece of a width that is no multiple of 8: element by element, nothing beyond d_in is read
-                        unsigned h[8];
-#pragma unroll
-                        for (int j = 0; j < 8; ++j) h[j] = k + j < d_in ? X[row * ldx + k + j] : 0u;
-                        a[rt] = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
-                    }
-                }
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt) {
-                    if (nt < nt_n) {
-                        const uint4 b = *reinterpret_cast<const uint4 *>(&Wt[(nt * 16 + m) * KP + ks * 32 + kb * 8]);
-#pragma unroll
-                        for (int rt = 0; rt < WIDE_RT; ++rt) c[rt][nt] = mfma16<T>(a[rt], b, c[rt][nt]);
-                    }
-                }
-            }
-        }
-#pragma unroll
-        for (int rt = 0; rt < WIDE_RT; ++rt)
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                const int col = nt * 16 + m;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int64_t row = static_cast<int64_t>(tile0 + rt) * 16 + kb * 4 + i;
-                    if (row < n && col < d_out)
-                        store_elem(Z, row * ldz + col0 + col, zdt, epi.apply(epi.factor(static_cast<int>(row)), c[rt][nt][i]));
-                }
-            }
-    }
-}
-
-template <class T>
-static void gemm_mfma_wide_t(int n, const void *X, int ldx, int d_in, const void *W, int d_out, void *Z, int ldz,
-                             int zdt, Epi epi, hipStream_t s)
-{
-    const int64_t n_tiles = (static_cast<int64_t>(n) + 15) / 16;
-    // four tiles per wave: W is re-staged once per 256 rows (one tile per wave was measured 2.4 times slower
-    // at 100 k rows, although it starts four times as many workgroups)
-    const int64_t n_batches = (n_tiles + 15) / 16;
-    const unsigned grid = static_cast<unsigned>(n_batches < 256 * 4 ? n_batches : 256 * 4);
-    for (int col0 = 0; col0 < d_out; col0 += 64) {
-        const int cols = d_out - col0 < 64 ? d_out - col0 : 64;
-        hipLaunchKernelGGL((gemm_mfma_wide_kernel<T, 4>), dim3(grid), dim3(256), 0, s, n,
-                           static_cast<const uint16_t *>(X), ldx, d_in, static_cast<const uint16_t *>(W), d_out, col0,
-                           cols, Z, ldz, zdt, epi, static_cast<int>(n_batches));
-    }
-}
-
 template <class T>
 static bool gemm_mfma_t(int n, const void *X, int ldx, int d_in, const void *W, int d_out, void *Z, int ldz,
                         int zdt, Epi epi, hipStream_t s)
@@ -512,14 +402,6 @@ int32_t launch_gemm(int n, const void *X, int ldx, int dt, int d_in, const void 
         const bool done = fast && (dt == FTC_F16 ? gemm_mfma_t<F16>(n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi, s)
                                                  : gemm_mfma_t<BF16>(n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi, s));
         if (done) return launch_status("update_gemm mfma");
-        // beyond the register-resident shapes, or a width that is no multiple of 8 in padded rows; few rows are left to the
-        // general kernel, which splits the contraction over the waves (2708 x 1432 -> 16: 44 us here, 10 us there;
-        // 100 000 rows: 93 us here, 115 us there)
-        if ((d_in > 256 || d_out > 64 || !fast) && n > GEMM_SPLIT_ROWS) {
-            if (dt == FTC_F16) gemm_mfma_wide_t<F16>(n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi, s);
-            else gemm_mfma_wide_t<BF16>(n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi, s);
-            return launch_status("update_gemm mfma (wide)");
-        }
     }
     if (dt == FTC_F32 && fast && narrow_shape(d_in, d_out)) {
         const dim3 grid(static_cast<unsigned>((static_cast<int64_t>(n) + 255) / 256));
@@ -528,6 +410,7 @@ int32_t launch_gemm(int n, const void *X, int ldx, int dt, int d_in, const void 
         else hipLaunchKernelGGL(gemm_narrow_kernel<12>, grid, dim3(256), 0, s, n, x, ldx, d_in, w, d_out, Z, ldz, zdt, epi);
         return launch_status("update_gemm narrow");
     }
+    if (gemm_tile_better(n, dt, d_in, d_out)) return launch_gemm_tile(n, X, ldx, dt, d_in, W, d_out, Z, ldz, zdt, epi, s);
     if (dt == FTC_F32) gemm_any_t<F32>(n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi, s);
     else if (dt == FTC_F16) gemm_any_t<F16>(n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi, s);
     else gemm_any_t<BF16>(n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi, s);

@@ -1,0 +1,270 @@
+// Dense products Z = X W of many rows at any alignment and width on the 16-bit matrix cores (v_mfma_f32_16x16x32), 16-bit
+// inputs as they are, fp32 inputs in three exact bf16 pieces (bf16_split.hpp); and dX = G W^T, the same with W transposed (TRANS).
+//
+// A wave owns 16 rows of X and up to 16 NT columns; a workgroup, four waves, stages a chunk of KC rows of W in LDS, columns
+// first, in the operands' layout (eight consecutive k of a column are one 16-byte word), in pieces.
+//   A operand  lane l holds X[row0 + l%16][k0 + (l/16) 8 .. +7], loaded at element alignment; the chunk's are all loaded before W is
+//              staged, so that a chunk waits for memory once;
+//   C          lane l holds Z[row0 + (l/16) 4 + i][n0 + l%16].
+// Where one chunk holds all of W a workgroup walks over the rows and stages it once.
+//
+// Bound by reading X (and writing Z) up to about 32 columns, then by the chain load, stage, multiply of a chunk, which four workgroups
+// on a CU share.  Products and sums are no less exact than on v_mfma_f32_16x16x4_f32, where these products were before: six or one
+// instruction for what were eight, so fewer roundings, and the chunks' sums of 16-bit inputs are added up apart.  us and
+// error against 64 bits (2-norm), there / here:
+//   fp32  100 000 x 300 -> 128 112 / 78 (2.2e-7 / 0.9e-7), 400 000 x 301 -> 128 427 / 342, 100 000 x 500 -> 40 94 / 61, 1 000 000 x 33 -> 2
+//         57 / 40, 16 000 x 300 -> 128 40 / 19
+//   fp16  100 000 x 300 -> 128 110 / 45 (2.1e-7 / 0.8e-7), 400 000 x 301 -> 128 440 / 180, 179 245 x 18 -> 64 27 / 15, 16 000 x 1433 -> 32 47 / 28
+//   bf16  100 000 x 500 -> 40 91 / 35 (1.0e-7 / 0.6e-7), 5000 x 3001 -> 128 176 / 85 (1.3e-7 / 1.1e-7)
+// and against 16-bit rows staged in chunks of 256 for 256 rows at a time (aligned rows): fp16 20 000 x 304 -> 64 46 / 11, 100 000 x 1432 -> 16
+// 92 / 65, 400 000 x 128 -> 128 189 / 108.
+// Tried: eight waves instead of four (W staged half as often: 300 -> 128 level, 1433 -> 16 12 % slower), the next chunk of X in registers
+// (5 to 15 % slower), 128 columns of fp32 (107 us for 78: registers).
+#include "bf16_split.hpp"
+
+namespace ftc {
+
+typedef _Float16 gt_half8 __attribute__((ext_vector_type(8)));
+
+template <class T>
+struct GemmChunk {
+    static constexpr int PIECES = T::BYTES == 4 ? 3 : 1;
+    static constexpr int KC = T::BYTES == 4 ? 64 : 128;
+};
+
+// 8 elements at idx, elements from `left` on are zero and not read
+template <class T>
+struct Eight {
+    float f[T::BYTES == 4 ? 8 : 1];
+    uint4 h;
+};
+template <class T>
+__device__ __forceinline__ void load_eight(const void *base, int64_t idx, int left, Eight<T> &e)
+{
+    if constexpr (T::BYTES == 4) {
+        const float *p = static_cast<const float *>(base) + idx;
+        if (left >= 8) {
+            typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
+            const f4 a = *reinterpret_cast<const f4 *>(p), b = *reinterpret_cast<const f4 *>(p + 4);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) { e.f[j] = a[j]; e.f[4 + j] = b[j]; }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) e.f[j] = j < left ? p[j] : 0.f;
+        }
+    } else {
+        const uint16_t *p = static_cast<const uint16_t *>(base) + idx;
+        if (left >= 8) {
+            typedef uint32_t u4 __attribute__((ext_vector_type(4), aligned(2)));
+            const u4 a = *reinterpret_cast<const u4 *>(p);
+            e.h = make_uint4(a[0], a[1], a[2], a[3]);
+        } else {
+            uint32_t w[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) w[j] = j < left ? p[j] : 0u;
+            e.h = make_uint4(w[0] | (w[1] << 16), w[2] | (w[3] << 16), w[4] | (w[5] << 16), w[6] | (w[7] << 16));
+        }
+    }
+}
+
+template <class T, int NT, bool TRANS>
+__global__ __launch_bounds__(256, NT == 8 ? 2 : 4) void gemm_tile_kernel(int n, const void *__restrict__ X, int ldx, int d_in,
+                                                                         const void *__restrict__ W, int w_ld, int wdt, int d_out,
+                                                                         void *__restrict__ Z, int ldz, int zdt, Epi epi, int n_blocks)
+{
+    constexpr int P = GemmChunk<T>::PIECES, KC = GemmChunk<T>::KC, KP = KC + 8, COLS = 16 * NT, STEPS = KC / 32, SB = 2;
+    __shared__ __align__(16) uint16_t Ws[P][COLS * KP];
+    __shared__ int w_odd;  // some of W can't be taken in pieces
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int m = lane & 15, kb = lane >> 4;
+    const int col0 = blockIdx.y * COLS, cols = min(COLS, d_out - col0);
+    const bool whole = d_in <= KC;
+    constexpr int OWN = T::BYTES == 4 ? FTC_F32 : std::is_same<T, F16>::value ? FTC_F16 : FTC_BF16;
+    auto w_index = [&](int k, int o) {
+        return TRANS ? static_cast<int64_t>(col0 + o) * w_ld + k : static_cast<int64_t>(k) * w_ld + col0 + o;
+    };
+    if (P == 3 && tid == 0) w_odd = 0;
+    for (int block = blockIdx.x; block < n_blocks; block += gridDim.x) {  // uniform
+        const int64_t row0 = (static_cast<int64_t>(block) * 4 + wave) * 16;
+        const int64_t at = min(row0 + m, static_cast<int64_t>(n) - 1) * ldx;  // clamped: stores are predicated
+        // several sums per element: of the large and of the small products (fp32); of the first and second half of a chunk (16 bits)
+        constexpr int TOTAL = P == 3 ? 1 : NT == 8 ? 1 : 2;  // 16 bits: sum over the chunks, the others are the chunk's
+        split_f32x4 acc[TOTAL + 1][NT];
+        bool odd = false;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            acc[0][nt] = acc[1][nt] = acc[TOTAL][nt] = split_f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        Eight<T> x[STEPS];
+        auto load_x = [&](int kc, Eight<T> (&to)[STEPS]) {
+#pragma unroll
+            for (int s = 0; s < STEPS; ++s)
+                if (kc + s * 32 < d_in) load_eight<T>(X, at + kc + s * 32 + kb * 8, d_in - kc - s * 32 - kb * 8, to[s]);
+        };
+        for (int kc0 = 0; kc0 < d_in; kc0 += KC) {  // uniform
+            load_x(kc0, x);
+            if (!whole || block == static_cast<int>(blockIdx.x)) {
+                __syncthreads();  // the previous chunk has been consumed
+                const int k_end = min(KC, (d_in - kc0 + 31) / 32 * 32);
+                const int units = k_end / 8 * COLS;
+#pragma unroll 1
+                for (int t0 = tid; t0 < units; t0 += 256 * SB) {  // consecutive threads: consecutive columns (TRANS: k)
+                    float w[SB][P == 3 ? 8 : 1];
+                    uint32_t h[SB][P == 3 ? 1 : 8];
+#pragma unroll
+                    for (int u = 0; u < SB; ++u) {  // all loads of SB units in flight, from clamped addresses
+                        const int t = min(t0 + u * 256, units - 1);
+                        const int o = TRANS ? t / (k_end / 8) : t % COLS, k = (TRANS ? t % (k_end / 8) : t / COLS) * 8;
+                        const int left = o < cols ? d_in - kc0 - k : 0;
+                        const int64_t at_w = left > 0 ? w_index(kc0 + k, o) : 0;
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) {
+                            const int64_t i = at_w + (j < left ? static_cast<int64_t>(j) * (TRANS ? 1 : w_ld) : 0);
+                            if constexpr (P == 3) {
+                                const float v = load_elem(W, i, TRANS ? wdt : OWN);
+                                w[u][j] = j < left ? v : 0.f;
+                            } else {
+                                const uint32_t v = static_cast<const uint16_t *>(W)[i];
+                                h[u][j] = j < left ? v : 0u;
+                            }
+                        }
+                    }
+#pragma unroll
+                    for (int u = 0; u < SB; ++u) {
+                        const int t = t0 + u * 256;
+                        if (u > 0 && t >= units) break;
+                        const int o = TRANS ? t / (k_end / 8) : t % COLS, k = (TRANS ? t % (k_end / 8) : t / COLS) * 8;
+                        if constexpr (P == 3) {
+                            uint4 p[3];
+                            if (split8(w[u], p)) w_odd = 1;
+#pragma unroll
+                            for (int q = 0; q < 3; ++q) *reinterpret_cast<uint4 *>(&Ws[q][o * KP + k]) = p[q];
+                        } else {
+                            *reinterpret_cast<uint4 *>(&Ws[0][o * KP + k]) = make_uint4(h[u][0] | (h[u][1] << 16), h[u][2] | (h[u][3] << 16),
+                                                                                       h[u][4] | (h[u][5] << 16), h[u][6] | (h[u][7] << 16));
+                        }
+                    }
+                }
+                __syncthreads();
+            }
+#pragma unroll
+            for (int s = 0; s < STEPS; ++s) {
+                if (s > 0 && kc0 + s * 32 >= d_in) break;  // uniform
+                uint4 a[3];
+                if constexpr (P == 3) odd |= split8(x[s].f, a);
+                uint4 b[2][P];  // of this tile of columns and of the next
+                auto load_b = [&](int nt) {
+#pragma unroll
+                    for (int q = 0; q < P; ++q)
+                        b[nt & 1][q] = *reinterpret_cast<const uint4 *>(&Ws[q][(nt * 16 + m) * KP + s * 32 + kb * 8]);
+                };
+                load_b(0);
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    if (nt + 1 < NT) load_b(nt + 1);
+                    asm volatile("" ::: "memory");  // (else all tiles' loads are moved up here, and their registers with them)
+                    if constexpr (P == 3) {
+                        mfma_split(a, b[nt & 1], acc[0][nt], acc[1][nt]);
+                    } else {
+                        split_f32x4 &c = acc[TOTAL == 2 ? s >> 1 : 0][nt];
+                        if constexpr (std::is_same<T, F16>::value)
+                            c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(gt_half8, x[s].h), __builtin_bit_cast(gt_half8, b[nt & 1][0]), c, 0, 0, 0);
+                        else
+                            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(split_bf16x8, x[s].h), __builtin_bit_cast(split_bf16x8, b[nt & 1][0]), c, 0, 0, 0);
+                    }
+                }
+            }
+            if constexpr (P == 1) {
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    acc[TOTAL][nt] += TOTAL == 2 ? acc[0][nt] + acc[1][nt] : acc[0][nt];
+                    acc[0][nt] = split_f32x4{0.f, 0.f, 0.f, 0.f};
+                    if constexpr (TOTAL == 2) acc[1][nt] = acc[0][nt];
+                }
+            }
+        }
+        const bool plain = P == 3 && (__builtin_amdgcn_ballot_w64(odd) != 0 || w_odd);  // this wave's rows, in fp32
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int64_t row = row0 + kb * 4 + i;
+            if (row < n) {
+                const float f = epi.factor(row);
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    const int o = nt * 16 + m;
+                    if (o < cols && !plain) store_elem(Z, row * ldz + col0 + o, zdt, epi.apply(f, P == 3 ? acc[0][nt][i] + acc[1][nt][i] : acc[TOTAL][nt][i]));
+                }
+            }
+        }
+        if (__builtin_expect(plain, 0)) {
+#pragma unroll 1
+            for (int t = lane; t < 16 * cols; t += 64) {
+                const int64_t row = row0 + t / cols;
+                const int o = t % cols;
+                if (row >= n) break;
+                float v = 0.f;
+#pragma unroll 1
+                for (int k = 0; k < d_in; ++k) v = fmaf(static_cast<const float *>(X)[row * ldx + k], load_elem(W, w_index(k, o), TRANS ? wdt : OWN), v);
+                store_elem(Z, row * ldz + col0 + o, zdt, epi.apply(epi.factor(row), v));
+            }
+        }
+    }
+}
+
+// 16-bit rows into more than 64 columns: from here on in groups of 128, which read X half as often (fp16 301 -> 128, groups of 64 /
+// 128: 40 000 rows 24 / 25 us, 400 000 223 / 180; 17 -> 128 40 000 rows 11 / 14).
+constexpr int GEMM_TILE_WIDE_ROWS = 65536;
+
+template <class T, bool TRANS>
+static void gemm_tile_t(int n, const void *X, int ldx, int d_in, const void *W, int w_ld, int wdt, int d_out, void *Z, int ldz, int zdt,
+                        Epi epi, hipStream_t s)
+{
+    const int nt = d_out <= 16 ? 1 : d_out <= 32 ? 2 : d_out <= 64 || T::BYTES == 4 || n < GEMM_TILE_WIDE_ROWS ? 4 : 8;
+    const int n_blocks = static_cast<int>((static_cast<int64_t>(n) + 63) / 64);
+    const int groups = (d_out + nt * 16 - 1) / (nt * 16);
+    const int grid = d_in <= GemmChunk<T>::KC && n_blocks > 2048 ? 2048 : n_blocks;
+#define FTC_GT(N)                                                                                                                   \
+    if (nt == N)                                                                                                                    \
+        hipLaunchKernelGGL((gemm_tile_kernel<T, N, TRANS>), dim3(grid, groups), dim3(256), 0, s, n, X, ldx, d_in, W, w_ld, wdt, d_out, Z, \
+                           ldz, zdt, epi, n_blocks)
+    FTC_GT(1);
+    FTC_GT(2);
+    FTC_GT(4);
+    if constexpr (T::BYTES == 2) FTC_GT(8);
+#undef FTC_GT
+}
+
+// Where these kernels are ahead of gemm_any_kernel: see the sides at each line (there / here, us).
+bool gemm_tile_better(int n, int dt, int d_in, int d_out)
+{
+    if (d_out > 64) return true;  // (fp32 1000 x 65 -> 128 level, 1000 x 1433 -> 128 1.37 times; fp16 1.15 to 2)
+    if (dt == FTC_F32) {
+        // up to 16 columns both wait for X: 100 000 x 1433 -> 16 139 / 138, 65 000 x 65 -> 7 6.4 / 7.2, 1 000 000 x 33 -> 2 57 / 40
+        if (d_out <= 16) return n >= 98304;
+        // few rows are split over the waves there: 12 000 x 1433 -> 32 30 / 33, 16 000 level; 9000 x 150 -> 64 9.6 / 8.7, 6000 x 150 -> 64 8.3 / 8.6
+        return n > 12288 || (n > 8192 && d_out > 32 && d_in >= 128);
+    }
+    // 16 bits: 4000 x 1433 -> 32 15 / 24 and 600 -> 32 9.4 / 9.6, where 16 waves split the contraction; 6000 x 1433 -> 32 28 / 24, 600 -> 32
+    // 18 / 10; 4000 x 65 -> 64 6.0 / 7.1, 150 -> 64 7.4 / 6.9
+    return n > 4096 || (d_out > 32 && d_in >= 128);
+}
+
+int32_t launch_gemm_tile(int n, const void *X, int ldx, int dt, int d_in, const void *W, int d_out, void *Z, int ldz, int zdt, Epi epi,
+                         hipStream_t s)
+{
+    if (dt == FTC_F32) gemm_tile_t<F32, false>(n, X, ldx, d_in, W, d_out, dt, d_out, Z, ldz, zdt, epi, s);
+    else if (dt == FTC_F16) gemm_tile_t<F16, false>(n, X, ldx, d_in, W, d_out, dt, d_out, Z, ldz, zdt, epi, s);
+    else gemm_tile_t<BF16, false>(n, X, ldx, d_in, W, d_out, dt, d_out, Z, ldz, zdt, epi, s);
+    return launch_status("update_gemm tile");
+}
+
+// dX = G W^T for G in fp32: W (d_in x d_out) is read transposed, the contraction runs over d_out.
+int32_t launch_input_grad(int n, const float *G, int ldg, int d_out, const void *W, int wdt, int d_in, void *dX, int lddx, int dx_dt,
+                          hipStream_t s)
+{
+    if (n == 0) return FTC_OK;
+    gemm_tile_t<F32, true>(n, G, ldg, d_out, W, d_out, wdt, d_in, dX, lddx, dx_dt, Epi{0, nullptr}, s);
+    return launch_status("input_grad");
+}
+
+}  // namespace ftc

@@ -1,0 +1,72 @@
+"""Dense products of any width and alignment on the 16-bit matrix cores: edges of the tiles and chunks, the lines of their
+dispatch, numbers that can't be taken in bf16 pieces, and dX = G W^T.  Compared with fp64 torch, relative to the sum of the
+absolute terms.  A sum is rounded once per 32 terms (16 bits: a quarter of that and once per 128), the terms are exact or, in
+pieces, short of 2^-24 of themselves: (d_in / 16 + 8) 2^-24 is twice that."""
+import pytest
+import torch
+
+from paper_2412_12218_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+F32, F16, BF16 = torch.float32, torch.float16, torch.bfloat16
+
+
+def bound(d_in):
+    return (d_in / 16 + 8) * 2.0 ** -24
+
+
+def rel(Z, X, W):
+    ref, terms = X.double() @ W.double(), X.double().abs() @ W.double().abs()
+    return float(((Z.double() - ref).abs() / terms.clamp(min=1e-300)).max())
+
+
+@pytest.mark.parametrize("dtype", [F32, F16, BF16])
+@pytest.mark.parametrize("n,d_in,d_out", [
+    (1, 1, 65), (15, 31, 66), (65, 32, 80), (64, 33, 128), (1000, 63, 129), (4096, 127, 64), (4097, 127, 7), (4097, 64, 33),
+    (8193, 128, 33), (12288, 65, 17), (12289, 65, 17), (16385, 129, 16), (98303, 17, 16), (98304, 17, 16), (98305, 70, 3),
+    (65535, 40, 100), (65536, 40, 200), (131073, 20, 40), (5000, 641, 65), (20001, 257, 48)])
+def test_update_gemm_at_edges_of_tiles_and_chunks(dtype, n, d_in, d_out):
+    gen = torch.Generator(device="cuda").manual_seed(n + d_in + d_out)
+    buf = torch.full((n, d_in + 3), float("nan"), device="cuda", dtype=dtype)  # rows at the alignment of an element, nothing beside them is used
+    buf[:, 1:d_in + 1] = torch.randn((n, d_in), generator=gen, device="cuda").to(dtype)
+    X = buf[:, 1:d_in + 1]
+    W = torch.randn((d_in, d_out), generator=gen, device="cuda").to(dtype)
+    out = torch.full((n, d_out + 2), 7.0, device="cuda")
+    Z = B.ftc_update_gemm(X, W, out=out[:, 1:d_out + 1])
+    assert rel(Z, X, W) <= bound(d_in)
+    assert torch.all(out[:, 0] == 7.0) and torch.all(out[:, d_out + 1] == 7.0)
+
+
+@pytest.mark.parametrize("n,d_in,d_out", [(300, 70, 70), (20000, 33, 20)])
+def test_numbers_that_bf16_pieces_cannot_hold(n, d_in, d_out):
+    """Infinities, NaN, the largest and the smallest numbers: what fp32 arithmetic makes of them."""
+    gen = torch.Generator().manual_seed(1)
+    X, W = torch.randn((n, d_in), generator=gen), torch.randn((d_in, d_out), generator=gen)
+    X[3, 2], X[5, d_in - 1], X[70, 0], X[71, 1], X[200, 7] = float("inf"), float("-inf"), float("nan"), 3.4e38, 3.3961775e38
+    X[90:110] *= 1e-38  # subnormal, or pieces of them are
+    W[2, 3] = 0.0       # infinity times zero
+    for W1 in (W, torch.where(torch.arange(d_out) == 4, W * float("inf"), W), torch.where(torch.arange(d_out) == 5, W * 1e-39, W)):
+        ref = X @ W1
+        got = B.ftc_update_gemm(X.cuda(), W1.cuda()).cpu()
+        assert torch.equal(torch.isnan(got), torch.isnan(ref)) and torch.equal(torch.isposinf(got), torch.isposinf(ref))
+        assert torch.equal(torch.isneginf(got), torch.isneginf(ref))
+        ok = torch.isfinite(ref) & (ref.abs() > 1e-30)
+        terms = X.double().abs() @ W1.double().abs()
+        err = ((got.double() - X.double() @ W1.double()).abs() / terms)[ok & torch.isfinite(terms)]
+        assert float(err.max()) <= 1e-5  # a sum of d_in terms in fp32, one after the other
+        small = ref[90:110].double().abs()
+        live = (small > 1e-37) & torch.isfinite(terms[90:110])
+        assert float(((got[90:110].double() - X[90:110].double() @ W1.double()).abs() / terms[90:110])[live].max()) <= 1e-5
+
+
+@pytest.mark.parametrize("dtype", [F32, F16, BF16])
+@pytest.mark.parametrize("n,d_in,d_out", [(1, 1, 1), (63, 17, 5), (1000, 16, 22), (4000, 33, 64), (777, 128, 65), (300, 130, 130), (70_001, 65, 8)])
+def test_input_gradient_at_edges_of_tiles_and_chunks(dtype, n, d_in, d_out):
+    gen = torch.Generator(device="cuda").manual_seed(n + d_in)
+    X = torch.randn((n, d_in), generator=gen, device="cuda").to(dtype)
+    W = torch.randn((d_in, d_out), generator=gen, device="cuda").to(dtype)
+    G = torch.randn((n, d_out + 1), generator=gen, device="cuda")[:, 1:]
+    dX = torch.full((n, d_in + 1), 7.0, device="cuda")
+    B.ftc_update_gemm_backward(X, W, G, dX=dX[:, :d_in])
+    assert rel(dX[:, :d_in], G, W.T) <= bound(d_out)
+    assert torch.all(dX[:, d_in] == 7.0)
