@@ -143,6 +143,7 @@ int32_t launch_mask_scale(int n, int d, const float *dY, int lddy, const void *Y
 }
 
 // ---- dW = X^T G -----------------------------------------------------------------------------------
+// (more than 32 columns on either side and 32 768 rows: weight_grad_tile.hip)
 // A contraction over the rows, on the matrix cores in fp32 (v_mfma_f32_16x16x4_f32; 16-bit elements of X are widened), so
 // products and sums are those of fp32 arithmetic.  A wave takes four rows per step:
 //   A operand  lane l holds VA consecutive columns of row l/16 from column a0 + VA (l%16) on (one load; 64 columns a step for
@@ -156,7 +157,7 @@ int32_t launch_mask_scale(int n, int d, const float *dY, int lddy, const void *Y
 // of G counts only where Y is positive; no masked copy of G has to exist.
 // Bound by reading X and G (2^20 x 128 fp16, 32 columns of G: 0.40 GB) up to about 64 columns of G, by the fp32 matrix
 // rate beyond.  Measured, against rows staged in LDS and 4 x 4 register tiles on the vector units (us, with the sum over
-// the shares): fp32 100 000 x 300 -> 128: 324 / 126; fp16 2^20 x 128 -> 32:
+// the shares): fp32 100 000 x 300 -> 128: 324 / 126 (weight_grad_tile.hip: 78); fp16 2^20 x 128 -> 32:
 // 250 / 128 (with the mask, before as a pass of its own: 340 / 145).
 typedef float wg_f32x4 __attribute__((ext_vector_type(4)));
 
@@ -432,7 +433,8 @@ static int weight_grad_first_columns(int n, int xdt, int d_in, int d_out)
 // be taken in groups of columns instead (rows [k0, k0 + group) of dW are one contiguous block; the passes share the workspace).
 // A wave adds up a quarter of a share's rows in one chain, so the shares are also bounded from above: with at most
 // 384 + n / 384 rows each the error stays below that of the kernel this one replaced (which had n / 1024 rows, but added
-// twice as many shares in a chain; normal inputs, 2-norm against 64 bits, former kernel / chip-filling shares / this):
+// twice as many shares in a chain; normal inputs, 2-norm against 64 bits, former kernel / chip-filling shares / weight_grad_kernel with
+// this bound; the kernel of weight_grad_tile.hip, which most of these sizes take, is below it):
 //   400 000 x 1433 -> 128 4.1e-7 / 8.6e-7 / 3.1e-7 (us 3970 / 2110 / 2030), 400 000 x 1433 -> 256 4.1e-7 / 1.2e-6 / 3.3e-7 (7430 /
 //   4330 / 3760), 2^20 x 1433 -> 128 6.1e-7 / 1.4e-6 / 4.9e-7 (8780 / 5710 / 4890), 2^20 x 1024 -> 504 6.1e-7 / 3.2e-6 / 5.0e-7
 //   (113 000 / 15 300 / 14 100), 20 000 x 1433 -> 64 2.3e-7 / 2.5e-7 / 1.9e-7 (598 / 69 / 94).
@@ -442,15 +444,17 @@ int32_t launch_weight_grad(int n, const void *X, int ldx, int xdt, int d_in, con
                            const void *Y, int ldy, int ydt, float *dW, void *ws, hipStream_t s)
 {
     const int64_t room = static_cast<int64_t>(weight_grad_blocks(n)) * weight_grad_group(d_in, d_out);  // columns x shares
-    const int first = weight_grad_first_columns(n, xdt, d_in, d_out);
+    const WgPieces pieces = weight_grad_pieces(n, d_in, d_out);
+    const int first = pieces.na ? d_out : weight_grad_first_columns(n, xdt, d_in, d_out);
     const int64_t least = n / (384 + n / 384);
     int64_t want = 0;
     for (int b = 0; b < d_out; b = b == 0 ? first : d_out) {
         const int db = b == 0 ? first : d_out - first;
-        const WgTile tile = weight_grad_tile(d_in, db);
+        const WgTile tile = pieces.na ? WgTile{pieces.na, pieces.nb, 0} : weight_grad_tile(d_in, db);
         const int64_t tiles = static_cast<int64_t>((d_in + 16 * tile.va - 1) / (16 * tile.va)) *
                               ((db + 16 * tile.nt - 1) / (16 * tile.nt));
-        const int64_t fill = (tile.nt == 4 ? 2048 : 1024) / tiles;  // with 33 to 64 columns of G more, for shorter sums
+        // with 33 to 64 columns of G more, for shorter sums; what a CU holds of the other kernel's workgroups
+        const int64_t fill = (pieces.na ? (pieces.nb == 8 ? 512 : 1024) : tile.nt == 4 ? 2048 : 1024) / tiles;
         if (fill > want) want = fill;
     }
     if (want < least) want = least;
@@ -481,11 +485,16 @@ int32_t launch_weight_grad(int n, const void *X, int ldx, int xdt, int d_in, con
             const void *Xr = static_cast<const char *>(X) + (r0 * ldx + k0) * elem_size(xdt);
             for (int b = 0; b < d_out; b = b == 0 ? first : d_out) {
                 const int db = b == 0 ? first : d_out - first;
+                const float *Gr = G + r0 * ldg + b;
+                const void *Yr = Y ? static_cast<const char *>(Y) + (r0 * ldy + b) * elem_size(ydt) : nullptr;
+                if (pieces.na && dk > 1) {  // (it loads two columns at a time)
+                    launch_weight_grad_tile(pieces, rows, Xr, ldx, xdt, dk, Gr, ldg, db, Yr, ldy, mask, limit, partial,
+                                            static_cast<int>(splits), s);
+                    continue;
+                }
                 const WgTile tile = weight_grad_tile(d_in, db);
                 const int nt = tile.nt, va = dk <= 16 ? 1 : tile.va;
                 const dim3 grid(static_cast<unsigned>(splits), (dk + 16 * va - 1) / (16 * va), (db + 16 * nt - 1) / (16 * nt));
-                const float *Gr = G + r0 * ldg + b;
-                const void *Yr = Y ? static_cast<const char *>(Y) + (r0 * ldy + b) * elem_size(ydt) : nullptr;
 #define FTC_WGT(T)                                                                                                        \
     do {                                                                                                                  \
         if (va == 1) weight_grad_t<T, 1>(nt, mask, grid, s, rows, Xr, ldx, dk, Gr, ldg, db, Yr, ldy, limit, partial + b,  \

@@ -70,3 +70,38 @@ def test_input_gradient_at_edges_of_tiles_and_chunks(dtype, n, d_in, d_out):
     B.ftc_update_gemm_backward(X, W, G, dX=dX[:, :d_in])
     assert rel(dX[:, :d_in], G, W.T) <= bound(d_out)
     assert torch.all(dX[:, d_in] == 7.0)
+
+
+@pytest.mark.parametrize("dtype", [F32, F16, BF16])
+@pytest.mark.parametrize("n,d_in,d_out", [(32768, 33, 33), (32769, 64, 64), (32800, 65, 129), (65536, 128, 128), (65537, 129, 200), (70_003, 300, 65),
+                                          (33_000, 130, 47), (40_000, 1030, 65)])
+def test_weight_gradient_at_edges_of_tiles_and_steps(dtype, n, d_in, d_out):
+    """Rows in steps of 32, a sum of shares: 2 n / 32 / shares + shares / 4 + 8 roundings (at least 64 shares here), the terms are exact."""
+    gen = torch.Generator(device="cuda").manual_seed(n + d_in)
+    buf = torch.full((n, d_in + 2), float("nan"), device="cuda", dtype=dtype)
+    buf[:, 1:d_in + 1] = torch.randn((n, d_in), generator=gen, device="cuda").to(dtype)
+    X, G = buf[:, 1:d_in + 1], torch.randn((n, d_out + 1), generator=gen, device="cuda")[:, 1:]
+    W = torch.zeros((d_in, d_out), device="cuda", dtype=dtype)
+    for Z in (None, torch.randn((n, d_out), generator=gen, device="cuda"), torch.randn((n, d_out), generator=gen, device="cuda").to(F16)):
+        masked = G if Z is None else torch.where(Z > 0, G, torch.zeros_like(G))
+        dW = B.ftc_update_gemm_backward(X, W, G, Z=Z, want_dX=False)[1]
+        ref, terms = X.double().T @ masked.double(), X.double().abs().T @ masked.double().abs()
+        assert float(((dW.double() - ref).abs() / terms).max()) <= (2 * n / 32 / 64 + 64) * 2.0 ** -24
+
+
+@pytest.mark.parametrize("dtype", [F32, F16, BF16])
+def test_weight_gradient_of_numbers_that_bf16_pieces_cannot_hold(dtype):
+    gen = torch.Generator().manual_seed(2)
+    n, d_in, d_out = 32_800, 40, 70
+    X, G = torch.randn((n, d_in), generator=gen).to(dtype), torch.randn((n, d_out), generator=gen)
+    X[100, 3], X[5000, 39], G[7, 1], G[32_799, 69], G[40, 5] = float("inf"), float("nan"), float("-inf"), float("nan"), 3.4e38
+    X[40] = 0.5
+    G[300:310] *= 1e-38
+    X[7, 2] = 0.0  # infinity times zero
+    ref = X.double().T @ G.double()
+    dW = B.ftc_update_gemm_backward(X.cuda(), torch.zeros((d_in, d_out), dtype=dtype).cuda(), G.cuda(), want_dX=False)[1].cpu()
+    assert torch.equal(torch.isnan(dW), torch.isnan(ref)) and torch.equal(torch.isinf(dW), torch.isinf(ref))
+    assert torch.equal(dW > 0, ref.float() > 0)
+    terms = X.double().abs().T @ G.double().abs()
+    ok = torch.isfinite(terms)
+    assert float(((dW.double() - ref).abs() / terms)[ok].max()) <= 1e-5
