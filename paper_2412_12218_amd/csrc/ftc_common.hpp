@@ -79,8 +79,9 @@ int32_t launch_softmax_seg(const ftc_csr &g, const ftc_windows &w, const float *
 int32_t launch_row_rnorm(int n, const void *H, int ld, int dt, int D, float *rinv, hipStream_t s);
 int32_t launch_gemm(int n, const void *X, int ldx, int dt, int d_in, const void *W, int d_out, void *Z,
                     int ldz, int zdt, Epi epi, hipStream_t s);
-// gemm_tile.hip
-bool gemm_tile_better(int n, int dt, int d_in, int d_out);
+// gemm_slice.hip, gemm_tile.hip
+int32_t launch_gemm_slice(int n, const void *X, int ldx, int dt, int d_in, const void *W, int d_out, void *Z, int ldz, int zdt, Epi epi,
+                          hipStream_t s);
 int32_t launch_gemm_tile(int n, const void *X, int ldx, int dt, int d_in, const void *W, int d_out, void *Z, int ldz, int zdt, Epi epi,
                          hipStream_t s);
 int32_t launch_input_grad(int n, const float *G, int ldg, int d_out, const void *W, int wdt, int d_in, void *dX, int lddx, int dx_dt,

@@ -1,92 +1,41 @@
-// Dense update phase Z = X * W for tall-skinny shapes: X is streamed once, W sits in LDS.  Three kernels, all on the
-// matrix cores: 16-bit inputs with d_in <= 256, d_out <= 64 and aligned rows (the benchmark models) keep all of W on chip;
-// everything else (fp32, odd widths, rows that are not 16-byte aligned) goes through the kernels of gemm_tile.hip, and through
-// gemm_any_kernel where rows are few or, in fp32, columns.
+// Dense update phase Z = X * W for tall-skinny shapes: X is streamed once, W sits in LDS.  All kernels are on the matrix cores but
+// for one: 16-bit inputs with d_in <= 256, d_out <= 64 and aligned rows (the benchmark models) keep all of W on chip; few rows are
+// split along the contraction (gemm_slice.hip); the rest (fp32, odd widths, rows that are not 16-byte aligned) goes through the
+// kernels of gemm_tile.hip, and through gemm_any_kernel for few fp32 columns.
 #include "ftc_common.hpp"
 
 namespace ftc {
 
-// The kernel for few rows (GEMM_SPLIT_ROWS), and in fp32 for few columns of any number of rows: any element type, any width, rows at
-// any alignment of their elements.  Contraction in fp32 on the matrix cores (v_mfma_f32_16x16x4_f32; 16-bit elements are widened
-// first), so products and sums are those of fp32 arithmetic.  A wave owns a tile of 16 rows of X and up to 16 NT output columns:
-//   A operand  lane l holds X[row0 + l%16][k0 + (l/16) V .. + V - 1], one 16-byte load (V = 4 or 8 elements; 64
-//              contiguous bytes per row and step); the j-th product takes element j of every lane, so the contraction
-//              index runs in steps of 4 V in an order of its own, the same for A and B;
-//   B operand  W is staged in LDS as fp32 in chunks of KC rows, four consecutive k of a column side by side: lane l
-//              reads W[k .. k + 3][n0 + l%16] as one 16-byte word.
-// Bound by the chain of chunks (few rows) or by reading X.  SK = 4 or 16: the waves of a workgroup share one row tile and split every
-// chunk's k between them (the partial sums are added in wave order through LDS): 2708 rows would otherwise occupy 43 workgroups.
+// fp32 of at most 16 columns, of more rows than gemm_slice.hip takes: any width, rows at any alignment of their elements.  Contraction in fp32
+// on the matrix cores (v_mfma_f32_16x16x4_f32).  A wave owns a tile of 16 rows of X:
+//   A operand  lane l holds X[row0 + l%16][k0 + (l/16) 4 .. + 3], one 16-byte load (64 contiguous bytes per row and step); the
+//              j-th product takes element j of every lane, so the contraction
+//              index runs in steps of 16 in an order of its own, the same for A and B;
+//   B operand  W is staged in LDS in chunks of KC rows, four consecutive k of a column side by side: lane l
+//              reads W[k .. k + 3][l%16] as one 16-byte word.
+// Bound by the chain of chunks or by reading X.
 // One tile per wave, 32 KB of W: two tiles per wave were 10 % slower, 64 KB up to 20 %, 16 KB 5 %.
-// Measured, vector units (X staged element by element in LDS, or one row per thread) against this: fp32 65 000 x 65 -> 7 6.4 us here, 7.2 in
-// gemm_tile.hip; fp16 2708 x 1433 -> 16: 311 / 10 us, 20 in gemm_tile.hip.
+// 65 000 x 65 -> 7: 6.4 us here, 7.2 in gemm_tile.hip.
 typedef float float4v __attribute__((ext_vector_type(4)));
 
-// Up to this many rows the waves split the contraction (256 workgroups of 64 rows would be the most without).
-constexpr int GEMM_SPLIT_ROWS = 16384;
-// Few rows and a long contraction are split over 16 waves instead of 4: a workgroup is a chain of chunks (stage W, wait, load X,
-// multiply), which a quarter of the chunks is a quarter of.  us, 4 / 16 waves: fp16 2708 x 1433 -> 16 14.2 / 9.8, -> 32 22.1 / 14.8, bf16
-// 2708 x 3703 -> 32 53 / 33, fp32 8000 x 1433 -> 64 52 / 45, 2708 x 500 -> 32 9.0 / 8.8; but 8000 x 300 -> 32 9.0 / 9.4, 16 000 x 1433 -> 32 46 / 55
-// (the 16-bit ones above 4096 rows: gemm_tile.hip).
-// The chunk of 16 waves has to fit into LDS: up to 64 columns in fp32, 32 in 16 bits.
-constexpr int GEMM_SPLIT16_ROWS = 8192, GEMM_SPLIT16_IN = 512;
-
-// V elements at element index idx; only the alignment of one element is assumed (global loads need no more)
-template <class T>
-__device__ __forceinline__ void load_any(const void *base, int64_t idx, float (&f)[T::VEC])
-{
-    if constexpr (T::BYTES == 4) {
-        typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
-        const f4 v = *reinterpret_cast<const f4 *>(static_cast<const float *>(base) + idx);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) f[j] = v[j];
-    } else {
-        typedef uint16_t h8 __attribute__((ext_vector_type(8), aligned(2)));
-        const h8 v = *reinterpret_cast<const h8 *>(static_cast<const uint16_t *>(base) + idx);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) f[j] = std::is_same<T, F16>::value ? f16_bits_to_f32(v[j]) : bf16_bits_to_f32(v[j]);
-    }
-}
-
-template <class T>
-__device__ __forceinline__ float load_one(const void *base, int64_t idx)
-{
-    if constexpr (T::BYTES == 4) return static_cast<const float *>(base)[idx];
-    const uint32_t b = static_cast<const uint16_t *>(base)[idx];
-    return std::is_same<T, F16>::value ? f16_bits_to_f32(b) : bf16_bits_to_f32(b);
-}
-
-template <class T, int NT, int SK>
-__global__ __launch_bounds__(SK == 16 ? 1024 : 256) void gemm_any_kernel(int n, const void *__restrict__ X, int ldx, int d_in,
-                                                       const void *__restrict__ W, int w_ld, void *__restrict__ Z, int ldz,
+__global__ __launch_bounds__(256) void gemm_any_kernel(int n, const float *__restrict__ X, int ldx, int d_in,
+                                                       const float *__restrict__ W, int d_out, void *__restrict__ Z, int ldz,
                                                        int zdt, Epi epi)
 {
-    constexpr int V = T::VEC, STEP = 4 * V;  // contraction indices per step of a wave
-    constexpr int KC = 512 / NT > SK * STEP ? 512 / NT : SK * STEP, COLS = 16 * NT, U = 4;
-    constexpr int TH = SK == 16 ? 1024 : 256;  // threads
-    static_assert(KC % (SK * STEP) == 0, "every wave takes whole steps of a chunk");
-    static_assert(SK == 1 || KC >= SK * 16, "the partial tiles fit the staging memory");
+    constexpr int STEP = 16, KC = 512, COLS = 16, U = 4, TH = 256;  // contraction indices per step of a wave, of a chunk
     __shared__ __attribute__((aligned(16))) float Ws[KC * COLS];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int m = lane & 15, kb = lane >> 4;
-    const int col0 = blockIdx.y * COLS, cols = min(COLS, w_ld - col0);
-    const int64_t row0 = (SK == 1 ? static_cast<int64_t>(blockIdx.x) * 4 + wave : static_cast<int64_t>(blockIdx.x)) * 16;
-    const int wk = SK == 1 ? 0 : wave;
-    const int64_t at = min(row0 + m, static_cast<int64_t>(n) - 1) * ldx;  // clamped: stores are predicated
+    const int64_t row0 = (static_cast<int64_t>(blockIdx.x) * 4 + wave) * 16;
+    const float *x = X + min(row0 + m, static_cast<int64_t>(n) - 1) * ldx;  // clamped: stores are predicated
     // two sums per element, of the even and of the odd products: shorter chains of dependent instructions and of roundings
-    float4v acc[2][NT];
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) acc[0][nt] = acc[1][nt] = float4v{0.f, 0.f, 0.f, 0.f};
+    float4v acc[2] = {float4v{0.f, 0.f, 0.f, 0.f}, float4v{0.f, 0.f, 0.f, 0.f}};
+    typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));  // global loads need no more than the alignment of one element
 
-    auto multiply = [&](const float (&a)[V], int k) {  // k: first index of the step inside the chunk
+    auto multiply = [&](const f4 &a, int k) {  // k: first index of the step inside the chunk
+        const float4v b = *reinterpret_cast<const float4v *>(&Ws[((k / 4 + kb) * COLS + m) * 4]);
 #pragma unroll
-        for (int q = 0; q < V / 4; ++q)
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                const float4v b = *reinterpret_cast<const float4v *>(&Ws[(((k + kb * V) / 4 + q) * COLS + nt * 16 + m) * 4]);
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    acc[j & 1][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[4 * q + j], b[j], acc[j & 1][nt], 0, 0, 0);
-            }
+        for (int j = 0; j < 4; ++j) acc[j & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], acc[j & 1], 0, 0, 0);
     };
 
     for (int kc0 = 0; kc0 < d_in; kc0 += KC) {  // uniform
@@ -98,8 +47,8 @@ __global__ __launch_bounds__(SK == 16 ? 1024 : 256) void gemm_any_kernel(int n, 
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const int k = (t0 + j * TH) / COLS, o = (t0 + j * TH) % COLS;
-                ok[j] = k < kn && kc0 + k < d_in && o < cols;
-                w[j] = load_one<T>(W, ok[j] ? static_cast<int64_t>(kc0 + k) * w_ld + col0 + o : 0);
+                ok[j] = k < kn && kc0 + k < d_in && o < d_out;
+                w[j] = W[ok[j] ? static_cast<int64_t>(kc0 + k) * d_out + o : 0];
             }
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
@@ -108,60 +57,33 @@ __global__ __launch_bounds__(SK == 16 ? 1024 : 256) void gemm_any_kernel(int n, 
             }
         }
         __syncthreads();
-        int k = wk * (KC / SK);
-        const int k_end = min(k + KC / SK, d_in - kc0);  // this wave's share of the chunk
+        int k = 0;
+        const int k_end = min(KC, d_in - kc0);
         for (; k + U * STEP <= k_end; k += U * STEP) {
-            float a[U][V];
+            f4 a[U];
 #pragma unroll
-            for (int s = 0; s < U; ++s) load_any<T>(X, at + kc0 + k + s * STEP + kb * V, a[s]);
+            for (int s = 0; s < U; ++s) a[s] = *reinterpret_cast<const f4 *>(x + kc0 + k + s * STEP + kb * 4);
 #pragma unroll
             for (int s = 0; s < U; ++s) multiply(a[s], k + s * STEP);
         }
         for (; k < k_end; k += STEP) {
-            float a[V];
+            f4 a;
             if (k + STEP <= k_end) {
-                load_any<T>(X, at + kc0 + k + kb * V, a);
+                a = *reinterpret_cast<const f4 *>(x + kc0 + k + kb * 4);
             } else {  // nothing beyond d_in is read
 #pragma unroll
-                for (int j = 0; j < V; ++j) {
-                    const int kk = k + kb * V + j;
-                    a[j] = kk < k_end ? load_one<T>(X, at + kc0 + kk) : 0.f;
+                for (int j = 0; j < 4; ++j) {
+                    const int kk = k + kb * 4 + j;
+                    a[j] = kk < k_end ? x[kc0 + kk] : 0.f;
                 }
             }
             multiply(a, k);
         }
     }
-    float4v sum[NT];
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) sum[nt] = acc[0][nt] + acc[1][nt];
-    if constexpr (SK == 1) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int64_t row = row0 + kb * 4 + i;
-            if (row < n) {
-                const float f = epi.factor(row);
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt)
-                    if (nt * 16 + m < cols) store_elem(Z, row * ldz + col0 + nt * 16 + m, zdt, epi.apply(f, sum[nt][i]));
-            }
-        }
-    } else {
-        __syncthreads();
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) Ws[(wave * 16 + kb * 4 + i) * COLS + nt * 16 + m] = sum[nt][i];
-        __syncthreads();
-        for (int t = tid; t < 16 * COLS; t += TH) {
-            const int64_t row = row0 + t / COLS;
-            const int o = t % COLS;
-            if (row < n && o < cols) {
-                float v = Ws[t];
-#pragma unroll
-                for (int w = 1; w < SK; ++w) v += Ws[w * 16 * COLS + t];
-                store_elem(Z, row * ldz + col0 + o, zdt, epi.apply(epi.factor(row), v));
-            }
-        }
+    for (int i = 0; i < 4; ++i) {
+        const int64_t row = row0 + kb * 4 + i;
+        if (row < n && m < d_out) store_elem(Z, row * ldz + m, zdt, epi.apply(epi.factor(row), acc[0][i] + acc[1][i]));
     }
 }
 
@@ -204,29 +126,6 @@ __global__ __launch_bounds__(256) void gemm_narrow_kernel(int n, const float *__
 #pragma unroll
     for (int o = 0; o < GN_OUT; ++o)
         if (o < d_out) store_elem(Z, row * ldz + o, zdt, epi.apply(f, acc[o]));
-}
-
-template <class T>
-static void gemm_any_t(int n, const void *X, int ldx, int d_in, const void *W, int d_out, void *Z, int ldz, int zdt,
-                       Epi epi, hipStream_t s)
-{
-    const bool split = n <= GEMM_SPLIT_ROWS;
-    const int64_t per = split ? 16 : 64;
-    const int nt = d_out <= 16 ? 1 : d_out <= 32 ? 2 : 4;  // (more than 64 columns: gemm_tile.hip)
-    const bool split16 = n <= GEMM_SPLIT16_ROWS && d_in >= GEMM_SPLIT16_IN && nt <= (T::BYTES == 4 ? 4 : 2);
-    const dim3 grid(static_cast<unsigned>((n + per - 1) / per), static_cast<unsigned>((d_out + nt * 16 - 1) / (nt * 16)));
-#define FTC_GA1(N, SK, TH)                                                                                                   \
-    hipLaunchKernelGGL((gemm_any_kernel<T, N, SK>), grid, dim3(TH), 0, s, n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi)
-#define FTC_GA(N)                                       \
-    if (nt == N) {                                      \
-        if constexpr (N <= (T::BYTES == 4 ? 4 : 2))     \
-            if (split16) { FTC_GA1(N, 16, 1024); return; } \
-        if (split) FTC_GA1(N, 4, 256);                  \
-        else if constexpr (N == 1 && T::BYTES == 4) FTC_GA1(N, 1, 256); \
-    }
-    FTC_GA(1) FTC_GA(2) FTC_GA(4)
-#undef FTC_GA
-#undef FTC_GA1
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -389,6 +288,24 @@ static bool gemm_mfma_t(int n, const void *X, int ldx, int d_in, const void *W, 
     return false;
 }
 
+// Few rows: where the kernel that splits the contraction (gemm_slice.hip) is ahead of the one that takes the shape otherwise.  us, other / split:
+//   16 bits   gemm_mfma_kernel (`on_chip`): fp16 2708 x 256 -> 64 8.2 / 3.7, 2708 x 128 -> 16 3.4 / 2.2, 16 000 x 64 -> 32 3.4 / 3.1, 8000 x 32 -> 32 2.8 / 2.7,
+//             4096 x 16 -> 16 2.3 / 2.3; but 24 000 x 64 -> 32 3.6 / 3.6, 16 000 x 32 -> 32 3.0 / 3.1, 6000 x 16 -> 16 2.4 / 2.6
+//             gemm_tile.hip: 16 000 x 1433 -> 64 74 / 43, -> 7 25 / 25, 12 000 x 513 -> 128 31 / 28; but 24 000 x 301 -> 7 9.1 / 9.4, 16 000 x 16 -> 128 7.3 / 7.6
+//   fp32      gemm_narrow_kernel: 2708 x 16 -> 7 3.7 / 2.8, 16 000 x 16 -> 7 3.8 / 3.7 (24 000 3.8 / 4.2); gemm_any_kernel: 16 000 x 301 -> 16 7.7 / 5.8,
+//             24 000 x 513 -> 7 14.9 / 17.0; gemm_tile.hip: 12 000 x 150 -> 64 9.9 / 8.1, 6000 x 513 -> 128 22.7 / 21.6; but 12 000 x 16 -> 32 4.1 / 4.2,
+//             16 000 x 150 -> 64 10.2 / 11.0, 8192 x 513 -> 128 23.2 / 25.7
+static bool gemm_slice_better(int n, int dt, int d_in, int d_out, bool on_chip)
+{
+    if (dt != FTC_F32) {
+        if (on_chip) return n <= (d_in >= 64 ? 16384 : d_in >= 32 ? 8192 : 4096);
+        return n <= (d_out <= 64 ? 16384 : 12288);
+    }
+    if (d_out <= 16) return n <= 16384;
+    if (d_out <= 64) return n <= (d_in >= 32 ? 12288 : 8192);
+    return n <= 6144;
+}
+
 int32_t launch_gemm(int n, const void *X, int ldx, int dt, int d_in, const void *W, int d_out, void *Z, int ldz,
                     int zdt, Epi epi, hipStream_t s)
 {
@@ -396,24 +313,26 @@ int32_t launch_gemm(int n, const void *X, int ldx, int dt, int d_in, const void 
     const int v = dt == FTC_F32 ? 4 : 8;
     // vector loads of X: 16-byte aligned rows, whole vectors
     const bool fast = aligned16(X) && (static_cast<int64_t>(ldx) * elem_size(dt)) % 16 == 0 && d_in % v == 0;
-    // 16-bit inputs: matrix cores (needs 16-byte row pieces of X)
-    const bool rows16 = aligned16(X) && (static_cast<int64_t>(ldx) * elem_size(dt)) % 16 == 0;
-    if (dt != FTC_F32 && rows16) {
-        const bool done = fast && (dt == FTC_F16 ? gemm_mfma_t<F16>(n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi, s)
-                                                 : gemm_mfma_t<BF16>(n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi, s));
+    const bool on_chip = dt != FTC_F32 && fast && d_in <= 256 && d_out <= 64;
+    const bool narrow = dt == FTC_F32 && fast && narrow_shape(d_in, d_out);
+    if (gemm_slice_better(n, dt, d_in, d_out, on_chip) && !(narrow && d_in < 16))
+        return launch_gemm_slice(n, X, ldx, dt, d_in, W, d_out, Z, ldz, zdt, epi, s);
+    if (dt != FTC_F32 && fast) {  // 16-byte row pieces of X: all of W on chip
+        const bool done = dt == FTC_F16 ? gemm_mfma_t<F16>(n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi, s)
+                                        : gemm_mfma_t<BF16>(n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi, s);
         if (done) return launch_status("update_gemm mfma");
     }
-    if (dt == FTC_F32 && fast && narrow_shape(d_in, d_out)) {
+    if (narrow) {
         const dim3 grid(static_cast<unsigned>((static_cast<int64_t>(n) + 255) / 256));
         const float *x = static_cast<const float *>(X), *w = static_cast<const float *>(W);
         if (d_out <= 8) hipLaunchKernelGGL(gemm_narrow_kernel<8>, grid, dim3(256), 0, s, n, x, ldx, d_in, w, d_out, Z, ldz, zdt, epi);
         else hipLaunchKernelGGL(gemm_narrow_kernel<12>, grid, dim3(256), 0, s, n, x, ldx, d_in, w, d_out, Z, ldz, zdt, epi);
         return launch_status("update_gemm narrow");
     }
-    if (gemm_tile_better(n, dt, d_in, d_out)) return launch_gemm_tile(n, X, ldx, dt, d_in, W, d_out, Z, ldz, zdt, epi, s);
-    if (dt == FTC_F32) gemm_any_t<F32>(n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi, s);
-    else if (dt == FTC_F16) gemm_any_t<F16>(n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi, s);
-    else gemm_any_t<BF16>(n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi, s);
+    // up to 16 fp32 columns both wait for X: 100 000 x 1433 -> 16 139 (gemm_tile.hip) / 138, 65 000 x 65 -> 7 7.2 / 6.4, 1 000 000 x 33 -> 2 40 / 57
+    if (dt != FTC_F32 || d_out > 16 || n >= 98304) return launch_gemm_tile(n, X, ldx, dt, d_in, W, d_out, Z, ldz, zdt, epi, s);
+    hipLaunchKernelGGL(gemm_any_kernel, dim3(static_cast<unsigned>((n + 63) / 64)), dim3(256), 0, s, n, static_cast<const float *>(X), ldx, d_in,
+                       static_cast<const float *>(W), d_out, Z, ldz, zdt, epi);
     return launch_status("update_gemm");
 }
 

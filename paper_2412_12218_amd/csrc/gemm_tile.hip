@@ -234,21 +234,6 @@ static void gemm_tile_t(int n, const void *X, int ldx, int d_in, const void *W, 
 #undef FTC_GT
 }
 
-// Where these kernels are ahead of gemm_any_kernel: see the sides at each line (there / here, us).
-bool gemm_tile_better(int n, int dt, int d_in, int d_out)
-{
-    if (d_out > 64) return true;  // (fp32 1000 x 65 -> 128 level, 1000 x 1433 -> 128 1.37 times; fp16 1.15 to 2)
-    if (dt == FTC_F32) {
-        // up to 16 columns both wait for X: 100 000 x 1433 -> 16 139 / 138, 65 000 x 65 -> 7 6.4 / 7.2, 1 000 000 x 33 -> 2 57 / 40
-        if (d_out <= 16) return n >= 98304;
-        // few rows are split over the waves there: 12 000 x 1433 -> 32 30 / 33, 16 000 level; 9000 x 150 -> 64 9.6 / 8.7, 6000 x 150 -> 64 8.3 / 8.6
-        return n > 12288 || (n > 8192 && d_out > 32 && d_in >= 128);
-    }
-    // 16 bits: 4000 x 1433 -> 32 15 / 24 and 600 -> 32 9.4 / 9.6, where 16 waves split the contraction; 6000 x 1433 -> 32 28 / 24, 600 -> 32
-    // 18 / 10; 4000 x 65 -> 64 6.0 / 7.1, 150 -> 64 7.4 / 6.9
-    return n > 4096 || (d_out > 32 && d_in >= 128);
-}
-
 int32_t launch_gemm_tile(int n, const void *X, int ldx, int dt, int d_in, const void *W, int d_out, void *Z, int ldz, int zdt, Epi epi,
                          hipStream_t s)
 {
