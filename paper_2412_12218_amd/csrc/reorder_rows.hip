@@ -4,14 +4,14 @@
 // Rows are independent, so nothing is sorted across rows: a row is sorted where it fits,
 //   at most 16 / 32 / 64        a quarter, half or whole wave, one entry per lane (bitonic, data-parallel-primitive moves),
 //   at most 256 / 1024          a wave, 4 / 16 entries per lane,
-//   at most 8192                a workgroup of 1024 threads, in LDS,
+//   at most 4096 / 8192         a workgroup of 256 / 1024 threads, in registers and LDS,
 //   longer                      a bitmap of the columns in LDS (relabelling; duplicates: counters, see below) or
 //                               counters in LDS per 32 768 labels (label propagation); with more than 2^19 nodes those of
 //                               at most 32 768 entries are sorted in LDS instead of counted (many_ranges()).
 // What bounds them: the look-up.  Every entry is one 4-byte gather from an array that about fills an L2 (4 MB at
 // a million nodes); the streams around it (column ids in, columns out) are read and written once, non-temporal.
-// On the block model with a million nodes and 32 M entries a round of label propagation takes 0.21 ms and the
-// relabelled graph 0.33 ms (R-MAT, 2^20 nodes: 0.48); sorting all entries by label and row with the global radix sort took
+// On the block model with a million nodes and 32 M entries a round of label propagation takes 0.22 ms (the first, without look-ups, 0.08,
+// ten together 1.81: see vote_check_kernel) and the relabelled graph 0.33 ms (R-MAT, 2^20 nodes: 0.31); sorting all entries by label and row with the global radix sort took
 // 4.0 and 4.1 ms.  The sorting network is the other half: with min, max and a selection per stage, rows of 33 to 64 two at a time,
 // rows of any length below side by side in halves of the wave and each row's look-ups waiting for the one's before, a round took
 // 0.24 ms (500 000 nodes with nine entries each, the whole plan: 1.39 / 1.01 ms).
@@ -25,23 +25,26 @@ namespace ftc {
 
 constexpr int RS_ROWS = 32;         // consecutive rows per wave of the short-row part
 constexpr int RS_SHORT = 64;        // longest row handled there; the queues hold the rows above
-constexpr int RS_MID = 256, RS_LONG = 1024, RS_LDS = 8192;  // longest row of queues 0, 1, 2; queue 3 has the rest
-constexpr int RS_LDS_MOST = 32768;  // longest row of queue 2 in label propagation on many nodes (many_ranges())
+constexpr int RS_MID = 256, RS_LONG = 1024, RS_GROUP = 4096, RS_LDS = 8192;  // longest row of queues 0, 1, 2, 3; queue 4 has the rest
+constexpr int RS_QUEUES = 5;
+constexpr int RS_LDS_MOST = 32768;  // longest row of queue 3 in label propagation on many nodes (many_ranges())
 constexpr int RS_RANGE = 32768;     // counters per pass over a long row
 constexpr int RS_WORDS = RS_RANGE + RS_RANGE / 32;  // LDS words of the workgroups that take long rows
 constexpr int RS_BITS_LOG2 = 20;    // columns per bitmap pass over a long row (32 768 words)
+constexpr int VT_COUNTERS = 256;
 constexpr int RS_NONE = 0x7fffffff; // sorts behind every column and label
 
 // lengths of the rows: len[r] = rp[r + 1] - rp[r]; counts[q] rows of class q in rows[q]
 struct RowQueues {
     int *counts;
-    int *rows[4];
-    int *dup_rows;               // relabelling: long rows with duplicate columns, counts[4] of them
-    unsigned long long *best;    // label propagation: winner of every row of queue 3
+    int *rows[RS_QUEUES];
+    int *dup_rows;               // relabelling: long rows with duplicate columns, counts[RS_QUEUES] of them; label propagation:
+                                 // ranges of every row of queue 4 that have been counted
+    unsigned long long *best;    // label propagation: winner of every row of queue 4
     int *values;                 // what the columns of the counted rows become, at the place of the entry; NULL: not kept
 };
 
-// Passes over a row longer than queue 2's: counters for RS_RANGE of the n values each.
+// Passes over a row longer than queue 3's: counters for RS_RANGE of the n values each.
 __host__ __device__ inline int value_ranges(int n) { return (n + RS_RANGE - 1) / RS_RANGE; }
 
 // From this many passes on rows of up to 32 768 entries are sorted instead of counted (an entry costs about 25 ps sorted, 6 a
@@ -57,19 +60,19 @@ __host__ __device__ inline bool many_ranges(int n) { return value_ranges(n) > 16
 __global__ __launch_bounds__(1024) void row_classes_kernel(int n, const int *__restrict__ rp, int in_lds, RowQueues q)
 {
     constexpr int PER = 4;
-    __shared__ int cnt_s[4], base_s[4];
-    if (threadIdx.x < 4) cnt_s[threadIdx.x] = 0;
+    __shared__ int cnt_s[RS_QUEUES], base_s[RS_QUEUES];
+    if (threadIdx.x < RS_QUEUES) cnt_s[threadIdx.x] = 0;
     __syncthreads();
     int cls[PER], pos[PER];
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         const int64_t r = (static_cast<int64_t>(blockIdx.x) * PER + k) * 1024 + threadIdx.x;
         const int len = r < n ? rp[r + 1] - rp[r] : 0;
-        cls[k] = len <= RS_SHORT ? -1 : len <= RS_MID ? 0 : len <= RS_LONG ? 1 : len <= in_lds ? 2 : 3;
+        cls[k] = len <= RS_SHORT ? -1 : len <= RS_MID ? 0 : len <= RS_LONG ? 1 : len <= RS_GROUP ? 2 : len <= in_lds ? 3 : 4;
         pos[k] = cls[k] >= 0 ? atomicAdd(&cnt_s[cls[k]], 1) : 0;
     }
     __syncthreads();
-    if (threadIdx.x < 4 && cnt_s[threadIdx.x] > 0) base_s[threadIdx.x] = atomicAdd(&q.counts[threadIdx.x], cnt_s[threadIdx.x]);
+    if (threadIdx.x < RS_QUEUES && cnt_s[threadIdx.x] > 0) base_s[threadIdx.x] = atomicAdd(&q.counts[threadIdx.x], cnt_s[threadIdx.x]);
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < PER; ++k)
@@ -83,7 +86,7 @@ __global__ __launch_bounds__(1024) void row_classes_kernel(int n, const int *__r
 // end, so that the look-ups of several rows would follow one another instead of being in flight together.
 __device__ __forceinline__ int lookup_index(int c, int n) { return static_cast<unsigned>(c) < static_cast<unsigned>(n) ? c : 0; }
 struct Relabel {
-    static constexpr bool VOTES = false;
+    static constexpr bool VOTES = false, FIRST = false;
     int n;
     const int *row_ptr, *col_idx, *perm, *map, *rp;  // map: inv; rp: row starts of the relabelled graph
     int *out, *flag;
@@ -98,20 +101,46 @@ struct Relabel {
         atomicOr(flag, 1);
         return 0;
     }
-    __device__ __forceinline__ int value(int c) const { return settle(c, map[lookup_index(c, n)], true); }
+    __device__ __forceinline__ int look(int c) const { return map[lookup_index(c, n)]; }
+    __device__ __forceinline__ int value(int c) const { return settle(c, look(c), true); }
 };
+// FIRST: the first round, in which every node's label is its own id and nothing is looked up.
+template <bool FIRST_ROUND>
 struct Votes {
-    static constexpr bool VOTES = true;
+    static constexpr bool VOTES = true, FIRST = FIRST_ROUND;
     int n;
     const int *col_idx, *map, *rp;  // map: labels of the round before
     int *out;                       // labels of this round
+    uint32_t *changed;              // bit r >> shift of every row r whose label is another than before is set; NULL: not kept
+    int *changes;                   // .. and counted, spread over VT_COUNTERS
+    int shift;
+    const uint32_t *todo;           // rows of at most RS_SHORT entries that may change, a bit each; NULL: all
     __device__ __forceinline__ void row(int r, int &start, int &len) const
     {
         start = rp[r];
         len = rp[r + 1] - start;
     }
     __device__ __forceinline__ int settle(int c, int v, bool) const { return c >= 0 && c < n ? v : 0; }  // out of range: a vote for label 0
-    __device__ __forceinline__ int value(int c) const { return settle(c, map[lookup_index(c, n)], true); }
+    __device__ __forceinline__ int look(int c) const
+    {
+        if constexpr (FIRST) return c;
+        else return map[lookup_index(c, n)];
+    }
+    __device__ __forceinline__ int value(int c) const { return settle(c, look(c), true); }
+    __device__ __forceinline__ int before(int r) const
+    {
+        if constexpr (FIRST) return r;
+        else return map[r];
+    }
+    // one row's winner, by one lane
+    __device__ __forceinline__ void vote(int r, int w) const
+    {
+        out[r] = w;
+        if (changed && before(r) != w) {
+            atomicOr(&changed[(r >> shift) >> 5], 1u << ((r >> shift) & 31));
+            atomicAdd(&changes[r & (VT_COUNTERS - 1)], 1);
+        }
+    }
 };
 
 // ---- sorting in registers ------------------------------------------------------------------------------
@@ -247,7 +276,7 @@ __device__ __forceinline__ void row_done(const Use &u, int r, int dst, int len, 
     const int li = lane & (W - 1);
     if constexpr (Use::VOTES) {
         const int w = longest_run<K, W>(v, len, lane);
-        if (li == 0 && len > 0) u.out[r] = w;
+        if (li == 0 && len > 0) u.vote(r, w);
     } else {
 #pragma unroll
         for (int k = 0; k < K; ++k)
@@ -257,15 +286,13 @@ __device__ __forceinline__ void row_done(const Use &u, int r, int dst, int len, 
 
 // one row of a queue by one wave, K entries per lane
 template <class Use, int K>
-__device__ __forceinline__ void queued_row(const Use &u, int r, int lane)
+__device__ __forceinline__ void queued_row(const Use &u, int r, int start, int len, int lane)
 {
-    int start, len;
-    u.row(r, start, len);
     int c[K], v[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) c[k] = __builtin_nontemporal_load(u.col_idx + start + min(k * 64 + lane, len - 1));  // (no queued row is empty)
 #pragma unroll
-    for (int k = 0; k < K; ++k) v[k] = u.map[lookup_index(c[k], u.n)];
+    for (int k = 0; k < K; ++k) v[k] = u.look(c[k]);
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const bool in = k * 64 + lane < len;
@@ -277,9 +304,9 @@ __device__ __forceinline__ void queued_row(const Use &u, int r, int lane)
 }
 
 // The rows among the wave's RS_ROWS with more than `above` and at most W entries: 64 / W of them side by side in the wave, SETS such
-// sets in flight.  order: LDS of the wave.
+// sets in flight.  order, changed: LDS of the wave; votes: bit r - r0 of *changed is set where the label of row r is another than old_l.
 template <class Use, int W, int SETS>
-__device__ __forceinline__ void short_rows(const Use &u, int r0, int above, int start_l, int len_l, int dst_l, int lane, int *order)
+__device__ __forceinline__ void short_rows(const Use &u, int r0, int above, int start_l, int len_l, int dst_l, int old_l, int lane, int *order, uint32_t *changed)
 {
     constexpr int PER = 64 / W;
     const int part = lane / W, li = lane % W;
@@ -291,7 +318,7 @@ __device__ __forceinline__ void short_rows(const Use &u, int r0, int above, int 
     if (mine) order[__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(rows >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(rows), 0u))] = lane;
     wave_lds_sync();
     for (int s0 = 0; s0 < count; s0 += PER * SETS) {
-        int t[SETS], len[SETS], c[SETS], v[SETS];
+        int t[SETS], len[SETS], c[SETS], v[SETS], old[SETS];
 #pragma unroll
         for (int p = 0; p < SETS; ++p) {
             const int at = s0 + p * PER + part;
@@ -299,16 +326,30 @@ __device__ __forceinline__ void short_rows(const Use &u, int r0, int above, int 
             const int st = __shfl(start_l, t[p], 64), ln = __shfl(len_l, t[p], 64);
             c[p] = __builtin_nontemporal_load(u.col_idx + st + min(li, ln - 1));
             len[p] = at < count ? ln : 0;
+            old[p] = Use::VOTES ? __shfl(old_l, t[p], 64) : 0;
         }
 #pragma unroll
-        for (int p = 0; p < SETS; ++p) v[p] = u.map[lookup_index(c[p], u.n)];
+        for (int p = 0; p < SETS; ++p) v[p] = u.look(c[p]);
 #pragma unroll
         for (int p = 0; p < SETS; ++p) {
             if (s0 + p * PER >= count) break;  // uniform
             const bool in = li < len[p];
             int x[1] = {u.settle(c[p], v[p], in)};
             if (!in) x[0] = RS_NONE;
-            if constexpr (Use::VOTES && W > 16) {
+            auto vote = [&](int w) {
+                if constexpr (Use::VOTES) {
+                    u.out[r0 + t[p]] = w;
+                    if (u.changed && w != old[p]) atomicOr(changed, 1u << t[p]);
+                }
+            };
+            if constexpr (Use::FIRST) {
+                // distinct columns in ascending order have a vote each, and the first is the smallest
+                const int prev = __builtin_amdgcn_update_dpp(0, x[0], 0x138, 0xf, 0xf, false);  // wave_shr:1
+                if (__builtin_amdgcn_ballot_w64(in && li > 0 && x[0] <= prev) == 0ull) {
+                    if (li == 0 && len[p] > 0) vote(x[0]);
+                    continue;
+                }
+            } else if constexpr (Use::VOTES && W > 16) {
                 // a label that more than half of a row's entries hold wins without any sorting; two of the entries are tried.
                 // Labels settle after a few rounds and most rows pass then
                 const int c0 = __shfl(x[0], lane & ~(W - 1), 64), c1 = __shfl(x[0], (lane & ~(W - 1)) + 7, 64);
@@ -319,52 +360,20 @@ __device__ __forceinline__ void short_rows(const Use &u, int r0, int above, int 
                 }
                 const bool won0 = 2 * __popcll(e0) > len[p], won1 = 2 * __popcll(e1) > len[p];
                 if (__builtin_amdgcn_ballot_w64(len[p] > 0 && !won0 && !won1) == 0ull) {
-                    if (li == 0 && len[p] > 0) u.out[r0 + t[p]] = won0 ? c0 : c1;
+                    if (li == 0 && len[p] > 0) vote(won0 ? c0 : c1);
                     continue;
                 }
             }
             bitonic_sort<W, 1, W>(x);
-            row_done<Use, 1, W>(u, r0 + t[p], __shfl(dst_l, t[p], 64), len[p], x, lane);
+            if constexpr (Use::VOTES) {
+                const int w = longest_run<1, W>(x, len[p], lane);
+                if (li == 0 && len[p] > 0) vote(w);
+            } else row_done<Use, 1, W>(u, r0 + t[p], __shfl(dst_l, t[p], 64), len[p], x, lane);
         }
     }
 }
 
-// Workgroups below `queue_blocks` take the rows of 65 to 1024 entries from the queues, one wave a row; the
-// others take RS_ROWS consecutive rows per wave and sort the short ones among them: rows of at most 16 entries four at
-// a time, of at most 32 two at a time, then those of 33 to 64; four sets in flight.
-template <class Use>
-__global__ __launch_bounds__(256, 6) void row_sort_kernel(Use u, RowQueues q, int queue_blocks)
-{
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (static_cast<int>(blockIdx.x) < queue_blocks) {
-        const int first = blockIdx.x * 4 + wave, step = queue_blocks * 4;
-        const int n1 = q.counts[1], n0 = q.counts[0];
-        if constexpr (Use::VOTES) {  // the rows above RS_LDS collect their winner in q.best (row_sort_big_kernel)
-            const int n3 = q.counts[3];
-            for (int i = blockIdx.x * 256 + threadIdx.x; i < n3; i += queue_blocks * 256) q.best[i] = 0ull;
-        }
-        for (int i = first; i < n1; i += step) queued_row<Use, RS_LONG / 64>(u, q.rows[1][i], lane);
-        for (int i = first; i < n0; i += step) queued_row<Use, RS_MID / 64>(u, q.rows[0][i], lane);
-        return;
-    }
-    const int64_t r0 = (static_cast<int64_t>(blockIdx.x - queue_blocks) * 4 + wave) * RS_ROWS;
-    if (r0 >= u.n) return;
-    int start_l = 0, len_l = 0, dst_l = 0;
-    const int r_l = static_cast<int>(r0) + lane;
-    if (lane < RS_ROWS && r_l < u.n) {
-        u.row(r_l, start_l, len_l);
-        dst_l = u.rp[r_l];
-        if constexpr (Use::VOTES) {
-            if (len_l == 0) u.out[r_l] = u.map[r_l];  // a row without entries keeps its label
-        }
-    }
-    __shared__ int order[4][RS_ROWS];
-    short_rows<Use, 16, 4>(u, static_cast<int>(r0), 0, start_l, len_l, dst_l, lane, order[wave]);
-    short_rows<Use, 32, 4>(u, static_cast<int>(r0), 16, start_l, len_l, dst_l, lane, order[wave]);
-    short_rows<Use, 64, 4>(u, static_cast<int>(r0), 32, start_l, len_l, dst_l, lane, order[wave]);
-}
-
-// ---- rows above 1024 entries: a workgroup of 1024 threads ------------------------------------------------
+// ---- rows above 1024 entries: a workgroup of 256 (up to RS_GROUP entries) or 1024 threads ---------------------
 constexpr int RS_NT = 1024;
 
 // exclusive sum over the workgroup; every thread gets its prefix, *total the sum
@@ -385,7 +394,8 @@ __device__ __forceinline__ int group_exclusive_scan(int v, int *total, int *tmp)
     return before + incl - v;
 }
 
-// largest value over the workgroup, valid in thread 0
+// largest value over a workgroup of NT threads, valid in thread 0
+template <int NT>
 __device__ __forceinline__ unsigned long long group_max_u64(unsigned long long v, unsigned long long *tmp)
 {
 #pragma unroll
@@ -397,7 +407,7 @@ __device__ __forceinline__ unsigned long long group_max_u64(unsigned long long v
     if ((threadIdx.x & 63) == 0) tmp[threadIdx.x >> 6] = v;
     __syncthreads();
     if (threadIdx.x == 0)
-        for (int w = 1; w < RS_NT / 64; ++w) v = tmp[w] > v ? tmp[w] : v;
+        for (int w = 1; w < NT / 64; ++w) v = tmp[w] > v ? tmp[w] : v;
     return v;
 }
 
@@ -407,16 +417,17 @@ __device__ __forceinline__ unsigned long long ballot_of(int votes, int label)
     return (static_cast<unsigned long long>(static_cast<uint32_t>(votes)) << 32) | (0xffffffffu - static_cast<uint32_t>(label));
 }
 
-// 1025 .. 1024 K entries by 16 waves, K per lane (element i of the padded row in wave i / (64 K), register i / 64 % K, lane
+// At most NT K entries by NT / 64 waves, K per lane (element i of the padded row in wave i / (64 K), register i / 64 % K, lane
 // i % 64).  Every wave sorts its share in registers, then the shares are merged: only the steps whose partner sits in
 // another wave go through LDS (ten of them, in two buffers taken in turn with one barrier each, or for K = 32 in one buffer with
 // two), the rest stays in registers.
 // A share that has to descend is sorted as its complement.  (All steps in LDS, 66 to 91
-// barriers a row: the kernel takes 0.60 ms on the R-MAT graph, this way 0.26.)
-template <class Use, int K>
+// barriers a row: 0.60 ms on the R-MAT graph, this way 0.26; rows of up to 4096 entries by four waves beside the shorter rows instead of by
+// sixteen, alone on a compute unit, after them: relabelled R-MAT graph 0.46 / 0.37 ms, ten rounds of label propagation 6.5 / 4.8.)
+template <class Use, int K, int NT, int BUF>
 __device__ __forceinline__ void group_row(const Use &u, int r, int start, int len, int *s, unsigned long long *tmp)
 {
-    constexpr int SHARE = 64 * K, ALL = RS_NT * K;
+    constexpr int SHARE = 64 * K, ALL = NT * K;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, base = wave * SHARE;
     int v[K];
 #pragma unroll
@@ -446,7 +457,7 @@ __device__ __forceinline__ void group_row(const Use &u, int r, int start, int le
                 const int o = buf[(base ^ stride) + k * 64 + lane];
                 v[k] = low ? min(v[k], o) : max(v[k], o);
             }
-            if constexpr (2 * ALL <= RS_WORDS) buf = buf == s ? s + ALL : s;  // the next step writes where nobody reads any more
+            if constexpr (2 * ALL <= BUF) buf = buf == s ? s + ALL : s;  // the next step writes where nobody reads any more
             else __syncthreads();
         }
         const int flip = up ? 0 : -1;
@@ -461,7 +472,7 @@ __device__ __forceinline__ void group_row(const Use &u, int r, int start, int le
         for (int k = 0; k < K; ++k) buf[base + k * 64 + lane] = v[k];
         __syncthreads();
         unsigned long long best = 0ull;
-        for (int i = threadIdx.x; i < len; i += RS_NT) {
+        for (int i = threadIdx.x; i < len; i += NT) {
             const int x = buf[i];
             if (i > 0 && buf[i - 1] == x) continue;
             int lo = i + 1, hi = len;  // first element of the next run
@@ -472,8 +483,8 @@ __device__ __forceinline__ void group_row(const Use &u, int r, int start, int le
             const unsigned long long cand = ballot_of(lo - i, x);
             best = cand > best ? cand : best;
         }
-        best = group_max_u64(best, tmp);
-        if (threadIdx.x == 0) u.out[r] = static_cast<int>(0xffffffffu - static_cast<uint32_t>(best & 0xffffffffull));
+        best = group_max_u64<NT>(best, tmp);
+        if (threadIdx.x == 0) u.vote(r, static_cast<int>(0xffffffffu - static_cast<uint32_t>(best & 0xffffffffull)));
     } else {
         const int dst = u.rp[r];
 #pragma unroll
@@ -482,23 +493,129 @@ __device__ __forceinline__ void group_row(const Use &u, int r, int start, int le
     }
 }
 
+// entries first, first + step, .. of a row looked up, eight in flight a thread
+template <class Use>
+__device__ __forceinline__ void look_up_row(const Use &u, int start, int len, int first, int step, int *__restrict__ values)
+{
+    for (int64_t i0 = first; i0 < len; i0 += static_cast<int64_t>(step) * 8) {
+        int c[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) c[k] = u.col_idx[start + min(i0 + static_cast<int64_t>(k) * step, static_cast<int64_t>(len - 1))];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) c[k] = u.value(c[k]);
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (i0 + static_cast<int64_t>(k) * step < len) values[start + i0 + static_cast<int64_t>(k) * step] = c[k];
+    }
+}
+
+// Workgroups below `queue_blocks` take the rows of 65 to 4096 entries from the queues, those of 1025 and more one at a time, the
+// others one per wave; the
+// others take RS_ROWS consecutive rows per wave and sort the short ones among them: rows of at most 16 entries four at
+// a time, of at most 32 two at a time, then those of 33 to 64; four sets in flight.
+template <class Use>
+__global__ __launch_bounds__(256, 6) void row_sort_kernel(Use u, RowQueues q, int queue_blocks)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (static_cast<int>(blockIdx.x) < queue_blocks) {
+        const int first = blockIdx.x * 4 + wave, step = queue_blocks * 4;
+        const int n2 = q.counts[2], n1 = q.counts[1], n0 = q.counts[0];
+        if constexpr (Use::VOTES) {  // the rows that are counted collect their winner in q.best (row_sort_big_kernel)
+            const int n4 = q.counts[4];
+            for (int i = blockIdx.x * 256 + threadIdx.x; i < n4; i += queue_blocks * 256) {
+                q.best[i] = 0ull;
+                q.dup_rows[i] = 0;
+            }
+            // what they are looked up to, once for all passes, the workgroups spread over the rows
+            const int parts = n4 > 0 ? max(queue_blocks / n4, 1) : 0;
+            for (int h = n4 > 0 ? blockIdx.x % min(n4, queue_blocks) : 0; q.values && h < n4; h += queue_blocks) {
+                const int part = blockIdx.x / min(n4, queue_blocks);
+                if (part >= parts) break;
+                int start, len;
+                u.row(q.rows[4][h], start, len);
+                look_up_row(u, start, len, part * 256 + threadIdx.x, parts * 256, q.values);
+            }
+        }
+        __shared__ int s[RS_GROUP];
+        __shared__ unsigned long long tmp64[4];
+        for (int i = blockIdx.x; i < n2; i += queue_blocks) {  // uniform
+            const int r = q.rows[2][i];
+            int start, len;
+            u.row(r, start, len);
+            if (len <= RS_GROUP / 2) group_row<Use, RS_GROUP / 512, 256, RS_GROUP>(u, r, start, len, s, tmp64);
+            else group_row<Use, RS_GROUP / 256, 256, RS_GROUP>(u, r, start, len, s, tmp64);
+        }
+        // the network of half the size costs 0.4 of the whole one, and most rows of a class need no more (all in whole ones: relabelled R-MAT
+        // graph 0.30 ms of this kernel for 0.25, ten rounds of label propagation 4.8 for 4.2)
+        for (int i = first; i < n1; i += step) {
+            const int r = q.rows[1][i];
+            int start, len;
+            u.row(r, start, len);
+            if (len <= RS_LONG / 2) queued_row<Use, RS_LONG / 128>(u, r, start, len, lane);
+            else queued_row<Use, RS_LONG / 64>(u, r, start, len, lane);
+        }
+        for (int i = first; i < n0; i += step) {
+            const int r = q.rows[0][i];
+            int start, len;
+            u.row(r, start, len);
+            if (len <= RS_MID / 2) queued_row<Use, RS_MID / 128>(u, r, start, len, lane);
+            else queued_row<Use, RS_MID / 64>(u, r, start, len, lane);
+        }
+        return;
+    }
+    const int64_t r0 = (static_cast<int64_t>(blockIdx.x - queue_blocks) * 4 + wave) * RS_ROWS;
+    if (r0 >= u.n) return;
+    int start_l = 0, len_l = 0, dst_l = 0, old_l = 0;
+    const int r_l = static_cast<int>(r0) + lane;
+    if (lane < RS_ROWS && r_l < u.n) {
+        u.row(r_l, start_l, len_l);
+        dst_l = u.rp[r_l];
+        if constexpr (Use::VOTES) {
+            old_l = u.before(r_l);
+            if (u.todo && len_l <= RS_SHORT && !(u.todo[r0 >> 5] >> lane & 1u)) len_l = 0;  // nothing in the row has changed
+            if (len_l == 0) u.out[r_l] = old_l;  // as does a row without entries, it keeps its label
+        }
+    }
+    __shared__ int order[4][RS_ROWS];
+    __shared__ uint32_t changed[4];
+    if constexpr (Use::VOTES) {
+        if (lane == 0) changed[wave] = 0u;
+        static_assert(RS_ROWS == 32, "a word of u.todo and of u.changed");
+    }
+    short_rows<Use, 16, 4>(u, static_cast<int>(r0), 0, start_l, len_l, dst_l, old_l, lane, order[wave], &changed[wave]);
+    short_rows<Use, 32, 4>(u, static_cast<int>(r0), 16, start_l, len_l, dst_l, old_l, lane, order[wave], &changed[wave]);
+    short_rows<Use, 64, 4>(u, static_cast<int>(r0), 32, start_l, len_l, dst_l, old_l, lane, order[wave], &changed[wave]);
+    if constexpr (Use::VOTES) {
+        if (!u.changed) return;
+        wave_lds_sync();
+        const uint32_t m = changed[wave];
+        const int first = static_cast<int>(r0) >> u.shift;  // the 32 >> shift bits of these rows lie in one word
+        uint32_t bits = 0u;
+        if (u.shift == 0) bits = m;
+        else
+            for (uint32_t b = m; b; b &= b - 1u) bits |= 1u << (((__ffs(static_cast<int>(b)) - 1) >> u.shift) + (first & 31));
+        if (lane == 0 && m) {
+            atomicOr(&u.changed[first >> 5], bits);
+            atomicAdd(&u.changes[(r0 >> 5) & (VT_COUNTERS - 1)], __popc(m));
+        }
+    }
+}
+
 template <class Use>
 __device__ __forceinline__ void lds_row(const Use &u, int r, int *s, unsigned long long *tmp)
 {
     int start, len;
     u.row(r, start, len);  // uniform
-    if (len <= 2 * RS_NT) group_row<Use, 2>(u, r, start, len, s, tmp);
-    else if (len <= 4 * RS_NT) group_row<Use, 4>(u, r, start, len, s, tmp);
-    else if (len <= 8 * RS_NT) group_row<Use, 8>(u, r, start, len, s, tmp);
-    else if (len <= 16 * RS_NT) group_row<Use, 16>(u, r, start, len, s, tmp);
-    else group_row<Use, 32>(u, r, start, len, s, tmp);
+    if (len <= 8 * RS_NT) group_row<Use, 8, RS_NT, RS_WORDS>(u, r, start, len, s, tmp);
+    else if (len <= 16 * RS_NT) group_row<Use, 16, RS_NT, RS_WORDS>(u, r, start, len, s, tmp);
+    else group_row<Use, 32, RS_NT, RS_WORDS>(u, r, start, len, s, tmp);
 }
 
 __device__ __forceinline__ int pad_word(int i) { return i + (i >> 5); }  // a thread's 32 consecutive words on all banks
 
 // more than RS_LDS entries, relabelling: the columns as bits, read back in ascending order.  false (uniform): a column
 // occurs twice.
-__device__ __forceinline__ bool bitmap_row(const Relabel &u, int r, uint32_t *bits, int *tmp, int *dup)
+__device__ __forceinline__ bool bitmap_row(const Relabel &u, int r, uint32_t *bits, int *tmp, int *piece, int *dup)
 {
     int start, len;
     u.row(r, start, len);
@@ -510,29 +627,46 @@ __device__ __forceinline__ bool bitmap_row(const Relabel &u, int r, uint32_t *bi
         if (threadIdx.x == 0) *dup = 0;
         __syncthreads();
         bool twice = false;
-        for (int i = threadIdx.x; i < len; i += RS_NT) {
-            const int c = u.value(u.col_idx[start + i]) - base;
-            if (c >= 0 && c < span) {
-                const uint32_t m = 1u << (c & 31);
-                twice = twice || (atomicOr(&bits[pad_word(c >> 5)], m) & m) != 0u;
+        for (int i0 = threadIdx.x; i0 < len; i0 += RS_NT * 8) {  // eight look-ups in flight
+            int c[8], v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) c[k] = u.col_idx[start + min(i0 + k * RS_NT, len - 1)];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = u.look(c[k]);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int x = u.settle(c[k], v[k], true) - base;
+                if (i0 + k * RS_NT < len && x >= 0 && x < span) {
+                    const uint32_t m = 1u << (x & 31);
+                    twice = twice || (atomicOr(&bits[pad_word(x >> 5)], m) & m) != 0u;
+                }
             }
         }
         if (twice) *dup = 1;
         __syncthreads();
         if (*dup) return false;
-        int mine = 0;
-        const int w0 = threadIdx.x * 32;
-        for (int w = 0; w < 32; ++w) mine += __popc(bits[pad_word(w0 + w)]);
+        // 64 words at a time by a wave, a word a lane: the columns of a row can all lie close together, and a wave's words are as full
+        // as each other (32 words in a row by one thread: 74 us for the 211 rows of the R-MAT graph, this way 59)
+        constexpr int PIECES = 1 << (RS_BITS_LOG2 - 11), WAVES = RS_NT / 64;
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        for (int p = wave; p < PIECES; p += WAVES) {
+            const int incl = wave_inclusive_scan(__popc(bits[pad_word(p * 64 + lane)]));
+            if (lane == 63) piece[p] = incl;
+        }
+        __syncthreads();
         int total;
-        int pos = dst + group_exclusive_scan(mine, &total, tmp);
-        if (mine > 0)
-            for (int w = 0; w < 32; ++w) {
-                uint32_t b = bits[pad_word(w0 + w)];
-                while (b) {
-                    u.out[pos++] = base + (w0 + w) * 32 + __ffs(static_cast<int>(b)) - 1;
-                    b &= b - 1;
-                }
+        const int before = group_exclusive_scan(threadIdx.x < PIECES ? piece[threadIdx.x] : 0, &total, tmp);
+        if (threadIdx.x < PIECES) piece[threadIdx.x] = dst + before;
+        __syncthreads();
+        for (int p = wave; p < PIECES; p += WAVES) {
+            uint32_t b = bits[pad_word(p * 64 + lane)];
+            const int mine = __popc(b);
+            int pos = piece[p] + wave_inclusive_scan(mine) - mine;
+            while (b) {
+                u.out[pos++] = base + (p * 64 + lane) * 32 + __ffs(static_cast<int>(b)) - 1;
+                b &= b - 1;
             }
+        }
         dst += total;
     }
     return true;
@@ -556,26 +690,15 @@ __device__ __forceinline__ int count_range(const Use &u, const int *__restrict__
     return less;
 }
 
-// The look-ups of the rows that are counted, once instead of in every pass: one workgroup a row, eight in flight a thread.
-// *count rows in `rows`.
-template <class Use>
-__global__ __launch_bounds__(RS_NT) void long_row_values_kernel(Use u, const int *__restrict__ rows, const int *__restrict__ count,
+// The look-ups of the relabelled rows that are counted, once instead of in every pass: one workgroup a row.  *count rows in `rows`.
+__global__ __launch_bounds__(RS_NT) void long_row_values_kernel(Relabel u, const int *__restrict__ rows, const int *__restrict__ count,
                                                                 int *__restrict__ values)
 {
     const int n_rows = *count;
     for (int h = blockIdx.x; h < n_rows; h += gridDim.x) {
         int start, len;
         u.row(rows[h], start, len);
-        for (int i0 = threadIdx.x; i0 < len; i0 += RS_NT * 8) {
-            int c[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) c[k] = u.col_idx[start + min(i0 + k * RS_NT, len - 1)];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) c[k] = u.value(c[k]);
-#pragma unroll
-            for (int k = 0; k < 8; ++k)
-                if (i0 + k * RS_NT < len) values[start + i0 + k * RS_NT] = c[k];
-        }
+        look_up_row(u, start, len, threadIdx.x, RS_NT, values);
     }
 }
 
@@ -586,14 +709,14 @@ __global__ __launch_bounds__(RS_NT) void row_sort_big_kernel(Use u, RowQueues q)
     __shared__ unsigned long long tmp64[RS_NT / 64];
     __shared__ int tmp[RS_NT / 64];
     __shared__ int dup;
-    const int n3 = q.counts[3], n2 = q.counts[2];
+    const int n4 = q.counts[4], n3 = q.counts[3];
     if constexpr (Use::VOTES) {
         const int ranges = value_ranges(u.n);
-        const int64_t tasks = static_cast<int64_t>(n3) * ranges;
+        const int64_t tasks = static_cast<int64_t>(n4) * ranges;
         for (int64_t t = blockIdx.x; t < tasks; t += gridDim.x) {  // uniform
             const int h = static_cast<int>(t / ranges), base = static_cast<int>(t % ranges) * RS_RANGE;
             int start, len;
-            u.row(q.rows[3][h], start, len);
+            u.row(q.rows[4][h], start, len);
             count_range(u, q.values, start, len, base, s);
             unsigned long long best = 0ull;
             for (int i = threadIdx.x; i < RS_RANGE; i += RS_NT) {
@@ -601,18 +724,24 @@ __global__ __launch_bounds__(RS_NT) void row_sort_big_kernel(Use u, RowQueues q)
                 const unsigned long long cand = votes > 0 ? ballot_of(votes, base + i) : 0ull;
                 best = cand > best ? cand : best;
             }
-            best = group_max_u64(best, tmp64);
-            if (threadIdx.x == 0 && best != 0ull) atomicMax(&q.best[h], best);
+            best = group_max_u64<RS_NT>(best, tmp64);
+            if (threadIdx.x == 0) {  // the last of the row's ranges takes the winner
+                if (best != 0ull) atomicMax(&q.best[h], best);
+                __threadfence();
+                if (atomicAdd(&q.dup_rows[h], 1) == ranges - 1)
+                    u.vote(q.rows[4][h], static_cast<int>(0xffffffffu - static_cast<uint32_t>(atomicMax(&q.best[h], 0ull) & 0xffffffffull)));
+            }
         }
     } else {
-        for (int h = blockIdx.x; h < n3; h += gridDim.x) {
-            const int r = q.rows[3][h];
-            if (bitmap_row(u, r, reinterpret_cast<uint32_t *>(s), tmp, &dup)) continue;  // uniform
+        __shared__ int piece[1 << (RS_BITS_LOG2 - 11)];
+        for (int h = blockIdx.x; h < n4; h += gridDim.x) {
+            const int r = q.rows[4][h];
+            if (bitmap_row(u, r, reinterpret_cast<uint32_t *>(s), tmp, piece, &dup)) continue;  // uniform
             if (many_ranges(u.n) && u.rp[r + 1] - u.rp[r] <= RS_LDS_MOST) lds_row(u, r, s, tmp64);
-            else if (threadIdx.x == 0) q.dup_rows[atomicAdd(&q.counts[4], 1)] = r;
+            else if (threadIdx.x == 0) q.dup_rows[atomicAdd(&q.counts[RS_QUEUES], 1)] = r;
         }
     }
-    for (int i = blockIdx.x; i < n2; i += gridDim.x) lds_row(u, q.rows[2][i], s, tmp64);
+    for (int i = blockIdx.x; i < n3; i += gridDim.x) lds_row(u, q.rows[3][i], s, tmp64);
 }
 
 // long rows in which a column occurs more than once: counters instead of bits, one workgroup per row and range
@@ -621,7 +750,7 @@ __global__ __launch_bounds__(RS_NT) void row_sort_dup_kernel(Relabel u, RowQueue
     __shared__ int s[RS_WORDS];
     __shared__ int tmp[RS_NT / 64];
     const int ranges = value_ranges(u.n);
-    const int64_t tasks = static_cast<int64_t>(q.counts[4]) * ranges;
+    const int64_t tasks = static_cast<int64_t>(q.counts[RS_QUEUES]) * ranges;
     for (int64_t t = blockIdx.x; t < tasks; t += gridDim.x) {  // uniform
         const int r = q.dup_rows[t / ranges], base = static_cast<int>(t % ranges) * RS_RANGE;
         int start, len;
@@ -640,26 +769,121 @@ __global__ __launch_bounds__(RS_NT) void row_sort_dup_kernel(Relabel u, RowQueue
     }
 }
 
-__global__ __launch_bounds__(256) void take_winners_kernel(RowQueues q, int *__restrict__ out)
+// ---- label propagation: rows that may change ---------------------------------------------------------------
+// After some rounds few labels change, and a row none of whose columns has changed keeps its label: it is not voted on again.
+// Which rows these are takes a bit per column and no look-up in memory: the bits of the nodes that changed in the round before fit
+// into LDS (up to 2^20 nodes one each, above one for two or four nodes in a row).  Bound by reading the column ids.  Where most
+// rows would be left (the changed share times the mean number of entries above VT_MOST) all of them are, at once.
+// On the block model with a million nodes, 32 M entries, a check that leaves rows out takes 50 us, one that doesn't 5; the ninth and the
+// tenth round take 39 and 25 us after it instead of 212.
+constexpr int VT_BITS_LOG2 = 20;
+constexpr float VT_MOST = 0.6f;
+
+__global__ __launch_bounds__(RS_NT) void vote_check_kernel(int n, int nnz, const int *__restrict__ rp, const int *__restrict__ col_idx,
+                                                           const uint32_t *__restrict__ changed, const int *__restrict__ changes,
+                                                           uint32_t *__restrict__ next_changed, int *__restrict__ next_changes, int shift,
+                                                           uint32_t *__restrict__ todo)
 {
-    const int n3 = q.counts[3];
-    for (int h = blockIdx.x * 256 + threadIdx.x; h < n3; h += gridDim.x * 256)
-        out[q.rows[3][h]] = static_cast<int>(0xffffffffu - static_cast<uint32_t>(q.best[h] & 0xffffffffull));
+    constexpr int WAVES = RS_NT / 64, U = 8;
+    __shared__ uint32_t bits[1 << (VT_BITS_LOG2 - 5)];
+    __shared__ int starts[WAVES][65], tmp[WAVES];
+    __shared__ uint32_t hit[WAVES][2];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int words = (((n - 1) >> shift) >> 5) + 1, todo_words = (n + 31) / 32;
+    const int thread = blockIdx.x * RS_NT + threadIdx.x, threads = gridDim.x * RS_NT;
+    for (int i = thread; i < words; i += threads) next_changed[i] = 0u;
+    if (thread < VT_COUNTERS) next_changes[thread] = 0;
+    int total;
+    group_exclusive_scan(threadIdx.x < VT_COUNTERS ? changes[threadIdx.x] : 0, &total, tmp);
+    if (static_cast<float>(total) * static_cast<float>(nnz) > VT_MOST * static_cast<float>(n) * static_cast<float>(n)) {  // uniform over the grid
+        for (int i = thread; i < todo_words; i += threads) todo[i] = ~0u;
+        return;
+    }
+    for (int i = threadIdx.x; i < words; i += RS_NT) bits[i] = changed[i];
+    __syncthreads();  // (none below)
+    auto has_changed = [&](int c) {
+        const unsigned b = static_cast<unsigned>(lookup_index(c, n)) >> shift;
+        return c >= 0 && c < n && (bits[b >> 5] >> (b & 31u) & 1u);
+    };
+    for (int64_t r0 = (static_cast<int64_t>(blockIdx.x) * WAVES + wave) * 64; r0 < n; r0 += static_cast<int64_t>(gridDim.x) * WAVES * 64) {
+        const int r = static_cast<int>(min(r0 + lane, static_cast<int64_t>(n)));
+        const int st = rp[r], len = rp[min(r + 1, n)] - st;
+        wave_lds_sync();
+        starts[wave][lane] = st;
+        if (lane == 63) starts[wave][64] = st + len;
+        if (lane < 2) hit[wave][lane] = 0u;
+        wave_lds_sync();
+        if (__builtin_amdgcn_ballot_w64(len > RS_SHORT) == 0ull) {  // the entries of all 64 rows in one go
+            const int end = starts[wave][64];
+            for (int e0 = starts[wave][0]; e0 < end; e0 += 64 * U) {
+                int c[U];
+#pragma unroll
+                for (int k = 0; k < U; ++k) c[k] = __builtin_nontemporal_load(col_idx + min(e0 + k * 64 + lane, end - 1));
+#pragma unroll
+                for (int k = 0; k < U; ++k) {
+                    const int e = e0 + k * 64 + lane;
+                    if (e < end && has_changed(c[k])) {
+                        int t = 0;  // the last of the 64 rows that begins at or before e
+#pragma unroll
+                        for (int h = 32; h > 0; h /= 2) t += starts[wave][t + h] <= e ? h : 0;
+                        atomicOr(&hit[wave][t >> 5], 1u << (t & 31));
+                    }
+                }
+            }
+        } else {  // longer rows, which are voted on in any case, are left out: row by row, U rows in flight
+            for (int t0 = 0; t0 < 64; t0 += U) {
+                int c[U], ln[U];
+#pragma unroll
+                for (int k = 0; k < U; ++k) {
+                    const int s = __shfl(st, t0 + k, 64);
+                    ln[k] = __shfl(len, t0 + k, 64);
+                    if (ln[k] > RS_SHORT) ln[k] = 0;
+                    c[k] = col_idx[max(min(s + min(lane, ln[k] - 1), nnz - 1), 0)];
+                }
+#pragma unroll
+                for (int k = 0; k < U; ++k)
+                    if (__builtin_amdgcn_ballot_w64(lane < ln[k] && has_changed(c[k])) != 0ull && lane == 0)
+                        atomicOr(&hit[wave][(t0 + k) >> 5], 1u << ((t0 + k) & 31));
+            }
+        }
+        wave_lds_sync();
+        if (lane < 2 && (r0 >> 5) + lane < todo_words) todo[(r0 >> 5) + lane] = hit[wave][lane];
+    }
 }
 
 // ---- launchers --------------------------------------------------------------------------------------------
 // Queue capacities for nnz entries, in rows.
 static int64_t queue_cap(int nnz, int longer_than) { return nnz / (longer_than + 1) + 1; }
 
+// Label propagation looks for the rows that may change from this many entries on: a launch more a round (5 us) against the share of
+// a round (6.5 us a million entries) that the last ones save.  Ten rounds on the block model, with the look-ups of the first round, without the
+// check / as here: 32 M entries 2204 / 1811 us, 23 M 1472 / 1250, 16 M 1077 / 920.
+constexpr int VT_FROM = 12000000;
+static bool votes_are_checked(int nnz) { return nnz >= VT_FROM; }
+static int changed_shift(int n)
+{
+    int s = 0;
+    while ((n - 1) >> s >> VT_BITS_LOG2) ++s;
+    return s;
+}
+static int changed_words(int n) { return ((n - 1) >> changed_shift(n) >> 5) + 1; }
+
 size_t row_sort_ws(int n, int nnz)
 {
     auto ints = [](int64_t k) { return align_up(static_cast<size_t>(k) * sizeof(int), 256); };
     return 256 + ints(queue_cap(nnz, RS_SHORT)) + ints(queue_cap(nnz, RS_MID)) + ints(queue_cap(nnz, RS_LONG)) +
-           2 * ints(queue_cap(nnz, RS_LDS)) + align_up(static_cast<size_t>(queue_cap(nnz, RS_LDS)) * 8, 256) + ints(n) +
-           (nnz > RS_LDS_MOST && many_ranges(n) ? ints(nnz) : 0);
+           ints(queue_cap(nnz, RS_GROUP)) + 2 * ints(queue_cap(nnz, RS_LDS)) + align_up(static_cast<size_t>(queue_cap(nnz, RS_LDS)) * 8, 256) + ints(n) +
+           (nnz > RS_LDS_MOST && many_ranges(n) ? ints(nnz) : 0) +
+           (votes_are_checked(nnz) ? 2 * ints(VT_COUNTERS) + 2 * ints(changed_words(n)) + ints((n + 31) / 32) : 0);
 }
 
-static RowQueues carve(int n, int nnz, void *ws, int **labels)
+// of rounds with an even and an odd number
+struct VoteCheck {
+    int *changes[2];
+    uint32_t *changed[2], *todo;
+};
+
+static RowQueues carve(int n, int nnz, void *ws, int **labels, VoteCheck *vc)
 {
     char *p = static_cast<char *>(ws);
     auto ints = [&](int64_t k) {
@@ -672,21 +896,31 @@ static RowQueues carve(int n, int nnz, void *ws, int **labels)
     q.rows[0] = ints(queue_cap(nnz, RS_SHORT));
     q.rows[1] = ints(queue_cap(nnz, RS_MID));
     q.rows[2] = ints(queue_cap(nnz, RS_LONG));
-    q.rows[3] = ints(queue_cap(nnz, RS_LDS));
+    q.rows[3] = ints(queue_cap(nnz, RS_GROUP));
+    q.rows[4] = ints(queue_cap(nnz, RS_LDS));
     q.dup_rows = ints(queue_cap(nnz, RS_LDS));
     q.best = reinterpret_cast<unsigned long long *>(p);
     p += align_up(static_cast<size_t>(queue_cap(nnz, RS_LDS)) * 8, 256);
     *labels = ints(n);
     q.values = nnz > RS_LDS_MOST && many_ranges(n) ? ints(nnz) : nullptr;
+    if (vc) {
+        const bool kept = votes_are_checked(nnz);
+        for (int k = 0; k < 2; ++k) vc->changes[k] = kept ? ints(VT_COUNTERS) : nullptr;
+        for (int k = 0; k < 2; ++k) vc->changed[k] = kept ? reinterpret_cast<uint32_t *>(ints(changed_words(n))) : nullptr;
+        vc->todo = kept ? reinterpret_cast<uint32_t *>(ints((n + 31) / 32)) : nullptr;
+    }
     return q;
 }
 
-// clears the queue counters; labels: every node starts with its own id (NULL: none)
-__global__ __launch_bounds__(256) void row_sort_begin_kernel(int n, int *__restrict__ counts, int *__restrict__ labels)
+// clears the queue counters and, where they are kept, the changes of the second round
+__global__ __launch_bounds__(256) void row_sort_begin_kernel(int *__restrict__ counts, int *__restrict__ changes, uint32_t *__restrict__ changed,
+                                                             int changed_words)
 {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i < 64) counts[i] = 0;
-    if (labels && i < n) labels[i] = i;
+    if (!changes) return;
+    if (i < VT_COUNTERS) changes[i] = 0;
+    if (i < changed_words) changed[i] = 0u;
 }
 
 struct RowSortGrid {
@@ -699,14 +933,16 @@ static RowSortGrid row_sort_grid(int n, int nnz)
     const int64_t queued = queue_cap(nnz, RS_SHORT);
     g.queue_blocks = static_cast<int>((queued + 3) / 4 < 1024 ? (queued + 3) / 4 : 1024);
     g.blocks = g.queue_blocks + static_cast<int>((static_cast<int64_t>(n) + 4 * RS_ROWS - 1) / (4 * RS_ROWS));
-    const int64_t big = queue_cap(nnz, RS_LONG);
+    const int64_t big = queue_cap(nnz, RS_GROUP);
     g.big_blocks = static_cast<int>(big < 256 ? big : 256);
     return g;
 }
 
-static void classify_rows(int n, const int *rp, int in_lds, const RowQueues &q, int *labels, hipStream_t s)
+static void classify_rows(int n, const int *rp, int in_lds, const RowQueues &q, const VoteCheck *vc, hipStream_t s)
 {
-    hipLaunchKernelGGL(row_sort_begin_kernel, dim3(labels ? (n + 255) / 256 : 1), dim3(256), 0, s, n, q.counts, labels);
+    const int words = vc && vc->todo ? changed_words(n) : 0;
+    hipLaunchKernelGGL(row_sort_begin_kernel, dim3((words + 255) / 256 + 1), dim3(256), 0, s, q.counts, words ? vc->changes[1] : nullptr,
+                       words ? vc->changed[1] : nullptr, words);
     hipLaunchKernelGGL(row_classes_kernel, dim3((n + 4095) / 4096), dim3(1024), 0, s, n, rp, in_lds, q);
 }
 
@@ -715,40 +951,50 @@ int32_t launch_relabel_rows(const ftc_csr &g, const int *perm, const int *inv, c
                             void *ws, hipStream_t s)
 {
     int *unused;
-    const RowQueues q = carve(g.n, g.nnz, ws, &unused);
+    const RowQueues q = carve(g.n, g.nnz, ws, &unused, nullptr);
     const RowSortGrid grid = row_sort_grid(g.n, g.nnz);
     const Relabel u{g.n, g.row_ptr, g.col_idx, perm, inv, rp, col_idx_out, flag};
     classify_rows(g.n, rp, RS_LDS, q, nullptr, s);
-    if (g.nnz > RS_LONG) hipLaunchKernelGGL(row_sort_big_kernel<Relabel>, dim3(grid.big_blocks), dim3(RS_NT), 0, s, u, q);
+    if (g.nnz > RS_GROUP) hipLaunchKernelGGL(row_sort_big_kernel<Relabel>, dim3(grid.big_blocks), dim3(RS_NT), 0, s, u, q);
     hipLaunchKernelGGL(row_sort_kernel<Relabel>, dim3(grid.blocks), dim3(256), 0, s, u, q, grid.queue_blocks);
     if (g.nnz > RS_LDS) {
         if (q.values)
-            hipLaunchKernelGGL(long_row_values_kernel<Relabel>, dim3(grid.big_blocks), dim3(RS_NT), 0, s, u, q.dup_rows,
-                               q.counts + 4, q.values);
+            hipLaunchKernelGGL(long_row_values_kernel, dim3(grid.big_blocks), dim3(RS_NT), 0, s, u, q.dup_rows,
+                               q.counts + RS_QUEUES, q.values);
         hipLaunchKernelGGL(row_sort_dup_kernel, dim3(grid.big_blocks), dim3(RS_NT), 0, s, u, q);
     }
     return launch_status("relabel rows");
+}
+
+template <bool FIRST>
+static void label_round(const ftc_csr &g, const Votes<FIRST> &u, const RowQueues &q, const RowSortGrid &grid, hipStream_t s)
+{
+    hipLaunchKernelGGL(row_sort_kernel<Votes<FIRST>>, dim3(grid.blocks), dim3(256), 0, s, u, q, grid.queue_blocks);
+    if (g.nnz > RS_GROUP) hipLaunchKernelGGL(row_sort_big_kernel<Votes<FIRST>>, dim3(grid.big_blocks), dim3(RS_NT), 0, s, u, q);
 }
 
 // `labels` holds the labels after the last round; ws: row_sort_ws(n, nnz) bytes
 int32_t launch_label_rounds(const ftc_csr &g, int iters, int *labels, void *ws, hipStream_t s)
 {
     int *other;
-    const RowQueues q = carve(g.n, g.nnz, ws, &other);
+    VoteCheck vc;
+    const RowQueues q = carve(g.n, g.nnz, ws, &other, &vc);
     const RowSortGrid grid = row_sort_grid(g.n, g.nnz);
+    const int shift = changed_shift(g.n);
     // the rounds alternate between the two arrays and end in `labels`
     int *from = iters % 2 == 0 ? labels : other, *to = iters % 2 == 0 ? other : labels;
-    classify_rows(g.n, g.row_ptr, many_ranges(g.n) ? RS_LDS_MOST : RS_LDS, q, from, s);
+    classify_rows(g.n, g.row_ptr, many_ranges(g.n) ? RS_LDS_MOST : RS_LDS, q, &vc, s);
     for (int it = 0; it < iters; ++it) {
-        const Votes u{g.n, g.col_idx, from, g.row_ptr, to};
-        hipLaunchKernelGGL(row_sort_kernel<Votes>, dim3(grid.blocks), dim3(256), 0, s, u, q, grid.queue_blocks);
-        if (q.values)
-            hipLaunchKernelGGL(long_row_values_kernel<Votes>, dim3(grid.big_blocks), dim3(RS_NT), 0, s, u, q.rows[3], q.counts + 3,
-                               q.values);
-        if (g.nnz > RS_LONG) hipLaunchKernelGGL(row_sort_big_kernel<Votes>, dim3(grid.big_blocks), dim3(RS_NT), 0, s, u, q);
-        if (g.nnz > RS_LDS)
-            hipLaunchKernelGGL(take_winners_kernel, dim3(static_cast<unsigned>((queue_cap(g.nnz, RS_LDS) + 255) / 256)),
-                               dim3(256), 0, s, q, to);
+        // nearly all labels change in the first two rounds; the third is the first to ask which did in the one before
+        const bool kept = vc.todo && it >= 1 && it + 1 < iters, check = vc.todo && it >= 2;
+        if (check)
+            hipLaunchKernelGGL(vote_check_kernel, dim3(256), dim3(RS_NT), 0, s, g.n, g.nnz, g.row_ptr, g.col_idx, vc.changed[(it - 1) & 1],
+                               vc.changes[(it - 1) & 1], vc.changed[it & 1], vc.changes[it & 1], shift, vc.todo);
+        if (it == 0)
+            label_round(g, Votes<true>{g.n, g.col_idx, from, g.row_ptr, to, nullptr, nullptr, 0, nullptr}, q, grid, s);
+        else
+            label_round(g, Votes<false>{g.n, g.col_idx, from, g.row_ptr, to, kept ? vc.changed[it & 1] : nullptr, vc.changes[it & 1], shift,
+                                        check ? vc.todo : nullptr}, q, grid, s);
         int *t = from;
         from = to;
         to = t;

@@ -331,3 +331,41 @@ def test_row_lengths_at_the_edges_of_the_row_classes(n, distinct):
         label = voted(rows, label[col], n, label)
         got = B.ftc_label_propagation(dg, rounds).cpu().numpy()
         assert np.array_equal(got, label), f"{rounds} rounds"
+
+
+@pytest.mark.parametrize("kind,n,deg", [("blocks", 400_000, 34), ("uniform", 1_000_000, 16), ("skewed", 1 << 21, 8), ("directed", 1 << 20, 14),
+                                        ("duplicates", 300_001, 45)])
+def test_rounds_that_leave_out_the_rows_that_cannot_change(kind, n, deg):
+    """12 M entries and more: rounds after the second one vote only on rows a column of which has changed.  Every number of rounds,
+    against the same votes by sorting; columns that are unsorted, repeated, out of order with the rows that name them, hub rows;
+    2^20 nodes are the last with a bit each."""
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    m = n * deg
+    if kind == "blocks":  # pairs inside communities of 200, shuffled: labels settle after some rounds
+        perm = torch.randperm(n, generator=gen, device="cuda")
+        c = torch.randint(n // 200, (m,), generator=gen, device="cuda") * 200
+        r, c = (perm[c + torch.randint(200, (m,), generator=gen, device="cuda")] for _ in range(2))
+    elif kind == "skewed":  # three quarters of the entries in a few rows of all classes
+        hubs = torch.randint(3000, (m * 3 // 4,), generator=gen, device="cuda") ** 2 % 5000
+        r = torch.cat([hubs, torch.randint(n, (m - m * 3 // 4,), generator=gen, device="cuda")])
+        c = torch.randint(n, (m,), generator=gen, device="cuda") ** 2 % n
+    else:
+        r, c = (torch.randint(n, (m,), generator=gen, device="cuda") for _ in range(2))
+        if kind == "duplicates":
+            c = c // 50 * 50
+        if kind == "directed":
+            c = c * 3 // 4  # some nodes are nobody's column, and the pattern is not symmetric
+    if kind == "uniform":
+        r, c = torch.cat([r[:m // 2], c[:m // 2]]), torch.cat([c[:m // 2], r[:m // 2]])
+    r, order = torch.sort(r, stable=True)
+    c = c[order]
+    row_ptr = torch.zeros(n + 1, dtype=torch.int32, device="cuda")
+    row_ptr[1:] = torch.cumsum(torch.bincount(r, minlength=n), 0)
+    g = B.Graph(row_ptr, c.to(torch.int32))
+    assert g.nnz >= 12_000_000
+    label = torch.arange(n, device="cuda")
+    for rounds in range(1, 12):
+        key, votes = torch.unique(r * n + label[c], return_counts=True)
+        best = torch.zeros(n, dtype=torch.int64, device="cuda").scatter_reduce_(0, key // n, votes * n + (n - 1 - key % n), "amax")
+        label = torch.where(best > 0, n - 1 - best % n, label)
+        assert torch.equal(B.ftc_label_propagation(g, rounds).long(), label), f"{rounds} rounds"
