@@ -11,7 +11,8 @@
 //      bitmap in LDS (a coarse bitmap names the 32-column words the window touches, the fine bitmap
 //      holds one word per touched word): set bits, prefix sums of the popcounts, rank = prefix of the
 //      word + bits below the column's own.  The waves keep their column ids in registers; a CU works
-//      on as many windows at once as their bitmaps fit into its LDS;
+//      on as many windows at once as their bitmaps fit into its LDS (up to 2^20 nodes windows of up to LEAN_EDGES edges by
+//      a kernel of their own, which also takes whole graphs of few columns);
 //   3. above MID_CAP edges on graphs of up to DIRECT_MAX_RANGES ranges of 2^20 columns: one workgroup
 //      of 1024 threads with the whole bitmap of a range in LDS (no coarse level); windows of 10^5
 //      edges are queued in parts, each of which builds the bitmap and ranks its share of the edges;
@@ -1521,6 +1522,123 @@ __global__ __launch_bounds__(256) void win_flat_kernel(int n, const int *__restr
     if (tid == 0) uniq_count[w] = total;
 }
 
+// Windows of at most LEAN_EDGES edges on graphs of at most 2^18 CP columns: a wave each, and no work in proportion to the number of columns
+// but for one scan of their coarse bitmap (a bit per 32 columns: CP 16-byte pieces per lane).  The touched words are numbered through it
+// (at most one "slot" per edge), the fine bitmap holds a word per slot, and an edge's rank is its slot's prefix plus the bits below its
+// own.  Larger windows are queued for win_flat_big_kernel, those above MID_CAP edges in parts.
+// Bound by latency (row start, column ids, four passes over a few KB of LDS), which 20 (CP = 4: 12) waves on a CU hide: 12 500 windows of 304
+// edges 45 us with a workgroup and 32 KB of bitmap each (win_flat_kernel), 22 here; 62 500 windows of 522 edges of 10^6 columns 285 us in
+// win_bitmap_wave_kernel<1024, 1>, which runs all 1024 places of a window, 120 here, from its queue (list).
+constexpr int LEAN_EDGES = B1_CAP;
+
+template <int CP>
+__global__ __launch_bounds__(64) void win_lean_kernel(int n, const int *__restrict__ row_ptr, const int *__restrict__ col_idx, int blk_h,
+                                                      int *__restrict__ edge_to_row, int *__restrict__ edge_to_col,
+                                                      int *__restrict__ uniq_count, int *__restrict__ tmp_cols,
+                                                      const int4 *__restrict__ list, const int *__restrict__ count,
+                                                      int4 *__restrict__ list_mid, int4 *__restrict__ list_direct, int *__restrict__ counters)
+{
+    constexpr int EPL = LEAN_EDGES / 64, FP = LEAN_EDGES / 256;
+    __shared__ uint4 coarse4[64 * CP];
+    __shared__ uint2 cpre4[64 * CP];   // slots before each coarse word
+    __shared__ uint4 fine4[64 * FP];
+    __shared__ uint2 fpre4[64 * FP];   // unique columns before each slot
+    __shared__ int rp[65];
+    uint32_t *coarse = reinterpret_cast<uint32_t *>(coarse4), *fine = reinterpret_cast<uint32_t *>(fine4);
+    const uint16_t *cpre = reinterpret_cast<const uint16_t *>(cpre4), *fpre = reinterpret_cast<const uint16_t *>(fpre4);
+    const int lane = threadIdx.x;
+    int w = blockIdx.x, e0 = 0, cnt = 0;  // uniform
+    if (list) {
+        const int4 ent = list[blockIdx.x];
+        if (w >= *count) return;
+        w = ent.x;
+        e0 = ent.y;
+        cnt = ent.z;
+    }
+    const int r0 = w * blk_h, rows = min(n, r0 + blk_h) - r0;
+    if (!list) {
+        e0 = row_ptr[r0];
+        cnt = row_ptr[r0 + rows] - e0;
+    }
+    if (cnt > LEAN_EDGES) {
+        if (lane == 0) {
+            if (cnt <= MID_CAP) list_mid[atomicAdd(&counters[C_B2], 1)] = make_int4(w, e0, cnt, 1 << 8);
+            else {
+                const int parts = direct_parts(cnt), at = atomicAdd(&counters[C_DIRECT], parts);
+                for (int p = 0; p < parts; ++p) list_direct[at + p] = make_int4(w, e0, cnt, p | (parts << 8));
+            }
+        }
+        return;
+    }
+    int c[EPL], slot[EPL];
+    // unconditional loads from clamped addresses, half of them where the window has no more edges
+#pragma unroll
+    for (int k = 0; k < EPL / 2; ++k) c[k] = col_idx[max(e0 + min(k * 64 + lane, cnt - 1), 0)];  // (cnt may be 0, nnz is not)
+    if (cnt > LEAN_EDGES / 2) {
+#pragma unroll
+        for (int k = EPL / 2; k < EPL; ++k) c[k] = col_idx[e0 + min(k * 64 + lane, cnt - 1)];
+    }
+    rp[lane] = row_ptr[min(r0 + lane, r0 + rows)];
+    if (lane == 0) rp[64] = e0 + cnt;
+#pragma unroll
+    for (int q = 0; q < CP; ++q) coarse4[lane + 64 * q] = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+    for (int q = 0; q < FP; ++q)
+        if (q * 256 < cnt) fine4[lane + 64 * q] = make_uint4(0u, 0u, 0u, 0u);
+    wave_lds_sync();
+    auto valid = [&](int k) { return k * 64 + lane < cnt && static_cast<unsigned>(c[k]) < (static_cast<unsigned>(CP) << 18); };
+#pragma unroll
+    for (int k = 0; k < EPL; ++k) {
+        if (k * 64 >= cnt) break;  // uniform
+        if (valid(k)) atomicOr(&coarse[c[k] >> 10], 1u << ((c[k] >> 5) & 31));
+    }
+    wave_lds_sync();
+    int n_slots = 0;
+#pragma unroll
+    for (int q = 0; q < CP; ++q) {
+        const uint4 v = coarse4[lane + 64 * q];
+        const int c0 = __popc(v.x), c1 = c0 + __popc(v.y), c2 = c1 + __popc(v.z), mine = c2 + __popc(v.w);
+        const int incl = wave_inclusive_scan(mine);
+        const unsigned run = static_cast<unsigned>(n_slots + incl - mine);
+        cpre4[lane + 64 * q] = make_uint2(run | ((run + c0) << 16), (run + c1) | ((run + c2) << 16));
+        n_slots += __builtin_amdgcn_readlane(incl, 63);
+    }
+    wave_lds_sync();
+#pragma unroll
+    for (int k = 0; k < EPL; ++k) {
+        if (k * 64 >= cnt) break;  // uniform
+        if (valid(k)) {
+            slot[k] = cpre[c[k] >> 10] + __popc(coarse[c[k] >> 10] & ((1u << ((c[k] >> 5) & 31)) - 1u));
+            atomicOr(&fine[slot[k]], 1u << (c[k] & 31));
+        }
+    }
+    wave_lds_sync();
+    int total = 0;
+#pragma unroll
+    for (int q = 0; q < FP; ++q) {
+        if (q * 256 >= n_slots) break;  // uniform
+        const uint4 v = fine4[lane + 64 * q];
+        const int c0 = __popc(v.x), c1 = c0 + __popc(v.y), c2 = c1 + __popc(v.z), mine = c2 + __popc(v.w);
+        const int incl = wave_inclusive_scan(mine);
+        const unsigned run = static_cast<unsigned>(total + incl - mine);
+        fpre4[lane + 64 * q] = make_uint2(run | ((run + c0) << 16), (run + c1) | ((run + c2) << 16));
+        total += __builtin_amdgcn_readlane(incl, 63);
+    }
+    wave_lds_sync();
+#pragma unroll
+    for (int k = 0; k < EPL; ++k) {
+        if (k * 64 >= cnt) break;  // uniform
+        if (valid(k)) {
+            const int rank = fpre[slot[k]] + __popc(fine[slot[k]] & ((1u << (c[k] & 31)) - 1u));
+            __builtin_nontemporal_store(rank, edge_to_col + e0 + k * 64 + lane);
+            tmp_cols[e0 + rank] = c[k];  // edges with the same column store the same value
+        }
+    }
+    for (int r = 0; r < rows; ++r)
+        for (int e = rp[r] + lane; e < rp[r + 1]; e += 64) __builtin_nontemporal_store(r0 + r, edge_to_row + e);
+    if (lane == 0) uniq_count[w] = total;
+}
+
 // The queued windows, a part at a time, 1024 threads each whatever the size of the bitmap: with a thread per piece (512 for
 // graphs of up to 65 536 nodes) a CU held half as many waves (us): 20 000 nodes with 2000 entries a row 283 / 227, with 9000
 // 1680 / 1520; one window of 9.6 M entries 2511 / 1584.
@@ -1528,7 +1646,7 @@ template <int WORDS>
 __global__ __launch_bounds__(1024) void win_flat_big_kernel(
     int n, const int *__restrict__ row_ptr, const int *__restrict__ col_idx, int blk_h, int *__restrict__ edge_to_row,
     int *__restrict__ edge_to_col, int *__restrict__ uniq_count, int *__restrict__ tmp_cols, const int4 *__restrict__ list,
-    const int *__restrict__ count)
+    const int *__restrict__ count, const int4 *__restrict__ list_mid, const int *__restrict__ count_mid)
 {
     constexpr int PIECES = WORDS / 4, NT = 1024, PPT = PIECES < NT ? 1 : PIECES / NT, EB = 8;
     __shared__ uint4 bits[PIECES];
@@ -1538,9 +1656,9 @@ __global__ __launch_bounds__(1024) void win_flat_big_kernel(
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const bool owner = tid < PIECES;  // of a share of the bitmap
     uint32_t *words = reinterpret_cast<uint32_t *>(bits);
-    const int n_items = *count;
+    const int n_direct = *count, n_items = n_direct + *count_mid;
     for (int item = blockIdx.x; item < n_items; item += gridDim.x) {  // uniform
-        const int4 ent = list[item];
+        const int4 ent = item < n_direct ? list[item] : list_mid[item - n_direct];
         const int w = ent.x, e0 = ent.y, cnt = ent.z, part = ent.w & 255, parts = ent.w >> 8;
         const int per = ((cnt + parts - 1) / parts + NT - 1) / NT * NT;
         const int i_lo = min(cnt, part * per), i_hi = min(cnt, i_lo + per);
@@ -1660,6 +1778,9 @@ __global__ __launch_bounds__(256) void win_finish_kernel(int n, int n_windows, i
     }
 }
 
+// Words of a bitmap of n <= FLAT_NODES columns.
+static int bitmap_words(int n) { return n <= (1 << 16) ? 2048 : n <= (1 << 17) ? 4096 : 8192; }
+
 // Words of the bitmap of the flat kernel, 0: the size classes take the graph.  Clearing and scanning the bitmap is a fixed
 // cost per window, so windows have to hold enough edges: at 200 000 nodes the lines cross between 143 edges a window on
 // average (55 us here, 50 there) and 269 (62, 85); with the smaller bitmaps the flat kernel was ahead at every
@@ -1674,10 +1795,22 @@ __global__ __launch_bounds__(256) void win_finish_kernel(int n, int n_windows, i
 static int flat_words(int n, int nnz, int n_windows)
 {
     if (n > FLAT_NODES || nnz == 0) return 0;
-    const int words = n <= (1 << 16) ? 2048 : n <= (1 << 17) ? 4096 : 8192;
+    const int words = bitmap_words(n);
     const int mean = nnz / n_windows;  // edges a window
     if (n_windows <= FINISH_WINDOWS) return n_windows <= 2048 || mean < 3 * MID_CAP ? words : 0;
     return mean >= (words == 8192 ? 192 : words / 64) && mean < (words == 8192 ? 3584 : MID_CAP) ? words : 0;
+}
+
+// Where a wave per window (win_lean_kernel) is ahead of a workgroup with all of the bitmap (win_flat_kernel, of the size classes below its
+// line): the largest bitmap, as long as few windows are above LEAN_EDGES and with them in the queue.  us, there / here, by edges a window:
+//   uniform, 200 000 nodes 79 41 / 32, 142 50 / 33, 269 61 / 38, 522 70 / 54, 1029 101 / 218; 262 000 nodes 522 86 / 63
+//   power law, 200 000 nodes 73 51 / 34, 304 64 / 48, 476 71 / 60, 937 96 / 132; R-MAT, 262 144 nodes 75 96 / 66, 492 121 / 107, 968 170 / 189
+//   half the bitmap: uniform, 100 000 nodes 79 30 / 27, 269 32 / 29; power law 73 32 / 28, 131 31 / 32, 304 33 / 36; R-MAT, 131 072 nodes 75 55 / 50
+static bool lean_better(int n, int nnz, int n_windows)
+{
+    if (n > FLAT_NODES || nnz <= FLAT_ALL_EDGES || n_windows <= FINISH_WINDOWS) return false;
+    const int mean = nnz / n_windows;
+    return bitmap_words(n) == 8192 ? mean < 640 : bitmap_words(n) == 4096 && mean >= 64 && mean < 128;
 }
 
 // Everything after the windows are condensed: prefix of the unique counts, window arrays, packed lists.
@@ -1709,7 +1842,9 @@ static int32_t finish_windows(const ftc_csr &g, ftc_windows &w, const WinWorkspa
 // The classes of windows are condensed by different kernels, none of which depends on another and each of
 // which fills only part of the GPU.  With three side streams and four events from the caller they run side
 // by side after the classification: the caller's stream forks into the side streams with an event and
-// joins them again before the scan.  Nothing here waits on the host and the library keeps no state.
+// joins them again before the scan.  Nothing here waits on the host and the library keeps no state.  Up to 2^20 nodes one of
+// the three streams is used: a fork and a join cost 15 us a stream (us, three / one / none: block model, 10^6 nodes with 32 entries 254 / 225 / 220,
+// R-MAT, 2^20 nodes with 31 306 / 304 / 332, with 8 148 / 140 / 154, uniform, 500 000 nodes with 16 134 / 107 / 100).
 int32_t launch_build_windows(const ftc_csr &g, ftc_windows &w, void *ws, size_t ws_bytes, const ftc_side_streams *side_in,
                              hipStream_t s)
 {
@@ -1720,13 +1855,16 @@ int32_t launch_build_windows(const ftc_csr &g, ftc_windows &w, void *ws, size_t 
                            w.block_partition, w.summary);
         return launch_status("build_windows scan");
     }
-    const int flat = flat_words(g.n, g.nnz, w.n_windows);
+    const bool lean = lean_better(g.n, g.nnz, w.n_windows);
+    const int flat = lean ? bitmap_words(g.n) : flat_words(g.n, g.nnz, w.n_windows);
     const int hub_thr = hub_threshold(g.n, g.nnz);
     const bool direct = (static_cast<int64_t>(g.n) + (1 << WB_RANGE_LOG2) - 1) >> WB_RANGE_LOG2 <= DIRECT_MAX_RANGES;
     const bool queued = g.nnz > WAVE_CAP;  // otherwise no window can be queued
+    const bool lean_queue = queued && g.n <= 1 << 20;
     int32_t st = FTC_OK;
     hipStream_t s_mid = s, s_large = s, s_hub = s;
     const ftc_side_streams *side = nullptr;
+    int n_side = 3;
     // compute units of the current device: the persistent grids are multiples of it
     int n_cu = 256, dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
@@ -1735,17 +1873,21 @@ int32_t launch_build_windows(const ftc_csr &g, ftc_windows &w, void *ws, size_t 
         n_cu = 256;
     }
     if (flat) {
-        const int limit = g.nnz > FLAT_ALL_EDGES ? MID_CAP : FLAT_ALL_EDGES;
+        const int limit = g.nnz > FLAT_ALL_EDGES ? (lean ? LEAN_EDGES : MID_CAP) : FLAT_ALL_EDGES;
         if (g.nnz > limit) hipLaunchKernelGGL(win_clear_kernel, dim3(1), dim3(64), 0, s, k.counters);
-        const int big = k.cap_direct < 2 * n_cu ? k.cap_direct : 2 * n_cu;
+        const int queue = k.cap_direct + (lean ? k.cap_b[1] : 0), big = queue < 2 * n_cu ? queue : 2 * n_cu;
 #define FTC_FLAT(W)                                                                                                    \
     do {                                                                                                               \
-        hipLaunchKernelGGL(win_flat_kernel<W>, dim3(w.n_windows), dim3(256), 0, s, g.n, g.row_ptr, g.col_idx, w.blk_h, \
-                           w.edge_to_row, w.edge_to_col, k.uniq_count, k.tmp_cols, limit, k.list_direct, k.counters);  \
+        if (lean)                                                                                                      \
+            hipLaunchKernelGGL(win_lean_kernel<1>, dim3(w.n_windows), dim3(64), 0, s, g.n, g.row_ptr, g.col_idx, w.blk_h, w.edge_to_row, \
+                               w.edge_to_col, k.uniq_count, k.tmp_cols, nullptr, nullptr, k.list_b[1], k.list_direct, k.counters); \
+        else                                                                                                           \
+            hipLaunchKernelGGL(win_flat_kernel<W>, dim3(w.n_windows), dim3(256), 0, s, g.n, g.row_ptr, g.col_idx, w.blk_h, \
+                               w.edge_to_row, w.edge_to_col, k.uniq_count, k.tmp_cols, limit, k.list_direct, k.counters); \
         if (g.nnz > limit)                                                                                             \
             hipLaunchKernelGGL(win_flat_big_kernel<W>, dim3(big), dim3(1024), 0, s, g.n, g.row_ptr, g.col_idx, w.blk_h, \
                                w.edge_to_row, w.edge_to_col, k.uniq_count, k.tmp_cols, k.list_direct,                  \
-                               k.counters + C_DIRECT);                                                                 \
+                               k.counters + C_DIRECT, k.list_b[1], k.counters + C_B2);                                                                 \
     } while (0)
         if (flat == 2048) FTC_FLAT(2048);
         else if (flat == 4096) FTC_FLAT(4096);
@@ -1767,10 +1909,11 @@ int32_t launch_build_windows(const ftc_csr &g, ftc_windows &w, void *ws, size_t 
         st = launch_status("build_windows classify");
         if (st != FTC_OK) return st;
         side = side_in;
+        n_side = lean_queue ? 1 : 3;
         if (side) {
             hipEvent_t fork = static_cast<hipEvent_t>(side->fork);
             bool good = hipEventRecord(fork, s) == hipSuccess;
-            for (int i = 0; i < 3 && good; ++i)
+            for (int i = 0; i < n_side && good; ++i)
                 good = hipStreamWaitEvent(static_cast<hipStream_t>(side->stream[i]), fork, 0) == hipSuccess;
             if (!good) {
                 // a side stream that did not take the dependency must not be used; the ones that did only
@@ -1782,12 +1925,13 @@ int32_t launch_build_windows(const ftc_csr &g, ftc_windows &w, void *ws, size_t 
             s_mid = static_cast<hipStream_t>(side->stream[0]);
             s_large = static_cast<hipStream_t>(side->stream[1]);
             s_hub = static_cast<hipStream_t>(side->stream[2]);
+            if (n_side == 1) s_large = s_hub = s_mid;
         }
     }
-    // The one-workgroup bitmap kernel is the longest chain of the build.  With side streams it stays on the caller's
-    // stream and is launched first (a dependency between streams costs about 20 us before the dependent kernel
-    // starts, and again at the join if the side stream is the last to finish); the wave kernel takes its place on the
-    // side stream.
+    // The one-workgroup bitmap kernel is the longest chain of the build of a skewed graph, the kernel of the windows of 257 to 1024 edges that
+    // of a flat one.  With side streams they stay on the caller's stream and are launched first (a dependency between streams
+    // costs about 20 us before the dependent kernel starts, and again at the join if the side stream is the last to finish);
+    // the wave kernel takes the place on the side stream.
     hipStream_t s_wave = s;
     if (queued && g.nnz > MID_CAP && direct) {
         hipLaunchKernelGGL(win_direct_kernel, dim3(k.cap_direct < n_cu ? k.cap_direct : n_cu), dim3(1024), 0, s, g.n,
@@ -1796,6 +1940,11 @@ int32_t launch_build_windows(const ftc_csr &g, ftc_windows &w, void *ws, size_t 
         st = launch_status("build_windows direct bitmap (above 4096 edges)");
         if (st != FTC_OK && !side) return st;
         s_wave = s_large;
+    }
+    if (lean_queue && st == FTC_OK) {
+        hipLaunchKernelGGL(win_lean_kernel<4>, dim3(k.cap_b[0]), dim3(64), 0, s, g.n, g.row_ptr, g.col_idx, w.blk_h,
+                           w.edge_to_row, w.edge_to_col, k.uniq_count, k.tmp_cols, k.list_b[0], k.counters + C_B1, nullptr, nullptr, nullptr);
+        st = launch_status("build_windows lean (257 .. 1024 edges)");
     }
     if (st == FTC_OK) {
         hipLaunchKernelGGL(win_wave_kernel, dim3(w.n_windows), dim3(64), 0, s_wave, g.n, g.row_ptr, g.col_idx, w.blk_h,
@@ -1827,7 +1976,7 @@ int32_t launch_build_windows(const ftc_csr &g, ftc_windows &w, void *ws, size_t 
             FTC_WB(2048, 2, 8, 1, C_B2, direct ? s_hub : s_mid);  // the hub stream is free when the direct kernel takes the hubs
             st = launch_status("build_windows bitmap (1025 .. 2048 edges)");
         }
-        if (st == FTC_OK) {
+        if (st == FTC_OK && !lean_queue) {
             // last on the caller's stream when that stream also runs the one-workgroup kernel: the stream that
             // finishes last should be the caller's, whose wait for the side streams then costs nothing
             FTC_WB(1024, 1, 13, 0, C_B1, (direct && g.nnz > MID_CAP) ? s : s_mid);
@@ -1855,7 +2004,7 @@ int32_t launch_build_windows(const ftc_csr &g, ftc_windows &w, void *ws, size_t 
         }
         if (side) {
             // join: also after a failed launch, so that no side stream is left ahead of the caller's
-            for (int i = 0; i < 3; ++i) {
+            for (int i = 0; i < n_side; ++i) {
                 if (hipEventRecord(static_cast<hipEvent_t>(side->join[i]), static_cast<hipStream_t>(side->stream[i])) !=
                         hipSuccess ||
                     hipStreamWaitEvent(s, static_cast<hipEvent_t>(side->join[i]), 0) != hipSuccess) {
