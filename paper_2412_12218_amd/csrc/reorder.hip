@@ -5,9 +5,9 @@
 // nodes, which the paper takes as given.
 //
 // Everything here is integer work with a unique result (stable sorts), built on two primitives:
-//   * an exclusive scan of int32 (three kernels: block sums, scan of the sums, block scans),
+//   * an exclusive scan of int32 (block sums and block scans; many blocks: a scan of the sums in between),
 //   * a stable least-significant-digit radix sort of (key, value) pairs with 8-bit digits.
-// The radix pass splits the input into wave tiles of RX_TILE consecutive elements.  A histogram
+// The radix pass splits the input into wave tiles of 64 times radix_rounds() consecutive elements.  A histogram
 // kernel counts the digits of every tile, the scan over the (digit, tile) table gives every tile
 // the first output position of each of its digits, and the scatter kernel walks the tile 64
 // elements at a time: lanes that hold the same digit find each other with eight ballots, take
@@ -20,6 +20,7 @@ namespace ftc {
 // ---- exclusive scan ---------------------------------------------------------------------------
 constexpr int SC_ITEMS = 16;
 constexpr int SC_BLOCK = 256 * SC_ITEMS;  // elements per workgroup
+constexpr int SC_SUMS_EACH = 1024;        // up to this many workgroups each adds up the sums itself: four loads a thread against a launch
 
 __device__ __forceinline__ int block_exclusive_scan(int v, int *total)
 {
@@ -62,7 +63,9 @@ __global__ __launch_bounds__(256) void scan_of_sums_kernel(int *sums, int n_sums
     if (threadIdx.x == 0) sums[n_sums] = carry;
 }
 
-// out[i] = sum of in[0 .. i); out[count] = total when `with_total`.  in == out is allowed.
+// out[i] = sum of in[0 .. i); out[count] = total when `with_total`.  in == out is allowed.  SCANNED: sums are prefixes; else every
+// workgroup adds up the ones before its own itself.
+template <bool SCANNED>
 __global__ __launch_bounds__(256) void scan_apply_kernel(const int *in, int64_t count, const int *__restrict__ sums,
                                                          int n_sums, int *out, int with_total)
 {
@@ -74,13 +77,26 @@ __global__ __launch_bounds__(256) void scan_apply_kernel(const int *in, int64_t 
         t += v[k];
     }
     int total;
-    int run = sums[blockIdx.x] + block_exclusive_scan(t, &total);
+    int before = 0, all = 0;
+    if constexpr (SCANNED) {
+        before = sums[blockIdx.x];
+    } else {
+        int b = 0, a = 0;
+        for (int i = threadIdx.x; i < n_sums; i += 256) {
+            const int x = sums[i];
+            a += x;
+            b += i < static_cast<int>(blockIdx.x) ? x : 0;
+        }
+        block_exclusive_scan(b, &before);
+        block_exclusive_scan(a, &all);
+    }
+    int run = before + block_exclusive_scan(t, &total);
 #pragma unroll
     for (int k = 0; k < SC_ITEMS; ++k) {
         if (base + k < count) out[base + k] = run;
         run += v[k];
     }
-    if (with_total && blockIdx.x == 0 && threadIdx.x == 0) out[count] = sums[n_sums];
+    if (with_total && blockIdx.x == 0 && threadIdx.x == 0) out[count] = SCANNED ? sums[n_sums] : all;
 }
 
 static size_t scan_ws(int64_t count) { return align_up(((count + SC_BLOCK - 1) / SC_BLOCK + 1) * sizeof(int), 256); }
@@ -91,15 +107,24 @@ static int32_t exclusive_scan(const int *in, int64_t count, int *out, bool with_
     const int n_sums = static_cast<int>((count + SC_BLOCK - 1) / SC_BLOCK);
     int *sums = static_cast<int *>(ws);
     hipLaunchKernelGGL(scan_sums_kernel, dim3(n_sums), dim3(256), 0, s, in, count, sums);
-    hipLaunchKernelGGL(scan_of_sums_kernel, dim3(1), dim3(256), 0, s, sums, n_sums);
-    hipLaunchKernelGGL(scan_apply_kernel, dim3(n_sums), dim3(256), 0, s, in, count, sums, n_sums, out,
-                       with_total ? 1 : 0);
+    if (n_sums <= SC_SUMS_EACH) {
+        hipLaunchKernelGGL(scan_apply_kernel<false>, dim3(n_sums), dim3(256), 0, s, in, count, sums, n_sums, out, with_total ? 1 : 0);
+    } else {
+        hipLaunchKernelGGL(scan_of_sums_kernel, dim3(1), dim3(256), 0, s, sums, n_sums);
+        hipLaunchKernelGGL(scan_apply_kernel<true>, dim3(n_sums), dim3(256), 0, s, in, count, sums, n_sums, out, with_total ? 1 : 0);
+    }
     return launch_status("exclusive scan");
 }
 
 // ---- stable radix sort of pairs ----------------------------------------------------------------
-constexpr int RX_ROUNDS = 32;
-constexpr int RX_TILE = 64 * RX_ROUNDS;  // elements per wave
+// Rounds of 64 elements a wave takes: few elements need short tiles to occupy the chip, many a small table.  Order by key, four passes, us, rounds
+// 8 / 16 / 32: 20 000 keys 79 / 93 / 121, 200 000 88 / 104 / 141, 500 000 107 / 118 / 151, 10^6 145 / 140 / 169, 2 10^6 224 / 208 / 217,
+// 4 10^6 396 / 332 / 346 (with a scan of the sums as a launch of its own and 32: 128, 147, 157, 176, 225, 351).
+constexpr int RX_ROUNDS_MANY = 32;
+static int radix_rounds(int64_t count) { return count <= (1 << 19) ? 8 : count <= (1 << 22) ? 16 : RX_ROUNDS_MANY; }
+// The table of short tiles takes up to two bytes an element, that of long ones half of one, which is what radix_ws() has room for: only the
+// orders of the n nodes are sorted with short tiles, in a workspace that holds label propagation's arrays of the same n (36 bytes a node, of
+// which an order takes 18).
 
 __device__ __forceinline__ void wave_lds_fence()
 {
@@ -109,6 +134,7 @@ __device__ __forceinline__ void wave_lds_fence()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+template <int RX_ROUNDS>
 __global__ __launch_bounds__(256) void radix_hist_kernel(const uint32_t *__restrict__ keys, int64_t count, int shift,
                                                          int64_t n_tiles, int *__restrict__ hist)
 {
@@ -120,7 +146,7 @@ __global__ __launch_bounds__(256) void radix_hist_kernel(const uint32_t *__restr
 #pragma unroll
     for (int k = 0; k < 4; ++k) cnt[lane + 64 * k] = 0;
     wave_lds_fence();
-    const int64_t base = tile * RX_TILE;
+    const int64_t base = tile * (64 * RX_ROUNDS);
 #pragma unroll 8
     for (int r = 0; r < RX_ROUNDS; ++r) {
         const int64_t i = base + r * 64 + lane;
@@ -131,6 +157,7 @@ __global__ __launch_bounds__(256) void radix_hist_kernel(const uint32_t *__restr
     for (int k = 0; k < 4; ++k) hist[(lane + 64 * k) * n_tiles + tile] = cnt[lane + 64 * k];
 }
 
+template <int RX_ROUNDS>
 __global__ __launch_bounds__(256) void radix_scatter_kernel(const uint32_t *__restrict__ keys,
                                                             const uint32_t *__restrict__ vals, int64_t count,
                                                             int shift, int64_t n_tiles, const int *__restrict__ pos,
@@ -145,7 +172,7 @@ __global__ __launch_bounds__(256) void radix_scatter_kernel(const uint32_t *__re
 #pragma unroll
     for (int k = 0; k < 4; ++k) next[lane + 64 * k] = pos[(lane + 64 * k) * n_tiles + tile];
     wave_lds_fence();
-    const int64_t base = tile * RX_TILE;
+    const int64_t base = tile * (64 * RX_ROUNDS);
     const uint64_t below = (1ull << lane) - 1ull;
     // the whole tile is loaded before the first element is placed: 2 * RX_ROUNDS loads in flight per lane
     uint32_t key[RX_ROUNDS], val[RX_ROUNDS];
@@ -178,7 +205,7 @@ __global__ __launch_bounds__(256) void radix_scatter_kernel(const uint32_t *__re
     }
 }
 
-static int64_t radix_tiles(int64_t count) { return (count + RX_TILE - 1) / RX_TILE; }
+static int64_t radix_tiles(int64_t count, int rounds = RX_ROUNDS_MANY) { return (count + 64 * rounds - 1) / (64 * rounds); }
 
 static size_t radix_ws(int64_t count)
 {
@@ -188,15 +215,17 @@ static size_t radix_ws(int64_t count)
 
 // Sorts `count` pairs by the low `bits` bits of the key, ascending and stable.  Input in (k0, v0);
 // the passes alternate between (k0, v0) and (k1, v1); the values of the last pass go to `v_final`
-// when it is not NULL.  *k_result / *v_result point at the sorted arrays.
+// when it is not NULL.  *k_result / *v_result point at the sorted arrays.  roomy: `ws` has room for the table of short tiles.
 static int32_t radix_sort_pairs(uint32_t *k0, uint32_t *v0, uint32_t *k1, uint32_t *v1, int64_t count, int bits,
-                                uint32_t *v_final, uint32_t **k_result, uint32_t **v_result, void *ws, hipStream_t s)
+                                uint32_t *v_final, uint32_t **k_result, uint32_t **v_result, void *ws, hipStream_t s,
+                                bool roomy = false)
 {
     *k_result = k0;
     *v_result = v0;
     if (count <= 0) return FTC_OK;
     const int passes = (bits + 7) / 8 < 1 ? 1 : (bits + 7) / 8;
-    const int64_t n_tiles = radix_tiles(count);
+    const int rounds = roomy ? radix_rounds(count) : RX_ROUNDS_MANY;
+    const int64_t n_tiles = radix_tiles(count, rounds);
     if (256 * n_tiles > INT32_MAX) {
         set_error("radix sort: %lld elements are more than the digit table can index", static_cast<long long>(count));
         return FTC_EUNSUPPORTED;
@@ -207,11 +236,17 @@ static int32_t radix_sort_pairs(uint32_t *k0, uint32_t *v0, uint32_t *k1, uint32
     uint32_t *ki = k0, *vi = v0, *ko = k1, *vo = v1;
     for (int p = 0; p < passes; ++p) {
         uint32_t *v_dst = (p == passes - 1 && v_final) ? v_final : vo;
-        hipLaunchKernelGGL(radix_hist_kernel, dim3(grid), dim3(256), 0, s, ki, count, 8 * p, n_tiles, table);
+#define FTC_RX(KERNEL, ...)                                                                       \
+    do {                                                                                          \
+        if (rounds == 8) hipLaunchKernelGGL(KERNEL<8>, dim3(grid), dim3(256), 0, s, __VA_ARGS__);  \
+        else if (rounds == 16) hipLaunchKernelGGL(KERNEL<16>, dim3(grid), dim3(256), 0, s, __VA_ARGS__); \
+        else hipLaunchKernelGGL(KERNEL<RX_ROUNDS_MANY>, dim3(grid), dim3(256), 0, s, __VA_ARGS__); \
+    } while (0)
+        FTC_RX(radix_hist_kernel, ki, count, 8 * p, n_tiles, table);
         const int32_t st = exclusive_scan(table, 256 * n_tiles, table, false, ws_scan, s);
         if (st != FTC_OK) return st;
-        hipLaunchKernelGGL(radix_scatter_kernel, dim3(grid), dim3(256), 0, s, ki, vi, count, 8 * p, n_tiles, table, ko,
-                           v_dst);
+        FTC_RX(radix_scatter_kernel, ki, vi, count, 8 * p, n_tiles, table, ko, v_dst);
+#undef FTC_RX
         *k_result = ko;
         *v_result = v_dst;
         uint32_t *t = ki; ki = ko; ko = t;
@@ -311,7 +346,7 @@ int32_t launch_degree_order(const ftc_csr &g, int mode, int *perm, int *inv, voi
     hipLaunchKernelGGL(degree_keys_kernel, dim3((n + 255) / 256), dim3(256), 0, s, n, g.row_ptr, mode, k0, v0);
     uint32_t *kr, *vr;
     const int bits = mode == FTC_ORDER_DEGREE ? 31 : 6;
-    const int32_t st = radix_sort_pairs(k0, v0, k1, v1, n, bits, reinterpret_cast<uint32_t *>(perm), &kr, &vr, ws_sort, s);
+    const int32_t st = radix_sort_pairs(k0, v0, k1, v1, n, bits, reinterpret_cast<uint32_t *>(perm), &kr, &vr, ws_sort, s, true);
     if (st != FTC_OK) return st;
     hipLaunchKernelGGL(invert_perm_kernel, dim3((n + 255) / 256), dim3(256), 0, s, n, perm, inv);
     return launch_status("degree order");
@@ -340,7 +375,7 @@ int32_t launch_order_by_key(int n, const int *keys_in, int *perm, int *inv, int 
     void *ws_sort = p + 4 * arr;
     hipLaunchKernelGGL(key_pairs_kernel, dim3((n + 255) / 256), dim3(256), 0, s, n, keys_in, k0, v0, flag);
     uint32_t *kr, *vr;
-    const int32_t st = radix_sort_pairs(k0, v0, k1, v1, n, 31, reinterpret_cast<uint32_t *>(perm), &kr, &vr, ws_sort, s);
+    const int32_t st = radix_sort_pairs(k0, v0, k1, v1, n, 31, reinterpret_cast<uint32_t *>(perm), &kr, &vr, ws_sort, s, true);
     if (st != FTC_OK) return st;
     hipLaunchKernelGGL(invert_perm_kernel, dim3((n + 255) / 256), dim3(256), 0, s, n, perm, inv);
     return launch_status("order by key");

@@ -369,3 +369,18 @@ def test_rounds_that_leave_out_the_rows_that_cannot_change(kind, n, deg):
         best = torch.zeros(n, dtype=torch.int64, device="cuda").scatter_reduce_(0, key // n, votes * n + (n - 1 - key % n), "amax")
         label = torch.where(best > 0, n - 1 - best % n, label)
         assert torch.equal(B.ftc_label_propagation(g, rounds).long(), label), f"{rounds} rounds"
+
+
+@pytest.mark.parametrize("n", [1, 511, 512, 513, (1 << 19) - 1, 1 << 19, (1 << 19) + 1, (1 << 22), (1 << 22) + 1])
+def test_order_by_key_at_the_lines_of_its_tiles(n):
+    """Keys of all four digits, many equal: stable, in a workspace of exactly the size that is asked for a graph without entries."""
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    keys = torch.randint(1 << 31, (n,), generator=gen, device="cuda").to(torch.int32)
+    keys[::3] = keys[::3] % 1000
+    size = B.lib().ftc_reorder_workspace_bytes(n, 0)
+    ws = torch.full((size + 4096,), 0x5a, dtype=torch.uint8, device="cuda")
+    perm, inv, flag = B.ftc_order_by_key(keys, ws=ws[:size])
+    ref = torch.sort(keys, stable=True).indices
+    assert int(flag.item()) == 0 and torch.equal(perm.long(), ref)
+    assert torch.equal(inv.long()[ref], torch.arange(n, device="cuda"))
+    assert torch.all(ws[size:] == 0x5a)
