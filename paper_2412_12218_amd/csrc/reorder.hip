@@ -266,12 +266,14 @@ __global__ void reorder_set_int_kernel(int *p, int v) { *p = v; }
 
 // ---- degree statistics ---------------------------------------------------------------------------
 // stats[0] = sum of squared row lengths, stats[1] = longest row (both exact integers).
-__global__ __launch_bounds__(256) void degree_stats_kernel(int n, const int *__restrict__ row_ptr,
+__global__ __launch_bounds__(1024) void degree_stats_kernel(int n, const int *__restrict__ row_ptr,
                                                            unsigned long long *__restrict__ stats)
 {
-    __shared__ unsigned long long red_s[4], red_m[4];
+    constexpr int NT = 1024;
+    __shared__ unsigned long long red_s[NT / 64], red_m[NT / 64];
     unsigned long long sq = 0, mx = 0;
-    for (int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; i < n; i += static_cast<int64_t>(gridDim.x) * 256) {
+#pragma unroll 4
+    for (int64_t i = static_cast<int64_t>(blockIdx.x) * NT + threadIdx.x; i < n; i += static_cast<int64_t>(gridDim.x) * NT) {
         const unsigned long long d = static_cast<unsigned long long>(row_ptr[i + 1] - row_ptr[i]);
         sq += d * d;
         mx = d > mx ? d : mx;
@@ -285,9 +287,12 @@ __global__ __launch_bounds__(256) void degree_stats_kernel(int n, const int *__r
     if ((threadIdx.x & 63) == 0) { red_s[threadIdx.x >> 6] = sq; red_m[threadIdx.x >> 6] = mx; }
     __syncthreads();
     if (threadIdx.x == 0) {
-        unsigned long long m2 = red_m[0];
-        for (int w = 1; w < 4; ++w) m2 = red_m[w] > m2 ? red_m[w] : m2;
-        atomicAdd(&stats[0], red_s[0] + red_s[1] + red_s[2] + red_s[3]);
+        unsigned long long m2 = red_m[0], s2 = red_s[0];
+        for (int w = 1; w < NT / 64; ++w) {
+            m2 = red_m[w] > m2 ? red_m[w] : m2;
+            s2 += red_s[w];
+        }
+        atomicAdd(&stats[0], s2);
         atomicMax(&stats[1], m2);
     }
 }
@@ -299,8 +304,9 @@ int32_t launch_degree_stats(const ftc_csr &g, int64_t *stats, hipStream_t s)
     unsigned long long *st = reinterpret_cast<unsigned long long *>(stats);
     hipLaunchKernelGGL(clear_stats_kernel, dim3(1), dim3(1), 0, s, st);
     if (g.n > 0) {
-        const int blocks = (g.n + 255) / 256 < 1024 ? (g.n + 255) / 256 : 1024;
-        hipLaunchKernelGGL(degree_stats_kernel, dim3(blocks), dim3(256), 0, s, g.n, g.row_ptr, st);
+        // two atomics on the same two words a workgroup, 12 ns each: 1024 workgroups 28 us for 10^6 rows, 128 7
+        const int blocks = ceil_div(g.n, 1024) < 128 ? ceil_div(g.n, 1024) : 128;
+        hipLaunchKernelGGL(degree_stats_kernel, dim3(blocks), dim3(1024), 0, s, g.n, g.row_ptr, st);
     }
     return launch_status("degree statistics");
 }

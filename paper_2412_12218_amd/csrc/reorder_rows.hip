@@ -10,8 +10,8 @@
 //                               at most 32 768 entries are sorted in LDS instead of counted (many_ranges()).
 // What bounds them: the look-up.  Every entry is one 4-byte gather from an array that about fills an L2 (4 MB at
 // a million nodes); the streams around it (column ids in, columns out) are read and written once, non-temporal.
-// On the block model with a million nodes and 32 M entries a round of label propagation takes 0.22 ms (the first, without look-ups, 0.08,
-// ten together 1.81: see vote_check_kernel) and the relabelled graph 0.33 ms (R-MAT, 2^20 nodes: 0.31); sorting all entries by label and row with the global radix sort took
+// On the block model with a million nodes and 32 M entries a round of label propagation takes 0.21 ms (the first, without look-ups, 0.06,
+// ten together 1.74: see vote_check_kernel) and the relabelled graph 0.33 ms (R-MAT, 2^20 nodes: 0.31); sorting all entries by label and row with the global radix sort took
 // 4.0 and 4.1 ms.  The sorting network is the other half: with min, max and a selection per stage, rows of 33 to 64 two at a time,
 // rows of any length below side by side in halves of the wave and each row's look-ups waiting for the one's before, a round took
 // 0.24 ms (500 000 nodes with nine entries each, the whole plan: 1.39 / 1.01 ms).
@@ -304,29 +304,60 @@ __device__ __forceinline__ void queued_row(const Use &u, int r, int start, int l
 }
 
 // The rows among the wave's RS_ROWS with more than `above` and at most W entries: 64 / W of them side by side in the wave, SETS such
-// sets in flight.  order, changed: LDS of the wave; votes: bit r - r0 of *changed is set where the label of row r is another than old_l.
+// sets in flight.  order, win: LDS of the wave; votes: win[r - r0] becomes the winner of row r.  Which rows a set holds is scalar work for
+// sets of one or two, and the winners leave in one store for all rows: through LDS, cross-lane moves and a store per row a round without
+// look-ups took 79 us, this way 64, one with look-ups 217 / 211 (block model with 10^6 nodes, 32 M entries).
 template <class Use, int W, int SETS>
-__device__ __forceinline__ void short_rows(const Use &u, int r0, int above, int start_l, int len_l, int dst_l, int old_l, int lane, int *order, uint32_t *changed)
+__device__ __forceinline__ void short_rows(const Use &u, int r0, int above, int start_l, int len_l, int dst_l, int lane, int *order, int *win)
 {
     constexpr int PER = 64 / W;
     const int part = lane / W, li = lane % W;
     const bool mine = len_l > above && len_l <= W;
-    const unsigned long long rows = __builtin_amdgcn_ballot_w64(mine);
-    const int count = __popcll(rows);
+    uint32_t left = static_cast<uint32_t>(__builtin_amdgcn_ballot_w64(mine));  // rows that are not in a set yet
+    const int count = __popc(left);
     if (count == 0) return;  // uniform
-    wave_lds_sync();  // the order of the class before has been read
-    if (mine) order[__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(rows >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(rows), 0u))] = lane;
-    wave_lds_sync();
+    if constexpr (PER > 2) {
+        wave_lds_sync();  // the order of the class before has been read
+        if (mine) order[__popc(left & ((1u << lane) - 1u))] = lane;
+        wave_lds_sync();
+    }
+    int last = 0;
+    auto next_row = [&](int &st, int &ln, int &dst, bool &ok) {  // beyond the last row that one's
+        ok = left != 0u;
+        if (ok) last = __ffs(static_cast<int>(left)) - 1;
+        left &= left - 1u;
+        st = __builtin_amdgcn_readlane(start_l, last);
+        ln = __builtin_amdgcn_readlane(len_l, last);
+        dst = Use::VOTES ? 0 : __builtin_amdgcn_readlane(dst_l, last);
+        return last;
+    };
     for (int s0 = 0; s0 < count; s0 += PER * SETS) {
-        int t[SETS], len[SETS], c[SETS], v[SETS], old[SETS];
+        int t[SETS], len[SETS], c[SETS], v[SETS], dst[SETS];
 #pragma unroll
         for (int p = 0; p < SETS; ++p) {
-            const int at = s0 + p * PER + part;
-            t[p] = order[min(at, count - 1)];
-            const int st = __shfl(start_l, t[p], 64), ln = __shfl(len_l, t[p], 64);
+            int st, ln;
+            bool ok;
+            if constexpr (PER == 1) {
+                t[p] = next_row(st, ln, dst[p], ok);
+            } else if constexpr (PER == 2) {
+                int st1, ln1, dst1;
+                bool ok1;
+                const int t0 = next_row(st, ln, dst[p], ok), t1 = next_row(st1, ln1, dst1, ok1);
+                t[p] = part ? t1 : t0;
+                st = part ? st1 : st;
+                ln = part ? ln1 : ln;
+                dst[p] = part ? dst1 : dst[p];
+                ok = part ? ok1 : ok;
+            } else {
+                const int at = s0 + p * PER + part;
+                ok = at < count;
+                t[p] = order[min(at, count - 1)];
+                st = __shfl(start_l, t[p], 64);
+                ln = __shfl(len_l, t[p], 64);
+                dst[p] = Use::VOTES ? 0 : __shfl(dst_l, t[p], 64);
+            }
             c[p] = __builtin_nontemporal_load(u.col_idx + st + min(li, ln - 1));
-            len[p] = at < count ? ln : 0;
-            old[p] = Use::VOTES ? __shfl(old_l, t[p], 64) : 0;
+            len[p] = ok ? ln : 0;
         }
 #pragma unroll
         for (int p = 0; p < SETS; ++p) v[p] = u.look(c[p]);
@@ -336,23 +367,22 @@ __device__ __forceinline__ void short_rows(const Use &u, int r0, int above, int 
             const bool in = li < len[p];
             int x[1] = {u.settle(c[p], v[p], in)};
             if (!in) x[0] = RS_NONE;
-            auto vote = [&](int w) {
-                if constexpr (Use::VOTES) {
-                    u.out[r0 + t[p]] = w;
-                    if (u.changed && w != old[p]) atomicOr(changed, 1u << t[p]);
-                }
-            };
             if constexpr (Use::FIRST) {
                 // distinct columns in ascending order have a vote each, and the first is the smallest
                 const int prev = __builtin_amdgcn_update_dpp(0, x[0], 0x138, 0xf, 0xf, false);  // wave_shr:1
                 if (__builtin_amdgcn_ballot_w64(in && li > 0 && x[0] <= prev) == 0ull) {
-                    if (li == 0 && len[p] > 0) vote(x[0]);
+                    if (li == 0 && len[p] > 0) win[t[p]] = x[0];
                     continue;
                 }
             } else if constexpr (Use::VOTES && W > 16) {
                 // a label that more than half of a row's entries hold wins without any sorting; two of the entries are tried.
                 // Labels settle after a few rounds and most rows pass then
-                const int c0 = __shfl(x[0], lane & ~(W - 1), 64), c1 = __shfl(x[0], (lane & ~(W - 1)) + 7, 64);
+                int c0 = __builtin_amdgcn_readlane(x[0], 0), c1 = __builtin_amdgcn_readlane(x[0], 7);
+                if constexpr (W == 32) {
+                    const int d0 = __builtin_amdgcn_readlane(x[0], 32), d1 = __builtin_amdgcn_readlane(x[0], 39);
+                    c0 = part ? d0 : c0;
+                    c1 = part ? d1 : c1;
+                }
                 unsigned long long e0 = __builtin_amdgcn_ballot_w64(in && x[0] == c0), e1 = __builtin_amdgcn_ballot_w64(in && x[0] == c1);
                 if constexpr (W == 32) {
                     e0 = lane < 32 ? e0 & 0xffffffffull : e0 >> 32;
@@ -360,15 +390,15 @@ __device__ __forceinline__ void short_rows(const Use &u, int r0, int above, int 
                 }
                 const bool won0 = 2 * __popcll(e0) > len[p], won1 = 2 * __popcll(e1) > len[p];
                 if (__builtin_amdgcn_ballot_w64(len[p] > 0 && !won0 && !won1) == 0ull) {
-                    if (li == 0 && len[p] > 0) vote(won0 ? c0 : c1);
+                    if (li == 0 && len[p] > 0) win[t[p]] = won0 ? c0 : c1;
                     continue;
                 }
             }
             bitonic_sort<W, 1, W>(x);
             if constexpr (Use::VOTES) {
                 const int w = longest_run<1, W>(x, len[p], lane);
-                if (li == 0 && len[p] > 0) vote(w);
-            } else row_done<Use, 1, W>(u, r0 + t[p], __shfl(dst_l, t[p], 64), len[p], x, lane);
+                if (li == 0 && len[p] > 0) win[t[p]] = w;
+            } else row_done<Use, 1, W>(u, r0 + t[p], dst[p], len[p], x, lane);
         }
     }
 }
@@ -566,29 +596,29 @@ __global__ __launch_bounds__(256, 6) void row_sort_kernel(Use u, RowQueues q, in
     const int64_t r0 = (static_cast<int64_t>(blockIdx.x - queue_blocks) * 4 + wave) * RS_ROWS;
     if (r0 >= u.n) return;
     int start_l = 0, len_l = 0, dst_l = 0, old_l = 0;
+    bool short_row = false;  // votes: this lane's row is decided here
     const int r_l = static_cast<int>(r0) + lane;
     if (lane < RS_ROWS && r_l < u.n) {
         u.row(r_l, start_l, len_l);
         dst_l = u.rp[r_l];
         if constexpr (Use::VOTES) {
             old_l = u.before(r_l);
-            if (u.todo && len_l <= RS_SHORT && !(u.todo[r0 >> 5] >> lane & 1u)) len_l = 0;  // nothing in the row has changed
-            if (len_l == 0) u.out[r_l] = old_l;  // as does a row without entries, it keeps its label
+            short_row = len_l <= RS_SHORT;
+            if (u.todo && short_row && !(u.todo[r0 >> 5] >> lane & 1u)) len_l = 0;  // nothing in the row has changed
         }
     }
-    __shared__ int order[4][RS_ROWS];
-    __shared__ uint32_t changed[4];
+    __shared__ int order[4][RS_ROWS], win[4][RS_ROWS];
+    static_assert(RS_ROWS == 32, "a word of u.todo and of u.changed, of the masks in short_rows()");
+    short_rows<Use, 16, 4>(u, static_cast<int>(r0), 0, start_l, len_l, dst_l, lane, order[wave], win[wave]);
+    short_rows<Use, 32, 4>(u, static_cast<int>(r0), 16, start_l, len_l, dst_l, lane, order[wave], win[wave]);
+    short_rows<Use, 64, 4>(u, static_cast<int>(r0), 32, start_l, len_l, dst_l, lane, order[wave], win[wave]);
     if constexpr (Use::VOTES) {
-        if (lane == 0) changed[wave] = 0u;
-        static_assert(RS_ROWS == 32, "a word of u.todo and of u.changed");
-    }
-    short_rows<Use, 16, 4>(u, static_cast<int>(r0), 0, start_l, len_l, dst_l, old_l, lane, order[wave], &changed[wave]);
-    short_rows<Use, 32, 4>(u, static_cast<int>(r0), 16, start_l, len_l, dst_l, old_l, lane, order[wave], &changed[wave]);
-    short_rows<Use, 64, 4>(u, static_cast<int>(r0), 32, start_l, len_l, dst_l, old_l, lane, order[wave], &changed[wave]);
-    if constexpr (Use::VOTES) {
-        if (!u.changed) return;
         wave_lds_sync();
-        const uint32_t m = changed[wave];
+        // a row that has no entries, or none that changed, keeps its label
+        const int w = len_l > 0 ? win[wave][lane & (RS_ROWS - 1)] : old_l;
+        if (short_row) u.out[r_l] = w;
+        if (!u.changed) return;
+        const uint32_t m = static_cast<uint32_t>(__builtin_amdgcn_ballot_w64(short_row && w != old_l));
         const int first = static_cast<int>(r0) >> u.shift;  // the 32 >> shift bits of these rows lie in one word
         uint32_t bits = 0u;
         if (u.shift == 0) bits = m;
@@ -775,7 +805,7 @@ __global__ __launch_bounds__(RS_NT) void row_sort_dup_kernel(Relabel u, RowQueue
 // into LDS (up to 2^20 nodes one each, above one for two or four nodes in a row).  Bound by reading the column ids.  Where most
 // rows would be left (the changed share times the mean number of entries above VT_MOST) all of them are, at once.
 // On the block model with a million nodes, 32 M entries, a check that leaves rows out takes 50 us, one that doesn't 5; the ninth and the
-// tenth round take 39 and 25 us after it instead of 212.
+// tenth round take 37 and 25 us after it instead of 210.
 constexpr int VT_BITS_LOG2 = 20;
 constexpr float VT_MOST = 0.6f;
 
@@ -857,7 +887,7 @@ static int64_t queue_cap(int nnz, int longer_than) { return nnz / (longer_than +
 
 // Label propagation looks for the rows that may change from this many entries on: a launch more a round (5 us) against the share of
 // a round (6.5 us a million entries) that the last ones save.  Ten rounds on the block model, with the look-ups of the first round, without the
-// check / as here: 32 M entries 2204 / 1811 us, 23 M 1472 / 1250, 16 M 1077 / 920.
+// check / as here: 32 M entries 2204 / 1738 us, 23 M 1472 / 1234, 16 M 1077 / 912.
 constexpr int VT_FROM = 12000000;
 static bool votes_are_checked(int nnz) { return nnz >= VT_FROM; }
 static int changed_shift(int n)
