@@ -5,7 +5,10 @@
 // first, in the operands' layout (eight consecutive k of a column are one 16-byte word), in pieces.
 //   A operand  lane l holds X[row0 + l%16][k0 + (l/16) 8 .. +7], loaded at element alignment; the chunk's are all loaded before W is
 //              staged, so that a chunk waits for memory once;
-//   C          lane l holds Z[row0 + (l/16) 4 + i][n0 + l%16].
+//   C          W is the first operand of the instruction (QUADS): lane l holds Z[row0 + l%16][n0 + (l/16) 4 + i], four columns that leave in
+//              one store at the alignment of an element.  With X first, a column a lane, us, that way / this: dX fp16 2^20 rows 8 -> 32 48 / 34,
+//              fp32 100 000 rows 10 -> 128 29 / 24, Z fp32 1 000 000 x 33 -> 2 39 / 29, 300 -> 128 82.5 / 79.3, fp16 179 245 x 18 -> 64 18.1 / 13.7,
+//              400 000 x 301 -> 128 287 / 267; but fp32 100 000 x 128 -> 10 13.1 / 13.6, 1433 -> 16 139.8 / 142.7, which stay with it.
 // Where one chunk holds all of W a workgroup walks over the rows and stages it once.
 //
 // Bound by reading X (and writing Z) up to about 32 columns, then by the chain load, stage, multiply of a chunk, which four workgroups
@@ -67,7 +70,7 @@ __device__ __forceinline__ void load_eight(const void *base, int64_t idx, int le
     }
 }
 
-template <class T, int NT, bool TRANS>
+template <class T, int NT, bool TRANS, bool QUADS>
 __global__ __launch_bounds__(256, NT == 8 ? 2 : 4) void gemm_tile_kernel(int n, const void *__restrict__ X, int ldx, int d_in,
                                                                          const void *__restrict__ W, int w_ld, int wdt, int d_out,
                                                                          void *__restrict__ Z, int ldz, int zdt, Epi epi, int n_blocks)
@@ -164,13 +167,15 @@ __global__ __launch_bounds__(256, NT == 8 ? 2 : 4) void gemm_tile_kernel(int n, 
                     if (nt + 1 < NT) load_b(nt + 1);
                     asm volatile("" ::: "memory");  // (else all tiles' loads are moved up here, and their registers with them)
                     if constexpr (P == 3) {
-                        mfma_split(a, b[nt & 1], acc[0][nt], acc[1][nt]);
+                        if constexpr (QUADS) mfma_split(b[nt & 1], a, acc[0][nt], acc[1][nt]);
+                        else mfma_split(a, b[nt & 1], acc[0][nt], acc[1][nt]);
                     } else {
                         split_f32x4 &c = acc[TOTAL == 2 ? s >> 1 : 0][nt];
+                        const uint4 first = b[nt & 1][0], second = x[s].h;
                         if constexpr (std::is_same<T, F16>::value)
-                            c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(gt_half8, x[s].h), __builtin_bit_cast(gt_half8, b[nt & 1][0]), c, 0, 0, 0);
+                            c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(gt_half8, first), __builtin_bit_cast(gt_half8, second), c, 0, 0, 0);
                         else
-                            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(split_bf16x8, x[s].h), __builtin_bit_cast(split_bf16x8, b[nt & 1][0]), c, 0, 0, 0);
+                            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(split_bf16x8, first), __builtin_bit_cast(split_bf16x8, second), c, 0, 0, 0);
                     }
                 }
             }
@@ -184,15 +189,32 @@ __global__ __launch_bounds__(256, NT == 8 ? 2 : 4) void gemm_tile_kernel(int n, 
             }
         }
         const bool plain = P == 3 && (__builtin_amdgcn_ballot_w64(odd) != 0 || w_odd);  // this wave's rows, in fp32
+        if constexpr (!QUADS) {
+            static_assert(P == 3, "16-bit operands change places");
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int64_t row = row0 + kb * 4 + i;
-            if (row < n) {
+            for (int i = 0; i < 4; ++i) {
+                const int64_t row = row0 + kb * 4 + i;
+                if (row >= n || plain) continue;
                 const float f = epi.factor(row);
 #pragma unroll
-                for (int nt = 0; nt < NT; ++nt) {
-                    const int o = nt * 16 + m;
-                    if (o < cols && !plain) store_elem(Z, row * ldz + col0 + o, zdt, epi.apply(f, P == 3 ? acc[0][nt][i] + acc[1][nt][i] : acc[TOTAL][nt][i]));
+                for (int nt = 0; nt < NT; ++nt)
+                    if (nt * 16 + m < cols) store_elem(Z, row * ldz + col0 + nt * 16 + m, zdt, epi.apply(f, acc[0][nt][i] + acc[1][nt][i]));
+            }
+        } else if (row0 + m < n && !plain) {
+            const int64_t row = row0 + m;
+            const float f = epi.factor(row);
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                const int o = nt * 16 + kb * 4;
+                float z[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) z[i] = epi.apply(f, P == 3 ? acc[0][nt][i] + acc[1][nt][i] : acc[TOTAL][nt][i]);
+                if (o + 4 <= cols) {
+                    store_vec_any<4>(Z, row * ldz + col0 + o, zdt, z);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (o + i < cols) store_elem(Z, row * ldz + col0 + o + i, zdt, z[i]);
                 }
             }
         }
@@ -223,15 +245,22 @@ static void gemm_tile_t(int n, const void *X, int ldx, int d_in, const void *W, 
     const int n_blocks = static_cast<int>((static_cast<int64_t>(n) + 63) / 64);
     const int groups = (d_out + nt * 16 - 1) / (nt * 16);
     const int grid = d_in <= GemmChunk<T>::KC && n_blocks > 2048 ? 2048 : n_blocks;
-#define FTC_GT(N)                                                                                                                   \
-    if (nt == N)                                                                                                                    \
-        hipLaunchKernelGGL((gemm_tile_kernel<T, N, TRANS>), dim3(grid, groups), dim3(256), 0, s, n, X, ldx, d_in, W, w_ld, wdt, d_out, Z, \
-                           ldz, zdt, epi, n_blocks)
+#define FTC_GT1(N, Q)                                                                                                                  \
+    hipLaunchKernelGGL((gemm_tile_kernel<T, N, TRANS, Q>), dim3(grid, groups), dim3(256), 0, s, n, X, ldx, d_in, W, w_ld, wdt, d_out, Z, \
+                       ldz, zdt, epi, n_blocks)
+#define FTC_GT(N) if (nt == N) FTC_GT1(N, true)
+    if constexpr (T::BYTES == 4 && !TRANS) {
+        if (nt == 1 && d_in > GemmChunk<T>::KC) {
+            FTC_GT1(1, false);
+            return;
+        }
+    }
     FTC_GT(1);
     FTC_GT(2);
     FTC_GT(4);
     if constexpr (T::BYTES == 2) FTC_GT(8);
 #undef FTC_GT
+#undef FTC_GT1
 }
 
 int32_t launch_gemm_tile(int n, const void *X, int ldx, int dt, int d_in, const void *W, int d_out, void *Z, int ldz, int zdt, Epi epi,
