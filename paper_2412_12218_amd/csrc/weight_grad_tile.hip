@@ -137,6 +137,7 @@ __global__ __launch_bounds__(256, NA * NB >= 64 ? 2 : NA * NB >= 32 ? 3 : 4) voi
         return odd;
     };
     if (r_begin < r_end) load_step(r_begin);
+    __syncthreads();  // odd_s is cleared before any wave sets it in the first step
     int step = 0;
     for (int64_t r0 = r_begin; r0 < r_end; r0 += WT_ROWS, ++step) {  // uniform
         bool odd = false;

@@ -105,3 +105,15 @@ def test_weight_gradient_of_numbers_that_bf16_pieces_cannot_hold(dtype):
     terms = X.double().abs().T @ G.double().abs()
     ok = torch.isfinite(terms)
     assert float(((dW.double() - ref).abs() / terms)[ok].max()) <= 1e-5
+
+
+@pytest.mark.parametrize("dtype", [F32, F16, BF16])
+@pytest.mark.parametrize("column", [0, -1])
+def test_weight_gradient_of_an_infinity_in_the_first_step_of_every_share(dtype, column):
+    """Row 31 of every 32 rows is loaded by the last wave, row 0 by the first: whichever wave finds the infinity, the step is not taken in pieces."""
+    gen = torch.Generator().manual_seed(3)
+    n, d_in, d_out = 40_000, 48, 64
+    X, G = (torch.rand((n, d_in), generator=gen) + 0.5).to(dtype).cuda(), torch.randn((n, d_out), generator=gen).cuda()
+    G[31 if column else 0::32, column] = float("inf")
+    dW = B.ftc_update_gemm_backward(X, torch.zeros((d_in, d_out), dtype=dtype).cuda(), G, want_dX=False)[1]
+    assert torch.isposinf(dW[:, column]).all() and int(torch.isfinite(dW).sum()) == d_in * (d_out - 1)
