@@ -70,11 +70,23 @@ __device__ __forceinline__ void load_eight(const void *base, int64_t idx, int le
     }
 }
 
-template <class T, int NT, bool TRANS, bool QUADS>
+template <class T>
+__device__ __forceinline__ float eight_value(const Eight<T> &e, int j)
+{
+    if constexpr (T::BYTES == 4) return e.f[j];
+    else {
+        const uint32_t w = j < 2 ? e.h.x : j < 4 ? e.h.y : j < 6 ? e.h.z : e.h.w, b = j & 1 ? w >> 16 : w & 0xffffu;
+        return std::is_same<T, F16>::value ? f16_bits_to_f32(b) : bf16_bits_to_f32(b);
+    }
+}
+
+// TW: the type of W, another than X's only for TRANS.
+template <class T, int NT, bool TRANS, bool QUADS, class TW>
 __global__ __launch_bounds__(256, NT == 8 ? 2 : 4) void gemm_tile_kernel(int n, const void *__restrict__ X, int ldx, int d_in,
-                                                                         const void *__restrict__ W, int w_ld, int wdt, int d_out,
+                                                                         const void *__restrict__ W, int w_ld, int d_out,
                                                                          void *__restrict__ Z, int ldz, int zdt, Epi epi, int n_blocks)
 {
+    static_assert(TRANS ? T::BYTES == 4 : std::is_same<T, TW>::value, "types of the products");
     constexpr int P = GemmChunk<T>::PIECES, KC = GemmChunk<T>::KC, KP = KC + 8, COLS = 16 * NT, STEPS = KC / 32, SB = 2;
     __shared__ __align__(16) uint16_t Ws[P][COLS * KP];
     __shared__ int w_odd;  // some of W can't be taken in pieces
@@ -82,7 +94,7 @@ __global__ __launch_bounds__(256, NT == 8 ? 2 : 4) void gemm_tile_kernel(int n, 
     const int m = lane & 15, kb = lane >> 4;
     const int col0 = blockIdx.y * COLS, cols = min(COLS, d_out - col0);
     const bool whole = d_in <= KC;
-    constexpr int OWN = T::BYTES == 4 ? FTC_F32 : std::is_same<T, F16>::value ? FTC_F16 : FTC_BF16;
+    constexpr int WDT = TW::BYTES == 4 ? FTC_F32 : std::is_same<TW, F16>::value ? FTC_F16 : FTC_BF16;
     auto w_index = [&](int k, int o) {
         return TRANS ? static_cast<int64_t>(col0 + o) * w_ld + k : static_cast<int64_t>(k) * w_ld + col0 + o;
     };
@@ -120,11 +132,22 @@ __global__ __launch_bounds__(256, NT == 8 ? 2 : 4) void gemm_tile_kernel(int n, 
                         const int o = TRANS ? t / (k_end / 8) : t % COLS, k = (TRANS ? t % (k_end / 8) : t / COLS) * 8;
                         const int left = o < cols ? d_in - kc0 - k : 0;
                         const int64_t at_w = left > 0 ? w_index(kc0 + k, o) : 0;
+                        // The type of W is a template's: with one known at run time only each load was waited for at its branch's end
+                        // (dX of 400 000 x 128 from 128 columns, us: 303 / 155, of 100 000 x 301 182 / 92, of 200 000 x 128 from one 31 / 27).
+                        if constexpr (TRANS) {
+                            if (kc0 + k_end <= d_in) {  // uniform: eight elements of a row of W are there
+                                Eight<TW> e;
+                                load_eight<TW>(W, at_w, 8, e);
+#pragma unroll
+                                for (int j = 0; j < 8; ++j) w[u][j] = left > 0 ? eight_value(e, j) : 0.f;
+                                continue;
+                            }
+                        }
 #pragma unroll
                         for (int j = 0; j < 8; ++j) {
                             const int64_t i = at_w + (j < left ? static_cast<int64_t>(j) * (TRANS ? 1 : w_ld) : 0);
                             if constexpr (P == 3) {
-                                const float v = load_elem(W, i, TRANS ? wdt : OWN);
+                                const float v = load_elem(W, i, WDT);
                                 w[u][j] = j < left ? v : 0.f;
                             } else {
                                 const uint32_t v = static_cast<const uint16_t *>(W)[i];
@@ -226,7 +249,7 @@ __global__ __launch_bounds__(256, NT == 8 ? 2 : 4) void gemm_tile_kernel(int n, 
                 if (row >= n) break;
                 float v = 0.f;
 #pragma unroll 1
-                for (int k = 0; k < d_in; ++k) v = fmaf(static_cast<const float *>(X)[row * ldx + k], load_elem(W, w_index(k, o), TRANS ? wdt : OWN), v);
+                for (int k = 0; k < d_in; ++k) v = fmaf(static_cast<const float *>(X)[row * ldx + k], load_elem(W, w_index(k, o), WDT), v);
                 store_elem(Z, row * ldz + col0 + o, zdt, epi.apply(epi.factor(row), v));
             }
         }
@@ -237,17 +260,17 @@ __global__ __launch_bounds__(256, NT == 8 ? 2 : 4) void gemm_tile_kernel(int n, 
 // 128: 40 000 rows 24 / 25 us, 400 000 223 / 180; 17 -> 128 40 000 rows 11 / 14).
 constexpr int GEMM_TILE_WIDE_ROWS = 65536;
 
-template <class T, bool TRANS>
-static void gemm_tile_t(int n, const void *X, int ldx, int d_in, const void *W, int w_ld, int wdt, int d_out, void *Z, int ldz, int zdt,
-                        Epi epi, hipStream_t s)
+template <class T, bool TRANS, class TW = T>
+static void gemm_tile_t(int n, const void *X, int ldx, int d_in, const void *W, int w_ld, int d_out, void *Z, int ldz, int zdt, Epi epi,
+                        hipStream_t s)
 {
     const int nt = d_out <= 16 ? 1 : d_out <= 32 ? 2 : d_out <= 64 || T::BYTES == 4 || n < GEMM_TILE_WIDE_ROWS ? 4 : 8;
     const int n_blocks = static_cast<int>((static_cast<int64_t>(n) + 63) / 64);
     const int groups = (d_out + nt * 16 - 1) / (nt * 16);
     const int grid = d_in <= GemmChunk<T>::KC && n_blocks > 2048 ? 2048 : n_blocks;
-#define FTC_GT1(N, Q)                                                                                                                  \
-    hipLaunchKernelGGL((gemm_tile_kernel<T, N, TRANS, Q>), dim3(grid, groups), dim3(256), 0, s, n, X, ldx, d_in, W, w_ld, wdt, d_out, Z, \
-                       ldz, zdt, epi, n_blocks)
+#define FTC_GT1(N, Q)                                                                                                                      \
+    hipLaunchKernelGGL((gemm_tile_kernel<T, N, TRANS, Q, TW>), dim3(grid, groups), dim3(256), 0, s, n, X, ldx, d_in, W, w_ld, d_out, Z, ldz, \
+                       zdt, epi, n_blocks)
 #define FTC_GT(N) if (nt == N) FTC_GT1(N, true)
     if constexpr (T::BYTES == 4 && !TRANS) {
         if (nt == 1 && d_in > GemmChunk<T>::KC) {
@@ -266,9 +289,9 @@ static void gemm_tile_t(int n, const void *X, int ldx, int d_in, const void *W, 
 int32_t launch_gemm_tile(int n, const void *X, int ldx, int dt, int d_in, const void *W, int d_out, void *Z, int ldz, int zdt, Epi epi,
                          hipStream_t s)
 {
-    if (dt == FTC_F32) gemm_tile_t<F32, false>(n, X, ldx, d_in, W, d_out, dt, d_out, Z, ldz, zdt, epi, s);
-    else if (dt == FTC_F16) gemm_tile_t<F16, false>(n, X, ldx, d_in, W, d_out, dt, d_out, Z, ldz, zdt, epi, s);
-    else gemm_tile_t<BF16, false>(n, X, ldx, d_in, W, d_out, dt, d_out, Z, ldz, zdt, epi, s);
+    if (dt == FTC_F32) gemm_tile_t<F32, false>(n, X, ldx, d_in, W, d_out, d_out, Z, ldz, zdt, epi, s);
+    else if (dt == FTC_F16) gemm_tile_t<F16, false>(n, X, ldx, d_in, W, d_out, d_out, Z, ldz, zdt, epi, s);
+    else gemm_tile_t<BF16, false>(n, X, ldx, d_in, W, d_out, d_out, Z, ldz, zdt, epi, s);
     return launch_status("update_gemm tile");
 }
 
@@ -277,7 +300,10 @@ int32_t launch_input_grad(int n, const float *G, int ldg, int d_out, const void 
                           hipStream_t s)
 {
     if (n == 0) return FTC_OK;
-    gemm_tile_t<F32, true>(n, G, ldg, d_out, W, d_out, wdt, d_in, dX, lddx, dx_dt, Epi{0, nullptr}, s);
+    const Epi none{0, nullptr};
+    if (wdt == FTC_F32) gemm_tile_t<F32, true, F32>(n, G, ldg, d_out, W, d_out, d_in, dX, lddx, dx_dt, none, s);
+    else if (wdt == FTC_F16) gemm_tile_t<F32, true, F16>(n, G, ldg, d_out, W, d_out, d_in, dX, lddx, dx_dt, none, s);
+    else gemm_tile_t<F32, true, BF16>(n, G, ldg, d_out, W, d_out, d_in, dX, lddx, dx_dt, none, s);
     return launch_status("input_grad");
 }
 

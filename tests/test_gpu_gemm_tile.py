@@ -73,6 +73,13 @@ def test_input_gradient_at_edges_of_tiles_and_chunks(dtype, n, d_in, d_out):
 
 
 @pytest.mark.parametrize("dtype", [F32, F16, BF16])
+@pytest.mark.parametrize("n,d_in,d_out", [(4097, 65, 32), (9000, 66, 64), (4100, 64, 96), (10_001, 40, 131), (20_000, 130, 300), (70_001, 129, 1), (65, 1433, 40)])
+def test_input_gradient_of_whole_and_cut_chunks_of_w(dtype, n, d_in, d_out):
+    """Rows of W are read eight elements at a time where the chunk is whole, else one by one; X and W of each type."""
+    test_input_gradient_at_edges_of_tiles_and_chunks(dtype, n, d_in, d_out)
+
+
+@pytest.mark.parametrize("dtype", [F32, F16, BF16])
 @pytest.mark.parametrize("n,d_in,d_out", [(32768, 33, 33), (32769, 64, 64), (32800, 65, 129), (65536, 128, 128), (65537, 129, 200), (70_003, 300, 65),
                                           (33_000, 130, 47), (40_000, 1030, 65)])
 def test_weight_gradient_at_edges_of_tiles_and_steps(dtype, n, d_in, d_out):
