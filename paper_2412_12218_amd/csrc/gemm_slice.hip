@@ -1,5 +1,6 @@
 // Dense products Z = X W of few rows, on the 16-bit matrix cores (v_mfma_f32_16x16x32): 16-bit inputs as they are, fp32 inputs in
-// three exact bf16 pieces (bf16_split.hpp).  Rows at any alignment of their elements, any width.
+// three exact bf16 pieces (bf16_split.hpp); and dX = G W^T, the same with W transposed (TRANS).  Rows at any alignment of their
+// elements, any width.
 //
 // A workgroup of SW waves owns 16 rows of X and up to 16 NT columns; wave w takes the steps w, w + SW, .. of 32 contraction indices,
 // so that 2708 rows occupy 170 compute units, and adds its partial tile to the others' through LDS at the end, the only barrier.
@@ -40,10 +41,39 @@ __device__ __forceinline__ auto slice_load(const void *base, int64_t i)
     else return static_cast<uint32_t>(static_cast<const uint16_t *>(base)[i]);
 }
 
-template <class T, int NT, int SW>
-__global__ __launch_bounds__(64 * SW) void gemm_slice_kernel(int n, const void *__restrict__ X, int ldx, int d_in, const void *__restrict__ W,
-                                                             int d_out, void *__restrict__ Z, int ldz, int zdt, Epi epi)
+// one element, and eight in a row, of a W whose type is another than X's: widened
+template <class T, class TW>
+__device__ __forceinline__ auto slice_w(const void *W, int64_t i)
 {
+    if constexpr (std::is_same<T, TW>::value) return slice_load<T>(W, i);
+    else return std::is_same<TW, F16>::value ? f16_bits_to_f32(slice_load<TW>(W, i)) : bf16_bits_to_f32(slice_load<TW>(W, i));
+}
+template <class TW>
+__device__ __forceinline__ void slice_load8(const void *W, int64_t i, SliceRaw<F32> &r)
+{
+    if constexpr (TW::BYTES == 4) {
+        typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
+        const float *p = static_cast<const float *>(W) + i;
+        const f4 x = *reinterpret_cast<const f4 *>(p), y = *reinterpret_cast<const f4 *>(p + 4);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { r.e[j] = x[j]; r.e[4 + j] = y[j]; }
+    } else {
+        typedef uint32_t u4 __attribute__((ext_vector_type(4), aligned(2)));
+        const u4 x = *reinterpret_cast<const u4 *>(static_cast<const uint16_t *>(W) + i);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const uint32_t b = j & 1 ? x[j / 2] >> 16 : x[j / 2] & 0xffffu;
+            r.e[j] = std::is_same<TW, F16>::value ? f16_bits_to_f32(b) : bf16_bits_to_f32(b);
+        }
+    }
+}
+
+// TW: the type of W, another than X's only for TRANS, where it is widened.
+template <class T, int NT, int SW, bool TRANS, class TW>
+__global__ __launch_bounds__(64 * SW) void gemm_slice_kernel(int n, const void *__restrict__ X, int ldx, int d_in, const void *__restrict__ W,
+                                                             int w_ld, int d_out, void *__restrict__ Z, int ldz, int zdt, Epi epi)
+{
+    static_assert(TRANS ? T::BYTES == 4 : std::is_same<T, TW>::value, "types of the products");
     constexpr int COLS = 16 * NT, P = T::BYTES == 4 ? 3 : 1, U = T::BYTES == 4 ? (NT == 4 ? 1 : 2) : (NT == 4 ? 2 : 4);
     __shared__ float part[SW * 16 * COLS];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -55,6 +85,7 @@ __global__ __launch_bounds__(64 * SW) void gemm_slice_kernel(int n, const void *
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) hi[nt] = lo[P == 3 ? nt : 0] = split_f32x4{0.f, 0.f, 0.f, 0.f};
     bool odd = false;
+    auto w_index = [&](int k, int o) { return TRANS ? static_cast<int64_t>(o) * w_ld + k : static_cast<int64_t>(k) * w_ld + o; };
     auto product = [&](const uint4 (&a)[P], const SliceRaw<T> (&w)[NT]) {
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
@@ -95,8 +126,10 @@ __global__ __launch_bounds__(64 * SW) void gemm_slice_kernel(int n, const void *
             }
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt)
+                if constexpr (TRANS) slice_load8<TW>(W, w_index(k, wc[nt]), w[u][nt]);
+                else
 #pragma unroll
-                for (int j = 0; j < 8; ++j) w[u][nt].e[j] = slice_load<T>(W, static_cast<int64_t>(k + j) * d_out + wc[nt]);
+                    for (int j = 0; j < 8; ++j) w[u][nt].e[j] = slice_load<T>(W, w_index(k + j, wc[nt]));
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -122,7 +155,7 @@ __global__ __launch_bounds__(64 * SW) void gemm_slice_kernel(int n, const void *
             x.e[j] = in ? v : 0;
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
-                const auto y = slice_load<T>(W, static_cast<int64_t>(kk) * d_out + wc[nt]);
+                const auto y = slice_w<T, TW>(W, w_index(kk, wc[nt]));
                 w[nt].e[j] = in && col_ok[nt] ? y : 0;
             }
         }
@@ -150,7 +183,7 @@ __global__ __launch_bounds__(64 * SW) void gemm_slice_kernel(int n, const void *
             v = 0.f;
 #pragma unroll 1
             for (int k = 0; k < d_in; ++k)
-                v = fmaf(load_elem(X, row * ldx + k, FTC_F32), load_elem(W, static_cast<int64_t>(k) * d_out + col0 + o, FTC_F32), v);
+                v = fmaf(load_elem(X, row * ldx + k, FTC_F32), slice_w<F32, typename std::conditional<TRANS, TW, F32>::type>(W, w_index(k, col0 + o)), v);
         } else {
             v = 0.f;
 #pragma unroll
@@ -163,16 +196,17 @@ __global__ __launch_bounds__(64 * SW) void gemm_slice_kernel(int n, const void *
     }
 }
 
-template <class T>
-static void gemm_slice_t(int n, const void *X, int ldx, int d_in, const void *W, int d_out, void *Z, int ldz, int zdt, Epi epi, hipStream_t s)
+template <class T, bool TRANS, class TW = T>
+static void gemm_slice_t(int n, const void *X, int ldx, int d_in, const void *W, int w_ld, int d_out, void *Z, int ldz, int zdt, Epi epi,
+                         hipStream_t s)
 {
     const int64_t tiles = (static_cast<int64_t>(n) + 15) / 16;
     const bool wide = d_in >= 512;  // sixteen waves
     int nt = d_out <= 16 ? 1 : d_out <= 32 ? 2 : 4;
     while (nt > 1 && tiles * ((d_out + nt * 8 - 1) / (nt * 8)) <= (wide ? 256 : 1024)) nt /= 2;
     const dim3 grid(static_cast<unsigned>(tiles), static_cast<unsigned>((d_out + nt * 16 - 1) / (nt * 16)));
-#define FTC_GS(N, SW) \
-    hipLaunchKernelGGL((gemm_slice_kernel<T, N, SW>), grid, dim3(64 * SW), 0, s, n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi)
+#define FTC_GS(N, SW)                                                                                                                    \
+    hipLaunchKernelGGL((gemm_slice_kernel<T, N, SW, TRANS, TW>), grid, dim3(64 * SW), 0, s, n, X, ldx, d_in, W, w_ld, d_out, Z, ldz, zdt, epi)
     if (wide) {
         if (nt == 1) FTC_GS(1, 16);
         else if (nt == 2) FTC_GS(2, 16);
@@ -188,10 +222,21 @@ static void gemm_slice_t(int n, const void *X, int ldx, int d_in, const void *W,
 int32_t launch_gemm_slice(int n, const void *X, int ldx, int dt, int d_in, const void *W, int d_out, void *Z, int ldz, int zdt, Epi epi,
                           hipStream_t s)
 {
-    if (dt == FTC_F32) gemm_slice_t<F32>(n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi, s);
-    else if (dt == FTC_F16) gemm_slice_t<F16>(n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi, s);
-    else gemm_slice_t<BF16>(n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi, s);
+    if (dt == FTC_F32) gemm_slice_t<F32, false>(n, X, ldx, d_in, W, d_out, d_out, Z, ldz, zdt, epi, s);
+    else if (dt == FTC_F16) gemm_slice_t<F16, false>(n, X, ldx, d_in, W, d_out, d_out, Z, ldz, zdt, epi, s);
+    else gemm_slice_t<BF16, false>(n, X, ldx, d_in, W, d_out, d_out, Z, ldz, zdt, epi, s);
     return launch_status("update_gemm slice");
+}
+
+// dX = G W^T for G in fp32: W (d_in x d_out) is read transposed, the contraction runs over d_out.
+int32_t launch_input_grad_slice(int n, const float *G, int ldg, int d_out, const void *W, int wdt, int d_in, void *dX, int lddx, int dx_dt,
+                                hipStream_t s)
+{
+    const Epi none{0, nullptr};
+    if (wdt == FTC_F32) gemm_slice_t<F32, true, F32>(n, G, ldg, d_out, W, d_out, d_in, dX, lddx, dx_dt, none, s);
+    else if (wdt == FTC_F16) gemm_slice_t<F32, true, F16>(n, G, ldg, d_out, W, d_out, d_in, dX, lddx, dx_dt, none, s);
+    else gemm_slice_t<F32, true, BF16>(n, G, ldg, d_out, W, d_out, d_in, dX, lddx, dx_dt, none, s);
+    return launch_status("input_grad slice");
 }
 
 }  // namespace ftc

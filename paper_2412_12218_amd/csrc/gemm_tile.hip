@@ -133,7 +133,7 @@ __global__ __launch_bounds__(256, NT == 8 ? 2 : 4) void gemm_tile_kernel(int n, 
                         const int left = o < cols ? d_in - kc0 - k : 0;
                         const int64_t at_w = left > 0 ? w_index(kc0 + k, o) : 0;
                         // The type of W is a template's: with one known at run time only each load was waited for at its branch's end
-                        // (dX of 400 000 x 128 from 128 columns, us: 303 / 155, of 100 000 x 301 182 / 92, of 200 000 x 128 from one 31 / 27).
+                        // (dX of 400 000 x 128 from 128 columns, us: 303 / 155, of 100 000 x 301 182 / 92, of 200 000 x 128 from one 31 / 28).
                         if constexpr (TRANS) {
                             if (kc0 + k_end <= d_in) {  // uniform: eight elements of a row of W are there
                                 Eight<TW> e;
@@ -295,11 +295,14 @@ int32_t launch_gemm_tile(int n, const void *X, int ldx, int dt, int d_in, const 
     return launch_status("update_gemm tile");
 }
 
-// dX = G W^T for G in fp32: W (d_in x d_out) is read transposed, the contraction runs over d_out.
+// dX = G W^T for G in fp32: W (d_in x d_out) is read transposed, the contraction runs over d_out.  Few results of a contraction of more than
+// one chunk go through gemm_slice.hip, which has it split over the waves of a workgroup (us, here / there: 500 x 300 from 300 columns XX):
 int32_t launch_input_grad(int n, const float *G, int ldg, int d_out, const void *W, int wdt, int d_in, void *dX, int lddx, int dx_dt,
                           hipStream_t s)
 {
     if (n == 0) return FTC_OK;
+    if (d_out > GemmChunk<F32>::KC && static_cast<int64_t>(n) * d_in <= 1 << 18)
+        return launch_input_grad_slice(n, G, ldg, d_out, W, wdt, d_in, dX, lddx, dx_dt, s);
     const Epi none{0, nullptr};
     if (wdt == FTC_F32) gemm_tile_t<F32, true, F32>(n, G, ldg, d_out, W, d_out, d_in, dX, lddx, dx_dt, none, s);
     else if (wdt == FTC_F16) gemm_tile_t<F32, true, F16>(n, G, ldg, d_out, W, d_out, d_in, dX, lddx, dx_dt, none, s);

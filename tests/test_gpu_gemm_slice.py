@@ -63,3 +63,18 @@ def test_infinities_and_nan(dtype, d_in):
         ok = torch.isfinite(ref)
         terms = (X.double().abs() @ W1.double().abs())[ok]
         assert float(((got.double()[ok] - ref[ok]).abs() / terms).max()) <= 1e-5  # (fp32: a sum of d_in terms, one after the other)
+
+
+@pytest.mark.parametrize("dtype", [F32, F16, BF16])
+@pytest.mark.parametrize("n,d_in,d_out", [(1, 1, 65), (17, 33, 65), (500, 300, 300), (2731, 96, 96), (4096, 64, 66), (4097, 64, 66), (2708, 7, 504), (13_107, 20, 129)])
+def test_input_gradient_of_few_results(dtype, n, d_in, d_out):
+    """dX = G W^T of a contraction of more than 64 columns: the rows of W are read eight elements at a time, or one by one in the last step."""
+    gen = torch.Generator(device="cuda").manual_seed(n + d_in)
+    X = torch.randn((n, d_in), generator=gen, device="cuda").to(dtype)
+    W = torch.randn((d_in, d_out), generator=gen, device="cuda").to(dtype)
+    G = torch.randn((n, d_out + 1), generator=gen, device="cuda")[:, 1:]
+    dX = torch.full((n, d_in + 2), 7.0, device="cuda")
+    B.ftc_update_gemm_backward(X, W, G, dX=dX[:, 1:d_in + 1])
+    ref, terms = G.double() @ W.double().T.contiguous(), G.double().abs() @ W.double().abs().T.contiguous()
+    assert float(((dX[:, 1:d_in + 1].double() - ref).abs() / terms.clamp(min=1e-300)).max()) <= (d_out / 16 + 8) * 2.0 ** -24
+    assert torch.all(dX[:, 0] == 7.0) and torch.all(dX[:, d_in + 1] == 7.0)
