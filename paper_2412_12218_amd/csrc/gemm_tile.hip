@@ -84,7 +84,8 @@ __device__ __forceinline__ float eight_value(const Eight<T> &e, int j)
 template <class T, int NT, bool TRANS, bool QUADS, class TW>
 __global__ __launch_bounds__(256, NT == 8 ? 2 : 4) void gemm_tile_kernel(int n, const void *__restrict__ X, int ldx, int d_in,
                                                                          const void *__restrict__ W, int w_ld, int d_out,
-                                                                         void *__restrict__ Z, int ldz, int zdt, Epi epi, int n_blocks)
+                                                                         void *__restrict__ Z, int ldz, int zdt, Epi epi, int n_blocks,
+                                                                         int neighbours)
 {
     static_assert(TRANS ? T::BYTES == 4 : std::is_same<T, TW>::value, "types of the products");
     constexpr int P = GemmChunk<T>::PIECES, KC = GemmChunk<T>::KC, KP = KC + 8, COLS = 16 * NT, STEPS = KC / 32, SB = 2;
@@ -92,14 +93,20 @@ __global__ __launch_bounds__(256, NT == 8 ? 2 : 4) void gemm_tile_kernel(int n, 
     __shared__ int w_odd;  // some of W can't be taken in pieces
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int m = lane & 15, kb = lane >> 4;
-    const int col0 = blockIdx.y * COLS, cols = min(COLS, d_out - col0);
+    int first = blockIdx.x, group = blockIdx.y;
+    if (TRANS && neighbours) {  // the groups of a block of rows one after the other on one of the eight dies (gridDim.x is a multiple of 8)
+        const unsigned id = blockIdx.y * gridDim.x + blockIdx.x, slot = id / 8u;
+        group = static_cast<int>(slot % gridDim.y);
+        first = static_cast<int>(slot / gridDim.y * 8u + id % 8u);
+    }
+    const int col0 = group * COLS, cols = min(COLS, d_out - col0);
     const bool whole = d_in <= KC;
     constexpr int WDT = TW::BYTES == 4 ? FTC_F32 : std::is_same<TW, F16>::value ? FTC_F16 : FTC_BF16;
     auto w_index = [&](int k, int o) {
         return TRANS ? static_cast<int64_t>(col0 + o) * w_ld + k : static_cast<int64_t>(k) * w_ld + col0 + o;
     };
     if (P == 3 && tid == 0) w_odd = 0;
-    for (int block = blockIdx.x; block < n_blocks; block += gridDim.x) {  // uniform
+    for (int block = first; block < n_blocks; block += gridDim.x) {  // uniform
         const int64_t row0 = (static_cast<int64_t>(block) * 4 + wave) * 16;
         const int64_t at = min(row0 + m, static_cast<int64_t>(n) - 1) * ldx;  // clamped: stores are predicated
         // several sums per element: of the large and of the small products (fp32); of the first and second half of a chunk (16 bits)
@@ -118,7 +125,7 @@ __global__ __launch_bounds__(256, NT == 8 ? 2 : 4) void gemm_tile_kernel(int n, 
         };
         for (int kc0 = 0; kc0 < d_in; kc0 += KC) {  // uniform
             load_x(kc0, x);
-            if (!whole || block == static_cast<int>(blockIdx.x)) {
+            if (!whole || block == first) {
                 __syncthreads();  // the previous chunk has been consumed
                 const int k_end = min(KC, (d_in - kc0 + 31) / 32 * 32);
                 const int units = k_end / 8 * COLS;
@@ -267,10 +274,18 @@ static void gemm_tile_t(int n, const void *X, int ldx, int d_in, const void *W, 
     const int nt = d_out <= 16 ? 1 : d_out <= 32 ? 2 : d_out <= 64 || T::BYTES == 4 || n < GEMM_TILE_WIDE_ROWS ? 4 : 8;
     const int n_blocks = static_cast<int>((static_cast<int64_t>(n) + 63) / 64);
     const int groups = (d_out + nt * 16 - 1) / (nt * 16);
-    const int grid = d_in <= GemmChunk<T>::KC && n_blocks > 2048 ? 2048 : n_blocks;
+    // dX of several groups and fewer rows: as many workgroups as the chip holds at once (but 40 a group), which stage W once, and the groups of
+    // the same rows together, whose lines of dX are shared (us, 2048 workgroups a group / this; input_grad_kernel before: 100 000 x 128 from 1
+    // column 19.8 / 14.4; 17.1, from 10 23.4 / 16.5; 21.9, 200 000 x 128 from 7 30.6 / 23.3; 27.2, 100 000 x 301 from 7 42.6 / 35.6; 36.0, 40 000 x
+    // 1433 from 7 122.8 / 83.1; 101.2; 262 144 x 128 from 7 40.9 / 36.3; 37.4; but 400 000 x 128
+    // from 64 75.8 / 86.5, from 40 71.3 / 79.9).
+    const bool neighbours = TRANS && groups > 1 && n < 327680;
+    const int most = !neighbours ? 2048 : groups <= 25 ? 1024 / groups : 40;
+    int grid = d_in <= GemmChunk<T>::KC && n_blocks > most ? most : n_blocks;
+    if (neighbours) grid = (grid + 7) / 8 * 8;
 #define FTC_GT1(N, Q)                                                                                                                      \
     hipLaunchKernelGGL((gemm_tile_kernel<T, N, TRANS, Q, TW>), dim3(grid, groups), dim3(256), 0, s, n, X, ldx, d_in, W, w_ld, d_out, Z, ldz, \
-                       zdt, epi, n_blocks)
+                       zdt, epi, n_blocks, neighbours ? 1 : 0)
 #define FTC_GT(N) if (nt == N) FTC_GT1(N, true)
     if constexpr (T::BYTES == 4 && !TRANS) {
         if (nt == 1 && d_in > GemmChunk<T>::KC) {
@@ -296,7 +311,9 @@ int32_t launch_gemm_tile(int n, const void *X, int ldx, int dt, int d_in, const 
 }
 
 // dX = G W^T for G in fp32: W (d_in x d_out) is read transposed, the contraction runs over d_out.  Few results of a contraction of more than
-// one chunk go through gemm_slice.hip, which has it split over the waves of a workgroup (us, here / there: 500 x 300 from 300 columns XX):
+// one chunk go through gemm_slice.hip, where the waves of a workgroup share it (us, here / there: 500 x 64 from 300 columns 13.5 / 3.6, 2708 x 64 from
+// 504 23.2 / 16.5, 6000 x 33 from 300 14.5 / 8.5, 16 000 x 16 from 300 10.5 / 7.7; but 2708 x 301 from 128 8.2 / 11.6, 16 000 x 33 from 300
+// 16.4 / 17.8; W transposed into a buffer and gemm_any_kernel: 12.9, 18.3, 16.3, 11.2, 15.4, 23.1).
 int32_t launch_input_grad(int n, const float *G, int ldg, int d_out, const void *W, int wdt, int d_in, void *dX, int lddx, int dx_dt,
                           hipStream_t s)
 {
