@@ -143,7 +143,7 @@ int32_t launch_mask_scale(int n, int d, const float *dY, int lddy, const void *Y
 }
 
 // ---- dW = X^T G -----------------------------------------------------------------------------------
-// (more than 32 columns on either side and 32 768 rows: weight_grad_tile.hip)
+// (many rows and columns: weight_grad_tile.hip)
 // A contraction over the rows, on the matrix cores in fp32 (v_mfma_f32_16x16x4_f32; 16-bit elements of X are widened), so
 // products and sums are those of fp32 arithmetic.  A wave takes four rows per step:
 //   A operand  lane l holds VA consecutive columns of row l/16 from column a0 + VA (l%16) on (one load; 64 columns a step for
@@ -419,13 +419,16 @@ static WgTile weight_grad_tile(int d_in, int d_out)
 // less, next to more than 64 columns of X in fp32 (24 such products of 200 000 to 10^6 rows: 0.82 of the time on average, at
 // most 1.03; fp32 10^6 x 200 -> 136 1433 / 1192 us, 200 000 x 200 -> 129 327 / 199).  With a tenth instead of a sixth 100 -> 129 and
 // 65 -> 264 lose 10 to 17 % at 500 000 rows; 16-bit X, where the first launch is bound by its reads sooner, up to 16 %.
-static int weight_grad_first_columns(int n, int xdt, int d_in, int d_out)
+// *cost: of the launches, 10^-4 ps a row.
+static int weight_grad_first_columns(int n, int xdt, int d_in, int d_out, int64_t *cost)
 {
     const int first = d_out / 128 * 128, rest = d_out - first;
+    const int64_t whole = *cost = weight_grad_tile(d_in, d_out).cost;
     if (xdt != FTC_F32 || first == 0 || rest == 0 || rest > 8 || d_in <= 64) return d_out;
-    const int64_t whole = weight_grad_tile(d_in, d_out).cost;  // 10^-4 ps a row
-    const int64_t saved = whole - weight_grad_tile(d_in, first).cost - weight_grad_tile(d_in, rest).cost;
-    return saved * 6 >= whole && saved >= 200000000000 / (n < 1 ? 1 : n) ? first : d_out;
+    const int64_t split = weight_grad_tile(d_in, first).cost + weight_grad_tile(d_in, rest).cost, saved = whole - split;
+    if (saved * 6 < whole || saved < 200000000000 / (n < 1 ? 1 : n)) return d_out;
+    *cost = split;
+    return first;
 }
 
 // dW = X^T (G masked by Y; Y == NULL: no mask).  The shares of the rows: enough workgroups for the chip, at least 64 rows
@@ -444,8 +447,10 @@ int32_t launch_weight_grad(int n, const void *X, int ldx, int xdt, int d_in, con
                            const void *Y, int ldy, int ydt, float *dW, void *ws, hipStream_t s)
 {
     const int64_t room = static_cast<int64_t>(weight_grad_blocks(n)) * weight_grad_group(d_in, d_out);  // columns x shares
-    const WgPieces pieces = weight_grad_pieces(n, d_in, d_out);
-    const int first = pieces.na ? d_out : weight_grad_first_columns(n, xdt, d_in, d_out);
+    int64_t cost;
+    int first = weight_grad_first_columns(n, xdt, d_in, d_out, &cost);
+    const WgPieces pieces = weight_grad_pieces(n, d_in, d_out, cost);
+    if (pieces.na) first = d_out;
     const int64_t least = n / (384 + n / 384);
     int64_t want = 0;
     for (int b = 0; b < d_out; b = b == 0 ? first : d_out) {

@@ -140,7 +140,7 @@ int32_t launch_mask_scale(int n, int d, const float *dY, int lddy, const void *Y
                           const float *scale, float *out, int ldo, hipStream_t s);
 // weight_grad_tile.hip: 16 na columns of X and 16 nb columns of G per workgroup; na = 0: left to weight_grad_kernel
 struct WgPieces { int na, nb; };
-WgPieces weight_grad_pieces(int n, int d_in, int d_out);
+WgPieces weight_grad_pieces(int n, int d_in, int d_out, int64_t other);
 void launch_weight_grad_tile(WgPieces t, int n, const void *X, int ldx, int xdt, int d_in, const float *G, int ldg, int d_out, const void *Y,
                              int ldy, int mask, unsigned limit, float *partial, int splits, hipStream_t s);
 int weight_grad_group(int d_in, int d_out);

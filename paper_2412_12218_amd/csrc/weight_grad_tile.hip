@@ -243,16 +243,28 @@ __global__ __launch_bounds__(256, NA * NB >= 64 ? 2 : NA * NB >= 32 ? 3 : 4) voi
         }
 }
 
-// Up to 32 columns of G weight_grad_kernel is bound by reading X once (1 000 000 x 128, 32 fp32 134 us there, 131 here; x 16 43 / 58), as with
-// few columns of X (200 000 x 16, 128 34 / 46); few rows leave a workgroup too few steps (15 000 x 128, 128 17.7 / 18.2, 40 000 36.8 / 23.4;
-// 5000 x 300, 128 20 / 25).  128 columns of G a workgroup from 65 536 rows on (40 000 x 128, 128 23.4 with 64, 27 with 128; 100 000 47 / 40).
-WgPieces weight_grad_pieces(int n, int d_in, int d_out)
+// The tile, or none: weight_grad_kernel, by the time of a row next to `other`, that kernel's (10^-4 ps, as in its table): padded columns of X
+// times those of G times 255, 250 or 170 for 4 x 4, 8 x 4 and 8 x 8 tiles, and 2 or (8 x 8) 4 us for the first step and the sum over
+// the shares.  Up to 32 columns on either side and below 32 768 rows it is always the other one (1 000 000 x 128, 32 fp32 134 us there, 131 here;
+// 15 000 x 128, 128 17.7 / 18.2).  Of 1926 products (fp32 and fp16, 33 to 500 by 33 to 256 columns, 16 384 to 10^6 rows), each with and
+// without the mask, this rule takes 0.84 of weight_grad_kernel's time on average (the best of all four choices 0.81) and in 47 of 3852
+// more than 1.03 times, at most 1.17; 8 tiles of X wherever G has more than 64 columns, and no table, 0.87, 623 and 1.52 (500 000 x 33, 200 fp32 with
+// the mask 291 / 463 us, 4 x 4 tiles 327; 200 000 x 40, 72 44 / 59, now weight_grad_kernel).
+WgPieces weight_grad_pieces(int n, int d_in, int d_out, int64_t other)
 {
     if (n < 32768 || d_in <= 32 || d_out <= 32) return {0, 0};
     auto padded = [](int d, int t) { return (static_cast<int64_t>(d) + t - 1) / t * t; };
-    const int nb = n >= 65536 && d_out > 64 && padded(d_out, 128) == padded(d_out, 64) ? 8 : 4;
-    const int na = nb == 8 || padded(d_in, 128) == padded(d_in, 64) ? 8 : 4;  // (300 x 64: 4 x 4 tiles 54 us, 8 x 4 64)
-    return {na, nb};
+    struct { WgPieces tile; int64_t cost, us; } const tiles[] = {{{4, 4}, 255, 2}, {{8, 4}, 250, 2}, {{8, 8}, 170, 4}};
+    WgPieces best = {0, 0};
+    int64_t least = other + other / 20;
+    for (const auto &t : tiles) {
+        const int64_t cost = padded(d_in, 16 * t.tile.na) * padded(d_out, 16 * t.tile.nb) * t.cost + t.us * 10000000000 / n;
+        if (cost < least) {
+            least = cost;
+            best = t.tile;
+        }
+    }
+    return best;
 }
 
 template <class T>

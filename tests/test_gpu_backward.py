@@ -736,8 +736,8 @@ def test_weight_grad_edges(dtype, n, d_in, d_out):
 
 @pytest.mark.parametrize("n,d_in,d_out", [(100_000, 200, 136), (200_001, 65, 129), (150_007, 257, 257)])
 def test_weight_grad_with_a_few_columns_beyond_the_tiles_of_128(n, d_in, d_out):
-    """fp32 products whose last columns of G (8 and 1 beyond 128, 1 beyond 256) take a launch of their own: both write their part
-    of every share's result; rows at element alignment, with and without the mask.  Against 64 bits in torch."""
+    """fp32 products whose last columns of G (8 and 1 beyond 128) take a launch of their own: both write their part of every share's
+    result; the third has 1 beyond 256 in tiles of 128 columns, the last of them nearly empty; rows at element alignment, with and without the mask.  Against 64 bits in torch."""
     gen = torch.Generator(device="cuda")
     gen.manual_seed(n)
     X = torch.randn((n, d_in + 1), generator=gen, device="cuda")[:, 1:]

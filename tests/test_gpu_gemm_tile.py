@@ -99,11 +99,20 @@ def test_weight_gradient_at_edges_of_tiles_and_steps(dtype, n, d_in, d_out):
 
 
 @pytest.mark.parametrize("dtype", [F32, F16, BF16])
-def test_weight_gradient_of_numbers_that_bf16_pieces_cannot_hold(dtype):
+@pytest.mark.parametrize("n,d_in,d_out", [(100_001, 64, 64), (200_001, 33, 50), (100_003, 300, 33), (66_000, 128, 60), (100_003, 97, 40), (33_001, 500, 48),
+                                          (45_000, 128, 128), (65_600, 65, 65), (33_000, 200, 200), (100_000, 200, 136)])
+def test_weight_gradient_by_tiles_of_each_size(dtype, n, d_in, d_out):
+    """Three each that go to 4 x 4, 8 x 4 and 8 x 8 tiles of 16 columns; the last, in fp32, to two launches of the other kernel."""
+    test_weight_gradient_at_edges_of_tiles_and_steps(dtype, n, d_in, d_out)
+
+
+@pytest.mark.parametrize("dtype", [F32, F16, BF16])
+@pytest.mark.parametrize("n,d_in,d_out", [(32_800, 40, 70), (100_001, 40, 64), (66_000, 128, 60), (45_000, 100, 128)])
+def test_weight_gradient_of_numbers_that_bf16_pieces_cannot_hold(dtype, n, d_in, d_out):
+    """By the fp32 kernel, and by 4 x 4, 8 x 4 and 8 x 8 tiles."""
     gen = torch.Generator().manual_seed(2)
-    n, d_in, d_out = 32_800, 40, 70
     X, G = torch.randn((n, d_in), generator=gen).to(dtype), torch.randn((n, d_out), generator=gen)
-    X[100, 3], X[5000, 39], G[7, 1], G[32_799, 69], G[40, 5] = float("inf"), float("nan"), float("-inf"), float("nan"), 3.4e38
+    X[100, 3], X[5000, 39], G[7, 1], G[n - 1, d_out - 1], G[40, 5] = float("inf"), float("nan"), float("-inf"), float("nan"), 3.4e38
     X[40] = 0.5
     G[300:310] *= 1e-38
     X[7, 2] = 0.0  # infinity times zero
@@ -121,7 +130,7 @@ def test_weight_gradient_of_numbers_that_bf16_pieces_cannot_hold(dtype):
 def test_weight_gradient_of_an_infinity_in_the_first_step_of_every_share(dtype, column):
     """Row 31 of every 32 rows is loaded by the last wave, row 0 by the first: whichever wave finds the infinity, the step is not taken in pieces."""
     gen = torch.Generator().manual_seed(3)
-    n, d_in, d_out = 40_000, 48, 64
+    n, d_in, d_out = 100_000, 48, 64
     X, G = (torch.rand((n, d_in), generator=gen) + 0.5).to(dtype).cuda(), torch.randn((n, d_out), generator=gen).cuda()
     G[31 if column else 0::32, column] = float("inf")
     dW = B.ftc_update_gemm_backward(X, torch.zeros((d_in, d_out), dtype=dtype).cuda(), G, want_dX=False)[1]
