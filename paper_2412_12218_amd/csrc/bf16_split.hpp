@@ -3,8 +3,13 @@
 // three smallest (a2 b3, a3 b2, a3 b3: together below 2^-24 of a b, an fp32 rounding) are left out; the other six are exact in fp32
 // and take six instructions at sixteen times the rate of v_mfma_f32_16x16x4_f32.
 // Not so: infinities and NaN (inf - inf in the second piece), numbers that round to an infinite a1, and rests below the
-// smallest normal number.  All of these show in the last piece (NaN, or subnormal), so that is what is looked at, and the
-// step of the contraction they are in takes the fp32 instruction instead.
+// smallest normal number.  All of these show in the last piece (NaN, or subnormal), so that is what is looked at, and what they
+// are part of takes the fp32 instruction instead: the step of the contraction in weight_grad_tile.hip, a wave's share of it in gemm_slice.hip,
+// a wave's tile in gemm_tile.hip, the latter two computed again from memory.  The time of a product depends on its numbers that far (us,
+// none / one in W / one in every 16 rows, dW 32): update 100 000 x 300 -> 128 74 / 148 / 212, 100 000 x 1433 -> 16 138 / 305 / 308, 1 000 000 x 33 -> 2
+// 28 / 67 / 68, 2708 x 1433 -> 64 13 / 15 / 15; dX of 100 000 x 300 from 128 77 / 118 / 200; dW 100 000 x 300, 128 79 / - / 250 (weight_grad_kernel 118).
+// Tried: a flag and a branch for every step or chunk of gemm_tile.hip (86 and 96 for the 148 and 212 us, but 2 to 7 % more without any such
+// number: registers, and no splitting of one step during the products of the one before).
 #pragma once
 #include "ftc_common.hpp"
 

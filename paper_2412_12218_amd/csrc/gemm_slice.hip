@@ -7,6 +7,7 @@
 //   A operand  lane l holds X[row0 + l%16][k0 + (l/16) 8 .. +7], loaded at element alignment;
 //   B operand  lane l holds W[k0 + (l/16) 8 .. +7][n0 + l%16], eight loads of one element: a workgroup needs every element of W once, so
 //              that a copy in LDS would only add a wait.
+// A wave whose numbers can't all be taken in pieces does its steps again in fp32.
 // Bound by two memory latencies and the launch, not by bytes; from about 10 000 rows by the loads of W, which every 16 rows make anew.
 // Sixteen waves from 512 indices on, else four.  Fewer columns a workgroup (down to 16) as long as all fit the chip at once: a short
 // wave is worth more than reading X again.  us and error against 64 bits (2-norm), before (W staged in LDS chunk by chunk, products in
@@ -163,6 +164,27 @@ __global__ __launch_bounds__(64 * SW) void gemm_slice_kernel(int n, const void *
         odd |= slice_operand<T>(x, a);
         product(a, w);
     }
+    if constexpr (P == 3) {
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(odd) != 0, 0)) {  // this wave's steps in fp32, product j of a step takes the lanes' j-th index
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) hi[nt] = lo[nt] = split_f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+            for (int k0 = wave * 32; k0 < d_in; k0 += SW * 32) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    if (k0 + j >= d_in) break;  // uniform
+                    const int k = k0 + kb * 8 + j;
+                    const bool in = k < d_in;
+                    const float v = load_elem(X, at + (in ? k : 0), FTC_F32), x = in ? v : 0.f;
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) {
+                        const float y = slice_w<F32, typename std::conditional<TRANS, TW, F32>::type>(W, w_index(in ? k : 0, wc[nt]));
+                        hi[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, in && col_ok[nt] ? y : 0.f, hi[nt], 0, 0, 0);
+                    }
+                }
+            }
+        }
+    }
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
@@ -171,26 +193,16 @@ __global__ __launch_bounds__(64 * SW) void gemm_slice_kernel(int n, const void *
             if constexpr (P == 3) v += lo[nt][i];
             part[(wave * 16 + kb * 4 + i) * COLS + nt * 16 + m] = v;
         }
-    bool plain = false;  // some of the 16 rows or of W can't be taken in pieces: the tile in fp32
-    if constexpr (P == 3) plain = __syncthreads_or(odd);
-    else __syncthreads();
+    __syncthreads();
     for (int t = tid; t < 16 * COLS; t += 64 * SW) {
         const int64_t row = row0 + t / COLS;
         const int o = t % COLS;
         if (row >= n || o >= cols) continue;
-        float v;
-        if (__builtin_expect(plain, 0)) {
-            v = 0.f;
-#pragma unroll 1
-            for (int k = 0; k < d_in; ++k)
-                v = fmaf(load_elem(X, row * ldx + k, FTC_F32), slice_w<F32, typename std::conditional<TRANS, TW, F32>::type>(W, w_index(k, col0 + o)), v);
-        } else {
-            v = 0.f;
+        float v = 0.f;
 #pragma unroll
-            for (int w = 0; w < SW; w += 4) {  // four at a time: fewer roundings one after the other
-                const float *p = part + w * 16 * COLS + t;
-                v += (p[0] + p[16 * COLS]) + (p[32 * COLS] + p[48 * COLS]);
-            }
+        for (int w = 0; w < SW; w += 4) {  // four at a time: fewer roundings one after the other
+            const float *p = part + w * 16 * COLS + t;
+            v += (p[0] + p[16 * COLS]) + (p[32 * COLS] + p[48 * COLS]);
         }
         store_elem(Z, row * ldz + col0 + o, zdt, epi.apply(epi.factor(row), v));
     }

@@ -112,7 +112,6 @@ __global__ __launch_bounds__(256, NT == 8 ? 2 : 4) void gemm_tile_kernel(int n, 
         // several sums per element: of the large and of the small products (fp32); of the first and second half of a chunk (16 bits)
         constexpr int TOTAL = P == 3 ? 1 : NT == 8 ? 1 : 2;  // 16 bits: sum over the chunks, the others are the chunk's
         split_f32x4 acc[TOTAL + 1][NT];
-        bool odd = false;
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
             acc[0][nt] = acc[1][nt] = acc[TOTAL][nt] = split_f32x4{0.f, 0.f, 0.f, 0.f};
@@ -123,6 +122,7 @@ __global__ __launch_bounds__(256, NT == 8 ? 2 : 4) void gemm_tile_kernel(int n, 
             for (int s = 0; s < STEPS; ++s)
                 if (kc + s * 32 < d_in) load_eight<T>(X, at + kc + s * 32 + kb * 8, d_in - kc - s * 32 - kb * 8, to[s]);
         };
+        bool odd = false;
         for (int kc0 = 0; kc0 < d_in; kc0 += KC) {  // uniform
             load_x(kc0, x);
             if (!whole || block == first) {
@@ -218,19 +218,57 @@ __global__ __launch_bounds__(256, NT == 8 ? 2 : 4) void gemm_tile_kernel(int n, 
                 }
             }
         }
-        const bool plain = P == 3 && (__builtin_amdgcn_ballot_w64(odd) != 0 || w_odd);  // this wave's rows, in fp32
+        if constexpr (P == 3) {
+            // numbers that can't be taken in pieces: the tile again, in fp32, from X and W as they are.  Product j of a step takes the j-th of every
+            // lane's eight indices.  Bound by its loads of W, which every wave makes itself.
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(odd) != 0 || w_odd, 0)) {
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) acc[0][nt] = acc[1][nt] = split_f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+                for (int k0 = 0; k0 < d_in; k0 += 32) {
+                    int k = k0 + kb * 8;
+                    asm volatile("" : "+v"(k));  // (else addresses are kept over all of the kernel)
+                    Eight<T> xe;
+                    load_eight<T>(X, at + (k < d_in ? k : 0), d_in - k, xe);
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) {
+                        const int left = nt * 16 + m < cols ? d_in - k : 0;
+                        float b[8];
+                        if constexpr (TRANS) {
+                            Eight<TW> e;
+                            load_eight<TW>(W, left > 0 ? w_index(k, nt * 16 + m) : 0, left, e);
+#pragma unroll
+                            for (int j = 0; j < 8; ++j) b[j] = eight_value(e, j);
+                        } else {
+#pragma unroll
+                            for (int j = 0; j < 8; ++j) {
+                                const float v = load_elem(W, j < left ? w_index(k + j, nt * 16 + m) : 0, WDT);
+                                b[j] = j < left ? v : 0.f;
+                            }
+                        }
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) {
+                            split_f32x4 &c = acc[j & 1][nt];
+                            c = QUADS ? __builtin_amdgcn_mfma_f32_16x16x4f32(b[j], xe.f[j], c, 0, 0, 0)
+                                      : __builtin_amdgcn_mfma_f32_16x16x4f32(xe.f[j], b[j], c, 0, 0, 0);
+                        }
+                        asm volatile("" ::: "memory");  // (else all tiles' loads are moved up here, and their registers with them)
+                    }
+                }
+            }
+        }
         if constexpr (!QUADS) {
             static_assert(P == 3, "16-bit operands change places");
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int64_t row = row0 + kb * 4 + i;
-                if (row >= n || plain) continue;
+                if (row >= n) continue;
                 const float f = epi.factor(row);
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt)
                     if (nt * 16 + m < cols) store_elem(Z, row * ldz + col0 + nt * 16 + m, zdt, epi.apply(f, acc[0][nt][i] + acc[1][nt][i]));
             }
-        } else if (row0 + m < n && !plain) {
+        } else if (row0 + m < n) {
             const int64_t row = row0 + m;
             const float f = epi.factor(row);
 #pragma unroll
@@ -246,18 +284,6 @@ __global__ __launch_bounds__(256, NT == 8 ? 2 : 4) void gemm_tile_kernel(int n, 
                     for (int i = 0; i < 4; ++i)
                         if (o + i < cols) store_elem(Z, row * ldz + col0 + o + i, zdt, z[i]);
                 }
-            }
-        }
-        if (__builtin_expect(plain, 0)) {
-#pragma unroll 1
-            for (int t = lane; t < 16 * cols; t += 64) {
-                const int64_t row = row0 + t / cols;
-                const int o = t % cols;
-                if (row >= n) break;
-                float v = 0.f;
-#pragma unroll 1
-                for (int k = 0; k < d_in; ++k) v = fmaf(static_cast<const float *>(X)[row * ldx + k], load_elem(W, w_index(k, o), WDT), v);
-                store_elem(Z, row * ldz + col0 + o, zdt, epi.apply(epi.factor(row), v));
             }
         }
     }

@@ -135,3 +135,66 @@ def test_weight_gradient_of_an_infinity_in_the_first_step_of_every_share(dtype, 
     G[31 if column else 0::32, column] = float("inf")
     dW = B.ftc_update_gemm_backward(X, torch.zeros((d_in, d_out), dtype=dtype).cuda(), G, want_dX=False)[1]
     assert torch.isposinf(dW[:, column]).all() and int(torch.isfinite(dW).sum()) == d_in * (d_out - 1)
+
+
+def us(f):
+    """Least time of a call over five batches."""
+    for _ in range(3):
+        f()
+    best = float("inf")
+    for _ in range(5):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(10):
+            f()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) * 100)
+    return best
+
+
+@pytest.mark.parametrize("kind,n,d_in,d_out", [("update", 100_000, 300, 128), ("update", 100_000, 1433, 16), ("update", 2708, 1433, 64), ("update", 8000, 301, 64),
+                                               ("dX", 100_000, 300, 128), ("dX", 2708, 64, 504), ("dW", 100_000, 300, 128), ("dW", 66_000, 128, 60)])
+def test_small_numbers_cost_the_fp32_instruction_and_no_more(kind, n, d_in, d_out):
+    """A number that bf16 pieces can't hold in one place of W, or in one row of 16 (dW: 32): the tiles (dW: steps) it is in by the fp32
+    instruction from memory, about as long as that kernel alone took, and the pieces before.  (One term after the other: 20 to 100 times.)"""
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    X, G = torch.randn((n, d_in), generator=gen, device="cuda"), torch.randn((n, d_out), generator=gen, device="cuda")
+    W = torch.randn((d_in, d_out), generator=gen, device="cuda")
+    out, dX = torch.empty((n, d_out), device="cuda"), torch.empty((n, d_in), device="cuda")
+
+    def run():
+        if kind == "update":
+            B.ftc_update_gemm(X, W, out=out)
+        elif kind == "dX":
+            B.ftc_update_gemm_backward(X, W, G, dX=dX)
+        else:
+            B.ftc_update_gemm_backward(X, W, G, want_dX=False)
+    plain = us(run)
+    A = X if kind == "update" else G
+    times = []
+    if kind != "dW":
+        W[d_in // 2, d_out // 2] = 1.2345679e-36
+        times.append(us(run))
+        W[d_in // 2, d_out // 2] = 1.0
+    A[5::16 if kind != "dW" else 32, 3] = 1.2345679e-36
+    times.append(us(run))
+    print(kind, n, d_in, d_out, "us", plain, times)
+    assert max(times) <= 4 * plain
+
+
+@pytest.mark.parametrize("n,d_in,d_out", [(20_000, 64, 64), (20_000, 63, 33), (100_000, 200, 16), (20_000, 200, 70), (300, 70, 70), (2708, 504, 33)])
+def test_small_numbers_in_any_step(n, d_in, d_out):
+    """Columns of W, rows of X and rows of W (in dX: columns) that bf16 pieces can't hold, in each step: rounded no more than once per four terms."""
+    gen = torch.Generator(device="cuda").manual_seed(n + d_in)
+    for k in range(5, d_in, 32):
+        X, W = torch.randn((n, d_in), generator=gen, device="cuda"), torch.randn((d_in, d_out), generator=gen, device="cuda")
+        W[:, d_out // 2] *= 1e-33
+        W[k, 0] = 1e-34
+        X[n // 2 + k % 16] *= 1e-3
+        X[3::64, k] = 1e-33
+        Z = B.ftc_update_gemm(X, W)
+        assert rel(Z, X, W) <= (d_in / 4 + 8) * 2.0 ** -24
+        dX = torch.empty((n, d_out), device="cuda")  # X as the gradient of a product with W^T
+        B.ftc_update_gemm_backward(torch.empty((n, d_out), device="cuda"), W.T.contiguous(), X, dX=dX)
+        assert rel(dX, X, W) <= (d_in / 4 + 8) * 2.0 ** -24
