@@ -2,6 +2,9 @@
 // bf16 numbers, exactly: a1 = a rounded, a2 = (a - a1) rounded, a3 = the rest.  Of the nine products of two such sums the
 // three smallest (a2 b3, a3 b2, a3 b3: together below 2^-24 of a b, an fp32 rounding) are left out; the other six are exact in fp32
 // and take six instructions at sixteen times the rate of v_mfma_f32_16x16x4_f32.
+// A sum of one or two products would be further off like this than in fp32, where a product is rounded once and exact before (one: at
+// most 0.91e-7 for 0.60e-7 of itself; two: 1.23e-7 for 1.14e-7 of their absolute sum), so up to SPLIT_FROM products, which are one
+// v_mfma_f32_16x16x4_f32, are summed in fp32.
 // Not so: infinities and NaN (inf - inf in the second piece), numbers that round to an infinite a1, and rests below the
 // smallest normal number.  All of these show in the last piece (NaN, or subnormal), so that is what is looked at, and what they
 // are part of takes the fp32 instruction instead: the step of the contraction in weight_grad_tile.hip, a wave's share of it in gemm_slice.hip,
@@ -15,6 +18,8 @@
 
 namespace ftc {
 #if defined(__HIPCC__)
+
+constexpr int SPLIT_FROM = 4;
 
 typedef float split_f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 split_bf16x2 __attribute__((ext_vector_type(2)));

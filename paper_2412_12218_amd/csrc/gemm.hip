@@ -2,7 +2,7 @@
 // for one: 16-bit inputs with d_in <= 256, d_out <= 64 and aligned rows (the benchmark models) keep all of W on chip; few rows are
 // split along the contraction (gemm_slice.hip); the rest (fp32, odd widths, rows that are not 16-byte aligned) goes through the
 // kernels of gemm_tile.hip, and through gemm_any_kernel for few fp32 columns.
-#include "ftc_common.hpp"
+#include "bf16_split.hpp"
 
 namespace ftc {
 
@@ -315,7 +315,8 @@ int32_t launch_gemm(int n, const void *X, int ldx, int dt, int d_in, const void 
     const bool fast = aligned16(X) && (static_cast<int64_t>(ldx) * elem_size(dt)) % 16 == 0 && d_in % v == 0;
     const bool on_chip = dt != FTC_F32 && fast && d_in <= 256 && d_out <= 64;
     const bool narrow = dt == FTC_F32 && fast && narrow_shape(d_in, d_out);
-    if (gemm_slice_better(n, dt, d_in, d_out, on_chip) && !(narrow && d_in < 16))
+    const bool few = dt == FTC_F32 && d_in <= SPLIT_FROM;  // fp32 products of a sum this short are not taken in pieces
+    if (gemm_slice_better(n, dt, d_in, d_out, on_chip) && !(narrow && d_in < 16) && !few)
         return launch_gemm_slice(n, X, ldx, dt, d_in, W, d_out, Z, ldz, zdt, epi, s);
     if (dt != FTC_F32 && fast) {  // 16-byte row pieces of X: all of W on chip
         const bool done = dt == FTC_F16 ? gemm_mfma_t<F16>(n, X, ldx, d_in, W, d_out, Z, ldz, zdt, epi, s)
@@ -330,7 +331,7 @@ int32_t launch_gemm(int n, const void *X, int ldx, int dt, int d_in, const void 
         return launch_status("update_gemm narrow");
     }
     // up to 16 fp32 columns both wait for X: 100 000 x 1433 -> 16 139 (gemm_tile.hip) / 138, 65 000 x 65 -> 7 7.2 / 6.4, 1 000 000 x 33 -> 2 40 / 57
-    if (dt != FTC_F32 || d_out > 16 || n >= 98304) return launch_gemm_tile(n, X, ldx, dt, d_in, W, d_out, Z, ldz, zdt, epi, s);
+    if (dt != FTC_F32 || d_out > 16 || n >= 98304 || few) return launch_gemm_tile(n, X, ldx, dt, d_in, W, d_out, Z, ldz, zdt, epi, s);
     hipLaunchKernelGGL(gemm_any_kernel, dim3(static_cast<unsigned>((n + 63) / 64)), dim3(256), 0, s, n, static_cast<const float *>(X), ldx, d_in,
                        static_cast<const float *>(W), d_out, Z, ldz, zdt, epi);
     return launch_status("update_gemm");

@@ -289,6 +289,58 @@ __global__ __launch_bounds__(256, NT == 8 ? 2 : 4) void gemm_tile_kernel(int n, 
     }
 }
 
+// fp32 products of at most SPLIT_FROM indices: one v_mfma_f32_16x16x4_f32 a tile, lane l holding index l/16; rows, columns, stores and `neighbours`
+// as above.  W stays in registers.  Bound by writing Z (us, in pieces / here: 200 000 x 1 -> 128 22.9 / 18.4, 1 000 000 x 4 -> 8
+// 20.2 / 9.9, dX of 200 000 x 128 from one column 21 / 19, of 100 000 x 64 from three 13.7 / 9.1).
+template <int NT, bool TRANS, class TW>
+__global__ __launch_bounds__(256) void gemm_few_kernel(int n, const float *__restrict__ X, int ldx, int d_in, const void *__restrict__ W, int w_ld,
+                                                       int d_out, void *__restrict__ Z, int ldz, int zdt, Epi epi, int n_blocks, int neighbours)
+{
+    constexpr int COLS = 16 * NT;
+    constexpr int WDT = TW::BYTES == 4 ? FTC_F32 : std::is_same<TW, F16>::value ? FTC_F16 : FTC_BF16;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int m = lane & 15, kb = lane >> 4;
+    int first = blockIdx.x, group = blockIdx.y;
+    if (TRANS && neighbours) {
+        const unsigned id = blockIdx.y * gridDim.x + blockIdx.x, slot = id / 8u;
+        group = static_cast<int>(slot % gridDim.y);
+        first = static_cast<int>(slot / gridDim.y * 8u + id % 8u);
+    }
+    const int col0 = group * COLS, cols = min(COLS, d_out - col0);
+    float w[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+        const int o = nt * 16 + m;
+        const bool in = kb < d_in && o < cols;
+        const int64_t i = TRANS ? static_cast<int64_t>(col0 + o) * w_ld + kb : static_cast<int64_t>(kb) * w_ld + col0 + o;
+        const float v = load_elem(W, in ? i : 0, WDT);
+        w[nt] = in ? v : 0.f;
+    }
+    for (int block = first; block < n_blocks; block += gridDim.x) {  // uniform
+        const int64_t row = (static_cast<int64_t>(block) * 4 + wave) * 16 + m;
+        const float v = X[min(row, static_cast<int64_t>(n) - 1) * ldx + min(kb, d_in - 1)], x = kb < d_in ? v : 0.f;
+        split_f32x4 c[NT];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) c[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[nt], x, split_f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+        if (row >= n) continue;
+        const float f = epi.factor(row);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const int o = nt * 16 + kb * 4;
+            float z[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) z[i] = epi.apply(f, c[nt][i]);
+            if (o + 4 <= cols) {
+                store_vec_any<4>(Z, row * ldz + col0 + o, zdt, z);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (o + i < cols) store_elem(Z, row * ldz + col0 + o + i, zdt, z[i]);
+            }
+        }
+    }
+}
+
 // 16-bit rows into more than 64 columns: from here on in groups of 128, which read X half as often (fp16 301 -> 128, groups of 64 /
 // 128: 40 000 rows 24 / 25 us, 400 000 223 / 180; 17 -> 128 40 000 rows 11 / 14).
 constexpr int GEMM_TILE_WIDE_ROWS = 65536;
@@ -313,6 +365,19 @@ static void gemm_tile_t(int n, const void *X, int ldx, int d_in, const void *W, 
     hipLaunchKernelGGL((gemm_tile_kernel<T, N, TRANS, Q, TW>), dim3(grid, groups), dim3(256), 0, s, n, X, ldx, d_in, W, w_ld, d_out, Z, ldz, \
                        zdt, epi, n_blocks, neighbours ? 1 : 0)
 #define FTC_GT(N) if (nt == N) FTC_GT1(N, true)
+    if constexpr (T::BYTES == 4) {
+        if (d_in <= SPLIT_FROM) {
+#define FTC_GF(N)                                                                                                                              \
+    if (nt == N)                                                                                                                               \
+        hipLaunchKernelGGL((gemm_few_kernel<N, TRANS, TW>), dim3(grid, groups), dim3(256), 0, s, n, static_cast<const float *>(X), ldx, d_in, W, \
+                           w_ld, d_out, Z, ldz, zdt, epi, n_blocks, neighbours ? 1 : 0)
+            FTC_GF(1);
+            FTC_GF(2);
+            FTC_GF(4);
+#undef FTC_GF
+            return;
+        }
+    }
     if constexpr (T::BYTES == 4 && !TRANS) {
         if (nt == 1 && d_in > GemmChunk<T>::KC) {
             FTC_GT1(1, false);

@@ -198,3 +198,36 @@ def test_small_numbers_in_any_step(n, d_in, d_out):
         dX = torch.empty((n, d_out), device="cuda")  # X as the gradient of a product with W^T
         B.ftc_update_gemm_backward(torch.empty((n, d_out), device="cuda"), W.T.contiguous(), X, dX=dX)
         assert rel(dX, X, W) <= (d_in / 4 + 8) * 2.0 ** -24
+
+
+@pytest.mark.parametrize("dtype", [F32, F16])
+@pytest.mark.parametrize("n,d_in,d_out", [(20_000, 1, 70), (20_000, 2, 33), (100_001, 1, 3), (100_000, 2, 200), (300, 1, 20), (5000, 2, 64), (33, 2, 7), (6000, 1, 130)])
+def test_sums_of_one_and_two_products_are_rounded_once_and_twice(dtype, n, d_in, d_out):
+    """Half a unit in the last place of the product, or of one of the products and of the sum: what fused multiply-adds leave."""
+    gen = torch.Generator(device="cuda").manual_seed(n + d_in)
+    X, W = torch.randn((n, d_in), generator=gen, device="cuda"), torch.randn((d_in, d_out), generator=gen, device="cuda")
+    Wt = W.T.to(dtype)  # the gradient's weights may be of another type
+    dX = torch.full((n, d_out + 1), 7.0, device="cuda")
+    B.ftc_update_gemm_backward(torch.zeros((n, d_out), device="cuda", dtype=dtype), Wt.contiguous(), X, dX=dX[:, :d_out])
+    assert torch.all(dX[:, d_out] == 7.0)
+    for Z, W1 in ((B.ftc_update_gemm(X, W), W), (dX[:, :d_out], Wt.float().T)):
+        terms = X.double()[:, :, None] * W1.double()[None]
+        ref = terms.sum(1)
+        allowed = ref.abs() + (terms.abs().amax(1) if d_in == 2 else 0.0)
+        assert float(((Z.double() - ref).abs() / allowed).max()) <= 2.0 ** -24 * (1 + 2.0 ** -20)
+
+
+@pytest.mark.parametrize("n,d_in,d_out", [(20_000, 3, 70), (20_000, 4, 16), (300, 3, 20), (5000, 4, 64), (20_000, 5, 16), (300, 5, 20)])
+def test_infinities_and_nan_in_sums_of_few_products(n, d_in, d_out):
+    gen = torch.Generator().manual_seed(d_in)
+    X, W = torch.randn((n, d_in), generator=gen), torch.randn((d_in, d_out), generator=gen)
+    X[3, 2], X[40, d_in - 1], X[70, 0], W[d_in - 1, 4], W[2, 5] = float("inf"), float("-inf"), float("nan"), 0.0, float("inf")
+    X[90:110] *= 1e-36
+    ref = X.double() @ W.double()
+    dX = torch.empty((n, d_out), device="cuda")
+    B.ftc_update_gemm_backward(torch.zeros((n, d_out), device="cuda"), W.T.contiguous().cuda(), X.cuda(), dX=dX)
+    for got in (B.ftc_update_gemm(X.cuda(), W.cuda()).cpu(), dX.cpu()):
+        assert torch.equal(torch.isnan(got), torch.isnan(ref)) and torch.equal(torch.isposinf(got), torch.isposinf(ref))
+        ok = torch.isfinite(ref)
+        terms = (X.double().abs() @ W.double().abs())[ok]
+        assert float(((got.double()[ok] - ref[ok]).abs() / terms).max()) <= d_in * 2.0 ** -24 * (1 + 2.0 ** -20)
