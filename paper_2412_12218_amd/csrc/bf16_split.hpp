@@ -6,8 +6,11 @@
 // most 0.91e-7 for 0.60e-7 of itself; two: 1.23e-7 for 1.14e-7 of their absolute sum), so up to SPLIT_FROM products, which are one
 // v_mfma_f32_16x16x4_f32, are summed in fp32.
 // Not so: infinities and NaN (inf - inf in the second piece), numbers that round to an infinite a1, and rests below the
-// smallest normal number.  All of these show in the last piece (NaN, or subnormal), so that is what is looked at, and what they
-// are part of takes the fp32 instruction instead: the step of the contraction in weight_grad_tile.hip, a wave's share of it in gemm_slice.hip,
+// smallest normal number.  All of these show in the last piece (NaN, or subnormal), so that is what is looked at.  And a1 b1 can be
+// infinite where a b is not: a1 is up to 2^-8 of a larger than it, so this takes results within a hundredth of the largest number; it
+// shows in the sum, which then is not finite whatever follows.  What these
+// are part of takes the fp32 instruction instead: the step of the contraction in weight_grad_tile.hip (an infinite sum: a
+// wave's rows), a wave's share of it in gemm_slice.hip,
 // a wave's tile in gemm_tile.hip, the latter two computed again from memory.  The time of a product depends on its numbers that far (us,
 // none / one in W / one in every 16 rows, dW 32): update 100 000 x 300 -> 128 74 / 148 / 212, 100 000 x 1433 -> 16 138 / 305 / 308, 1 000 000 x 33 -> 2
 // 28 / 67 / 68, 2708 x 1433 -> 64 13 / 15 / 15; dX of 100 000 x 300 from 128 77 / 118 / 200; dW 100 000 x 300, 128 79 / - / 250 (weight_grad_kernel 118).
@@ -52,6 +55,14 @@ __device__ __forceinline__ bool split8(const float (&a)[8], uint4 (&p)[3])
 #pragma unroll
     for (int q = 0; q < 3; ++q) p[q] = make_uint4(w[q][0], w[q][1], w[q][2], w[q][3]);
     return odd;
+}
+
+// NaN if one of v is not finite, else t
+__device__ __forceinline__ float not_finite(const split_f32x4 &v, float t)
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i) t = fmaf(v[i], 0.f, t);
+    return t;
 }
 
 // lo, hi += the six products of a step of 32: the large one apart from the small ones, whose roundings then don't count

@@ -165,7 +165,10 @@ __global__ __launch_bounds__(64 * SW) void gemm_slice_kernel(int n, const void *
         product(a, w);
     }
     if constexpr (P == 3) {
-        if (__builtin_expect(__builtin_amdgcn_ballot_w64(odd) != 0, 0)) {  // this wave's steps in fp32, product j of a step takes the lanes' j-th index
+        float zero = 0.f;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) zero = not_finite(hi[nt] + lo[nt], zero);
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(odd || zero != 0.f) != 0, 0)) {  // this wave's steps in fp32, product j of a step takes the lanes' j-th index
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) hi[nt] = lo[nt] = split_f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1

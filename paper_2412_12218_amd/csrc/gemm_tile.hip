@@ -82,7 +82,7 @@ __device__ __forceinline__ float eight_value(const Eight<T> &e, int j)
 
 // TW: the type of W, another than X's only for TRANS.
 template <class T, int NT, bool TRANS, bool QUADS, class TW>
-__global__ __launch_bounds__(256, NT == 8 ? 2 : 4) void gemm_tile_kernel(int n, const void *__restrict__ X, int ldx, int d_in,
+__global__ __launch_bounds__(256, NT == 8 ? 2 : NT == 2 && !TRANS ? 5 : 4) void gemm_tile_kernel(int n, const void *__restrict__ X, int ldx, int d_in,
                                                                          const void *__restrict__ W, int w_ld, int d_out,
                                                                          void *__restrict__ Z, int ldz, int zdt, Epi epi, int n_blocks,
                                                                          int neighbours)
@@ -219,9 +219,12 @@ __global__ __launch_bounds__(256, NT == 8 ? 2 : 4) void gemm_tile_kernel(int n, 
             }
         }
         if constexpr (P == 3) {
+            float zero = 0.f;
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) zero = not_finite(acc[0][nt] + acc[1][nt], zero);
             // numbers that can't be taken in pieces: the tile again, in fp32, from X and W as they are.  Product j of a step takes the j-th of every
             // lane's eight indices.  Bound by its loads of W, which every wave makes itself.
-            if (__builtin_expect(__builtin_amdgcn_ballot_w64(odd) != 0 || w_odd, 0)) {
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(odd || zero != 0.f) != 0 || w_odd, 0)) {
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt) acc[0][nt] = acc[1][nt] = split_f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1

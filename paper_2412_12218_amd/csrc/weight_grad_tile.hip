@@ -8,7 +8,7 @@
 // lane; columns 80 bytes apart: no bank conflicts).  A wave holds (NA / WA) x (NB / WB) tiles.  The small products of a step are summed
 // apart and added once, so a step rounds a sum twice.  Shares, their sums and the ReLU mask: as in weight_grad_kernel (backward.hip).
 // Columns and rows beyond the end are zeros in LDS.  A step with numbers that can't be taken in pieces (an infinity times a piece that
-// is zero would be NaN) goes through v_mfma_f32_16x16x4_f32 from X and G as they are.
+// is zero would be NaN) goes through v_mfma_f32_16x16x4_f32 from X and G as they are, and so do all steps of a wave whose sums are not finite.
 //
 // Bound by the work of taking apart (8 instructions a number, 30 us for 100 000 x 300, 128) next to the products (25 us), two or three
 // workgroups a CU; weight_grad_kernel by reading X and G five and two times.  us, there / here, with the sums over the shares, and
@@ -136,9 +136,39 @@ __global__ __launch_bounds__(256, NA * NB >= 64 ? 2 : NA * NB >= 32 ? 3 : 4) voi
         }
         return odd;
     };
+    // a step in fp32, from X and G as they are; no barrier
+    auto plain_step = [&](int64_t r0) {
+#pragma unroll 1
+        for (int k = 0; k < 8; ++k) {
+            const int64_t row = r0 + kb * 8 + k, rc = min(row, r_end - 1);
+            float a[PA], b[PB];
+#pragma unroll
+            for (int i = 0; i < PA; ++i) {
+                const int c = a0 + (wa + i) * 16 + m;
+                const float v = load_elem(X, rc * ldx + min(c, d_in - 1), T::BYTES == 4 ? FTC_F32 : std::is_same<T, F16>::value ? FTC_F16 : FTC_BF16);
+                a[i] = c < d_in && row < r_end ? v : 0.f;
+            }
+#pragma unroll
+            for (int j = 0; j < PB; ++j) {
+                const int c = b0 + (wb + j) * 16 + m, cc = min(c, d_out - 1);
+                float v = G[rc * ldg + cc];
+                if constexpr (MASK == 1) v = static_cast<const float *>(Y)[rc * ldy + cc] > 0.f ? v : 0.f;
+                if constexpr (MASK == 2) {
+                    const unsigned y = static_cast<const uint16_t *>(Y)[rc * ldy + cc];
+                    v = (y != 0u && y <= limit) ? v : 0.f;
+                }
+                b[j] = c < d_out && row < r_end ? v : 0.f;
+            }
+#pragma unroll
+            for (int i = 0; i < PA; ++i)
+#pragma unroll
+                for (int j = 0; j < PB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], acc[i][j], 0, 0, 0);
+        }
+    };
     if (r_begin < r_end) load_step(r_begin);
     __syncthreads();  // odd_s is cleared before any wave sets it in the first step
     int step = 0;
+    bool pieces = false;  // uniform: some steps were taken in pieces
     for (int64_t r0 = r_begin; r0 < r_end; r0 += WT_ROWS, ++step) {  // uniform
         bool odd = false;
 #pragma unroll
@@ -173,7 +203,8 @@ __global__ __launch_bounds__(256, NA * NB >= 64 ? 2 : NA * NB >= 32 ? 3 : 4) voi
         __syncthreads();
         if (r0 + WT_ROWS < r_end) load_step(r0 + WT_ROWS);
         if (tid == 0) odd_s[(step + 1) & 1] = 0;
-        if (!odd_s[step & 1]) {
+        if (!__builtin_amdgcn_readfirstlane(odd_s[step & 1])) {
+            pieces = true;
             uint4 b[PB][3];
 #pragma unroll
             for (int j = 0; j < PB; ++j)
@@ -198,35 +229,23 @@ __global__ __launch_bounds__(256, NA * NB >= 64 ? 2 : NA * NB >= 32 ? 3 : 4) voi
                     acc[i][j] += small;
                 }
             }
-        } else {  // in fp32, from X and G as they are
-#pragma unroll 1
-            for (int k = 0; k < 8; ++k) {
-                const int64_t row = r0 + kb * 8 + k, rc = min(row, r_end - 1);
-                float a[PA], b[PB];
-#pragma unroll
-                for (int i = 0; i < PA; ++i) {
-                    const int c = a0 + (wa + i) * 16 + m;
-                    const float v = load_elem(X, rc * ldx + min(c, d_in - 1), T::BYTES == 4 ? FTC_F32 : std::is_same<T, F16>::value ? FTC_F16 : FTC_BF16);
-                    a[i] = c < d_in && row < r_end ? v : 0.f;
-                }
-#pragma unroll
-                for (int j = 0; j < PB; ++j) {
-                    const int c = b0 + (wb + j) * 16 + m, cc = min(c, d_out - 1);
-                    float v = G[rc * ldg + cc];
-                    if constexpr (MASK == 1) v = static_cast<const float *>(Y)[rc * ldy + cc] > 0.f ? v : 0.f;
-                    if constexpr (MASK == 2) {
-                        const unsigned y = static_cast<const uint16_t *>(Y)[rc * ldy + cc];
-                        v = (y != 0u && y <= limit) ? v : 0.f;
-                    }
-                    b[j] = c < d_out && row < r_end ? v : 0.f;
-                }
-#pragma unroll
-                for (int i = 0; i < PA; ++i)
-#pragma unroll
-                    for (int j = 0; j < PB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], acc[i][j], 0, 0, 0);
-            }
+        } else {
+            plain_step(r0);
         }
         __syncthreads();
+    }
+    float zero = 0.f;
+#pragma unroll
+    for (int i = 0; i < PA; ++i)
+#pragma unroll
+        for (int j = 0; j < PB; ++j) zero = not_finite(acc[i][j], zero);
+    if (__builtin_expect(pieces && __builtin_amdgcn_ballot_w64(zero != 0.f) != 0, 0)) {  // pieces may have made it so: this wave's sums without them
+#pragma unroll
+        for (int i = 0; i < PA; ++i)
+#pragma unroll
+            for (int j = 0; j < PB; ++j) acc[i][j] = split_f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+        for (int64_t r0 = r_begin; r0 < r_end; r0 += WT_ROWS) plain_step(r0);
     }
     float *out = partial + static_cast<size_t>(blockIdx.x) * d_in * ldp;
 #pragma unroll

@@ -231,3 +231,45 @@ def test_infinities_and_nan_in_sums_of_few_products(n, d_in, d_out):
         ok = torch.isfinite(ref)
         terms = (X.double().abs() @ W.double().abs())[ok]
         assert float(((got.double()[ok] - ref[ok]).abs() / terms).max()) <= d_in * 2.0 ** -24 * (1 + 2.0 ** -20)
+
+
+LARGE = 1.998046875 * 2.0 ** 63  # its first bf16 piece is 2^64
+
+
+@pytest.mark.parametrize("n,d_in,d_out", [(20_000, 70, 70), (100_000, 33, 9), (100_000, 100, 16), (300, 70, 20), (2708, 504, 64), (20_000, 33, 20)])
+def test_products_and_sums_below_the_largest_number_are_finite(n, d_in, d_out):
+    """One product, and a sum of two, of 0.999 times the largest number, whose bf16 pieces make infinity."""
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    X, W = torch.randn((n, d_in), generator=gen, device="cuda"), torch.randn((d_in, d_out), generator=gen, device="cuda")
+    W[d_in - 1, 2], W[3, 2], W[9, 2] = 2.0 ** 64, 2.0 ** 63, 2.0 ** 63
+    X[5], X[n - 1], X[7] = 0.0, 0.0, 0.0
+    X[:, 3], X[:, 9], X[:, d_in - 1] = 0.0, 0.0, 0.0
+    X[5, d_in - 1], X[n - 1, 3], X[n - 1, 9], X[7, d_in - 1] = LARGE, LARGE, LARGE, -LARGE
+    X[9, 3] = float("inf")
+    dX = torch.empty((n, d_out), device="cuda")
+    B.ftc_update_gemm_backward(torch.zeros((n, d_out), device="cuda"), W.T.contiguous(), X, dX=dX)
+    for Z in (B.ftc_update_gemm(X, W), dX):
+        assert Z[5, 2] == LARGE * 2.0 ** 64 and Z[n - 1, 2] == LARGE * 2.0 ** 64 and Z[7, 2] == -LARGE * 2.0 ** 64
+        assert torch.isinf(Z[9]).all()
+        Z[9] = 0.0
+        X1 = X.clone()
+        X1[9] = 0.0
+        assert rel(Z, X1, W) <= (d_in / 4 + 8) * 2.0 ** -24
+
+
+@pytest.mark.parametrize("dtype", [F32, F16, BF16])
+@pytest.mark.parametrize("n,d_in,d_out", [(32_800, 40, 70), (100_001, 40, 64), (66_000, 128, 60), (45_000, 100, 128)])
+def test_weight_gradients_below_the_largest_number_are_finite(dtype, n, d_in, d_out):
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    X, G = torch.randn((n, d_in), generator=gen, device="cuda").to(dtype), torch.randn((n, d_out), generator=gen, device="cuda")
+    rows = [n // 3, n - 1]
+    X[rows], G[rows] = 0.0, 0.0
+    X[:, 3], G[:, 2], G[:, 4] = 0.0, 0.0, 0.0
+    X[rows[0], 3], G[rows[0], 2] = 2.0 ** 14, LARGE * 2.0 ** 50
+    X[rows[1], 3], G[rows[1], 4] = 2.0 ** 14, -LARGE * 2.0 ** 50
+    for masked in (False, True):
+        Z = torch.ones((n, d_out), device="cuda") if masked else None
+        dW = B.ftc_update_gemm_backward(X, torch.zeros((d_in, d_out), dtype=dtype, device="cuda"), G, Z=Z, want_dX=False)[1]
+        assert dW[3, 2] == LARGE * 2.0 ** 64 and dW[3, 4] == -LARGE * 2.0 ** 64
+        ref, terms = X.double().T @ G.double(), X.double().abs().T @ G.double().abs()
+        assert float(((dW.double() - ref).abs() / terms.clamp(min=1e-300)).max()) <= 1e-5
