@@ -292,10 +292,15 @@ __global__ __launch_bounds__(256, NT == 8 ? 2 : NT == 2 && !TRANS ? 5 : 4) void 
     }
 }
 
-// fp32 products of at most SPLIT_FROM indices: one v_mfma_f32_16x16x4_f32 a tile, lane l holding index l/16; rows, columns, stores and `neighbours`
-// as above.  W stays in registers.  Bound by writing Z (us, in pieces / here: 200 000 x 1 -> 128 22.9 / 18.4, 1 000 000 x 4 -> 8
-// 20.2 / 9.9, dX of 200 000 x 128 from one column 21 / 19, of 100 000 x 64 from three 13.7 / 9.1).
-template <int NT, bool TRANS, class TW>
+// fp32 products of at most 4 KS indices: KS v_mfma_f32_16x16x4_f32 a tile, lane l holding index l/16 of four; rows, columns, stores and
+// `neighbours` as above.  W stays in registers.  Up to SPLIT_FROM indices for the exact products, dX up to FEW_BACK for the time.  Bound by writing Z.  us, in
+// pieces / here: 200 000 x 1 -> 128 22.9 / 18.4, 1 000 000 x 4 -> 8 20.2 / 9.9; dX with dW (with input_grad_kernel before) 200 000 x 128 from one column 47.0
+// / 44.1 (51.5), 602 932 x 120 from 8 190 / 179 (178), 213 277 x 331 from 8 210 / 197 (205), 100 000 x 300 from 8 68 / 62 (72), 1 000 000 x 128 from 3 300 / 286 (274).
+// Tried: an fp32 product a lane and column, whole rows a wave (400 000 x 128 from 7 123 us for 110); non-temporal stores (1 000 000 x 64 from 4
+// 155 / 135, but 224 774 x 506 from 2, where rows are no whole lines, 270 / 551).
+constexpr int FEW_BACK = 8;
+
+template <int NT, int KS, bool TRANS, class TW>
 __global__ __launch_bounds__(256) void gemm_few_kernel(int n, const float *__restrict__ X, int ldx, int d_in, const void *__restrict__ W, int w_ld,
                                                        int d_out, void *__restrict__ Z, int ldz, int zdt, Epi epi, int n_blocks, int neighbours)
 {
@@ -310,21 +315,28 @@ __global__ __launch_bounds__(256) void gemm_few_kernel(int n, const float *__res
         first = static_cast<int>(slot / gridDim.y * 8u + id % 8u);
     }
     const int col0 = group * COLS, cols = min(COLS, d_out - col0);
-    float w[NT];
+    float w[KS][NT];
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-        const int o = nt * 16 + m;
-        const bool in = kb < d_in && o < cols;
-        const int64_t i = TRANS ? static_cast<int64_t>(col0 + o) * w_ld + kb : static_cast<int64_t>(kb) * w_ld + col0 + o;
-        const float v = load_elem(W, in ? i : 0, WDT);
-        w[nt] = in ? v : 0.f;
-    }
+    for (int q = 0; q < KS; ++q)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const int o = nt * 16 + m, k = q * 4 + kb;
+            const bool in = k < d_in && o < cols;
+            const int64_t i = TRANS ? static_cast<int64_t>(col0 + o) * w_ld + k : static_cast<int64_t>(k) * w_ld + col0 + o;
+            const float v = load_elem(W, in ? i : 0, WDT);
+            w[q][nt] = in ? v : 0.f;
+        }
     for (int block = first; block < n_blocks; block += gridDim.x) {  // uniform
         const int64_t row = (static_cast<int64_t>(block) * 4 + wave) * 16 + m;
-        const float v = X[min(row, static_cast<int64_t>(n) - 1) * ldx + min(kb, d_in - 1)], x = kb < d_in ? v : 0.f;
         split_f32x4 c[NT];
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) c[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[nt], x, split_f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+        for (int q = 0; q < KS; ++q) {
+            const int k = q * 4 + kb;
+            const float v = X[min(row, static_cast<int64_t>(n) - 1) * ldx + min(k, d_in - 1)], x = k < d_in ? v : 0.f;
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+                c[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[q][nt], x, q == 0 ? split_f32x4{0.f, 0.f, 0.f, 0.f} : c[nt], 0, 0, 0);
+        }
         if (row >= n) continue;
         const float f = epi.factor(row);
 #pragma unroll
@@ -360,7 +372,9 @@ static void gemm_tile_t(int n, const void *X, int ldx, int d_in, const void *W, 
     // column 19.8 / 14.4; 17.1, from 10 23.4 / 16.5; 21.9, 200 000 x 128 from 7 30.6 / 23.3; 27.2, 100 000 x 301 from 7 42.6 / 35.6; 36.0, 40 000 x
     // 1433 from 7 122.8 / 83.1; 101.2; 262 144 x 128 from 7 40.9 / 36.3; 37.4; but 400 000 x 128
     // from 64 75.8 / 86.5, from 40 71.3 / 79.9).
-    const bool neighbours = TRANS && groups > 1 && n < 327680;
+    // Products of few indices always do (us, apart / together: 602 932 x 120 from 8 193 / 182, 1 000 000 x 128 from 3 301 / 289, 400 000 x 70 from 5 71.5 / 67.6).
+    constexpr int FEW = TRANS ? FEW_BACK : SPLIT_FROM;
+    const bool neighbours = TRANS && groups > 1 && (n < 327680 || d_in <= FEW);
     const int most = !neighbours ? 2048 : groups <= 25 ? 1024 / groups : 40;
     int grid = d_in <= GemmChunk<T>::KC && n_blocks > most ? most : n_blocks;
     if (neighbours) grid = (grid + 7) / 8 * 8;
@@ -369,15 +383,20 @@ static void gemm_tile_t(int n, const void *X, int ldx, int d_in, const void *W, 
                        zdt, epi, n_blocks, neighbours ? 1 : 0)
 #define FTC_GT(N) if (nt == N) FTC_GT1(N, true)
     if constexpr (T::BYTES == 4) {
-        if (d_in <= SPLIT_FROM) {
-#define FTC_GF(N)                                                                                                                              \
-    if (nt == N)                                                                                                                               \
-        hipLaunchKernelGGL((gemm_few_kernel<N, TRANS, TW>), dim3(grid, groups), dim3(256), 0, s, n, static_cast<const float *>(X), ldx, d_in, W, \
-                           w_ld, d_out, Z, ldz, zdt, epi, n_blocks, neighbours ? 1 : 0)
-            FTC_GF(1);
-            FTC_GF(2);
-            FTC_GF(4);
+        if (d_in <= FEW) {
+#define FTC_GF1(N, K)                                                                                                                          \
+    hipLaunchKernelGGL((gemm_few_kernel<N, K, TRANS, TW>), dim3(grid, groups), dim3(256), 0, s, n, static_cast<const float *>(X), ldx, d_in, W, \
+                       w_ld, d_out, Z, ldz, zdt, epi, n_blocks, neighbours ? 1 : 0)
+#define FTC_GF(N)                                     \
+    if (nt == N) {                                    \
+        if (d_in <= 4) FTC_GF1(N, 1);                 \
+        else if constexpr (TRANS) FTC_GF1(N, 2);      \
+    }
+            FTC_GF(1)
+            FTC_GF(2)
+            FTC_GF(4)
 #undef FTC_GF
+#undef FTC_GF1
             return;
         }
     }
