@@ -522,6 +522,53 @@ int32_t launch_weight_grad(int n, const void *X, int ldx, int xdt, int d_in, con
     return launch_status("weight_grad");
 }
 
+// ---- dX = G W^T, large and from few columns -----------------------------------------------------------
+// A thread owns one input feature a and keeps row a of W in registers; the rows of G are staged in LDS and read as broadcasts.  Bound by
+// writing dX, in rows of which a workgroup stores 256 columns at once: beyond the memory-side cache (256 MB) that is ahead of the tiles of 64 columns of
+// gemm_tile.hip, which leave lines of memory in parts, most of all where rows are no whole lines (launch_input_grad() there has the line).
+constexpr int IG_ROWS = 64;
+
+template <int DOUT>  // d_out padded to a multiple of 4
+__global__ __launch_bounds__(256) void input_grad_kernel(int n, const float *__restrict__ G, int ldg, int d_out,
+                                                         const void *__restrict__ W, int wdt, int d_in,
+                                                         void *__restrict__ dX, int lddx, int dx_dt)
+{
+    __shared__ __attribute__((aligned(16))) float Gs[IG_ROWS * DOUT];
+    const int tid = threadIdx.x;
+    const int64_t r0 = static_cast<int64_t>(blockIdx.x) * IG_ROWS;
+    for (int t = tid; t < IG_ROWS * DOUT; t += 256) {
+        const int r = t / DOUT, b = t % DOUT;
+        Gs[t] = (r0 + r < n && b < d_out) ? G[(r0 + r) * ldg + b] : 0.f;
+    }
+    __syncthreads();
+    for (int a = tid; a < d_in; a += 256) {
+        float w[DOUT];
+#pragma unroll
+        for (int b = 0; b < DOUT; ++b) w[b] = b < d_out ? load_elem(W, static_cast<int64_t>(a) * d_out + b, wdt) : 0.f;
+        for (int r = 0; r < IG_ROWS && r0 + r < n; ++r) {
+            float acc = 0.f;
+#pragma unroll
+            for (int b = 0; b < DOUT; b += 4) {
+                const float4 z = *reinterpret_cast<const float4 *>(&Gs[r * DOUT + b]);
+                acc = fmaf(z.x, w[b], acc);
+                acc = fmaf(z.y, w[b + 1], acc);
+                acc = fmaf(z.z, w[b + 2], acc);
+                acc = fmaf(z.w, w[b + 3], acc);
+            }
+            store_elem(dX, (r0 + r) * lddx + a, dx_dt, acc);
+        }
+    }
+}
+
+int32_t launch_input_grad_rows(int n, const float *G, int ldg, int d_out, const void *W, int wdt, int d_in, void *dX, int lddx, int dx_dt,
+                               hipStream_t s)
+{
+    const unsigned grid = static_cast<unsigned>((static_cast<int64_t>(n) + IG_ROWS - 1) / IG_ROWS);
+    if (d_out <= 8) hipLaunchKernelGGL(input_grad_kernel<8>, dim3(grid), dim3(256), 0, s, n, G, ldg, d_out, W, wdt, d_in, dX, lddx, dx_dt);
+    else hipLaunchKernelGGL(input_grad_kernel<16>, dim3(grid), dim3(256), 0, s, n, G, ldg, d_out, W, wdt, d_in, dX, lddx, dx_dt);
+    return launch_status("input_grad rows");
+}
+
 // ---- out[e] = alpha * (wa * a[e] + wb * a[T[e]]) * cs[col[e]] -------------------------------------
 __global__ __launch_bounds__(256) void edge_combine_kernel(int nnz, const float *__restrict__ a,
                                                            const int *__restrict__ T, float wa, float wb, float alpha,

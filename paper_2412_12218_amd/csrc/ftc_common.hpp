@@ -84,6 +84,8 @@ int32_t launch_gemm_slice(int n, const void *X, int ldx, int dt, int d_in, const
                           hipStream_t s);
 int32_t launch_gemm_tile(int n, const void *X, int ldx, int dt, int d_in, const void *W, int d_out, void *Z, int ldz, int zdt, Epi epi,
                          hipStream_t s);
+int32_t launch_input_grad_rows(int n, const float *G, int ldg, int d_out, const void *W, int wdt, int d_in, void *dX, int lddx, int dx_dt,
+                               hipStream_t s);
 int32_t launch_input_grad_slice(int n, const float *G, int ldg, int d_out, const void *W, int wdt, int d_in, void *dX, int lddx, int dx_dt,
                                 hipStream_t s);
 int32_t launch_input_grad(int n, const float *G, int ldg, int d_out, const void *W, int wdt, int d_in, void *dX, int lddx, int dx_dt,

@@ -427,12 +427,25 @@ int32_t launch_gemm_tile(int n, const void *X, int ldx, int dt, int d_in, const 
 // one chunk go through gemm_slice.hip, where the waves of a workgroup share it (us, here / there: 500 x 64 from 300 columns 13.5 / 3.6, 2708 x 64 from
 // 504 23.2 / 16.5, 6000 x 33 from 300 14.5 / 8.5, 16 000 x 16 from 300 10.5 / 7.7; but 2708 x 301 from 128 8.2 / 11.6, 16 000 x 33 from 300
 // 16.4 / 17.8; W transposed into a buffer and gemm_any_kernel: 12.9, 18.3, 16.3, 11.2, 15.4, 23.1).
+//
+// Large dX from few columns, by input_grad_kernel (backward.hip), which has whole rows of 256 columns in flight (us, that / here: 260 MB, rows of 91
+// columns from 8 104 / 117, from 16 124 / 152, of 128 from 8 98 / 103, from 16 112 / 93; 420 MB 91 from 1 147 / 167, from 10 180 / 266, 128 from 4 140 / 154, from 16
+// 174 / 178, 256 from 16 169 / 150, 506 from 1 164 / 174, from 16 195 / 168; 600 MB 207 from 10 216 / 319; but 200 MB 91 from 4 81 / 80, 420 MB 48 from 4 170 / 158).
+static bool whole_rows_better(int n, int d_out, int d_in, const void *dX, int lddx, int dx_dt)
+{
+    const int64_t row = static_cast<int64_t>(d_in) * elem_size(dx_dt), all = n * row;
+    if (all < 250000000 || d_in <= 64 || d_out > 16) return false;
+    const bool lines = (reinterpret_cast<uintptr_t>(dX) | static_cast<uintptr_t>(lddx) * elem_size(dx_dt)) % 128 == 0;
+    return d_out <= 8 || (d_in <= 256 && (!lines || all >= 400000000));
+}
+
 int32_t launch_input_grad(int n, const float *G, int ldg, int d_out, const void *W, int wdt, int d_in, void *dX, int lddx, int dx_dt,
                           hipStream_t s)
 {
     if (n == 0) return FTC_OK;
     if (d_out > GemmChunk<F32>::KC && static_cast<int64_t>(n) * d_in <= 1 << 18)
         return launch_input_grad_slice(n, G, ldg, d_out, W, wdt, d_in, dX, lddx, dx_dt, s);
+    if (whole_rows_better(n, d_out, d_in, dX, lddx, dx_dt)) return launch_input_grad_rows(n, G, ldg, d_out, W, wdt, d_in, dX, lddx, dx_dt, s);
     const Epi none{0, nullptr};
     if (wdt == FTC_F32) gemm_tile_t<F32, true, F32>(n, G, ldg, d_out, W, d_out, d_in, dX, lddx, dx_dt, none, s);
     else if (wdt == FTC_F16) gemm_tile_t<F32, true, F16>(n, G, ldg, d_out, W, d_out, d_in, dX, lddx, dx_dt, none, s);
