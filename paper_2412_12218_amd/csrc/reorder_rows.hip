@@ -20,6 +20,7 @@
 // entries are in rows of more than 32 768 entries with repeated columns (2^22 nodes, 65 M entries, 95 % of them in rows of
 // 60 000: 18 against 9 ms; half of them: 9.7 against 9.4; label propagation on the first: 16 ms a round on either).
 #include "edge_ranges.hpp"
+#include "entry_index.hpp"
 
 namespace ftc {
 
@@ -657,16 +658,16 @@ __device__ __forceinline__ bool bitmap_row(const Relabel &u, int r, uint32_t *bi
         if (threadIdx.x == 0) *dup = 0;
         __syncthreads();
         bool twice = false;
-        for (int i0 = threadIdx.x; i0 < len; i0 += RS_NT * 8) {  // eight look-ups in flight
+        for (uint32_t i0 = threadIdx.x; entry_in(i0, len); i0 += RS_NT * 8) {  // eight look-ups in flight
             int c[8], v[8];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) c[k] = u.col_idx[start + min(i0 + k * RS_NT, len - 1)];
+            for (int k = 0; k < 8; ++k) c[k] = u.col_idx[start + entry_or_last(i0 + k * RS_NT, len)];
 #pragma unroll
             for (int k = 0; k < 8; ++k) v[k] = u.look(c[k]);
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
                 const int x = u.settle(c[k], v[k], true) - base;
-                if (i0 + k * RS_NT < len && x >= 0 && x < span) {
+                if (entry_in(i0 + k * RS_NT, len) && x >= 0 && x < span) {
                     const uint32_t m = 1u << (x & 31);
                     twice = twice || (atomicOr(&bits[pad_word(x >> 5)], m) & m) != 0u;
                 }
@@ -711,7 +712,7 @@ __device__ __forceinline__ int count_range(const Use &u, const int *__restrict__
     for (int i = threadIdx.x; i < pad_word(RS_RANGE); i += RS_NT) cnt[i] = 0;
     __syncthreads();
     int less = 0;
-    for (int i = threadIdx.x; i < len; i += RS_NT) {
+    for (uint32_t i = threadIdx.x; entry_in(i, len); i += RS_NT) {
         const int c = (values ? values[start + i] : u.value(u.col_idx[start + i])) - base;
         if (c < 0) ++less;
         else if (c < RS_RANGE) atomicAdd(&cnt[pad_word(c)], 1);
@@ -845,14 +846,14 @@ __global__ __launch_bounds__(RS_NT) void vote_check_kernel(int n, int nnz, const
         wave_lds_sync();
         if (__builtin_amdgcn_ballot_w64(len > RS_SHORT) == 0ull) {  // the entries of all 64 rows in one go
             const int end = starts[wave][64];
-            for (int e0 = starts[wave][0]; e0 < end; e0 += 64 * U) {
+            for (uint32_t e0 = starts[wave][0]; entry_in(e0, end); e0 += 64 * U) {
                 int c[U];
 #pragma unroll
-                for (int k = 0; k < U; ++k) c[k] = __builtin_nontemporal_load(col_idx + min(e0 + k * 64 + lane, end - 1));
+                for (int k = 0; k < U; ++k) c[k] = __builtin_nontemporal_load(col_idx + entry_or_last(e0 + k * 64 + lane, end));
 #pragma unroll
                 for (int k = 0; k < U; ++k) {
-                    const int e = e0 + k * 64 + lane;
-                    if (e < end && has_changed(c[k])) {
+                    if (entry_in(e0 + k * 64 + lane, end) && has_changed(c[k])) {
+                        const int e = static_cast<int>(e0) + k * 64 + lane;
                         int t = 0;  // the last of the 64 rows that begins at or before e
 #pragma unroll
                         for (int h = 32; h > 0; h /= 2) t += starts[wave][t + h] <= e ? h : 0;
