@@ -4,7 +4,7 @@
 // Rows are independent, so nothing is sorted across rows: a row is sorted where it fits,
 //   at most 16 / 32 / 64        a quarter, half or whole wave, one entry per lane (bitonic, data-parallel-primitive moves),
 //   at most 256 / 1024          a wave, 4 / 16 entries per lane,
-//   at most 4096 / 8192         a workgroup of 256 / 1024 threads, in registers and LDS,
+//   at most 4096 / 8192         a workgroup of 256 / 1024 threads, in registers and LDS (see RS_GROUP_FEW),
 //   longer                      a bitmap of the columns in LDS (relabelling; duplicates: counters, see below) or
 //                               counters in LDS per 32 768 labels (label propagation); with more than 2^19 nodes those of
 //                               at most 32 768 entries are sorted in LDS instead of counted (many_ranges()).
@@ -33,6 +33,11 @@ constexpr int RS_RANGE = 32768;     // counters per pass over a long row
 constexpr int RS_WORDS = RS_RANGE + RS_RANGE / 32;  // LDS words of the workgroups that take long rows
 constexpr int RS_BITS_LOG2 = 20;    // columns per bitmap pass over a long row (32 768 words)
 constexpr int VT_COUNTERS = 256;
+// Up to this many rows in queue 2, the workgroups of the kernel of the longer ones, those above 2048 entries are sorted there, by 1024 threads: beside
+// the short rows a workgroup of 256 needs 60 us for one, which a small graph waits for.  us, label propagation of ten rounds, always beside the
+// short ones / by this line: R-MAT, 2^15 nodes, 10^6 entries (120 rows) 605 / 406, 2^17 nodes, 1.1 M (17) 617 / 422, 3.1 M (136) 789 / 690, 2^18 nodes, 4.2 M (153)
+// 890 / 808; with 512 instead 2^20 nodes, 8.8 M (388) 2002 / 2042, with 1024 or for all rows of the queue 2^17 nodes, 6 M (816) 820 / 990.
+constexpr int RS_GROUP_FEW = 256;
 constexpr int RS_NONE = 0x7fffffff; // sorts behind every column and label
 
 // lengths of the rows: len[r] = rp[r + 1] - rp[r]; counts[q] rows of class q in rows[q]
@@ -549,8 +554,10 @@ __global__ __launch_bounds__(256, 6) void row_sort_kernel(Use u, RowQueues q, in
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (static_cast<int>(blockIdx.x) < queue_blocks) {
-        const int first = blockIdx.x * 4 + wave, step = queue_blocks * 4;
-        const int n2 = q.counts[2], n1 = q.counts[1], n0 = q.counts[0];
+        const int n2 = q.counts[2], longest = n2 > RS_GROUP_FEW ? RS_GROUP : RS_GROUP / 2, n1 = q.counts[1], n0 = q.counts[0];
+        // each class of rows begins with the workgroup (wave) after the last one of the class before, which was the longer one (ten rounds of label
+        // propagation, R-MAT, 2^15 nodes 427 / 406 us, 2^16 nodes, 553 000 entries 337 / 314)
+        const int first = static_cast<int>((blockIdx.x + queue_blocks - n2 % queue_blocks) % queue_blocks) * 4 + wave, step = queue_blocks * 4;
         if constexpr (Use::VOTES) {  // the rows that are counted collect their winner in q.best (row_sort_big_kernel)
             const int n4 = q.counts[4];
             for (int i = blockIdx.x * 256 + threadIdx.x; i < n4; i += queue_blocks * 256) {
@@ -574,7 +581,7 @@ __global__ __launch_bounds__(256, 6) void row_sort_kernel(Use u, RowQueues q, in
             int start, len;
             u.row(r, start, len);
             if (len <= RS_GROUP / 2) group_row<Use, RS_GROUP / 512, 256, RS_GROUP>(u, r, start, len, s, tmp64);
-            else group_row<Use, RS_GROUP / 256, 256, RS_GROUP>(u, r, start, len, s, tmp64);
+            else if (len <= longest) group_row<Use, RS_GROUP / 256, 256, RS_GROUP>(u, r, start, len, s, tmp64);
         }
         // the network of half the size costs 0.4 of the whole one, and most rows of a class need no more (all in whole ones: relabelled R-MAT
         // graph 0.30 ms of this kernel for 0.25, ten rounds of label propagation 4.8 for 4.2)
@@ -585,7 +592,8 @@ __global__ __launch_bounds__(256, 6) void row_sort_kernel(Use u, RowQueues q, in
             if (len <= RS_LONG / 2) queued_row<Use, RS_LONG / 128>(u, r, start, len, lane);
             else queued_row<Use, RS_LONG / 64>(u, r, start, len, lane);
         }
-        for (int i = first; i < n0; i += step) {
+        const int first0 = (first + step - n1 % step) % step;
+        for (int i = first0; i < n0; i += step) {
             const int r = q.rows[0][i];
             int start, len;
             u.row(r, start, len);
@@ -637,7 +645,8 @@ __device__ __forceinline__ void lds_row(const Use &u, int r, int *s, unsigned lo
 {
     int start, len;
     u.row(r, start, len);  // uniform
-    if (len <= 8 * RS_NT) group_row<Use, 8, RS_NT, RS_WORDS>(u, r, start, len, s, tmp);
+    if (len <= 4 * RS_NT) group_row<Use, 4, RS_NT, RS_WORDS>(u, r, start, len, s, tmp);
+    else if (len <= 8 * RS_NT) group_row<Use, 8, RS_NT, RS_WORDS>(u, r, start, len, s, tmp);
     else if (len <= 16 * RS_NT) group_row<Use, 16, RS_NT, RS_WORDS>(u, r, start, len, s, tmp);
     else group_row<Use, 32, RS_NT, RS_WORDS>(u, r, start, len, s, tmp);
 }
@@ -773,6 +782,14 @@ __global__ __launch_bounds__(RS_NT) void row_sort_big_kernel(Use u, RowQueues q)
         }
     }
     for (int i = blockIdx.x; i < n3; i += gridDim.x) lds_row(u, q.rows[3][i], s, tmp64);
+    const int n2 = q.counts[2];
+    if (n2 <= RS_GROUP_FEW)  // from the workgroup after the last one above on
+        for (int i = (blockIdx.x + gridDim.x - n3 % gridDim.x) % gridDim.x; i < n2; i += gridDim.x) {
+            const int r = q.rows[2][i];
+            int start, len;
+            u.row(r, start, len);
+            if (len > RS_GROUP / 2) lds_row(u, r, s, tmp64);
+        }
 }
 
 // long rows in which a column occurs more than once: counters instead of bits, one workgroup per row and range
@@ -964,7 +981,7 @@ static RowSortGrid row_sort_grid(int n, int nnz)
     const int64_t queued = queue_cap(nnz, RS_SHORT);
     g.queue_blocks = static_cast<int>((queued + 3) / 4 < 1024 ? (queued + 3) / 4 : 1024);
     g.blocks = g.queue_blocks + static_cast<int>((static_cast<int64_t>(n) + 4 * RS_ROWS - 1) / (4 * RS_ROWS));
-    const int64_t big = queue_cap(nnz, RS_GROUP);
+    const int64_t big = queue_cap(nnz, RS_LONG);
     g.big_blocks = static_cast<int>(big < 256 ? big : 256);
     return g;
 }
@@ -986,7 +1003,7 @@ int32_t launch_relabel_rows(const ftc_csr &g, const int *perm, const int *inv, c
     const RowSortGrid grid = row_sort_grid(g.n, g.nnz);
     const Relabel u{g.n, g.row_ptr, g.col_idx, perm, inv, rp, col_idx_out, flag};
     classify_rows(g.n, rp, RS_LDS, q, nullptr, s);
-    if (g.nnz > RS_GROUP) hipLaunchKernelGGL(row_sort_big_kernel<Relabel>, dim3(grid.big_blocks), dim3(RS_NT), 0, s, u, q);
+    if (g.nnz > RS_LONG) hipLaunchKernelGGL(row_sort_big_kernel<Relabel>, dim3(grid.big_blocks), dim3(RS_NT), 0, s, u, q);
     hipLaunchKernelGGL(row_sort_kernel<Relabel>, dim3(grid.blocks), dim3(256), 0, s, u, q, grid.queue_blocks);
     if (g.nnz > RS_LDS) {
         if (q.values)
@@ -1001,7 +1018,7 @@ template <bool FIRST>
 static void label_round(const ftc_csr &g, const Votes<FIRST> &u, const RowQueues &q, const RowSortGrid &grid, hipStream_t s)
 {
     hipLaunchKernelGGL(row_sort_kernel<Votes<FIRST>>, dim3(grid.blocks), dim3(256), 0, s, u, q, grid.queue_blocks);
-    if (g.nnz > RS_GROUP) hipLaunchKernelGGL(row_sort_big_kernel<Votes<FIRST>>, dim3(grid.big_blocks), dim3(RS_NT), 0, s, u, q);
+    if (g.nnz > RS_LONG) hipLaunchKernelGGL(row_sort_big_kernel<Votes<FIRST>>, dim3(grid.big_blocks), dim3(RS_NT), 0, s, u, q);
 }
 
 // `labels` holds the labels after the last round; ws: row_sort_ws(n, nnz) bytes

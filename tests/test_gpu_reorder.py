@@ -384,3 +384,32 @@ def test_order_by_key_at_the_lines_of_its_tiles(n):
     assert int(flag.item()) == 0 and torch.equal(perm.long(), ref)
     assert torch.equal(inv.long()[ref], torch.arange(n, device="cuda"))
     assert torch.all(ws[size:] == 0x5a)
+
+
+@pytest.mark.parametrize("long_rows", [1, 200, 255, 256, 257, 1500])
+@pytest.mark.parametrize("distinct", [True, False])
+def test_few_and_many_rows_of_a_workgroup_each(long_rows, distinct):
+    """Up to 256 rows of 1025 to 4096 entries those above 2048 are sorted by the kernel of the longer rows, from 257 on beside the short
+    ones; with rows of every class around them."""
+    rng = np.random.default_rng(long_rows)
+    n = 9000
+    deg = rng.integers(0, 40, size=n)
+    at = rng.choice(n, size=long_rows + 120, replace=False)
+    deg[at[:long_rows]] = np.resize([4096, 1025, 2049, 2048, 3000], long_rows)
+    deg[at[long_rows:]] = np.resize([65, 128, 129, 256, 257, 512, 513, 1024, 4097, 8192, 8193], 120)
+    row_ptr = np.zeros(n + 1, dtype=np.int32)
+    row_ptr[1:] = np.cumsum(deg)
+    rows = np.repeat(np.arange(n, dtype=np.int64), deg)
+    col = np.concatenate([rng.choice(n, size=d, replace=False) if distinct else rng.integers(0, n // 4, size=d) for d in deg]).astype(np.int64)
+    perm = rng.permutation(n)
+    inv = np.empty(n, dtype=np.int64)
+    inv[perm] = np.arange(n)
+    dg = dev_graph(synth.Graph(n, row_ptr, col.astype(np.int32), "long rows"))
+    i32 = lambda a: torch.from_numpy(a.astype(np.int32)).cuda()
+    pg, flag = B.ftc_permute_graph(dg, i32(perm), i32(inv))
+    assert int(flag.item()) == 0
+    assert np.array_equal(pg.col_idx.cpu().numpy(), np.sort(inv[rows] * n + inv[col]) % n)
+    label = np.arange(n, dtype=np.int64)
+    for rounds in (1, 2, 3):
+        label = voted(rows, label[col], n, label)
+        assert np.array_equal(B.ftc_label_propagation(dg, rounds).cpu().numpy(), label), f"{rounds} rounds"
