@@ -330,8 +330,10 @@ int32_t launch_gemm(int n, const void *X, int ldx, int dt, int d_in, const void 
         else hipLaunchKernelGGL(gemm_narrow_kernel<12>, grid, dim3(256), 0, s, n, x, ldx, d_in, w, d_out, Z, ldz, zdt, epi);
         return launch_status("update_gemm narrow");
     }
-    // up to 16 fp32 columns both wait for X: 100 000 x 1433 -> 16 139 (gemm_tile.hip) / 138, 65 000 x 65 -> 7 7.2 / 6.4, 1 000 000 x 33 -> 2 40 / 57
-    if (dt != FTC_F32 || d_out > 16 || n >= 98304 || few) return launch_gemm_tile(n, X, ldx, dt, d_in, W, d_out, Z, ldz, zdt, epi, s);
+    // Up to 16 fp32 columns both wait for X, gemm_any_kernel in longer chunks, gemm_tile.hip with fewer loads of W.  That one's time over this one's, 5 to
+    // 1433 indices into 2, 7, 10, 16 columns: 30 000 rows 1.02 to 1.17, 45 000 0.95 to 1.08, 65 000 0.91 to 1.04, 98 000 0.74 to 0.90, 131 000 0.75 to 1.02, 10^6
+    // 0.49 to 0.85.
+    if (dt != FTC_F32 || d_out > 16 || n >= 65536 || few) return launch_gemm_tile(n, X, ldx, dt, d_in, W, d_out, Z, ldz, zdt, epi, s);
     hipLaunchKernelGGL(gemm_any_kernel, dim3(static_cast<unsigned>((n + 63) / 64)), dim3(256), 0, s, n, static_cast<const float *>(X), ldx, d_in,
                        static_cast<const float *>(W), d_out, Z, ldz, zdt, epi);
     return launch_status("update_gemm");

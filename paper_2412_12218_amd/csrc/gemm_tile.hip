@@ -7,8 +7,8 @@
 //              staged, so that a chunk waits for memory once;
 //   C          W is the first operand of the instruction (QUADS): lane l holds Z[row0 + l%16][n0 + (l/16) 4 + i], four columns that leave in
 //              one store at the alignment of an element.  With X first, a column a lane, us, that way / this: dX fp16 2^20 rows 8 -> 32 48 / 34,
-//              fp32 100 000 rows 10 -> 128 29 / 24, Z fp32 1 000 000 x 33 -> 2 39 / 29, 300 -> 128 82.5 / 79.3, fp16 179 245 x 18 -> 64 18.1 / 13.7,
-//              400 000 x 301 -> 128 287 / 267; but fp32 100 000 x 128 -> 10 13.1 / 13.6, 1433 -> 16 139.8 / 142.7, which stay with it.
+//              fp32 100 000 rows 10 -> 128 29 / 24, Z 300 -> 128 82.5 / 79.3, fp16 179 245 x 18 -> 64 18.1 / 13.7, 400 000 x 301 -> 128 287 / 267; fp32 into
+//              at most 16 columns over more than one chunk this way too, but with seven workgroups on some compute units (gemm_tile_t()).
 // Where one chunk holds all of W a workgroup walks over the rows and stages it once.
 //
 // Bound by reading X (and writing Z) up to about 32 columns, then by the chain load, stage, multiply of a chunk, which four workgroups
@@ -401,7 +401,10 @@ static void gemm_tile_t(int n, const void *X, int ldx, int d_in, const void *W, 
         }
     }
     if constexpr (T::BYTES == 4 && !TRANS) {
-        if (nt == 1 && d_in > GemmChunk<T>::KC) {
+        // A compute unit holds seven workgroups of these.  Where some have seven and the others six, all wait for those with seven, which are ahead with a
+        // column a lane (us, a column a lane / four, into 16: 99 000 rows of 300 26.9 / 27.7, of 700 57.6 / 60.2, of 1433 137 / 141, 110 000 of 700 64.3 / 67.5, of 1433
+        // 143 / 147); with fewer rows or more they are behind (98 000 of 300 25.7 / 24.7, of 1433 125 / 123, 115 000 of 300 32.2 / 30.3, of 1433 161 / 157, 170 000 225 / 222).
+        if (nt == 1 && d_in > GemmChunk<T>::KC && n_blocks > 6 * 256 && n_blocks <= 7 * 256) {
             FTC_GT1(1, false);
             return;
         }

@@ -23,7 +23,7 @@ def rel(Z, X, W):
 @pytest.mark.parametrize("dtype", [F32, F16, BF16])
 @pytest.mark.parametrize("n,d_in,d_out", [
     (1, 1, 65), (15, 31, 66), (65, 32, 80), (64, 33, 128), (1000, 63, 129), (4096, 127, 64), (4097, 127, 7), (4097, 64, 33),
-    (8193, 128, 33), (12288, 65, 17), (12289, 65, 17), (16385, 129, 16), (98303, 17, 16), (98304, 17, 16), (98305, 70, 3),
+    (8193, 128, 33), (12288, 65, 17), (12289, 65, 17), (16385, 129, 16), (98303, 17, 16), (98304, 17, 16), (98305, 70, 3), (65535, 70, 9), (65536, 70, 9), (65537, 200, 16), (98304, 70, 16), (98305, 200, 7), (114688, 65, 16), (114689, 70, 10),
     (65535, 40, 100), (65536, 40, 200), (131073, 20, 40), (5000, 641, 65), (20001, 257, 48)])
 def test_update_gemm_at_edges_of_tiles_and_chunks(dtype, n, d_in, d_out):
     gen = torch.Generator(device="cuda").manual_seed(n + d_in + d_out)
