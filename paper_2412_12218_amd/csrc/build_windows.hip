@@ -1782,9 +1782,8 @@ __global__ __launch_bounds__(256) void win_finish_kernel(int n, int n_windows, i
 static int bitmap_words(int n) { return n <= (1 << 16) ? 2048 : n <= (1 << 17) ? 4096 : 8192; }
 
 // Words of the bitmap of the flat kernel, 0: the size classes take the graph.  Clearing and scanning the bitmap is a fixed
-// cost per window, so windows have to hold enough edges: at 200 000 nodes the lines cross between 143 edges a window on
-// average (55 us here, 50 there) and 269 (62, 85); with the smaller bitmaps the flat kernel was ahead at every
-// density that was measured (80 edges a window: 100 000 nodes 31 / 38 us, 60 000 nodes 21 / 31 us).
+// cost per window, so windows have to hold enough edges; with the smallest bitmap the flat kernel was ahead at every
+// density that was measured (60 000 nodes, 80 edges a window: 21 / 31 us), the larger ones are win_lean_kernel's where windows are small.
 // Where most windows are above MID_CAP edges the first kernel only queues them, one workgroup and one atomic on the same
 // counter each, which the size classes do 1024 windows at a time (us here / there, equal rows): 100 000 nodes with 250
 // entries a row 154 / 184, with 270 269 / 248, with 512 399 / 376; 200 000 nodes with 250 359 / 350, with 270 531 / 481;
@@ -1798,19 +1797,21 @@ static int flat_words(int n, int nnz, int n_windows)
     const int words = bitmap_words(n);
     const int mean = nnz / n_windows;  // edges a window
     if (n_windows <= FINISH_WINDOWS) return n_windows <= 2048 || mean < 3 * MID_CAP ? words : 0;
-    return mean >= (words == 8192 ? 192 : words / 64) && mean < (words == 8192 ? 3584 : MID_CAP) ? words : 0;
+    return mean >= words / 64 && mean < (words == 8192 ? 3584 : MID_CAP) ? words : 0;
 }
 
 // Where a wave per window (win_lean_kernel) is ahead of a workgroup with all of the bitmap (win_flat_kernel, of the size classes below its
-// line): the largest bitmap, as long as few windows are above LEAN_EDGES and with them in the queue.  us, there / here, by edges a window:
-//   uniform, 200 000 nodes 79 41 / 32, 142 50 / 33, 269 61 / 38, 522 70 / 54, 1029 101 / 218; 262 000 nodes 522 86 / 63
-//   power law, 200 000 nodes 73 51 / 34, 304 64 / 48, 476 71 / 60, 937 96 / 132; R-MAT, 262 144 nodes 75 96 / 66, 492 121 / 107, 968 170 / 189
-//   half the bitmap: uniform, 100 000 nodes 79 30 / 27, 269 32 / 29; power law 73 32 / 28, 131 31 / 32, 304 33 / 36; R-MAT, 131 072 nodes 75 55 / 50
+// line): the larger bitmaps, as long as few windows are above LEAN_EDGES and with them in the queue.  Its time over theirs, by edges a window:
+//   131 073 to 262 144 nodes   uniform and blocks 30 .89 to .98, 142 .66 to .69, 329 .61 to .71, 522 .73 to .82, 643 .81 to .89, 956 .97 to 1.06; power law 30
+//                              .76 to .83, 188 .59 to .62, 476 .80 to .88, 592 .88 to 1.01, 880 1.27 to 1.30; R-MAT 30 .74, 135 .72, 611 .89; 2 to 40
+//                              entries in any rows .93 to .97
+//   65 537 to 131 072 nodes    uniform and blocks 30 .81 to .89, 63 .75 to .80, 142 .86 to .92, 266 .90 to .94, 520 .99 to 1.05; power law 30 .72 to .77, 59 .65
+//                              to .70, 131 .94 to 1.01, 188 1.02 to 1.09, 304 1.05 to 1.11; R-MAT 30 .67, 149 .93, 492 .93; 4 to 40 entries .85 to .94
 static bool lean_better(int n, int nnz, int n_windows)
 {
     if (n > FLAT_NODES || nnz <= FLAT_ALL_EDGES || n_windows <= FINISH_WINDOWS) return false;
     const int mean = nnz / n_windows;
-    return bitmap_words(n) == 8192 ? mean < 640 : bitmap_words(n) == 4096 && mean >= 64 && mean < 128;
+    return bitmap_words(n) == 8192 ? mean < 640 : bitmap_words(n) == 4096 && mean < 160;
 }
 
 // Everything after the windows are condensed: prefix of the unique counts, window arrays, packed lists.

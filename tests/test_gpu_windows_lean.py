@@ -53,7 +53,7 @@ def window_sizes_graph(n, blk_h, fill, seed):
     return row_ptr, cols.to(torch.int32)
 
 
-@pytest.mark.parametrize("n,blk_h,fill", [(65_537, 16, 100), (131_072, 16, 127), (131_072, 16, 129), (131_073, 16, 40), (200_003, 16, 300),
+@pytest.mark.parametrize("n,blk_h,fill", [(65_537, 16, 100), (131_072, 16, 127), (131_072, 16, 129), (131_072, 16, 5), (65_537, 16, 60), (80_000, 16, 150), (100_000, 64, 40), (131_073, 16, 40), (200_003, 16, 300),
                                           (200_003, 32, 639), (262_144, 16, 600), (262_144, 64, 500), (262_144, 8, 20), (262_145, 16, 300),
                                           (262_145, 64, 700), (500_001, 16, 10), (1 << 20, 16, 260), ((1 << 20) + 1, 16, 260)])
 @pytest.mark.parametrize("side", [False, True])
