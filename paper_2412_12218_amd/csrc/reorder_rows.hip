@@ -38,6 +38,7 @@ constexpr int VT_COUNTERS = 256;
 // short ones / by this line: R-MAT, 2^15 nodes, 10^6 entries (120 rows) 605 / 406, 2^17 nodes, 1.1 M (17) 617 / 422, 3.1 M (136) 789 / 690, 2^18 nodes, 4.2 M (153)
 // 890 / 808; with 512 instead 2^20 nodes, 8.8 M (388) 2002 / 2042, with 1024 or for all rows of the queue 2^17 nodes, 6 M (816) 820 / 990.
 constexpr int RS_GROUP_FEW = 256;
+constexpr int RS_SHORT_ENTRIES = RS_QUEUES + 1;  // of RowQueues::counts: entries of the rows in no queue
 constexpr int RS_NONE = 0x7fffffff; // sorts behind every column and label
 
 // lengths of the rows: len[r] = rp[r + 1] - rp[r]; counts[q] rows of class q in rows[q]
@@ -66,18 +67,23 @@ __host__ __device__ inline bool many_ranges(int n) { return value_ranges(n) > 16
 __global__ __launch_bounds__(1024) void row_classes_kernel(int n, const int *__restrict__ rp, int in_lds, RowQueues q)
 {
     constexpr int PER = 4;
-    __shared__ int cnt_s[RS_QUEUES], base_s[RS_QUEUES];
+    __shared__ int cnt_s[RS_QUEUES], base_s[RS_QUEUES], short_s;
     if (threadIdx.x < RS_QUEUES) cnt_s[threadIdx.x] = 0;
+    if (threadIdx.x == 0) short_s = 0;
     __syncthreads();
-    int cls[PER], pos[PER];
+    int cls[PER], pos[PER], in_short = 0;
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         const int64_t r = (static_cast<int64_t>(blockIdx.x) * PER + k) * 1024 + threadIdx.x;
         const int len = r < n ? rp[r + 1] - rp[r] : 0;
         cls[k] = len <= RS_SHORT ? -1 : len <= RS_MID ? 0 : len <= RS_LONG ? 1 : len <= RS_GROUP ? 2 : len <= in_lds ? 3 : 4;
         pos[k] = cls[k] >= 0 ? atomicAdd(&cnt_s[cls[k]], 1) : 0;
+        in_short += cls[k] < 0 ? len : 0;
     }
+    in_short = wave_inclusive_scan(in_short);
+    if ((threadIdx.x & 63) == 63) atomicAdd(&short_s, in_short);
     __syncthreads();
+    if (threadIdx.x == 0 && short_s > 0) atomicAdd(&q.counts[RS_SHORT_ENTRIES], short_s);
     if (threadIdx.x < RS_QUEUES && cnt_s[threadIdx.x] > 0) base_s[threadIdx.x] = atomicAdd(&q.counts[threadIdx.x], cnt_s[threadIdx.x]);
     __syncthreads();
 #pragma unroll
@@ -110,6 +116,11 @@ struct Relabel {
     __device__ __forceinline__ int look(int c) const { return map[lookup_index(c, n)]; }
     __device__ __forceinline__ int value(int c) const { return settle(c, look(c), true); }
 };
+constexpr int VT_BITS_LOG2 = 20;
+constexpr float VT_MOST = 0.6f;
+// Only rows of at most RS_SHORT entries are left out (see vote_check_kernel): worth looking for where three quarters of the entries are in these
+// (see VT_FROM; 10^6 nodes, 60 entries each, 0.66 3631 / 3513 us always looking, power law with 0.72 1393 / 1577).
+__host__ __device__ inline bool short_rows_count(int in_short, int nnz) { return static_cast<int64_t>(in_short) * 4 >= static_cast<int64_t>(nnz) * 3; }
 // FIRST: the first round, in which every node's label is its own id and nothing is looked up.
 template <bool FIRST_ROUND>
 struct Votes {
@@ -120,6 +131,7 @@ struct Votes {
     uint32_t *changed;              // bit r >> shift of every row r whose label is another than before is set; NULL: not kept
     int *changes;                   // .. and counted, spread over VT_COUNTERS
     int shift;
+    int nnz;
     const uint32_t *todo;           // rows of at most RS_SHORT entries that may change, a bit each; NULL: all
     __device__ __forceinline__ void row(int r, int &start, int &len) const
     {
@@ -626,7 +638,7 @@ __global__ __launch_bounds__(256, 6) void row_sort_kernel(Use u, RowQueues q, in
         // a row that has no entries, or none that changed, keeps its label
         const int w = len_l > 0 ? win[wave][lane & (RS_ROWS - 1)] : old_l;
         if (short_row) u.out[r_l] = w;
-        if (!u.changed) return;
+        if (!u.changed || !short_rows_count(q.counts[RS_SHORT_ENTRIES], u.nnz)) return;
         const uint32_t m = static_cast<uint32_t>(__builtin_amdgcn_ballot_w64(short_row && w != old_l));
         const int first = static_cast<int>(r0) >> u.shift;  // the 32 >> shift bits of these rows lie in one word
         uint32_t bits = 0u;
@@ -828,10 +840,8 @@ __global__ __launch_bounds__(RS_NT) void row_sort_dup_kernel(Relabel u, RowQueue
 // rows would be left (the changed share times the mean number of entries above VT_MOST) all of them are, at once.
 // On the block model with a million nodes, 32 M entries, a check that leaves rows out takes 50 us, one that doesn't 5; the ninth and the
 // tenth round take 37 and 25 us after it instead of 210.
-constexpr int VT_BITS_LOG2 = 20;
-constexpr float VT_MOST = 0.6f;
 
-__global__ __launch_bounds__(RS_NT) void vote_check_kernel(int n, int nnz, const int *__restrict__ rp, const int *__restrict__ col_idx,
+__global__ __launch_bounds__(RS_NT) void vote_check_kernel(int n, int nnz, const int *__restrict__ in_short, const int *__restrict__ rp, const int *__restrict__ col_idx,
                                                            const uint32_t *__restrict__ changed, const int *__restrict__ changes,
                                                            uint32_t *__restrict__ next_changed, int *__restrict__ next_changes, int shift,
                                                            uint32_t *__restrict__ todo)
@@ -843,6 +853,10 @@ __global__ __launch_bounds__(RS_NT) void vote_check_kernel(int n, int nnz, const
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int words = (((n - 1) >> shift) >> 5) + 1, todo_words = (n + 31) / 32;
     const int thread = blockIdx.x * RS_NT + threadIdx.x, threads = gridDim.x * RS_NT;
+    if (!short_rows_count(*in_short, nnz)) {  // uniform over the grid
+        for (int i = thread; i < todo_words; i += threads) todo[i] = ~0u;
+        return;
+    }
     for (int i = thread; i < words; i += threads) next_changed[i] = 0u;
     if (thread < VT_COUNTERS) next_changes[thread] = 0;
     int total;
@@ -908,8 +922,11 @@ __global__ __launch_bounds__(RS_NT) void vote_check_kernel(int n, int nnz, const
 static int64_t queue_cap(int nnz, int longer_than) { return nnz / (longer_than + 1) + 1; }
 
 // Label propagation looks for the rows that may change from this many entries on: a launch more a round (5 us) against the share of
-// a round (6.5 us a million entries) that the last ones save.  Ten rounds on the block model, with the look-ups of the first round, without the
-// check / as here: 32 M entries 2204 / 1738 us, 23 M 1472 / 1234, 16 M 1077 / 912.
+// a round (6.5 us a million entries) that the last ones save, which depends on the graph.  Ten rounds, never / always, us: uniform 10^6 nodes, 5.0 M entries 399 / 389,
+// 8.9 M 570 / 486, 250 000 nodes, 8.2 M 580 / 602, 500 000 nodes, 12.4 M 807 / 838, 10^6 nodes, 12.9 M 830 / 609, 16.8 M 1086 / 757, 32.7 M 2004 / 2038, 2 10^6 nodes, 29.7 M
+// 2518 / 1508; blocks 10^6 nodes, 8.8 M 566 / 649, 12.8 M 820 / 855, 500 000 nodes, 12.3 M 789 / 736, 16.2 M 1021 / 922, 10^6 nodes, 32.4 M 1975 / 1729.  Graphs with most entries
+// in longer rows lose 3 to 17 % (power law, 10^6 nodes, 19 M, 0.59 of them in short rows 1418 / 1569, now 1463; R-MAT, 2^20 nodes, 32 M, 0.22 3620 / 3974,
+// now 3673): short_rows_count(), which leaves them the empty launch.
 constexpr int VT_FROM = 12000000;
 static bool votes_are_checked(int nnz) { return nnz >= VT_FROM; }
 static int changed_shift(int n)
@@ -1040,12 +1057,12 @@ int32_t launch_label_rounds(const ftc_csr &g, int iters, int *labels, void *ws, 
         // nearly all labels change in the first two rounds; the third is the first to ask which did in the one before
         const bool kept = vc.todo && it >= 1 && it + 1 < iters, check = vc.todo && it >= 2;
         if (check)
-            hipLaunchKernelGGL(vote_check_kernel, dim3(256), dim3(RS_NT), 0, s, g.n, g.nnz, g.row_ptr, g.col_idx, vc.changed[(it - 1) & 1],
+            hipLaunchKernelGGL(vote_check_kernel, dim3(256), dim3(RS_NT), 0, s, g.n, g.nnz, q.counts + RS_SHORT_ENTRIES, g.row_ptr, g.col_idx, vc.changed[(it - 1) & 1],
                                vc.changes[(it - 1) & 1], vc.changed[it & 1], vc.changes[it & 1], shift, vc.todo);
         if (it == 0)
-            label_round(g, Votes<true>{g.n, g.col_idx, from, g.row_ptr, to, nullptr, nullptr, 0, nullptr}, q, grid, s);
+            label_round(g, Votes<true>{g.n, g.col_idx, from, g.row_ptr, to, nullptr, nullptr, 0, g.nnz, nullptr}, q, grid, s);
         else
-            label_round(g, Votes<false>{g.n, g.col_idx, from, g.row_ptr, to, kept ? vc.changed[it & 1] : nullptr, vc.changes[it & 1], shift,
+            label_round(g, Votes<false>{g.n, g.col_idx, from, g.row_ptr, to, kept ? vc.changed[it & 1] : nullptr, vc.changes[it & 1], shift, g.nnz,
                                         check ? vc.todo : nullptr}, q, grid, s);
         int *t = from;
         from = to;
