@@ -23,6 +23,8 @@ namespace ftc {
 #if defined(__HIPCC__)
 
 constexpr int SPLIT_FROM = 4;
+// Columns of a launch: 65 535 groups of 16, the most workgroups there are in y.
+constexpr int GEMM_MOST_COLUMNS = 65535 * 16;
 
 typedef float split_f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 split_bf16x2 __attribute__((ext_vector_type(2)));

@@ -364,6 +364,13 @@ template <class T, bool TRANS, class TW = T>
 static void gemm_tile_t(int n, const void *X, int ldx, int d_in, const void *W, int w_ld, int d_out, void *Z, int ldz, int zdt, Epi epi,
                         hipStream_t s)
 {
+    if (d_out > GEMM_MOST_COLUMNS) {
+        for (int64_t c = 0; c < d_out; c += GEMM_MOST_COLUMNS)
+            gemm_tile_t<T, TRANS, TW>(n, X, ldx, d_in, static_cast<const char *>(W) + c * (TRANS ? w_ld : 1) * TW::BYTES, w_ld,
+                                      static_cast<int>(d_out - c < GEMM_MOST_COLUMNS ? d_out - c : GEMM_MOST_COLUMNS),
+                                      static_cast<char *>(Z) + c * elem_size(zdt), ldz, zdt, epi, s);
+        return;
+    }
     const int nt = d_out <= 16 ? 1 : d_out <= 32 ? 2 : d_out <= 64 || T::BYTES == 4 || n < GEMM_TILE_WIDE_ROWS ? 4 : 8;
     const int n_blocks = static_cast<int>((static_cast<int64_t>(n) + 63) / 64);
     const int groups = (d_out + nt * 16 - 1) / (nt * 16);

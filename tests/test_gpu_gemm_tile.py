@@ -275,3 +275,16 @@ def test_weight_gradients_below_the_largest_number_are_finite(dtype, n, d_in, d_
         assert dW[3, 2] == LARGE * 2.0 ** 64 and dW[3, 4] == -LARGE * 2.0 ** 64
         ref, terms = X.double().T @ G.double(), X.double().abs().T @ G.double().abs()
         assert float(((dW.double() - ref).abs() / terms.clamp(min=1e-300)).max()) <= 1e-5
+
+
+@pytest.mark.parametrize("dtype,k", [(F32, 3), (F32, 9), (BF16, 70), (F16, 2)])
+def test_more_columns_than_a_launch_takes(dtype, k):
+    """65 535 groups of 64 columns and more, forward and in the input gradient."""
+    gen = torch.Generator(device="cuda").manual_seed(k)
+    n, d = 3, 65_535 * 64 + 1000
+    X, W = torch.randn((n, k), generator=gen, device="cuda").to(dtype), torch.randn((k, d), generator=gen, device="cuda").to(dtype)
+    assert rel(B.ftc_update_gemm(X, W), X, W) <= bound(k)
+    dX = torch.empty((n, d), device="cuda")
+    G = X.float()
+    B.ftc_update_gemm_backward(torch.zeros((n, d), device="cuda", dtype=dtype), W.T.contiguous(), G, dX=dX)
+    assert rel(dX, G, W) <= bound(k)
