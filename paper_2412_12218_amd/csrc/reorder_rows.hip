@@ -616,6 +616,8 @@ __global__ __launch_bounds__(256, 6) void row_sort_kernel(Use u, RowQueues q, in
     }
     const int64_t r0 = (static_cast<int64_t>(blockIdx.x - queue_blocks) * 4 + wave) * RS_ROWS;
     if (r0 >= u.n) return;
+    bool kept = false;  // votes: the rows whose label is another than before are
+    if constexpr (Use::VOTES) kept = u.changed && short_rows_count(q.counts[RS_SHORT_ENTRIES], u.nnz);
     int start_l = 0, len_l = 0, dst_l = 0, old_l = 0;
     bool short_row = false;  // votes: this lane's row is decided here
     const int r_l = static_cast<int>(r0) + lane;
@@ -638,7 +640,7 @@ __global__ __launch_bounds__(256, 6) void row_sort_kernel(Use u, RowQueues q, in
         // a row that has no entries, or none that changed, keeps its label
         const int w = len_l > 0 ? win[wave][lane & (RS_ROWS - 1)] : old_l;
         if (short_row) u.out[r_l] = w;
-        if (!u.changed || !short_rows_count(q.counts[RS_SHORT_ENTRIES], u.nnz)) return;
+        if (!kept) return;
         const uint32_t m = static_cast<uint32_t>(__builtin_amdgcn_ballot_w64(short_row && w != old_l));
         const int first = static_cast<int>(r0) >> u.shift;  // the 32 >> shift bits of these rows lie in one word
         uint32_t bits = 0u;
@@ -761,7 +763,8 @@ __global__ __launch_bounds__(RS_NT) void row_sort_big_kernel(Use u, RowQueues q)
     __shared__ unsigned long long tmp64[RS_NT / 64];
     __shared__ int tmp[RS_NT / 64];
     __shared__ int dup;
-    const int n4 = q.counts[4], n3 = q.counts[3];
+    const int n4 = q.counts[4], n3 = q.counts[3], n2 = q.counts[2], n32 = n3 + (n2 <= RS_GROUP_FEW ? n2 : 0);
+    if (n4 + n32 == 0) return;  // uniform over the grid
     if constexpr (Use::VOTES) {
         const int ranges = value_ranges(u.n);
         const int64_t tasks = static_cast<int64_t>(n4) * ranges;
@@ -793,19 +796,16 @@ __global__ __launch_bounds__(RS_NT) void row_sort_big_kernel(Use u, RowQueues q)
             else if (threadIdx.x == 0) q.dup_rows[atomicAdd(&q.counts[RS_QUEUES], 1)] = r;
         }
     }
-    // every class begins with the workgroup after the last one of the class before: a row a workgroup where there are few (2^17 nodes, 2.6 M
-    // entries, one row counted in four parts, 17 of up to 8192 entries: 38 / 26 us a round)
-    const int grid = gridDim.x, at = static_cast<int>(blockIdx.x) + grid;
+    // the classes begin with the workgroup after the last one above: a row a workgroup where there are few (2^17 nodes, 2.6 M entries, one row
+    // counted in four parts, 17 of up to 8192 entries: 38 / 26 us a round)
+    const int grid = gridDim.x;
     const int end4 = static_cast<int>((Use::VOTES ? static_cast<int64_t>(n4) * value_ranges(u.n) : n4) % grid);
-    for (int i = (at - end4) % grid; i < n3; i += grid) lds_row(u, q.rows[3][i], s, tmp64);
-    const int n2 = q.counts[2];
-    if (n2 <= RS_GROUP_FEW)
-        for (int i = (at - (end4 + n3) % grid) % grid; i < n2; i += grid) {
-            const int r = q.rows[2][i];
-            int start, len;
-            u.row(r, start, len);
-            if (len > RS_GROUP / 2) lds_row(u, r, s, tmp64);
-        }
+    for (int i = (static_cast<int>(blockIdx.x) + grid - end4) % grid; i < n32; i += grid) {
+        const int r = i < n3 ? q.rows[3][i] : q.rows[2][i - n3];
+        int start, len;
+        u.row(r, start, len);
+        if (len > RS_GROUP / 2) lds_row(u, r, s, tmp64);
+    }
 }
 
 // long rows in which a column occurs more than once: counters instead of bits, one workgroup per row and range
@@ -853,15 +853,12 @@ __global__ __launch_bounds__(RS_NT) void vote_check_kernel(int n, int nnz, const
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int words = (((n - 1) >> shift) >> 5) + 1, todo_words = (n + 31) / 32;
     const int thread = blockIdx.x * RS_NT + threadIdx.x, threads = gridDim.x * RS_NT;
-    if (!short_rows_count(*in_short, nnz)) {  // uniform over the grid
-        for (int i = thread; i < todo_words; i += threads) todo[i] = ~0u;
-        return;
-    }
+    const bool worth = short_rows_count(*in_short, nnz);  // this and the next are uniform over the grid
     for (int i = thread; i < words; i += threads) next_changed[i] = 0u;
     if (thread < VT_COUNTERS) next_changes[thread] = 0;
     int total;
     group_exclusive_scan(threadIdx.x < VT_COUNTERS ? changes[threadIdx.x] : 0, &total, tmp);
-    if (static_cast<float>(total) * static_cast<float>(nnz) > VT_MOST * static_cast<float>(n) * static_cast<float>(n)) {  // uniform over the grid
+    if (!worth || static_cast<float>(total) * static_cast<float>(nnz) > VT_MOST * static_cast<float>(n) * static_cast<float>(n)) {
         for (int i = thread; i < todo_words; i += threads) todo[i] = ~0u;
         return;
     }
