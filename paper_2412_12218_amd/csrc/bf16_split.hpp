@@ -1,19 +1,19 @@
 // fp32 products on the bf16 matrix cores.  A float has 24 significant bits, a bf16 eight, so a = a1 + a2 + a3 with three
 // bf16 numbers, exactly: a1 = a rounded, a2 = (a - a1) rounded, a3 = the rest.  Of the nine products of two such sums the
 // three smallest (a2 b3, a3 b2, a3 b3: together below 2^-24 of a b, an fp32 rounding) are left out; the other six are exact in fp32
-// and take six instructions at sixteen times the rate of v_mfma_f32_16x16x4_f32.
+// and take six instructions at sixteen times the rate of v_mfma_f32_16x16x4_f32 (Henry, Tang, Heinecke: Leveraging the bfloat16 Artificial
+// Intelligence Datatype For Higher-Precision Computations, ARITH 2019).
 // A sum of one or two products would be further off like this than in fp32, where a product is rounded once and exact before (one: at
 // most 0.91e-7 for 0.60e-7 of itself; two: 1.23e-7 for 1.14e-7 of their absolute sum), so up to SPLIT_FROM products, which are one
 // v_mfma_f32_16x16x4_f32, are summed in fp32.
 // Not so: infinities and NaN (inf - inf in the second piece), numbers that round to an infinite a1, and rests below the
 // smallest normal number.  All of these show in the last piece (NaN, or subnormal), so that is what is looked at.  And a1 b1 can be
 // infinite where a b is not: a1 is up to 2^-8 of a larger than it, so this takes results within a hundredth of the largest number; it
-// shows in the sum, which then is not finite whatever follows.  What these
-// are part of takes the fp32 instruction instead: the step of the contraction in weight_grad_tile.hip (an infinite sum: a
-// wave's rows), a wave's share of it in gemm_slice.hip,
-// a wave's tile in gemm_tile.hip, the latter two computed again from memory.  The time of a product depends on its numbers that far (us,
+// shows in the sum, which then is not finite whatever follows.  What these are part of takes the fp32 instruction instead, from memory: the
+// step of the contraction in weight_grad_tile.hip (a sum that is not finite: all steps of the wave), a wave's share of it in
+// gemm_slice.hip, a wave's tile in gemm_tile.hip, the latter two computed again.  The time of a product depends on its numbers that far (us,
 // none / one in W / one in every 16 rows, dW 32): update 100 000 x 300 -> 128 74 / 148 / 212, 100 000 x 1433 -> 16 138 / 305 / 308, 1 000 000 x 33 -> 2
-// 28 / 67 / 68, 2708 x 1433 -> 64 13 / 15 / 15; dX of 100 000 x 300 from 128 77 / 118 / 200; dW 100 000 x 300, 128 79 / - / 250 (weight_grad_kernel 118).
+// 28 / 67 / 68, 2708 x 1433 -> 64 13 / 15 / 15; dX of 100 000 x 300 from 128 77 / 118 / 200; dW 100 000 x 300, 128 79 / - / 267 (weight_grad_kernel 118).
 // Tried: a flag and a branch for every step or chunk of gemm_tile.hip (86 and 96 for the 148 and 212 us, but 2 to 7 % more without any such
 // number: registers, and no splitting of one step during the products of the one before).
 #pragma once

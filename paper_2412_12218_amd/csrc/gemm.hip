@@ -6,7 +6,7 @@
 
 namespace ftc {
 
-// fp32 of at most 16 columns, of more rows than gemm_slice.hip takes: any width, rows at any alignment of their elements.  Contraction in fp32
+// fp32 of at most 16 columns, of more rows than gemm_slice.hip takes and fewer than gemm_tile.hip: any width, rows at any alignment of their elements.  Contraction in fp32
 // on the matrix cores (v_mfma_f32_16x16x4_f32).  A wave owns a tile of 16 rows of X:
 //   A operand  lane l holds X[row0 + l%16][k0 + (l/16) 4 .. + 3], one 16-byte load (64 contiguous bytes per row and step); the
 //              j-th product takes element j of every lane, so the contraction
@@ -15,7 +15,7 @@ namespace ftc {
 //              reads W[k .. k + 3][l%16] as one 16-byte word.
 // Bound by the chain of chunks or by reading X.
 // One tile per wave, 32 KB of W: two tiles per wave were 10 % slower, 64 KB up to 20 %, 16 KB 5 %.
-// 65 000 x 65 -> 7: 6.4 us here, 7.2 in gemm_tile.hip.
+// 45 000 x 65 -> 7: 0.93 of the time in gemm_tile.hip; up to 65 535 rows (launch_gemm()).
 typedef float float4v __attribute__((ext_vector_type(4)));
 
 __global__ __launch_bounds__(256) void gemm_any_kernel(int n, const float *__restrict__ X, int ldx, int d_in,

@@ -223,21 +223,23 @@ static void gemm_slice_t(int n, const void *X, int ldx, int d_in, const void *W,
         return;
     }
     const int64_t tiles = (static_cast<int64_t>(n) + 15) / 16;
-    const bool wide = d_in >= 512;  // sixteen waves
+    const bool wide = !TRANS && d_in >= 512;  // sixteen waves (the contraction of dX is at most 504 long)
     int nt = d_out <= 16 ? 1 : d_out <= 32 ? 2 : 4;
     while (nt > 1 && tiles * ((d_out + nt * 8 - 1) / (nt * 8)) <= (wide ? 256 : 1024)) nt /= 2;
     const dim3 grid(static_cast<unsigned>(tiles), static_cast<unsigned>((d_out + nt * 16 - 1) / (nt * 16)));
 #define FTC_GS(N, SW)                                                                                                                    \
     hipLaunchKernelGGL((gemm_slice_kernel<T, N, SW, TRANS, TW>), grid, dim3(64 * SW), 0, s, n, X, ldx, d_in, W, w_ld, d_out, Z, ldz, zdt, epi)
-    if (wide) {
-        if (nt == 1) FTC_GS(1, 16);
-        else if (nt == 2) FTC_GS(2, 16);
-        else FTC_GS(4, 16);
-    } else {
-        if (nt == 1) FTC_GS(1, 4);
-        else if (nt == 2) FTC_GS(2, 4);
-        else FTC_GS(4, 4);
+    if constexpr (!TRANS) {
+        if (wide) {
+            if (nt == 1) FTC_GS(1, 16);
+            else if (nt == 2) FTC_GS(2, 16);
+            else FTC_GS(4, 16);
+            return;
+        }
     }
+    if (nt == 1) FTC_GS(1, 4);
+    else if (nt == 2) FTC_GS(2, 4);
+    else FTC_GS(4, 4);
 #undef FTC_GS
 }
 

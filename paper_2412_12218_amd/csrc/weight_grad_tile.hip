@@ -11,9 +11,10 @@
 // is zero would be NaN) goes through v_mfma_f32_16x16x4_f32 from X and G as they are, and so do all steps of a wave whose sums are not finite.
 //
 // Bound by the work of taking apart (8 instructions a number, 30 us for 100 000 x 300, 128) next to the products (25 us), two or three
-// workgroups a CU; weight_grad_kernel by reading X and G five and two times.  us, there / here, with the sums over the shares, and
-// error against 64 bits: fp32 100 000 x 300, 128 118 / 78 (2.2e-7 / 1.8e-7), 400 000 x 128, 128 218 / 114, 100 000 x 300, 64 75 / 54, 200 000 x
-// 500, 64 199 / 149; fp16 100 000 x 300, 128 115 / 72, 400 000 x 128, 128 197 / 97.
+// workgroups a CU; weight_grad_kernel by reading X and G five and two times.  us, there / here, of calls repeated on the same
+// inputs, with the sums over the shares (in a training pass, where they are no longer in a cache, 84 and 7 for 78), and error against 64 bits: fp32 100 000 x 300, 128 118 / 78 (2.2e-7 / 1.8e-7), 400 000 x 128, 128 218 / 114, 100 000 x 300, 64 75 / 54, 200 000 x
+// 500, 64 199 / 149; fp16 100 000 x 300, 128 115 / 72, 400 000 x 128, 128 197 / 97.  With the mask: fp32 100 000 x 300, 128
+// 90, 400 000 x 128, 128 133 (103 and 163 with 12 registers spilled, before the fp32 step was a function of its own).
 // Tried: eight waves with a unit each (8 x 8 tiles: 107 us for 78, registers; 1 000 000 x 128, 32 194 for 131).
 #include "bf16_split.hpp"
 

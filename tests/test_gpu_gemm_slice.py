@@ -38,7 +38,8 @@ def test_rows_at_the_alignment_of_an_element(dtype, n, d_in, d_out):
 
 @pytest.mark.parametrize("dtype", [F32, F16, BF16])
 @pytest.mark.parametrize("n,d_in,d_out", [(4096, 16, 16), (4097, 16, 16), (8192, 32, 7), (8193, 32, 7), (16384, 64, 64), (16385, 64, 64),
-                                          (500, 256, 64), (500, 264, 64), (777, 12, 8), (777, 16, 8), (777, 16, 12), (16385, 32, 8)])
+                                          (500, 256, 64), (500, 264, 64), (777, 12, 8), (777, 16, 8), (777, 16, 12), (16385, 32, 8),
+                                          (777, 3, 40), (16385, 4, 130), (100_001, 2, 16)])
 def test_aligned_rows_with_the_epilogue(dtype, n, d_in, d_out):
     gen = torch.Generator(device="cuda").manual_seed(n + d_in + d_out)
     X = torch.randn((n, d_in), generator=gen, device="cuda").to(dtype)

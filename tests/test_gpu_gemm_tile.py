@@ -288,3 +288,19 @@ def test_more_columns_than_a_launch_takes(dtype, k):
     G = X.float()
     B.ftc_update_gemm_backward(torch.zeros((n, d), device="cuda", dtype=dtype), W.T.contiguous(), G, dX=dX)
     assert rel(dX, G, W) <= bound(k)
+
+
+@pytest.mark.parametrize("dtype", [F16, BF16])
+@pytest.mark.parametrize("n,d_in,d_out", [(20_000, 70, 3), (5000, 200, 8), (700_001, 200, 7), (700_001, 201, 12), (20_000, 70, 40)])
+def test_input_gradient_in_16_bits(dtype, n, d_in, d_out):
+    """The same as in 32 bits, rounded once; a contraction of few indices, whole rows above 250 MB, tiles."""
+    gen = torch.Generator(device="cuda").manual_seed(n + d_in)
+    X, W = torch.zeros((n, d_in), device="cuda", dtype=dtype), torch.randn((d_in, d_out), generator=gen, device="cuda").to(dtype)
+    G = torch.randn((n, d_out), generator=gen, device="cuda")
+    dX = torch.full((n, d_in + 3), 7.0, device="cuda", dtype=dtype)
+    B.ftc_update_gemm_backward(X, W, G, dX=dX[:, :d_in])
+    ref = G.double() @ W.double().T.contiguous()
+    eps = 2.0 ** (-11 if dtype == F16 else -8)
+    terms = G.double().abs() @ W.double().abs().T.contiguous()
+    assert bool(((dX[:, :d_in].double() - ref).abs() <= eps * ref.abs() + bound(d_out) * terms * 1.01 + 2.0 ** -25).all())
+    assert torch.all(dX[:, d_in:] == 7.0)
