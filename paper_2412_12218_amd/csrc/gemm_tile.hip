@@ -379,9 +379,12 @@ static void gemm_tile_t(int n, const void *X, int ldx, int d_in, const void *W, 
     // column 19.8 / 14.4; 17.1, from 10 23.4 / 16.5; 21.9, 200 000 x 128 from 7 30.6 / 23.3; 27.2, 100 000 x 301 from 7 42.6 / 35.6; 36.0, 40 000 x
     // 1433 from 7 122.8 / 83.1; 101.2; 262 144 x 128 from 7 40.9 / 36.3; 37.4; but 400 000 x 128
     // from 64 75.8 / 86.5, from 40 71.3 / 79.9).
-    // Products of few indices always do (us, apart / together: 602 932 x 120 from 8 193 / 182, 1 000 000 x 128 from 3 301 / 289, 400 000 x 70 from 5 71.5 / 67.6).
+    // Products of few indices always do (us, apart / together: 602 932 x 120 from 8 193 / 182, 1 000 000 x 128 from 3 301 / 289, 400 000 x 70 from 5 71.5 / 67.6), and
+    // rows that are no whole lines of memory, whose lines two groups share (549 450 x 91 from 10 98 / 82, from 64 142 / 119, 1 153 846 x 91 from 25 293 / 207, 966 183 x
+    // 207 from 25 539 / 352, from 100 856 / 669, 454 545 x 330 from 64 383 / 344).
     constexpr int FEW = TRANS ? FEW_BACK : SPLIT_FROM;
-    const bool neighbours = TRANS && groups > 1 && (n < 327680 || d_in <= FEW);
+    const bool lines = (reinterpret_cast<uintptr_t>(Z) | static_cast<uintptr_t>(ldz) * elem_size(zdt)) % 128 == 0;
+    const bool neighbours = TRANS && groups > 1 && (n < 327680 || d_in <= FEW || !lines);
     const int most = !neighbours ? 2048 : groups <= 25 ? 1024 / groups : 40;
     int grid = d_in <= GemmChunk<T>::KC && n_blocks > most ? most : n_blocks;
     if (neighbours) grid = (grid + 7) / 8 * 8;
@@ -438,15 +441,14 @@ int32_t launch_gemm_tile(int n, const void *X, int ldx, int dt, int d_in, const 
 // 504 23.2 / 16.5, 6000 x 33 from 300 14.5 / 8.5, 16 000 x 16 from 300 10.5 / 7.7; but 2708 x 301 from 128 8.2 / 11.6, 16 000 x 33 from 300
 // 16.4 / 17.8; W transposed into a buffer and gemm_any_kernel: 12.9, 18.3, 16.3, 11.2, 15.4, 23.1).
 //
-// Large dX from few columns, by input_grad_kernel (backward.hip), which has whole rows of 256 columns in flight (us, that / here: 260 MB, rows of 91
-// columns from 8 104 / 117, from 16 124 / 152, of 128 from 8 98 / 103, from 16 112 / 93; 420 MB 91 from 1 147 / 167, from 10 180 / 266, 128 from 4 140 / 154, from 16
-// 174 / 178, 256 from 16 169 / 150, 506 from 1 164 / 174, from 16 195 / 168; 600 MB 207 from 10 216 / 319; but 200 MB 91 from 4 81 / 80, 420 MB 48 from 4 170 / 158).
-static bool whole_rows_better(int n, int d_out, int d_in, const void *dX, int lddx, int dx_dt)
+// Large dX from up to 16 columns, by input_grad_kernel (backward.hip), which has whole rows of 256 columns in flight.  us, that / here, by columns of dX, from 1, 8, 12
+// columns: 220 MB 91 88 / 91, 93 / 99, 94 / 87; 260 MB 70 103 / 95, 108 / 116, 121 / 116, 91 102 / 111, 104 / 118, 114 / 116, 128 92 / 92, 98 / 103, 101 / 92, 207 82 / 91, 88 / 97, 90 / 90;
+// 420 MB 91 147 / 167, 165 / 199, 184 / 196, 128 135 / 146, 149 / 165, 164 / 176, 256 125 / 143, 142 / 162, 155 / 150, 366 MB 157 from 16 251 / 276 with dW; 420 MB 506 160 / 170, 170 / 170, 181 / 166; 600 MB 91 205 / 240, 233 / 289,
+// 259 / 285, 207 189 / 227, 213 / 249, 221 / 245, 506 214 / 225, 227 / 239, 241 / 239; 420 MB 48 from 4 170 / 158; from 20 600 MB 91 400 / 293, 207 313 / 263.
+static bool whole_rows_better(int n, int d_out, int d_in, int dx_dt)
 {
-    const int64_t row = static_cast<int64_t>(d_in) * elem_size(dx_dt), all = n * row;
-    if (all < 250000000 || d_in <= 64 || d_out > 16) return false;
-    const bool lines = (reinterpret_cast<uintptr_t>(dX) | static_cast<uintptr_t>(lddx) * elem_size(dx_dt)) % 128 == 0;
-    return d_out <= 8 || (d_in <= 256 && (!lines || all >= 400000000));
+    const int64_t all = static_cast<int64_t>(n) * d_in * elem_size(dx_dt);
+    return d_in > 64 && (d_out <= 8 ? all >= 250000000 : d_out <= 16 && d_in <= 256 && all >= 350000000);
 }
 
 int32_t launch_input_grad(int n, const float *G, int ldg, int d_out, const void *W, int wdt, int d_in, void *dX, int lddx, int dx_dt,
@@ -455,7 +457,7 @@ int32_t launch_input_grad(int n, const float *G, int ldg, int d_out, const void 
     if (n == 0) return FTC_OK;
     if (d_out > GemmChunk<F32>::KC && static_cast<int64_t>(n) * d_in <= 1 << 18)
         return launch_input_grad_slice(n, G, ldg, d_out, W, wdt, d_in, dX, lddx, dx_dt, s);
-    if (whole_rows_better(n, d_out, d_in, dX, lddx, dx_dt)) return launch_input_grad_rows(n, G, ldg, d_out, W, wdt, d_in, dX, lddx, dx_dt, s);
+    if (whole_rows_better(n, d_out, d_in, dx_dt)) return launch_input_grad_rows(n, G, ldg, d_out, W, wdt, d_in, dX, lddx, dx_dt, s);
     const Epi none{0, nullptr};
     if (wdt == FTC_F32) gemm_tile_t<F32, true, F32>(n, G, ldg, d_out, W, d_out, d_in, dX, lddx, dx_dt, none, s);
     else if (wdt == FTC_F16) gemm_tile_t<F32, true, F16>(n, G, ldg, d_out, W, d_out, d_in, dX, lddx, dx_dt, none, s);

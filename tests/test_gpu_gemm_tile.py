@@ -75,11 +75,11 @@ def test_input_gradient_at_edges_of_tiles_and_chunks(dtype, n, d_in, d_out):
 @pytest.mark.parametrize("dtype", [F32, F16, BF16])
 @pytest.mark.parametrize("n,d_in,d_out", [(4097, 65, 32), (9000, 66, 64), (4100, 64, 96), (10_001, 40, 131), (20_000, 130, 300), (70_001, 129, 1), (65, 1433, 40),
                                           (3000, 1700, 7), (327_679, 65, 3), (327_680, 65, 3), (327_680, 65, 9), (70_001, 130, 5), (4097, 17, 8), (1000, 65, 9),
-                                          (700_001, 91, 8), (700_001, 91, 13), (700_001, 91, 17), (500_009, 128, 3)])
+                                          (700_001, 91, 8), (700_001, 91, 13), (700_001, 91, 17), (1_200_001, 91, 16), (1_200_001, 91, 17), (400_001, 330, 9), (500_009, 128, 3)])
 def test_input_gradient_of_whole_and_cut_chunks_of_w(dtype, n, d_in, d_out):
     """Rows of W are read eight elements at a time where the chunk is whole, else one by one; X and W of each type.  Several groups of
     64 columns of dX: a workgroup each on neighbouring places up to 327 679 rows, in walks of 1024 / groups or 40 workgroups a group.  Above 250 MB
-    from up to 16 columns: whole rows."""
+    from up to 8 columns, 350 MB from up to 16: whole rows."""
     test_input_gradient_at_edges_of_tiles_and_chunks(dtype, n, d_in, d_out)
 
 
