@@ -20,7 +20,8 @@
 //   fp16  100 000 x 300 -> 128 110 / 45 (2.1e-7 / 0.8e-7), 400 000 x 301 -> 128 440 / 180, 179 245 x 18 -> 64 27 / 15, 16 000 x 1433 -> 32 47 / 28
 //   bf16  100 000 x 500 -> 40 91 / 35 (1.0e-7 / 0.6e-7), 5000 x 3001 -> 128 176 / 85 (1.3e-7 / 1.1e-7)
 // and against 16-bit rows staged in chunks of 256 for 256 rows at a time (aligned rows): fp16 20 000 x 304 -> 64 46 / 11, 100 000 x 1432 -> 16
-// 92 / 65, 400 000 x 128 -> 128 189 / 108.
+// 92 / 65, 400 000 x 128 -> 128 189 / 108.  Many 16-bit rows of 256 (192) elements and more into more than 32 columns
+// have a kernel of their own since (gemm_rows_kernel).
 // Tried: eight waves instead of four (W staged half as often: 300 -> 128 level, 1433 -> 16 12 % slower), the next chunk of X in registers
 // (5 to 15 % slower), 128 columns of fp32 (107 us for 78: registers).
 #include "bf16_split.hpp"
@@ -356,9 +357,129 @@ __global__ __launch_bounds__(256) void gemm_few_kernel(int n, const float *__res
     }
 }
 
+// 16-bit products of long rows, RT tiles of 16 rows a wave: an operand of W that comes from LDS is used RT times and a chunk of W staged for
+// 64 RT rows, where one tile a wave (above) waits for both.  A workgroup has 64 RT rows and up to 64 columns, W in chunks of 256 indices (34 KB);
+// the groups of 64 columns of the same rows follow one another on one of the eight dies.  Sums of 128 indices
+// (SETS = 2: of 64, in pairs) are added up apart, as in the kernel above with 128 (up to 64) columns: the same results.  Registers set the
+// workgroups on a compute unit, two (RT = 2: three, 12 registers spilled: 400 000 x 400 -> 33 121 us, 141 with two).  us, by
+// gemm_tile_kernel / here (before both, with four tiles a wave too, a launch per 64 columns, other instructions for odd rows): fp16 400 000 x 512 -> 129 718 / 257 (470), -> 65 360 / 192 (292), -> 128 370 / 199 (331), 200 000 x 512 -> 160 353 / 125 (253),
+// 1433 -> 128 100 000 rows 311 / 245 (498), 400 000 x 512 -> 40 169 / 133 (149), odd rows 244 / 199 (354).
+template <class T, int RT, int SETS>
+__global__ __launch_bounds__(256, RT == 4 ? 2 : 3) void gemm_rows_kernel(int n, const void *__restrict__ X, int ldx, int d_in, const uint16_t *__restrict__ W,
+                                                           int d_out, void *__restrict__ Z, int ldz, int zdt, Epi epi, int n_batches, int groups)
+{
+    constexpr int NT = 4, KC = 256, KP = KC + 8, COLS = 16 * NT, SB = 2;
+    __shared__ __align__(16) uint16_t Ws[COLS * KP];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int m = lane & 15, kb = lane >> 4;
+    const unsigned slot = blockIdx.x / 8u;  // gridDim.x is a multiple of 8 groups
+    const int col0 = static_cast<int>(slot % groups) * COLS, cols = min(COLS, d_out - col0);
+    const int first = static_cast<int>(slot / groups * 8u + blockIdx.x % 8u), step = static_cast<int>(gridDim.x / groups);
+    const bool whole = d_in <= KC;
+    for (int batch = first; batch < n_batches; batch += step) {  // uniform
+        const int64_t row0 = (static_cast<int64_t>(batch) * 4 + wave) * (16 * RT);
+        int64_t at[RT];
+        split_f32x4 total[RT][NT], c[SETS][RT][NT];
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+            at[rt] = min(row0 + rt * 16 + m, static_cast<int64_t>(n) - 1) * ldx;  // clamped: stores are predicated
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) total[rt][nt] = c[0][rt][nt] = c[SETS - 1][rt][nt] = split_f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        for (int kc0 = 0; kc0 < d_in; kc0 += KC) {  // uniform
+            if (!whole || batch == first) {
+                __syncthreads();  // the previous chunk has been consumed
+                const int units = min(KC, (d_in - kc0 + 31) / 32 * 32) / 8 * COLS;
+                for (int t0 = tid; t0 < units; t0 += 256 * SB) {
+                    uint32_t h[SB][8];
+#pragma unroll
+                    for (int u = 0; u < SB; ++u) {
+                        const int t = t0 + u * 256;
+                        const int o = t % COLS, k = t / COLS * 8;
+                        const int left = o < cols && t < units ? d_in - kc0 - k : 0;
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) {
+                            const uint32_t v = W[j < left ? static_cast<int64_t>(kc0 + k + j) * d_out + col0 + o : 0];
+                            h[u][j] = j < left ? v : 0u;
+                        }
+                    }
+#pragma unroll
+                    for (int u = 0; u < SB; ++u) {
+                        const int t = t0 + u * 256;
+                        if (t < units)
+                            *reinterpret_cast<uint4 *>(&Ws[t % COLS * KP + t / COLS * 8]) =
+                                make_uint4(h[u][0] | (h[u][1] << 16), h[u][2] | (h[u][3] << 16), h[u][4] | (h[u][5] << 16), h[u][6] | (h[u][7] << 16));
+                    }
+                }
+                __syncthreads();
+            }
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                if (half > 0 && kc0 + 128 >= d_in) break;  // uniform
+#pragma unroll
+                for (int s = half * 4; s < half * 4 + 4; ++s) {
+                    if (kc0 + s * 32 >= d_in) break;  // uniform
+                    const int k = kc0 + s * 32 + kb * 8;
+                    Eight<T> a[RT];
+#pragma unroll
+                    for (int rt = 0; rt < RT; ++rt) load_eight<T>(X, at[rt] + k, d_in - k, a[rt]);
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) {
+                        if (nt * 16 >= cols) break;  // uniform
+                        const uint4 b = *reinterpret_cast<const uint4 *>(&Ws[(nt * 16 + m) * KP + s * 32 + kb * 8]);
+#pragma unroll
+                        for (int rt = 0; rt < RT; ++rt) {
+                            split_f32x4 &v = c[SETS == 2 ? s >> 1 & 1 : 0][rt][nt];
+                            if constexpr (std::is_same<T, F16>::value)
+                                v = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(gt_half8, b), __builtin_bit_cast(gt_half8, a[rt].h), v, 0, 0, 0);
+                            else
+                                v = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(split_bf16x8, b), __builtin_bit_cast(split_bf16x8, a[rt].h), v, 0, 0, 0);
+                        }
+                    }
+                }
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) {
+                        total[rt][nt] += SETS == 2 ? c[0][rt][nt] + c[SETS - 1][rt][nt] : c[0][rt][nt];
+                        c[0][rt][nt] = c[SETS - 1][rt][nt] = split_f32x4{0.f, 0.f, 0.f, 0.f};
+                    }
+            }
+        }
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+            const int64_t row = row0 + rt * 16 + m;
+            if (row >= n) continue;
+            const float f = epi.factor(row);
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                const int o = nt * 16 + kb * 4;
+                float z[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) z[i] = epi.apply(f, total[rt][nt][i]);
+                if (o + 4 <= cols) {
+                    store_vec_any<4>(Z, row * ldz + col0 + o, zdt, z);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (o + i < cols) store_elem(Z, row * ldz + col0 + o + i, zdt, z[i]);
+                }
+            }
+        }
+    }
+}
+
 // 16-bit rows into more than 64 columns: from here on in groups of 128, which read X half as often (fp16 301 -> 128, groups of 64 /
 // 128: 40 000 rows 24 / 25 us, 400 000 223 / 180; 17 -> 128 40 000 rows 11 / 14).
 constexpr int GEMM_TILE_WIDE_ROWS = 65536;
+
+// Where gemm_rows_kernel is ahead: its time over that of gemm_tile_kernel, fp16, aligned rows; odd ones, 66 000 to 10^6 of them, by indices: into 65 to 256 columns 128
+// .54 to 1.55; .77 to 1.85, 192 .43 to .94; .66 to 1.14, 256 .39 to .78; .65 to 1.03, 512 .35 to .57; .60 to .94, 1433 .48 to .80; .48 to .80; into 33 to 64 from 100 000
+// rows on 192 .77 to 1.09; .81 to .97, 256 .67 to .91; .79 to .92, 768 .67 to .81; .82 to .86, of 66 000 rows 256 to 768 .76 to 1.04; .96 to 1.09.
+static bool rows_better(int n, bool aligned, int d_in, int d_out)
+{
+    return d_out > 64 ? n >= GEMM_TILE_WIDE_ROWS && d_in >= (aligned ? 192 : 256) : d_out > 32 && n >= 98304 && d_in >= 256;
+}
 
 template <class T, bool TRANS, class TW = T>
 static void gemm_tile_t(int n, const void *X, int ldx, int d_in, const void *W, int w_ld, int d_out, void *Z, int ldz, int zdt, Epi epi,
@@ -370,6 +491,19 @@ static void gemm_tile_t(int n, const void *X, int ldx, int d_in, const void *W, 
                                       static_cast<int>(d_out - c < GEMM_MOST_COLUMNS ? d_out - c : GEMM_MOST_COLUMNS),
                                       static_cast<char *>(Z) + c * elem_size(zdt), ldz, zdt, epi, s);
         return;
+    }
+    if constexpr (T::BYTES == 2 && !TRANS) {
+        if (rows_better(n, aligned16(X) && ldx % 8 == 0, d_in, d_out)) {
+            const int rt = d_out > 64 ? 4 : 2, groups = (d_out + 63) / 64;
+            const int n_batches = static_cast<int>((static_cast<int64_t>(n) + 64 * rt - 1) / (64 * rt));
+            int per = d_in <= 256 && n_batches > 1024 / groups + 32 ? 1024 / groups + 32 : n_batches;  // staged once where one chunk holds W
+            per = (per + 7) / 8 * 8;
+            const dim3 grid(static_cast<unsigned>(per) * static_cast<unsigned>(groups));
+            const uint16_t *w = static_cast<const uint16_t *>(W);
+            if (rt == 4) hipLaunchKernelGGL((gemm_rows_kernel<T, 4, 1>), grid, dim3(256), 0, s, n, X, ldx, d_in, w, d_out, Z, ldz, zdt, epi, n_batches, groups);
+            else hipLaunchKernelGGL((gemm_rows_kernel<T, 2, 2>), grid, dim3(256), 0, s, n, X, ldx, d_in, w, d_out, Z, ldz, zdt, epi, n_batches, groups);
+            return;
+        }
     }
     const int nt = d_out <= 16 ? 1 : d_out <= 32 ? 2 : d_out <= 64 || T::BYTES == 4 || n < GEMM_TILE_WIDE_ROWS ? 4 : 8;
     const int n_blocks = static_cast<int>((static_cast<int64_t>(n) + 63) / 64);

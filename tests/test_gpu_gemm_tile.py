@@ -37,6 +37,40 @@ def test_update_gemm_at_edges_of_tiles_and_chunks(dtype, n, d_in, d_out):
     assert torch.all(out[:, 0] == 7.0) and torch.all(out[:, d_out + 1] == 7.0)
 
 
+@pytest.mark.parametrize("dtype", [F16, BF16])
+@pytest.mark.parametrize("n,d_in,d_out", [(65_535, 256, 65), (65_536, 255, 65), (65_536, 256, 65), (65_537, 257, 128), (65_600, 384, 129), (70_001, 513, 200), (98_303, 300, 33),
+                                          (98_304, 256, 33), (98_305, 385, 64), (100_001, 1433, 40), (300_001, 256, 48), (300_001, 256, 500), (65_791, 700, 64 * 33)])
+def test_long_16_bit_rows_in_tiles_of_four_and_two_a_wave(dtype, n, d_in, d_out):
+    """Rows, columns and chunks that end inside a tile, a step and a half chunk; W staged once and per chunk."""
+    test_update_gemm_at_edges_of_tiles_and_chunks(dtype, n, d_in, d_out)
+
+
+@pytest.mark.parametrize("dtype", [F16, BF16])
+@pytest.mark.parametrize("n,d_in,d_out", [(65_537, 264, 130), (98_311, 520, 40), (65_536, 192, 65), (70_001, 184, 65), (70_001, 248, 129)])
+def test_long_16_bit_rows_scaled_and_clipped_in_aligned_rows(dtype, n, d_in, d_out):
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    X, W = torch.randn((n, d_in), generator=gen, device="cuda").to(dtype), torch.randn((d_in, d_out), generator=gen, device="cuda").to(dtype)
+    scale = torch.rand((n,), generator=gen, device="cuda") + 0.5
+    X[5, 7], X[n - 1, d_in - 1] = float("inf"), float("nan")
+    Z = B.ftc_update_gemm(X, W, row_scale=scale, relu=True, out=torch.empty((n, d_out), device="cuda"))
+    ref, terms = X.double() @ W.double() * scale.double()[:, None], X.double().abs() @ W.double().abs() * scale.double()[:, None]
+    ok = torch.ones(n, dtype=torch.bool, device="cuda")
+    ok[5] = ok[n - 1] = False
+    assert float(((Z.double() - ref.clamp(min=0))[ok].abs() / terms[ok]).max()) <= bound(d_in) + 2.0 ** -23
+    assert torch.equal(torch.isposinf(Z[5]), torch.isposinf(ref[5]))
+
+
+def test_a_few_columns_beyond_a_group_do_not_cost_a_group():
+    """16-bit rows of 512 elements into 129 columns next to 128: twice as long when the second group took all 128 columns' time."""
+    X = torch.randn((400_000, 512), device="cuda").to(F16)
+    times = []
+    for d in (128, 129):
+        W, out = torch.randn((512, d), device="cuda").to(F16), torch.empty((400_000, d), device="cuda", dtype=F16)
+        times.append(us(lambda: B.ftc_update_gemm(X, W, out=out)))
+    print("us", times)
+    assert times[1] <= 1.6 * times[0]
+
+
 @pytest.mark.parametrize("n,d_in,d_out", [(300, 70, 70), (20000, 33, 20)])
 def test_numbers_that_bf16_pieces_cannot_hold(n, d_in, d_out):
     """Infinities, NaN, the largest and the smallest numbers: what fp32 arithmetic makes of them."""
