@@ -303,9 +303,10 @@ static bool gemm_slice_better(int n, int dt, int d_in, int d_out, bool on_chip)
     }
     if (d_out <= 16) return n <= 16384;
     if (d_out <= 64) return n <= (d_in >= 32 ? 12288 : 8192);
-    // one step of the contraction is one wave's, the other three have nothing to do: in tiles where the workgroups don't fit the chip at once (us, split / tile:
-    // 6000 x 8 -> 500 16.0 / 7.5, 6000 x 32 -> 256 8.6 / 5.8, 4000 x 16 -> 200 7.9 / 5.5, 2000 x 8 -> 500 8.1 / 5.8; up to 2000 x 256, 4000 x 140 level)
-    if (d_in <= 32 && static_cast<int64_t>(n) * d_out > 1 << 19) return false;
+    // one step of the contraction, or two, are one or two waves', the others have nothing to do: in tiles where the workgroups don't fit the chip at once (us,
+    // split / tile: 6000 x 8 -> 500 16.0 / 7.5, 6000 x 32 -> 256 8.6 / 5.8, 4000 x 16 -> 200 7.9 / 5.5, 2000 x 8 -> 500 8.1 / 5.8, 6144 x 48 -> 256 10.3 / 6.8; up to 2000 x
+    // 256, 4000 x 130 level).  From 49 to 64 indices the tile is as far ahead, but its two steps one after the other are further from 64 bits (64: 4 %).
+    if (d_in <= 48 && static_cast<int64_t>(n) * d_out > 1 << 19) return false;
     return n <= 6144;
 }
 

@@ -60,16 +60,17 @@ def test_long_16_bit_rows_scaled_and_clipped_in_aligned_rows(dtype, n, d_in, d_o
     assert torch.equal(torch.isposinf(Z[5]), torch.isposinf(ref[5]))
 
 
-@pytest.mark.parametrize("n,d_in,d_out", [(6144, 8, 85), (6144, 8, 86), (1048, 32, 500), (1049, 32, 500), (1049, 33, 500), (6144, 5, 500), (6143, 17, 131)])
-def test_one_step_of_the_contraction_on_both_sides_of_its_line(n, d_in, d_out):
+@pytest.mark.parametrize("n,d_in,d_out", [(6144, 8, 85), (6144, 8, 86), (1048, 32, 500), (1049, 32, 500), (1049, 48, 500), (1049, 49, 500), (6144, 5, 500), (6143, 33, 131)])
+def test_one_and_two_steps_of_the_contraction_on_both_sides_of_their_line(n, d_in, d_out):
     test_update_gemm_at_edges_of_tiles_and_chunks(F32, n, d_in, d_out)
 
 
-def test_products_of_one_step_take_the_same_time_on_both_sides_of_the_line_of_few_rows():
-    """6144 and 6145 rows of 8 fp32 elements into 500 columns: twice the time where a wave of four had work."""
+@pytest.mark.parametrize("d_in", [8, 48])
+def test_products_of_one_and_two_steps_take_the_same_time_on_both_sides_of_the_line_of_few_rows(d_in):
+    """6144 and 6145 rows of 8 and 48 fp32 elements into 500 columns: twice the time where one or two waves of four had work."""
     times = []
     for n in (6144, 6145):
-        X, W, out = torch.randn((n, 8), device="cuda"), torch.randn((8, 500), device="cuda"), torch.empty((n, 500), device="cuda")
+        X, W, out = torch.randn((n, d_in), device="cuda"), torch.randn((d_in, 500), device="cuda"), torch.empty((n, 500), device="cuda")
         times.append(us(lambda: B.ftc_update_gemm(X, W, out=out)))
     print("us", times)
     assert times[0] <= 1.6 * times[1]
